@@ -90,7 +90,7 @@ _STAGE_KERNELS = {
     "gather_dot": ("k_gather_dot", "k_sm1_gather<true", "k_sm1_final"),
     "select_k": ("k_select<double", "k_select_nonneg<double", "k_select_refine"),
     "select_k_softmax": ("k_select<double",),
-    "second_layer": ("k_w2_tokens", "k_w2_reduce"),
+    "second_layer": ("k_w2_list",),
     "shard_step": ("k_ffn_shard",),
     "reduce": ("k_fast_reduce", "k_shard_reduce"),
     "select_gather": ("k_fast_gather",),

@@ -57,8 +57,8 @@ struct StepBuffers {
   int32_t* cand;     // U
   double* h;         // [B, cap_u]
   int32_t* pos;      // [B,k] positions inside U of every token's selected units
-  int32_t* sel_idx;  // [B,k] when the caller does not ask for topk_idx
-  float* partial;    // second-layer partial sums
+  uint2* list;       // [B,k] selected units as (row, coefficient), for the second layer
+  float* partial;    // second-layer partial sums (batch-1 route with several row groups)
   // filter and refine of the exact stage (batches): upper bounds of the tokens' norms, the fp32 stored values
   float* xnorm;      // [B]
   float* hf;         // [B, hf_stride]
@@ -119,12 +119,10 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   if (s.sm1_ok || s.max_ok) s.sm1_slots = c.take<char>(maxima_select_slot_bytes(B, N));
   if (ffn) {
     s.pos = c.take<int32_t>((size_t)B * k);
-    s.sel_idx = c.take<int32_t>((size_t)B * k);
-    size_t partial = (size_t)w2_groups(k, B, d) * B * d;
+    s.list = c.take<uint2>((size_t)B * k);
     const bool fast = gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
                               : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime));
-    if (fast && ffn_fast_partial_floats(d, k, 0) > partial) partial = ffn_fast_partial_floats(d, k, 0);
-    s.partial = c.take<float>(partial);
+    s.partial = c.take<float>(fast ? ffn_fast_partial_floats(d, k, 0) : 0);
   }
   s.bytes = c.off;
   return s;
@@ -543,9 +541,9 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   sp.n_dev = s.counters;
   sp.n_cap = s.cap_u;
   sp.k = k;
-  sp.idx_out = topk_idx ? topk_idx : s.sel_idx;
+  sp.idx_out = topk_idx;
   sp.val_out = topk_val;
-  sp.pos_out = s.pos;
+  sp.list_out = s.list;
   sp.nonneg = 1;  // activations after the ReLU
   sp.window_misses = s.window_misses;
   // Batches: filter and refine.  The exact stage runs on the bf16 matrix cores and stores fp32 values within a
@@ -577,8 +575,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   HIRE_STAGE(6, st);
 
   // step 5: second layer over each token's selected rows
-  HIRE_TRY(launch_w2_tokens(static_cast<const uint16_t*>(L->w2u), d, B, k, s.pos, cand, s.h, s.cap_u, s.partial, y,
-                            0, nullptr, 0, st));
+  HIRE_TRY(launch_w2_list(static_cast<const uint16_t*>(L->w2u), d, B, k, s.list, nullptr, 0, nullptr, y, st));
   HIRE_STAGE(7, st);
   return HIRE_OK;
 }
@@ -637,15 +634,13 @@ size_t hire_ffn_group_workspace_bytes(const hire_ffn_layer* L, int B, int k, int
   return carve(nullptr, L->scorer_kind, B, L->d_model, L->d_ff, L->r, k, kprime, true, gs).bytes;
 }
 
-// Dense common-path units riding along with a group-sparse step (eq. (7)).  folded is set when the step's own
-// launches have added them to y; otherwise the caller adds them with kernels of their own.
+// Dense common-path units riding along with a group-sparse step (eq. (7)): the step's own launches add them to y.
 struct DenseRefs {
   const uint16_t* w1u;
   const uint16_t* w2u;
   int m1;
-  double* h;          // [m1] workspace
-  float* fast_partial; // ffn_fast_partial_floats(d, k, m1) floats
-  bool folded;
+  double* h;           // [B, m1] workspace
+  float* fast_partial; // ffn_fast_partial_floats(d, k, m1) floats (batch 1)
 };
 
 static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, int k, int kprime, int group, float* y,
@@ -681,7 +676,6 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
     if (dense != nullptr && dense->m1 > 0) {
       a.dense_w1u = dense->w1u; a.dense_w2u = dense->w2u; a.m1 = dense->m1; a.h_dense = dense->h;
       a.partial = dense->fast_partial;
-      dense->folded = true;
     }
     a.stage_events = g_stage_events;
     a.scorer_clocks = g_scorer_clocks;
@@ -710,17 +704,38 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
   sp.n_dev = s.counters;
   sp.n_cap = s.cap_u;
   sp.k = k >> gs;
-  sp.idx_out = topk_group ? topk_group : s.sel_idx;
+  sp.idx_out = topk_group;
   sp.map = cand;
-  sp.pos_out = s.pos;
+  sp.list_out = s.list;
+  if (gs > 0) {
+    sp.pos_out = s.pos;
+    sp.gs = gs;
+    sp.unit_h = s.h;
+    sp.unit_h_stride = (long long)s.cap_u << gs;
+    sp.unit_val_out = topk_val;
+  } else {
+    sp.val_out = topk_val;
+  }
   sp.nonneg = 1;  // activations after the ReLU, or sums of their absolute values
   sp.window_misses = s.window_misses;
   HIRE_TRY(launch_select_f64(sp, B, st));
   HIRE_STAGE(6, st);
 
-  // second layer over the units of each token's groups; it also hands out their activations
-  HIRE_TRY(launch_w2_tokens(static_cast<const uint16_t*>(L->w2u), d, B, k, s.pos, cand, s.h, (long long)s.cap_u << gs,
-                            s.partial, y, gs, topk_val, 0, st));
+  // second layer over the units of each token's groups, and over the dense units
+  if (dense != nullptr) {
+    const uint16_t* xb = static_cast<const uint16_t*>(x);
+    const HistRefs none{};
+    if (B >= kMfmaMinBatch)
+      HIRE_TRY(launch_gather_dot_mfma(dense->w1u, xb, B, d, nullptr, dense->m1, nullptr, dense->m1, 1, dense->h, dense->m1,
+                                      none, nullptr, 0, st));
+    else
+      HIRE_TRY(launch_gather_dot(dense->w1u, xb, d, nullptr, dense->m1, nullptr, dense->m1, 1, dense->h, none, nullptr, 0,
+                                 st));
+    HIRE_TRY(launch_w2_list(static_cast<const uint16_t*>(L->w2u), d, B, k, s.list, dense->w2u, dense->m1, dense->h, y,
+                            st));
+  } else {
+    HIRE_TRY(launch_w2_list(static_cast<const uint16_t*>(L->w2u), d, B, k, s.list, nullptr, 0, nullptr, y, st));
+  }
   HIRE_STAGE(7, st);
   return HIRE_OK;
 }
@@ -736,7 +751,6 @@ int hire_ffn_group_step(const hire_ffn_layer* L, const void* x, int B, int k, in
 struct CommonBuffers {
   size_t sparse_bytes;
   double* h;       // [B, m1]
-  float* partial;  // [w2_groups(m1, B, d), B, d]
   float* fast_partial;  // batch 1: the four-kernel route's partial rows, sparse and dense row groups together
   size_t bytes;
 };
@@ -746,7 +760,6 @@ static CommonBuffers carve_common(void* ws, const hire_ffn_layer* L, int m1, int
   Carver cv(ws);
   cv.take<char>(c.sparse_bytes);
   c.h = cv.take<double>((size_t)B * m1 + 2);
-  c.partial = cv.take<float>((size_t)w2_groups(m1 > 0 ? m1 : 1, B, L->d_model) * B * L->d_model);
   if (B == 1) c.fast_partial = cv.take<float>(ffn_fast_partial_floats(L->d_model, k, m1));
   c.bytes = cv.off;
   return c;
@@ -768,32 +781,15 @@ int hire_ffn_commonpath_step(const hire_ffn_layer* L, const void* dense_w1u, con
   if (gs < 0) return HIRE_EINVAL;
   const size_t need = hire_ffn_commonpath_workspace_bytes(L, m1, B, k, kprime, group);
   if (need != 0 && workspace_bytes < need) return HIRE_ENOSPC;
-  // the sparse units first: it validates the shared arguments and writes y; at batch 1 with groups of eight its
-  // own launches take the dense units along
   CommonBuffers c{};
   DenseRefs dense{};
   if (need != 0 && m1 > 0) {
     c = carve_common(workspace, L, m1, B, k, kprime, gs);
     dense = DenseRefs{static_cast<const uint16_t*>(dense_w1u), static_cast<const uint16_t*>(dense_w2u), m1, c.h,
-                      c.fast_partial, false};
+                      c.fast_partial};
   }
-  int rc = ffn_group_step_impl(L, x, B, k, kprime, group, y, topk_group, topk_val, cand_group, n_cand, scorer_acc,
-                               workspace, workspace_bytes, stream, (need != 0 && m1 > 0 && B == 1) ? &dense : nullptr);
-  if (rc != HIRE_OK || m1 == 0 || dense.folded) return rc;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const int d = L->d_model;
-  const uint16_t* xb = static_cast<const uint16_t*>(x);
-  const HistRefs none{};
-  // dense units: every row's activation, then the second layer over all of them, added onto y
-  if (B >= kMfmaMinBatch)
-    HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(dense_w1u), xb, B, d, nullptr, m1, nullptr, m1, 1, c.h,
-                                    m1, none, nullptr, 0, st));
-  else
-    HIRE_TRY(launch_gather_dot(static_cast<const uint16_t*>(dense_w1u), xb, d, nullptr, m1, nullptr, m1, 1, c.h, none,
-                               nullptr, 0, st));
-  HIRE_TRY(launch_w2_tokens(static_cast<const uint16_t*>(dense_w2u), d, B, m1, nullptr, nullptr, c.h, m1, c.partial, y,
-                            0, nullptr, 1, st));
-  return HIRE_OK;
+  return ffn_group_step_impl(L, x, B, k, kprime, group, y, topk_group, topk_val, cand_group, n_cand, scorer_acc,
+                             workspace, workspace_bytes, stream, (need != 0 && m1 > 0) ? &dense : nullptr);
 }
 
 // The partial rows sit behind the places of the two route headers, so that a workspace shared with the other

@@ -1,6 +1,6 @@
 // Exact stage of HiRE (arXiv 2402.09360, Algorithm 1 line 2 and eq. (4)):
 //   gather_dot    h[b,t] = phi(<z_{U[t]}, x_b>) over the candidate rows only
-//   w2_tokens     y_b    = sum_{j in S_b} h[b,j] v_j over the selected rows only
+//   w2_list       y_b    = sum_{j in S_b} h[b,j] v_j over the selected rows only
 // Rows are unit-major, so every gathered row is one contiguous run of 2*d bytes
 // read with 16-byte loads.
 //
@@ -71,161 +71,121 @@ __global__ __launch_bounds__(256) void k_gather_dot(const uint16_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Second layer, token by token: y_b = sum_{i < k} fl32(h[b, pos[b, i]]) * W2[map[pos[b, i]], :].
-// grid = (column slices of 512, row groups, tokens).  Wave w of a block takes batches of eight of its row
-// group's entries: the eight positions, row numbers and coefficients are fetched by eight lanes and handed
-// round as wave-uniform values, so the eight row loads (16 bytes per lane, 8 columns) are in flight together
-// instead of each waiting for its own index chain.  The four waves are summed through LDS in a fixed order and
-// the block writes one partial row; k_w2_reduce then adds the groups in a fixed order.  Rows chosen by several
-// tokens are read once per token; the repeats are served by the caches.
-// gs > 0 (group-sparse FFN): pos lists k >> gs selected groups per token; entry e < k is unit e % 2^gs of group
-// e >> gs, its row map[pos] * 2^gs + l and its coefficient h[pos * 2^gs + l].  val_out (optional): the k
-// coefficients in entry order, as fp32.
-constexpr int kW2Cols = 512;
-constexpr int kW2Batch = 8;
+// Second layer, y_b = sum_e coef(b, e) * W2[row(b, e), :] over the k entries (row, coefficient) that the selection
+// left for token b, plus (CommonPath, eq. (7)) sum_r fl32(hd[b, r]) * Wd[r, :] over m1 dense rows.  One kernel, no
+// partial sums: a workgroup owns 8 LPR columns of one token and all of its rows, and writes y itself.  The entries
+// pass through LDS in chunks; LPR lanes share a row (16 bytes each), and a lane has two batches of FL rows in
+// flight, the next one requested before the current one is added up.
+//
+// Bound: the round trips list -> rows for few tokens; for many the caches (64 tokens read 215 MB of rows that are
+// 67 MB in HBM, 11 TB/s).  Narrow slices spread few tokens over the chip; wide ones read longer runs and are faster
+// once 256 workgroups exist (64 tokens: 128-byte runs 29 us, 256-byte 22, 512-byte 19.5).  The dispatcher places
+// workgroup i on die i % 8, and die x takes the column slices x, 8 + x, ..., one for all tokens before the next, so
+// that the tokens share a slice's rows in one L2 (32-column slices: the two halves of a line on one die).  Measured at d = 2048, k = 819 of 16384 units, 4 / 16 / 64 tokens:
+// 5 / 8.4 / 19.5 us, against 9.4 / 12.2 us for a kernel with partial sums and a reducing one, 23.7 us for
+// 256-column workgroups without the second batch in flight.
+constexpr int kW2Threads = 512;
+constexpr int kW2Waves = kW2Threads / kWave;
+constexpr int kW2Chunk = 1024;  // entries staged in LDS at a time
 
-__global__ __launch_bounds__(256) void k_w2_tokens(const uint16_t* __restrict__ W2, int d, int k,
-                                                   const int32_t* __restrict__ pos, const int32_t* __restrict__ map,
-                                                   const double* __restrict__ h, long long h_stride,
-                                                   float* __restrict__ partial, int gs,
-                                                   float* __restrict__ val_out) {
-  __shared__ float red[4][kW2Cols];
-  const int groups = (int)gridDim.y, g = (int)blockIdx.y, b = (int)blockIdx.z, B = (int)gridDim.z;
-  const int rpg = (k + groups - 1) / groups;
-  const int p0 = g * rpg, p1 = min(k, p0 + rpg);
-  const int lane = lane_id(), w = wave_id();
-  const int col0 = (int)blockIdx.x * kW2Cols + lane * 8;
-  const int colc = min(col0, d - 8);  // d is a multiple of 8
+template <int LPR, int FL>
+__global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __restrict__ W2, int d, int B, int k,
+                                                           const uint2* __restrict__ list,
+                                                           const uint16_t* __restrict__ Wd, int m1,
+                                                           const double* __restrict__ hd, float* __restrict__ y) {
+  constexpr int kCols = 8 * LPR;                         // columns of the workgroup
+  constexpr int kStride = kW2Waves * (kWave / LPR);      // rows of the workgroup per load instruction
+  static_assert(kW2Chunk % (kStride * FL) == 0 && kCols <= kW2Threads, "whole batches per chunk, a thread per column");
+  __shared__ uint2 entries[kW2Chunk];
+  __shared__ float red[kW2Waves][kCols];
+  const int lane = lane_id(), w = wave_id(), tid = (int)threadIdx.x;
+  constexpr int kPair = LPR < 8 ? 8 / LPR : 1;  // slices that share a 128-byte line stay on one die
+  const int seq = (int)(blockIdx.x >> 3) / B, b = (int)(blockIdx.x >> 3) % B;
+  const int slice = ((seq / kPair) * 8 + (int)(blockIdx.x & 7)) * kPair + seq % kPair;
+  if (slice * kCols >= d) return;  // uniform: the last group of slices may be partial
+  const int sub = lane % LPR, first = w * (kWave / LPR) + lane / LPR;
+  const int colc = min(slice * kCols + sub * 8, d - 8);  // d is a multiple of 8
   float acc[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  // wave w owns entries p0 + w*kW2Batch + [0, kW2Batch), then strides by four batches
-  for (int pb = p0 + w * kW2Batch; pb < p1; pb += 4 * kW2Batch) {
-    const int pe = min(pb + (lane & (kW2Batch - 1)), p1 - 1);
-    const int l = pe & ((1 << gs) - 1);
-    const int ps = pos ? pos[(size_t)b * (k >> gs) + (pe >> gs)] : pe >> gs;  // no list: all k entries in order
-    const int row = ((map ? map[ps] : ps) << gs) + l;
-    const float c = (float)h[(size_t)b * h_stride + ((size_t)ps << gs) + l];
-    if (val_out != nullptr && blockIdx.x == 0 && lane < kW2Batch && pb + lane < p1) val_out[(size_t)b * k + pe] = c;
-    uint4 wv[kW2Batch];
+  // adds up the n entries in LDS (row 0 with coefficient 0 from n to the end of its batch)
+  auto add_chunk = [&](const uint16_t* __restrict__ M, int n) {
+    const uint16_t* base = M + colc;
+    auto request = [&](int t0, uint4 (&wv)[FL], float (&cf)[FL]) {
 #pragma unroll
-    for (int u = 0; u < kW2Batch; ++u) {
-      const int ru = __builtin_amdgcn_readlane(row, u);
-      wv[u] = *reinterpret_cast<const uint4*>(W2 + (size_t)ru * d + colc);
-    }
-#pragma unroll
-    for (int u = 0; u < kW2Batch; ++u) {
-      float cu = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), u));
-      if (pb + u >= p1) cu = 0.0f;
-      const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
-                           bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] = fmaf(cu, wf[q], acc[q]);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) red[w][lane * 8 + q] = acc[q];
-  __syncthreads();
-  // 256 threads, 512 columns: two columns each, waves added in order 0..3
-  for (int c = (int)threadIdx.x; c < kW2Cols; c += 256) {
-    const int col = (int)blockIdx.x * kW2Cols + c;
-    if (col < d) partial[((size_t)g * B + b) * d + col] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
-  }
-}
-
-// The same product for plain units (no groups), one kernel: a workgroup owns 64 columns (128 bytes of every
-// selected row) of one token and all of its k rows, so it writes y itself and nothing has to be reduced across
-// workgroups.  The token's rows and coefficients go to LDS first (two dependent loads per entry, all in flight
-// together); then eight lanes share a row, a wave reads eight rows per instruction and has eight instructions in
-// flight; the lanes' sums are folded by a fixed shuffle tree, the waves' through LDS in wave order.
-constexpr int kW2dMaxK = 4096;
-
-// LPR: lanes per row (8 columns each)
-template <int LPR>
-__global__ __launch_bounds__(256) void k_w2_direct(const uint16_t* __restrict__ W2, int d, int k,
-                                                   const int32_t* __restrict__ pos, const int32_t* __restrict__ map,
-                                                   const double* __restrict__ h, long long h_stride,
-                                                   float* __restrict__ y, float* __restrict__ val_out) {
-  __shared__ int32_t rows_l[kW2dMaxK];
-  __shared__ float coef_l[kW2dMaxK];
-  constexpr int kW2dCols = 8 * LPR, RPI = kWave / LPR;  // columns of the workgroup, rows per wave and instruction
-  __shared__ float red[4][kW2dCols];
-  const int b = (int)blockIdx.y, tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
-  for (int t0 = tid; t0 < k; t0 += 4 * 256) {  // four entries per thread in flight
-    int ps[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) ps[u] = pos ? pos[(size_t)b * k + min(t0 + u * 256, k - 1)] : min(t0 + u * 256, k - 1);
-    int row[4];
-    double hv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      row[u] = map ? map[ps[u]] : ps[u];
-      hv[u] = h[(size_t)b * h_stride + ps[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int t = t0 + u * 256;
-      if (t < k) {
-        rows_l[t] = row[u];
-        coef_l[t] = (float)hv[u];
-        if (val_out != nullptr && blockIdx.x == 0) val_out[(size_t)b * k + t] = (float)hv[u];
+      for (int u = 0; u < FL; ++u) {
+        const uint2 e = entries[min(t0 + u * kStride, kW2Chunk - 1)];
+        cf[u] = __uint_as_float(e.y);
+        wv[u] = *reinterpret_cast<const uint4*>(base + (size_t)e.x * d);
       }
+    };
+    auto add = [&](const uint4 (&wv)[FL], const float (&cf)[FL]) {
+#pragma unroll
+      for (int u = 0; u < FL; ++u) {
+        const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
+                             bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf[u], wf[q], acc[q]);
+      }
+    };
+    constexpr int kBatch = kStride * FL;
+    uint4 wa[FL], wb[FL];
+    float ca[FL], cb[FL];
+    request(first, wa, ca);
+    for (int t0 = 0; t0 < n; t0 += 2 * kBatch) {  // uniform; the scheduling barriers keep the requests ahead
+      const bool more = t0 + kBatch < n;
+      if (more) request(t0 + kBatch + first, wb, cb);
+      __builtin_amdgcn_sched_barrier(0);
+      add(wa, ca);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!more) break;
+      if (t0 + 2 * kBatch < n) request(t0 + 2 * kBatch + first, wa, ca);
+      __builtin_amdgcn_sched_barrier(0);
+      add(wb, cb);
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  const uint2* mine = list + (size_t)b * k;
+  for (int e0 = 0; e0 < k; e0 += kW2Chunk) {
+    if (e0 > 0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kW2Chunk / kW2Threads; ++u) {
+      const int i = u * kW2Threads + tid;
+      const uint2 e = mine[min(e0 + i, k - 1)];
+      entries[i] = e0 + i < k ? e : make_uint2(0u, 0u);
+    }
+    __syncthreads();
+    add_chunk(W2, min(kW2Chunk, k - e0));
   }
-  __syncthreads();
-  const int sub = lane % LPR, rw = lane / LPR;
-  const int col0 = (int)blockIdx.x * kW2dCols + sub * 8;
-  const int colc = min(col0, d - 8);  // d is a multiple of 8
-  float acc[8];
+  for (int e0 = 0; e0 < m1; e0 += kW2Chunk) {
+    __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  for (int tb = w * RPI + rw; tb < k; tb += 8 * 4 * RPI) {  // lane's rows tb, tb + 4 RPI, ...: eight in flight
-    uint4 wv[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = min(tb + u * 4 * RPI, k - 1);
-      wv[u] = *reinterpret_cast<const uint4*>(W2 + (size_t)rows_l[t] * d + colc);
+    for (int u = 0; u < kW2Chunk / kW2Threads; ++u) {
+      const int i = u * kW2Threads + tid;
+      const float c = (float)hd[(size_t)b * m1 + min(e0 + i, m1 - 1)];
+      entries[i] = e0 + i < m1 ? make_uint2((uint32_t)(e0 + i), __float_as_uint(c)) : make_uint2(0u, 0u);
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = tb + u * 4 * RPI;
-      const float c = t < k ? coef_l[t] : 0.0f;
-      const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
-                           bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] = fmaf(c, wf[q], acc[q]);
-    }
+    __syncthreads();
+    add_chunk(Wd, min(kW2Chunk, m1 - e0));
   }
+  // the lanes of a wave that hold the same columns (fixed tree), then the waves in order
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {  // the row lanes of a column chunk
+  for (int q = 0; q < 8; ++q) {
 #pragma unroll
     for (int m = LPR; m < kWave; m <<= 1) acc[q] += __shfl_xor(acc[q], m);
   }
-  if (rw == 0) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) red[w][sub * 8 + q] = acc[q];
+  if (lane < LPR) {
+    float4* dst = reinterpret_cast<float4*>(&red[w][sub * 8]);
+    dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
   }
   __syncthreads();
-  if (tid < kW2dCols) {
-    const int col = (int)blockIdx.x * kW2dCols + tid;
-    if (col < d) y[(size_t)b * d + col] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
-  }
-}
-
-// accumulate: add to what y holds (the dense common path on top of the sparse part).
-__global__ __launch_bounds__(256) void k_w2_reduce(const float* __restrict__ partial, int groups, int B, int d,
-                                                   float* __restrict__ y, int accumulate) {
-  const int col = (int)(blockIdx.x * blockDim.x + threadIdx.x), b = (int)blockIdx.y;
-  if (col >= d) return;
-  float s = 0.0f;
-  for (int g0 = 0; g0 < groups; g0 += 8) {  // eight loads in flight; added in group order
-    float v[8];
+  if (tid < kCols && slice * kCols + tid < d) {
+    float s = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = partial[((size_t)min(g0 + j, groups - 1) * B + b) * d + col];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s += g0 + j < groups ? v[j] : 0.0f;
+    for (int u = 0; u < kW2Waves; ++u) s += red[u][tid];
+    y[(size_t)b * d + slice * kCols + tid] = s;
   }
-  y[(size_t)b * d + col] = accumulate ? y[(size_t)b * d + col] + s : s;
 }
 
 // ---------------------------------------------------------------------------
@@ -285,29 +245,18 @@ hipError_t launch_gather_dot(const uint16_t* W, const uint16_t* x, int d, const 
                 u, share, gs);
 }
 
-// Row groups per token: enough workgroups to fill the machine, at least a few batches of rows each.
-int w2_groups(int k, int B, int d) {
-  const int slices = (d + kW2Cols - 1) / kW2Cols;
-  int g = 1024 / (slices * B);
-  const int by_rows = (k + 4 * kW2Batch - 1) / (4 * kW2Batch);
-  if (g > by_rows) g = by_rows;
-  if (g > 64) g = 64;
-  if (g < 1) g = 1;
-  return g;
-}
-
-hipError_t launch_w2_tokens(const uint16_t* W2, int d, int B, int k, const int32_t* pos, const int32_t* map,
-                            const double* h, long long h_stride, float* partial, float* y, int gs, float* val_out,
-                            int accumulate, hipStream_t s) {
-  // many tokens, plain units: one kernel, no partial sums (256 columns per workgroup still make 8 B workgroups)
-  if (gs == 0 && !accumulate && k <= kW2dMaxK && d % 256 == 0 && B >= 32)
-    return launch(k_w2_direct<32>, dim3(d / 256, B), dim3(256), 0, s, W2, d, k, pos, map, h, h_stride, y, val_out);
-  const int groups = w2_groups(k, B, d);
-  const int slices = (d + kW2Cols - 1) / kW2Cols;
-  hipError_t e = launch(k_w2_tokens, dim3(slices, groups, B), dim3(256), 0, s, W2, d, k, pos, map, h, h_stride,
-                        partial, gs, val_out);
-  if (e != hipSuccess) return e;
-  return launch(k_w2_reduce, dim3((d + 255) / 256, B), dim3(256), 0, s, partial, groups, B, d, y, accumulate);
+hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* list, const uint16_t* Wd, int m1,
+                          const double* hd, float* y, hipStream_t s) {
+  auto go = [&](auto kernel, int cols) {
+    const int slices = (d + cols - 1) / cols, step = max(8, 512 / cols);
+    return launch(kernel, dim3((slices + step - 1) / step * step * B), dim3(kW2Threads), 0, s, W2, d, B, k,
+                  static_cast<const uint2*>(list), Wd, m1, hd, y);
+  };
+  // the widest slices that still give a workgroup to every compute unit
+  if (d / 256 * B >= 256) return go(k_w2_list<32, 4>, 256);
+  if (d / 128 * B >= 160) return go(k_w2_list<16, 4>, 128);
+  if (d / 64 * B >= 160) return go(k_w2_list<8, 8>, 64);
+  return go(k_w2_list<4, 8>, 32);
 }
 
 }  // namespace hire

@@ -114,8 +114,7 @@ struct SelectParams {
   // Filter and refine (launch_select_refine only): vals are fp32 rows written by launch_gather_dot_bf16, within
   // err_c |u| |x| of the activations; map lists the rows' units.  The kernel recomputes in fp64
   // (relu(<refine_w[map[i], :], refine_x[b, :]>)) every non-zero entry within 2 * err_c * xnorm[b] * *wnorm_max of the
-  // k-th largest stored value and selects on the result.  refine_h [B, refine_h_stride] (fp64) receives the value
-  // of every selected entry (and of others): the second layer reads its coefficients there.
+  // k-th largest stored value and selects on the result.  refine_h [B, refine_h_stride]: fp64 scratch.
   const uint16_t* refine_w;  // bf16 [rows, refine_d]
   const uint16_t* refine_x;  // bf16 [B, refine_d]
   int refine_d;
@@ -126,6 +125,16 @@ struct SelectParams {
   float err_c;
   int nonneg;               // != 0: every value is known to be >= 0 (keys and activations after a ReLU); such rows
                             // of 1025..16384 entries in index order take a leaner kernel
+  // Second layer: list_out (optional) receives for every row its k << gs selected units in ascending order, as
+  // (row of the weight matrix, fp32 value): what launch_w2_list reads.  gs = 0: the selected entries themselves
+  // (through map) with their values.  gs > 0: the entries are groups of 2^gs units; unit l of the group at position
+  // pos has the row (map[pos] << gs) + l and the value unit_h[b * unit_h_stride + (pos << gs) + l]; unit_val_out
+  // (optional, [B, k << gs]) receives the values.  gs > 0 needs pos_out.
+  uint2* list_out;
+  int gs;
+  const double* unit_h;
+  long long unit_h_stride;
+  float* unit_val_out;
   int group8;               // != 0 (rows of at most kSelectGroup8Max entries): entry i is the sum of |vals[8 i + l]|,
                             // l < 8, added in index order in the values'
                             // type (group activations of eq. (6)); stride counts values, n / n_dev / n_cap entries
@@ -242,15 +251,10 @@ hipError_t launch_group_sums_f32(const float* in, int B, long long stride_in, in
 hipError_t launch_group_sums_f64(const double* in, int B, long long stride_in, int n, const int32_t* n_dev, int n_cap,
                                  int gs, double* out, long long stride_out, hipStream_t s);
 
-// y[b,:] = sum_{i < k} fl32(h[b*h_stride + pos[b*k + i]]) * W2[map[pos[b*k + i]], :]; deterministic two-stage
-// reduction.  partial: fp32 [w2_groups(k, B, d), B, d] scratch.
-// gs > 0: pos is [B, k >> gs] groups; entry i < k is unit i % 2^gs of group i >> gs (row map[pos] * 2^gs + l,
-// coefficient h[pos * 2^gs + l]).  val_out (optional): fp32 [B, k] coefficients in entry order.
-// pos == nullptr: entries 0 .. k-1 in order for every token.  accumulate != 0: y += the sum instead of y = it.
-int w2_groups(int k, int B, int d);
-hipError_t launch_w2_tokens(const uint16_t* W2, int d, int B, int k, const int32_t* pos, const int32_t* map,
-                            const double* h, long long h_stride, float* partial, float* y, int gs, float* val_out,
-                            int accumulate, hipStream_t s);
+// y[b,:] = sum_{e < k} coef * W2[row, :] over token b's entries (row, coefficient) of list [B, k] (SelectParams::
+// list_out), plus sum_{r < m1} fl32(hd[b*m1 + r]) * Wd[r, :] (CommonPath's dense units; m1 = 0: none).  Fixed order.
+hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* list, const uint16_t* Wd, int m1,
+                          const double* hd, float* y, hipStream_t s);
 
 // ---- ffn_fast.hip ----------------------------------------------------------
 // Batch-1 FFN step in three kernels; see the file header.  All pointers device.

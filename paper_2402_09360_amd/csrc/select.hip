@@ -278,6 +278,7 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
         if (p.idx_out) p.idx_out[(size_t)b * k + out] = mi;
         if (p.pos_out) p.pos_out[(size_t)b * k + out] = i;
         if (p.val_out) p.val_out[(size_t)b * k + out] = (float)v;
+        if (p.list_out && p.gs == 0) p.list_out[(size_t)b * k + out] = make_uint2((uint32_t)mi, __float_as_uint((float)v));
       }
     }
   };
@@ -295,10 +296,40 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
   if (packed) {
     __syncthreads();
     for (int t = (int)threadIdx.x; t < k; t += kSelThreads) {
-      const int i = pk_pos[t];
-      if (p.idx_out) p.idx_out[(size_t)b * k + t] = map ? map[i] : i;
+      const int i = pk_pos[t], mi = map ? map[i] : i;
+      const float v = (float)key_value(pk_key[t]);
+      if (p.idx_out) p.idx_out[(size_t)b * k + t] = mi;
       if (p.pos_out) p.pos_out[(size_t)b * k + t] = i;
-      if (p.val_out) p.val_out[(size_t)b * k + t] = (float)key_value(pk_key[t]);
+      if (p.val_out) p.val_out[(size_t)b * k + t] = v;
+      if (p.list_out && p.gs == 0) p.list_out[(size_t)b * k + t] = make_uint2((uint32_t)mi, __float_as_uint(v));
+    }
+  }
+  if (p.list_out != nullptr && p.gs > 0) {  // the selected groups' units with their activations
+    __syncthreads();  // pos_out of this row: written by this workgroup, visible after the barrier
+    const int gmask = (1 << p.gs) - 1, ku = k << p.gs;
+    const double* uh = p.unit_h + (size_t)b * p.unit_h_stride;
+    for (int t0 = (int)threadIdx.x; t0 < ku; t0 += 4 * kSelThreads) {  // four position -> value chains in flight
+      int ps[4], row[4];
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = min(t0 + u * kSelThreads, ku - 1) >> p.gs;
+        ps[u] = packed ? pk_pos[t] : p.pos_out[(size_t)b * k + t];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int l = min(t0 + u * kSelThreads, ku - 1) & gmask;
+        row[u] = ((map ? map[ps[u]] : ps[u]) << p.gs) + l;
+        v[u] = uh[((size_t)ps[u] << p.gs) + l];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * kSelThreads;
+        if (t < ku) {
+          p.list_out[(size_t)b * ku + t] = make_uint2((uint32_t)row[u], __float_as_uint((float)v[u]));
+          if (p.unit_val_out) p.unit_val_out[(size_t)b * ku + t] = (float)v[u];
+        }
+      }
     }
   }
   if (!p.rank_order) return;
@@ -781,11 +812,9 @@ __device__ __forceinline__ Selection<K> lean_select(const KeyRegs<K, LOADS, kSel
 }
 
 // The selected entries, packed in LDS in output order, to the index / position / value outputs.
-// emit_all(fn): calls fn(position, output slot, value as float) for every selected entry.  coeff (optional):
-// coeff[position] receives the value as well (after the barrier, so nothing waits for those stores).
+// emit_all(fn): calls fn(position, output slot, value as float) for every selected entry.
 template <typename EmitAll>
-__device__ __forceinline__ void lean_outputs(const SelectParams& p, int b, int k, LeanShared& L, EmitAll&& emit_all,
-                                             double* coeff = nullptr) {
+__device__ __forceinline__ void lean_outputs(const SelectParams& p, int b, int k, LeanShared& L, EmitAll&& emit_all) {
   const int tid = (int)threadIdx.x;
   int* pk_pos = reinterpret_cast<int*>(L.win);  // k <= kWin / 2
   float* pk_val = reinterpret_cast<float*>(L.win + kWin / 2);
@@ -796,11 +825,12 @@ __device__ __forceinline__ void lean_outputs(const SelectParams& p, int b, int k
   __syncthreads();
   const int32_t* map = p.map ? p.map + (size_t)b * p.map_stride : nullptr;
   for (int t = tid; t < k; t += kSelThreads) {
-    const int i = pk_pos[t];
-    if (p.idx_out) p.idx_out[(size_t)b * k + t] = map ? map[i] : i;
+    const int i = pk_pos[t], mi = map ? map[i] : i;
+    const float v = pk_val[t];
+    if (p.idx_out) p.idx_out[(size_t)b * k + t] = mi;
     if (p.pos_out) p.pos_out[(size_t)b * k + t] = i;
-    if (p.val_out) p.val_out[(size_t)b * k + t] = pk_val[t];
-    if (coeff) coeff[i] = (double)pk_val[t];
+    if (p.val_out) p.val_out[(size_t)b * k + t] = v;
+    if (p.list_out) p.list_out[(size_t)b * k + t] = make_uint2((uint32_t)mi, __float_as_uint(v));
   }
 }
 
@@ -839,7 +869,7 @@ __device__ __forceinline__ void lean_row(const SelectParams& p, int b, const V* 
       if (lane % LPW == 0 && bits != 0u) atomicOr(&p.bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / LPW], bits);
     }
   }
-  if (p.idx_out != nullptr || p.pos_out != nullptr || p.val_out != nullptr) {
+  if (p.idx_out != nullptr || p.pos_out != nullptr || p.val_out != nullptr || p.list_out != nullptr) {
     lean_outputs(p, b, k, L, [&](auto&& put) {
       fast_emit(kr, sel, 0, k, [&](int i, int out, K bits, int, int) {
         V v;
@@ -865,8 +895,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_nonneg(SelectParams p) {
 // within hw = 2 err_c xnorm[b] *wnorm_max of the k-th, recomputes those in fp64 (every wave its own entries) into
 // refine_h and lists them (value, position) in LDS.  What lies above the band is larger than the true k-th
 // activation, what lies below is smaller, so with A entries above the band the k - A largest listed ones
-// complete the selection.  refine_h finally receives the value (as rounded to fp32, which is what the second
-// layer uses) of every selected entry: the second layer reads its coefficients there.  If the list does not settle it (band reaching the zeros, more
+// complete the selection.  If the list does not settle it (band reaching the zeros, more
 // entries than the list holds, counts that do not fit), the row's remaining stored values are written to
 // refine_h as well and the row is selected again there in fp64, as launch_select_f64 would.
 
@@ -1017,7 +1046,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_refine(SelectParams p) {
   if (k >= n) {  // uniform: every entry of the row is selected, nothing was refined
     lean_outputs(p, b, k, L, [&](auto&& put) {
       fast_emit(kr, sel0, 0, k, [&](int i, int out, K key, int, int) { put(i, out, __uint_as_float(key)); });
-    }, h);
+    });
     HIRE_TS(TB + 7);
     return;
   }
@@ -1067,7 +1096,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_refine(SelectParams p) {
                                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             put(i, out, (float)v);
           });
-    }, h);
+    });
     HIRE_TS(TB + 7);
     return;
   }
@@ -1275,7 +1304,7 @@ hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s) {
 template <typename V>
 static bool select_is_lean(const SelectParams& p) {
   const int cap = p.n_dev ? p.n_cap : p.n;
-  return p.nonneg && !p.rank_order && !p.group8 && !p.relu && cap > kSelThreads && cap <= kCachedMax &&
+  return p.nonneg && !p.rank_order && !p.group8 && p.gs == 0 && !p.relu && cap > kSelThreads && cap <= kCachedMax &&
          p.k <= kWin / 2 && reinterpret_cast<uintptr_t>(p.vals) % 16 == 0 && (p.stride * (long long)sizeof(V)) % 16 == 0;
 }
 bool select_refine_supported(const SelectParams& p) {

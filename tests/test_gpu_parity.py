@@ -166,6 +166,19 @@ def ffn_1b(hire, oracle):
     return L, layer, scorer
 
 
+@pytest.mark.parametrize("d,N,B,k,kp", [
+    (2080, 1500, 33, 1100, 1300),   # 256-column slices, the last one partial; two chunks of entries, the second short
+    (1056, 1030, 40, 64, 300),      # 128-column slices
+    (800, 1600, 13, 1024, 1200),    # 64-column slices, one whole chunk
+    (96, 1100, 2, 1025, 1100),      # 32-column slices, more slots than slices
+])
+def test_second_layer_slices(hire, oracle, d, N, B, k, kp):
+    log(f"second layer d={d} N={N} B={B} k={k}")
+    L = I.ffn_layer(90 + B, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    T.check_ffn(layer, scorer, L, I.tokens(91 + B, B, d), k, kp)
+
+
 @pytest.mark.parametrize("B", [1, 4, 16])
 def test_ffn_step_1b_shape(hire, oracle, ffn_1b, B):
     """Config 2: d_m=2048, d_ff=16384, k=819, k'=3276, iid tokens, union across the batch."""
