@@ -20,9 +20,9 @@ using namespace hire;
 constexpr size_t kAlign = 256;
 constexpr int kSingleWgMaxRow = 32768;  // up to this row length one workgroup per token selects the k' keys
 constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the gather run on the matrix cores
-constexpr int kFilterMinBatch = 16;  // filter and refine pays from here on (the fp64 tile count grows with the batch)
+constexpr int kSoftmaxFilterMinBatch = 16;  // softmax step: filter and refine from here on (the refining selection is
+                                            // dearer than ranking fp64 logits until the fp64 tiles outgrow it)
 constexpr int kCounters = 64;     // int32 counters behind the union bitmap, cleared with it by a step's first kernel
-constexpr int kCntWnormMax = 8;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
@@ -45,11 +45,12 @@ struct StepBuffers {
   uint32_t* window_misses;  // counter inside the header
   unsigned long long sig;  // names this layout
   int8_t* xq;
-  float* sx;
+  float* sumabs;     // [B] sums of the tokens' absolute int8 codes
   uint16_t* t;       // low-rank intermediate, bf16 [B, r]
   float* keys_t;     // int4 low-rank scorer: the intermediate before rounding, fp32 [B, r]
   double* t_partial; // its per-slice partial sums
-  void* keys;        // fp32 or fp64 [B, N]
+  void* keys;        // fp32 or fp64 [B, key_stride]
+  long long key_stride;
   void* gkeys;       // group-sparse: summed absolute keys, same type, [B, N >> gs]
   double* hg;        // group-sparse: summed absolute exact activations [B, cap_u]
   uint32_t* bitmap;  // candidate union bitmap, then (after it) the counters
@@ -61,8 +62,11 @@ struct StepBuffers {
   float* partial;    // second-layer partial sums (batch-1 route with several row groups)
   // filter and refine of the exact stage (batches): upper bounds of the tokens' norms, the fp32 stored values
   float* xnorm;      // [B]
-  float* hf;         // [B, hf_stride]
-  int hf_stride;
+  float* wnorm_tiles; // largest candidate row norm of every workgroup of the filter stage
+  float* hf;         // [B, hf_stride]: by unit (by_unit: FFN) or by rank in the union (softmax)
+  long long hf_stride;
+  bool by_unit;
+  double* h64;       // by_unit: [B, hf_stride] scratch of the refining selection
   void* sm1_slots;   // long rows: slots of the keys at or above the bound from the scorer's maxima
   bool sm1_ok;       // ... which this layout has
   bool max_ok;       // long rows: slots for the selection of k' from the scorer's maxima
@@ -85,11 +89,13 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
                                                                  general_fallbacks_offset(1))
                                   : nullptr;
   const bool int4_like = scorer_kind == HIRE_SCORER_INT4 || scorer_kind == HIRE_SCORER_LRQ;
+  s.by_unit = ffn && B >= kMfmaMinBatch && gs == 0 && batch_select_supported(N, k);
+  s.key_stride = s.by_unit ? (N + 3) / 4 * 4 : N;  // whole 16-byte vectors
   if (int4_like && N > kSingleWgMaxRow && gs == 0) s.hist.multi_body = c.take<char>(multi_body_bytes_host(B));
   if (int4_like) {
     s.xq = c.take<int8_t>((size_t)B * (d > r ? d : r));
-    s.sx = c.take<float>(B);
-    s.keys = c.take<float>((size_t)B * N + 4);
+    s.sumabs = c.take<float>(B);
+    s.keys = c.take<float>((size_t)B * s.key_stride + 4);
     if (gs > 0) s.gkeys = c.take<float>((size_t)B * Ns + 4);
     if (scorer_kind == HIRE_SCORER_LRQ) {
       s.keys_t = c.take<float>((size_t)B * r + 4);
@@ -98,22 +104,26 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   } else {
     s.t = c.take<uint16_t>((size_t)B * r);
     s.t_partial = c.take<double>((size_t)B * lr_project_slices(d) * r);
-    s.keys = c.take<double>((size_t)B * N);
+    s.keys = c.take<double>((size_t)B * s.key_stride);
     if (gs > 0) s.gkeys = c.take<double>((size_t)B * Ns);
   }
-  // bitmap and counters are contiguous so that one pass clears both.  counters[0] = |U|, [kCntWnormMax] = largest
-  // candidate row norm of the filter stage (float bits)
+  // bitmap and counters are contiguous so that one pass clears both.  counters[0] = |U|
   s.bitmap = c.take<uint32_t>((size_t)s.words + kCounters);
   s.counters = s.bitmap ? reinterpret_cast<int32_t*>(s.bitmap + s.words) : nullptr;
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
-  s.h = c.take<double>(((size_t)B * s.cap_u << gs) + 2);
-  if (gs > 0) s.hg = c.take<double>((size_t)B * s.cap_u + 2);
-  if (B >= kFilterMinBatch && gs == 0 && (ffn || s.cap_u <= kSoftmaxRefineMaxRow)) {
+  const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
+  if (s.by_unit || sm_filter) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
-    s.hf_stride = (s.cap_u + 3) / 4 * 4;  // rows start at multiples of 16 bytes
+    s.wnorm_tiles = c.take<float>(filter_tiles(s.by_unit ? N : s.cap_u));
+    s.hf_stride = ((s.by_unit ? N : s.cap_u) + 3) / 4 * 4;  // rows start at multiples of 16 bytes
     s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
+  // by_unit: one place for the exact route's activations and the refining selection's scratch
+  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, h64_doubles = s.by_unit ? (size_t)B * s.hf_stride : 0;
+  s.h = c.take<double>(h_doubles > h64_doubles ? h_doubles : h64_doubles);
+  s.h64 = s.by_unit ? s.h : nullptr;
+  if (gs > 0) s.hg = c.take<double>((size_t)B * s.cap_u + 2);
   s.sm1_ok = !ffn && B == 1 && gs == 0 && int4_like && N > kSingleWgMaxRow && softmax_b1_supported(N, d, 1, 1);
   s.max_ok = gs == 0 && int4_like && N > kSingleWgMaxRow && maxima_select_supported(N);
   if (s.sm1_ok || s.max_ok) s.sm1_slots = c.take<char>(maxima_select_slot_bytes(B, N));
@@ -188,7 +198,7 @@ ScorerRefs scorer_of(const Layer* L) {
   return ScorerRefs{L->scorer_kind, L->q4, L->q4_scale, L->lr_a, L->lr_b, L->r, L->lr_a_scale, L->lr_b_scale};
 }
 
-// filter: the exact stage writes the fast bf16 approximations (launch_gather_dot_bf16) instead of the fp64
+// filter: the exact stage writes the fast bf16 approximations (launch_filter_bf16) instead of the fp64
 // activations; the caller then refines around the selection threshold.
 // maxima_out (one token, int4 scorers): return after the scorer, with the number of maxima it left.
 int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const void* x, int B, int d, int N,
@@ -212,7 +222,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   const bool in_select = gs == 3 && Ns <= kSelectGroup8Max;
   SelectParams sp{};
   sp.group8 = in_select ? 1 : 0;
-  sp.stride = in_select ? N : Ns;
+  sp.stride = gs == 0 ? s.key_stride : (in_select ? N : Ns);
   sp.n = Ns;
   sp.n_cap = Ns;
   sp.k = kprime >> gs;
@@ -237,9 +247,9 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_TRY(launch_scorer_int4_fused(qa, sc.lr_a_scale, xb, false, r, d, 0, s.keys_t, nullptr, header_only, s.bitmap,
                                         s.zero_words, s.sig, st));
     } else {
-      HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sx, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
       if (B >= kMfmaMinBatch)
-        HIRE_TRY(launch_scorer_int4_mfma(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
+        HIRE_TRY(launch_scorer_int4_mfma(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, r, nullptr, header_only, st));
       else
         HIRE_TRY(launch_scorer_int4(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
     }
@@ -250,7 +260,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   if (int4_like) {
     const bool fused = B == 1 && scorer_int4_fused_supported(sd);  // the scorer quantises the token itself
     if (!fused)
-      HIRE_TRY(launch_quantize_tokens(tok, B, sd, s.xq, s.sx, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      HIRE_TRY(launch_quantize_tokens(tok, B, sd, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
     HIRE_STAGE(1, st);
     int slots;
     if (fused) {
@@ -262,7 +272,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       slots = scorer_int4_fused_maxima(N, sd);
     } else if (B >= kMfmaMinBatch) {
       HIRE_TRY(launch_scorer_int4_mfma(static_cast<const uint32_t*>(q4), q4_scale, s.xq, B, N, sd, relu,
-                                       static_cast<float*>(s.keys), scorer_acc, s.hist, st));
+                                       static_cast<float*>(s.keys), s.key_stride, scorer_acc, s.hist, st));
       slots = scorer_mfma_maxima(N);
     } else {
       HIRE_TRY(launch_scorer_int4(static_cast<const uint32_t*>(q4), q4_scale, s.xq, B, N, sd, relu,
@@ -289,6 +299,11 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_STAGE(3, st);
       HIRE_TRY(launch_resolve_compact(static_cast<const float*>(s.keys), B, N, kprime, s.hist, s.bitmap, s.words,
                                       in_gather ? nullptr : cand, s.counters, n_cand, nullptr, 0, st));
+    } else if (s.by_unit) {
+      HIRE_TRY(launch_keys_select(static_cast<const float*>(s.keys), s.key_stride, B, N, kprime, s.sumabs,
+                                  reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2)),
+                                  s.bitmap, s.window_misses, st));
+      HIRE_STAGE(3, st);
     } else {
       HIRE_TRY(launch_select_f32(sp, B, st));
       HIRE_STAGE(3, st);
@@ -300,7 +315,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     HIRE_STAGE(1, st);
     if (B >= kMfmaMinBatch)  // the same contraction as the exact stage, over all rows of Z2 with t as the tokens
       HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(lr_b), s.t, B, r, nullptr, N, nullptr, N, relu,
-                                      static_cast<double*>(s.keys), N, s.hist, nullptr, 0, st));
+                                      static_cast<double*>(s.keys), s.key_stride, s.hist, nullptr, 0, st));
     else
       HIRE_TRY(launch_lr_score(static_cast<const uint16_t*>(lr_b), s.t, N, r, relu, static_cast<double*>(s.keys), st));
     HIRE_STAGE(2, st);
@@ -313,9 +328,9 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   }
   HIRE_STAGE(4, st);
   if (filter)
-    HIRE_TRY(launch_gather_dot_bf16(static_cast<const uint16_t*>(W), xb, B, d, cand, s.counters, s.cap_u, s.hf,
-                                    s.hf_stride, s.hist, in_gather ? &un : nullptr, N, relu, s.xnorm,
-                                    reinterpret_cast<uint32_t*>(s.counters + kCntWnormMax), st));
+    HIRE_TRY(launch_filter_bf16(static_cast<const uint16_t*>(W), xb, B, d, cand, s.counters, s.cap_u, s.hf, s.hf_stride,
+                                s.hist, (in_gather || s.by_unit) ? &un : nullptr, N, s.by_unit, s.xnorm, s.wnorm_tiles, nullptr,
+                                st));
   else if (B >= kMfmaMinBatch)
     HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(W), xb, B, d, cand, 0, s.counters, s.cap_u, relu, s.h,
                                     (long long)s.cap_u << gs, s.hist, in_gather ? &un : nullptr, gs, st));
@@ -421,9 +436,9 @@ int hire_debug_filter_stage(const void* W, const void* x, int B, int d, int rows
       d < 8 || d % 8 != 0 || !aligned(W, 16) || !aligned(x, 16))
     return HIRE_EINVAL;
   *err_c = gather_filter_error(B);
-  HIRE_TRY(launch_gather_dot_bf16(static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(x), B, d, nullptr,
-                                  rows_dev, rows, stored, rows, HistRefs{}, nullptr, rows, 1, xnorm, wnorm_max,
-                                  static_cast<hipStream_t>(stream)));
+  HIRE_TRY(launch_filter_bf16(static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(x), B, d, nullptr, rows_dev,
+                              rows, stored, rows, HistRefs{}, nullptr, rows, true, xnorm, nullptr, wnorm_max,
+                              static_cast<hipStream_t>(stream)));
   return HIRE_OK;
 }
 
@@ -534,44 +549,53 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     return HIRE_OK;
   }
 
-  // step 4: exact top-k of h over U for every token
-  SelectParams sp{};
-  sp.vals = s.h;
-  sp.stride = s.cap_u;
-  sp.n_dev = s.counters;
-  sp.n_cap = s.cap_u;
-  sp.k = k;
-  sp.idx_out = topk_idx;
-  sp.val_out = topk_val;
-  sp.list_out = s.list;
-  sp.nonneg = 1;  // activations after the ReLU
-  sp.window_misses = s.window_misses;
-  // Batches: filter and refine.  The exact stage runs on the bf16 matrix cores and stores fp32 values within a
-  // proven distance of the activations; the selection finds the k-th largest stored value of every token,
-  // recomputes in fp64 the entries within twice that distance of it and selects on the result.  Whatever lies
-  // outside that band is on the same side of the threshold in fp64 as its stored value, so the selected sets are
-  // those of the fp64 activations.
-  SelectParams fr = sp;
-  fr.vals = s.hf;
-  fr.stride = s.hf_stride;
-  fr.refine_w = static_cast<const uint16_t*>(L->w1u);
-  fr.refine_x = static_cast<const uint16_t*>(x);
-  fr.refine_d = d;
-  fr.refine_h = s.h;
-  fr.refine_h_stride = s.cap_u;
-  fr.xnorm = s.xnorm;
-  fr.wnorm_max = reinterpret_cast<const uint32_t*>(s.counters + kCntWnormMax);
-  fr.err_c = gather_filter_error(B);
-  const bool filter = B >= kFilterMinBatch && s.hf != nullptr && select_refine_supported(fr) && !g_force_exact_stage;
+  // steps 1-3.  Batches: filter and refine.  The exact stage runs on the bf16 matrix cores and stores fp32 values
+  // within a proven distance of the activations; the selection recomputes in fp64 those around every token's k-th
+  // largest.  Whatever lies outside that band is on the same side of the threshold in fp64 as its stored value, so
+  // the selected sets are those of the fp64 activations.
+  const bool filter = s.by_unit && !g_force_exact_stage;
   rc = run_front(s, scorer_of(L), L->w1u, x, B, d, N, kprime, 1, cand_idx, n_cand, scorer_acc, st, 0, filter);
   if (rc != HIRE_OK) return rc;
-  const int32_t* cand = cand_idx ? cand_idx : s.cand;
-  sp.map = fr.map = cand;
   HIRE_STAGE(5, st);
-  if (filter)
-    HIRE_TRY(launch_select_refine(fr, B, st));
-  else
+
+  // step 4: exact top-k over U for every token
+  if (filter) {
+    RefineParams rp{};
+    rp.vals = s.hf;
+    rp.stride = s.hf_stride;
+    rp.B = B; rp.N = N; rp.k = k; rp.d = d;
+    rp.W = static_cast<const uint16_t*>(L->w1u);
+    rp.x = static_cast<const uint16_t*>(x);
+    rp.xnorm = s.xnorm;
+    rp.wnorm_tiles = s.wnorm_tiles;
+    rp.wnorm_n = filter_tiles(N);
+    rp.err_c = gather_filter_error(B);
+    rp.bitmap = s.bitmap;
+    if (cand_idx != nullptr || n_cand != nullptr) {
+      rp.cand_out = cand_idx != nullptr ? cand_idx : s.cand;
+      rp.n_cand_out = n_cand;
+    }
+    rp.h64 = s.h64;
+    rp.idx_out = topk_idx;
+    rp.val_out = topk_val;
+    rp.list_out = s.list;
+    rp.window_misses = s.window_misses;
+    HIRE_TRY(launch_refine(rp, st));
+  } else {
+    SelectParams sp{};
+    sp.vals = s.h;
+    sp.stride = s.cap_u;
+    sp.n_dev = s.counters;
+    sp.n_cap = s.cap_u;
+    sp.k = k;
+    sp.idx_out = topk_idx;
+    sp.val_out = topk_val;
+    sp.list_out = s.list;
+    sp.map = cand_idx ? cand_idx : s.cand;
+    sp.nonneg = 1;  // activations after the ReLU
+    sp.window_misses = s.window_misses;
     HIRE_TRY(launch_select_f64(sp, B, st));
+  }
   HIRE_STAGE(6, st);
 
   // step 5: second layer over each token's selected rows
@@ -657,6 +681,9 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
   const int gs = group_shift(group);
   if (gs < 0 || N % group || k % group || kprime % group) return HIRE_EINVAL;
   if ((N >> gs) > kSingleWgMaxRow) return HIRE_EUNSUPPORTED;
+  if (gs == 0 && dense == nullptr)  // groups of one: the plain step, which has the same workspace layout
+    return hire_ffn_step(L, x, B, k, kprime, y, topk_group, topk_val, cand_group, n_cand, scorer_acc, workspace,
+                         workspace_bytes, stream);
   const StepBuffers s = carve(workspace, L->scorer_kind, B, d, N, L->r, k, kprime, true, gs);
   if (workspace_bytes < s.bytes) return HIRE_ENOSPC;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -853,7 +880,7 @@ int hire_softmax_step(const hire_softmax_layer* L, const void* x, int B, int k, 
 
   // Batches: filter and refine as in the FFN step - fp32 logits with a proven error from the bf16 matrix cores,
   // fp64 only for the entries that can still be among the k largest.
-  const bool filter = B >= kFilterMinBatch && s.hf != nullptr && s.cap_u <= kSoftmaxRefineMaxRow &&
+  const bool filter = B >= kSoftmaxFilterMinBatch && s.hf != nullptr && s.cap_u <= kSoftmaxRefineMaxRow &&
                       k <= kSoftmaxRefineMaxK && d % 8 == 0 && !g_force_exact_stage;
   // One token on a long vocabulary: the scorer (both int4 kinds), the exact logits of a superset of the shortlist
   // (from the scorer's maxima), and the final selections with the softmax.
@@ -897,7 +924,8 @@ int hire_softmax_step(const hire_softmax_layer* L, const void* x, int B, int k, 
     sp.refine_x = static_cast<const uint16_t*>(x);
     sp.refine_d = d;
     sp.xnorm = s.xnorm;
-    sp.wnorm_max = reinterpret_cast<const uint32_t*>(s.counters + kCntWnormMax);
+    sp.wnorm_tiles = s.wnorm_tiles;
+    sp.wnorm_n = filter_tiles(s.cap_u);
     sp.err_c = gather_filter_error(B);
     HIRE_TRY(launch_softmax_refine(sp, B, st));
   } else {

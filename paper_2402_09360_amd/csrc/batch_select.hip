@@ -1,0 +1,462 @@
+// The two selections of a batched FFN step (TopInd_k of arXiv 2402.09360 Sec. 3.1, both lines of Algorithm 1), one
+// workgroup of sixteen waves per token, rows of up to 32768 units:
+//
+//   k_keys_select  the k' largest scorer keys of a token -> its bits of the union bitmap
+//   k_refine       the k largest exact activations of a token from the filter stage's values (launch_filter_bf16,
+//                  in unit order), recomputing in fp64 what lies around the threshold -> indices, values and the
+//                  (row, coefficient) list of the second layer
+//
+// Both are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
+// count per thread times 16 cycles (four waves share a SIMD), so what counts is the number of sections and of passes
+// over the register-resident row.  The window histogram (fast_select.h) is anchored at an a-priori bound of the
+// row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves, so the
+// number of entries above the bin it proposes is exact and no counting pass confirms it.
+#include "fast_select.h"
+#include "kernels.h"
+
+namespace hire {
+
+constexpr int kBsCap = 128;  // refined entries around the threshold kept in LDS
+
+template <int LOADS>
+struct BatchKeys {
+  using Keys = KeyRegs<uint32_t, LOADS, kSelThreads>;
+  static_assert(LOADS * Keys::PER <= 32, "one bit per key of a lane");
+};
+
+// Window histogram of the registers' values below `anchor` (zeros are never counted) and the bin that holds the k-th
+// largest.  false: fewer than k values in the window.  *bin: that bin; *above: the values in higher bins.
+template <typename Keys>
+__device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int k, uint32_t* win,
+                                           SelSharedT<kSelThreads>& sh, uint32_t* bin, int* above) {
+#pragma unroll
+  for (int e = 0; e < (int)(sizeof(kr.r) / sizeof(kr.r[0])); ++e)
+#pragma unroll
+    for (int q = 0; q < Keys::PER; ++q) {
+      const uint32_t slot = anchor - fine_bin(kr.r[e][q]);
+      if (kr.r[e][q] != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
+    }
+  __syncthreads();
+  WinRegs<kSelThreads> wr;
+  wr.issue(win);
+  const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
+  *bin = anchor - (uint32_t)wk.slot;
+  *above = wk.above;
+  return wk.found && *bin >= 1u && *bin <= anchor;  // uniform
+}
+
+// ---------------------------------------------------------------------------------------------------
+// sumabs[b]: sum of the token's |int8 codes|, *smax: the largest row scale of the int4 copy that the keys were scored
+// with: key_j = fl(fl(acc_j) s_j) <= fl(7 sumabs smax), rounding being monotone (7 sumabs < 2^24).
+template <int LOADS>
+__global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __restrict__ keys, long long stride, int N,
+                                                             int kprime, const float* __restrict__ sumabs,
+                                                             const float* __restrict__ smax,
+                                                             uint32_t* __restrict__ bitmap,
+                                                             uint32_t* __restrict__ window_misses) {
+  using Keys = typename BatchKeys<LOADS>::Keys;
+  constexpr int PER = Keys::PER;
+  __shared__ SelSharedT<kSelThreads> sh;
+  __shared__ __align__(16) uint32_t win[kWin];
+  __shared__ int wave_cnt[kSelWaves];
+  __shared__ uint32_t l_key[kFastAmbCap];
+  __shared__ int l_idx[kFastAmbCap];
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
+  HIRE_TS(10);
+  const float* row = keys + (size_t)b * stride;
+  Keys kr;
+  kr.issue_clamped(row, N);  // rows are padded to whole vectors
+  const uint32_t anchor = fine_bin(__float_as_uint(7.0f * sumabs[b] * *smax));
+  {
+    uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
+    z[0] = z[1] = make_uint4(0, 0, 0, 0);
+  }
+  if (tid == 0) sh.list_n = 0;
+  kr.finish();
+  kr.mask_beyond(N);
+  __syncthreads();
+  HIRE_TS(11);
+  uint32_t bin;
+  int above;
+  bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above);
+  HIRE_TS(12);
+  Selection<uint32_t> sel;
+  if (known) {  // the bin's own few keys, ranked by every wave
+    const uint32_t lo = bin_floor<uint32_t>(bin), width = bin_floor<uint32_t>(bin + 1u) - lo;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        if (kr.r[e][q] - lo < width) {
+          const int p = atomicAdd(&sh.list_n, 1);
+          if (p < kFastAmbCap) {
+            l_key[p] = kr.r[e][q];
+            l_idx[p] = kr.index(e, q);
+          }
+        }
+    __syncthreads();
+    HIRE_TS(13);
+    const int m = sh.list_n, need = kprime - above;
+    known = m <= kFastAmbCap;  // uniform
+    if (known) {
+      const uint32_t mine_k = lane < m ? l_key[lane] : 0u;
+      const int mine_i = lane < m ? l_idx[lane] : 0x7FFFFFFF;
+      int rank = 0;
+      for (int u = 0; u < m; ++u)
+        rank += ranks_ahead(read_lane(mine_k, u), __builtin_amdgcn_readlane(mine_i, u), mine_k, mine_i) ? 1 : 0;
+      const int src = __builtin_ctzll(__ballot(lane < m && rank == need - 1));  // exactly one lane
+      sel.cut.key = read_lane(mine_k, src);
+      sel.cut.idx = __builtin_amdgcn_readlane(mine_i, src);
+      sel.plain = __ballot(lane < m && rank >= need && mine_k == sel.cut.key) == 0ull;
+    }
+    HIRE_TS(14);
+  }
+  if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
+    WinRegs<kSelThreads> none{};
+    sel = fast_select<60>(kr, row, kprime, none, 0u, false, sh, wave_cnt, window_misses, 0, kprime, true);
+  }
+  // A bitmap word covers 32 consecutive indices: the keys of 32 / PER neighbouring lanes of one load.  Those lanes
+  // fold their bits together and one of them adds the word to the union.
+  constexpr int LPW = 32 / PER;
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e) {
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const bool take = sel.plain ? kr.r[e][q] >= sel.cut.key
+                                  : (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)));
+      bits |= take ? 1u << q : 0u;
+    }
+    bits <<= (lane % LPW) * PER;
+#pragma unroll
+    for (int m = 1; m < LPW; m <<= 1) bits |= (uint32_t)__shfl_xor((int)bits, m);
+    if (lane % LPW == 0 && bits != 0u) atomicOr(&bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / LPW], bits);
+  }
+  HIRE_TS(15);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.
+__device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row, const uint4* tok, int d) {
+  const int cpr = d / 8, lane = lane_id();
+  const uint4* r4 = reinterpret_cast<const uint4*>(row);
+  double acc0 = 0.0, acc1 = 0.0;
+#pragma nounroll
+  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
+    uint4 wv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) wv[v] = r4[min(c0 + v * kWave + lane, cpr - 1)];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (c0 + v * kWave + lane < cpr) {
+        const uint4 xv = tok[c0 + v * kWave + lane];
+        const uint32_t wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, xd[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc0 += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
+          acc1 += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
+        }
+      }
+  }
+  const double s = wave_sum(acc0 + acc1);
+  return s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
+}
+
+struct RefineShared {
+  SelSharedT<kSelThreads> sh;
+  __align__(16) uint32_t win[kWin];  // window histogram; then the packed outputs (k <= kWin / 2)
+  unsigned long long l_val[kBsCap];  // refined values (fp64 bits) and their units
+  int l_idx[kBsCap];
+  int wave_cnt[kSelWaves], wave_eq[kSelWaves];
+  float wave_max[kSelWaves];
+};
+
+// What the histogram and the list cannot settle (threshold among the zeros, very many activations within the error of
+// the threshold): exact, by streaming the row.  The k-th largest stored value among the candidates by range
+// narrowing; everything within hw of it recomputed in fp64; then the k-th largest of the row of fp64 values (stored
+// ones outside the band) with ties to the lower unit, and the outputs.
+__device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, const uint4* tok, RefineShared& L, double hw) {
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int N = p.N, k = p.k;
+  const float* row = p.vals + (size_t)b * p.stride;
+  double* h = p.h64 + (size_t)b * p.stride;
+  auto candidate = [&](int i) { return ((p.bitmap[i >> 5] >> (i & 31)) & 1u) != 0u; };
+  int mine = 0;
+  for (int i = tid; i < (N + 31) / 32; i += kSelThreads) mine += __popc(p.bitmap[i]);
+  int n_units;
+  wg_scan_incl<kSelThreads>(mine, L.sh, &n_units);
+  const uint32_t okey = wg_kth_largest<uint32_t>(
+      [&](auto&& f) {
+#pragma unroll 1
+        for (int i = tid; i < N; i += kSelThreads) f(candidate(i) ? order_key(row[i]) : 0u);
+      },
+      N, k, L.sh);
+  const double cut0 = (double)key_value(okey);
+  const double lo = cut0 - hw, hi = cut0 + hw;
+  // the same positions are written and read by this workgroup only; a barrier orders them
+#pragma unroll 1
+  for (int i0 = w * kWave; i0 < N; i0 += kSelThreads) {
+    const int i = i0 + lane;
+    const float v = i < N ? row[i] : 0.0f;
+    const bool cand = i < N && candidate(i);
+    if (i < N) h[i] = cand ? (double)v : -1.0;
+    // exact zeros are activations already; with k = all candidates nothing needs to be decided
+    uint64_t band = __ballot(cand && k < n_units && v > 0.0f && (double)v >= lo && (double)v <= hi);
+    while (band != 0ull) {
+      const int s = __builtin_ctzll(band);
+      band &= band - 1ull;
+      const double r = wave_row_dot(p.W + (size_t)(i0 + s) * p.d, tok, p.d);
+      if (lane == s) h[i] = r;
+    }
+  }
+  __syncthreads();
+  const uint64_t t = wg_kth_largest<uint64_t>(
+      [&](auto&& f) {
+#pragma unroll 1
+        for (int i = tid; i < N; i += kSelThreads) f(order_key(h[i]));
+      },
+      N, k, L.sh);
+  const int M = ((N + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave * kWave, i_lo = w * M, i_hi = min(N, i_lo + M);
+  int gt = 0, eq = 0;
+#pragma unroll 1
+  for (int i = i_lo + lane; i < i_hi; i += kWave) {
+    const uint64_t key = order_key(h[i]);
+    gt += key > t ? 1 : 0;
+    eq += key == t ? 1 : 0;
+  }
+  gt = wave_sum(gt);
+  eq = wave_sum(eq);
+  __syncthreads();
+  if (lane == 0) {
+    L.wave_cnt[w] = gt;
+    L.wave_eq[w] = eq;
+  }
+  __syncthreads();
+  int run_gt = 0, run_eq = 0, all_gt = 0;
+  for (int u = 0; u < kSelWaves; ++u) {
+    run_gt += u < w ? L.wave_cnt[u] : 0;
+    run_eq += u < w ? L.wave_eq[u] : 0;
+    all_gt += L.wave_cnt[u];
+  }
+  const int need_eq = k - all_gt;
+#pragma unroll 1
+  for (int i0 = i_lo; i0 < i_hi; i0 += kWave) {  // uniform trip count per wave
+    const int i = i0 + lane;
+    const double v = i < i_hi ? h[i] : -1.0;
+    const uint64_t key = order_key(v);
+    const uint64_t mg = __ballot(i < i_hi && key > t), me = __ballot(i < i_hi && key == t);
+    const int gt_before = run_gt + mask_prefix(mg), eq_before = run_eq + mask_prefix(me);
+    run_gt += __popcll(mg);
+    run_eq += __popcll(me);
+    if (i < i_hi && (key > t || (key == t && eq_before < need_eq))) {
+      const size_t o = (size_t)b * k + gt_before + min(eq_before, need_eq);
+      if (p.idx_out) p.idx_out[o] = i;
+      if (p.val_out) p.val_out[o] = (float)v;
+      p.list_out[o] = make_uint2((uint32_t)i, __float_as_uint((float)v));
+    }
+  }
+}
+
+// The stored values are within delta(b, j) = err_c |u_j| |x_b| of the activations.  With f and c the edges of the fine
+// bin that holds the k-th largest stored value and hw = 2 err_c max|u| |x| >= 2 delta, the true k-th largest lies in
+// [f - hw/2, c + hw/2): entries stored above H = c + hw are larger, entries stored below f - hw smaller, and what lies
+// between is recomputed in fp64 (about fifteen entries at the ~1B shape).  With A entries above, the k - A largest recomputed
+// ones complete the selection.  The outcome is checked and not taken on trust: if the (k - A)-th largest recomputed
+// value r satisfies L + hw/2 <= r <= H - hw/2, every entry above H is at least r and every one below L less than r.
+template <int LOADS>
+__global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
+  using K = uint32_t;
+  using Keys = typename BatchKeys<LOADS>::Keys;
+  constexpr int PER = Keys::PER;
+  __shared__ RefineShared L;
+  extern __shared__ uint4 tok_sh[];  // the token, d <= kRefineTokenMax
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int N = p.N, k = p.k, d = p.d;
+  if (b == p.B) {  // one more workgroup lists the candidates meanwhile
+    const int n = list_bitmap<kSelThreads>(p.bitmap, (N + 31) / 32, p.cand_out, L.sh);
+    if (tid == 0 && p.n_cand_out) *p.n_cand_out = n;
+    return;
+  }
+  HIRE_TS(40);
+  const float* row = p.vals + (size_t)b * p.stride;
+  const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * d);
+  Keys kr;
+  kr.issue_clamped(row, N);
+  if (d <= kRefineTokenMax) {
+    for (int i = tid; i < d / 8; i += kSelThreads) tok_sh[i] = tok[i];
+    tok = tok_sh;
+  }
+  const float xn = p.xnorm[b];
+  float wn = 0.0f;
+  for (int i = tid; i < p.wnorm_n; i += kSelThreads) wn = fmaxf(wn, p.wnorm_tiles[i]);
+  wn = wave_max(wn);
+  if (lane == 0) L.wave_max[w] = wn;
+  {
+    uint4* z = reinterpret_cast<uint4*>(L.win) + 2 * tid;
+    z[0] = z[1] = make_uint4(0, 0, 0, 0);
+  }
+  if (tid == 0) L.sh.list_n = 0;
+  kr.finish();
+  kr.mask_beyond(N);
+  __syncthreads();
+  wn = wave_max(lane < kSelWaves ? L.wave_max[lane] : 0.0f);
+  const uint32_t anchor = fine_bin(__float_as_uint(xn * wn * 1.001f));  // of a bound of every stored value
+  const double hw = 2.0 * (double)p.err_c * (double)xn * (double)wn * 1.000001;
+  HIRE_TS(41);
+  uint32_t bin;
+  int above_bin;
+  const bool found = window_bin(kr, anchor, k, L.win, L.sh, &bin, &above_bin);
+  HIRE_TS(42);
+  (void)above_bin;  // the band's own counts decide
+  if (found) {  // uniform
+    const double f = (double)__uint_as_float(bin << kFineShift), c = (double)__uint_as_float((bin + 1u) << kFineShift);
+    const double lo_v = f - hw, hi_v = c + hw;
+    const K lo_k = __float_as_uint(__double2float_rd(lo_v)), hi_k = __float_as_uint(__double2float_ru(hi_v));
+    if (lo_v > 0.0) {  // uniform; non-negative floats order like their bit patterns
+      const K width = hi_k - lo_k;
+      int gt = 0;
+      uint32_t bits = 0u;  // bit e * PER + q: this lane's key (e, q) lies in the band
+#pragma unroll
+      for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+          gt += kr.r[e][q] > hi_k ? 1 : 0;
+          bits |= (K)(kr.r[e][q] - lo_k) <= width ? 1u << (e * PER + q) : 0u;
+        }
+      const int above = wave_sum(gt);
+      if (lane == 0) L.wave_cnt[w] = above;
+      uint32_t slots = 0u;  // list places of this lane's first four band keys
+      int nb = 0;
+      for (uint32_t m = bits; m != 0u; m &= m - 1u, ++nb) {
+        const int t = __builtin_ctz(m), slot = atomicAdd(&L.sh.list_n, 1);
+        if (slot < kBsCap) L.l_idx[slot] = kr.index(t / PER, t % PER);
+        if (nb < 4) slots |= (uint32_t)min(slot, 255) << (8 * nb);
+      }
+      __syncthreads();
+      HIRE_TS(43);
+      const int pa = wave_scan_incl(lane < kSelWaves ? L.wave_cnt[lane] : 0);
+      const int A = __builtin_amdgcn_readlane(pa, kSelWaves - 1), C = L.sh.list_n, need = k - A;
+      if (C <= kBsCap && need >= 1 && need <= C) {  // uniform
+        for (int i = w; i < C; i += kSelWaves) {    // a wave per entry
+          const double s = wave_row_dot(p.W + (size_t)L.l_idx[i] * d, tok, d);
+          if (lane == 0) L.l_val[i] = (unsigned long long)__double_as_longlong(s);
+        }
+        __syncthreads();
+        HIRE_TS(44);
+        // ranks (value descending, unit ascending), in every wave: lane l holds entries l and l + 64
+        unsigned long long kv[2];
+        int ki[2], rank[2] = {0, 0};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int i = lane + u * kWave;
+          kv[u] = i < C ? L.l_val[i] : 0ull;
+          ki[u] = i < C ? L.l_idx[i] : 0x7FFFFFFF;
+        }
+        for (int j0 = 0; j0 < C; j0 += 4) {  // broadcast reads, four in flight
+          unsigned long long ov[4];
+          int oi[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            ov[j] = L.l_val[min(j0 + j, C - 1)];
+            oi[j] = L.l_idx[min(j0 + j, C - 1)];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (j0 + j < C) {
+              rank[0] += ranks_ahead((uint64_t)ov[j], oi[j], (uint64_t)kv[0], ki[0]) ? 1 : 0;
+              if (C > kWave) rank[1] += ranks_ahead((uint64_t)ov[j], oi[j], (uint64_t)kv[1], ki[1]) ? 1 : 0;
+            }
+        }
+        double cut = 0.0;
+        uint64_t taken[2];
+        uint32_t selbits = 0u;
+        int lower = 0, here = 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bool in = lane + u * kWave < C, take = in && rank[u] < need;
+          const uint64_t last = __ballot(in && rank[u] == need - 1);
+          if (last != 0ull) cut = __longlong_as_double((long long)read_lane(kv[u], __builtin_ctzll(last)));
+          const int rel = ki[u] - kr.base;
+          taken[u] = __ballot(take && rel >= 0 && rel < kr.len);
+          lower += __popcll(__ballot(take && rel < 0));
+          here += __popcll(taken[u]);
+          for (uint64_t m = taken[u]; m != 0ull; m &= m - 1ull) {  // mark this wave's own at their lanes
+            const int r = __builtin_amdgcn_readlane(rel, __builtin_ctzll(m));
+            if (lane == (r % Keys::SPAN) / PER) selbits |= 1u << (r / Keys::SPAN * PER + r % PER);
+          }
+        }
+        HIRE_TS(45);
+        if (cut >= lo_v + 0.5 * hw && cut <= hi_v - 0.5 * hw) {  // uniform
+          int* pk_pos = reinterpret_cast<int*>(L.win);
+          float* pk_val = reinterpret_cast<float*>(L.win + kWin / 2);
+          const int above_before = w > 0 ? __builtin_amdgcn_readlane(pa, w - 1) : 0;
+          fast_emit_if(
+              kr, above_before + lower, above + here, 0, k,
+              [&](int e, int q) { return kr.r[e][q] > hi_k || ((selbits >> (e * PER + q)) & 1u) != 0u; },
+              [&](int i, int out, K key, int e, int q) {
+                float v = __uint_as_float(key);
+                if (((selbits >> (e * PER + q)) & 1u) != 0u) {  // recomputed: that value
+                  const int n = __popc(bits & ((1u << (e * PER + q)) - 1u));
+                  int slot = (int)(slots >> (8 * n)) & 255;
+                  if (n >= 4)
+                    for (slot = 0; L.l_idx[slot] != i;) ++slot;
+                  v = (float)__longlong_as_double((long long)L.l_val[slot]);
+                }
+                pk_pos[out] = i;
+                pk_val[out] = v;
+              });
+          __syncthreads();
+          HIRE_TS(46);
+          for (int t = tid; t < k; t += kSelThreads) {
+            const int i = pk_pos[t];
+            const float v = pk_val[t];
+            const size_t o = (size_t)b * k + t;
+            p.list_out[o] = make_uint2((uint32_t)i, __float_as_uint(v));
+            if (p.idx_out) p.idx_out[o] = i;
+            if (p.val_out) p.val_out[o] = v;
+          }
+          HIRE_TS(47);
+          return;
+        }
+      }
+    }
+  }
+  if (tid == 0 && p.window_misses) atomicAdd(p.window_misses, 1u);
+  __syncthreads();
+  refine_streaming(p, b, tok, L, hw);
+}
+
+// ---------------------------------------------------------------------------------------------------
+bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k <= kWin / 2; }
+
+hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
+                              const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s) {
+  if (N > 32768 || stride % 4 != 0 || reinterpret_cast<uintptr_t>(keys) % 16 != 0) return hipErrorInvalidValue;
+  if (N <= 16384)
+    return launch(k_keys_select<4>, dim3(B), dim3(kSelThreads), 0, s, keys, stride, N, kprime, sumabs, smax, bitmap,
+                  window_misses);
+  return launch(k_keys_select<8>, dim3(B), dim3(kSelThreads), 0, s, keys, stride, N, kprime, sumabs, smax, bitmap,
+                window_misses);
+}
+
+hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
+  if (!batch_select_supported(p.N, p.k) || p.stride % 4 != 0 || reinterpret_cast<uintptr_t>(p.vals) % 16 != 0 || p.d % 8 != 0)
+    return hipErrorInvalidValue;
+  const size_t lds = p.d <= kRefineTokenMax ? (size_t)p.d * 2 : 0;
+  static std::atomic<size_t> raised_to[2] = {};
+  auto go = [&](auto kernel, std::atomic<size_t>& raised) {
+    if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
+      return e;
+    return launch(kernel, dim3(p.B + (p.cand_out != nullptr ? 1 : 0)), dim3(kSelThreads), lds, s, p);
+  };
+  return p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
+}
+
+}  // namespace hire
+
+#ifdef HIRE_TIMESTAMPS
+extern "C" int hire_debug_timestamps_batch_select(unsigned long long* host64) {
+  return (int)hipMemcpyFromSymbol(host64, HIP_SYMBOL(hire_ts), sizeof(hire_ts));
+}
+#endif

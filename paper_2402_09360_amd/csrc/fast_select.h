@@ -131,7 +131,7 @@ struct KeyRegs {
 // caller as its first loads).  found == false if the window holds fewer than `need` keys; otherwise the slot
 // holding the need-th largest counted key, to all threads.
 struct WinWalk {
-  int slot;
+  int slot, above;  // above: the keys counted in the slots before it
   bool found;
 };
 template <int NT>
@@ -159,7 +159,7 @@ __device__ __forceinline__ WinWalk walk_window(const WinRegs<NT>& wr, int need, 
   const int incl = wg_scan_incl<NT, true>(s, sh, &total);
   WinWalk r;
   r.found = total >= need;  // uniform
-  r.slot = 0;
+  r.slot = r.above = 0;
   if (!r.found) return r;
   int run = incl - s;
   if (run < need && need <= incl) {  // one thread of the workgroup
@@ -170,7 +170,10 @@ __device__ __forceinline__ WinWalk walk_window(const WinRegs<NT>& wr, int need, 
         int rr = run;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if (rr < need && need <= rr + c[q]) sh.bc_bin = (VEC * tid + u) * 4 + q;
+          if (rr < need && need <= rr + c[q]) {
+            sh.bc_bin = (VEC * tid + u) * 4 + q;
+            sh.bc_above = rr;
+          }
           rr += c[q];
         }
       }
@@ -179,6 +182,7 @@ __device__ __forceinline__ WinWalk walk_window(const WinRegs<NT>& wr, int need, 
   }
   __syncthreads();
   r.slot = sh.bc_bin;
+  r.above = sh.bc_above;
   return r;
 }
 

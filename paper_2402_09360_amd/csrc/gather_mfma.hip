@@ -151,11 +151,11 @@ __global__ __launch_bounds__(256) void k_gather_dot_mfma(const uint16_t* __restr
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Filter stage of the exact pre-activations for batches (filter and refine): the same tile on the bf16 matrix
-// cores, 50 times the fp64 rate, so the stage is a read of the candidate rows.  Tokens are the A matrix,
+// Filter stage of the exact pre-activations for batches (filter and refine): candidate rows times tokens on the
+// bf16 matrix cores, 50 times the fp64 rate, so the stage is a read of the candidate rows.  Tokens are the A matrix,
 // candidate rows the B matrix of a 16x16x32 MFMA: lane (j, g) feeds 16-byte chunk 4 it + g of token j and of
 // candidate j as they come from memory, no conversion; result value i of lane l belongs to token 4 (l / 16) + i
-// and candidate l % 16.  The K range is split over the four waves as above.
+// and candidate l % 16.
 //
 // What is stored is not the activation but a value within a proven distance of it.  Every MFMA (with more than
 // 32 tokens, where the fp64 additions pace the kernel: every second one) starts from a zero accumulator, so a
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256) void k_gather_dot_mfma(const uint16_t* __restr
 // positive float if it lies in (-2 delta, 0], where the true activation may still be positive; exactly 0 below
 // that, where the true activation is exactly 0.  The selection (k_select_refine) recomputes in fp64 the entries
 // whose stored value lies within 2 max_j delta(b, j) of the k-th largest stored value and selects on the result:
-// the selected set is that of the fp64 values.  xnorm[b] receives an upper bound of |x_b| (tile 0), *wnorm_max (float bits, atomic
-// max, cleared by the step's first kernel) one of the largest |u_j| over the candidates.
+// the selected set is that of the fp64 values.  xnorm[b] receives an upper bound of |x_b|, wnorm_tiles[i] one of the
+// largest |u_j| over workgroup i's candidates (or, without it, *wnorm_max over all: float bits, atomic max).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -185,337 +185,277 @@ __device__ __forceinline__ float pick4(const f32x4& v, int i) {
   return i == 0 ? v[0] : (i == 1 ? v[1] : (i == 2 ? v[2] : v[3]));
 }
 
-// profiling build: the same stamps for the grid's last workgroup, four slots further on
-#ifdef HIRE_TIMESTAMPS
-#define HIRE_TS_BOTH(i)                                                              \
-  do {                                                                               \
-    HIRE_TS(i);                                                                      \
-    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1 && blockIdx.y == 0) {        \
-      hire_ts[(i) + 4] = wall_clock64();                                             \
-      hire_ts[64 + (i) + 4] = clock64();                                             \
-    }                                                                                \
-  } while (0)
-#else
-#define HIRE_TS_BOTH(i) ((void)0)
-#endif
+// Layout.  A workgroup owns 64 candidates and all of the batch's tokens (TT tiles of 16): 4 groups of 16
+// candidates times TG shares of the token tiles, one wave each.  K goes by in stages of 128 elements: 256 bytes of
+// every row, brought into LDS by asynchronous 16-byte loads that bypass the registers (a wave's instruction fills 1
+// KiB, four rows), kStages deep: a stage is requested three stages before it is used, and one barrier per stage
+// (which also waits for this wave's share of it) is all the synchronisation.  LDS position p of a row holds its chunk
+// p ^ (row % 16), so that the sixteen lanes that read one chunk column of sixteen rows hit different banks; the
+// permutation is applied to the addresses the lanes load from (inside two cache lines).  Rows past the candidates'
+// end repeat the last one and tokens past the batch the last token: their results are dropped.
+//
+// UNIT (the FFN): the workgroup's candidates are the set bits of its own 64 units' bitmap words, so nothing has to be
+// located and nothing mapped back: stored values go to h[token][unit], zeros where a unit is no candidate (a ReLU
+// activation of zero never displaces a positive one; the selection asks the bitmap where zeros are selected).
+// Otherwise (the classifier: the union is a small part of a long vocabulary): the candidates with ranks 64 i .. in the
+// union bitmap (or list), values go to h[token][rank].
+//
+// Bound: HBM; one workgroup per compute unit keeps 48 KB of rows in flight.  Measured at d = 2048: 16 tokens, 15900
+// candidates (65 MB) 17.6 us, 64 tokens, 16384 candidates 19.9 us, 4 tokens, 9750 candidates (40 MB) 14.1 us (whole
+// kernels in a step: 3.7, 3.4 and 2.8 TB/s).  The kernel before this one staged through registers and located its
+// candidates by rank: 22.4 us at 16 tokens, 30 at 64; four tokens took 18.2 us on the fp64 matrix cores.
+constexpr int kFtRows = 64;        // candidates per workgroup
+constexpr int kFtChunks = 16;      // 16-byte chunks of a row per stage
+constexpr int kFtStages = 4;
+constexpr int kFtRowBytes = 16 * kFtChunks;
+constexpr int kFtSteps = kFtChunks / 4;  // MFMA steps per stage
+constexpr int ft_stage_bytes(int TT) { return (kFtRows + 16 * TT) * kFtRowBytes; }
 
-constexpr int kWaveLocateWords = 512;
-
-// The indices of the set bits with ranks [r0, r0 + R) of a bitmap of at most 512 words, found by one wave on its
-// own (lane l holds words 8 l .. 8 l + 7, requested by issue()): no barrier, so loads issued after the bitmap's
-// stay in flight meanwhile.  out[r - r0] receives the index of rank r (this wave's LDS); returns the number of set bits.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Asynchronous load of 16 bytes per lane into LDS: lane l's go to lds_off + 16 l.  Not tracked by the compiler: the
+// barrier below waits for it.
+__device__ __forceinline__ void load_to_lds(const void* g, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_off) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+// Workgroup barrier behind which everything but this wave's N youngest loads has arrived and every LDS read of the
+// workgroup is done.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+// The same for `stages` (uniform, at most kFtStages - 2) whole stages of CI or fewer candidate and TI token loads.
+template <int CI, int TI>
+__device__ __forceinline__ void stage_barrier_loads(int ci, bool whole) {
+  if (!whole) {
+    stage_barrier<0>();
+  } else if constexpr (CI == 1) {
+    stage_barrier<(kFtStages - 2) * (1 + TI)>();
+  } else {
+    if (ci >= CI) stage_barrier<(kFtStages - 2) * (CI + TI)>();
+    else stage_barrier_loads<CI - 1, TI>(ci, true);
+  }
 }
 
-struct WaveBitmap {
-  uint4 lo, hi;
-  __device__ __forceinline__ void issue(const uint32_t* __restrict__ bitmap, int words) {
-    const uint4* b4 = reinterpret_cast<const uint4*>(bitmap);
-    const int last_vec = (words - 1) / 4, lane = lane_id();
-    lo = b4[min(2 * lane, last_vec)];
-    hi = b4[min(2 * lane + 1, last_vec)];
-  }
-};
-__device__ __forceinline__ int wave_locate(const WaveBitmap& wb, int words, int r0, int R, int32_t* out) {
-  const int lane = lane_id();
-  const uint4 lo = wb.lo, hi = wb.hi;
-  uint32_t m[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-  int c = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    m[i] = 8 * lane + i < words ? m[i] : 0u;  // clamped loads repeat words, the last vector may reach past the bitmap
-    c += __popc(m[i]);
-  }
-  const int incl = wave_scan_incl(c);
-  const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-  // lane j resolves rank r0 + j (R <= 64): the lane that holds it by bisection over the lanes' running counts, the
-  // word among that lane's eight, the bit inside the word by bisection over its halves
-  const int r = r0 + lane;
-  int lo_l = 0, hi_l = kWave - 1;
-#pragma unroll
-  for (int st = 0; st < 6; ++st) {
-    const int mid = (lo_l + hi_l) >> 1;
-    const int v = __shfl(incl, mid);
-    if (v > r) hi_l = mid;
-    else lo_l = mid + 1;
-  }
-  const int owner = min(lo_l, kWave - 1);
-  int rem = r - __shfl(incl - c, owner);  // which of the owner's bits
-  uint32_t word = 0u;
-  int widx = 0;
-  bool found = false;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t wi = (uint32_t)__shfl((int)m[i], owner);
-    const int pc = __popc(wi);
-    if (!found && rem < pc) {
-      word = wi;
-      widx = i;
-      found = true;
-    }
-    if (!found) rem -= pc;
-  }
-  int pos = 0;
-#pragma unroll
-  for (int sh = 16; sh >= 1; sh >>= 1) {
-    const int below = __popc(word & (((1u << sh) - 1u) << pos));
-    if (rem >= below) {
-      rem -= below;
-      pos += sh;
-    }
-  }
-  if (lane < R && r < total && found) out[lane] = (8 * owner + widx) * 32 + pos;
-  wave_lds_fence();
-  return total;
-}
-
-// Operands pass through LDS: a lane of the matrix cores wants 16 bytes of each of 16 different rows, which as a
-// global load touches 16 cache lines per quarter wave; instead every load instruction brings 1 KiB of one row
-// (lane l its chunk l) and an LDS slab of 16 rows (row stride 1040 bytes: conflict-free 16-byte reads down a
-// column) turns them round.  A workgroup of NWV waves owns 16 NWV candidates, 16 per wave, and all of the batch's
-// tokens (TT tiles of 16); K goes by in passes of 64 chunks (512 elements).  Per pass the waves stage the tokens' slab
-// together; every wave stages its own candidates' slab, whose loads for the next pass are requested before the
-// matrix cores start on this one, so that candidate rows are in flight all the time.  The barriers between the
-// phases wait for LDS only, not for those loads.
-constexpr int kSlabChunks = 64;                          // 16-byte chunks of a row per pass: one per lane
-constexpr int kSlabRowBytes = kSlabChunks * 16 + 16;     // padded
-constexpr int kSlabBytes = 16 * kSlabRowBytes;           // 16 rows
-constexpr int kSlabSteps = kSlabChunks / 4;              // MFMA steps per pass
-static_assert(sizeof(SelSharedT<256>) <= 4 * (size_t)kSlabBytes, "the long-bitmap search borrows the slabs' memory");
-
-// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-template <int TT, int NWV, int TSPLIT, bool RELU>
-__global__ __launch_bounds__(64 * NWV * TSPLIT) void k_gather_dot_bf16(const uint16_t* __restrict__ W, const uint16_t* __restrict__ x,
-                                                         int B, int d, const int32_t* __restrict__ list, int n_host,
-                                                         const int32_t* __restrict__ n_dev, int n_cap,
-                                                         float* __restrict__ h, long long stride_h, GatherUnion un,
-                                                         float* __restrict__ xnorm, uint32_t* __restrict__ wnorm_max,
-                                                         float err_c) {
-  // NWV groups of 16 candidates, each shared by TSPLIT waves that take TT / TSPLIT of the token tiles (and
-  // 16 / TSPLIT of the group's rows when its slab is staged)
-  constexpr int NW = NWV * TSPLIT, TTW = TT / TSPLIT, RPW = 16 / TSPLIT;
-  static_assert(TT <= NWV && 16 * TT % NW == 0 && TT % TSPLIT == 0 && 16 % TSPLIT == 0,
-                "one wave per token tile for the norms, equal shares of the tokens' and candidates' rows");
-  constexpr int kTile = 16 * NWV;  // candidates of the workgroup
-  extern __shared__ __align__(16) unsigned char lds[];  // NWV candidate slabs (one per wave), then TT token slabs
+template <int TT, int TG, bool UNIT>
+__global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __restrict__ W, const uint16_t* __restrict__ x,
+                                                          int B, int d, const int32_t* __restrict__ list,
+                                                          const int32_t* __restrict__ n_dev, int n_cap,
+                                                          float* __restrict__ h, long long stride_h, GatherUnion un,
+                                                          float* __restrict__ xnorm, float* __restrict__ wnorm_tiles,
+                                                          uint32_t* __restrict__ wnorm_max, float err_c) {
+  constexpr int NW = 4 * TG, NT = 64 * NW, TTW = TT / TG;
+  constexpr int CI = kFtRows / (4 * NW), TI = 16 * TT / (4 * NW);  // load instructions per wave and stage
+  constexpr int kStage = ft_stage_bytes(TT);
+  constexpr int kSegSteps = filter_segment_steps(16 * TT);  // MFMA steps per fp32 segment
+  static_assert(TT % TG == 0 && CI >= 1 && TI >= 1 && 4 * TI * NW == 16 * TT && kFtSteps % kSegSteps == 0, "equal shares");
+  static_assert(TT <= NW && kFtRows * 16 * TT * 4 <= kFtStages * kStage, "the result tile reuses the stages' memory");
+  extern __shared__ __align__(16) unsigned char lds[];
+  __shared__ int32_t rows_sh[kFtRows];
   __shared__ float xsq[TT][16];
   __shared__ float wmx[NW];
-  __shared__ int32_t rows_sh[kTile];  // the tile's candidates
-  __shared__ int n_sh;
-  const int tile = (int)blockIdx.x;
-  const int lane = lane_id(), jl = lane & 15, g = lane >> 4;
+  const int tid = (int)threadIdx.x, lane = lane_id(), jl = lane & 15, g = lane >> 4;
   // known to be uniform: a matrix-core instruction must never sit behind a branch that is lowered to lane masking
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int e0 = tile * kTile;
-  const int cpr = d / 8;  // 16-byte chunks per row
-  HIRE_TS_BOTH(55);
-  // The tile's candidates: wave 0 finds them in a short bitmap on its own, a long bitmap takes the whole
-  // workgroup, a list is read.
-  const bool in_wave = un.bitmap != nullptr && un.words <= kWaveLocateWords;
-  if (in_wave) {
-    if (w == 0) {
-      WaveBitmap wb;
-      wb.issue(un.bitmap, un.words);
-      const int total = wave_locate(wb, un.words, e0, kTile, rows_sh);
-      if (lane == 0) n_sh = total;
+  const int tile = (int)blockIdx.x;
+  const int e0 = tile * kFtRows;  // first unit (UNIT) or rank of the workgroup
+  const int cpr = d / 8;          // 16-byte chunks per row
+  HIRE_TS(55);
+  int c;  // candidates of the workgroup
+  if constexpr (UNIT) {
+    uint64_t m;
+    if (un.bitmap != nullptr) {
+      m = reinterpret_cast<const uint64_t*>(un.bitmap)[tile];  // padded to whole 64-bit words, no bits past the rows
+    } else {  // every row below the count
+      const int left = min(*n_dev, n_cap) - e0;
+      m = left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
     }
-  } else if (un.bitmap != nullptr) {
-    const int total = union_locate<64 * NW>(un.bitmap, un.words, *reinterpret_cast<SelSharedT<64 * NW>*>(lds), e0, kTile, rows_sh);
-    if (threadIdx.x == 0) n_sh = total;
+    m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    c = __popcll(m);
+    if (w == 0 && ((m >> lane) & 1ull)) rows_sh[mask_prefix(m)] = e0 + lane;
+    __syncthreads();
   } else {
-    const int total = n_dev ? *n_dev : n_host;
-    const int t = (int)threadIdx.x;
-    if (t < kTile) rows_sh[t] = list != nullptr ? list[min(e0 + t, max(min(total, n_cap), 1) - 1)] : e0 + t;
-    if (t == 0) n_sh = total;
+    int n;
+    if (un.bitmap != nullptr) {
+      n = min(union_locate<NT>(un.bitmap, un.words, *reinterpret_cast<SelSharedT<NT>*>(lds), e0, kFtRows, rows_sh), n_cap);
+      if (tile == 0) publish_union(un, n);
+      if (tid < kFtRows && e0 + tid < n) un.list_out[e0 + tid] = rows_sh[tid];
+    } else {
+      n = min(*n_dev, n_cap);
+      if (tid < kFtRows) rows_sh[tid] = list[min(e0 + tid, max(n, 1) - 1)];
+      __syncthreads();
+    }
+    c = min(n - e0, kFtRows);
+    if (c <= 0) {  // uniform over the workgroup
+      if (tid == 0 && wnorm_tiles != nullptr) wnorm_tiles[tile] = 0.0f;
+      return;
+    }
   }
-  __syncthreads();
-  const int n = min(n_sh, n_cap);
-  if (un.bitmap != nullptr) {
-    if (tile == 0) publish_union(un, n);
-    const int t = (int)threadIdx.x;
-    if (t < kTile && e0 + t < n) un.list_out[e0 + t] = rows_sh[t];
-  }
-  HIRE_TS_BOTH(56);
-  if (e0 >= n) return;  // uniform over the workgroup
-  const int cw = w % NWV, tsp = w / NWV;  // candidate group, share of the token tiles (uniform)
-  const int tt0 = tsp * TTW;
-  unsigned char* wslab = lds + cw * kSlabBytes;
-  unsigned char* xslab = lds + NWV * kSlabBytes;
-  const unsigned char* wcol = wslab + jl * kSlabRowBytes + 16 * g;  // this lane's operand of step u: + 64 u
-  const unsigned char* xcol = xslab + jl * kSlabRowBytes + 16 * g;  // ... of token tile tt: + tt * kSlabBytes
+  HIRE_TS(56);
+  const int cw = w & 3, tt0 = (w >> 2) * TTW;  // this wave's candidate group and first token tile
   double acc[TTW][4];
 #pragma unroll
-  for (int tt = 0; tt < TTW; ++tt)
+  for (int t = 0; t < TTW; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[tt][r] = 0.0;
+    for (int r = 0; r < 4; ++r) acc[t][r] = 0.0;
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  f32x4 accw = zero, accx = zero;  // rows times rows (this wave's 16), tokens times tokens (one tile, for some waves)
-  // A pass's operands in registers: this wave's 16 candidate rows (one register per row) and its share of the
-  // tokens' rows (rows w, w + NWV, ... of the 16 TT; tokens past the batch are zeros), all requested together.
-  // DEPTH such sets are in flight; with many token tiles (little register space, long matrix-core phases) the
-  // tokens are requested at the start of their own pass instead.
-  constexpr int DEPTH = TTW <= 2 ? 2 : 1;
-  constexpr bool kTokensAhead = TTW <= 2;
-  constexpr int kLdsBatch = TTW == 1 ? 4 : 2;
-  constexpr int kSegSteps = filter_segment_steps(16 * TT);
-  static_assert(kLdsBatch % kSegSteps == 0 && kSlabSteps % kLdsBatch == 0, "whole segments per batch");
-  struct Operands {
-    uint4 wv[RPW];
-    uint4 xv[16 * TT / NW];
-  };
-  auto request_tokens = [&](int cs, Operands& o) {
-    const int nch = min(kSlabChunks, cpr - cs);
+  f32x4 accw = zero, accx[TTW];  // rows times rows; tokens times tokens (group 0's waves, which always have candidates)
 #pragma unroll
-    for (int i = 0; i < 16 * TT / NW; ++i) {
-      const int row = w + NW * i;
-      o.xv[i] = make_uint4(0, 0, 0, 0);
-      if (lane < nch && row < B) o.xv[i] = reinterpret_cast<const uint4*>(x + (size_t)row * d)[cs + lane];
-    }
-  };
-  auto request = [&](int cs, Operands& o) {
-    const int nch = min(kSlabChunks, cpr - cs);
+  for (int t = 0; t < TTW; ++t) accx[t] = zero;
+  if (c > 0) {
+    const uint32_t base = lds_offset(lds);
+    const int nst = (cpr + kFtChunks - 1) / kFtChunks;
+    const int ci = (c + 4 * NW - 1) / (4 * NW);  // candidate loads of a stage: groups without candidates are left out
+    // instruction i of this wave fills rows 4 NW i + 4 w .. + 3 of the candidates' (tokens') part of a stage
+    const char* wptr[CI];
+    const char* xptr[TI];
+    const int r4 = 4 * w + g, ch = jl ^ (r4 & 15);  // lane's row inside an instruction's stripe, its chunk of a stage
+    static_assert(4 * NW % 16 == 0, "a lane's chunk is the same for all of its instructions");
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-      o.wv[r] = make_uint4(0, 0, 0, 0);
-      const int cand = __builtin_amdgcn_readfirstlane(rows_sh[min(e0 + 16 * cw + tsp * RPW + r, n - 1) - e0]);  // scalar address
-      if (lane < nch) o.wv[r] = reinterpret_cast<const uint4*>(W + (size_t)cand * d)[cs + lane];
-    }
-    if (kTokensAhead) request_tokens(cs, o);
-  };
-  // One pass: the operands go to LDS, their registers are asked to fetch the pass DEPTH further on, the matrix
-  // cores work.
-  auto run_pass = [&](int cs, Operands& o) {
-    const int nch = min(kSlabChunks, cpr - cs), steps = (nch + 3) / 4;  // uniform
-    [[maybe_unused]] const int ts0 = 1 + 6 * min(cs / kSlabChunks, 7);  // profiling build: six stamps per pass
-    HIRE_TS(ts0);
-    if (!kTokensAhead) request_tokens(cs, o);
+    for (int i = 0; i < CI; ++i)
+      wptr[i] = reinterpret_cast<const char*>(W + (size_t)rows_sh[min(4 * NW * i + r4, c - 1)] * d);
 #pragma unroll
-    for (int i = 0; i < 16 * TT / NW; ++i)
-      *reinterpret_cast<uint4*>(xslab + (w + NW * i) * kSlabRowBytes + 16 * lane) = o.xv[i];
-    HIRE_TS(ts0 + 1);
+    for (int i = 0; i < TI; ++i) xptr[i] = reinterpret_cast<const char*>(x + (size_t)min(4 * NW * i + r4, B - 1) * d);
+    auto request = [&](int st, int slot) {
+      const int at = kFtChunks * st + ch;
+      const int off = 16 * (at < cpr ? at : 0);  // past the row's end: its first chunk, masked when it is used
+      const uint32_t to = base + slot * kStage + 1024 * w;
 #pragma unroll
-    for (int r = 0; r < RPW; ++r)
-      *reinterpret_cast<uint4*>(wslab + (tsp * RPW + r) * kSlabRowBytes + 16 * lane) = o.wv[r];
-    HIRE_TS(ts0 + 2);
-    if (cs + DEPTH * kSlabChunks < cpr) request(cs + DEPTH * kSlabChunks, o);  // in flight while the matrix cores work
-    lds_barrier();
-    HIRE_TS(ts0 + 3);
-    // operands come from LDS kLdsBatch steps at a time: one wait for their latency, not one per step
+      for (int i = 0; i < CI; ++i)
+        if (i < ci) load_to_lds(wptr[i] + off, to + 1024 * NW * i);
 #pragma unroll
-    for (int u0 = 0; u0 < kSlabSteps; u0 += kLdsBatch) {
-      if (u0 < steps) {  // uniform; steps past the row's end inside a batch multiply zeros
-        bf16x8 wk[kLdsBatch], tk[TTW][kLdsBatch];
+      for (int i = 0; i < TI; ++i) load_to_lds(xptr[i] + off, to + kFtRows * kFtRowBytes + 1024 * NW * i);
+    };
 #pragma unroll
-        for (int v = 0; v < kLdsBatch; ++v) {
-          wk[v] = as_bf16x8(*reinterpret_cast<const uint4*>(wcol + 64 * (u0 + v)));
+    for (int st = 0; st < kFtStages - 1; ++st)
+      if (st < nst) request(st, st);
+    int slot = 0;
+    for (int st = 0; st < nst; ++st) {
+      stage_barrier_loads<CI, TI>(ci, st + kFtStages - 2 < nst);
+      if (st + kFtStages - 1 < nst) request(st + kFtStages - 1, slot == 0 ? kFtStages - 1 : slot - 1);
+      if (16 * cw < c) {  // uniform
+        const unsigned char* wcol = lds + slot * kStage + (16 * cw + jl) * kFtRowBytes;
+        const unsigned char* xcol = lds + slot * kStage + (kFtRows + 16 * tt0 + jl) * kFtRowBytes;
+        const int left = cpr - kFtChunks * st;  // chunks of the row from this stage on
+        bf16x8 wk[kFtSteps], tk[TTW][kFtSteps];
 #pragma unroll
-          for (int tt = 0; tt < TTW; ++tt)
-            tk[tt][v] = as_bf16x8(*reinterpret_cast<const uint4*>(xcol + (tt0 + tt) * kSlabBytes + 64 * (u0 + v)));
+        for (int u = 0; u < kFtSteps; ++u) {
+          const int o = ((4 * u + g) ^ jl) * 16;
+          wk[u] = as_bf16x8(*reinterpret_cast<const uint4*>(wcol + o));
+#pragma unroll
+          for (int t = 0; t < TTW; ++t) tk[t][u] = as_bf16x8(*reinterpret_cast<const uint4*>(xcol + t * 16 * kFtRowBytes + o));
         }
-        // kSegSteps steps (32 products each) per fp32 segment; the segments of a batch are started side by side so
-        // that no matrix-core instruction waits for the one issued just before it
-        constexpr int kSeg = kLdsBatch / kSegSteps;
+        if (left < kFtChunks) {  // uniform: the row ends inside the stage
 #pragma unroll
-        for (int v = 0; v < kLdsBatch; ++v) accw = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wk[v], wk[v], accw, 0, 0, 0);
+          for (int u = 0; u < kFtSteps; ++u)
+            if (4 * u + g >= left) {
+              wk[u] = as_bf16x8(make_uint4(0, 0, 0, 0));
+#pragma unroll
+              for (int t = 0; t < TTW; ++t) tk[t][u] = as_bf16x8(make_uint4(0, 0, 0, 0));
+            }
+        }
+        constexpr int kSeg = kFtSteps / kSegSteps;
         f32x4 part[TTW][kSeg];
 #pragma unroll
-        for (int tt = 0; tt < TTW; ++tt)
+        for (int v = 0; v < kSegSteps; ++v)
 #pragma unroll
-          for (int q = 0; q < kSeg; ++q)
-            part[tt][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[tt][kSegSteps * q], wk[kSegSteps * q], zero, 0, 0, 0);
-#pragma unroll
-        for (int st = 1; st < kSegSteps; ++st)
-#pragma unroll
-          for (int tt = 0; tt < TTW; ++tt)
+          for (int t = 0; t < TTW; ++t)
 #pragma unroll
             for (int q = 0; q < kSeg; ++q)
-              part[tt][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[tt][kSegSteps * q + st], wk[kSegSteps * q + st],
-                                                                    part[tt][q], 0, 0, 0);
+              part[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[t][kSegSteps * q + v], wk[kSegSteps * q + v],
+                                                                   v == 0 ? zero : part[t][q], 0, 0, 0);
+        if (tt0 == 0) {  // uniform
 #pragma unroll
-        for (int tt = 0; tt < TTW; ++tt) {
-          if ((tt0 + tt) % NWV == cw) {  // uniform: token tile t's norms are formed by the wave of group t % NWV that has it
+          for (int u = 0; u < kFtSteps; ++u) accw = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wk[u], wk[u], accw, 0, 0, 0);
+        }
 #pragma unroll
-            for (int v = 0; v < kLdsBatch; ++v)
-              accx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[tt][v], tk[tt][v], accx, 0, 0, 0);
+        for (int t = 0; t < TTW; ++t) {
+          if (cw == 0) {  // uniform
+#pragma unroll
+            for (int u = 0; u < kFtSteps; ++u)
+              accx[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[t][u], tk[t][u], accx[t], 0, 0, 0);
           }
 #pragma unroll
           for (int q = 0; q < kSeg; ++q)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[tt][r] += (double)part[tt][q][r];
+            for (int r = 0; r < 4; ++r) acc[t][r] += (double)part[t][q][r];
         }
       }
+      slot = slot == kFtStages - 1 ? 0 : slot + 1;
     }
-    HIRE_TS(ts0 + 4);
-    lds_barrier();  // the slabs are read before they are filled again
-    HIRE_TS(ts0 + 5);
-  };
-  Operands op[DEPTH];
-#pragma unroll
-  for (int q = 0; q < DEPTH; ++q)
-    if (q * kSlabChunks < cpr) request(q * kSlabChunks, op[q]);
-#pragma nounroll
-  for (int cs = 0; cs < cpr; cs += DEPTH * kSlabChunks) {
-#pragma unroll
-    for (int q = 0; q < DEPTH; ++q)
-      if (cs + q * kSlabChunks < cpr) run_pass(cs + q * kSlabChunks, op[q]);  // uniform
   }
-  HIRE_TS_BOTH(57);
+  HIRE_TS(57);
   // entry (i, i) of a 16 x 16 result sits in value i % 4 of lane 16 (i / 4) + i
   const float up = 1.0f + (float)d * 0x1p-22f;  // more than the relative error of the norms' sums
-  if (cw < TT && cw / TTW == tsp && (jl >> 2) == g) xsq[cw][jl] = pick4(accx, jl & 3);
-  float wn2 = (jl >> 2) == g ? pick4(accw, jl & 3) : 0.0f;  // |u_jl|^2 sits in lane 16 (jl / 4) + jl: to all four
-  wn2 = fmaxf(wn2, __shfl_xor(wn2, 16));
-  wn2 = fmaxf(wn2, __shfl_xor(wn2, 32));
-  const float wnorm = sqrtf(wn2 * up) * 1.0001f;
-  const int t_idx = e0 + 16 * cw + jl;
-  {
-    float m = t_idx < n ? wnorm : 0.0f;
+  if (cw == 0 && (jl >> 2) == g) {
+#pragma unroll
+    for (int t = 0; t < TTW; ++t) xsq[tt0 + t][jl] = pick4(accx[t], jl & 3);
+  }
+  // |u_jl|^2, formed by the group's wave of the first share: to all four lanes of the candidate, through LDS to the
+  // other shares
+  float* wsq = reinterpret_cast<float*>(lds) + 16 * TT * kFtRows;  // [64] behind the result tile
+  static_assert((16 * TT + 1) * kFtRows * 4 <= kFtStages * kStage, "result tile and norms");
+  __syncthreads();  // the stages' memory is free
+  if (tt0 == 0 && (jl >> 2) == g) wsq[16 * cw + jl] = pick4(accw, jl & 3);
+  float* tile_out = reinterpret_cast<float*>(lds);  // [16 TT][64]
+  if constexpr (UNIT) {
+    for (int i = tid; i < 16 * TT * kFtRows / 4; i += NT) reinterpret_cast<float4*>(tile_out)[i] = make_float4(0, 0, 0, 0);
+  }
+  __syncthreads();
+  const float wnorm = sqrtf(wsq[16 * cw + jl] * up) * 1.0001f;
+  const int ce = 16 * cw + jl;  // this lane's candidate
+  if (tt0 == 0) {
+    float m = ce < c ? wnorm : 0.0f;
     m = fmaxf(m, __shfl_xor(m, 1));
     m = fmaxf(m, __shfl_xor(m, 2));
     m = fmaxf(m, __shfl_xor(m, 4));
     m = fmaxf(m, __shfl_xor(m, 8));
-    if (lane == 0) wmx[w] = m;
+    if (lane == 0) wmx[cw] = m;
   }
-  __syncthreads();
-  // what the maximum holds so far: requested before the stores below, looked at after them (and after the
-  // barrier, which would wait for it)
-  uint32_t seen_max = 0u;
-  if (w == 0 && lane == 0) seen_max = *reinterpret_cast<volatile uint32_t*>(wnorm_max);
 #pragma unroll
-  for (int tt = 0; tt < TTW; ++tt)
+  for (int t = 0; t < TTW; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int tl = 4 * g + r, tk = 16 * (tt0 + tt) + tl;
-      const float xnrm = sqrtf(xsq[tt0 + tt][tl] * up) * 1.0001f;
-      const double s = acc[tt][r];
-      const double delta = (double)(err_c * wnorm * xnrm);
-      const float tiny = __uint_as_float(1u);  // the smallest positive float
+      const int tl = 4 * g + r, tk = 16 * (tt0 + t) + tl;
+      const double s = acc[t][r];
       float v = (float)s;  // phi = identity (the classifier): the sum itself
-      if constexpr (RELU) {
+      if constexpr (UNIT) {
+        const float xnrm = sqrtf(xsq[tt0 + t][tl] * up) * 1.0001f;
+        const double delta = (double)(err_c * wnorm * xnrm);
+        const float tiny = __uint_as_float(1u);  // the smallest positive float
         v = 0.0f;
         if (s > 0.0) v = fmaxf((float)s, tiny);
         else if (s > -2.0 * delta) v = tiny;  // the true activation may still be positive
+        if (ce < c) tile_out[tk * kFtRows + rows_sh[ce] - e0] = v;
+      } else {
+        if (tk < B && ce < c) h[(size_t)tk * stride_h + e0 + ce] = v;
       }
-      if (tk < B && t_idx < n) h[(size_t)tk * stride_h + t_idx] = v;
     }
-  if (w == 0) {  // one atomic per workgroup at most
-    float m = wmx[0];
-#pragma unroll
-    for (int q = 1; q < NW; ++q) m = fmaxf(m, wmx[q]);
-    // most workgroups found a maximum at least as large already there and skip the atomic
-    if (lane == 0 && __float_as_uint(m) > seen_max) atomicMax(wnorm_max, __float_as_uint(m));
+  __syncthreads();
+  if constexpr (UNIT) {  // 64 units of every token, 16 bytes per lane where the rows are aligned
+    if (stride_h % 4 == 0) {
+      for (int i = tid; i < B * (kFtRows / 4); i += NT) {
+        const int t = i / (kFtRows / 4), q = 4 * (i % (kFtRows / 4));
+        if (e0 + q < stride_h) *reinterpret_cast<float4*>(h + (size_t)t * stride_h + e0 + q) = *reinterpret_cast<float4*>(tile_out + 4 * i);
+      }
+    } else {
+      for (int i = tid; i < B * kFtRows; i += NT) {
+        const int t = i / kFtRows, q = i % kFtRows;
+        if (e0 + q < stride_h) h[(size_t)t * stride_h + e0 + q] = tile_out[i];
+      }
+    }
   }
-  if (tile == 0 && w == 0) {
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-      if (lane < 16 && 16 * tt + lane < B) xnorm[16 * tt + lane] = sqrtf(xsq[tt][lane] * up) * 1.0001f;
+  if (tid == 0) {  // a place per workgroup: 256 atomics on one address at the kernel's end took 7 us
+    const float m = c > 0 ? fmaxf(fmaxf(wmx[0], wmx[1]), fmaxf(wmx[2], wmx[3])) : 0.0f;
+    if (wnorm_tiles != nullptr) wnorm_tiles[tile] = m;
+    else atomicMax(wnorm_max, __float_as_uint(m));
   }
-  HIRE_TS_BOTH(58);
+  if (c <= 0) return;
+  if (UNIT || tile == 0)  // UNIT: the same values from every workgroup that has candidates
+    for (int t = tid; t < B; t += NT) xnorm[t] = sqrtf(xsq[t / 16][t % 16] * up) * 1.0001f;
+  HIRE_TS(58);
 }
 
 static int gather_mfma_tiles(int cap, int gs) { return max(1, (int)((((long long)cap << gs) + 15) / 16)); }
@@ -532,36 +472,42 @@ hipError_t launch_gather_dot_mfma(const uint16_t* W, const uint16_t* x, int B, i
                 u.bitmap ? nullptr : list, n, n_dev, cap, relu, h, stride_h, u, gs);
 }
 
-hipError_t launch_gather_dot_bf16(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
-                                  const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
-                                  const UnionRefs* un, int n_rows, int relu, float* xnorm, uint32_t* wnorm_max,
-                                  hipStream_t s) {
-  GatherUnion u = make_gather_union(un, hr, B);
-  u.words = min(u.words, (n_rows + 31) / 32);  // the bitmap's padding words hold no bits
-  if (B < 1 || B > 64) return hipErrorInvalidValue;
-  static std::atomic<size_t> raised_to[8] = {};
-  auto go = [&](auto kernel, int tt, int nwv, int tsplit, std::atomic<size_t>& raised) {
-    const size_t lds = (size_t)(nwv + tt) * kSlabBytes;
+int filter_tiles(int n) { return max(1, (n + kFtRows - 1) / kFtRows); }
+
+hipError_t launch_filter_bf16(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
+                              const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
+                              const UnionRefs* un, int n_rows, bool by_unit, float* xnorm, float* wnorm_tiles,
+                              uint32_t* wnorm_max, hipStream_t s) {
+  if (B < 1 || B > 64 || d % 8 != 0) return hipErrorInvalidValue;
+  GatherUnion u{};
+  int tiles = filter_tiles(n_cap);
+  if (by_unit && un != nullptr) {
+    u.bitmap = un->bitmap;
+    tiles = filter_tiles(n_rows);
+    if (un->words < 2 * tiles) return hipErrorInvalidValue;
+  } else if (!by_unit) {
+    u = make_gather_union(un, hr, B);
+    u.words = min(u.words, (n_rows + 31) / 32);  // the bitmap's padding words hold no bits
+    if (u.bitmap == nullptr && list == nullptr) return hipErrorInvalidValue;
+  }
+  static std::atomic<size_t> raised_to[6] = {};
+  auto go = [&](auto kernel, int tt, int tg, std::atomic<size_t>& raised) {
+    const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
       return e;
-    const int tile = 16 * nwv;
-    return launch(kernel, dim3(max(1, (n_cap + tile - 1) / tile)), dim3(64 * nwv * tsplit), lds, s, W, x, B, d,
-                  u.bitmap ? nullptr : list, 0, n_dev, n_cap, h, stride_h, u, xnorm, wnorm_max, gather_filter_error(B));
+    return launch(kernel, dim3(tiles), dim3(256 * tg), lds, s, W, x, B, d, list, n_dev, n_cap, h, stride_h, u, xnorm,
+                  wnorm_tiles, wnorm_max, gather_filter_error(B));
   };
-  // few tokens: small workgroups, so that every compute unit holds several and has enough loads in flight;
-  // beyond 32 tokens two waves share a group of candidates, two token tiles each: the fp64 additions that pace
-  // the passes are spread over twice the waves
-  const bool small = B <= 16 && (u.bitmap == nullptr || u.words <= kWaveLocateWords);
-  if (relu) {
-    if (small) return go(k_gather_dot_bf16<1, 2, 1, true>, 1, 2, 1, raised_to[0]);
-    if (B <= 16) return go(k_gather_dot_bf16<1, 4, 1, true>, 1, 4, 1, raised_to[1]);
-    if (B <= 32) return go(k_gather_dot_bf16<2, 4, 1, true>, 2, 4, 1, raised_to[2]);
-    return go(k_gather_dot_bf16<4, 4, 2, true>, 4, 4, 2, raised_to[3]);
+  // beyond 16 tokens two waves share a group of candidates, half of the token tiles each: the fp64 additions and
+  // the operand reads are spread over twice the waves
+  if (by_unit) {
+    if (B <= 16) return go(k_filter_bf16<1, 1, true>, 1, 1, raised_to[0]);
+    if (B <= 32) return go(k_filter_bf16<2, 2, true>, 2, 2, raised_to[1]);
+    return go(k_filter_bf16<4, 2, true>, 4, 2, raised_to[2]);
   }
-  if (small) return go(k_gather_dot_bf16<1, 2, 1, false>, 1, 2, 1, raised_to[4]);
-  if (B <= 16) return go(k_gather_dot_bf16<1, 4, 1, false>, 1, 4, 1, raised_to[5]);
-  if (B <= 32) return go(k_gather_dot_bf16<2, 4, 1, false>, 2, 4, 1, raised_to[6]);
-  return go(k_gather_dot_bf16<4, 4, 2, false>, 4, 4, 2, raised_to[7]);
+  if (B <= 16) return go(k_filter_bf16<1, 1, false>, 1, 1, raised_to[3]);
+  if (B <= 32) return go(k_filter_bf16<2, 2, false>, 2, 2, raised_to[4]);
+  return go(k_filter_bf16<4, 2, false>, 4, 2, raised_to[5]);
 }
 
 }  // namespace hire

@@ -46,9 +46,9 @@ constexpr size_t kPackTrailerBytes = 64;
 hipError_t launch_pack_int4(const uint16_t* w, int rows, int cols, uint32_t* q4, float* scale, hipStream_t s);
 hipError_t launch_unpack_int4(const uint32_t* q4, int rows, int cols, int8_t* codes, hipStream_t s);
 
-// x bf16 [B,d] -> xq int8 [B,d], sx fp32 [B]; also clears `zero_words` 32-bit words at zero_ptr.  As a step's
-// first kernel it checks the general header (optional) against the layout signature.
-hipError_t launch_quantize_tokens(const uint16_t* x, int B, int d, int8_t* xq, float* sx, uint32_t* zero_ptr,
+// x bf16 [B,d] -> xq int8 [B,d], sumabs fp32 [B] = sum |xq|; also clears `zero_words` 32-bit words at zero_ptr.  As
+// a step's first kernel it checks the general header (optional) against the layout signature.
+hipError_t launch_quantize_tokens(const uint16_t* x, int B, int d, int8_t* xq, float* sumabs, uint32_t* zero_ptr,
                                   int zero_words, void* general_header, unsigned long long sig, hipStream_t s);
 
 // One token (B == 1): keys[j] = phi(float(sum_i q[j,i] xq[i]) * scale[j]); acc (optional) gets the integer sums.
@@ -69,9 +69,9 @@ hipError_t launch_scorer_int4_fused(const uint32_t* q4, const float* scale, cons
 bool scorer_int4_fused_takes_f32(int d);
 int scorer_int4_fused_blocks(int N, int d);  // workgroups launch_scorer_int4_fused uses
 int scorer_int4_fused_maxima(int N, int d);  // maxima it leaves per token: one per workgroup, short rows one per wave
-// The same on the int8 matrix cores, for batches (scorer_mfma.hip); B <= 64.
+// The same on the int8 matrix cores, for batches (scorer_mfma.hip); B <= 64.  keys: [B, stride].
 hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
-                                   int relu, float* keys, int32_t* acc, const HistRefs& hr, hipStream_t s);
+                                   int relu, float* keys, long long stride, int32_t* acc, const HistRefs& hr, hipStream_t s);
 int scorer_mfma_blocks(int N);
 int scorer_mfma_maxima(int N);  // maxima it leaves per token: one per wave
 
@@ -111,17 +111,15 @@ struct SelectParams {
   float* prob_out;          // [B,k] softmax over the selected values (rank order only), optional
   uint32_t* bitmap;         // optional: bit i set (atomic or) for every selected position of any row
   uint32_t* window_misses;  // optional device counter: rows whose window histogram did not give the k-th largest
-  // Filter and refine (launch_select_refine only): vals are fp32 rows written by launch_gather_dot_bf16, within
-  // err_c |u| |x| of the activations; map lists the rows' units.  The kernel recomputes in fp64
-  // (relu(<refine_w[map[i], :], refine_x[b, :]>)) every non-zero entry within 2 * err_c * xnorm[b] * *wnorm_max of the
-  // k-th largest stored value and selects on the result.  refine_h [B, refine_h_stride]: fp64 scratch.
+  // Filter and refine (launch_softmax_refine only): vals are fp32 rows written by launch_filter_bf16, within
+  // err_c |u| |x| of the logits; map lists the rows' classes.  The kernel recomputes in fp64
+  // (<refine_w[map[i], :], refine_x[b, :]>) what can still be among the k largest.
   const uint16_t* refine_w;  // bf16 [rows, refine_d]
   const uint16_t* refine_x;  // bf16 [B, refine_d]
   int refine_d;
-  double* refine_h;
-  long long refine_h_stride;
   const float* xnorm;
-  const uint32_t* wnorm_max;
+  const float* wnorm_tiles;  // [wnorm_n]
+  int wnorm_n;
   float err_c;
   int nonneg;               // != 0: every value is known to be >= 0 (keys and activations after a ReLU); such rows
                             // of 1025..16384 entries in index order take a leaner kernel
@@ -148,10 +146,7 @@ size_t topk_long_workspace_bytes(int B, int N);
 hipError_t launch_topk_long(const float* scores, int B, int N, int k, int relu, int32_t* idx_out, float* val_out,
                             void* general_header, void* body, unsigned long long sig, hipStream_t s);
 hipError_t launch_select_f64(const SelectParams& p, int B, hipStream_t s);
-// Filter and refine: see SelectParams.  Rows of 1025..16384 fp32 entries, k <= 4096, 16-byte aligned rows.
-bool select_refine_supported(const SelectParams& p);
-hipError_t launch_select_refine(const SelectParams& p, int B, hipStream_t s);
-// The same for the classifier (phi = identity, signed values, rank order, softmax over the k survivors): every
+// Filter and refine for the classifier (phi = identity, signed values, rank order, softmax over the k survivors): every
 // entry within 2 * err_c * xnorm[b] * *wnorm_max below the k-th largest stored value is recomputed in fp64 and the k
 // largest of those are returned in rank order (idx_out through map, val_out, prob_out).  Rows of at most
 // kSoftmaxRefineMaxRow fp32 entries, k <= kSoftmaxRefineMaxK.
@@ -185,6 +180,37 @@ hipError_t launch_maxima_select(const float* keys, int B, int N, int sd, int kpr
 // Also clears zero_words words at zero_ptr (may be nullptr).
 hipError_t launch_bitmap_compact(const uint32_t* bitmap, int words, int32_t* list_out, int32_t* count_out,
                                  int32_t* count_out2, uint32_t* zero_ptr, int zero_words, hipStream_t s);
+
+// ---- batch_select.hip --------------------------------------------------------
+// The selections of a batched FFN step, one workgroup per token, rows of at most 32768 units, k <= 4096.
+bool batch_select_supported(int N, int k);
+// The k' largest keys of every row (non-negative fp32 rows of keys, stride a multiple of 4) -> bits of the union
+// bitmap.  sumabs[b], *smax: bound of token b's keys (launch_quantize_tokens, the trailer of the packed codes).
+hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
+                              const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s);
+// The k largest activations relu(<W[j, :], x_b>) of every token among the bitmap's units, ties to the lower unit, from
+// the filter stage's values in unit order (launch_filter_bf16 by_unit).
+constexpr int kRefineTokenMax = 8192;  // longest token staged in LDS
+struct RefineParams {
+  const float* vals;        // [B, stride], 16-byte aligned rows
+  long long stride;
+  int B, N, k, d;
+  const uint16_t* W;        // bf16 [N, d]
+  const uint16_t* x;        // bf16 [B, d]
+  const float* xnorm;       // [B], wnorm_tiles [wnorm_n], err_c: bounds of the values' error
+  const float* wnorm_tiles;
+  int wnorm_n;
+  float err_c;
+  const uint32_t* bitmap;   // the candidates; they are listed as well: ascending, and their number
+  int32_t* cand_out;        // optional
+  int32_t* n_cand_out;      // optional (with cand_out)
+  double* h64;              // [B, stride] scratch
+  int32_t* idx_out;         // optional [B, k] ascending
+  float* val_out;           // optional [B, k]
+  uint2* list_out;          // [B, k] (unit, value) for launch_w2_list
+  uint32_t* window_misses;  // optional counter: tokens that the histogram and the list in LDS did not settle
+};
+hipError_t launch_refine(const RefineParams& p, hipStream_t s);
 
 // Histogram-guided top-k' of every token's keys and their union, for keys whose producer has filled the
 // key histograms:
@@ -232,17 +258,22 @@ hipError_t launch_gather_dot_mfma(const uint16_t* W, const uint16_t* x, int B, i
                                   const int32_t* n_dev, int n_cap, int relu, double* h, long long stride_h,
                                   const HistRefs& hr, const UnionRefs* un, int gs, hipStream_t s);
 
-// Filter stage of the exact pre-activations for batches: h[b*stride_h + t] = a value within
-// gather_filter_error(B) * |u_{list[t]}| * |x_b| of relu(<u_{list[t]}, x_b>) (bf16 matrix cores, fp32 segments of 32 or 64 products;
-// see the kernel for what exactly is stored), xnorm[b] = |x_b|, *wnorm_max = max_t |u_{list[t]}| as float bits
-// (atomic max: cleared before the step).  n_dev / n_cap as above; rows only (no groups); n_rows: rows of W (what
-// the union bitmap spans).
+// Filter stage of the exact pre-activations for batches: values within gather_filter_error(B) * |u_j| * |x_b| of
+// phi(<u_j, x_b>) (bf16 matrix cores, fp32 segments of 32 or 64 products; see the kernel for what exactly is stored),
+// xnorm[b] = |x_b|, wnorm_tiles[filter_tiles(.)] = max |u_j| over the candidates of every workgroup (without it
+// *wnorm_max = the maximum over all as float bits, by atomics: cleared before).
+// by_unit (phi = ReLU): the candidates are the bits of un->bitmap (n_rows of them; without un: rows below *n_dev <=
+// n_cap), the value of unit j goes to h[b*stride_h + j], zeros where j is no candidate (also up to the stride,
+// which covers n_rows).
+// Otherwise (phi = identity): the candidate of rank t (of un's bitmap, or list with n_dev / n_cap) goes to
+// h[b*stride_h + t].  Rows only (no groups); n_rows: rows of W.
 constexpr int filter_segment_steps(int B) { return B > 32 ? 2 : 1; }  // 32-product MFMA steps per fp32 segment
 inline float gather_filter_error(int B) { return (float)filter_segment_steps(B) * 0x1p-17f; }
-hipError_t launch_gather_dot_bf16(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
-                                  const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
-                                  const UnionRefs* un, int n_rows, int relu, float* xnorm, uint32_t* wnorm_max,
-                                  hipStream_t s);
+hipError_t launch_filter_bf16(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
+                              const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
+                              const UnionRefs* un, int n_rows, bool by_unit, float* xnorm, float* wnorm_tiles,
+                              uint32_t* wnorm_max, hipStream_t s);
+int filter_tiles(int n);  // workgroups for n rows (by_unit) or candidates
 
 // out[b*stride_out + J] = sum_{l < 2^gs} |in[b*stride_in + J*2^gs + l]| for J < n, added in index order in the
 // input's type (the group activations of eq. (6)).

@@ -81,11 +81,12 @@ __global__ __launch_bounds__(256) void k_unpack_int4(const uint32_t* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Per-token int8 activations: one block per token.
+// Per-token int8 activations and the sum of their absolute values: one block per token.
 __global__ __launch_bounds__(256) void k_quantize_tokens(const uint16_t* __restrict__ x, int d, int8_t* __restrict__ xq,
-                                                         float* __restrict__ sx, uint32_t* zero_ptr, int zero_words,
+                                                         float* __restrict__ sumabs, uint32_t* zero_ptr, int zero_words,
                                                          GeneralHeader* gh, unsigned long long sig) {
   __shared__ float red[4];
+  __shared__ int isum[4];
   zero_slice(zero_ptr, zero_words);
   if (blockIdx.x == 0) general_header_check(gh, sig);
   const int b = (int)blockIdx.x;
@@ -101,10 +102,11 @@ __global__ __launch_bounds__(256) void k_quantize_tokens(const uint16_t* __restr
   amax = block_max_256(amax, red);
   float s = __fdiv_rn(amax, 127.0f);
   if (amax == 0.0f) s = 1.0f;
-  if (threadIdx.x == 0) sx[b] = s;
+  int sabs = 0;
   auto code = [&](float f) -> uint32_t {
     float r = rintf(__fdiv_rn(f, s));
     r = fminf(fmaxf(r, -127.0f), 127.0f);
+    sabs += (int)fabsf(r);
     return (uint32_t)((int)r) & 0xFFu;
   };
   for (int c = (int)threadIdx.x; c < chunks; c += 256) {
@@ -115,6 +117,10 @@ __global__ __launch_bounds__(256) void k_quantize_tokens(const uint16_t* __restr
     o.y = code(bf16_lo(w[2])) | code(bf16_hi(w[2])) << 8 | code(bf16_lo(w[3])) << 16 | code(bf16_hi(w[3])) << 24;
     reinterpret_cast<uint2*>(xq + (size_t)b * d)[c] = o;
   }
+  sabs = wave_sum(sabs);
+  if (lane_id() == 0) isum[wave_id()] = sabs;
+  __syncthreads();
+  if (threadIdx.x == 0) sumabs[b] = (float)(isum[0] + isum[1] + isum[2] + isum[3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -499,9 +505,9 @@ hipError_t launch_unpack_int4(const uint32_t* q4, int rows, int cols, int8_t* co
   return launch(k_unpack_int4, dim3(rows), dim3(256), 0, s, q4, cols, codes);
 }
 
-hipError_t launch_quantize_tokens(const uint16_t* x, int B, int d, int8_t* xq, float* sx, uint32_t* zero_ptr,
+hipError_t launch_quantize_tokens(const uint16_t* x, int B, int d, int8_t* xq, float* sumabs, uint32_t* zero_ptr,
                                   int zero_words, void* general_header, unsigned long long sig, hipStream_t s) {
-  return launch(k_quantize_tokens, dim3(B), dim3(256), 0, s, x, d, xq, sx, zero_ptr, zero_words,
+  return launch(k_quantize_tokens, dim3(B), dim3(256), 0, s, x, d, xq, sumabs, zero_ptr, zero_words,
                 static_cast<GeneralHeader*>(general_header), sig);
 }
 

@@ -29,7 +29,7 @@ template <int CT, int KI>
 __global__ __launch_bounds__(64 * kMfmaWaves) void k_scorer_int4_mfma(const uint4* __restrict__ q4,
                                                                       const float* __restrict__ scale,
                                                                       const int8_t* __restrict__ xq, int B, int N, int d,
-                                                                      int relu, float* __restrict__ keys,
+                                                                      int relu, float* __restrict__ keys, long long stride,
                                                                       int32_t* __restrict__ acc_out, MultiRegion mr) {
   constexpr int kTok = 16 * CT;
   constexpr int kSegQ = KI * 8;        // uint4 (16 int8) per token and segment
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void k_scorer_int4_mfma(const uint
           float key = (float)sum * sj;
           if (relu) key = key > 0.0f ? key : 0.0f;
           if (key == 0.0f) key = 0.0f;
-          keys[(size_t)t * N + j] = key;
+          keys[(size_t)t * stride + j] = key;
           if (acc_out) acc_out[(size_t)t * N + j] = sum;
           const uint32_t ok = order_key(key);
           wmax[ct][r] = ok > wmax[ct][r] ? ok : wmax[ct][r];
@@ -162,33 +162,33 @@ static_assert(kMfmaWaves * 768 <= kWgMaxSlots, "one maximum slot per wave of the
 
 template <int CT, int KI>
 static hipError_t scorer_mfma_launch(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
-                                     int relu, float* keys, int32_t* acc, const MultiRegion& mr, hipStream_t s) {
+                                     int relu, float* keys, long long stride, int32_t* acc, const MultiRegion& mr, hipStream_t s) {
   const size_t lds = (size_t)16 * CT * (KI * 8 + 1) * sizeof(uint4);
   auto kernel = k_scorer_int4_mfma<CT, KI>;
   static std::atomic<size_t> raised_to{0};
   if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to); e != hipSuccess)
     return e;
   return launch(kernel, dim3(scorer_mfma_blocks(N)), dim3(64 * kMfmaWaves), lds, s,
-                reinterpret_cast<const uint4*>(q4), scale, xq, B, N, d, relu, keys, acc, mr);
+                reinterpret_cast<const uint4*>(q4), scale, xq, B, N, d, relu, keys, stride, acc, mr);
 }
 
 hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
-                                   int relu, float* keys, int32_t* acc, const HistRefs& hr, hipStream_t s) {
+                                   int relu, float* keys, long long stride, int32_t* acc, const HistRefs& hr, hipStream_t s) {
   MultiRegion mr = multi_of(hr, B);
   if (!multi_producer_counts(N, B)) mr.hist = nullptr;  // then the selection counts in a pass of its own
   if (d <= 128) {  // short rows (the int4 low-rank scorer's second product): K segments no longer than a row
-    if (B <= 16) return scorer_mfma_launch<1, 1>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-    if (B <= 32) return scorer_mfma_launch<2, 1>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-    return scorer_mfma_launch<4, 1>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
+    if (B <= 16) return scorer_mfma_launch<1, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+    if (B <= 32) return scorer_mfma_launch<2, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+    return scorer_mfma_launch<4, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
   }
   if (d <= 512) {
-    if (B <= 16) return scorer_mfma_launch<1, 4>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-    if (B <= 32) return scorer_mfma_launch<2, 4>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-    return scorer_mfma_launch<4, 4>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
+    if (B <= 16) return scorer_mfma_launch<1, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+    if (B <= 32) return scorer_mfma_launch<2, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+    return scorer_mfma_launch<4, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
   }
-  if (B <= 16) return scorer_mfma_launch<1, 16>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-  if (B <= 32) return scorer_mfma_launch<2, 16>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
-  return scorer_mfma_launch<4, 16>(q4, scale, xq, B, N, d, relu, keys, acc, mr, s);
+  if (B <= 16) return scorer_mfma_launch<1, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+  if (B <= 32) return scorer_mfma_launch<2, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+  return scorer_mfma_launch<4, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
 }
 
 }  // namespace hire

@@ -300,4 +300,29 @@ __device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap,
   return total;
 }
 
+// The set bits of a bitmap as an ascending list, by one workgroup (NT threads, words <= 16 NT).
+template <int NT>
+__device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, int words, int32_t* __restrict__ out,
+                                           SelSharedT<NT>& sh) {
+  const int tid = (int)threadIdx.x;
+  int base = 0;
+  for (int w0 = 0; w0 < words; w0 += NT * 4) {
+    uint32_t m[4];
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t v = bitmap[min(w0 + tid * 4 + j, words - 1)];
+      m[j] = w0 + tid * 4 + j < words ? v : 0u;
+      cnt += __popc(m[j]);
+    }
+    int total;
+    int at = base + wg_scan_incl<NT>(cnt, sh, &total) - cnt;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      for (uint32_t mm = m[j]; mm != 0u; mm &= mm - 1u) out[at++] = (w0 + tid * 4 + j) * 32 + __builtin_ctz(mm);
+    base += total;
+  }
+  return base;
+}
+
 }  // namespace hire

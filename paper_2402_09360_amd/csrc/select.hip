@@ -770,7 +770,6 @@ struct LeanShared {
   uint32_t win[kWin];  // the window histogram; afterwards the row's bitmap, or the packed outputs
   int wave_cnt[kSelWaves];
   uint32_t wmax[kSelWaves];
-  int band_n;
 };
 
 // The row's keys are in kr (loaded, masked beyond n): anchor, window histogram, selection of the k largest.
@@ -889,47 +888,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select_nonneg(SelectParams p) {
   lean_row<TB, V>(p, (int)blockIdx.x, reinterpret_cast<const V*>(p.vals) + (size_t)blockIdx.x * p.stride, L);
 }
 
-// ---------------------------------------------------------------------------
-// Filter and refine (SelectParams::refine_w): the row holds fp32 values within err_c |u| |x| of the activations
-// (launch_gather_dot_bf16).  The kernel selects the k largest stored values, takes the band of non-zero entries
-// within hw = 2 err_c xnorm[b] *wnorm_max of the k-th, recomputes those in fp64 (every wave its own entries) into
-// refine_h and lists them (value, position) in LDS.  What lies above the band is larger than the true k-th
-// activation, what lies below is smaller, so with A entries above the band the k - A largest listed ones
-// complete the selection.  If the list does not settle it (band reaching the zeros, more
-// entries than the list holds, counts that do not fit), the row's remaining stored values are written to
-// refine_h as well and the row is selected again there in fp64, as launch_select_f64 would.
-
-// fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.
-__device__ __forceinline__ double wave_row_dot_f64(const uint16_t* row, const uint16_t* tok, int d) {
-  const int cpr = d / 8, lane = lane_id();
-  const uint4* r4 = reinterpret_cast<const uint4*>(row);
-  const uint4* t4 = reinterpret_cast<const uint4*>(tok);
-  double acc = 0.0;
-#pragma nounroll
-  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
-    uint4 wv[4], xv[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int c = min(c0 + v * kWave + lane, cpr - 1);
-      wv[v] = r4[c];
-      xv[v] = t4[c];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (c0 + v * kWave + lane < cpr) {
-        const uint32_t wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, xd[4] = {xv[v].x, xv[v].y, xv[v].z, xv[v].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
-          acc += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
-        }
-      }
-  }
-  return wave_sum(acc);
-}
-
-// The same for up to four rows at once (the first nr count; the others must point at readable rows): all their
-// loads of a 256-chunk slice are in flight together.
+// fp64 dot products of up to four bf16 rows (the first nr count; the others must point at readable rows) and a bf16
+// token by one wave: products exact in fp32, sums in fp64; all loads of a 256-chunk slice are in flight together.
 __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4], int nr, const uint16_t* tok, int d,
                                                   double (&out)[4]) {
   const int cpr = d / 8, lane = lane_id();
@@ -965,156 +925,6 @@ __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4
 #pragma unroll
   for (int u = 0; u < 4; ++u) out[u] = wave_sum(acc[u]);
 }
-
-__global__ __launch_bounds__(kSelThreads) void k_select_refine(SelectParams p) {
-  using K = uint32_t;
-  constexpr int LOADS = 4, TB = 40;
-  using Keys = KeyRegs<K, LOADS, kSelThreads>;
-  constexpr int PER = Keys::PER;
-  static_assert(Keys::CAPACITY == kCachedMax && LOADS * PER <= 32, "rows of up to 16384 entries, one bit per key of a lane");
-  __shared__ LeanShared L;
-  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
-  const int w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int cap = p.n_dev ? p.n_cap : p.n, k = p.k;
-  const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
-  double* h = p.refine_h + (size_t)b * p.refine_h_stride;
-  HIRE_TS(TB);
-  const int n_raw = p.n_dev ? *p.n_dev : p.n;
-  Keys kr;
-  kr.issue_clamped(vals, cap);
-  if (tid == 0) L.band_n = 0;
-  kr.finish();
-  const int n = p.n_dev ? min(n_raw, p.n_cap) : p.n;
-  kr.mask_beyond(n);
-  const Selection<K> sel0 = lean_select<TB>(kr, vals, k, L, p.window_misses);
-  // the band around the k-th stored value, as bit patterns of non-negative floats (they order like the values);
-  // its bounds are rounded outwards, zeros are never part of it; with k = n everything is selected anyway
-  const double cut0 = (double)__uint_as_float(sel0.cut.key);
-  const double hw = 2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)__uint_as_float(*p.wnorm_max) * 1.000001;
-  const double lo_v = cut0 - hw, hi_v = cut0 + hw;
-  const float lo_f = __double2float_rd(lo_v), hi_f = __double2float_ru(hi_v);
-  const K lo_k = lo_f > 0.0f ? __float_as_uint(lo_f) : 1u, hi_k = __float_as_uint(hi_f);
-  const bool any = k < n && hi_k >= lo_k;
-  const K width = any ? hi_k - lo_k : 0u;
-  int gt = 0;
-  uint32_t bits = 0u;  // bit e * PER + q: this lane's key (e, q) lies in the band
-#pragma unroll
-  for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const K key = kr.r[e][q];
-      gt += key > hi_k ? 1 : 0;
-      if (any && (K)(key - lo_k) <= width) bits |= 1u << (e * PER + q);
-    }
-  const int above = wave_sum(gt);
-  __syncthreads();  // every wave has left the selection: its list in LDS and its counts are free
-  if (lane == 0) L.wave_cnt[w] = above;
-  HIRE_TS(49);
-  unsigned long long* lkey = reinterpret_cast<unsigned long long*>(L.sh.hist);  // [kFastAmbCap] refined values
-  int* lidx = reinterpret_cast<int*>(L.sh.hist + 2 * kFastAmbCap);              // [kFastAmbCap] their positions
-  {
-    const int32_t* map = p.map + (size_t)b * p.map_stride;
-    const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
-    uint64_t owners = __ballot(bits != 0u);
-    while (owners != 0ull) {  // uniform over the wave
-      const int src = __builtin_ctzll(owners);
-      owners &= owners - 1ull;
-      uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)bits, src);
-      while (sb != 0u) {
-        const int t = __builtin_ctz(sb);
-        sb &= sb - 1u;
-        const int pos = kr.base + (t / PER) * Keys::SPAN + src * PER + (t % PER);
-        const int unit = map[pos];
-        double s = wave_row_dot_f64(p.refine_w + (size_t)unit * p.refine_d, tok, p.refine_d);
-        s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-        if (lane == 0) {
-          h[pos] = s;
-          const int slot = atomicAdd(&L.band_n, 1);
-          if (slot < kFastAmbCap) {
-            lkey[slot] = (unsigned long long)__double_as_longlong(s);
-            lidx[slot] = pos;
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  HIRE_TS(50);
-  const int pa = wave_scan_incl(lane < kSelWaves ? L.wave_cnt[lane] : 0);
-  const int A = __builtin_amdgcn_readlane(pa, kSelWaves - 1), C = L.band_n;
-  const int need = k - A;
-  if (k >= n) {  // uniform: every entry of the row is selected, nothing was refined
-    lean_outputs(p, b, k, L, [&](auto&& put) {
-      fast_emit(kr, sel0, 0, k, [&](int i, int out, K key, int, int) { put(i, out, __uint_as_float(key)); });
-    });
-    HIRE_TS(TB + 7);
-    return;
-  }
-  bool settled = false;
-  int first = 0, count = 0;
-  uint32_t selbits = 0u;  // bit e * PER + q: this lane's band key (e, q) is selected
-  if (lo_v > 0.0 && C <= kFastAmbCap && need >= 1 && need <= C) {  // uniform over the workgroup
-    const int m = C;
-    const unsigned long long mine_k = lane < m ? lkey[lane] : 0ull;
-    const int mine_i = lane < m ? lidx[lane] : 0x7FFFFFFF;
-    int rank = 0;  // listed entries ahead of this lane's (value descending, position ascending)
-    for (int u = 0; u < m; ++u) {
-      const unsigned long long ok = read_lane(mine_k, u);
-      const int oi = __builtin_amdgcn_readlane(mine_i, u);
-      rank += ranks_ahead((uint64_t)ok, oi, (uint64_t)mine_k, mine_i) ? 1 : 0;
-    }
-    const bool taken = lane < m && rank < need;
-    const uint64_t last = __ballot(lane < m && rank == need - 1);  // exactly one lane
-    const double cut = __longlong_as_double((long long)read_lane(mine_k, __builtin_ctzll(last)));
-    if (cut > lo_v && cut < hi_v) {  // the true k-th activation lies inside the band
-      settled = true;
-      const int above_before = w > 0 ? __builtin_amdgcn_readlane(pa, w - 1) : 0;
-      const int rel = mine_i - kr.base;  // position inside this wave's range, if 0 <= rel < len
-      const bool here = taken && rel >= 0 && rel < kr.len;
-      first = above_before + __popcll(__ballot(taken && rel < 0));
-      count = above + __popcll(__ballot(here));
-      uint64_t mine = __ballot(here);  // the selected listed entries of this wave's range: mark them at their owners
-      while (mine != 0ull) {
-        const int s = __builtin_ctzll(mine);
-        mine &= mine - 1ull;
-        const int r = __builtin_amdgcn_readlane(rel, s);
-        const int e = r / Keys::SPAN, l = (r % Keys::SPAN) / PER, q = r % PER;
-        if (lane == l) selbits |= 1u << (e * PER + q);
-      }
-    }
-  }
-  HIRE_TS(51);
-  if (settled) {  // uniform over the workgroup
-    lean_outputs(p, b, k, L, [&](auto&& put) {
-      fast_emit_if(
-          kr, first, count, 0, k,
-          [&](int e, int q) { return kr.r[e][q] > hi_k || ((selbits >> (e * PER + q)) & 1u) != 0u; },
-          [&](int i, int out, K key, int e, int q) {
-            double v = (double)__uint_as_float(key);
-            if (((selbits >> (e * PER + q)) & 1u) != 0u)
-              v = __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(h + i),
-                                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            put(i, out, (float)v);
-          });
-    });
-    HIRE_TS(TB + 7);
-    return;
-  }
-  // not settled: the stored values outside the band join the refined ones, and the row is selected there
-#pragma unroll
-  for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-      if (kr.valid(e, q) && ((bits >> (e * PER + q)) & 1u) == 0u) h[kr.index(e, q)] = (double)__uint_as_float(kr.r[e][q]);
-  if (tid == 0 && p.window_misses) atomicAdd(p.window_misses, 1u);
-  __syncthreads();
-  SelectParams p2 = p;
-  p2.n_dev = nullptr;
-  p2.n = n;
-  p2.n_cap = n;
-  lean_row<TB, double>(p2, b, h, L);
-}
-
 
 // ---------------------------------------------------------------------------
 // Filter and refine for the classifier (Algorithm 1 with phi = identity, then eq. (2)): the row holds fp32 logits
@@ -1162,6 +972,9 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
 #pragma unroll
   for (int i = 0; i < kSmItems; ++i) mx = key[i] > mx ? key[i] : mx;
   mx = wg_max_u32(mx, sh);
+  uint32_t wn = 0u;  // largest row norm: non-negative floats order like their bits
+  for (int i = tid; i < p.wnorm_n; i += kSelThreads) wn = max(wn, __float_as_uint(p.wnorm_tiles[i]));
+  wn = wg_max_u32(wn, sh);
   int anchor = (int)(mx >> kFineShift), above = 0;
   uint32_t floor_key = 0u;  // 0: every entry of the row
   while (true) {  // uniform
@@ -1204,7 +1017,7 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
     if (anchor < 0) break;  // cannot happen with k <= n: every key lies in some window
   }
   const double mark = (floor_key != 0u ? (double)key_value(floor_key) : -__builtin_huge_val()) -
-                      2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)__uint_as_float(*p.wnorm_max) * 1.000001;
+                      2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)__uint_as_float(wn) * 1.000001;
   const uint32_t mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
   unsigned long long pending = 0ull;  // bit i: value i has to be recomputed and has not been listed yet
 #pragma unroll
@@ -1293,7 +1106,7 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
 hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s) {
   const int cap = p.n_dev ? p.n_cap : p.n;
   if (cap < 1 || cap > kSoftmaxRefineMaxRow || p.k < 1 || p.k > kSoftmaxRefineMaxK || !p.refine_w || !p.refine_x ||
-      p.refine_d % 8 != 0 || !p.map || !p.xnorm || !p.wnorm_max || !p.vals)
+      p.refine_d % 8 != 0 || !p.map || !p.xnorm || !p.wnorm_tiles || !p.vals)
     return hipErrorInvalidValue;
   if (cap <= 16 * kSelThreads) return launch(k_softmax_refine<16>, dim3(B), dim3(kSelThreads), 0, s, p);
   if (cap <= 32 * kSelThreads) return launch(k_softmax_refine<32>, dim3(B), dim3(kSelThreads), 0, s, p);
@@ -1307,23 +1120,12 @@ static bool select_is_lean(const SelectParams& p) {
   return p.nonneg && !p.rank_order && !p.group8 && p.gs == 0 && !p.relu && cap > kSelThreads && cap <= kCachedMax &&
          p.k <= kWin / 2 && reinterpret_cast<uintptr_t>(p.vals) % 16 == 0 && (p.stride * (long long)sizeof(V)) % 16 == 0;
 }
-bool select_refine_supported(const SelectParams& p) {
-  return select_is_lean<float>(p) && p.bitmap == nullptr && reinterpret_cast<uintptr_t>(p.refine_h) % 16 == 0 &&
-         (p.refine_h_stride * (long long)sizeof(double)) % 16 == 0 && p.refine_d % 8 == 0;
-}
-hipError_t launch_select_refine(const SelectParams& p, int B, hipStream_t s) {
-  if (!select_refine_supported(p) || !p.refine_w || !p.refine_x || !p.refine_h || !p.map || !p.xnorm || !p.wnorm_max)
-    return hipErrorInvalidValue;
-  return launch(k_select_refine, dim3(B), dim3(kSelThreads), 0, s, p);
-}
-
 template <typename V>
 static hipError_t launch_select(const SelectParams& p, int B, hipStream_t s) {
   size_t lds = 0;
   if (p.rank_order) lds = (size_t)p.k * (sizeof(typename KeyOf<V>::K) + 2 * sizeof(int));
   const int cap = p.n_dev ? p.n_cap : p.n;
   if (select_is_lean<V>(p)) return launch(k_select_nonneg<V>, dim3(B), dim3(kSelThreads), 0, s, p);
-  if (p.refine_w != nullptr) return hipErrorInvalidValue;  // launch_select_refine's business
   if (p.group8) {  // rows of at most kSelectGroup8Max groups
     if (cap <= kSelThreads) return launch(k_select<V, 1, true>, dim3(B), dim3(kSelThreads), lds, s, p);
     if (cap <= 4 * kSelThreads) return launch(k_select<V, 4, true>, dim3(B), dim3(kSelThreads), lds, s, p);

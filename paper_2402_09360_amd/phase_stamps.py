@@ -34,23 +34,20 @@ FAST = [
                    (22, "ranked"), (25, "selection returned"), (26, "selected rows and coefficients in LDS"),
                    (27, "second-layer rows read and accumulated"), (28, "reduced over the waves, y written")]),
 ]
-GENERAL = [
-    ("k_select_nonneg<float> (top-k' of the keys)",
-     [(10, "kernel start"), (11, "keys loaded, anchor known"), (12, "window histogram built"), (13, "window walked"),
-      (14, "counted and listed"), (15, "ranked"), (16, "selection returned"), (17, "bitmap / outputs written")]),
-    ("k_select_nonneg<double> or k_select_refine (top-k of the activations)",
-     [(40, "kernel start"), (41, "values loaded, anchor known"), (42, "window histogram built"), (43, "window walked"),
-      (44, "counted and listed"), (45, "ranked"), (46, "selection returned"),
-      (49, "band marked (filter and refine)"), (50, "band recomputed in fp64"), (51, "band ranked"),
+BATCH = [
+    ("k_keys_select (top-k' of the keys)",
+     [(10, "kernel start"), (11, "keys loaded, window cleared"), (12, "window built and walked: threshold bin known"),
+      (13, "bin listed"), (14, "bin ranked: cut known"), (15, "union bits set")]),
+    ("k_refine (top-k of the activations)",
+     [(40, "kernel start"), (41, "values loaded, window cleared, bound known"),
+      (42, "window built and walked: threshold bin known"), (43, "entries above counted, band listed"),
+      (44, "band recomputed in fp64"), (45, "band ranked"), (46, "selected entries packed in output order"),
       (47, "outputs written")]),
 ]
 GATHER = [
-    ("k_gather_dot_bf16 (filter stage, first workgroup)",
-     [(55, "kernel start"), (56, "tile's candidates known")] +
-     [(1 + 6 * p + j, f"pass {p}: {what}") for p in range(4) for j, what in enumerate(
-         ["start", "tokens' slab stored", "candidates' slab stored", "next pass requested, barrier passed",
-          "matrix cores done", "barrier passed"])] +
-     [(57, "all passes done"), (58, "norms, stored values, maxima written")]),
+    ("k_filter_bf16 (filter stage, first workgroup)",
+     [(55, "kernel start"), (56, "candidates known"), (57, "all stages done"),
+      (58, "norms, stored values, maximum written")]),
 ]
 
 
@@ -132,7 +129,7 @@ def main():
     if B == 1 and not args.general:
         show(FAST, *table("hire_debug_timestamps_fast"))
     else:
-        show(GENERAL, *table("hire_debug_timestamps_select"))
+        show(BATCH, *table("hire_debug_timestamps_batch_select"))
         show(GATHER, *table("hire_debug_timestamps_gather"))
 
 

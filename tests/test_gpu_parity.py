@@ -167,6 +167,21 @@ def ffn_1b(hire, oracle):
 
 
 @pytest.mark.parametrize("d,N,B,k,kp", [
+    (160, 20003, 3, 900, 3000),     # rows beyond 16384 (32 keys per thread), a row's second stage of 32 elements
+    (256, 16385, 64, 700, 1100),    # ... one unit more than 16384, whole stages
+    (8224, 200, 17, 20, 60),        # token beyond the LDS copy, 65 stages, the last one short
+    (96, 65, 2, 5, 20),             # a workgroup with one unit
+    (544, 1279, 16, 4, 40),         # sparse union: workgroups with few candidates
+    (1184, 641, 48, 600, 620),      # nearly everything selected
+])
+def test_batched_filter_and_refine_edges(hire, oracle, d, N, B, k, kp):
+    log(f"filter and refine d={d} N={N} B={B} k={k} kp={kp}")
+    L = I.ffn_layer(95 + B, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    T.check_ffn(layer, scorer, L, I.tokens(96 + B, B, d), k, kp)
+
+
+@pytest.mark.parametrize("d,N,B,k,kp", [
     (2080, 1500, 33, 1100, 1300),   # 256-column slices, the last one partial; two chunks of entries, the second short
     (1056, 1030, 40, 64, 300),      # 128-column slices
     (800, 1600, 13, 1024, 1200),    # 64-column slices, one whole chunk
