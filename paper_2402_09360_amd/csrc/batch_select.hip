@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
         double cut = 0.0;
         uint64_t taken[2];
         uint32_t selbits = 0u;
-        int lower = 0, here = 0;
+        int lower = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const bool in = lane + u * kWave < C, take = in && rank[u] < need;
@@ -380,7 +380,6 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
           const int rel = ki[u] - kr.base;
           taken[u] = __ballot(take && rel >= 0 && rel < kr.len);
           lower += __popcll(__ballot(take && rel < 0));
-          here += __popcll(taken[u]);
           for (uint64_t m = taken[u]; m != 0ull; m &= m - 1ull) {  // mark this wave's own at their lanes
             const int r = __builtin_amdgcn_readlane(rel, __builtin_ctzll(m));
             if (lane == (r % Keys::SPAN) / PER) selbits |= 1u << (r / Keys::SPAN * PER + r % PER);
@@ -391,21 +390,45 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
           int* pk_pos = reinterpret_cast<int*>(L.win);
           float* pk_val = reinterpret_cast<float*>(L.win + kWin / 2);
           const int above_before = w > 0 ? __builtin_amdgcn_readlane(pa, w - 1) : 0;
-          fast_emit_if(
-              kr, above_before + lower, above + here, 0, k,
-              [&](int e, int q) { return kr.r[e][q] > hi_k || ((selbits >> (e * PER + q)) & 1u) != 0u; },
-              [&](int i, int out, K key, int e, int q) {
-                float v = __uint_as_float(key);
-                if (((selbits >> (e * PER + q)) & 1u) != 0u) {  // recomputed: that value
-                  const int n = __popc(bits & ((1u << (e * PER + q)) - 1u));
-                  int slot = (int)(slots >> (8 * n)) & 255;
-                  if (n >= 4)
-                    for (slot = 0; L.l_idx[slot] != i;) ++slot;
-                  v = (float)__longlong_as_double((long long)L.l_val[slot]);
+          // This lane's selected keys of every load, counted in 16-bit fields (a wave holds at most 256 per load);
+          // two prefix sums over the lanes give the places of all of them at once.
+          uint32_t take = selbits;
+#pragma unroll
+          for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+            for (int q = 0; q < PER; ++q) take |= kr.r[e][q] > hi_k ? 1u << (e * PER + q) : 0u;
+          // recomputed values take the stored ones' places (few waves have any)
+          for (uint32_t m = selbits; __ballot(m != 0u) != 0ull; m &= m - 1u) {
+            const int t = m != 0u ? __builtin_ctz(m) : 0, n = __popc(bits & ((1u << t) - 1u));
+            int slot = (int)(slots >> (8 * (n & 3))) & 255;
+            if (n >= 4)
+              for (slot = 0; L.l_idx[slot] != kr.index(t / PER, t % PER);) ++slot;
+            const uint32_t now = m & (0u - m);
+            const K v = __float_as_uint((float)__longlong_as_double((long long)L.l_val[min(slot, kBsCap - 1)]));
+#pragma unroll
+            for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+              for (int q = 0; q < PER; ++q) kr.r[e][q] = (now >> (e * PER + q) & 1u) != 0u ? v : kr.r[e][q];
+          }
+          int run = above_before + lower;
+#pragma unroll
+          for (int e0 = 0; e0 < LOADS; e0 += 2) {
+            constexpr uint32_t kField = (1u << PER) - 1u;
+            const int c0 = __popc(take >> (e0 * PER) & kField), c1 = __popc(take >> ((e0 + 1) * PER) & kField);
+            const int incl = wave_scan_incl(c0 | c1 << 16), tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+            int at[2] = {run + (incl & 0xFFFF) - c0, run + (tot & 0xFFFF) + (incl >> 16) - c1};
+            run += (tot & 0xFFFF) + (tot >> 16);
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+              for (int q = 0; q < PER; ++q) {
+                const int bit = (e0 + f) * PER + q;
+                if ((take >> bit & 1u) != 0u) {
+                  pk_pos[at[f]] = kr.index(e0 + f, q);
+                  pk_val[at[f]++] = __uint_as_float(kr.r[e0 + f][q]);
                 }
-                pk_pos[out] = i;
-                pk_val[out] = v;
-              });
+              }
+          }
           __syncthreads();
           HIRE_TS(46);
           for (int t = tid; t < k; t += kSelThreads) {

@@ -186,7 +186,8 @@ __device__ __forceinline__ float pick4(const f32x4& v, int i) {
 }
 
 // Layout.  A workgroup owns 64 candidates and all of the batch's tokens (TT tiles of 16): 4 groups of 16
-// candidates times TG shares of the token tiles, one wave each.  K goes by in stages of 128 elements: 256 bytes of
+// candidates times TG shares of the token tiles times KS shares of every stage's K steps, one wave each (the K shares
+// are added in fp64 at the end).  K goes by in stages of 128 elements: 256 bytes of
 // every row, brought into LDS by asynchronous 16-byte loads that bypass the registers (a wave's instruction fills 1
 // KiB, four rows), kStages deep: a stage is requested three stages before it is used, and one barrier per stage
 // (which also waits for this wave's share of it) is all the synchronisation.  LDS position p of a row holds its chunk
@@ -201,9 +202,9 @@ __device__ __forceinline__ float pick4(const f32x4& v, int i) {
 // union bitmap (or list), values go to h[token][rank].
 //
 // Bound: HBM; one workgroup per compute unit keeps 48 KB of rows in flight.  Measured at d = 2048: 16 tokens, 15900
-// candidates (65 MB) 17.6 us, 64 tokens, 16384 candidates 19.9 us, 4 tokens, 9750 candidates (40 MB) 14.1 us (whole
-// kernels in a step: 3.7, 3.4 and 2.8 TB/s).  The kernel before this one staged through registers and located its
-// candidates by rank: 22.4 us at 16 tokens, 30 at 64; four tokens took 18.2 us on the fp64 matrix cores.
+// candidates (65 MB) 17.5 us, 64 tokens, 16384 candidates 19.3 us (of which the stages 12: 5.6 TB/s), 4 tokens, 9750
+// candidates (40 MB) 12.3 us.  The kernel before this one staged through registers and located its candidates by
+// rank: 22.4 us at 16 tokens, 30 at 64; four tokens took 18.2 us on the fp64 matrix cores.  KS = 1: 17.6, 19.9, 14.1.
 constexpr int kFtRows = 64;        // candidates per workgroup
 constexpr int kFtChunks = 16;      // 16-byte chunks of a row per stage
 constexpr int kFtStages = 4;
@@ -238,23 +239,25 @@ __device__ __forceinline__ void stage_barrier_loads(int ci, bool whole) {
   }
 }
 
-template <int TT, int TG, bool UNIT>
-__global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __restrict__ W, const uint16_t* __restrict__ x,
+template <int TT, int TG, int KS, bool UNIT>
+__global__ __launch_bounds__(256 * TG * KS) void k_filter_bf16(const uint16_t* __restrict__ W, const uint16_t* __restrict__ x,
                                                           int B, int d, const int32_t* __restrict__ list,
                                                           const int32_t* __restrict__ n_dev, int n_cap,
                                                           float* __restrict__ h, long long stride_h, GatherUnion un,
                                                           float* __restrict__ xnorm, float* __restrict__ wnorm_tiles,
                                                           uint32_t* __restrict__ wnorm_max, float err_c) {
-  constexpr int NW = 4 * TG, NT = 64 * NW, TTW = TT / TG;
-  constexpr int CI = kFtRows / (4 * NW), TI = 16 * TT / (4 * NW);  // load instructions per wave and stage
+  constexpr int NW = 4 * TG * KS, NT = 64 * NW, TTW = TT / TG;
+  constexpr int kSteps = kFtSteps / KS;                       // MFMA steps per wave and stage
+  constexpr int CI = kFtRows / (4 * NW);                      // load instructions per wave and stage: candidates,
+  constexpr int TI = 16 * TT > 4 * NW ? 16 * TT / (4 * NW) : 1;  // tokens (fewer than one per wave: loaded twice)
   constexpr int kStage = ft_stage_bytes(TT);
   constexpr int kSegSteps = filter_segment_steps(16 * TT);  // MFMA steps per fp32 segment
-  static_assert(TT % TG == 0 && CI >= 1 && TI >= 1 && 4 * TI * NW == 16 * TT && kFtSteps % kSegSteps == 0, "equal shares");
-  static_assert(TT <= NW && kFtRows * 16 * TT * 4 <= kFtStages * kStage, "the result tile reuses the stages' memory");
+  static_assert(TT % TG == 0 && CI >= 1 && 4 * CI * NW == kFtRows && kSteps % kSegSteps == 0, "equal shares");
+  static_assert(4 * TI * NW == 16 * TT || 4 * NW % (16 * TT) == 0, "whole token rows");
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int32_t rows_sh[kFtRows];
-  __shared__ float xsq[TT][16];
-  __shared__ float wmx[NW];
+  __shared__ float xsq[KS][TT][16];
+  __shared__ float wmx[4];
   const int tid = (int)threadIdx.x, lane = lane_id(), jl = lane & 15, g = lane >> 4;
   // known to be uniform: a matrix-core instruction must never sit behind a branch that is lowered to lane masking
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
     }
   }
   HIRE_TS(56);
-  const int cw = w & 3, tt0 = (w >> 2) * TTW;  // this wave's candidate group and first token tile
+  const int cw = w & 3, tt0 = (w >> 2) % TG * TTW, kh = (w >> 2) / TG;  // this wave's candidates, tokens, steps (uniform)
   double acc[TTW][4];
 #pragma unroll
   for (int t = 0; t < TTW; ++t)
@@ -317,16 +320,17 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
     for (int i = 0; i < CI; ++i)
       wptr[i] = reinterpret_cast<const char*>(W + (size_t)rows_sh[min(4 * NW * i + r4, c - 1)] * d);
 #pragma unroll
-    for (int i = 0; i < TI; ++i) xptr[i] = reinterpret_cast<const char*>(x + (size_t)min(4 * NW * i + r4, B - 1) * d);
+    for (int i = 0; i < TI; ++i) xptr[i] = reinterpret_cast<const char*>(x + (size_t)min((4 * NW * i + r4) % (16 * TT), B - 1) * d);
     auto request = [&](int st, int slot) {
       const int at = kFtChunks * st + ch;
       const int off = 16 * (at < cpr ? at : 0);  // past the row's end: its first chunk, masked when it is used
       const uint32_t to = base + slot * kStage + 1024 * w;
+      const uint32_t to_tok = base + slot * kStage + kFtRows * kFtRowBytes + 1024 * w % (16 * TT * kFtRowBytes);
 #pragma unroll
       for (int i = 0; i < CI; ++i)
         if (i < ci) load_to_lds(wptr[i] + off, to + 1024 * NW * i);
 #pragma unroll
-      for (int i = 0; i < TI; ++i) load_to_lds(xptr[i] + off, to + kFtRows * kFtRowBytes + 1024 * NW * i);
+      for (int i = 0; i < TI; ++i) load_to_lds(xptr[i] + off, to_tok + 1024 * NW * i);
     };
 #pragma unroll
     for (int st = 0; st < kFtStages - 1; ++st)
@@ -339,24 +343,24 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
         const unsigned char* wcol = lds + slot * kStage + (16 * cw + jl) * kFtRowBytes;
         const unsigned char* xcol = lds + slot * kStage + (kFtRows + 16 * tt0 + jl) * kFtRowBytes;
         const int left = cpr - kFtChunks * st;  // chunks of the row from this stage on
-        bf16x8 wk[kFtSteps], tk[TTW][kFtSteps];
+        bf16x8 wk[kSteps], tk[TTW][kSteps];
 #pragma unroll
-        for (int u = 0; u < kFtSteps; ++u) {
-          const int o = ((4 * u + g) ^ jl) * 16;
+        for (int u = 0; u < kSteps; ++u) {
+          const int o = ((4 * (u + kh * kSteps) + g) ^ jl) * 16;
           wk[u] = as_bf16x8(*reinterpret_cast<const uint4*>(wcol + o));
 #pragma unroll
           for (int t = 0; t < TTW; ++t) tk[t][u] = as_bf16x8(*reinterpret_cast<const uint4*>(xcol + t * 16 * kFtRowBytes + o));
         }
         if (left < kFtChunks) {  // uniform: the row ends inside the stage
 #pragma unroll
-          for (int u = 0; u < kFtSteps; ++u)
-            if (4 * u + g >= left) {
+          for (int u = 0; u < kSteps; ++u)
+            if (4 * (u + kh * kSteps) + g >= left) {
               wk[u] = as_bf16x8(make_uint4(0, 0, 0, 0));
 #pragma unroll
               for (int t = 0; t < TTW; ++t) tk[t][u] = as_bf16x8(make_uint4(0, 0, 0, 0));
             }
         }
-        constexpr int kSeg = kFtSteps / kSegSteps;
+        constexpr int kSeg = kSteps / kSegSteps;
         f32x4 part[TTW][kSeg];
 #pragma unroll
         for (int v = 0; v < kSegSteps; ++v)
@@ -368,13 +372,13 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
                                                                    v == 0 ? zero : part[t][q], 0, 0, 0);
         if (tt0 == 0) {  // uniform
 #pragma unroll
-          for (int u = 0; u < kFtSteps; ++u) accw = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wk[u], wk[u], accw, 0, 0, 0);
+          for (int u = 0; u < kSteps; ++u) accw = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wk[u], wk[u], accw, 0, 0, 0);
         }
 #pragma unroll
         for (int t = 0; t < TTW; ++t) {
           if (cw == 0) {  // uniform
 #pragma unroll
-            for (int u = 0; u < kFtSteps; ++u)
+            for (int u = 0; u < kSteps; ++u)
               accx[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tk[t][u], tk[t][u], accx[t], 0, 0, 0);
           }
 #pragma unroll
@@ -387,52 +391,70 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
     }
   }
   HIRE_TS(57);
-  // entry (i, i) of a 16 x 16 result sits in value i % 4 of lane 16 (i / 4) + i
-  const float up = 1.0f + (float)d * 0x1p-22f;  // more than the relative error of the norms' sums
+  // LDS from here on: the result tile [16 TT][64], the rows' squared norms [KS][64], the other K shares' sums
+  float* tile_out = reinterpret_cast<float*>(lds);
+  float* wsq = tile_out + 16 * TT * kFtRows;
+  double* shares = reinterpret_cast<double*>(wsq + KS * kFtRows);  // [KS - 1][4 TG][TTW * 4][64]
+  static_assert((16 * TT + KS) * kFtRows * 4 + (KS - 1) * 4 * TG * TTW * 4 * kWave * 8 <= kFtStages * kStage, "LDS");
+  __syncthreads();  // the stages' memory is free
+  // entry (i, i) of a 16 x 16 result sits in value i % 4 of lane 16 (i / 4) + i.  Token norms from group 0's waves,
+  // candidate norms from those of the first token share
   if (cw == 0 && (jl >> 2) == g) {
 #pragma unroll
-    for (int t = 0; t < TTW; ++t) xsq[tt0 + t][jl] = pick4(accx[t], jl & 3);
+    for (int t = 0; t < TTW; ++t) xsq[kh][tt0 + t][jl] = pick4(accx[t], jl & 3);
   }
-  // |u_jl|^2, formed by the group's wave of the first share: to all four lanes of the candidate, through LDS to the
-  // other shares
-  float* wsq = reinterpret_cast<float*>(lds) + 16 * TT * kFtRows;  // [64] behind the result tile
-  static_assert((16 * TT + 1) * kFtRows * 4 <= kFtStages * kStage, "result tile and norms");
-  __syncthreads();  // the stages' memory is free
-  if (tt0 == 0 && (jl >> 2) == g) wsq[16 * cw + jl] = pick4(accw, jl & 3);
-  float* tile_out = reinterpret_cast<float*>(lds);  // [16 TT][64]
+  if (tt0 == 0 && (jl >> 2) == g) wsq[kh * kFtRows + 16 * cw + jl] = pick4(accw, jl & 3);
+  if (KS > 1 && kh > 0) {
+#pragma unroll
+    for (int t = 0; t < TTW; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        shares[((((kh - 1) * TG + tt0 / TTW) * 4 + cw) * TTW * 4 + t * 4 + r) * kWave + lane] = acc[t][r];
+  }
   if constexpr (UNIT) {
     for (int i = tid; i < 16 * TT * kFtRows / 4; i += NT) reinterpret_cast<float4*>(tile_out)[i] = make_float4(0, 0, 0, 0);
   }
   __syncthreads();
-  const float wnorm = sqrtf(wsq[16 * cw + jl] * up) * 1.0001f;
-  const int ce = 16 * cw + jl;  // this lane's candidate
-  if (tt0 == 0) {
-    float m = ce < c ? wnorm : 0.0f;
+  const float up = 1.0f + (float)d * 0x1p-22f;  // more than the relative error of the norms' sums
+  const int ce = 16 * cw + jl;                  // this lane's candidate
+  float wn2 = 0.0f;
+#pragma unroll
+  for (int q = 0; q < KS; ++q) wn2 += wsq[q * kFtRows + ce];
+  wn2 *= up;
+  if (w < 4) {  // tt0 == 0, kh == 0
+    float m = ce < c ? wn2 : 0.0f;
     m = fmaxf(m, __shfl_xor(m, 1));
     m = fmaxf(m, __shfl_xor(m, 2));
     m = fmaxf(m, __shfl_xor(m, 4));
     m = fmaxf(m, __shfl_xor(m, 8));
     if (lane == 0) wmx[cw] = m;
   }
+  if (kh == 0) {
+    const double four_err2 = 4.001 * (double)err_c * (double)err_c * (double)wn2;
 #pragma unroll
-  for (int t = 0; t < TTW; ++t)
+    for (int t = 0; t < TTW; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int tl = 4 * g + r, tk = 16 * (tt0 + t) + tl;
-      const double s = acc[t][r];
-      float v = (float)s;  // phi = identity (the classifier): the sum itself
-      if constexpr (UNIT) {
-        const float xnrm = sqrtf(xsq[tt0 + t][tl] * up) * 1.0001f;
-        const double delta = (double)(err_c * wnorm * xnrm);
-        const float tiny = __uint_as_float(1u);  // the smallest positive float
-        v = 0.0f;
-        if (s > 0.0) v = fmaxf((float)s, tiny);
-        else if (s > -2.0 * delta) v = tiny;  // the true activation may still be positive
-        if (ce < c) tile_out[tk * kFtRows + rows_sh[ce] - e0] = v;
-      } else {
-        if (tk < B && ce < c) h[(size_t)tk * stride_h + e0 + ce] = v;
+      for (int r = 0; r < 4; ++r) {
+        const int tl = 4 * g + r, tk = 16 * (tt0 + t) + tl;
+        double s = acc[t][r];
+#pragma unroll
+        for (int q = 1; q < KS; ++q)
+          s += shares[((((q - 1) * TG + tt0 / TTW) * 4 + cw) * TTW * 4 + t * 4 + r) * kWave + lane];
+        float v = (float)s;  // phi = identity (the classifier): the sum itself
+        if constexpr (UNIT) {
+          float xn2 = 0.0f;
+#pragma unroll
+          for (int q = 0; q < KS; ++q) xn2 += xsq[q][tt0 + t][tl];
+          const float tiny = __uint_as_float(1u);  // the smallest positive float
+          v = 0.0f;
+          if (s > 0.0) v = fmaxf((float)s, tiny);
+          else if (s * s < four_err2 * (double)(xn2 * up)) v = tiny;  // s > -2 delta: the true activation may be positive
+          if (ce < c) tile_out[tk * kFtRows + rows_sh[ce] - e0] = v;
+        } else {
+          if (tk < B && ce < c) h[(size_t)tk * stride_h + e0 + ce] = v;
+        }
       }
-    }
+  }
   __syncthreads();
   if constexpr (UNIT) {  // 64 units of every token, 16 bytes per lane where the rows are aligned
     if (stride_h % 4 == 0) {
@@ -448,13 +470,18 @@ __global__ __launch_bounds__(256 * TG) void k_filter_bf16(const uint16_t* __rest
     }
   }
   if (tid == 0) {  // a place per workgroup: 256 atomics on one address at the kernel's end took 7 us
-    const float m = c > 0 ? fmaxf(fmaxf(wmx[0], wmx[1]), fmaxf(wmx[2], wmx[3])) : 0.0f;
+    const float m = c > 0 ? sqrtf(fmaxf(fmaxf(wmx[0], wmx[1]), fmaxf(wmx[2], wmx[3]))) * 1.0001f : 0.0f;
     if (wnorm_tiles != nullptr) wnorm_tiles[tile] = m;
     else atomicMax(wnorm_max, __float_as_uint(m));
   }
   if (c <= 0) return;
   if (UNIT || tile == 0)  // UNIT: the same values from every workgroup that has candidates
-    for (int t = tid; t < B; t += NT) xnorm[t] = sqrtf(xsq[t / 16][t % 16] * up) * 1.0001f;
+    for (int t = tid; t < B; t += NT) {
+      float xn2 = 0.0f;
+#pragma unroll
+      for (int q = 0; q < KS; ++q) xn2 += xsq[q][t / 16][t % 16];
+      xnorm[t] = sqrtf(xn2 * up) * 1.0001f;
+    }
   HIRE_TS(58);
 }
 
@@ -491,23 +518,24 @@ hipError_t launch_filter_bf16(const uint16_t* W, const uint16_t* x, int B, int d
     if (u.bitmap == nullptr && list == nullptr) return hipErrorInvalidValue;
   }
   static std::atomic<size_t> raised_to[6] = {};
-  auto go = [&](auto kernel, int tt, int tg, std::atomic<size_t>& raised) {
+  auto go = [&](auto kernel, int tt, int waves, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
       return e;
-    return launch(kernel, dim3(tiles), dim3(256 * tg), lds, s, W, x, B, d, list, n_dev, n_cap, h, stride_h, u, xnorm,
+    return launch(kernel, dim3(tiles), dim3(64 * waves), lds, s, W, x, B, d, list, n_dev, n_cap, h, stride_h, u, xnorm,
                   wnorm_tiles, wnorm_max, gather_filter_error(B));
   };
-  // beyond 16 tokens two waves share a group of candidates, half of the token tiles each: the fp64 additions and
-  // the operand reads are spread over twice the waves
+  // Two (beyond 32 tokens four) waves share a group of candidates: halves of every stage's steps and, with several
+  // token tiles, halves of the tiles, so that the fp64 additions and the operand reads of a stage are short next to
+  // its loads.
   if (by_unit) {
-    if (B <= 16) return go(k_filter_bf16<1, 1, true>, 1, 1, raised_to[0]);
-    if (B <= 32) return go(k_filter_bf16<2, 2, true>, 2, 2, raised_to[1]);
-    return go(k_filter_bf16<4, 2, true>, 4, 2, raised_to[2]);
+    if (B <= 16) return go(k_filter_bf16<1, 1, 2, true>, 1, 8, raised_to[0]);
+    if (B <= 32) return go(k_filter_bf16<2, 2, 2, true>, 2, 16, raised_to[1]);
+    return go(k_filter_bf16<4, 2, 2, true>, 4, 16, raised_to[2]);
   }
-  if (B <= 16) return go(k_filter_bf16<1, 1, false>, 1, 1, raised_to[3]);
-  if (B <= 32) return go(k_filter_bf16<2, 2, false>, 2, 2, raised_to[4]);
-  return go(k_filter_bf16<4, 2, false>, 4, 2, raised_to[5]);
+  if (B <= 16) return go(k_filter_bf16<1, 1, 2, false>, 1, 8, raised_to[3]);
+  if (B <= 32) return go(k_filter_bf16<2, 2, 2, false>, 2, 16, raised_to[4]);
+  return go(k_filter_bf16<4, 2, 2, false>, 4, 16, raised_to[5]);
 }
 
 }  // namespace hire
