@@ -87,7 +87,7 @@ _STAGE_KERNELS = {
     "select_kprime": ("k_select<float", "k_select_nonneg<float", "k_keys_select", "k_count_f32", "k_mark_f32", "k_group_sums",
                       "k_sm1_gather<false"),
     "union": ("k_resolve_compact", "k_bitmap_compact", "k_union_compact", "k_max_resolve"),
-    "gather_dot": ("k_gather_dot", "k_filter_bf16", "k_sm1_gather<true", "k_sm1_final"),
+    "gather_dot": ("k_gather_dot", "k_filter_units", "k_filter_ranks", "k_sm1_gather<true", "k_sm1_final"),
     "select_k": ("k_select<double", "k_select_nonneg<double", "k_refine"),
     "select_k_softmax": ("k_select<double",),
     "second_layer": ("k_w2_list",),

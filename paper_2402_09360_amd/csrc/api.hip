@@ -63,6 +63,8 @@ struct StepBuffers {
   // filter and refine of the exact stage (batches): upper bounds of the tokens' norms, the fp32 stored values
   float* xnorm;      // [B]
   float* wnorm_tiles; // largest candidate row norm of every workgroup of the filter stage
+  void* refine_slots; // softmax: the final selection's slots
+  float* maxima;     // softmax: [B, kFilterMaxima] largest values of parts of hf's rows
   float* hf;         // [B, hf_stride]: by unit (by_unit: FFN) or by rank in the union (softmax)
   long long hf_stride;
   bool by_unit;
@@ -115,7 +117,11 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
   if (s.by_unit || sm_filter) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
-    s.wnorm_tiles = c.take<float>(filter_tiles(s.by_unit ? N : s.cap_u));
+    s.wnorm_tiles = c.take<float>(s.by_unit ? filter_tiles(N) : filter_rank_blocks(s.cap_u));
+    if (!s.by_unit) {
+      s.maxima = c.take<float>((size_t)B * kFilterMaxima);
+      s.refine_slots = c.take<char>(softmax_refine_slot_bytes(B));
+    }
     s.hf_stride = ((s.by_unit ? N : s.cap_u) + 3) / 4 * 4;  // rows start at multiples of 16 bytes
     s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
@@ -198,7 +204,7 @@ ScorerRefs scorer_of(const Layer* L) {
   return ScorerRefs{L->scorer_kind, L->q4, L->q4_scale, L->lr_a, L->lr_b, L->r, L->lr_a_scale, L->lr_b_scale};
 }
 
-// filter: the exact stage writes the fast bf16 approximations (launch_filter_bf16) instead of the fp64
+// filter: the exact stage writes the fast bf16 approximations (launch_filter_units) instead of the fp64
 // activations; the caller then refines around the selection threshold.
 // maxima_out (one token, int4 scorers): return after the scorer, with the number of maxima it left.
 int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const void* x, int B, int d, int N,
@@ -327,10 +333,12 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     if (!in_gather) HIRE_TRY(launch_bitmap_compact(s.bitmap, s.words, cand, s.counters, n_cand, nullptr, 0, st));
   }
   HIRE_STAGE(4, st);
-  if (filter)
-    HIRE_TRY(launch_filter_bf16(static_cast<const uint16_t*>(W), xb, B, d, cand, s.counters, s.cap_u, s.hf, s.hf_stride,
-                                s.hist, (in_gather || s.by_unit) ? &un : nullptr, N, s.by_unit, s.xnorm, s.wnorm_tiles, nullptr,
-                                st));
+  if (filter && s.by_unit)
+    HIRE_TRY(launch_filter_units(static_cast<const uint16_t*>(W), xb, B, d, s.bitmap, nullptr, N, s.hf, s.hf_stride, s.xnorm,
+                                 s.wnorm_tiles, nullptr, st));
+  else if (filter)
+    HIRE_TRY(launch_filter_ranks(static_cast<const uint16_t*>(W), xb, B, d, cand, s.counters, s.cap_u, s.hf, s.hf_stride,
+                                 s.hist, in_gather ? &un : nullptr, N, s.xnorm, s.wnorm_tiles, s.maxima, st));
   else if (B >= kMfmaMinBatch)
     HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(W), xb, B, d, cand, 0, s.counters, s.cap_u, relu, s.h,
                                     (long long)s.cap_u << gs, s.hist, in_gather ? &un : nullptr, gs, st));
@@ -436,9 +444,8 @@ int hire_debug_filter_stage(const void* W, const void* x, int B, int d, int rows
       d < 8 || d % 8 != 0 || !aligned(W, 16) || !aligned(x, 16))
     return HIRE_EINVAL;
   *err_c = gather_filter_error(B);
-  HIRE_TRY(launch_filter_bf16(static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(x), B, d, nullptr, rows_dev,
-                              rows, stored, rows, HistRefs{}, nullptr, rows, true, xnorm, nullptr, wnorm_max,
-                              static_cast<hipStream_t>(stream)));
+  HIRE_TRY(launch_filter_units(static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(x), B, d, nullptr, rows_dev,
+                               rows, stored, rows, xnorm, nullptr, wnorm_max, static_cast<hipStream_t>(stream)));
   return HIRE_OK;
 }
 
@@ -925,7 +932,10 @@ int hire_softmax_step(const hire_softmax_layer* L, const void* x, int B, int k, 
     sp.refine_d = d;
     sp.xnorm = s.xnorm;
     sp.wnorm_tiles = s.wnorm_tiles;
-    sp.wnorm_n = filter_tiles(s.cap_u);
+    sp.wnorm_n = filter_rank_blocks(s.cap_u);
+    sp.maxima = s.maxima;
+    sp.refine_slots = s.refine_slots;
+    sp.n_maxima = 4 * filter_rank_blocks(s.cap_u);
     sp.err_c = gather_filter_error(B);
     HIRE_TRY(launch_softmax_refine(sp, B, st));
   } else {

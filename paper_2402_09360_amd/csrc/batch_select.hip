@@ -2,7 +2,7 @@
 // workgroup of sixteen waves per token, rows of up to 32768 units:
 //
 //   k_keys_select  the k' largest scorer keys of a token -> its bits of the union bitmap
-//   k_refine       the k largest exact activations of a token from the filter stage's values (launch_filter_bf16,
+//   k_refine       the k largest exact activations of a token from the filter stage's values (launch_filter_units,
 //                  in unit order), recomputing in fp64 what lies around the threshold -> indices, values and the
 //                  (row, coefficient) list of the second layer
 //

@@ -111,7 +111,7 @@ struct SelectParams {
   float* prob_out;          // [B,k] softmax over the selected values (rank order only), optional
   uint32_t* bitmap;         // optional: bit i set (atomic or) for every selected position of any row
   uint32_t* window_misses;  // optional device counter: rows whose window histogram did not give the k-th largest
-  // Filter and refine (launch_softmax_refine only): vals are fp32 rows written by launch_filter_bf16, within
+  // Filter and refine (launch_softmax_refine only): vals are fp32 rows written by launch_filter_ranks, within
   // err_c |u| |x| of the logits; map lists the rows' classes.  The kernel recomputes in fp64
   // (<refine_w[map[i], :], refine_x[b, :]>) what can still be among the k largest.
   const uint16_t* refine_w;  // bf16 [rows, refine_d]
@@ -121,6 +121,9 @@ struct SelectParams {
   const float* wnorm_tiles;  // [wnorm_n]
   int wnorm_n;
   float err_c;
+  const float* maxima;      // [B, kFilterMaxima], n_maxima of them used: largest values of disjoint parts of the row
+  int n_maxima;
+  void* refine_slots;       // softmax_refine_slot_bytes(B) of scratch
   int nonneg;               // != 0: every value is known to be >= 0 (keys and activations after a ReLU); such rows
                             // of 1025..16384 entries in index order take a leaner kernel
   // Second layer: list_out (optional) receives for every row its k << gs selected units in ascending order, as
@@ -151,6 +154,7 @@ hipError_t launch_select_f64(const SelectParams& p, int B, hipStream_t s);
 // largest of those are returned in rank order (idx_out through map, val_out, prob_out).  Rows of at most
 // kSoftmaxRefineMaxRow fp32 entries, k <= kSoftmaxRefineMaxK.
 constexpr int kSoftmaxRefineMaxRow = 65536, kSoftmaxRefineMaxK = 512;
+size_t softmax_refine_slot_bytes(int B);
 hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s);
 
 // HiRE-Softmax for one token after launch_scorer_int4_fused on a long vocabulary (key histograms present): from the
@@ -189,7 +193,7 @@ bool batch_select_supported(int N, int k);
 hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
                               const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s);
 // The k largest activations relu(<W[j, :], x_b>) of every token among the bitmap's units, ties to the lower unit, from
-// the filter stage's values in unit order (launch_filter_bf16 by_unit).
+// the filter stage's values in unit order (launch_filter_units).
 constexpr int kRefineTokenMax = 8192;  // longest token staged in LDS
 struct RefineParams {
   const float* vals;        // [B, stride], 16-byte aligned rows
@@ -259,21 +263,28 @@ hipError_t launch_gather_dot_mfma(const uint16_t* W, const uint16_t* x, int B, i
                                   const HistRefs& hr, const UnionRefs* un, int gs, hipStream_t s);
 
 // Filter stage of the exact pre-activations for batches: values within gather_filter_error(B) * |u_j| * |x_b| of
-// phi(<u_j, x_b>) (bf16 matrix cores, fp32 segments of 32 or 64 products; see the kernel for what exactly is stored),
-// xnorm[b] = |x_b|, wnorm_tiles[filter_tiles(.)] = max |u_j| over the candidates of every workgroup (without it
-// *wnorm_max = the maximum over all as float bits, by atomics: cleared before).
-// by_unit (phi = ReLU): the candidates are the bits of un->bitmap (n_rows of them; without un: rows below *n_dev <=
-// n_cap), the value of unit j goes to h[b*stride_h + j], zeros where j is no candidate (also up to the stride,
-// which covers n_rows).
-// Otherwise (phi = identity): the candidate of rank t (of un's bitmap, or list with n_dev / n_cap) goes to
-// h[b*stride_h + t].  Rows only (no groups); n_rows: rows of W.
+// <u_j, x_b> (bf16 matrix cores, fp32 segments of 32 or 64 products; see the kernels for what exactly is stored),
+// xnorm[b] = |x_b|, wnorm_tiles = max |u_j| over the candidates of every workgroup.  Rows only (no groups).
 constexpr int filter_segment_steps(int B) { return B > 32 ? 2 : 1; }  // 32-product MFMA steps per fp32 segment
 inline float gather_filter_error(int B) { return (float)filter_segment_steps(B) * 0x1p-17f; }
-hipError_t launch_filter_bf16(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
-                              const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
-                              const UnionRefs* un, int n_rows, bool by_unit, float* xnorm, float* wnorm_tiles,
-                              uint32_t* wnorm_max, hipStream_t s);
-int filter_tiles(int n);  // workgroups for n rows (by_unit) or candidates
+// FFN (phi = ReLU): the candidates are the bits of the union bitmap over n_rows rows (whole 64-bit words; nullptr: rows
+// below *n_dev <= n_rows), the value of unit j goes to h[b*stride_h + j], zeros where j is no candidate (also up to
+// the stride, which covers n_rows).  wnorm_tiles [filter_tiles(n_rows)]; without it *wnorm_max receives the maximum
+// over all as float bits, by atomics (cleared before).
+int filter_tiles(int n);
+hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int d, const uint32_t* bitmap,
+                               const int32_t* n_dev, int n_rows, float* h, long long stride_h, float* xnorm,
+                               float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s);
+// Classifier (phi = identity): the candidate of rank t (of un's bitmap over n_rows classes, or list with n_dev) goes to
+// h[b*stride_h + t]; n_cap <= kSoftmaxRefineMaxRow.  wnorm_tiles [filter_rank_blocks(n_cap)]; maxima [B,
+// kFilterMaxima], 4 filter_rank_blocks(n_cap) of them per token: the largest values of as many disjoint groups of
+// candidates (-inf: of none).
+constexpr int kFilterMaxima = 1024;
+int filter_rank_blocks(int n_cap);
+hipError_t launch_filter_ranks(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,
+                               const int32_t* n_dev, int n_cap, float* h, long long stride_h, const HistRefs& hr,
+                               const UnionRefs* un, int n_rows, float* xnorm, float* wnorm_tiles, float* maxima,
+                               hipStream_t s);
 
 // out[b*stride_out + J] = sum_{l < 2^gs} |in[b*stride_in + J*2^gs + l]| for J < n, added in index order in the
 // input's type (the group activations of eq. (6)).

@@ -241,9 +241,10 @@ __device__ K wg_kth_largest(ForEach&& for_each, int n, int k, SelSharedT<NT>& sh
 constexpr int kLocateSteps = 32;       // 64-word steps per wave
 constexpr int kLocateStepsShort = 4;
 
-template <int NT, int STEPS = kLocateSteps>
-__device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap, int words, SelSharedT<NT>& sh,
-                                            int r0, int R, int32_t* out_sh) {
+// range(total, r0, R) names the wanted ranks once the total is known.
+template <int NT, int STEPS, typename Range>
+__device__ __forceinline__ int union_locate_range(const uint32_t* __restrict__ bitmap, int words, SelSharedT<NT>& sh,
+                                                  Range&& range, int32_t* out_sh) {
   constexpr int NW = NT / kWave;
   const int lane = lane_id(), w = wave_id();
   const int per_wave = ((words + NW - 1) / NW + kWave - 1) / kWave * kWave;
@@ -273,6 +274,8 @@ __device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap,
     base += u < w ? t : 0;
     total += t;
   }
+  int r0, R;
+  range(total, r0, R);
   if (base < r0 + R && base + mine > r0) {  // this wave's bits meet the wanted ranks (uniform over the wave)
     int run = base;
 #pragma unroll
@@ -298,6 +301,18 @@ __device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap,
   }
   __syncthreads();
   return total;
+}
+
+template <int NT, int STEPS = kLocateSteps>
+__device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap, int words, SelSharedT<NT>& sh,
+                                            int first, int count, int32_t* out_sh) {
+  return union_locate_range<NT, STEPS>(
+      bitmap, words, sh,
+      [&](int, int& r0, int& R) {
+        r0 = first;
+        R = count;
+      },
+      out_sh);
 }
 
 // The set bits of a bitmap as an ascending list, by one workgroup (NT threads, words <= 16 NT).

@@ -931,99 +931,215 @@ __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4
 // within err_c |w| |x| of the true ones.  With t~ the k-th largest stored value, every entry stored below
 // t~ - 2 err_c |x| max|w| has a true logit below that of k others, so only the entries at or above that mark -
 // k and a few - are recomputed in fp64 (a wave per row), ranked (value descending, position ascending) and the
-// first k kept, in rank order, with the softmax over them.  (A lower bound of t~ serves as well.)  The entries go through an LDS list of kSmList; rows
-// with more of them (many equal logits) take several rounds, each merged with the best k so far.
+// first k kept, in rank order, with the softmax over them.  A lower bound of t~ serves as well: the k-th largest of
+// the maxima that the filter stage left (up to 1024 per token; each is a value of an entry of its own), or the lower
+// edge of its fine bin.  With M maxima about -M ln(1 - k/M) entries reach it, 66 for k = 64 of 1024; the row itself
+// is passed over once, against the mark.  The entries go through an LDS list of kSmList; rows with more of them (many
+// equal logits, fewer maxima than k) take several rounds, each merged with the best k so far.
+// Measured at 64 tokens, 57600 entries: 13.7 + 7.0 us, 16 tokens, 16000 entries: 7.9 + 7.1.  One kernel with one
+// workgroup per token and a histogram of the whole row: 31 and 21 us, half of it the products and a ranking loop of
+// one thread per entry.
 constexpr int kSmList = 1024;
 static_assert(kSoftmaxRefineMaxRow / kSelThreads == 64, "one bit of a 64-bit mask per value of a thread");
 
-// kSmItems: values per thread (rows of up to 1024 kSmItems entries)
-template <int kSmItems>
+// Two kernels.  k_softmax_parts: every workgroup of a token takes an equal part of the row, finds the bound from the
+// maxima itself, recomputes its own part's entries at or above the mark and leaves them in its slots (position order).
+// k_softmax_refine (one workgroup per token) ranks them and takes the softmax.  One compute unit alone would be bound
+// by the fp64 products of some 75 rows (160 vector instructions per row and wave, 8 us at 64 tokens).  Rows with more
+// such entries than slots are left to the second kernel, which then does the whole work by itself, in rounds.
+constexpr int kSpThreads = 256;
+constexpr int kSpWinBins = 2048;  // bins of 2^kSpShift order keys
+constexpr int kSpShift = 16;
+struct SmEntry {
+  unsigned long long key;  // order key of the fp64 logit
+  int pos, pad;
+};
+// Slots of a token (kSmList in all, shared out evenly over its parts) behind the parts' counts.
+__host__ __device__ inline int softmax_parts(int B) { return B > 32 ? 16 : 32; }
+constexpr int kSpMaxParts = 32;
+size_t softmax_refine_slot_bytes(int B) { return (size_t)B * (kSpMaxParts * sizeof(int) + kSmList * sizeof(SmEntry)); }
+__device__ __forceinline__ int* sp_counts(void* slots, int b) { return static_cast<int*>(slots) + b * kSpMaxParts; }
+__device__ __forceinline__ SmEntry* sp_entries(void* slots, int B, int b) {
+  return reinterpret_cast<SmEntry*>(static_cast<int*>(slots) + B * kSpMaxParts) + (size_t)b * kSmList;
+}
+
+__global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
+  constexpr int NW = kSpThreads / kWave, kPer = kFilterMaxima / kSpThreads, kBins = kSpWinBins / kSpThreads;
+  __shared__ SelSharedT<kSpThreads> sh;
+  __shared__ uint32_t win[kSpWinBins], wave_a[NW], wave_b[NW];
+  __shared__ int l_pos[kSmList / 8];
+  __shared__ unsigned long long l_key[kSmList / 8];
+  const int part = (int)blockIdx.x, P = (int)gridDim.x, b = (int)blockIdx.y, B = (int)gridDim.y;
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int cap = kSmList / P;
+  float mx[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) mx[u] = p.maxima[(size_t)b * kFilterMaxima + min(tid + u * kSpThreads, p.n_maxima - 1)];
+  const float tile_norm = p.wnorm_tiles[min(tid, p.wnorm_n - 1)];  // wnorm_n <= 256
+  const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
+#pragma unroll
+  for (int u = 0; u < kBins; ++u) win[u * kSpThreads + tid] = 0u;
+  if (tid == 0) sh.list_n = 0;
+  uint32_t key[kPer], top = 0u;  // order keys of the maxima; none: 0, below every number
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    key[u] = tid + u * kSpThreads < p.n_maxima && mx[u] > -__builtin_inff() ? order_key(mx[u]) : 0u;
+    top = key[u] > top ? key[u] : top;
+  }
+  const uint32_t wa = wave_max(top), wb = wave_max(__float_as_uint(tile_norm));  // non-negative floats order like their bits
+  if (lane == 0) {
+    wave_a[w] = wa;
+    wave_b[w] = wb;
+  }
+  __syncthreads();
+  const int anchor = (int)(wave_max(lane < NW ? wave_a[lane] : 0u) >> kSpShift);
+  const float wn = __uint_as_float(wave_max(lane < NW ? wave_b[lane] : 0u));
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int s = anchor - (int)(key[u] >> kSpShift);
+    if (key[u] != 0u && s < kSpWinBins) atomicAdd(&win[s], 1u);
+  }
+  __syncthreads();
+  int c[kBins], mine = 0;
+#pragma unroll
+  for (int u = 0; u < kBins; ++u) {
+    c[u] = (int)win[kBins * tid + u];
+    mine += c[u];
+  }
+  int total, run = wg_scan_incl<kSpThreads>(mine, sh, &total) - mine;
+  if (run < p.k && p.k <= run + mine) {
+#pragma unroll
+    for (int u = 0; u < kBins; ++u) {
+      if (run < p.k && p.k <= run + c[u]) sh.bc_bin = kBins * tid + u;
+      run += c[u];
+    }
+  }
+  __syncthreads();
+  uint32_t mark_key = 1u;  // fewer than k maxima inside the window: every entry
+  if (total >= p.k) {      // uniform
+    const uint32_t floor_key = (uint32_t)max(anchor - sh.bc_bin, 0) << kSpShift;
+    const double hw = 2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001;
+    if (floor_key != 0u) mark_key = order_key(__double2float_rd((double)key_value(floor_key) - hw));
+  }
+  // this part's entries, in chunks of eight per thread: thread t of a chunk holds entries t, t + 256, ...
+  const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
+  const int per = (n + P - 1) / P, i_lo = min(n, part * per), i_hi = min(n, i_lo + per);
+  for (int i0 = i_lo; i0 < i_hi; i0 += 8 * kSpThreads) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = vals[min(i0 + u * kSpThreads + tid, n - 1)];  // clamped, unconditional
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * kSpThreads + tid;
+      if (i < i_hi && order_key(v[u]) >= mark_key) {
+        const int slot = atomicAdd(&sh.list_n, 1);
+        if (slot < cap) l_pos[slot] = i;
+      }
+    }
+  }
+  __syncthreads();
+  const int m = sh.list_n;
+  if (tid == 0) sp_counts(p.refine_slots, b)[part] = m;
+  if (m > cap) return;  // uniform: left to the second kernel
+  const int32_t* map = p.map + (size_t)b * p.map_stride;
+  const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
+  for (int e0 = w; e0 < m; e0 += 4 * NW) {  // a wave per row, four rows in flight per wave
+    const uint16_t* row[4];
+    int nr = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = e0 + u * NW;
+      if (e < m) nr = u + 1;
+      row[u] = p.refine_w + (size_t)map[l_pos[min(e, m - 1)]] * p.refine_d;
+    }
+    double s4[4];
+    wave_rows_dot_f64(row, nr, tok, p.refine_d, s4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (lane == 0 && u < nr) l_key[e0 + u * NW] = order_key(s4[u]);  // -0 counts as +0
+  }
+  __syncthreads();
+  SmEntry* out = sp_entries(p.refine_slots, B, b) + part * cap;
+  for (int t = tid; t < m; t += kSpThreads) out[t] = SmEntry{l_key[t], l_pos[t], 0};
+}
+
 __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) {
   __shared__ SelShared sh;
-  __shared__ __align__(16) uint32_t win[kWin];  // window histogram of the stored values' fine bins; then the list
-  static_assert(kSmList * (sizeof(int) + sizeof(double)) <= kWin * sizeof(uint32_t), "the list fits the window's memory");
-  double* l_val = reinterpret_cast<double*>(win);
+  __shared__ __align__(16) uint32_t win[kWin];  // window histogram of the maxima's fine bins; then the list
+  static_assert(kSmList * (sizeof(int) + sizeof(unsigned long long)) <= kWin * sizeof(uint32_t), "the list fits the window's memory");
+  static_assert(kFilterMaxima <= kSelThreads, "one maximum per thread");
+  unsigned long long* l_key = reinterpret_cast<unsigned long long*>(win);  // order keys of fp64 logits
   int* l_pos = reinterpret_cast<int*>(win + 2 * kSmList);
   __shared__ int b_pos[2][kSoftmaxRefineMaxK];
-  __shared__ double b_val[2][kSoftmaxRefineMaxK];
+  __shared__ unsigned long long b_key[2][kSoftmaxRefineMaxK];
   __shared__ int l_n;
+  __shared__ uint32_t wave_a[kSelWaves], wave_b[kSelWaves];
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
   const int k = p.k;
-  const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
-  const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
+  HIRE_TS(50);
   const int32_t* map = p.map + (size_t)b * p.map_stride;
-  // value i of thread t is entry t + 1024 i; order keys, 0 (below every number) past the row's end
-  uint32_t key[kSmItems];
-  static_assert(kSmItems % 16 == 0 && kSmItems <= 64, "whole batches of loads");
-#pragma unroll
-  for (int i0 = 0; i0 < kSmItems; i0 += 16) {
-    float v[16];
-    if (kSelThreads * i0 < n) {  // uniform: short rows skip the batches past their end
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = vals[min(tid + kSelThreads * (i0 + u), n - 1)];  // clamped, unconditional
+  const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
+  // what the parts left: thread t holds slot t; the valid ones move together in slot order
+  const int P = softmax_parts((int)gridDim.x), cap = kSmList / P;
+  const int have_n = sp_counts(p.refine_slots, b)[min(tid / cap, P - 1)];
+  const SmEntry entry = sp_entries(p.refine_slots, (int)gridDim.x, b)[tid];
+  const bool mine_valid = tid % cap < have_n;
+  unsigned long long pending = 0ull;  // bit i: value i has to be recomputed and has not been listed yet
+  int ready = 0;                      // entries the parts have recomputed
+  if (!__syncthreads_or(have_n > cap)) {
+    const uint64_t vm = __ballot(mine_valid);
+    if (lane == 0) wave_a[w] = (uint32_t)__popcll(vm);
+    __syncthreads();
+    const int incl = wave_scan_incl(lane < kSelWaves ? (int)wave_a[lane] : 0);
+    ready = __builtin_amdgcn_readlane(incl, kSelWaves - 1);
+    const int ws = __builtin_amdgcn_readfirstlane(w);
+    const int at = (ws > 0 ? __builtin_amdgcn_readlane(incl, ws - 1) : 0) + mask_prefix(vm);
+    if (mine_valid) {
+      l_key[at] = entry.key;
+      l_pos[at] = entry.pos;
     }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) key[i0 + u] = tid + kSelThreads * (i0 + u) < n ? order_key(v[u]) : 0u;
-  }
-  // A lower bound of the k-th largest stored value is enough (a lower mark only lists a few more entries): the
-  // lower edge of the fine bin (2^14 consecutive order keys) that holds it, found by walking a window histogram of
-  // the 8192 bins below the row's largest key; if fewer than k keys lie inside, the next 8192 bins, and so on.
-  uint32_t mx = 0u;
-#pragma unroll
-  for (int i = 0; i < kSmItems; ++i) mx = key[i] > mx ? key[i] : mx;
-  mx = wg_max_u32(mx, sh);
-  uint32_t wn = 0u;  // largest row norm: non-negative floats order like their bits
-  for (int i = tid; i < p.wnorm_n; i += kSelThreads) wn = max(wn, __float_as_uint(p.wnorm_tiles[i]));
-  wn = wg_max_u32(wn, sh);
-  int anchor = (int)(mx >> kFineShift), above = 0;
-  uint32_t floor_key = 0u;  // 0: every entry of the row
-  while (true) {  // uniform
-    __syncthreads();  // the window's readers of the round before are done
+  } else {
+    const float mine_max = p.maxima[(size_t)b * kFilterMaxima + min(tid, p.n_maxima - 1)];
+    float tile_norm = p.wnorm_tiles[min(tid, p.wnorm_n - 1)];  // wnorm_n <= 256
+    const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
+    const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
     {
       uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
       z[0] = z[1] = make_uint4(0, 0, 0, 0);
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSmItems; ++i) {
-      const uint32_t slot = (uint32_t)(anchor - (int)(key[i] >> kFineShift));
-      if (key[i] != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
+    // order key of this thread's maximum; none: 0, below every number
+    const uint32_t key = tid < p.n_maxima && mine_max > -__builtin_inff() ? order_key(mine_max) : 0u;
+    const uint32_t wa = wave_max(key), wb = wave_max(__float_as_uint(tile_norm));  // non-negative floats order like their bits
+    if (lane == 0) {
+      wave_a[w] = wa;
+      wave_b[w] = wb;
     }
     __syncthreads();
-    const uint4 c0 = reinterpret_cast<const uint4*>(win)[2 * tid], c1 = reinterpret_cast<const uint4*>(win)[2 * tid + 1];
-    const int c[8] = {(int)c0.x, (int)c0.y, (int)c0.z, (int)c0.w, (int)c1.x, (int)c1.y, (int)c1.z, (int)c1.w};
-    int mine = 0;
+    const uint32_t anchor = wave_max(lane < kSelWaves ? wave_a[lane] : 0u) >> kFineShift;
+    const float wn = __uint_as_float(wave_max(lane < kSelWaves ? wave_b[lane] : 0u));
+    const uint32_t slot = anchor - (key >> kFineShift);
+    if (key != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
+    __syncthreads();
+    WinRegs<kSelThreads> wr;
+    wr.issue(win);
+    const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
+    HIRE_TS(51);
+    // fewer than k maxima inside the window (few candidates, widely spread values): every entry is recomputed
+    const uint32_t floor_key = wk.found ? (anchor - (uint32_t)wk.slot) << kFineShift : 0u;
+    const double mark = (floor_key != 0u ? (double)key_value(floor_key) : 0.0) -
+                        2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001;
+    const uint32_t mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
+    // value i of thread t is entry t + 1024 i
+    for (int i0 = 0; kSelThreads * i0 < n; i0 += 16) {  // uniform
+      float v[16];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) mine += c[q];
-    int total;
-    const int incl = wg_scan_incl<kSelThreads>(mine, sh, &total);
-    const int need = k - above;  // >= 1
-    if (total >= need) {         // uniform: one thread holds the bin of the need-th key
-      int run = incl - mine;
-      if (run < need && need <= incl) {
+      for (int u = 0; u < 16; ++u) v[u] = vals[min(tid + kSelThreads * (i0 + u), n - 1)];  // clamped, unconditional
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (run < need && need <= run + c[q]) sh.bc_bin = 8 * tid + q;
-          run += c[q];
-        }
-      }
-      __syncthreads();
-      const int bin = anchor - sh.bc_bin;  // >= 0
-      floor_key = bin > 0 ? (uint32_t)bin << kFineShift : 0u;
-      break;
+      for (int u = 0; u < 16; ++u)
+        if (order_key(v[u]) >= mark_key && tid + kSelThreads * (i0 + u) < n) pending |= 1ull << (i0 + u);
     }
-    above += total;
-    anchor -= kWin;
-    if (anchor < 0) break;  // cannot happen with k <= n: every key lies in some window
+    HIRE_TS(52);
   }
-  const double mark = (floor_key != 0u ? (double)key_value(floor_key) : -__builtin_huge_val()) -
-                      2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)__uint_as_float(wn) * 1.000001;
-  const uint32_t mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
-  unsigned long long pending = 0ull;  // bit i: value i has to be recomputed and has not been listed yet
-#pragma unroll
-  for (int i = 0; i < kSmItems; ++i)
-    if (key[i] != 0u && key[i] >= mark_key) pending |= 1ull << i;
-  const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
   int have = 0, cur = 0;  // entries of the best list so far, and which of its two copies holds them
   while (true) {  // uniform
     __syncthreads();  // the list and the counters of the round before have been read
@@ -1038,79 +1154,89 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
       pending &= pending - 1ull;
     }
     __syncthreads();
-    const int listed = min(l_n, room);
-    for (int e0 = w; e0 < listed; e0 += 4 * kSelWaves) {  // a wave per row, four rows in flight per wave
+    HIRE_TS(53);
+    const int fresh = min(l_n, room), listed = ready > 0 ? ready : fresh;
+    for (int e0 = w; e0 < fresh; e0 += 4 * kSelWaves) {  // a wave per row, four rows in flight per wave
       const uint16_t* row[4];
       int nr = 0;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int e = e0 + u * kSelWaves;
-        if (e < listed) nr = u + 1;
-        row[u] = p.refine_w + (size_t)map[l_pos[min(e, listed - 1)]] * p.refine_d;
+        if (e < fresh) nr = u + 1;
+        row[u] = p.refine_w + (size_t)map[l_pos[min(e, fresh - 1)]] * p.refine_d;
       }
       double s4[4];
       wave_rows_dot_f64(row, nr, tok, p.refine_d, s4);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (lane == 0 && u < nr) l_val[e0 + u * kSelWaves] = s4[u] == 0.0 ? 0.0 : s4[u];  // -0 -> +0
+        if (lane == 0 && u < nr) l_key[e0 + u * kSelWaves] = order_key(s4[u]);  // -0 counts as +0
     }
-    // the best so far join the list, then every entry is ranked among all of them
+    HIRE_TS(54);
+    // the best so far join the list, then every entry is ranked among all of them, sixteen lanes per entry
     for (int t = tid; t < have; t += kSelThreads) {
       l_pos[listed + t] = b_pos[cur][t];
-      l_val[listed + t] = b_val[cur][t];
+      l_key[listed + t] = b_key[cur][t];
     }
     __syncthreads();
-    const int m = listed + have;
-    if (tid < m) {
-      const double mine = l_val[tid];
-      const int mine_pos = l_pos[tid];
+    const int m = listed + have, sub = tid & 15;
+    for (int t0 = 0; t0 < m; t0 += kSelThreads / 16) {  // uniform
+      const int t = min(t0 + tid / 16, m - 1);
+      const uint64_t mine = l_key[t];
+      const int mine_pos = l_pos[t];
       int rank = 0;
-      for (int u0 = 0; u0 < m; u0 += 8) {  // eight LDS reads in flight
-        double ov[8];
-        int op[8];
+      for (int u0 = sub; u0 < m; u0 += 64) {  // four LDS reads in flight
+        uint64_t ok[4];
+        int op[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          ov[j] = l_val[min(u0 + j, m - 1)];
-          op[j] = l_pos[min(u0 + j, m - 1)];
+        for (int j = 0; j < 4; ++j) {
+          ok[j] = l_key[min(u0 + 16 * j, m - 1)];
+          op[j] = l_pos[min(u0 + 16 * j, m - 1)];
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          rank += (u0 + j < m) && (ov[j] > mine || (ov[j] == mine && op[j] < mine_pos));
+        for (int j = 0; j < 4; ++j) rank += u0 + 16 * j < m && ranks_ahead(ok[j], op[j], mine, mine_pos) ? 1 : 0;
       }
-      if (rank < k) {
+      auto add = [](int a, int b) { return a + b; };
+      rank = add(rank, dpp_move<0x111, 0xF>(0, rank));  // the row's last lane holds the sum of its sixteen
+      rank = add(rank, dpp_move<0x112, 0xF>(0, rank));
+      rank = add(rank, dpp_move<0x114, 0xF>(0, rank));
+      rank = add(rank, dpp_move<0x118, 0xF>(0, rank));
+      if (sub == 15 && t0 + tid / 16 < m && rank < k) {
         b_pos[cur ^ 1][rank] = mine_pos;
-        b_val[cur ^ 1][rank] = mine;
+        b_key[cur ^ 1][rank] = mine;
       }
     }
     have = min(k, m);
     cur ^= 1;
     if (!__syncthreads_or(pending != 0ull)) break;
   }
+  HIRE_TS(55);
   // the k survivors in rank order; softmax: exp(z - zmax) / sum
-  const double zmax = b_val[cur][0];
+  const double zmax = key_value((uint64_t)b_key[cur][0]);
   double part = 0.0;
-  for (int t = tid; t < k; t += kSelThreads) part += exp(b_val[cur][t] - zmax);
+  for (int t = tid; t < k; t += kSelThreads) part += exp(key_value((uint64_t)b_key[cur][t]) - zmax);
   part = wave_sum(part);
   if (lane == 0) sh.red_a[w] = (unsigned long long)__double_as_longlong(part);
   __syncthreads();
   double sum = 0.0;
   for (int u = 0; u < kSelWaves; ++u) sum += __longlong_as_double((long long)sh.red_a[u]);
   for (int t = tid; t < k; t += kSelThreads) {
-    const double z = b_val[cur][t];
+    const double z = key_value((uint64_t)b_key[cur][t]);
     if (p.idx_out) p.idx_out[(size_t)b * k + t] = map[b_pos[cur][t]];
     if (p.val_out) p.val_out[(size_t)b * k + t] = (float)z;
     if (p.prob_out) p.prob_out[(size_t)b * k + t] = (float)(exp(z - zmax) / sum);
   }
+  HIRE_TS(56);
 }
 
 hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s) {
   const int cap = p.n_dev ? p.n_cap : p.n;
   if (cap < 1 || cap > kSoftmaxRefineMaxRow || p.k < 1 || p.k > kSoftmaxRefineMaxK || !p.refine_w || !p.refine_x ||
-      p.refine_d % 8 != 0 || !p.map || !p.xnorm || !p.wnorm_tiles || !p.vals)
+      p.refine_d % 8 != 0 || !p.map || !p.xnorm || !p.wnorm_tiles || !p.maxima || !p.refine_slots || p.n_maxima > kFilterMaxima ||
+      p.wnorm_n > kSpThreads || p.n_maxima < 1 || p.wnorm_n < 1 || !p.vals)
     return hipErrorInvalidValue;
-  if (cap <= 16 * kSelThreads) return launch(k_softmax_refine<16>, dim3(B), dim3(kSelThreads), 0, s, p);
-  if (cap <= 32 * kSelThreads) return launch(k_softmax_refine<32>, dim3(B), dim3(kSelThreads), 0, s, p);
-  return launch(k_softmax_refine<64>, dim3(B), dim3(kSelThreads), 0, s, p);
+  const hipError_t e = launch(k_softmax_parts, dim3(softmax_parts(B), B), dim3(kSpThreads), 0, s, p);
+  if (e != hipSuccess) return e;
+  return launch(k_softmax_refine, dim3(B), dim3(kSelThreads), 0, s, p);
 }
 
 // ---------------------------------------------------------------------------

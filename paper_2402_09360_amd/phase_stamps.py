@@ -45,7 +45,7 @@ BATCH = [
       (47, "outputs written")]),
 ]
 GATHER = [
-    ("k_filter_bf16 (filter stage, first workgroup)",
+    ("k_filter_units (filter stage, first workgroup)",
      [(55, "kernel start"), (56, "candidates known"), (57, "all stages done"),
       (58, "norms, stored values, maximum written")]),
 ]

@@ -860,6 +860,18 @@ def test_softmax_step_filter_and_refine(hire, oracle, d, c, B, k, kp):
     assert np.array_equal(exact["top_idx"], got["top_idx"])
 
 
+@pytest.mark.parametrize("d,c,B,k,kp", [
+    (96, 60001, 64, 33, 1000),    # several tiles per workgroup, a row shorter than a stage
+    (288, 33000, 17, 512, 2000),  # the largest k: about as many maxima above the bound as there are
+    (2048, 20000, 40, 64, 1200),  # three token tiles, tiles of the union that end between groups of sixteen
+])
+def test_softmax_step_filter_by_rank(hire, oracle, d, c, B, k, kp):
+    log(f"softmax_step filter by rank d={d} c={c} B={B} k={k} kp={kp}")
+    W = I.classifier(155 + B, c, d)
+    layer, scorer = T.make_softmax_layer(W)
+    T.check_softmax(layer, scorer, W, I.tokens(156 + B, B, d), k, kp)
+
+
 @pytest.mark.parametrize("copies", [40, 3000])
 def test_softmax_step_filter_and_refine_equal_logits(hire, oracle, copies):
     """Classes repeated many times: blocks of exactly equal logits around the k-th, settled by index; 3000 copies
