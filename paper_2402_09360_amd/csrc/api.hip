@@ -959,9 +959,14 @@ int topk_select(const float* scores, int B, int N, int k, int flags, int32_t* id
     float* val_tmp = reinterpret_cast<float*>(reinterpret_cast<char*>(idx_tmp) +
                                               align_up((size_t)B * k * sizeof(int32_t)));
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const unsigned long long sig = layout_signature(2 /* neither scorer: a bare selection */, B, 0, N, 0, k, 0, flags);
+    if (topk_rows_supported(N, k)) {
+      HIRE_TRY(launch_topk_rows(scores, B, N, k, (flags & HIRE_RELU) ? 1 : 0, rank ? 1 : 0, idx_out, val_out, base, body,
+                                sig, st));
+      return HIRE_OK;
+    }
     HIRE_TRY(launch_topk_long(scores, B, N, k, (flags & HIRE_RELU) ? 1 : 0, rank ? idx_tmp : idx_out,
-                              rank ? val_tmp : val_out, base, body,
-                              layout_signature(2 /* neither scorer: a bare selection */, B, 0, N, 0, k, 0, flags), st));
+                              rank ? val_tmp : val_out, base, body, sig, st));
     if (rank) {  // all k entries of the index-ordered list, in rank order
       SelectParams sp{};
       sp.vals = val_tmp;  // max(., 0) already applied where asked for

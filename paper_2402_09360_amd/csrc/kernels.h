@@ -148,6 +148,10 @@ hipError_t launch_select_f32(const SelectParams& p, int B, hipStream_t s);
 size_t topk_long_workspace_bytes(int B, int N);
 hipError_t launch_topk_long(const float* scores, int B, int N, int k, int relu, int32_t* idx_out, float* val_out,
                             void* general_header, void* body, unsigned long long sig, hipStream_t s);
+// The same for few entries of long rows, in either order, without histograms (topk_rows_supported): the same places.
+bool topk_rows_supported(int N, int k);
+hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, int rank_order, int32_t* idx_out,
+                            float* val_out, void* general_header, void* body, unsigned long long sig, hipStream_t s);
 hipError_t launch_select_f64(const SelectParams& p, int B, hipStream_t s);
 // Filter and refine for the classifier (phi = identity, signed values, rank order, softmax over the k survivors): every
 // entry within 2 * err_c * xnorm[b] * *wnorm_max below the k-th largest stored value is recomputed in fp64 and the k

@@ -340,4 +340,51 @@ __device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, 
   return base;
 }
 
+// Ranks of n <= kBucketMax entries in a total order whose keys are get(id), larger ahead, id < n; ahead(a, b) says
+// whether entry a comes before entry b (consulted between entries of one bin only).  The keys between the smallest and
+// the largest go to 2048 equal bins, a scan gives every bin's first rank, the entries are listed bin by bin and each
+// counts those ahead of it inside its bin: a few instead of n comparisons per entry (all of them only where all keys
+// crowd into one bin).  emit(id, rank) is called once per entry.  bins: 2 * kSelBins + kBucketMax words of LDS.
+// All threads call this; keys and entries must be visible (the first step is a barrier).
+constexpr int kBucketMax = 4096;
+template <typename K, typename Get, typename Ahead, typename Emit>
+__device__ __forceinline__ void bucket_ranks(int n, Get&& get, Ahead&& ahead, uint32_t* bins, SelShared& sh, Emit&& emit) {
+  static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
+  uint32_t* cursor = bins + kSelBins;
+  int* list = reinterpret_cast<int*>(bins + 2 * kSelBins);
+  const int tid = (int)threadIdx.x;
+  K lo = ~(K)0, hi = 0;
+  bins[tid] = bins[tid + kSelThreads] = 0u;
+  __syncthreads();
+  for (int id = tid; id < n; id += kSelThreads) {
+    const K k = get(id);
+    lo = k < lo ? k : lo;
+    hi = k > hi ? k : hi;
+  }
+  wg_minmax(lo, hi, sh);
+  const int shift = hi > lo ? max(0, ilog2_u64((uint64_t)(hi - lo)) + 1 - 11) : 0;
+  auto bin_of = [&](K k) { return (int)((hi - k) >> shift); };
+  for (int id = tid; id < n; id += kSelThreads) atomicAdd(&bins[bin_of(get(id))], 1u);
+  __syncthreads();
+  const int c0 = (int)bins[2 * tid], c1 = (int)bins[2 * tid + 1];
+  const int start = wg_scan_incl(c0 + c1, sh) - (c0 + c1);  // a barrier inside: every thread has read its counters
+  bins[2 * tid] = cursor[2 * tid] = (uint32_t)start;
+  bins[2 * tid + 1] = cursor[2 * tid + 1] = (uint32_t)(start + c0);
+  __syncthreads();
+  for (int id = tid; id < n; id += kSelThreads) list[atomicAdd(&cursor[bin_of(get(id))], 1u)] = id;
+  __syncthreads();
+  for (int id = tid; id < n; id += kSelThreads) {
+    const int b = bin_of(get(id)), first = (int)bins[b], end = (int)cursor[b];
+    int rank = first;
+    for (int u0 = first; u0 < end; u0 += 4) {  // four LDS reads in flight
+      int other[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) other[j] = list[min(u0 + j, end - 1)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) rank += u0 + j < end && ahead(other[j], id) ? 1 : 0;
+    }
+    emit(id, rank);
+  }
+}
+
 }  // namespace hire

@@ -366,28 +366,30 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
   V my_val[kPerThread];
 #pragma unroll
   for (int q = 0; q < kPerThread; ++q) {
-    const int t = (int)threadIdx.x + q * kSelThreads;
     my_rank[q] = -1;
     my_val[q] = (V)0;
-    if (t < k) {
-      const K mine = rk_key[t];
-      int rank = spread ? rk_rank[t] : 0;
-      for (int u0 = 0; u0 < (spread ? 0 : k); u0 += 8) {  // eight LDS reads in flight
-        K other[8];
+  }
+  auto put = [&](int t, int rank) {
+    const int i = rk_pos[t];
+    const V v = key_value(rk_key[t]);
+    if (p.idx_out) p.idx_out[(size_t)b * k + rank] = map ? map[i] : i;
+    if (p.pos_out) p.pos_out[(size_t)b * k + rank] = i;
+    if (p.val_out) p.val_out[(size_t)b * k + rank] = (float)v;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) other[j] = rk_key[min(u0 + j, k - 1)];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)  // the list is in index order, so u < t is "lower index"
-          rank += (u0 + j < k) && ((other[j] > mine) || (other[j] == mine && u0 + j < t));
+    for (int q = 0; q < kPerThread; ++q)
+      if (t == (int)threadIdx.x + q * kSelThreads) {
+        my_rank[q] = rank;
+        my_val[q] = v;
       }
-      const int i = rk_pos[t];
-      const V v = key_value(mine);
-      if (p.idx_out) p.idx_out[(size_t)b * k + rank] = map ? map[i] : i;
-      if (p.pos_out) p.pos_out[(size_t)b * k + rank] = i;
-      if (p.val_out) p.val_out[(size_t)b * k + rank] = (float)v;
-      my_rank[q] = rank;
-      my_val[q] = v;
-    }
+  };
+  if (spread) {
+    if ((int)threadIdx.x < k) put((int)threadIdx.x, rk_rank[threadIdx.x]);
+  } else {  // many entries: by bins of their keys (1024 entries: 3 us; every entry against every other: 66)
+    static_assert(2 * kSelBins + kBucketMax <= kHistWindow && kRankMax <= kBucketMax, "the bins reuse the window's memory");
+    bucket_ranks<K>(
+        k, [&](int t) { return rk_key[t]; },
+        [&](int o, int t) { return rk_key[o] > rk_key[t] || (rk_key[o] == rk_key[t] && o < t); },  // index order
+        win, sh, put);
   }
   HIRE_TS(34);
   if (!p.prob_out) return;
@@ -754,6 +756,164 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
     mr.hdr->layout_b = (uint32_t)B;
     mr.hdr->cookie = kMultiCookie;
   }
+}
+
+// ---------------------------------------------------------------------------
+// topk_select on long rows with few entries wanted (rows beyond 32768, k <= 2048): three kernels, without a histogram
+// of the row.
+//
+//   k_tk_maxima  4096 disjoint groups of every row, interleaved (entry i belongs to group i % 4096): their largest keys
+//   k_tk_gather  every workgroup of a row bounds the k-th largest key from below by the k-th largest of the maxima (the
+//                lower edge of its fine bin: each maximum is a key of its own, so at least k keys reach it) and appends
+//                its own keys at or above the bound to the row's list: about -4096 ln(1 - k / 4096) of them, 1180 for
+//                k = 1024, in any order
+//   k_tk_final   one workgroup per row ranks the list by (key descending, index ascending); the first k are the result,
+//                in that order or once more ranked by index
+//
+// The list is counted, not trusted: a row that has no bound (its maxima spread beyond the window) or more such keys
+// than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
+// largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
+// Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
+// Measured for 16 rows of 256000, k = 1024, rank order: 21.6 us (6.3 + 9.5 + 6.4); the histogram route below took 45, of it 9 for
+// the ranking pass.
+constexpr int kTkGroups = 4096;
+constexpr int kTkMaxK = 2048;
+constexpr int kTkMaxThreads = 256;
+constexpr int kTkKeys = 16;  // keys per thread of the gathering kernel
+static_assert(kTkGroups == kWgMaxSlots && kAmbCap == kBucketMax, "the maxima and the list use the histogram route's places");
+static_assert(kTkMaxK * (4 + 2 * 4) <= kAmbCap * (int)sizeof(AmbEntry), "rank order from memory: the list's LDS");
+
+__device__ __forceinline__ uint32_t row_key(float v, int relu) { return order_key(relu && !(v > 0.0f) ? 0.0f : v); }
+
+// Grid (16, B).  Also the sequence's first kernel: empties the rows' lists and checks the layout signature.
+__global__ __launch_bounds__(kTkMaxThreads) void k_tk_maxima(const float* __restrict__ keys, int N, int relu,
+                                                             MultiRegion mr, GeneralHeader* gh, unsigned long long sig) {
+  if (blockIdx.x == 0 && blockIdx.y == 0) general_header_check(gh, sig);
+  const int b = (int)blockIdx.y, g = (int)blockIdx.x * kTkMaxThreads + (int)threadIdx.x;
+  const float* row = keys + (size_t)b * N;
+  uint32_t m = 0u;
+  for (int i0 = g; i0 < N; i0 += 16 * kTkGroups) {  // sixteen loads in flight; those past the end repeat the first
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = row[i0 + u * kTkGroups < N ? i0 + u * kTkGroups : i0];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const uint32_t k = row_key(v[u], relu);
+      m = k > m ? k : m;
+    }
+  }
+  mr.wgmax[(size_t)b * kWgMaxSlots + g] = m;
+  if (g == 0) mr.amb_n[b] = 0u;
+}
+
+// Grid (ceil(N / 16384), B).
+__global__ __launch_bounds__(kSelThreads) void k_tk_gather(const float* __restrict__ keys, int N, int k, int relu,
+                                                           MultiRegion mr) {
+  __shared__ SelShared sh;
+  __shared__ __align__(16) uint32_t win[kWin];
+  __shared__ int base_sh;
+  const int b = (int)blockIdx.y, tid = (int)threadIdx.x;
+  const float* row = keys + (size_t)b * N;
+  const int i0 = (int)blockIdx.x * (kSelThreads * kTkKeys);
+  const uint4 mx4 = reinterpret_cast<const uint4*>(mr.wgmax + (size_t)b * kWgMaxSlots)[tid];
+  float v[kTkKeys];
+#pragma unroll
+  for (int e = 0; e < kTkKeys; ++e) v[e] = row[min(i0 + e * kSelThreads + tid, N - 1)];
+  {
+    uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
+    z[0] = z[1] = make_uint4(0, 0, 0, 0);
+  }
+  const uint32_t mx[4] = {mx4.x, mx4.y, mx4.z, mx4.w};
+  const uint32_t top = wg_max_u32(max(max(mx[0], mx[1]), max(mx[2], mx[3])), sh);  // barriers inside: win is clear
+  const uint32_t anchor = top >> kFineShift;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t slot = anchor - (mx[q] >> kFineShift);
+    if (slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
+  }
+  __syncthreads();
+  WinRegs<kSelThreads> wr;
+  wr.issue(win);
+  const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
+  if (!wk.found) {  // uniform
+    if (blockIdx.x == 0 && tid == 0) mr.amb_n[b] = kAmbCap + 1;
+    return;
+  }
+  const uint32_t bound = max((anchor - (uint32_t)wk.slot) << kFineShift, 1u);  // key 0 stands for "past the end"
+  uint32_t key[kTkKeys];
+  int c = 0;
+#pragma unroll
+  for (int e = 0; e < kTkKeys; ++e) {
+    key[e] = i0 + e * kSelThreads + tid < N ? row_key(v[e], relu) : 0u;
+    c += key[e] >= bound ? 1 : 0;
+  }
+  int total;
+  const int incl = wg_scan_incl(c, sh, &total);
+  if (total == 0) return;  // uniform
+  if (tid == 0) base_sh = (int)atomicAdd(&mr.amb_n[b], (uint32_t)total);
+  __syncthreads();
+  int at = base_sh + incl - c;
+#pragma unroll
+  for (int e = 0; e < kTkKeys; ++e)
+    if (key[e] >= bound) {
+      if (at < kAmbCap) mr.amb[(size_t)b * kAmbCap + at] = AmbEntry{key[e], i0 + e * kSelThreads + tid};
+      ++at;
+    }
+}
+
+__global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restrict__ keys, int B, int N, int k, int relu,
+                                                          int rank_order, MultiRegion mr, int32_t* __restrict__ idx_out,
+                                                          float* __restrict__ val_out) {
+  __shared__ SelShared sh;
+  __shared__ __align__(16) uint32_t bins[kHistWindow];
+  __shared__ __align__(16) AmbEntry list[kAmbCap];
+  __shared__ AmbEntry chosen[kTkMaxK];
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x;
+  const int n = (int)mr.amb_n[b];
+  int32_t* idx = idx_out + (size_t)b * k;
+  float* val = val_out ? val_out + (size_t)b * k : nullptr;
+  if (b == 0 && tid == 0 && !multi_hist_ok(mr.hdr, B)) {  // the workspace has taken this layout
+    mr.hdr->fallbacks = 0u;
+    mr.hdr->stamps += 1u;
+    mr.hdr->layout_b = (uint32_t)B;
+    mr.hdr->cookie = kMultiCookie;
+  }
+  if (n < k || n > kAmbCap) {  // uniform
+    SelectParams sp{};
+    sp.vals = keys;
+    sp.stride = N;
+    sp.n = N;
+    sp.n_cap = N;
+    sp.k = k;
+    sp.relu = relu;
+    sp.rank_order = rank_order;
+    sp.idx_out = idx_out;
+    sp.val_out = val_out;
+    select_row<float, 0>(sp, b, sh, reinterpret_cast<unsigned long long*>(list), bins);
+    if (tid == 0) atomicAdd(&mr.hdr->fallbacks, 1u);
+    return;
+  }
+  for (int i = tid; i < n; i += kSelThreads) list[i] = mr.amb[(size_t)b * kAmbCap + i];
+  bucket_ranks<uint32_t>(
+      n, [&](int i) { return list[i].okey; },
+      [&](int o, int i) { return list[o].okey > list[i].okey || (list[o].okey == list[i].okey && list[o].idx < list[i].idx); },
+      bins, sh, [&](int i, int rank) {
+        if (rank >= k) return;
+        if (rank_order) {
+          idx[rank] = list[i].idx;
+          if (val) val[rank] = key_value(list[i].okey);
+        } else {
+          chosen[rank] = list[i];
+        }
+      });
+  if (rank_order) return;
+  __syncthreads();
+  bucket_ranks<uint32_t>(
+      k, [&](int i) { return ~(uint32_t)chosen[i].idx; }, [&](int o, int i) { return chosen[o].idx < chosen[i].idx; }, bins, sh,
+      [&](int i, int rank) {
+        idx[rank] = chosen[i].idx;
+        if (val) val[rank] = key_value(chosen[i].okey);
+      });
 }
 
 // ---------------------------------------------------------------------------
@@ -1314,6 +1474,20 @@ hipError_t launch_resolve_compact(const float* keys, int B, int N, int kprime, c
   if (e != hipSuccess || list_out == nullptr) return e;  // no list wanted: the gather compacts the bitmap itself
   return launch(k_union_compact, dim3(1), dim3(kSelThreads), 0, s, B, mr, bitmap, words, list_out, count_out,
                 count_out2, zero_ptr, zero_words);
+}
+
+bool topk_rows_supported(int N, int k) { return N > 8 * kTkGroups && k <= kTkMaxK; }
+
+hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, int rank_order, int32_t* idx_out,
+                            float* val_out, void* general_header, void* body, unsigned long long sig, hipStream_t s) {
+  GeneralHeader* gh = static_cast<GeneralHeader*>(general_header);
+  const MultiRegion mr = carve_multi(&gh->multi, body, B);
+  hipError_t e = launch(k_tk_maxima, dim3(kTkGroups / kTkMaxThreads, B), dim3(kTkMaxThreads), 0, s, scores, N, relu, mr, gh,
+                        sig);
+  if (e != hipSuccess) return e;
+  const int chunks = (N + kSelThreads * kTkKeys - 1) / (kSelThreads * kTkKeys);
+  if ((e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr)) != hipSuccess) return e;
+  return launch(k_tk_final, dim3(B), dim3(kSelThreads), 0, s, scores, B, N, k, relu, rank_order, mr, idx_out, val_out);
 }
 
 size_t topk_long_workspace_bytes(int B, int N) {
