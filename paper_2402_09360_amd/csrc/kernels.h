@@ -9,14 +9,18 @@
 
 namespace hire {
 
-// Launch and report this launch's status only: the sticky "last error" is cleared first, because other users
-// of the runtime in the same process (PyTorch) may have left an unrelated one behind.
+// Launch and report this launch's status only.  One runtime call: the launch syntax pushes and pops its configuration
+// and would need the sticky "last error" cleared before and read after, because other users of the runtime in the
+// same process (PyTorch) may have left an unrelated one behind.
 template <typename... Params, typename... Args>
 inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_t lds, hipStream_t stream,
                          Args... args) {
-  (void)hipGetLastError();
-  kernel<<<grid, block, lds, stream>>>(args...);
-  return hipGetLastError();
+  return [&](Params... params) {
+    void* pointers[] = {const_cast<void*>(static_cast<const void*>(&params))...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, pointers, lds, stream);
+    if (e != hipSuccess) (void)hipGetLastError();  // reported to the caller, not left behind
+    return e;
+  }(static_cast<Params>(args)...);
 }
 
 // Dynamic LDS beyond the default limit needs the kernel's attribute raised before the launch.  `raised_to` is a

@@ -129,13 +129,26 @@ def _check(code: int, where: str):
         raise HireError(code, where)
 
 
+# A step of a small layer takes about as long on the host as on the GPU, so the marshalling is kept short: addresses go
+# to ctypes as plain ints (every function below has its argtypes), and the current stream's handle is asked for
+# without making a Stream object (1.5 us; the object's handle where this PyTorch has no such query).
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:
+        if _raw_stream is not None and _current_device is not None:
+            return _raw_stream(_current_device())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
+
+
+_FIVE_NONE = (None,) * 5
 
 
 def hire_version() -> int:
@@ -268,6 +281,7 @@ class FFNLayer:
         p = lambda t: t.data_ptr() if t is not None else None
         self.c = _FFNLayer(self.d_model, self.d_ff, w1u.data_ptr(), w2u.data_ptr(), self.kind, p(q4), p(q4_scale),
                            p(self.lr_a), p(self.lr_b), self.r, p(self.lr_a_scale), p(self.lr_b_scale), None)
+        self.ref = C.byref(self.c)
         self.row_norm_bounds = None
         if self.kind in (SCORER_LOWRANK, SCORER_LRQ) and prepare:
             # one-off preparation: row-norm bounds that let batch-1 steps take the short kernel sequence
@@ -303,6 +317,7 @@ class SoftmaxLayer:
         p = lambda t: t.data_ptr() if t is not None else None
         self.c = _SoftmaxLayer(self.d_model, self.vocab, w.data_ptr(), self.kind, p(q4), p(q4_scale), p(self.lr_a),
                                p(self.lr_b), self.r, p(self.lr_a_scale), p(self.lr_b_scale))
+        self.ref = C.byref(self.c)
 
     @classmethod
     def with_lrq_scorer(cls, w, z1, z2):
@@ -352,8 +367,8 @@ def hire_ffn_step(layer: FFNLayer, x: torch.Tensor, k: int, kprime: int, out: FF
                   stream=None, minimal: bool = False) -> None:
     """Enqueue one HiRE-FFN step.  With minimal=True only y is requested (the optional outputs are skipped)."""
     B = x.shape[0]
-    opt = (None,) * 5 if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_ffn_step(C.byref(layer.c), _ptr(x), B, k, kprime, _ptr(out.y), *[_ptr(t) for t in opt],
+    opt = _FIVE_NONE if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
+    rc = _lib.hire_ffn_step(layer.ref, _ptr(x), B, k, kprime, _ptr(out.y), *[_ptr(t) for t in opt],
                             _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "hire_ffn_step")
 
@@ -366,8 +381,8 @@ def hire_ffn_step_static(layer: FFNLayer, x: torch.Tensor, k: int, kprime: int, 
     """hire_ffn_step on the library's own statically allocated scratch memory: no workspace argument, nothing
     allocated by the call (for callers that cannot allocate; steps beyond STATIC_SCRATCH_BYTES are refused)."""
     B = x.shape[0]
-    opt = (None,) * 5 if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_ffn_step_static(C.byref(layer.c), _ptr(x), B, k, kprime, _ptr(out.y), *[_ptr(t) for t in opt],
+    opt = _FIVE_NONE if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
+    rc = _lib.hire_ffn_step_static(layer.ref, _ptr(x), B, k, kprime, _ptr(out.y), *[_ptr(t) for t in opt],
                                    _stream(stream))
     _check(rc, "hire_ffn_step_static")
 
@@ -394,8 +409,8 @@ def hire_ffn_group_step(layer: FFNLayer, x: torch.Tensor, k: int, kprime: int, g
                         workspace: torch.Tensor, stream=None, minimal: bool = False) -> None:
     """Enqueue one group-sparse HiRE-FFN step.  With minimal=True only y is requested."""
     B = x.shape[0]
-    opt = (None,) * 5 if minimal else (out.topk_group, out.topk_val, out.cand_group, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_ffn_group_step(C.byref(layer.c), _ptr(x), B, k, kprime, group, _ptr(out.y),
+    opt = _FIVE_NONE if minimal else (out.topk_group, out.topk_val, out.cand_group, out.n_cand, out.scorer_acc)
+    rc = _lib.hire_ffn_group_step(layer.ref, _ptr(x), B, k, kprime, group, _ptr(out.y),
                                   *[_ptr(t) for t in opt], _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "hire_ffn_group_step")
 
@@ -411,8 +426,8 @@ def hire_ffn_commonpath_step(layer: FFNLayer, dense_w1u, dense_w2u, x: torch.Ten
     group-sparse step on `layer`.  Outputs as for hire_ffn_group_step."""
     B = x.shape[0]
     m1 = 0 if dense_w1u is None else dense_w1u.shape[0]
-    opt = (None,) * 5 if minimal else (out.topk_group, out.topk_val, out.cand_group, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_ffn_commonpath_step(C.byref(layer.c), _ptr(dense_w1u), _ptr(dense_w2u), m1, _ptr(x), B, k, kprime,
+    opt = _FIVE_NONE if minimal else (out.topk_group, out.topk_val, out.cand_group, out.n_cand, out.scorer_acc)
+    rc = _lib.hire_ffn_commonpath_step(layer.ref, _ptr(dense_w1u), _ptr(dense_w2u), m1, _ptr(x), B, k, kprime,
                                        group, _ptr(out.y), *[_ptr(t) for t in opt], _ptr(workspace),
                                        workspace.numel(), _stream(stream))
     _check(rc, "hire_ffn_commonpath_step")
@@ -441,8 +456,8 @@ def hire_ffn_shard_step(layer: FFNLayer, x: torch.Tensor, k: int, kprime: int, s
                         workspace: torch.Tensor, stream=None, minimal: bool = False) -> None:
     """Enqueue one HiRE-FFN step with Algorithm 2's sharded top-k.  With minimal=True only y is requested."""
     B = x.shape[0]
-    opt = (None,) * 5 if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_ffn_shard_step(C.byref(layer.c), _ptr(x), B, k, kprime, shards, _ptr(out.y),
+    opt = _FIVE_NONE if minimal else (out.topk_idx, out.topk_val, out.cand_idx, out.n_cand, out.scorer_acc)
+    rc = _lib.hire_ffn_shard_step(layer.ref, _ptr(x), B, k, kprime, shards, _ptr(out.y),
                                   *[_ptr(t) for t in opt], _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "hire_ffn_shard_step")
 
@@ -463,7 +478,7 @@ def hire_softmax_step(layer: SoftmaxLayer, x: torch.Tensor, k: int, kprime: int,
                       workspace: torch.Tensor, stream=None, minimal: bool = False) -> None:
     B = x.shape[0]
     opt = (None,) * 4 if minimal else (out.top_logit, out.cand_idx, out.n_cand, out.scorer_acc)
-    rc = _lib.hire_softmax_step(C.byref(layer.c), _ptr(x), B, k, kprime, _ptr(out.top_idx), _ptr(out.top_prob),
+    rc = _lib.hire_softmax_step(layer.ref, _ptr(x), B, k, kprime, _ptr(out.top_idx), _ptr(out.top_prob),
                                 *[_ptr(t) for t in opt], _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "hire_softmax_step")
 
