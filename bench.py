@@ -92,7 +92,7 @@ _STAGE_KERNELS = {
     "select_k_softmax": ("k_select<double",),
     "second_layer": ("k_w2_list",),
     "shard_step": ("k_ffn_shard",),
-    "reduce": ("k_fast_reduce", "k_shard_reduce"),
+    "reduce": ("k_shard_reduce",),
     "select_gather": ("k_fast_gather",),
     "select_w2": ("k_fast_w2",),
 }

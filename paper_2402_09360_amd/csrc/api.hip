@@ -59,7 +59,8 @@ struct StepBuffers {
   double* h;         // [B, cap_u]
   int32_t* pos;      // [B,k] positions inside U of every token's selected units
   uint2* list;       // [B,k] selected units as (row, coefficient), for the second layer
-  float* partial;    // second-layer partial sums (batch-1 route with several row groups)
+  float* h32;        // batch-1 route: activations by unit (by group) in fp32
+  float* u32;        // ... groups: the units'
   // filter and refine of the exact stage (batches): upper bounds of the tokens' norms, the fp32 stored values
   float* xnorm;      // [B]
   float* wnorm_tiles; // largest candidate row norm of every workgroup of the filter stage
@@ -126,8 +127,15 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
   // by_unit: one place for the exact route's activations and the refining selection's scratch
-  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, h64_doubles = s.by_unit ? (size_t)B * s.hf_stride : 0;
+  const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
+                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the batch-1 route
+  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2,
+               h64_doubles = s.by_unit ? (size_t)B * s.hf_stride : (fast ? ffn_fast_entries(N, gs) : 0);
   s.h = c.take<double>(h_doubles > h64_doubles ? h_doubles : h64_doubles);
+  if (fast) {
+    s.h32 = c.take<float>(ffn_fast_entries(N, gs));
+    if (gs > 0) s.u32 = c.take<float>(ffn_fast_entries(N, 0));
+  }
   s.h64 = s.by_unit ? s.h : nullptr;
   if (gs > 0) s.hg = c.take<double>((size_t)B * s.cap_u + 2);
   s.sm1_ok = !ffn && B == 1 && gs == 0 && int4_like && N > kSingleWgMaxRow && softmax_b1_supported(N, d, 1, 1);
@@ -136,9 +144,6 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   if (ffn) {
     s.pos = c.take<int32_t>((size_t)B * k);
     s.list = c.take<uint2>((size_t)B * k);
-    const bool fast = gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
-                              : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime));
-    s.partial = c.take<float>(fast ? ffn_fast_partial_floats(d, k, 0) : 0);
   }
   s.bytes = c.off;
   return s;
@@ -547,9 +552,9 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     a.w1u = static_cast<const uint16_t*>(L->w1u); a.w2u = static_cast<const uint16_t*>(L->w2u);
     a.x = static_cast<const uint16_t*>(x); a.y = y;
     a.topk_idx = topk_idx; a.topk_val = topk_val;
-    a.cand = s.cand; a.cand_out = cand_idx; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
+    a.cand_out = cand_idx; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
     a.fast_region = s.fast_region;
-    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.partial = s.partial;
+    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.h32 = s.h32;
     a.stage_events = g_stage_events;
     a.scorer_clocks = g_scorer_clocks;
     HIRE_TRY(launch_ffn_fast(a, st));
@@ -671,7 +676,6 @@ struct DenseRefs {
   const uint16_t* w2u;
   int m1;
   double* h;           // [B, m1] workspace
-  float* fast_partial; // ffn_fast_partial_floats(d, k, m1) floats (batch 1)
 };
 
 static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, int k, int kprime, int group, float* y,
@@ -703,13 +707,12 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
     a.w1u = static_cast<const uint16_t*>(L->w1u); a.w2u = static_cast<const uint16_t*>(L->w2u);
     a.x = static_cast<const uint16_t*>(x); a.y = y;
     a.topk_idx = topk_group; a.topk_val = topk_val;
-    a.cand = s.cand; a.cand_out = cand_group; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
+    a.cand_out = cand_group; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
     a.fast_region = s.fast_region;
-    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.partial = s.partial;
-    a.gs = 3; a.gkeys = static_cast<float*>(s.gkeys); a.hg = s.hg;
+    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.h32 = s.h32;
+    a.gs = 3; a.gkeys = static_cast<float*>(s.gkeys); a.u32 = s.u32;
     if (dense != nullptr && dense->m1 > 0) {
       a.dense_w1u = dense->w1u; a.dense_w2u = dense->w2u; a.m1 = dense->m1; a.h_dense = dense->h;
-      a.partial = dense->fast_partial;
     }
     a.stage_events = g_stage_events;
     a.scorer_clocks = g_scorer_clocks;
@@ -785,7 +788,6 @@ int hire_ffn_group_step(const hire_ffn_layer* L, const void* x, int B, int k, in
 struct CommonBuffers {
   size_t sparse_bytes;
   double* h;       // [B, m1]
-  float* fast_partial;  // batch 1: the four-kernel route's partial rows, sparse and dense row groups together
   size_t bytes;
 };
 static CommonBuffers carve_common(void* ws, const hire_ffn_layer* L, int m1, int B, int k, int kprime, int gs) {
@@ -794,7 +796,6 @@ static CommonBuffers carve_common(void* ws, const hire_ffn_layer* L, int m1, int
   Carver cv(ws);
   cv.take<char>(c.sparse_bytes);
   c.h = cv.take<double>((size_t)B * m1 + 2);
-  if (B == 1) c.fast_partial = cv.take<float>(ffn_fast_partial_floats(L->d_model, k, m1));
   c.bytes = cv.off;
   return c;
 }
@@ -819,8 +820,7 @@ int hire_ffn_commonpath_step(const hire_ffn_layer* L, const void* dense_w1u, con
   DenseRefs dense{};
   if (need != 0 && m1 > 0) {
     c = carve_common(workspace, L, m1, B, k, kprime, gs);
-    dense = DenseRefs{static_cast<const uint16_t*>(dense_w1u), static_cast<const uint16_t*>(dense_w2u), m1, c.h,
-                      c.fast_partial};
+    dense = DenseRefs{static_cast<const uint16_t*>(dense_w1u), static_cast<const uint16_t*>(dense_w2u), m1, c.h};
   }
   return ffn_group_step_impl(L, x, B, k, kprime, group, y, topk_group, topk_val, cand_group, n_cand, scorer_acc,
                              workspace, workspace_bytes, stream, (need != 0 && m1 > 0) ? &dense : nullptr);

@@ -73,6 +73,7 @@ struct KeyIO<uint64_t> {
 // kernels short of registers).
 template <typename K, int LOADS, int NT, bool FRESH = false>
 struct KeyRegs {
+  static constexpr int kLoads = LOADS;
   static constexpr int PER = KeyIO<K>::PER;
   static constexpr int SPAN = kWave * PER;  // keys per load of a wave
   static constexpr int NW = NT / kWave;

@@ -4,16 +4,13 @@
 //   k_fast_score   int8 token quantisation (redone by every workgroup, 4 KB), int4 scorer, keys to memory and
 //                  a fine histogram of the keys (integer atomics; a bin is 2^14 consecutive fp32 bit patterns,
 //                  i.e. exponent and nine mantissa bits, so that few keys share a counter)
-//   k_fast_gather  every workgroup walks the histogram from the top, ranks the handful of keys of the
-//                  threshold bin and so knows the exact k'-th key; the ascending candidate list follows from
-//                  prefix counts, each workgroup materialises only its own share and computes the exact
-//                  pre-activations of those rows; histogram of h the same way
+//   k_fast_gather  every workgroup walks the histogram from the top to the bin of the k'-th key and computes the exact
+//                  pre-activations of those of its own 64 units that belong to the shortlist; histogram of h the
+//                  same way
 //   k_fast_w2      the same selection on h (exact top-k), then sum_j h_j v_j over all selected rows for the
-//                  workgroup's 64 columns, reduced inside the workgroup in a fixed order: y itself, no
+//                  workgroup's 32 columns, reduced inside the workgroup in a fixed order: y itself, no
 //                  kernel follows.  Clears the key histogram (the next step's scorer kernel clears the h
 //                  histogram, which nobody reads in between).
-//   k_fast_reduce  only for steps whose second layer runs in several row groups (more than 1024 selected
-//                  rows, or dense common-path units): adds the groups' partial rows in a fixed order
 //
 // A kernel boundary is the cheapest device-wide synchronisation on this machine (a spinning grid barrier
 // costs several microseconds per round with 256 workgroups), hence separate kernels instead of one
@@ -22,9 +19,8 @@
 // sections: a SIMD issues one vector instruction every four cycles, so with sixteen waves on a CU each wave
 // gets one every ~16 cycles and a section of a hundred instructions takes 0.7 us.  Hence
 //
-//  * the gather runs sixteen waves per workgroup (four keys per lane, one row in flight per wave) and the
-//    second layer eight: fewer waves per workgroup were measured slower for the same work (the serial sections
-//    of a lone wave run at 10 to 15 cycles per instruction);
+//  * both run sixteen waves per workgroup: fewer were measured slower for the same work (the serial sections of a
+//    lone wave run at 10 to 15 cycles per instruction);
 //  * The histograms are windows of 8192 bins at FIXED addresses: slot s counts the keys of bin anchor - s.
 //    The anchors are rigorous upper bounds of the keys and of the activations that the scorer kernel derives
 //    from the quantised token alone (sum |xq|) and the layer's largest row scale (kept behind the packed int4
@@ -47,15 +43,15 @@
 namespace hire {
 
 constexpr unsigned long long kCookie = 0x48695245464e4f4cull;
-constexpr int kShareCap = 64;                     // rows one gather workgroup handles at most
 
 // Layout of the fast-path region at the head of the workspace.
 struct FastRegion {
   unsigned long long cookie;
   uint32_t fallbacks[2];     // steps whose k'-th key / k-th h were found without the histogram (statistics)
-  uint32_t pad1;
+  uint32_t bin1;             // threshold bin of the keys of the running step, 0: not known from the histogram; by the
+                             // gathering kernel, with need1 the keys of that bin that are selected
   uint32_t anchor1, anchor2; // top bins of the two windows for the running step, written by the scorer kernel
-  uint32_t pad0;
+  uint32_t need1;
   uint32_t zeros[8];         // stays zero: what lanes beyond the end of a key array load
   uint32_t pad[48];
   uint32_t hist1[kWin];      // slot s: scorer keys in fine bin anchor1 - s
@@ -370,81 +366,96 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Kernel 2: exact k'-th key, this workgroup's share of the candidate list, exact pre-activations.
-// Sixteen waves per workgroup, sixteen keys per lane.  K: the keys' bit patterns, 32 bits for the int4 scorer's
-// fp32 keys, 64 for the low-rank scorer's fp64 ones.
-constexpr int kGT = 1024;  // smaller workgroups were measured: slower (fewer waves to hide each phase's latency)
-constexpr int kGW = kGT / kWave;
-constexpr int kGatherLoads = 64 / kGW;    // waves x loads x 256 keys = 16384
-constexpr int kGatherRows = 16 / kGW;     // rows a wave has in flight: sixteen per workgroup
-using GatherShared = SelSharedT<kGT>;
+// Selection of the `need` largest keys, as kernels 2 and 3 do it.  The window histogram is exact - integer counts that
+// the producing kernel added for every positive key, all keys at or below the anchor - so the walk gives the bin of the
+// need-th key and the number of keys above it, and only the bin's own few keys (`list`, 64 at most) have to be compared:
+// no pass counts what lies above.
 template <typename K>
-using GatherKeys = KeyRegs<K, kGatherLoads * (int)(sizeof(K) / 4), kGT>;  // 16384 keys either way
+struct BinList {
+  K key[kFastAmbCap];
+  int idx[kFastAmbCap];
+};
+// Of the entry (key, index): selected, if fewer than `need` of the m list entries, one per lane, are ahead of it (key
+// descending, index ascending).  A wave asks this for its own entries alone, one or two of them: ranking the whole list
+// in every wave cost a serial step per entry.
+template <typename K>
+__device__ __forceinline__ bool list_takes(K mine_k, int mine_i, int m, int need, K key, int idx) {
+  return (int)__popcll(__ballot(lane_id() < m && ranks_ahead(mine_k, mine_i, key, idx))) < need;
+}
+
+// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// ---------------------------------------------------------------------------------------------------
+// Kernel 2: the shortlist and its exact pre-activations.  A workgroup owns 64 adjacent units, about a fifth of which
+// are shortlisted: with the threshold bin known from the walk, a ballot over its 64 keys names its rows, and their loads
+// go out at once - nothing is counted, listed or placed first.  Only a workgroup that holds a key of the threshold bin
+// itself looks through all keys for that bin's others, while its rows are in flight, and settles which of its own belong
+// to the shortlist.  Activations are left by unit (fp32 for the selection that follows, fp64 for its ties; 0 and -1
+// where a unit is not shortlisted), so no list of candidates is needed in between; the caller's is written beside
+// kernel 3 (a 257th workgroup here would wait for a compute unit).  K: the keys' bit patterns, 32 bits for the int4
+// scorer's fp32 keys, 64 for the low-rank scorer's fp64 ones; LOADS: 16-byte loads of keys per thread.
+// Measured at the ~1B shape: 7.7 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
+// its rows.  Inside: 1.8 until the window is walked, 2.0 for the rows; the workgroups that own a key of the threshold bin
+// need 1.6 more for its list and are the last to end.
+constexpr int kGT = 1024;
+constexpr int kGW = kGT / kWave;
+constexpr int kOwnUnits = 64;  // units of a workgroup
+using GatherShared = SelSharedT<kGT>;
 
 struct FastGatherParams {
-  const void* keys;           // [N] fp32 (fp64), zero up to the next multiple of 4 (2)
-  int N, kprime, d;
+  const void* keys;           // [N >> gs] fp32 (fp64), zero up to the next multiple of 4 (2)
+  int N, kprime, d;           // units; selected entries (units or groups)
   FastRegion* fr;
   const uint16_t* W1;         // [N, d] bf16
   const uint4* x;             // token, d/8 uint4
-  int32_t* cand;              // [kprime] ascending candidate list in the workspace (read back by the next kernel)
-  int32_t* cand_out;          // optional: the caller's copy
   int32_t* n_cand;            // optional
-  double* h;                  // [kprime << gs] (+ zero padding to a multiple of 2 when gs = 0)
-  // gs = 3 (group-sparse step): keys are group activations, N and kprime count groups of eight units, cand lists
-  // groups; h holds the eight units of every candidate group and hg[kprime] their exact group activations
-  // sum_l |h|, which are what is counted in the histogram and ranked by the next kernel.  gs = 0: units.
+  float* h32;                 // [N >> gs, up to a multiple of 64] activations, 0 where not shortlisted
+  double* h64;                // the same in fp64, -1 where not shortlisted
+  // gs = 3 (group-sparse step): keys are group activations, kprime counts groups of eight units, h32 / h64 hold the
+  // groups' exact activations sum_l |h|, which are what is counted in the histogram and ranked by the next kernel, and
+  // u32 [N, up to a multiple of 64] the units'.  gs = 0: units.
   int gs;
-  double* hg;
-  // CommonPath (eq. (7)): workgroups sparse_blocks .. gridDim.x - 1 skip the selection and compute the
-  // activations of the m1 dense units, kGW * kGatherRows rows per workgroup: hd[r] = relu(<Wd[r, :], x>).
-  int sparse_blocks;
+  float* u32;
+  // workgroups from own_blocks on (CommonPath, eq. (7)): the activations of the m1 dense units, kGW rows per workgroup:
+  // hd[r] = relu(<Wd[r, :], x>).
+  int own_blocks;
   const uint16_t* Wd;
   int m1;
   double* hd;
 };
 
-// relu(<row_u, x>) for up to kGatherRows rows per wave at once, the token as fp32 in LDS: sixteen bytes per lane
-// and load, all loads of the rows' 256-chunk slice in flight together; every bf16 product is exact in fp32 and
-// the sums run in fp64.  Only the first nr rows (uniform over the wave) are computed; the others must point at
-// row 0, whose loads they repeat.
-__device__ __forceinline__ void rows_dot_relu(const uint4* const (&row)[kGatherRows], int nr,
-                                              const float* __restrict__ xtok, int cpr, double (&out)[kGatherRows]) {
+// relu(<row, x>) by a wave, the token as fp32 in LDS: sixteen bytes per lane and load, 256 chunks in flight; every bf16
+// product is exact in fp32 and the sums run in fp64.
+struct RowChunks {
+  uint4 v[4];
+  __device__ __forceinline__ void issue(const uint4* row, int c0, int cpr) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = load_streaming(&row[min(c0 + u * kWave + lane_id(), cpr - 1)]);
+  }
+};
+__device__ __forceinline__ double row_dot_relu(const uint4* row, RowChunks first, const float* __restrict__ xtok, int cpr) {
   const int lane = lane_id();
-  double acc[kGatherRows];
-#pragma unroll
-  for (int u = 0; u < kGatherRows; ++u) acc[u] = 0.0;
+  double acc = 0.0;
   for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
-    uint4 wv[kGatherRows][4];
+    if (c0 > 0) first.issue(row, c0, cpr);
 #pragma unroll
-    for (int u = 0; u < kGatherRows; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) wv[u][v] = load_streaming(&row[u][min(c0 + v * kWave + lane, cpr - 1)]);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int c = c0 + v * kWave + lane;
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + u * kWave + lane;
       if (c < cpr) {
         const float4 xa = reinterpret_cast<const float4*>(xtok)[2 * c], xb = reinterpret_cast<const float4*>(xtok)[2 * c + 1];
         const float xf[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
+        const uint32_t wd[4] = {first.v[u].x, first.v[u].y, first.v[u].z, first.v[u].w};
 #pragma unroll
-        for (int u = 0; u < kGatherRows; ++u) {
-          if (u < nr) {
-            const uint32_t wd[4] = {wv[u][v].x, wv[u][v].y, wv[u][v].z, wv[u][v].w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              acc[u] += (double)(bf16_lo(wd[q]) * xf[2 * q]);
-              acc[u] += (double)(bf16_hi(wd[q]) * xf[2 * q + 1]);
-            }
-          }
+        for (int q = 0; q < 4; ++q) {
+          acc += (double)(bf16_lo(wd[q]) * xf[2 * q]);
+          acc += (double)(bf16_hi(wd[q]) * xf[2 * q + 1]);
         }
       }
     }
   }
-#pragma unroll
-  for (int u = 0; u < kGatherRows; ++u) {
-    const double s = wave_sum(acc[u]);
-    out[u] = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-  }
+  const double s = wave_sum(acc);
+  return s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
 }
 
 __device__ __forceinline__ void token_to_lds(const uint4* __restrict__ x, int xvecs, float* xtok) {
@@ -459,155 +470,281 @@ __device__ __forceinline__ void token_to_lds(const uint4* __restrict__ x, int xv
   }
 }
 
+// Places, in index order, of this lane's selected keys (bit e * PER + q of take): put(place, e, q), the wave's first
+// at `run`.  A wave holds at most 256 selected keys per load: the lanes' counts of two loads share a prefix sum.
+// Returns the place after the wave's last.
+template <typename Keys, typename Put>
+__device__ __forceinline__ int place_taken(uint32_t take, int run, Put&& put) {
+  constexpr int LOADS = Keys::kLoads, PER = Keys::PER;
+  constexpr uint32_t kField = (1u << PER) - 1u;
+#pragma unroll
+  for (int e0 = 0; e0 < LOADS; e0 += 2) {
+    const int c0 = __popc(take >> (e0 * PER) & kField), c1 = e0 + 1 < LOADS ? __popc(take >> ((e0 + 1) * PER) & kField) : 0;
+    const int incl = wave_scan_incl(c0 | c1 << 16), tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+    int at[2] = {run + (incl & 0xFFFF) - c0, run + (tot & 0xFFFF) + (incl >> 16) - c1};
+    run += (tot & 0xFFFF) + (tot >> 16);
+#pragma unroll
+    for (int f = 0; f < 2 && e0 + f < LOADS; ++f)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        if ((take >> ((e0 + f) * PER + q) & 1u) != 0u) put(at[f]++, e0 + f, q);
+  }
+  return run;
+}
+
+// One pass over a lane's keys against a bin: bit COUNT - 1 - j of above / inside says where key j = e * PER + q lies.
+// The masks are shifted in through the carry input: five instructions per key.
 template <typename K>
+struct BinMasks {
+  uint32_t above, inside;
+};
+template <typename K, typename Keys>
+__device__ __forceinline__ BinMasks<K> bin_masks(const Keys& kr, K lo, K up) {
+  BinMasks<K> m{0u, 0u};
+  const K width = up - lo;
+#pragma unroll
+  for (int e = 0; e < Keys::kLoads; ++e)
+#pragma unroll
+    for (int q = 0; q < Keys::PER; ++q) {
+      m.above = m.above + m.above + (kr.r[e][q] >= up ? 1u : 0u);
+      m.inside = m.inside + m.inside + ((K)(kr.r[e][q] - lo) < width ? 1u : 0u);
+    }
+  return m;
+}
+// Index of the key that the highest bit of m stands for; the bit is cleared.
+template <typename Keys>
+__device__ __forceinline__ int pop_first(const Keys& kr, uint32_t& m) {
+  constexpr int COUNT = Keys::kLoads * Keys::PER;
+  const int bit = 31 - __clz((int)m), j = COUNT - 1 - bit;
+  m ^= 1u << bit;
+  return kr.base + j / Keys::PER * Keys::SPAN + lane_id() * Keys::PER + j % Keys::PER;
+}
+// The bits of those keys of the wave that are among the list's `need` first, lane l holding entry l.
+template <typename Keys, typename K>
+__device__ __forceinline__ uint32_t taken_of_list(const Keys& kr, K mine_k, int mine_i, int m, int need) {
+  constexpr int COUNT = Keys::kLoads * Keys::PER;
+  uint32_t take = 0u;
+  for (uint64_t t = __ballot(lane_id() < m && mine_i >= kr.base && mine_i - kr.base < kr.len); t != 0ull; t &= t - 1ull) {
+    const int u = __builtin_ctzll(t), i = __builtin_amdgcn_readlane(mine_i, u), rel = i - kr.base;
+    const bool in = list_takes<K>(mine_k, mine_i, m, need, read_lane(mine_k, u), i);  // uniform
+    const int j = rel / Keys::SPAN * Keys::PER + rel % Keys::PER;
+    if (in && lane_id() == rel % Keys::SPAN / Keys::PER) take |= 1u << (COUNT - 1 - j);
+  }
+  return take;
+}
+// Key j of a lane, j not known at compile time: a tree of selections.
+template <int LO, int COUNT, typename Keys>
+__device__ __forceinline__ auto key_at(const Keys& kr, int j) {
+  if constexpr (COUNT == 1) {
+    return kr.r[LO / Keys::PER][LO % Keys::PER];
+  } else {
+    const auto a = key_at<LO, COUNT / 2>(kr, j), b = key_at<LO + COUNT / 2, COUNT / 2>(kr, j);
+    return (j & (COUNT / 2)) != 0 ? b : a;
+  }
+}
+// The keys that the masks place inside the bin -> list, in no particular order; list_n counts them, a barrier has to
+// follow.  Few lanes of few waves have any.
+template <typename K, typename Keys>
+__device__ __forceinline__ void list_inside(const Keys& kr, uint32_t inside, int* list_n, BinList<K>& list) {
+  constexpr int COUNT = Keys::kLoads * Keys::PER;
+  while (inside != 0u) {
+    const int j = COUNT - 1 - (31 - __clz((int)inside)), i = pop_first(kr, inside), at = atomicAdd(list_n, 1);
+    if (at < kFastAmbCap) {
+      list.key[at] = key_at<0, COUNT>(kr, j);
+      list.idx[at] = i;
+    }
+  }
+}
+
+template <typename K, int LOADS>
 __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
+  using Keys = KeyRegs<K, LOADS, kGT>;
   __shared__ GatherShared sh;
   __shared__ int wave_cnt[kGW];
-  __shared__ int my_rows[kShareCap];
-  __shared__ double unit_h[kShareCap];  // group-sparse: the units' activations of this workgroup's (<= 8) groups
-  extern __shared__ float xtok[];  // token as fp32, d floats
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
-  const int G = p.sparse_blocks, g = (int)blockIdx.x;
-  const int xvecs = p.d / 8;
-  if (g >= G) {  // dense common-path units: token into LDS, then kGatherRows rows per wave
+  __shared__ BinList<K> list;
+  __shared__ double unit_h[kOwnUnits];  // group-sparse: the units' activations
+  extern __shared__ float xtok[];       // token as fp32, d floats
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int g = (int)blockIdx.x, xvecs = p.d / 8, gs = p.gs;
+  if (g >= p.own_blocks) {  // dense common-path units: a row per wave
     token_to_lds(p.x, xvecs, xtok);
+    const int r = (g - p.own_blocks) * kGW + w;
+    const uint4* row = reinterpret_cast<const uint4*>(p.Wd + (size_t)min(r, p.m1 - 1) * p.d);
+    RowChunks first;
+    first.issue(row, 0, xvecs);
     __syncthreads();
-    const int r0 = (g - G) * (kGW * kGatherRows);
-    const int have = min(kGW * kGatherRows, p.m1 - r0);
-    if (w >= have) return;
-    const uint4* row[kGatherRows];
-    double sd[kGatherRows];
-    const int nr = (have - w + kGW - 1) / kGW;  // rows w, w + kGW, ... below have
-#pragma unroll
-    for (int u = 0; u < kGatherRows; ++u)
-      row[u] = reinterpret_cast<const uint4*>(p.Wd + (size_t)(r0 + (u < nr ? w + kGW * u : w)) * p.d);
-    rows_dot_relu(row, nr, xtok, xvecs, sd);
-#pragma unroll
-    for (int u = 0; u < kGatherRows; ++u)
-      if (lane == 0 && w + kGW * u < have) p.hd[r0 + w + kGW * u] = sd[u];
+    if (r >= p.m1) return;
+    const double s = row_dot_relu(row, first, xtok, xvecs);
+    if (lane == 0) p.hd[r] = s;
     return;
   }
   HIRE_TS(10);
   // every load of the selection goes out here, before the first wait
+  const int n = p.N >> gs;
   const bool hist_ok = p.fr->cookie == kCookie;
   const uint32_t anchor1 = p.fr->anchor1, anchor2 = p.fr->anchor2;
   WinRegs<kGT> wr;
   wr.issue(p.fr->hist1);
-  GatherKeys<K> kr;
-  kr.issue(p.keys, p.N, p.fr->zeros);
+  const int u0 = g * kOwnUnits;                // first unit of the workgroup
+  const int entry = (u0 + lane) >> gs;         // lane's unit, or its group
+  const bool valid = u0 + lane < p.N;
+  const K own = reinterpret_cast<const K*>(p.keys)[min(entry, n - 1)];
+  Keys kr;
+  kr.issue(p.keys, n, p.fr->zeros);
   token_to_lds(p.x, xvecs, xtok);
+  if (tid == 0) sh.list_n = 0;
+  if (tid < kOwnUnits) unit_h[tid] = 0.0;
   kr.finish();
   HIRE_TS(11);
-#ifdef HIRE_TIMESTAMPS
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // profiling build only: when has everything requested arrived?
-  HIRE_TS(18);
-#endif
-  const int share = (p.kprime + G - 1) / G;
-  const int lo = min(p.kprime, g * share), hi = min(p.kprime, lo + share);
-  const Selection<K> sel = fast_select<15>(
-      kr, p.keys, p.kprime, wr, anchor1, hist_ok, sh, wave_cnt,
-      hist_ok ? &p.fr->fallbacks[0] : static_cast<uint32_t*>(nullptr),  // a fresh workspace's first step is not counted
-      lo, hi);
+  uint64_t taken = 0ull, rows = 0ull;  // units of the workgroup: shortlisted; whose rows are read
+  WinWalk wk{0, 0, false};
+  if (hist_ok) wk = walk_window<kGT>(wr, p.kprime, sh);
+  HIRE_TS(15);
+  const uint32_t bin = anchor1 - (uint32_t)wk.slot;
+  const bool found = wk.found && bin >= 1u && bin <= anchor1;  // uniform
+  bool known = false;  // which of the workgroup's units are shortlisted is
+  RowChunks first;
+  int pos = 0;         // the wave's row (unit of the workgroup)
+  const uint4* row = nullptr;
+  // the r-th unit of `rows`, and its first loads
+  auto aim = [&](int r) {
+    pos = __builtin_ctzll(__ballot(((rows >> lane) & 1ull) != 0ull && mask_prefix(rows) == r));
+    row = reinterpret_cast<const uint4*>(p.W1 + (size_t)(u0 + pos) * p.d);
+    first.issue(row, 0, xvecs);
+  };
+  int cnt = 0;
+  // The keys have arrived by now.  Said to the compiler here, before the rows' loads go out: where paths with and without
+  // those meet, it would otherwise wait for the youngest loads, the rows, wherever a key is used.
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  if (found) {
+    const K lo = bin_floor<K>(bin), up = bin_floor<K>(bin + 1u);
+    taken = __ballot(valid && own >= up);
+    const uint64_t open = __ballot(valid && own >= lo && own < up);
+    rows = taken | open;
+    cnt = __popcll(rows);
+    if (w < cnt) aim(w);
+    __builtin_amdgcn_sched_barrier(0);  // the rows' loads are not sunk below what follows
+    if (open != 0ull) {                 // uniform over the workgroup
+      list_inside<K>(kr, bin_masks<K>(kr, lo, up).inside, &sh.list_n, list);
+      lds_barrier();
+      const int m = sh.list_n, need = p.kprime - wk.above;
+      known = m <= kFastAmbCap && need >= 1 && need <= m;  // uniform
+      if (known) {
+        const K mine_k = lane < m ? list.key[lane] : (K)0;
+        const int mine_i = lane < m ? list.idx[lane] : 0x7FFFFFFF;
+        for (uint64_t o = open; o != 0ull;) {
+          const int l = __builtin_ctzll(o), e = (u0 + l) >> gs;
+          const uint64_t units = (gs != 0 ? 0xFFull : 1ull) << l;  // (whole groups: l is a multiple of eight)
+          if (list_takes<K>(mine_k, mine_i, m, need, read_lane(own, l), e)) taken |= units & open;
+          o &= ~units;
+        }
+      }
+    } else {
+      known = true;  // no unit of this workgroup depends on the cut
+    }
+  }
   HIRE_TS(12);
-
-  fast_emit(kr, sel, lo, hi, [&](int i, int out, K, int, int) { my_rows[out - lo] = i; });
-  __syncthreads();  // my_rows, and the token in LDS (no global store is pending here: a barrier would wait for it)
+  if (!known) {  // fresh workspace, threshold among the zeros or below the window, crowded bin: range narrowing
+    const Selection<K> sel = fast_select<60>(kr, p.keys, p.kprime, wr, anchor1, false, sh, wave_cnt,
+                                             hist_ok ? &p.fr->fallbacks[0] : static_cast<uint32_t*>(nullptr), 0, p.kprime);
+    taken = __ballot(valid && cut_takes(sel.cut, own, entry));
+  }
+  if (!found) {
+    rows = taken;
+    cnt = __popcll(rows);
+    if (w < cnt) aim(w);
+  }
   HIRE_TS(13);
-
-  const int gs = p.gs, gmask = (1 << gs) - 1;
-  const int cnt = (hi - lo) << gs;  // rows of this workgroup
   auto count_h = [&](double v) {  // the scorer kernel of this step has cleared the window
     if (v > 0.0) {
       const uint32_t slot = anchor2 - fine_bin((uint64_t)__double_as_longlong(v));  // v lies at or below the anchor
       if (slot < (uint32_t)kWin) atomicAdd(&p.fr->hist2[slot], 1u);
     }
   };
-  for (int r0 = 0; r0 < cnt; r0 += kGW * kGatherRows) {  // one trip unless groups are gathered
-    if (r0 + w >= cnt) break;                             // uniform over the wave
-    const uint4* row[kGatherRows];
-    double s[kGatherRows];
-    const int nr = min(kGatherRows, (cnt - r0 - w + kGW - 1) / kGW);  // rows r0 + w, r0 + w + kGW, ... below cnt
-#pragma unroll
-    for (int u = 0; u < kGatherRows; ++u) {
-      const int r = r0 + w + (u < nr ? kGW * u : 0);
-      const size_t unit = ((size_t)my_rows[r >> gs] << gs) + (r & gmask);
-      row[u] = reinterpret_cast<const uint4*>(p.W1 + unit * p.d);
-    }
-    rows_dot_relu(row, nr, xtok, xvecs, s);
-#pragma unroll
-    for (int u = 0; u < kGatherRows; ++u) {
-      const int r = r0 + w + kGW * u;
-      if (lane == 0 && r < cnt) {
-        p.h[((size_t)lo << gs) + r] = s[u];
-        if ((r & gmask) == 0) {
-          p.cand[lo + (r >> gs)] = my_rows[r >> gs];
-          if (p.cand_out) p.cand_out[lo + (r >> gs)] = my_rows[r >> gs];
-        }
-        if (gs != 0) {
-          unit_h[r] = s[u];
-        } else {
-          count_h(s[u]);
-        }
+  if (!found) __syncthreads();  // the token in LDS
+  for (int r = w; r < cnt; r += kGW) {  // uniform over the wave; one trip for most
+    if (r > w) aim(r);
+    const double s = row_dot_relu(row, first, xtok, xvecs);
+    const bool in = ((taken >> pos) & 1ull) != 0ull;
+    if (lane == 0) {
+      if (gs != 0) {
+        unit_h[pos] = s;
+      } else {
+        p.h32[u0 + pos] = in ? (float)s : 0.0f;
+        p.h64[u0 + pos] = in ? s : -1.0;
+        if (in) count_h(s);
       }
     }
   }
-  if (gs != 0) {  // exact group activations, units added in order
+  if (gs == 0) {
+    if (w == kGW - 1 && ((rows >> lane) & 1ull) == 0ull) {
+      p.h32[u0 + lane] = 0.0f;
+      p.h64[u0 + lane] = -1.0;
+    }
+  } else {  // exact group activations, units added in order
     __syncthreads();
-    if (tid < hi - lo) {
+    if (tid < kOwnUnits) p.u32[u0 + tid] = ((taken >> tid) & 1ull) != 0ull ? (float)unit_h[tid] : 0.0f;
+    if (tid < kOwnUnits >> gs) {
+      const bool in = ((taken >> (tid << gs)) & 1ull) != 0ull;
       double e = 0.0;
-      for (int l = 0; l <= gmask; ++l) e += fabs(unit_h[(tid << gs) + l]);
-      p.hg[lo + tid] = e;
-      count_h(e);
+      for (int l = 0; l < (1 << gs); ++l) e += fabs(unit_h[(tid << gs) + l]);
+      p.h32[(u0 >> gs) + tid] = in ? (float)e : 0.0f;
+      p.h64[(u0 >> gs) + tid] = in ? e : -1.0;
+      if (in) count_h(e);
     }
   }
   if (g == 0 && tid == 0) {
     if (p.n_cand) *p.n_cand = p.kprime;
-    if (p.kprime & 1) (p.gs != 0 ? p.hg : p.h)[p.kprime] = 0.0;  // zero padding of what the next kernel ranks
+    p.fr->bin1 = found ? bin : 0u;
+    p.fr->need1 = (uint32_t)(p.kprime - wk.above);
   }
   HIRE_TS(14);
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Kernel 3: exact top-k of h, then sum_j h_j v_j over the selected rows for this workgroup's 32 columns.
-// A workgroup reads a 64-byte slice of every selected row (four lanes per row, sixteen rows per wave and load,
-// all loads of a wave in flight together) and reduces inside itself in a fixed order, so with one row group
-// the result is y itself and no kernel follows.  Steps with more than kRowsCap selected rows, and the dense
-// common-path units, add row groups whose partial rows k_fast_reduce sums.
-constexpr int kWT = 512;
+// Kernel 3: exact top-k of the activations, then sum_j h_j v_j over the selected rows for this workgroup's 32 columns
+// (64 bytes of every selected row: four lanes per row, sixteen rows per wave and load).  Every wave lists the selected
+// units of its own part of the row in LDS and adds up their rows, so no barrier and no prefix over the waves lies between
+// the cut and the rows' loads; the workgroup then reduces inside itself in a fixed order and writes y.  CommonPath's
+// dense units (eq. (7)) are shared out over the waves behind the selected ones.  One more workgroup writes the selected
+// entries and their values for the caller.
+//
+// The selection works on the activations rounded to fp32 (rounding is monotone; the coefficients of the second layer are
+// these values anyway); the keys of the threshold bin, and a selection without histogram, go by the fp64 values.
+// Measured at the ~1B shape: 9.5 us with the reduction over the workgroups' shares and the shortlist's list in it.  Inside:
+// window walked 1.9, masks 0.6, bin settled 0.8, rows listed 0.5, rows 2.4 to 3.3, reduction 1.4.
+constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
-constexpr int kW2Loads = 32 / kWW;   // waves x loads x 128 activations = 4096
 using W2Shared = SelSharedT<kWT>;
-using W2Keys = KeyRegs<uint64_t, kW2Loads, kWT>;
-static_assert(GatherKeys<uint32_t>::CAPACITY >= 16384 && GatherKeys<uint64_t>::CAPACITY >= 16384 && W2Keys::CAPACITY >= 4096, "register capacity of the selecting workgroups");
-
-struct FastW2Params {
-  const double* h;       // [n], zero up to the next multiple of 2
-  int n, k, d;
-  FastRegion* fr;
-  const int32_t* cand;   // [n] unit index of each position, readable to the next multiple of 2
-  const uint16_t* W2;    // [N, d] bf16
-  int32_t* topk_idx;     // optional [k]
-  float* topk_val;       // optional [k]
-  float* out;            // row_groups + dense_groups == 1: y [d]; otherwise partial [row_groups + dense_groups, d]
-  int row_groups, col_slices;
-  // gs = 3 (group-sparse step): h holds exact group activations, n and k count groups, cand lists groups;
-  // unit_h[n << gs] holds the units' activations (the second layer's coefficients) and topk_val receives the
-  // eight of every selected group.  gs = 0: units, unit_h unused.
-  int gs;
-  const double* unit_h;
-  // CommonPath (eq. (7)): row groups row_groups .. row_groups + dense_groups - 1 (times the column slices) add
-  // the m1 dense units, kRowsCap rows each: out += fl32(hd[r]) * W2d[r, :].  dense_groups = 0: none.
-  int dense_groups;
-  const uint16_t* W2d;
-  const double* hd;
-  int m1;
-};
-
 constexpr int kSliceCols = 32;  // columns per workgroup: 64 bytes of a row
-constexpr int kRowsCap = 1024;    // rows per workgroup
 constexpr int kRowLanes = kSliceCols / 8;        // lanes that share a row: 16 bytes each
 constexpr int kRowsPerLoad = kWave / kRowLanes;  // rows a wave covers with one load instruction
 constexpr int kW2Batch = 8;       // loads a lane has in flight
+constexpr int kSegRows = kRowsPerLoad * kW2Batch;  // rows a wave lists at a time
+
+struct FastW2Params {
+  const float* h32;      // [n up to a multiple of 64] activations by unit (gs = 3: by group), 0: not shortlisted
+  const double* h64;     // the same in fp64, -1: not shortlisted
+  int n, k, d;           // entries, selected entries
+  FastRegion* fr;
+  const uint16_t* W2;    // [N, d] bf16
+  int32_t* topk_idx;     // optional [k]
+  float* topk_val;       // optional [k << gs]
+  float* y;              // [d]
+  int col_slices;
+  int out_block;         // the workgroup that writes topk_idx / topk_val; -1: none
+  // the workgroup that writes the shortlist (-1: none): the kprime largest of the n keys, ascending
+  int list_block;
+  const void* keys;
+  int kprime;
+  int32_t* cand_out;
+  // gs = 3 (group-sparse step): entries are groups of eight units, u32 holds the units' activations.
+  int gs;
+  const float* u32;
+  const uint16_t* W2d;   // CommonPath: y += fl32(hd[r]) * W2d[r, :], r < m1
+  const double* hd;
+  int m1;
+};
 
 // Column slice of a workgroup: slices 2i and 2i+1 are the two halves of the same 128-byte lines; they go to
 // workgroups b and b + 8, which the dispatcher places on the same die (workgroups go round the eight dies),
@@ -617,152 +754,272 @@ __device__ __forceinline__ int slice_of(int b, int slices) {
   return 2 * (b % 8) + (b / 8) % 2 + 16 * (b / 16);
 }
 
-__global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
-  __shared__ W2Shared sh;
-  __shared__ int wave_cnt[kWW];
-  __shared__ int my_unit[kRowsCap];
-  __shared__ float my_h[kRowsCap];
-  __shared__ int grp_unit[kRowsCap / 8], grp_pos[kRowsCap / 8];  // group-sparse: the selected groups
-  __shared__ float red[kWW * kRowsPerLoad][kSliceCols];
-  __shared__ float red2[kWW][kSliceCols];
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
-  const int cs = slice_of((int)blockIdx.x % p.col_slices, p.col_slices), rg = (int)blockIdx.x / p.col_slices;
-  const bool dense = rg >= p.row_groups;  // uniform over the workgroup
-  const int n_selecting = p.row_groups * p.col_slices;
-  int cnt, lo = 0, hi = 0;
-  const uint16_t* W2 = p.W2;
-  if (dense) {  // no selection: this group's dense rows with their activations as coefficients
-    const int r0 = (rg - p.row_groups) * kRowsCap;
-    cnt = min(kRowsCap, p.m1 - r0);
-    for (int i = tid; i < cnt; i += kWT) {
-      my_unit[i] = r0 + i;
-      my_h[i] = (float)p.hd[r0 + i];
-    }
-    W2 = p.W2d;
-    __syncthreads();
-  } else {
-    HIRE_TS(24);
-    const uint32_t anchor2 = p.fr->anchor2;
-    WinRegs<kWT> wr;
-    wr.issue(p.fr->hist2);
-    W2Keys kr;
-    kr.issue(p.h, p.n, p.fr->zeros);
-    // unit index of each of this thread's positions: position (e, lane, q) is 2 * (vector index) + q
-    int2 cu[kW2Loads];
-#pragma unroll
-    for (int e = 0; e < kW2Loads; ++e) {
-      const int vec = min((kr.base + e * W2Keys::SPAN) / 2 + lane, (p.n - 1) / 2);
-      cu[e] = reinterpret_cast<const int2*>(p.cand)[vec];
-    }
-    kr.finish();
-    // the activations' window is valid on any workspace: this step's scorer kernel cleared it, its gather filled it
-    const int share = min(kRowsCap >> p.gs, (p.k + p.row_groups - 1) / p.row_groups);
-    lo = min(p.k, rg * share);
-    hi = min(p.k, lo + share);
-    const Selection<uint64_t> sel = fast_select<20>(kr, p.h, p.k, wr, anchor2, true, sh, wave_cnt,
-                                                    &p.fr->fallbacks[1], lo, hi);
-    HIRE_TS(25);
-    // into LDS only: a global store here would be waited for by the barrier that follows
-    fast_emit(kr, sel, lo, hi, [&](int i, int out, uint64_t bits, int e, int q) {
-      const int unit = q ? cu[e].y : cu[e].x;
-      if (p.gs == 0) {
-        my_unit[out - lo] = unit;
-        my_h[out - lo] = (float)__longlong_as_double((long long)bits);
-      } else {
-        grp_unit[out - lo] = unit;
-        grp_pos[out - lo] = i;
-      }
-    });
-    __syncthreads();
-    cnt = (hi - lo) << p.gs;  // rows of this workgroup
-    if (p.gs != 0) {  // the selected groups' units and their coefficients
-      const int gmask = (1 << p.gs) - 1;
-      for (int r = tid; r < cnt; r += kWT) {
-        const float hv = (float)p.unit_h[((size_t)grp_pos[r >> p.gs] << p.gs) + (r & gmask)];
-        my_unit[r] = (grp_unit[r >> p.gs] << p.gs) + (r & gmask);
-        my_h[r] = hv;
-      }
-      __syncthreads();
-    }
-    HIRE_TS(26);
-  }
-
-  // rows r = (step * kWW + w) * kRowsPerLoad + slot for this lane's slot; eight columns per lane
-  const int slot = lane / kRowLanes, part = lane % kRowLanes;
-  const int col = cs * kSliceCols + part * 8;
-  const int colc = min(col, p.d - 8);
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  constexpr int kStride = kWW * kRowsPerLoad;  // rows the workgroup covers per load of every wave
-  for (int r0 = w * kRowsPerLoad + slot; r0 < cnt; r0 += kStride * kW2Batch) {
-    uint4 wv[kW2Batch];
-    float cf[kW2Batch];
-#pragma unroll
-    for (int u = 0; u < kW2Batch; ++u) {
-      const int r = r0 + kStride * u, rc = min(r, cnt - 1);
-      wv[u] = load_streaming(reinterpret_cast<const uint4*>(W2 + (size_t)my_unit[rc] * p.d + colc));
-      cf[u] = r < cnt ? my_h[rc] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kW2Batch; ++u) {
-      const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
-                           bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf[u], wf[q], acc[q]);
-    }
-  }
-  HIRE_TS(27);
-  // fixed-order reduction: the (wave, slot) partial rows -> one per wave -> 1
-  {
-    float4* dst = reinterpret_cast<float4*>(&red[w * kRowsPerLoad + slot][part * 8]);
-    dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-  }
+// The shortlist in ascending order, for the caller, by one workgroup: K, LK as in the gathering kernel.
+template <typename K, int LK>
+__device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& sh, int* wave_cnt, BinList<K>& list) {
+  using Keys = KeyRegs<K, LK, kWT>;
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const uint32_t bin = p.fr->bin1;
+  const int need = (int)p.fr->need1;
+  Keys kr;
+  kr.issue(p.keys, p.n, p.fr->zeros);
+  if (tid == 0) sh.list_n = 0;
+  kr.finish();
   __syncthreads();
-  if (tid < kWW * kSliceCols) {
-    const int c = tid % kSliceCols, j = tid / kSliceCols;  // j < kWW
-    float t = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kRowsPerLoad; ++u) t += red[j * kRowsPerLoad + u][c];
-    red2[j][c] = t;
-  }
-  __syncthreads();
-  if (tid < kSliceCols) {
-    const int c = cs * kSliceCols + tid;
-    if (c < p.d) {
-      float t = 0.0f;
-#pragma unroll
-      for (int u = 0; u < kWW; ++u) t += red2[u][tid];
-      p.out[(size_t)(p.row_groups + p.dense_groups == 1 ? 0 : rg) * p.d + c] = t;
+  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
+  bool known = false;
+  if (bin != 0u) {  // uniform
+    const BinMasks<K> bm = bin_masks<K>(kr, bin_floor<K>(bin), bin_floor<K>(bin + 1u));
+    list_inside<K>(kr, bm.inside, &sh.list_n, list);
+    __syncthreads();
+    const int m = sh.list_n;
+    known = m <= kFastAmbCap && need >= 1 && need <= m;  // uniform
+    if (known) {
+      const K mine_k = lane < m ? list.key[lane] : (K)0;
+      const int mine_i = lane < m ? list.idx[lane] : 0x7FFFFFFF;
+      take = bm.above | taken_of_list<Keys>(kr, mine_k, mine_i, m, need);
     }
   }
-  HIRE_TS(28);
-  if (dense) return;
-  if (cs == 0) {  // the selected entries and their activations, in the order of the second layer's rows
-    if (p.topk_idx)
-      for (int j = tid; j < hi - lo; j += kWT) p.topk_idx[lo + j] = p.gs == 0 ? my_unit[j] : grp_unit[j];
-    if (p.topk_val)
-      for (int r = tid; r < cnt; r += kWT) p.topk_val[((size_t)lo << p.gs) + r] = my_h[r];
+  if (!known) {
+    WinRegs<kWT> none{};
+    const Selection<K> sel = fast_select<60>(kr, p.keys, p.kprime, none, 0u, false, sh, wave_cnt,
+                                             static_cast<uint32_t*>(nullptr), 0, p.kprime);
+    take = 0u;
+#pragma unroll
+    for (int e = 0; e < LK; ++e)
+#pragma unroll
+      for (int q = 0; q < Keys::PER; ++q)
+        take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
   }
-  // The key histogram has served its purpose: the selecting workgroups clear it between them and say so in the
-  // cookie (the same value from each; the next kernel that looks at either starts after this one has ended).
-  for (int i = (int)blockIdx.x * kWT + tid; i < kWin; i += n_selecting * kWT) p.fr->hist1[i] = 0u;
-  if (tid == 0) p.fr->cookie = kCookie;
+  const int mine = wave_sum(__popc(take));
+  __syncthreads();
+  if (lane == 0) wave_cnt[w] = mine;
+  __syncthreads();
+  const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
+  place_taken<Keys>(__brev(take) >> (32 - LK * Keys::PER), w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0,
+                    [&](int at, int e, int q) { p.cand_out[at] = kr.index(e, q); });
 }
 
-// Kernel 4 (only when the second layer ran in several row groups): y = their sum, in order.
-__global__ __launch_bounds__(256) void k_fast_reduce(const float* __restrict__ partial, int groups, int d,
-                                                     float* __restrict__ y) {
-  const int col = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  const int colc = min(col, d - 1);
-  float s = 0.0f;
-  for (int g0 = 0; g0 < groups; g0 += 8) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)min(g0 + u, groups - 1) * d + colc];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += g0 + u < groups ? v[u] : 0.0f;
+// KEY: the scorer keys' bit patterns (what the candidate list is selected from); LOADS: 16-byte loads of fp32
+// activations per thread.
+template <typename KEY, int LOADS>
+__global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
+  using K = uint32_t;
+  using Keys = KeyRegs<K, LOADS, kWT>;
+  constexpr int PER = Keys::PER;
+  __shared__ W2Shared sh;
+  __shared__ BinList<KEY> list;
+  __shared__ int wave_cnt[kWW], wave_eq[kWW];
+  __shared__ int seg[kWW][kSegRows];  // selected entries of every wave
+  static_assert(kRowLanes == 4 && kWW == 16, "four slots per DPP row, sixty-four rows to reduce");
+  __shared__ float red[4 * kWW][kSliceCols];
+  __shared__ float red2[8][kSliceCols];
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const bool output = (int)blockIdx.x == p.out_block;  // uniform
+  if ((int)blockIdx.x == p.list_block) {
+    list_shortlist<KEY, LOADS * (int)(sizeof(KEY) / 4)>(p, sh, wave_cnt, list);
+    return;
   }
-  if (col < d) y[col] = s;
+  const int cs = slice_of((int)blockIdx.x, p.col_slices);
+  HIRE_TS(24);
+  const uint32_t anchor2 = p.fr->anchor2;
+  WinRegs<kWT> wr;
+  wr.issue(p.fr->hist2);
+  Keys kr;
+  kr.issue(p.h32, p.n, p.fr->zeros);
+  if (tid == 0) sh.list_n = 0;
+  kr.finish();
+  // the activations' window is valid on any workspace: this step's scorer kernel cleared it, its gather filled it
+  const WinWalk wk = walk_window<kWT>(wr, p.k, sh);
+  HIRE_TS(20);
+  const uint32_t bin = anchor2 - (uint32_t)wk.slot;
+  const bool found = wk.found && bin >= 1u && bin <= anchor2;  // uniform
+  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
+  bool known = false;
+  if (found) {
+    const K lo = bin_floor<K>(bin), up = bin_floor<K>(bin + 1u);
+    const BinMasks<K> bm = bin_masks<K>(kr, lo, up);
+    for (uint32_t m = bm.inside; m != 0u;) {  // few lanes of few waves
+      const int i = pop_first(kr, m), at = atomicAdd(&sh.list_n, 1);
+      if (at < kFastAmbCap) list.idx[at] = i;
+    }
+    __syncthreads();
+    HIRE_TS(21);
+    const int m = sh.list_n, need = p.k - wk.above;
+    known = m <= kFastAmbCap && need >= 1 && need <= m;  // uniform
+    if (known) {
+      // the fp64 values of the bin's keys: they order what fp32 cannot
+      const int mine_i = lane < m ? list.idx[lane] : 0x7FFFFFFF;
+      const uint64_t mine_k = lane < m ? (uint64_t)__double_as_longlong(p.h64[mine_i]) : 0ull;
+      take = bm.above | taken_of_list<Keys>(kr, mine_k, mine_i, m, need);
+    }
+    HIRE_TS(22);
+  }
+  if (!known) {  // range narrowing over the fp64 values, ties to the lower index
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) atomicAdd(&p.fr->fallbacks[1], 1u);
+    const uint64_t t = wg_kth_largest<uint64_t>(
+        [&](auto&& f) {
+#pragma unroll 1
+          for (int i = tid; i < p.n; i += kWT) f(order_key(p.h64[i]));
+        },
+        p.n, p.k, sh);
+    int gt = 0, eq = 0;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        if (kr.valid(e, q)) {
+          const uint64_t key = order_key(p.h64[kr.index(e, q)]);
+          gt += key > t ? 1 : 0;
+          eq += key == t ? 1 : 0;
+        }
+    gt = wave_sum(gt);
+    eq = wave_sum(eq);
+    __syncthreads();
+    if (lane == 0) {
+      wave_cnt[w] = gt;
+      wave_eq[w] = eq;
+    }
+    __syncthreads();
+    int all_gt = 0, run_eq = 0;
+    for (int u = 0; u < kWW; ++u) {
+      all_gt += wave_cnt[u];
+      run_eq += u < w ? wave_eq[u] : 0;
+    }
+    const int need_eq = p.k - all_gt;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e) {
+      uint64_t key[PER];
+      int c = 0;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        key[q] = kr.valid(e, q) ? order_key(p.h64[kr.index(e, q)]) : 0ull;
+        c += key[q] == t ? 1 : 0;
+      }
+      const int incl = wave_scan_incl(c);
+      int before = run_eq + incl - c;  // equal values ahead of this lane's
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        take = take + take + (key[q] > t || (key[q] == t && before < need_eq) ? 1u : 0u);
+        before += key[q] == t ? 1 : 0;
+      }
+      run_eq += __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+  }
+  const int gs = p.gs;
+  if (output) {  // the selected entries and their activations, ascending
+    const int mine = wave_sum(__popc(take));
+    __syncthreads();
+    if (lane == 0) wave_cnt[w] = mine;
+    __syncthreads();
+    const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
+    const int run = w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0;
+    uint32_t ordered = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
+    place_taken<Keys>(ordered, run, [&](int at, int e, int q) {
+      const int i = kr.index(e, q);
+      if (p.topk_idx) p.topk_idx[at] = i;
+      if (p.topk_val) {
+        if (gs == 0) p.topk_val[at] = __uint_as_float(kr.r[e][q]);
+        else
+          for (int l = 0; l < (1 << gs); ++l) p.topk_val[(at << gs) + l] = p.u32[(i << gs) + l];
+      }
+    });
+  } else {
+    // rows of the wave: slot-th of every sixteen, eight columns per lane
+    const int slot = lane / kRowLanes, part = lane % kRowLanes;
+    const int colc = min(cs * kSliceCols + part * 8, p.d - 8);
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto add_rows = [&](const uint4 (&wv)[kW2Batch], const float (&cf)[kW2Batch]) {
+#pragma unroll
+      for (int u = 0; u < kW2Batch; ++u) {
+        const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
+                             bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf[u], wf[q], acc[q]);
+      }
+    };
+    // The wave's selected entries go to LDS lane by lane (any fixed order will do), at most kSegRows rows at a time;
+    // their coefficients are loaded with the rows.
+    const int mine_n = __popc(take), incl = wave_scan_incl(mine_n);
+    const int rows = __builtin_amdgcn_readlane(incl, kWave - 1) << gs;
+    const float* coef = gs == 0 ? p.h32 : p.u32;
+    for (int c0 = 0; c0 < rows; c0 += kSegRows) {  // uniform over the wave; one trip for most
+      int at = incl - mine_n - (c0 >> gs);
+      for (uint32_t m = take; m != 0u; ++at) {
+        const int i = pop_first(kr, m);
+        if (at >= 0 && at < kSegRows >> gs) seg[w][at] = i;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      HIRE_TS(26);
+      const int m = min(kSegRows, rows - c0);
+      uint4 wv[kW2Batch];
+      float cf[kW2Batch];
+#pragma unroll
+      for (int u = 0; u < kW2Batch; ++u)
+        if (u * kRowsPerLoad < m) {  // uniform
+          const int r = u * kRowsPerLoad + slot, rc = min(r, m - 1);
+          const int unit = (seg[w][rc >> gs] << gs) + (rc & ((1 << gs) - 1));
+          wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2 + (size_t)unit * p.d + colc));
+          const float c = coef[unit];
+          cf[u] = r < m ? c : 0.0f;
+        } else {
+          wv[u] = make_uint4(0, 0, 0, 0);
+          cf[u] = 0.0f;
+        }
+      add_rows(wv, cf);
+    }
+    for (int r0 = w * kRowsPerLoad + slot; r0 < p.m1; r0 += kWW * kRowsPerLoad * kW2Batch) {  // dense units
+      uint4 wv[kW2Batch];
+      float cf[kW2Batch];
+#pragma unroll
+      for (int u = 0; u < kW2Batch; ++u) {
+        const int r = r0 + u * kWW * kRowsPerLoad, rc = min(r, p.m1 - 1);
+        wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc));
+        const float c = (float)p.hd[rc];
+        cf[u] = r < p.m1 ? c : 0.0f;
+      }
+      add_rows(wv, cf);
+    }
+    HIRE_TS(27);
+    // fixed-order reduction: the four slots of a DPP row (its last four lanes then hold their sums), the rows of all
+    // waves in eight groups, the groups
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      acc[q] += dpp_move<0x114, 0xF>(0.0f, acc[q]);
+      acc[q] += dpp_move<0x118, 0xF>(0.0f, acc[q]);
+    }
+    if ((lane & 15) >= 12) {
+      float4* dst = reinterpret_cast<float4*>(&red[w * 4 + (lane >> 4)][part * 8]);
+      dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    }
+    __syncthreads();
+    if (tid < 8 * kSliceCols) {
+      const int c = tid % kSliceCols, j = tid / kSliceCols;
+      float t = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += red[j * 8 + u][c];
+      red2[j][c] = t;
+    }
+    __syncthreads();
+    if (tid < kSliceCols) {
+      const int c = cs * kSliceCols + tid;
+      if (c < p.d) {
+        float t = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t += red2[u][tid];
+        p.y[c] = t;
+      }
+    }
+    HIRE_TS(28);
+  }
+  // The key histogram has served its purpose: the workgroups clear it between them and say so in the
+  // cookie (the same value from each; the next kernel that looks at either starts after this one has ended).
+  for (int i = (int)blockIdx.x * kWT + tid; i < kWin; i += p.col_slices * kWT) p.fr->hist1[i] = 0u;
+  if (tid == 0) p.fr->cookie = kCookie;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -778,36 +1035,18 @@ void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_
 }
 int ffn_fast_score_blocks(int N) { return min(((N + kRPW - 1) / kRPW + kSW - 1) / kSW, 1024); }
 
-// Row groups and column slices of the second-layer kernel for `rows` selected rows (units).
-void ffn_fast_shape(int d, int rows, int* row_groups, int* col_slices) {
-  *col_slices = (d + kSliceCols - 1) / kSliceCols;
-  *row_groups = max(1, (rows + kRowsCap - 1) / kRowsCap);
-}
+constexpr int kFastMaxUnits = 16384;
 
-// Group-sparse step with groups of eight: N, k, k' count units.  The selections see N/8, k'/8 and k/8 entries; a
-// workgroup of the gather takes at most kShareCap / 8 groups (its units' activations pass through LDS).
+// Entries (units or groups) of the arrays of activations: whole workgroups of the gather write them.
+int ffn_fast_entries(int N, int gs) { return ((N + kOwnUnits - 1) / kOwnUnits * kOwnUnits) >> gs; }
+
+// Group-sparse step with groups of eight: N, k, k' count units.  The selections see N/8, k'/8 and k/8 entries.
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime) {
-  if (!(B == 1 && N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && N <= GatherKeys<uint32_t>::CAPACITY && d % 32 == 0 && d >= 64 &&
-        d <= 8192))
-    return false;
-  const int kpg = kprime / 8, G = max(1, min(kpg, 256));
-  return (kpg + G - 1) / G <= kShareCap / 8;
-}
-
-// Row groups (of kRowsCap rows) the m1 dense common-path units add to the second-layer kernel.
-int ffn_fast_dense_groups(int m1) { return (m1 + kRowsCap - 1) / kRowsCap; }
-
-// Floats of partial rows the step needs (0: the second-layer kernel writes y itself).
-size_t ffn_fast_partial_floats(int d, int k, int m1) {
-  int rg, cs;
-  ffn_fast_shape(d, k, &rg, &cs);
-  const int groups = rg + ffn_fast_dense_groups(m1);
-  return groups > 1 ? (size_t)groups * d : 0;
+  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime);
 }
 
 bool ffn_fast_supported(int B, int N, int d, int k, int kprime) {
-  return B == 1 && N <= GatherKeys<uint32_t>::CAPACITY && kprime <= W2Keys::CAPACITY && d % 32 == 0 && d >= 64 && d <= 8192 &&
-         k >= 1;
+  return B == 1 && N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 && k >= 1 && kprime <= N;
 }
 
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
@@ -821,7 +1060,6 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   const int n_sel = a.N >> gs, kp_sel = a.kprime >> gs, k_sel = a.k >> gs;
   const bool lowrank = a.lowrank;
   const void* sel_keys = lowrank ? static_cast<const void*>(a.keys64) : (gs ? a.gkeys : a.keys);
-  const double* sel_h = gs ? a.hg : a.h;
   if (lowrank) {
     if (gs != 0 || a.m1 != 0 || a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
     e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, 1, a.d, a.r, nullptr, a.t_partial, nullptr, 0, nullptr,
@@ -860,40 +1098,43 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     if ((e = mark(1)) != hipSuccess) return e;
   }
-  int G = gs ? kp_sel : (a.kprime + 7) / 8;  // a workgroup takes about eight rows: eight units or one group
-  G = max(1, min(G, 256));
   {
     FastGatherParams p{};
-    p.keys = sel_keys; p.N = n_sel; p.kprime = kp_sel; p.d = a.d;
+    p.keys = sel_keys; p.N = a.N; p.kprime = kp_sel; p.d = a.d;
     p.fr = fr; p.W1 = a.w1u; p.x = reinterpret_cast<const uint4*>(a.x);
-    p.cand = a.cand; p.cand_out = a.cand_out; p.n_cand = a.n_cand; p.h = a.h; p.gs = gs; p.hg = a.hg;
-    p.sparse_blocks = G; p.Wd = a.dense_w1u; p.m1 = a.m1; p.hd = a.h_dense;
-    const int dense_blocks = (a.m1 + kGW * kGatherRows - 1) / (kGW * kGatherRows);
-    e = lowrank ? launch(k_fast_gather<uint64_t>, dim3(G + dense_blocks), dim3(kGT), (size_t)a.d * 4, s, p)
-                : launch(k_fast_gather<uint32_t>, dim3(G + dense_blocks), dim3(kGT), (size_t)a.d * 4, s, p);
+    p.n_cand = a.n_cand; p.h32 = a.h32; p.h64 = a.h; p.gs = gs; p.u32 = a.u32;
+    p.own_blocks = (a.N + kOwnUnits - 1) / kOwnUnits;
+    p.Wd = a.dense_w1u; p.m1 = a.m1; p.hd = a.h_dense;
+    const dim3 grid(p.own_blocks + (a.m1 + kGW - 1) / kGW);
+    const size_t lds = (size_t)a.d * 4;
+    auto go = [&](auto kernel) { return launch(kernel, grid, dim3(kGT), lds, s, p); };
+    // the fewest loads that hold the keys: every pass over them is as long as a thread's share
+    if (lowrank)
+      e = n_sel <= 4096 ? go(k_fast_gather<uint64_t, 2>) : (n_sel <= 8192 ? go(k_fast_gather<uint64_t, 4>) : go(k_fast_gather<uint64_t, 8>));
+    else
+      e = n_sel <= 4096 ? go(k_fast_gather<uint32_t, 1>) : (n_sel <= 8192 ? go(k_fast_gather<uint32_t, 2>) : go(k_fast_gather<uint32_t, 4>));
     if (e != hipSuccess) return e;
     if ((e = mark(2)) != hipSuccess) return e;
   }
-  int rg, cs;
-  ffn_fast_shape(a.d, a.k, &rg, &cs);
-  const int dense_groups = ffn_fast_dense_groups(a.m1);
-  const bool direct = rg + dense_groups == 1;  // the second-layer kernel writes y itself
   {
     FastW2Params p{};
-    p.h = sel_h; p.n = kp_sel; p.k = k_sel; p.d = a.d; p.fr = fr; p.cand = a.cand; p.W2 = a.w2u;
-    p.topk_idx = a.topk_idx; p.topk_val = a.topk_val; p.out = direct ? a.y : a.partial; p.row_groups = rg;
-    p.col_slices = cs;
-    p.gs = gs; p.unit_h = a.h;
-    p.dense_groups = dense_groups; p.W2d = a.dense_w2u; p.hd = a.h_dense; p.m1 = a.m1;
-    e = launch(k_fast_w2, dim3((rg + dense_groups) * cs), dim3(kWT), 0, s, p);
+    p.h32 = a.h32; p.h64 = a.h; p.n = n_sel; p.k = k_sel; p.d = a.d; p.fr = fr; p.W2 = a.w2u;
+    p.topk_idx = a.topk_idx; p.topk_val = a.topk_val; p.y = a.y;
+    p.col_slices = (a.d + kSliceCols - 1) / kSliceCols;
+    int blocks = p.col_slices;
+    p.out_block = a.topk_idx || a.topk_val ? blocks++ : -1;
+    p.list_block = a.cand_out ? blocks++ : -1;
+    p.keys = sel_keys; p.kprime = kp_sel; p.cand_out = a.cand_out;
+    p.gs = gs; p.u32 = a.u32;
+    p.W2d = a.dense_w2u; p.hd = a.h_dense; p.m1 = a.m1;
+    auto go = [&](auto kernel) { return launch(kernel, dim3(blocks), dim3(kWT), 0, s, p); };
+    if (lowrank)
+      e = n_sel <= 4096 ? go(k_fast_w2<uint64_t, 1>) : (n_sel <= 8192 ? go(k_fast_w2<uint64_t, 2>) : go(k_fast_w2<uint64_t, 4>));
+    else
+      e = n_sel <= 4096 ? go(k_fast_w2<uint32_t, 1>) : (n_sel <= 8192 ? go(k_fast_w2<uint32_t, 2>) : go(k_fast_w2<uint32_t, 4>));
     if (e != hipSuccess) return e;
-    if ((e = mark(3)) != hipSuccess) return e;
   }
-  if (!direct) {
-    e = launch(k_fast_reduce, dim3((a.d + 255) / 256), dim3(256), 0, s, a.partial, rg + dense_groups, a.d, a.y);
-    if (e != hipSuccess) return e;
-  }
-  return mark(4);
+  return mark(3);
 }
 
 }  // namespace hire

@@ -318,20 +318,19 @@ struct FfnFastArgs {
   float* y;
   int32_t* topk_idx;   // optional
   float* topk_val;     // optional
-  int32_t* cand;       // [kprime] workspace, padded to a multiple of 2
   int32_t* cand_out;   // optional: the caller's copy of the candidate list
   int32_t* n_cand;     // optional
   int32_t* scorer_acc; // optional
   // workspace
   void* fast_region;   // ffn_fast_region_bytes() bytes at the head of the workspace (cookie, maxima, histograms)
   float* keys;         // [N] padded to a multiple of 4
-  double* h;           // [kprime] padded to a multiple of 2
-  float* partial;      // ffn_fast_partial_floats(d, k, m1) floats (none needed when that is 0)
-  // group-sparse step with groups of eight units (gs = 3; 0 otherwise): N, k, kprime still count units; cand,
-  // n_cand and topk_idx are in groups, topk_val and h per unit
+  double* h;           // [ffn_fast_entries(N, gs)]: activations of the units (gs = 3: of the groups)
+  float* h32;          // the same rounded to fp32
+  // group-sparse step with groups of eight units (gs = 3; 0 otherwise): N, k, kprime still count units; cand_out,
+  // n_cand and topk_idx are in groups, topk_val per unit
   int gs;
   float* gkeys;        // gs = 3: [N/8] padded to a multiple of 4
-  double* hg;          // gs = 3: [kprime/8] padded to a multiple of 2
+  float* u32;          // gs = 3: [ffn_fast_entries(N, 0)] activations of the units
   // CommonPath (eq. (7)): m1 dense units next to the sparse ones, folded into the gather and second-layer
   // launches as extra workgroups (m1 = 0: none).
   const uint16_t* dense_w1u;  // [m1, d]
@@ -354,7 +353,7 @@ struct FfnFastArgs {
   const float* lr_a_scale;
   const float* lr_b_scale;
   float* keys_t;
-  hipEvent_t* stage_events;  // optional: 5 events recorded around the four kernels
+  hipEvent_t* stage_events;  // optional: 5 events recorded around the kernels (the last two behind the last one)
   unsigned long long* scorer_clocks;  // optional: start/end wall clock (100 MHz ticks) of every scorer workgroup
 };
 size_t ffn_fast_region_bytes();
@@ -365,9 +364,7 @@ void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_
                            size_t* hist_words);
 bool ffn_fast_supported(int B, int N, int d, int k, int kprime);
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime);  // the same route for groups of eight units
-int ffn_fast_dense_groups(int m1);
-void ffn_fast_shape(int d, int rows, int* row_groups, int* col_slices);
-size_t ffn_fast_partial_floats(int d, int k, int m1);
+int ffn_fast_entries(int N, int gs);
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s);
 
 // ---- ffn_shard.hip -----------------------------------------------------------

@@ -26,13 +26,11 @@ FAST = [
                             (32, "token quantised, sum |xq| known (anchors)"), (33, "integer dot products done"),
                             (34, "keys stored and counted into the window histogram")]),
     ("k_fast_gather", [(10, "kernel start"), (11, "keys, window and token requested and unpacked"),
-                       (18, "everything requested has arrived (profiling build only)"),
-                       (15, "window walked: threshold bin proposed"), (16, "keys above the bin counted, bin listed"),
-                       (17, "bin ranked: cut known"), (12, "selection returned"),
-                       (13, "this workgroup's rows listed in LDS"), (14, "rows read, activations stored and counted")]),
-    ("k_fast_w2", [(24, "kernel start (row slice known)"), (20, "window walked"), (21, "counted and listed"),
-                   (22, "ranked"), (25, "selection returned"), (26, "selected rows and coefficients in LDS"),
-                   (27, "second-layer rows read and accumulated"), (28, "reduced over the waves, y written")]),
+                       (15, "window walked: threshold bin known"), (12, "workgroup's units of the bin settled"),
+                       (13, "shortlisted units known"), (14, "rows read, activations stored and counted")]),
+    ("k_fast_w2", [(24, "kernel start"), (20, "window walked: threshold bin known"), (21, "keys sorted into above and bin"),
+                   (22, "bin settled"), (26, "selected rows listed"), (27, "second-layer rows read and accumulated"),
+                   (28, "reduced over the waves, y written")]),
 ]
 BATCH = [
     ("k_keys_select (top-k' of the keys)",

@@ -194,6 +194,21 @@ def test_second_layer_slices(hire, oracle, d, N, B, k, kp):
     T.check_ffn(layer, scorer, L, I.tokens(91 + B, B, d), k, kp)
 
 
+@pytest.mark.parametrize("d,N,k,kp,lr", [
+    (64, 4097, 4000, 4090, 0),      # beyond 4096 units, nearly everything selected: several lists of rows per wave
+    (96, 8193, 8193, 8193, 0),      # beyond 8192 units, everything selected, one unit in the last workgroup
+    (8192, 500, 60, 170, 0),        # longest token: four loads of a row per lane
+    (2080, 16384, 1300, 5000, 0),   # most units, k' beyond 4096; last column slice whole, slices not in pairs
+    (64, 8256, 700, 2500, 24),      # fp64 keys, more than four loads of them per thread
+])
+def test_batch1_gather_and_second_layer_edges(hire, oracle, d, N, k, kp, lr):
+    log(f"batch 1 d={d} N={N} k={k} kp={kp} rank={lr}")
+    L = I.lowrank_ffn_layer(97 + d, d, N, lr) if lr else I.ffn_layer(97 + d, d, N)
+    L["w1u"][N // 4:N // 4 + 40] = L["w1u"][N // 4]     # equal activations, and (int4) equal keys
+    layer, scorer = T.make_ffn_layer(L, lowrank=bool(lr))
+    T.check_ffn(layer, scorer, L, I.tokens(98, 1, d), k, kp)
+
+
 @pytest.mark.parametrize("B", [1, 4, 16])
 def test_ffn_step_1b_shape(hire, oracle, ffn_1b, B):
     """Config 2: d_m=2048, d_ff=16384, k=819, k'=3276, iid tokens, union across the batch."""
