@@ -59,8 +59,7 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
   __shared__ SelSharedT<kSelThreads> sh;
   __shared__ __align__(16) uint32_t win[kWin];
   __shared__ int wave_cnt[kSelWaves];
-  __shared__ uint32_t l_key[kFastAmbCap];
-  __shared__ int l_idx[kFastAmbCap];
+  __shared__ BinList<uint32_t> list;
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
   HIRE_TS(10);
   const float* row = keys + (size_t)b * stride;
@@ -80,57 +79,41 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
   int above;
   bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above);
   HIRE_TS(12);
-  Selection<uint32_t> sel;
-  if (known) {  // the bin's own few keys, ranked by every wave
-    const uint32_t lo = bin_floor<uint32_t>(bin), width = bin_floor<uint32_t>(bin + 1u) - lo;
-#pragma unroll
-    for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-      for (int q = 0; q < PER; ++q)
-        if (kr.r[e][q] - lo < width) {
-          const int p = atomicAdd(&sh.list_n, 1);
-          if (p < kFastAmbCap) {
-            l_key[p] = kr.r[e][q];
-            l_idx[p] = kr.index(e, q);
-          }
-        }
+  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
+  if (known) {
+    const BinMasks<uint32_t> bm = bin_masks<uint32_t>(kr, bin_floor<uint32_t>(bin), bin_floor<uint32_t>(bin + 1u));
+    list_inside<uint32_t>(kr, bm.inside, &sh.list_n, list);
     __syncthreads();
     HIRE_TS(13);
-    const int m = sh.list_n, need = kprime - above;
+    const int m = sh.list_n;
     known = m <= kFastAmbCap;  // uniform
-    if (known) {
-      const uint32_t mine_k = lane < m ? l_key[lane] : 0u;
-      const int mine_i = lane < m ? l_idx[lane] : 0x7FFFFFFF;
-      int rank = 0;
-      for (int u = 0; u < m; ++u)
-        rank += ranks_ahead(read_lane(mine_k, u), __builtin_amdgcn_readlane(mine_i, u), mine_k, mine_i) ? 1 : 0;
-      const int src = __builtin_ctzll(__ballot(lane < m && rank == need - 1));  // exactly one lane
-      sel.cut.key = read_lane(mine_k, src);
-      sel.cut.idx = __builtin_amdgcn_readlane(mine_i, src);
-      sel.plain = __ballot(lane < m && rank >= need && mine_k == sel.cut.key) == 0ull;
-    }
+    if (known)
+      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
+                                      kprime - above);
     HIRE_TS(14);
   }
   if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
     WinRegs<kSelThreads> none{};
-    sel = fast_select<60>(kr, row, kprime, none, 0u, false, sh, wave_cnt, window_misses, 0, kprime, true);
+    const Selection<uint32_t> sel =
+        fast_select<60>(kr, row, kprime, none, 0u, false, sh, wave_cnt, window_misses, 0, kprime, true);
+    take = 0u;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
   }
-  // A bitmap word covers 32 consecutive indices: the keys of 32 / PER neighbouring lanes of one load.  Those lanes
+  // A bitmap word covers 32 consecutive indices: the keys of eight neighbouring lanes of one load.  Those lanes
   // fold their bits together and one of them adds the word to the union.
-  constexpr int LPW = 32 / PER;
+  static_assert(PER == 4, "eight lanes per word");
+  take = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
 #pragma unroll
   for (int e = 0; e < LOADS; ++e) {
-    uint32_t bits = 0u;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const bool take = sel.plain ? kr.r[e][q] >= sel.cut.key
-                                  : (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)));
-      bits |= take ? 1u << q : 0u;
-    }
-    bits <<= (lane % LPW) * PER;
-#pragma unroll
-    for (int m = 1; m < LPW; m <<= 1) bits |= (uint32_t)__shfl_xor((int)bits, m);
-    if (lane % LPW == 0 && bits != 0u) atomicOr(&bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / LPW], bits);
+    uint32_t bits = (take >> (e * PER) & 15u) << (lane % 8 * PER);
+    bits |= dpp_move<0xB1, 0xF>(0u, bits);   // lanes 1, 0, 3, 2 of a quad
+    bits |= dpp_move<0x4E, 0xF>(0u, bits);   // lanes 2, 3, 0, 1
+    bits |= dpp_move<0x141, 0xF>(0u, bits);  // eight lanes mirrored: the other quad
+    if (lane % 8 == 0 && bits != 0u) atomicOr(&bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / 8], bits);
   }
   HIRE_TS(15);
 }
@@ -164,7 +147,7 @@ __device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row,
 
 struct RefineShared {
   SelSharedT<kSelThreads> sh;
-  __align__(16) uint32_t win[kWin];  // window histogram; then the packed outputs (k <= kWin / 2)
+  __align__(16) uint32_t win[kWin + 2 * kWave];  // window histogram; then the packed outputs (k <= kWin / 2)
   unsigned long long l_val[kBsCap];  // refined values (fp64 bits) and their units
   int l_idx[kBsCap];
   int wave_cnt[kSelWaves], wave_eq[kSelWaves];
@@ -314,29 +297,17 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
     const double lo_v = f - hw, hi_v = c + hw;
     const K lo_k = __float_as_uint(__double2float_rd(lo_v)), hi_k = __float_as_uint(__double2float_ru(hi_v));
     if (lo_v > 0.0) {  // uniform; non-negative floats order like their bit patterns
-      const K width = hi_k - lo_k;
-      int gt = 0;
-      uint32_t bits = 0u;  // bit e * PER + q: this lane's key (e, q) lies in the band
-#pragma unroll
-      for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-          gt += kr.r[e][q] > hi_k ? 1 : 0;
-          bits |= (K)(kr.r[e][q] - lo_k) <= width ? 1u << (e * PER + q) : 0u;
-        }
-      const int above = wave_sum(gt);
-      if (lane == 0) L.wave_cnt[w] = above;
-      uint32_t slots = 0u;  // list places of this lane's first four band keys
-      int nb = 0;
-      for (uint32_t m = bits; m != 0u; m &= m - 1u, ++nb) {
-        const int t = __builtin_ctz(m), slot = atomicAdd(&L.sh.list_n, 1);
-        if (slot < kBsCap) L.l_idx[slot] = kr.index(t / PER, t % PER);
-        if (nb < 4) slots |= (uint32_t)min(slot, 255) << (8 * nb);
+      // above: stored above hi_k; inside: in [lo_k, hi_k], the band
+      const BinMasks<K> bm = bin_masks<K>(kr, lo_k, hi_k + 1u);
+      for (uint32_t m = bm.inside; m != 0u;) {  // few lanes
+        const int i = pop_first(kr, m), slot = atomicAdd(&L.sh.list_n, 1);
+        if (slot < kBsCap) L.l_idx[slot] = i;
       }
+      const int above = wave_sum(__popc(bm.above));
+      if (lane == 0) L.wave_cnt[w] = above;
       __syncthreads();
       HIRE_TS(43);
-      const int pa = wave_scan_incl(lane < kSelWaves ? L.wave_cnt[lane] : 0);
-      const int A = __builtin_amdgcn_readlane(pa, kSelWaves - 1), C = L.sh.list_n, need = k - A;
+      const int A = wave_sum(lane < kSelWaves ? L.wave_cnt[lane] : 0), C = L.sh.list_n, need = k - A;
       if (C <= kBsCap && need >= 1 && need <= C) {  // uniform
         for (int i = w; i < C; i += kSelWaves) {    // a wave per entry
           const double s = wave_row_dot(p.W + (size_t)L.l_idx[i] * d, tok, d);
@@ -344,100 +315,92 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
         }
         __syncthreads();
         HIRE_TS(44);
-        // ranks (value descending, unit ascending), in every wave: lane l holds entries l and l + 64
-        unsigned long long kv[2];
-        int ki[2], rank[2] = {0, 0};
+        // Lane l holds entries l and l + 64.  A wave ranks (value descending, unit ascending) the entries of its own
+        // part of the row only, one or two: as many as are ahead of them, by ballots.
+        uint64_t kv[2], own[2], taken[2] = {0ull, 0ull};
+        int ki[2], enough = 0, beyond = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int i = lane + u * kWave;
-          kv[u] = i < C ? L.l_val[i] : 0ull;
-          ki[u] = i < C ? L.l_idx[i] : 0x7FFFFFFF;
+          const bool in = i < C;
+          kv[u] = in ? L.l_val[i] : 0ull;
+          ki[u] = in ? L.l_idx[i] : 0x7FFFFFFF;
+          const double v = __longlong_as_double((long long)kv[u]);
+          enough += __popcll(__ballot(in && v >= lo_v + 0.5 * hw));
+          beyond += __popcll(__ballot(in && v > hi_v - 0.5 * hw));
+          own[u] = __ballot(in && ki[u] >= kr.base && ki[u] - kr.base < kr.len);
         }
-        for (int j0 = 0; j0 < C; j0 += 4) {  // broadcast reads, four in flight
-          unsigned long long ov[4];
-          int oi[4];
+        // this lane's key that list entry l of half u stands for, as a bit e * PER + q (0: another lane's)
+        auto bit_here = [&](int u, int l) -> uint32_t {
+          const int r = __builtin_amdgcn_readlane(ki[u], l) - kr.base;
+          return lane == r % Keys::SPAN / PER ? 1u << (r / Keys::SPAN * PER + r % PER) : 0u;
+        };
+        uint32_t take = __brev(bm.above) >> (32 - LOADS * PER);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            ov[j] = L.l_val[min(j0 + j, C - 1)];
-            oi[j] = L.l_idx[min(j0 + j, C - 1)];
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (j0 + j < C) {
-              rank[0] += ranks_ahead((uint64_t)ov[j], oi[j], (uint64_t)kv[0], ki[0]) ? 1 : 0;
-              if (C > kWave) rank[1] += ranks_ahead((uint64_t)ov[j], oi[j], (uint64_t)kv[1], ki[1]) ? 1 : 0;
+        for (int u = 0; u < 2; ++u)
+          for (uint64_t m = own[u]; m != 0ull; m &= m - 1ull) {
+            const int l = __builtin_ctzll(m), i = __builtin_amdgcn_readlane(ki[u], l);
+            const uint64_t v = read_lane(kv[u], l);
+            const int ahead = __popcll(__ballot(lane < C && ranks_ahead(kv[0], ki[0], v, i))) +
+                              __popcll(__ballot(lane + kWave < C && ranks_ahead(kv[1], ki[1], v, i)));
+            if (ahead < need) {  // uniform
+              taken[u] |= 1ull << l;
+              take |= bit_here(u, l);
             }
-        }
-        double cut = 0.0;
-        uint64_t taken[2];
-        uint32_t selbits = 0u;
-        int lower = 0;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const bool in = lane + u * kWave < C, take = in && rank[u] < need;
-          const uint64_t last = __ballot(in && rank[u] == need - 1);
-          if (last != 0ull) cut = __longlong_as_double((long long)read_lane(kv[u], __builtin_ctzll(last)));
-          const int rel = ki[u] - kr.base;
-          taken[u] = __ballot(take && rel >= 0 && rel < kr.len);
-          lower += __popcll(__ballot(take && rel < 0));
-          for (uint64_t m = taken[u]; m != 0ull; m &= m - 1ull) {  // mark this wave's own at their lanes
-            const int r = __builtin_amdgcn_readlane(rel, __builtin_ctzll(m));
-            if (lane == (r % Keys::SPAN) / PER) selbits |= 1u << (r / Keys::SPAN * PER + r % PER);
           }
-        }
         HIRE_TS(45);
-        if (cut >= lo_v + 0.5 * hw && cut <= hi_v - 0.5 * hw) {  // uniform
-          int* pk_pos = reinterpret_cast<int*>(L.win);
-          float* pk_val = reinterpret_cast<float*>(L.win + kWin / 2);
-          const int above_before = w > 0 ? __builtin_amdgcn_readlane(pa, w - 1) : 0;
-          // This lane's selected keys of every load, counted in 16-bit fields (a wave holds at most 256 per load);
-          // two prefix sums over the lanes give the places of all of them at once.
-          uint32_t take = selbits;
-#pragma unroll
-          for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-            for (int q = 0; q < PER; ++q) take |= kr.r[e][q] > hi_k ? 1u << (e * PER + q) : 0u;
-          // recomputed values take the stored ones' places (few waves have any)
-          for (uint32_t m = selbits; __ballot(m != 0u) != 0ull; m &= m - 1u) {
-            const int t = m != 0u ? __builtin_ctz(m) : 0, n = __popc(bits & ((1u << t) - 1u));
-            int slot = (int)(slots >> (8 * (n & 3))) & 255;
-            if (n >= 4)
-              for (slot = 0; L.l_idx[slot] != kr.index(t / PER, t % PER);) ++slot;
-            const uint32_t now = m & (0u - m);
-            const K v = __float_as_uint((float)__longlong_as_double((long long)L.l_val[min(slot, kBsCap - 1)]));
-#pragma unroll
-            for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-              for (int q = 0; q < PER; ++q) kr.r[e][q] = (now >> (e * PER + q) & 1u) != 0u ? v : kr.r[e][q];
-          }
-          int run = above_before + lower;
+        // the need-th largest value lies in [lo_v + hw/2, hi_v - hw/2]
+        if (enough >= need && beyond < need) {  // uniform
+          if (lane == 0) L.wave_eq[w] = above + __popcll(taken[0]) + __popcll(taken[1]);
+          __syncthreads();
+          const int pa = wave_scan_incl(lane < kSelWaves ? L.wave_eq[lane] : 0);
+          int run = w > 0 ? __builtin_amdgcn_readlane(pa, w - 1) : 0;
+          // This lane's selected keys of every load, counted in 16-bit fields (a wave holds at most 256 per load):
+          // a prefix sum over the lanes gives the places of two loads at once.  A key that is not selected goes to a
+          // place of its lane that nobody reads: a predicate per key would cost more than its store.
+          uint2* pk = reinterpret_cast<uint2*>(L.win);
+          constexpr uint32_t kField = (1u << PER) - 1u;
+          int first[LOADS];
 #pragma unroll
           for (int e0 = 0; e0 < LOADS; e0 += 2) {
-            constexpr uint32_t kField = (1u << PER) - 1u;
             const int c0 = __popc(take >> (e0 * PER) & kField), c1 = __popc(take >> ((e0 + 1) * PER) & kField);
             const int incl = wave_scan_incl(c0 | c1 << 16), tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-            int at[2] = {run + (incl & 0xFFFF) - c0, run + (tot & 0xFFFF) + (incl >> 16) - c1};
+            first[e0] = run + (incl & 0xFFFF) - c0;
+            first[e0 + 1] = run + (tot & 0xFFFF) + (incl >> 16) - c1;
             run += (tot & 0xFFFF) + (tot >> 16);
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-              for (int q = 0; q < PER; ++q) {
-                const int bit = (e0 + f) * PER + q;
-                if ((take >> bit & 1u) != 0u) {
-                  pk_pos[at[f]] = kr.index(e0 + f, q);
-                  pk_val[at[f]++] = __uint_as_float(kr.r[e0 + f][q]);
-                }
-              }
           }
+#pragma unroll
+          for (int e = 0; e < LOADS; ++e) {
+            int at = first[e];
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+              const bool in = (take >> (e * PER + q) & 1u) != 0u;
+              pk[in ? at : kWin / 2 + lane] = make_uint2((uint32_t)kr.index(e, q), kr.r[e][q]);
+              at += in ? 1 : 0;
+            }
+          }
+          // recomputed values over the stored ones (a wave's stores to LDS stay in order)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            for (uint64_t m = taken[u]; m != 0ull; m &= m - 1ull) {
+              const int l = __builtin_ctzll(m);
+              const uint32_t bit = bit_here(u, l), v = __float_as_uint((float)__longlong_as_double((long long)read_lane(kv[u], l)));
+              if (bit != 0u) {
+                const int e = __builtin_ctz(bit) / PER;
+                int at = first[0];
+#pragma unroll
+                for (int f = 1; f < LOADS; ++f) at = e == f ? first[f] : at;
+                pk[at + __popc(take & (bit - 1u) & (kField << (e * PER)))].y = v;
+              }
+            }
           __syncthreads();
           HIRE_TS(46);
           for (int t = tid; t < k; t += kSelThreads) {
-            const int i = pk_pos[t];
-            const float v = pk_val[t];
+            const uint2 v = pk[t];
             const size_t o = (size_t)b * k + t;
-            p.list_out[o] = make_uint2((uint32_t)i, __float_as_uint(v));
-            if (p.idx_out) p.idx_out[o] = i;
-            if (p.val_out) p.val_out[o] = v;
+            p.list_out[o] = v;
+            if (p.idx_out) p.idx_out[o] = (int)v.x;
+            if (p.val_out) p.val_out[o] = __uint_as_float(v.y);
           }
           HIRE_TS(47);
           return;

@@ -365,24 +365,6 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   HIRE_TS(34);
 }
 
-// ---------------------------------------------------------------------------------------------------
-// Selection of the `need` largest keys, as kernels 2 and 3 do it.  The window histogram is exact - integer counts that
-// the producing kernel added for every positive key, all keys at or below the anchor - so the walk gives the bin of the
-// need-th key and the number of keys above it, and only the bin's own few keys (`list`, 64 at most) have to be compared:
-// no pass counts what lies above.
-template <typename K>
-struct BinList {
-  K key[kFastAmbCap];
-  int idx[kFastAmbCap];
-};
-// Of the entry (key, index): selected, if fewer than `need` of the m list entries, one per lane, are ahead of it (key
-// descending, index ascending).  A wave asks this for its own entries alone, one or two of them: ranking the whole list
-// in every wave cost a serial step per entry.
-template <typename K>
-__device__ __forceinline__ bool list_takes(K mine_k, int mine_i, int m, int need, K key, int idx) {
-  return (int)__popcll(__ballot(lane_id() < m && ranks_ahead(mine_k, mine_i, key, idx))) < need;
-}
-
 // Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -467,92 +449,6 @@ __device__ __forceinline__ void token_to_lds(const uint4* __restrict__ x, int xv
                         bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
 #pragma unroll
     for (int q = 0; q < 8; ++q) xtok[8 * i + q] = f[q];
-  }
-}
-
-// Places, in index order, of this lane's selected keys (bit e * PER + q of take): put(place, e, q), the wave's first
-// at `run`.  A wave holds at most 256 selected keys per load: the lanes' counts of two loads share a prefix sum.
-// Returns the place after the wave's last.
-template <typename Keys, typename Put>
-__device__ __forceinline__ int place_taken(uint32_t take, int run, Put&& put) {
-  constexpr int LOADS = Keys::kLoads, PER = Keys::PER;
-  constexpr uint32_t kField = (1u << PER) - 1u;
-#pragma unroll
-  for (int e0 = 0; e0 < LOADS; e0 += 2) {
-    const int c0 = __popc(take >> (e0 * PER) & kField), c1 = e0 + 1 < LOADS ? __popc(take >> ((e0 + 1) * PER) & kField) : 0;
-    const int incl = wave_scan_incl(c0 | c1 << 16), tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-    int at[2] = {run + (incl & 0xFFFF) - c0, run + (tot & 0xFFFF) + (incl >> 16) - c1};
-    run += (tot & 0xFFFF) + (tot >> 16);
-#pragma unroll
-    for (int f = 0; f < 2 && e0 + f < LOADS; ++f)
-#pragma unroll
-      for (int q = 0; q < PER; ++q)
-        if ((take >> ((e0 + f) * PER + q) & 1u) != 0u) put(at[f]++, e0 + f, q);
-  }
-  return run;
-}
-
-// One pass over a lane's keys against a bin: bit COUNT - 1 - j of above / inside says where key j = e * PER + q lies.
-// The masks are shifted in through the carry input: five instructions per key.
-template <typename K>
-struct BinMasks {
-  uint32_t above, inside;
-};
-template <typename K, typename Keys>
-__device__ __forceinline__ BinMasks<K> bin_masks(const Keys& kr, K lo, K up) {
-  BinMasks<K> m{0u, 0u};
-  const K width = up - lo;
-#pragma unroll
-  for (int e = 0; e < Keys::kLoads; ++e)
-#pragma unroll
-    for (int q = 0; q < Keys::PER; ++q) {
-      m.above = m.above + m.above + (kr.r[e][q] >= up ? 1u : 0u);
-      m.inside = m.inside + m.inside + ((K)(kr.r[e][q] - lo) < width ? 1u : 0u);
-    }
-  return m;
-}
-// Index of the key that the highest bit of m stands for; the bit is cleared.
-template <typename Keys>
-__device__ __forceinline__ int pop_first(const Keys& kr, uint32_t& m) {
-  constexpr int COUNT = Keys::kLoads * Keys::PER;
-  const int bit = 31 - __clz((int)m), j = COUNT - 1 - bit;
-  m ^= 1u << bit;
-  return kr.base + j / Keys::PER * Keys::SPAN + lane_id() * Keys::PER + j % Keys::PER;
-}
-// The bits of those keys of the wave that are among the list's `need` first, lane l holding entry l.
-template <typename Keys, typename K>
-__device__ __forceinline__ uint32_t taken_of_list(const Keys& kr, K mine_k, int mine_i, int m, int need) {
-  constexpr int COUNT = Keys::kLoads * Keys::PER;
-  uint32_t take = 0u;
-  for (uint64_t t = __ballot(lane_id() < m && mine_i >= kr.base && mine_i - kr.base < kr.len); t != 0ull; t &= t - 1ull) {
-    const int u = __builtin_ctzll(t), i = __builtin_amdgcn_readlane(mine_i, u), rel = i - kr.base;
-    const bool in = list_takes<K>(mine_k, mine_i, m, need, read_lane(mine_k, u), i);  // uniform
-    const int j = rel / Keys::SPAN * Keys::PER + rel % Keys::PER;
-    if (in && lane_id() == rel % Keys::SPAN / Keys::PER) take |= 1u << (COUNT - 1 - j);
-  }
-  return take;
-}
-// Key j of a lane, j not known at compile time: a tree of selections.
-template <int LO, int COUNT, typename Keys>
-__device__ __forceinline__ auto key_at(const Keys& kr, int j) {
-  if constexpr (COUNT == 1) {
-    return kr.r[LO / Keys::PER][LO % Keys::PER];
-  } else {
-    const auto a = key_at<LO, COUNT / 2>(kr, j), b = key_at<LO + COUNT / 2, COUNT / 2>(kr, j);
-    return (j & (COUNT / 2)) != 0 ? b : a;
-  }
-}
-// The keys that the masks place inside the bin -> list, in no particular order; list_n counts them, a barrier has to
-// follow.  Few lanes of few waves have any.
-template <typename K, typename Keys>
-__device__ __forceinline__ void list_inside(const Keys& kr, uint32_t inside, int* list_n, BinList<K>& list) {
-  constexpr int COUNT = Keys::kLoads * Keys::PER;
-  while (inside != 0u) {
-    const int j = COUNT - 1 - (31 - __clz((int)inside)), i = pop_first(kr, inside), at = atomicAdd(list_n, 1);
-    if (at < kFastAmbCap) {
-      list.key[at] = key_at<0, COUNT>(kr, j);
-      list.idx[at] = i;
-    }
   }
 }
 
