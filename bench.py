@@ -321,9 +321,10 @@ def main():
     gbps = by["total"] / (us_per_step * 1e-6) / 1e9
 
     # ---------------- per-stage times, live, with HIP events on the launch stream ----------------
-    # the three-kernel batch-1 route (units, or groups of eight)
-    fast = B == 1 and ((kind in ("ffn", "ffn_small", "ffn_g8", "ffn_cp") and scorer == "int4") or
-                       (kind == "ffn" and scorer in ("lowrank", "lrq")))
+    # the three-kernel route for few tokens (units, or groups of eight)
+    fast = ((B <= 8 and kind in ("ffn_g8", "ffn_cp") and scorer == "int4") or
+            (B <= 4 and kind in ("ffn", "ffn_small") and scorer == "int4") or
+            (B <= 4 and kind == "ffn" and scorer == "lrq") or (B == 1 and kind == "ffn" and scorer == "lowrank"))
     stages = hire.SOFTMAX_STAGES if kind == "softmax" else (hire.FAST_FFN_STAGES if fast else hire.FFN_STAGES)
     if shards > 1:
         stages = ("shard_step", "reduce")

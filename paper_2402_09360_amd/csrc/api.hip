@@ -11,7 +11,9 @@
 // all zero when the code object is loaded (which is the state hire_workspace_init gives a workspace).  In host
 // code this name only stands for the symbol; the memory is reached through the per-device address that
 // hipGetSymbolAddress returns (static_scratch below), never through the name.
-static __device__ __align__(256) unsigned char scratch[HIRE_STATIC_SCRATCH_BYTES];
+// (the regions of further tokens at the head of every workspace come on top of what is announced)
+constexpr size_t kStaticBytes = (size_t)HIRE_STATIC_SCRATCH_BYTES + (hire::kFastTokens - 1) * hire::kFastRegionBytes;
+static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 namespace {
 
@@ -40,7 +42,7 @@ struct Carver {
 };
 
 struct StepBuffers {
-  void* fast_region;  // fixed offset 0: cookie, maxima and histograms of the batch-1 four-kernel route
+  void* fast_region;  // fixed offset 0: state and histograms of the three-kernel route, a region per token
   HistRefs hist;      // general route: header at a fixed offset after the fast region; key histograms (long rows)
   uint32_t* window_misses;  // counter inside the header
   unsigned long long sig;  // names this layout
@@ -51,7 +53,8 @@ struct StepBuffers {
   double* t_partial; // its per-slice partial sums
   void* keys;        // fp32 or fp64 [B, key_stride]
   long long key_stride;
-  void* gkeys;       // group-sparse: summed absolute keys, same type, [B, N >> gs]
+  void* gkeys;       // group-sparse: summed absolute keys, same type, [B, N >> gs] ([B, gkey_stride] for 1 to 8 tokens)
+  long long gkey_stride;
   double* hg;        // group-sparse: summed absolute exact activations [B, cap_u]
   uint32_t* bitmap;  // candidate union bitmap, then (after it) the counters
   int32_t* counters; // [0] = |U|
@@ -59,7 +62,7 @@ struct StepBuffers {
   double* h;         // [B, cap_u]
   int32_t* pos;      // [B,k] positions inside U of every token's selected units
   uint2* list;       // [B,k] selected units as (row, coefficient), for the second layer
-  float* h32;        // batch-1 route: activations by unit (by group) in fp32
+  float* h32;        // few tokens: activations by unit (by group) in fp32
   float* u32;        // ... groups: the units'
   // filter and refine of the exact stage (batches): upper bounds of the tokens' norms, the fp32 stored values
   float* xnorm;      // [B]
@@ -93,13 +96,16 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
                                   : nullptr;
   const bool int4_like = scorer_kind == HIRE_SCORER_INT4 || scorer_kind == HIRE_SCORER_LRQ;
   s.by_unit = ffn && B >= kMfmaMinBatch && gs == 0 && batch_select_supported(N, k);
-  s.key_stride = s.by_unit ? (N + 3) / 4 * 4 : N;  // whole 16-byte vectors
+  const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
+                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the route for few tokens
+  s.key_stride = s.by_unit || (fast && gs == 0) ? (N + 3) / 4 * 4 : N;  // whole 16-byte vectors
   if (int4_like && N > kSingleWgMaxRow && gs == 0) s.hist.multi_body = c.take<char>(multi_body_bytes_host(B));
   if (int4_like) {
     s.xq = c.take<int8_t>((size_t)B * (d > r ? d : r));
     s.sumabs = c.take<float>(B);
     s.keys = c.take<float>((size_t)B * s.key_stride + 4);
-    if (gs > 0) s.gkeys = c.take<float>((size_t)B * Ns + 4);
+    s.gkey_stride = (Ns + 3) / 4 * 4;
+    if (gs > 0) s.gkeys = c.take<float>((size_t)B * s.gkey_stride + 4);
     if (scorer_kind == HIRE_SCORER_LRQ) {
       s.keys_t = c.take<float>((size_t)B * r + 4);
       s.t = c.take<uint16_t>((size_t)B * r);
@@ -127,14 +133,13 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
   // by_unit: one place for the exact route's activations and the refining selection's scratch
-  const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
-                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the batch-1 route
-  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2,
-               h64_doubles = s.by_unit ? (size_t)B * s.hf_stride : (fast ? ffn_fast_entries(N, gs) : 0);
+  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, row_doubles = s.by_unit ? (size_t)s.hf_stride : 0,
+               entry_doubles = fast ? (size_t)ffn_fast_entries(N, gs) : 0,
+               h64_doubles = (size_t)B * (row_doubles > entry_doubles ? row_doubles : entry_doubles);
   s.h = c.take<double>(h_doubles > h64_doubles ? h_doubles : h64_doubles);
   if (fast) {
-    s.h32 = c.take<float>(ffn_fast_entries(N, gs));
-    if (gs > 0) s.u32 = c.take<float>(ffn_fast_entries(N, 0));
+    s.h32 = c.take<float>((size_t)B * ffn_fast_entries(N, gs));
+    if (gs > 0) s.u32 = c.take<float>((size_t)B * ffn_fast_entries(N, 0));
   }
   s.h64 = s.by_unit ? s.h : nullptr;
   if (gs > 0) s.hg = c.take<double>((size_t)B * s.cap_u + 2);
@@ -402,7 +407,7 @@ int hire_debug_fast_state(const void* workspace, uint32_t* host_out3, void* stre
   HIRE_TRY(hipMemcpyAsync(host.data(), base + h1, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   HIRE_TRY(hipMemcpyAsync(host.data() + words, base + h2, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   HIRE_TRY(hipStreamSynchronize(st));
-  host_out3[0] = cookie == want ? 1u : 0u;
+  host_out3[0] = cookie - want < (unsigned long long)kFastTokens ? 1u : 0u;
   host_out3[1] = host_out3[2] = 0u;
   for (size_t i = 0; i < words; ++i) {
     host_out3[1] += host[i] != 0u ? 1u : 0u;
@@ -538,9 +543,10 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr && L->r <= 1024;
   const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && L->r <= 8192 &&
                         scorer_int4_fused_supported(d);
-  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic) {
+  if ((fast_int4 || (fast_lr && B == 1) || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic &&
+      !(B > 1 && g_force_exact_stage)) {
     FfnFastArgs a{};
-    a.N = N; a.d = d; a.k = k; a.kprime = kprime;
+    a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;
     a.q4 = L->q4; a.q4_scale = L->q4_scale;
     a.lowrank = fast_lr;
     a.lrq = fast_lrq;
@@ -554,7 +560,8 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     a.topk_idx = topk_idx; a.topk_val = topk_val;
     a.cand_out = cand_idx; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
     a.fast_region = s.fast_region;
-    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.h32 = s.h32;
+    a.keys = static_cast<float*>(s.keys); a.key_stride = s.key_stride; a.h = s.h; a.h32 = s.h32;
+    a.bitmap = s.bitmap; a.cand_scratch = s.cand; a.xq = s.xq; a.sumabs = s.sumabs;
     a.stage_events = g_stage_events;
     a.scorer_clocks = g_scorer_clocks;
     HIRE_TRY(launch_ffn_fast(a, st));
@@ -643,11 +650,11 @@ int hire_ffn_step_static(const hire_ffn_layer* L, const void* x, int B, int k, i
                          float* topk_val, int32_t* cand_idx, int32_t* n_cand, int32_t* scorer_acc, void* stream) {
   const size_t need = hire_ffn_workspace_bytes(L, B, k, kprime);
   if (need == 0) return HIRE_EINVAL;
-  if (need > (size_t)HIRE_STATIC_SCRATCH_BYTES) return HIRE_ENOSPC;
+  if (need > kStaticBytes) return HIRE_ENOSPC;
   void* ws = nullptr;
   if (const int rc = static_scratch(&ws); rc != HIRE_OK) return rc;
   return hire_ffn_step(L, x, B, k, kprime, y, topk_idx, topk_val, cand_idx, n_cand, scorer_acc, ws,
-                       (size_t)HIRE_STATIC_SCRATCH_BYTES, stream);
+                       kStaticBytes, stream);
 }
 
 static int group_shift(int group) {
@@ -700,17 +707,18 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   if (L->scorer_kind == HIRE_SCORER_INT4 && gs == 3 && ffn_fast_group8_supported(B, N, d, k, kprime) &&
-      !g_force_generic) {  // batch 1, groups of eight: the four-kernel route on group activations
+      !g_force_generic) {  // few tokens, groups of eight: the three-kernel route on group activations
     FfnFastArgs a{};
-    a.N = N; a.d = d; a.k = k; a.kprime = kprime;
+    a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;
     a.q4 = L->q4; a.q4_scale = L->q4_scale;
     a.w1u = static_cast<const uint16_t*>(L->w1u); a.w2u = static_cast<const uint16_t*>(L->w2u);
     a.x = static_cast<const uint16_t*>(x); a.y = y;
     a.topk_idx = topk_group; a.topk_val = topk_val;
     a.cand_out = cand_group; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
     a.fast_region = s.fast_region;
-    a.keys = static_cast<float*>(s.keys); a.h = s.h; a.h32 = s.h32;
-    a.gs = 3; a.gkeys = static_cast<float*>(s.gkeys); a.u32 = s.u32;
+    a.keys = static_cast<float*>(s.keys); a.key_stride = s.key_stride; a.h = s.h; a.h32 = s.h32;
+    a.bitmap = s.bitmap; a.cand_scratch = s.cand;
+    a.gs = 3; a.gkeys = static_cast<float*>(s.gkeys); a.gkey_stride = s.gkey_stride; a.u32 = s.u32;
     if (dense != nullptr && dense->m1 > 0) {
       a.dense_w1u = dense->w1u; a.dense_w2u = dense->w2u; a.m1 = dense->m1; a.h_dense = dense->h;
     }

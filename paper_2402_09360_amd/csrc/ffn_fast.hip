@@ -37,27 +37,9 @@
 // and stamps a cookie into the workspace; on a workspace without the cookie (first use, arbitrary contents) the
 // first selection of one step takes a slower histogram-free route.  The h histogram is cleared by the scorer
 // kernel of the step that uses it.  No kernel waits for, or counts, the workgroups of another.
-#include "fast_select.h"
-#include "kernels.h"
+#include "ffn_fast.h"
 
 namespace hire {
-
-constexpr unsigned long long kCookie = 0x48695245464e4f4cull;
-
-// Layout of the fast-path region at the head of the workspace.
-struct FastRegion {
-  unsigned long long cookie;
-  uint32_t fallbacks[2];     // steps whose k'-th key / k-th h were found without the histogram (statistics)
-  uint32_t bin1;             // threshold bin of the keys of the running step, 0: not known from the histogram; by the
-                             // gathering kernel, with need1 the keys of that bin that are selected
-  uint32_t anchor1, anchor2; // top bins of the two windows for the running step, written by the scorer kernel
-  uint32_t need1;
-  uint32_t zeros[8];         // stays zero: what lanes beyond the end of a key array load
-  uint32_t pad[48];
-  uint32_t hist1[kWin];      // slot s: scorer keys in fine bin anchor1 - s
-  uint32_t hist2[kWin];      // slot s: activations in fine bin anchor2 - s
-};
-static_assert(offsetof(FastRegion, zeros) == 32 && offsetof(FastRegion, hist1) == 256, "region layout");
 
 // ---------------------------------------------------------------------------------------------------
 // Kernel 1: scorer.
@@ -94,7 +76,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
 
   // token first (loads return in order, and the token is needed first), then the first rows' weights and
   // scales: all of these loads are in flight together
-  const bool hist_ok = fr->cookie == kCookie;
+  const bool hist_ok = clean_regions(fr) > 0;
   const float smax = __uint_as_float(q4[(size_t)N * cpr].x);  // largest row scale, kept behind the codes
   // the window of the activations, filled by the next kernel, starts from zero (its last reader was the step before)
   for (int i = (int)blockIdx.x * kST + tid; i < kWin; i += (int)gridDim.x * kST) fr->hist2[i] = 0u;
@@ -278,7 +260,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   const int sub = lane % ROW_LANES, rw = lane / ROW_LANES;
   const int cpr = r / 8;
   HIRE_TS(30);
-  const bool hist_ok = fr->cookie == kCookie;
+  const bool hist_ok = clean_regions(fr) > 0;
   const float umax = bounds[0], zmax = bounds[1];
   for (int i = (int)blockIdx.x * kST + tid; i < kWin; i += (int)gridDim.x * kST) fr->hist2[i] = 0u;
   float tsq = 0.0f, xsq = 0.0f;
@@ -365,9 +347,6 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   HIRE_TS(34);
 }
 
-// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // ---------------------------------------------------------------------------------------------------
 // Kernel 2: the shortlist and its exact pre-activations.  A workgroup owns 64 adjacent units, about a fifth of which
 // are shortlisted: with the threshold bin known from the walk, a ballot over its 64 keys names its rows, and their loads
@@ -382,7 +361,6 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // need 1.6 more for its list and are the last to end.
 constexpr int kGT = 1024;
 constexpr int kGW = kGT / kWave;
-constexpr int kOwnUnits = 64;  // units of a workgroup
 using GatherShared = SelSharedT<kGT>;
 
 struct FastGatherParams {
@@ -409,13 +387,6 @@ struct FastGatherParams {
 
 // relu(<row, x>) by a wave, the token as fp32 in LDS: sixteen bytes per lane and load, 256 chunks in flight; every bf16
 // product is exact in fp32 and the sums run in fp64.
-struct RowChunks {
-  uint4 v[4];
-  __device__ __forceinline__ void issue(const uint4* row, int c0, int cpr) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_streaming(&row[min(c0 + u * kWave + lane_id(), cpr - 1)]);
-  }
-};
 __device__ __forceinline__ double row_dot_relu(const uint4* row, RowChunks first, const float* __restrict__ xtok, int cpr) {
   const int lane = lane_id();
   double acc = 0.0;
@@ -477,7 +448,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   HIRE_TS(10);
   // every load of the selection goes out here, before the first wait
   const int n = p.N >> gs;
-  const bool hist_ok = p.fr->cookie == kCookie;
+  const bool hist_ok = clean_regions(p.fr) > 0;
   const uint32_t anchor1 = p.fr->anchor1, anchor2 = p.fr->anchor2;
   WinRegs<kGT> wr;
   wr.issue(p.fr->hist1);
@@ -612,41 +583,40 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
 constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
 using W2Shared = SelSharedT<kWT>;
-constexpr int kSliceCols = 32;  // columns per workgroup: 64 bytes of a row
-constexpr int kRowLanes = kSliceCols / 8;        // lanes that share a row: 16 bytes each
-constexpr int kRowsPerLoad = kWave / kRowLanes;  // rows a wave covers with one load instruction
-constexpr int kW2Batch = 8;       // loads a lane has in flight
-constexpr int kSegRows = kRowsPerLoad * kW2Batch;  // rows a wave lists at a time
+constexpr int kW2Batch = 8;  // loads a lane has in flight
 
-struct FastW2Params {
-  const float* h32;      // [n up to a multiple of 64] activations by unit (gs = 3: by group), 0: not shortlisted
+struct FastW2Params {    // (what the first loads need comes first)
+  FastRegion* fr;        // of the first token
+  const float* h32;      // [B, entries] activations by unit (gs = 3: by group), 0: not shortlisted
   const double* h64;     // the same in fp64, -1: not shortlisted
-  int n, k, d;           // entries, selected entries
-  FastRegion* fr;
-  const uint16_t* W2;    // [N, d] bf16
-  int32_t* topk_idx;     // optional [k]
-  float* topk_val;       // optional [k << gs]
-  float* y;              // [d]
+  int n, k, d, entries;  // entries ranked, selected; columns; n up to a whole workgroup of the gather
   int col_slices;
   int out_block;         // the workgroup that writes topk_idx / topk_val; -1: none
-  // the workgroup that writes the shortlist (-1: none): the kprime largest of the n keys, ascending
-  int list_block;
+  int list_block;        // the workgroup that writes the shortlist; -1: none
+  // gs = 3 (group-sparse step): entries are groups of eight units, u32 holds the units' activations.
+  int gs;
+  const float* u32;      // [B, entries << gs]
+  const uint16_t* W2;    // [N, d] bf16
+  float* y;              // [B, d]
+  const uint16_t* W2d;   // CommonPath: y += fl32(hd[r]) * W2d[r, :], r < m1
+  const double* hd;      // [B, m1]
+  int m1;
+  int B;                 // tokens, a row of workgroups each
+  int32_t* topk_idx;     // optional [B, k]
+  float* topk_val;       // optional [B, k << gs]
+  // the shortlist, ascending: the kprime largest of the n keys; of several tokens the union, with its length
   const void* keys;
   int kprime;
   int32_t* cand_out;
-  // gs = 3 (group-sparse step): entries are groups of eight units, u32 holds the units' activations.
-  int gs;
-  const float* u32;
-  const uint16_t* W2d;   // CommonPath: y += fl32(hd[r]) * W2d[r, :], r < m1
-  const double* hd;
-  int m1;
+  const uint32_t* bitmap;
+  int32_t* n_cand;
 };
 
 // Column slice of a workgroup: slices 2i and 2i+1 are the two halves of the same 128-byte lines; they go to
 // workgroups b and b + 8, which the dispatcher places on the same die (workgroups go round the eight dies),
 // so that the second half of a line is found in that die's L2.
 __device__ __forceinline__ int slice_of(int b, int slices) {
-  if (kSliceCols != 32 || slices % 16 != 0) return b;
+  if (slices % 16 != 0) return b;
   return 2 * (b % 8) + (b / 8) % 2 + 16 * (b / 16);
 }
 
@@ -698,7 +668,7 @@ __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& 
 
 // KEY: the scorer keys' bit patterns (what the candidate list is selected from); LOADS: 16-byte loads of fp32
 // activations per thread.
-template <typename KEY, int LOADS>
+template <typename KEY, int LOADS, int COLS>
 __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   using K = uint32_t;
   using Keys = KeyRegs<K, LOADS, kWT>;
@@ -706,23 +676,39 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   __shared__ W2Shared sh;
   __shared__ BinList<KEY> list;
   __shared__ int wave_cnt[kWW], wave_eq[kWW];
-  __shared__ int seg[kWW][kSegRows];  // selected entries of every wave
-  static_assert(kRowLanes == 4 && kWW == 16, "four slots per DPP row, sixty-four rows to reduce");
-  __shared__ float red[4 * kWW][kSliceCols];
-  __shared__ float red2[8][kSliceCols];
+  constexpr int kRowLanes = COLS / 8;                // lanes that share a row: 16 bytes each
+  constexpr int kRowsPerLoad = kWave / kRowLanes;    // rows a wave covers with one load instruction
+  constexpr int kSegRows = kRowsPerLoad * kW2Batch;  // rows a wave lists at a time
+  static_assert((kRowLanes == 4 || kRowLanes == 8 || kRowLanes == 16) && kWW == 16, "whole DPP rows, 64 rows to reduce");
+  __shared__ int seg[kWW][kSegRows];                 // selected entries of every wave
+  __shared__ float red[4 * kWW][COLS];
+  __shared__ float red2[8][COLS];
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const bool output = (int)blockIdx.x == p.out_block;  // uniform
+  if ((int)blockIdx.x == p.list_block && p.B > 1) {
+    if (blockIdx.y > 0) return;
+    const int cnt = list_bitmap<kWT>(p.bitmap, (p.n + 31) / 32, p.cand_out, sh);
+    if (tid == 0 && p.n_cand) *p.n_cand = cnt;
+    return;
+  }
   if ((int)blockIdx.x == p.list_block) {
     list_shortlist<KEY, LOADS * (int)(sizeof(KEY) / 4)>(p, sh, wave_cnt, list);
     return;
   }
-  const int cs = slice_of((int)blockIdx.x, p.col_slices);
+  if ((int)blockIdx.x >= p.col_slices && !output) return;  // (the grid is padded)
+  const int cs = COLS == 32 ? slice_of((int)blockIdx.x, p.col_slices) : (int)blockIdx.x;
+  const size_t b = blockIdx.y;  // token
+  FastRegion* fr = p.fr + b;
+  const float* h32 = p.h32 + b * p.entries;
+  const double* h64 = p.h64 + b * p.entries;
+  const float* u32 = p.u32 + (b * p.entries << p.gs);  // (gs = 3 only)
   HIRE_TS(24);
-  const uint32_t anchor2 = p.fr->anchor2;
+  const uint32_t anchor2 = fr->anchor2;
+  const int clean = clean_regions(p.fr);  // (asked for here: at the end its latency would count)
   WinRegs<kWT> wr;
-  wr.issue(p.fr->hist2);
+  wr.issue(fr->hist2);
   Keys kr;
-  kr.issue(p.h32, p.n, p.fr->zeros);
+  kr.issue(h32, p.n, p.fr->zeros);
   if (tid == 0) sh.list_n = 0;
   kr.finish();
   // the activations' window is valid on any workspace: this step's scorer kernel cleared it, its gather filled it
@@ -746,7 +732,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     if (known) {
       // the fp64 values of the bin's keys: they order what fp32 cannot
       const int mine_i = lane < m ? list.idx[lane] : 0x7FFFFFFF;
-      const uint64_t mine_k = lane < m ? (uint64_t)__double_as_longlong(p.h64[mine_i]) : 0ull;
+      const uint64_t mine_k = lane < m ? (uint64_t)__double_as_longlong(h64[mine_i]) : 0ull;
       take = bm.above | taken_of_list<Keys>(kr, mine_k, mine_i, m, need);
     }
     HIRE_TS(22);
@@ -757,7 +743,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     const uint64_t t = wg_kth_largest<uint64_t>(
         [&](auto&& f) {
 #pragma unroll 1
-          for (int i = tid; i < p.n; i += kWT) f(order_key(p.h64[i]));
+          for (int i = tid; i < p.n; i += kWT) f(order_key(h64[i]));
         },
         p.n, p.k, sh);
     int gt = 0, eq = 0;
@@ -766,7 +752,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
 #pragma unroll
       for (int q = 0; q < PER; ++q)
         if (kr.valid(e, q)) {
-          const uint64_t key = order_key(p.h64[kr.index(e, q)]);
+          const uint64_t key = order_key(h64[kr.index(e, q)]);
           gt += key > t ? 1 : 0;
           eq += key == t ? 1 : 0;
         }
@@ -790,7 +776,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       int c = 0;
 #pragma unroll
       for (int q = 0; q < PER; ++q) {
-        key[q] = kr.valid(e, q) ? order_key(p.h64[kr.index(e, q)]) : 0ull;
+        key[q] = kr.valid(e, q) ? order_key(h64[kr.index(e, q)]) : 0ull;
         c += key[q] == t ? 1 : 0;
       }
       const int incl = wave_scan_incl(c);
@@ -814,17 +800,17 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     uint32_t ordered = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
     place_taken<Keys>(ordered, run, [&](int at, int e, int q) {
       const int i = kr.index(e, q);
-      if (p.topk_idx) p.topk_idx[at] = i;
+      if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
       if (p.topk_val) {
-        if (gs == 0) p.topk_val[at] = __uint_as_float(kr.r[e][q]);
+        if (gs == 0) p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
         else
-          for (int l = 0; l < (1 << gs); ++l) p.topk_val[(at << gs) + l] = p.u32[(i << gs) + l];
+          for (int l = 0; l < (1 << gs); ++l) p.topk_val[((b * p.k + at) << gs) + l] = u32[(i << gs) + l];
       }
     });
   } else {
     // rows of the wave: slot-th of every sixteen, eight columns per lane
     const int slot = lane / kRowLanes, part = lane % kRowLanes;
-    const int colc = min(cs * kSliceCols + part * 8, p.d - 8);
+    const int colc = min(cs * COLS + part * 8, p.d - 8);
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto add_rows = [&](const uint4 (&wv)[kW2Batch], const float (&cf)[kW2Batch]) {
 #pragma unroll
@@ -839,7 +825,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     // their coefficients are loaded with the rows.
     const int mine_n = __popc(take), incl = wave_scan_incl(mine_n);
     const int rows = __builtin_amdgcn_readlane(incl, kWave - 1) << gs;
-    const float* coef = gs == 0 ? p.h32 : p.u32;
+    const float* coef = gs == 0 ? h32 : u32;
     for (int c0 = 0; c0 < rows; c0 += kSegRows) {  // uniform over the wave; one trip for most
       int at = incl - mine_n - (c0 >> gs);
       for (uint32_t m = take; m != 0u; ++at) {
@@ -874,57 +860,57 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       for (int u = 0; u < kW2Batch; ++u) {
         const int r = r0 + u * kWW * kRowsPerLoad, rc = min(r, p.m1 - 1);
         wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc));
-        const float c = (float)p.hd[rc];
+        const float c = (float)p.hd[b * p.m1 + rc];
         cf[u] = r < p.m1 ? c : 0.0f;
       }
       add_rows(wv, cf);
     }
     HIRE_TS(27);
-    // fixed-order reduction: the four slots of a DPP row (its last four lanes then hold their sums), the rows of all
+    // fixed-order reduction: the slots of a DPP row (its last lanes then hold their sums), the rows of all
     // waves in eight groups, the groups
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      acc[q] += dpp_move<0x114, 0xF>(0.0f, acc[q]);
-      acc[q] += dpp_move<0x118, 0xF>(0.0f, acc[q]);
+      if constexpr (kRowLanes == 4) acc[q] += dpp_move<0x114, 0xF>(0.0f, acc[q]);
+      if constexpr (kRowLanes <= 8) acc[q] += dpp_move<0x118, 0xF>(0.0f, acc[q]);
     }
-    if ((lane & 15) >= 12) {
+    if ((lane & 15) >= 16 - kRowLanes) {
       float4* dst = reinterpret_cast<float4*>(&red[w * 4 + (lane >> 4)][part * 8]);
       dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
       dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
     }
     __syncthreads();
-    if (tid < 8 * kSliceCols) {
-      const int c = tid % kSliceCols, j = tid / kSliceCols;
+    if (tid < 8 * COLS) {
+      const int c = tid % COLS, j = tid / COLS;
       float t = 0.0f;
 #pragma unroll
       for (int u = 0; u < 8; ++u) t += red[j * 8 + u][c];
       red2[j][c] = t;
     }
     __syncthreads();
-    if (tid < kSliceCols) {
-      const int c = cs * kSliceCols + tid;
+    if (tid < COLS) {
+      const int c = cs * COLS + tid;
       if (c < p.d) {
         float t = 0.0f;
 #pragma unroll
         for (int u = 0; u < 8; ++u) t += red2[u][tid];
-        p.y[c] = t;
+        p.y[b * p.d + c] = t;
       }
     }
     HIRE_TS(28);
   }
   // The key histogram has served its purpose: the workgroups clear it between them and say so in the
   // cookie (the same value from each; the next kernel that looks at either starts after this one has ended).
-  for (int i = (int)blockIdx.x * kWT + tid; i < kWin; i += p.col_slices * kWT) p.fr->hist1[i] = 0u;
-  if (tid == 0) p.fr->cookie = kCookie;
+  for (int i = (int)blockIdx.x * kWT + tid; i < kWin; i += p.col_slices * kWT) fr->hist1[i] = 0u;
+  if (tid == 0) p.fr->cookie = kCookie + (unsigned long long)max(clean, p.B);
 }
 
 // ---------------------------------------------------------------------------------------------------
-size_t ffn_fast_region_bytes() { return sizeof(FastRegion); }
+size_t ffn_fast_region_bytes() { return kFastTokens * sizeof(FastRegion); }
 size_t ffn_fast_fallbacks_offset() { return offsetof(FastRegion, fallbacks); }
 void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_t* hist1_off, size_t* hist2_off,
                            size_t* hist_words) {
   *cookie_off = offsetof(FastRegion, cookie);
-  *cookie = kCookie;
+  *cookie = kCookie + 1;
   *hist1_off = offsetof(FastRegion, hist1);
   *hist2_off = offsetof(FastRegion, hist2);
   *hist_words = kWin;
@@ -938,11 +924,12 @@ int ffn_fast_entries(int N, int gs) { return ((N + kOwnUnits - 1) / kOwnUnits * 
 
 // Group-sparse step with groups of eight: N, k, k' count units.  The selections see N/8, k'/8 and k/8 entries.
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime) {
-  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime);
+  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime, true);
 }
 
-bool ffn_fast_supported(int B, int N, int d, int k, int kprime) {
-  return B == 1 && N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 && k >= 1 && kprime <= N;
+bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool groups) {
+  return (B == 1 || ffn_fast_tokens_supported(B, d, groups)) && N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 &&
+         k >= 1 && kprime <= N;
 }
 
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
@@ -954,7 +941,8 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   const int gs = a.gs;  // 0, or 3 for groups of eight units
   // what the selections rank: units with their keys and activations, or groups with their summed ones
   const int n_sel = a.N >> gs, kp_sel = a.kprime >> gs, k_sel = a.k >> gs;
-  const bool lowrank = a.lowrank;
+  const bool lowrank = a.lowrank, several = a.B > 1;
+  if (several && lowrank) return hipErrorInvalidValue;
   const void* sel_keys = lowrank ? static_cast<const void*>(a.keys64) : (gs ? a.gkeys : a.keys);
   if (lowrank) {
     if (gs != 0 || a.m1 != 0 || a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
@@ -975,15 +963,26 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     // first product: the r rows of the int4 copy of Z1^T against the token (no phi), fp32 intermediate; then the
     // scorer kernel on the int4 copy of Z2 with that intermediate as its token
     if (gs != 0 || a.m1 != 0 || a.r < 32 || a.r > 8192 || a.r % 32 != 0) return hipErrorInvalidValue;
-    e = launch_scorer_int4_fused(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.x, false, a.r, a.d, 0,
-                                 a.keys_t, nullptr, HistRefs{nullptr, nullptr}, nullptr, 0, 0ull, s);
-    if (e != hipSuccess) return e;
-    const size_t lds = (size_t)a.r * 2 + (size_t)a.r;
-    e = launch(k_fast_score_int4<true>, dim3(score_blocks), dim3(kST), lds, s, reinterpret_cast<const uint4*>(a.lr_b),
-               a.lr_b_scale, reinterpret_cast<const uint32_t*>(a.keys_t), a.N, a.r, a.keys, static_cast<int32_t*>(nullptr),
-               fr, a.scorer_clocks, static_cast<float*>(nullptr), reinterpret_cast<const uint4*>(a.x), a.d,
-               a.norm_bounds);
-    if (e != hipSuccess) return e;
+    if (several) {
+      if ((e = launch_quantize_tokens(a.x, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
+      e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.xq, a.B, a.r, a.d, 0, a.keys_t,
+                                  a.r, nullptr, HistRefs{nullptr, nullptr}, s);
+      if (e != hipSuccess) return e;
+      if ((e = launch_fast_score_tokens(a, a.keys_t, true, s)) != hipSuccess) return e;
+    } else {
+      e = launch_scorer_int4_fused(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.x, false, a.r, a.d, 0,
+                                   a.keys_t, nullptr, HistRefs{nullptr, nullptr}, nullptr, 0, 0ull, s);
+      if (e != hipSuccess) return e;
+      const size_t lds = (size_t)a.r * 2 + (size_t)a.r;
+      e = launch(k_fast_score_int4<true>, dim3(score_blocks), dim3(kST), lds, s, reinterpret_cast<const uint4*>(a.lr_b),
+                 a.lr_b_scale, reinterpret_cast<const uint32_t*>(a.keys_t), a.N, a.r, a.keys, static_cast<int32_t*>(nullptr),
+                 fr, a.scorer_clocks, static_cast<float*>(nullptr), reinterpret_cast<const uint4*>(a.x), a.d,
+                 a.norm_bounds);
+      if (e != hipSuccess) return e;
+    }
+    if ((e = mark(1)) != hipSuccess) return e;
+  } else if (several) {
+    if ((e = launch_fast_score_tokens(a, a.x, false, s)) != hipSuccess) return e;
     if ((e = mark(1)) != hipSuccess) return e;
   } else {
     const size_t lds = (size_t)a.d * 2 + (size_t)a.d;
@@ -994,7 +993,10 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     if ((e = mark(1)) != hipSuccess) return e;
   }
-  {
+  if (several) {
+    if ((e = launch_fast_gather_tokens(a, s)) != hipSuccess) return e;
+    if ((e = mark(2)) != hipSuccess) return e;
+  } else {
     FastGatherParams p{};
     p.keys = sel_keys; p.N = a.N; p.kprime = kp_sel; p.d = a.d;
     p.fr = fr; p.W1 = a.w1u; p.x = reinterpret_cast<const uint4*>(a.x);
@@ -1016,18 +1018,34 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     FastW2Params p{};
     p.h32 = a.h32; p.h64 = a.h; p.n = n_sel; p.k = k_sel; p.d = a.d; p.fr = fr; p.W2 = a.w2u;
     p.topk_idx = a.topk_idx; p.topk_val = a.topk_val; p.y = a.y;
-    p.col_slices = (a.d + kSliceCols - 1) / kSliceCols;
+    p.B = a.B; p.entries = ffn_fast_entries(a.N, gs); p.bitmap = a.bitmap; p.n_cand = a.n_cand;
+    // The narrowest slices whose workgroups fit the compute units, one each: what is left over would wait for a whole
+    // workgroup's time (registers do not admit two).
+    const int extra = (a.topk_idx || a.topk_val ? 1 : 0) + (a.cand_out || (several && a.n_cand) ? 1 : 0);
+    int cols = 32;
+    while (cols < 128 && ((a.d + cols - 1) / cols + extra) * a.B > 256) cols *= 2;
+    if (lowrank) cols = 32;
+    p.col_slices = (a.d + cols - 1) / cols;
     int blocks = p.col_slices;
     p.out_block = a.topk_idx || a.topk_val ? blocks++ : -1;
-    p.list_block = a.cand_out ? blocks++ : -1;
-    p.keys = sel_keys; p.kprime = kp_sel; p.cand_out = a.cand_out;
+    p.list_block = a.cand_out || (several && a.n_cand) ? blocks++ : -1;
+    // several tokens read the dense rows of a slice: on one die (workgroups go round the eight), so that they come from
+    // its L2 for all but the first
+    if (several && a.m1 > 0) blocks = (blocks + 7) / 8 * 8;
+    p.keys = sel_keys; p.kprime = kp_sel; p.cand_out = a.cand_out ? a.cand_out : a.cand_scratch;
     p.gs = gs; p.u32 = a.u32;
     p.W2d = a.dense_w2u; p.hd = a.h_dense; p.m1 = a.m1;
-    auto go = [&](auto kernel) { return launch(kernel, dim3(blocks), dim3(kWT), 0, s, p); };
+    auto go = [&](auto kernel) { return launch(kernel, dim3(blocks, a.B), dim3(kWT), 0, s, p); };
+    auto by_cols = [&](auto k32, auto k64, auto k128) { return cols == 32 ? go(k32) : (cols == 64 ? go(k64) : go(k128)); };
     if (lowrank)
-      e = n_sel <= 4096 ? go(k_fast_w2<uint64_t, 1>) : (n_sel <= 8192 ? go(k_fast_w2<uint64_t, 2>) : go(k_fast_w2<uint64_t, 4>));
+      e = n_sel <= 4096 ? go(k_fast_w2<uint64_t, 1, 32>)
+                        : (n_sel <= 8192 ? go(k_fast_w2<uint64_t, 2, 32>) : go(k_fast_w2<uint64_t, 4, 32>));
+    else if (n_sel <= 4096)
+      e = by_cols(k_fast_w2<uint32_t, 1, 32>, k_fast_w2<uint32_t, 1, 64>, k_fast_w2<uint32_t, 1, 128>);
+    else if (n_sel <= 8192)
+      e = by_cols(k_fast_w2<uint32_t, 2, 32>, k_fast_w2<uint32_t, 2, 64>, k_fast_w2<uint32_t, 2, 128>);
     else
-      e = n_sel <= 4096 ? go(k_fast_w2<uint32_t, 1>) : (n_sel <= 8192 ? go(k_fast_w2<uint32_t, 2>) : go(k_fast_w2<uint32_t, 4>));
+      e = by_cols(k_fast_w2<uint32_t, 4, 32>, k_fast_w2<uint32_t, 4, 64>, k_fast_w2<uint32_t, 4, 128>);
     if (e != hipSuccess) return e;
   }
   return mark(3);

@@ -1,0 +1,724 @@
+// HiRE-FFN step for two to eight tokens (arXiv 2402.09360, Algorithm 1 + eq. (4)): the scorer and the gather of the
+// batch-1 sequence (ffn_fast.hip) for several tokens at once; the second layer is that sequence's own kernel, a row of
+// workgroups per token.
+//
+// The longer sequence for batches runs seven kernels, of which the two selections keep one compute unit per token busy
+// for 6 and 10 us: at a few tokens that is a third of the step.  Here nothing runs on a unit per token.  The scorer
+// counts every token's keys into a window histogram in memory; every workgroup of the gather walks all tokens'
+// histograms, knows which of its own 64 units are shortlisted, and forms their activations for all tokens in fp64 on
+// the matrix cores, so that no band around the threshold has to be computed again.
+#include "ffn_fast.h"
+
+namespace hire {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int kTT = 1024;  // threads
+constexpr int kTW = kTT / kWave;
+constexpr int kTokRows = 64;  // rows of a workgroup of the scorer
+
+// ---------------------------------------------------------------------------------------------------
+// Kernel 1: scorer.  Every workgroup quantises the tokens itself (a kernel for that alone costs 3.3 us), kTW / TT waves
+// per token, then scores 64 rows on the int8 matrix cores, four rows per wave: v_mfma_i32_4x4x4 takes row l % 4 and
+// token l % 4 from lane l and adds up sixteen blocks of columns l / 4 separately, so that a load covers 256 bytes of
+// four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 11.8 us against 3.3 +
+// 7.6 with the quantisation in front; 5.6 of them until the keys are stored, the rest is the 33000 counts in memory.
+// TT: tokens rounded up to four or eight; VECS: 16-byte vectors of a token per thread.  LRQ: as in k_fast_score_int4.
+struct FastScoreTokens {
+  const uint4* q4;
+  const float* scale;
+  const void* x;       // [B, d] bf16 (LRQ: fp32)
+  int B, N, d;
+  float* keys;         // [B, stride]
+  long long stride;
+  int32_t* acc_out;    // optional [B, N]
+  FastRegion* fr;
+  float* gkeys;        // groups of eight: [B, gstride] their activations, which are ranked instead of the units' keys
+  long long gstride;
+  const uint4* xn;     // LRQ: the tokens, [B, xn_d]
+  int xn_d;
+  const float* umax;
+};
+
+template <bool LRQ, int TT, int VECS>
+__global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
+  constexpr int kWPT = kTW / TT;  // waves per token
+  extern __shared__ uint4 xs[];              // [TT][d / 16 + 1] int8 codes
+  __shared__ float red[kTW], isum[kTW], xsqs[kTW];
+  __shared__ float sxs[TT];
+  __shared__ int part[4][TT][kTokRows];      // columns' share, token, row
+  __shared__ float unit_keys[TT][kTokRows];
+  HIRE_TS(30);
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int B = p.B, N = p.N, d = p.d;
+  const int cpr = d / 32, xstride = d / 16 + 1;
+  const int clean = clean_regions(p.fr);
+  const float smax = __uint_as_float(p.q4[(size_t)N * cpr].x);  // largest row scale, kept behind the codes
+  // the windows of the activations, filled by the next kernel, start from zero
+  for (int i = (int)blockIdx.x * kTT + tid; i < B * kWin; i += (int)gridDim.x * kTT)
+    p.fr[i / kWin].hist2[i % kWin] = 0u;
+  const int t = w / kWPT, lt = w % kWPT * kWave + lane, nvec = d / 8;
+  auto token_vec = [&](int i) -> uint4 {
+    const size_t at = (size_t)min(t, B - 1) * nvec + min(i, nvec - 1);
+    if constexpr (!LRQ) {
+      return reinterpret_cast<const uint4*>(p.x)[at];
+    } else {
+      const uint4 a = reinterpret_cast<const uint4*>(p.x)[2 * at], b = reinterpret_cast<const uint4*>(p.x)[2 * at + 1];
+      auto rne = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; };
+      return make_uint4(rne(a.x) | (rne(a.y) << 16), rne(a.z) | (rne(a.w) << 16), rne(b.x) | (rne(b.y) << 16),
+                        rne(b.z) | (rne(b.w) << 16));
+    }
+  };
+  // All loads are unconditional: the wait for the tokens must not become one for the weights, which are issued next.
+  uint4 xv[VECS];
+#pragma unroll
+  for (int m = 0; m < VECS; ++m) xv[m] = token_vec(m * kWPT * kWave + lt);
+  // the wave's rows, sixteen chunks of sixteen bytes per load, four loads at a time
+  const int nsl = (cpr + 15) / 16;
+  const uint4* wrow = p.q4 + (size_t)min((int)blockIdx.x * kTokRows + w * 4 + (lane & 3), N - 1) * cpr;
+  uint4 wv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) wv[i] = load_streaming(&wrow[min(i * 16 + (lane >> 2), cpr - 1)]);
+  const float row_scale = p.scale[min((int)blockIdx.x * kTokRows + lane, N - 1)];
+
+  float amax = 0.0f;
+#pragma unroll
+  for (int m = 0; m < VECS; ++m) {
+    const uint32_t ud[4] = {xv[m].x, xv[m].y, xv[m].z, xv[m].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(ud[q])), fabsf(bf16_hi(ud[q]))));
+  }
+  amax = wave_max(amax);
+  if (lane == 0) red[w] = amax;
+  if constexpr (LRQ) {
+    float xsq = 0.0f;
+    for (int i = lt; i < p.xn_d / 8; i += kWPT * kWave) {
+      const uint4 u = p.xn[(size_t)min(t, B - 1) * (p.xn_d / 8) + i];
+      const uint32_t ud[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float a = bf16_lo(ud[q]), b = bf16_hi(ud[q]);
+        xsq = fmaf(a, a, xsq);
+        xsq = fmaf(b, b, xsq);
+      }
+    }
+    xsq = wave_sum(xsq);
+    if (lane == 0) xsqs[w] = xsq;
+  }
+  lds_barrier();
+  HIRE_TS(31);
+  amax = wave_max(lane < kWPT ? red[t * kWPT + lane] : 0.0f);
+  float sx = __fdiv_rn(amax, 127.0f);
+  if (amax == 0.0f) sx = 1.0f;
+  // code = rint(x / sx), the quotient correctly rounded: with the correctly rounded reciprocal of a divisor whose
+  // significand is not all ones, one residual corrects the product (Markstein, IBM J. Res. Dev. 34, 1990).  The
+  // division itself where that does not apply or the residual could underflow.
+  const float rs = __fdiv_rn(1.0f, sx);
+  const bool plain = sx > 0x1p-100f && sx < 0x1p100f && (__float_as_uint(sx) & 0x7FFFFFu) != 0x7FFFFFu;  // uniform
+  float sabs = 0.0f;
+#pragma unroll
+  for (int m = 0; m < VECS; ++m)
+    if (m * kWPT * kWave < nvec) {  // uniform
+      const uint32_t ud[4] = {xv[m].x, xv[m].y, xv[m].z, xv[m].w};
+      float r[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float f = (e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), y = f * rs;
+        r[e] = rintf(fmaf(fmaf(-y, sx, f), rs, y));
+      }
+      if (!plain) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          r[e] = rintf(__fdiv_rn((e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), sx));
+      }
+      uint32_t packed[2] = {0u, 0u};
+      float sum8 = 0.0f;
+      const int i = m * kWPT * kWave + lt;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        r[e] = fminf(fmaxf(r[e], -127.0f), 127.0f);
+        sum8 += fabsf(r[e]);
+        packed[e / 4] = __builtin_amdgcn_cvt_pk_u8_f32(r[e] + 128.0f, e & 3, packed[e / 4]);  // (whole numbers)
+      }
+      if (i < nvec) {
+        sabs += sum8;
+        reinterpret_cast<uint2*>(xs + t * xstride)[i] = make_uint2(packed[0] ^ 0x80808080u, packed[1] ^ 0x80808080u);
+      }
+    }
+  sabs = wave_sum(sabs);
+  if (lane == 0) {
+    isum[w] = sabs;
+    if (w % kWPT == 0) sxs[t] = sx;
+  }
+  lds_barrier();
+  HIRE_TS(32);
+
+  // Wave b will take the 64 keys of token b; its bounds, those of k_fast_score_int4, while the weights are under way.
+  const int b = w, bt = min(w, TT - 1);
+  const bool here = b < B;
+  const float sumabs = wave_sum(lane < kWPT ? isum[bt * kWPT + lane] : 0.0f);
+  const float group_factor = p.gkeys != nullptr ? 8.001f : 1.0f;
+  const float bound1 = 7.0f * sumabs * smax * group_factor;
+  float bound2 = smax * sxs[bt] * (7.6f * sumabs + 3.8f * (float)d + 1.0f) * 1.01f * group_factor;
+  if constexpr (LRQ) {
+    const float xsq = wave_sum(lane < kWPT ? xsqs[bt * kWPT + lane] : 0.0f);
+    bound2 = sqrtf(xsq * (1.0f + (float)p.xn_d * 0x1p-22f)) * 1.0001f * p.umax[0] * 1.0001f;
+  }
+  FastRegion* fr = p.fr + min(b, B - 1);
+  const uint32_t anchor1 = fine_bin(__float_as_uint(bound1)), anchor2 = fine_bin(__float_as_uint(bound2));
+  if (here && blockIdx.x == 0 && lane == 0) {
+    fr->anchor1 = anchor1;
+    fr->anchor2 = anchor2;
+  }
+
+  constexpr int kTok4 = TT / 4;
+  v4i acc[kTok4];
+#pragma unroll
+  for (int f = 0; f < kTok4; ++f) acc[f] = v4i{0, 0, 0, 0};
+  for (int s0 = 0; s0 < nsl; s0 += 4) {
+    if (s0 > 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wv[i] = load_streaming(&wrow[min((s0 + i) * 16 + (lane >> 2), cpr - 1)]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (s0 + i < nsl) {  // uniform
+        const int c = (s0 + i) * 16 + (lane >> 2), cc = min(c, cpr - 1);
+        const uint32_t keep = c < cpr ? 0xFFFFFFFFu : 0u;  // past the row's end: zeros
+        const uint32_t wd[4] = {wv[i].x & keep, wv[i].y & keep, wv[i].z & keep, wv[i].w & keep};
+#pragma unroll
+        for (int f = 0; f < kTok4; ++f) {
+          const uint4* xr = xs + (f * 4 + (lane & 3)) * xstride + 2 * cc;
+          const uint4 ta = xr[0], tb = xr[1];
+          const int xd[8] = {(int)ta.x, (int)ta.y, (int)ta.z, (int)ta.w, (int)tb.x, (int)tb.y, (int)tb.z, (int)tb.w};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[f] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)(wd[q] & 0xF0F0F0F0u), xd[2 * q], acc[f], 0, 0, 0);
+            acc[f] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)((wd[q] << 4) & 0xF0F0F0F0u), xd[2 * q + 1], acc[f], 0, 0, 0);
+          }
+        }
+      }
+  }
+  HIRE_TS(33);
+#pragma unroll
+  for (int f = 0; f < kTok4; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // row r, token l % 4: the four blocks of sixteen lanes
+      int v = acc[f][r];
+      v += dpp_move<0x124, 0xF>(0, v);
+      v += dpp_move<0x128, 0xF>(0, v);
+      if ((lane & 12) == 0) part[lane >> 4][f * 4 + (lane & 3)][w * 4 + r] = v;
+    }
+  lds_barrier();
+
+  if (b >= TT) {
+    if (p.gkeys != nullptr) lds_barrier();
+    return;
+  }
+  auto count_key = [&](float key) {
+    const uint32_t bits = __float_as_uint(key);
+    const uint32_t slot = anchor1 - fine_bin(bits);  // keys lie at or below the anchor; zeros are never counted
+    if (b < clean && bits != 0u && slot < (uint32_t)kWin) atomicAdd(&fr->hist1[slot], 1u);
+  };
+  const int j = (int)blockIdx.x * kTokRows + lane;
+  int sum = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum += part[q][b][lane];
+  sum >>= 4;  // every partial is a multiple of 16
+  float key = (float)sum * row_scale;
+  key = key > 0.0f ? key : 0.0f;  // ReLU, and -0 -> +0
+  if (here && j < N) {
+    if (p.acc_out) p.acc_out[(size_t)b * N + j] = sum;
+    if (p.gkeys == nullptr) {
+      p.keys[(size_t)b * p.stride + j] = key;
+      count_key(key);
+    }
+  }
+  if (p.gkeys != nullptr) {
+    unit_keys[b][lane] = key;
+    lds_barrier();
+    const int J = (int)blockIdx.x * (kTokRows / 8) + lane;
+    if (here && lane < kTokRows / 8 && J * 8 < N) {
+      float s = 0.0f;
+#pragma unroll
+      for (int l = 0; l < 8; ++l) s += fabsf(unit_keys[b][lane * 8 + l]);
+      p.gkeys[(size_t)b * p.gstride + J] = s;
+      count_key(s);
+    }
+  }
+  HIRE_TS(34);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Kernel 2: the shortlists and their exact pre-activations, as k_fast_gather, for all tokens.
+struct FastGatherTokens {
+  const void* keys;           // [B, stride] fp32 (fp64), rows at multiples of 16 bytes
+  long long stride;
+  int B, N, kprime, d;        // kprime: selected entries (units or groups) per token
+  FastRegion* fr;
+  const uint16_t* W1;         // [N, d] bf16
+  const uint4* x;             // [B, d] bf16
+  float* h32;                 // [B, entries] activations, 0 where no token shortlists the entry
+  double* h64;                // the same in fp64, -1 there
+  int entries;                // N >> gs up to a whole workgroup
+  int gs;                     // 3: groups of eight units, as in FastGatherParams
+  float* u32;                 // groups: [B, entries << gs] the units' activations
+  uint32_t* bitmap;           // union of the shortlists, (N >> gs) bits
+  // dense units: own_blocks workgroups take `share` each beside their own units, further workgroups kDenseRows each
+  int own_blocks, share;
+  const uint16_t* Wd;
+  int m1;
+  double* hd;                 // [B, m1]
+};
+constexpr int kDenseRows = 32, kMostRows = kOwnUnits + 32;
+
+// out(r, t, relu(<row r, x_t>)) for r < cnt <= kMostRows rows and all tokens, by the workgroup.  v_mfma_f64_4x4x4: four
+// rows and four tokens at a time, in lane l row l % 4 of A, token l % 4 of B and column chunk l / 4 of both, element by
+// element of the sixteen-byte chunks (the order of the columns does not matter to a dot product).  A wave has SL slices
+// of sixteen chunks of the columns, whose token values stay in its registers as fp64, and runs over its share of the
+// rows, four at a time, eight loads in flight; nothing goes through LDS but the waves' sums.  SL as large as the
+// registers allow: a wave then reads up to a KB of a row (9.9 us for the rows of four tokens at the ~1B shape with 256
+// bytes, 8.6 with a KB, 7.8 with whole rows).  red: [parts of the columns][groups of four rows][TT / 4][16] sums, added
+// in a fixed order.
+template <int TT, typename RowOf, typename Out>
+__device__ __forceinline__ void rows_by_tokens(int cnt, RowOf&& row_of, const uint4* __restrict__ x, int B, int nvec,
+                                               double* red, Out&& out) {
+  constexpr int kTok4 = TT / 4, SL = 4 / kTok4, kDepth = 8 / SL, kMaxGroups = kMostRows / 4;
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int nsl = (nvec + 15) / 16, ng = (cnt + 3) / 4;
+  int ps = 1;  // waves side by side over the columns: sixteen parts are enough (TT d <= 32768)
+  while (ps * SL < nsl) ps <<= 1;
+  const int s0 = (w & (ps - 1)) * SL, rp = w / ps, step = kTW / ps;
+  uint4 ring[kDepth][SL];
+  auto load = [&](int q, uint4 (&v)[SL]) {
+    const uint4* row = row_of(min(q * 4 + (lane & 3), cnt - 1));
+#pragma unroll
+    for (int j = 0; j < SL; ++j) v[j] = load_streaming(row + min((s0 + j) * 16 + (lane >> 2), nvec - 1));
+  };
+  uint4 xr[SL][kTok4];  // asked for ahead of the rows: loads return in order
+#pragma unroll
+  for (int j = 0; j < SL; ++j)
+#pragma unroll
+    for (int f = 0; f < kTok4; ++f)
+      xr[j][f] = x[(size_t)min(f * 4 + (lane & 3), B - 1) * nvec + min((s0 + j) * 16 + (lane >> 2), nvec - 1)];
+#pragma unroll
+  for (int i = 0; i < kDepth; ++i)
+    if (s0 < nsl && rp + i * step < ng) load(rp + i * step, ring[i]);  // uniform
+  if (s0 < nsl) {  // uniform over the wave
+    double xd[SL][kTok4][8];
+    uint32_t keep[SL];  // past the row's end: zeros
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const int c = (s0 + j) * 16 + (lane >> 2);
+      keep[j] = c < nvec ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+      for (int f = 0; f < kTok4; ++f) {
+        const uint4 u = xr[j][f];
+        const uint32_t ud[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          xd[j][f][2 * q] = (double)bf16_lo(ud[q]);
+          xd[j][f][2 * q + 1] = (double)bf16_hi(ud[q]);
+        }
+      }
+    }
+    for (int q0 = rp; q0 < ng; q0 += kDepth * step) {
+#pragma unroll
+      for (int i = 0; i < kDepth; ++i) {
+        const int q = q0 + i * step;
+        if (q < ng) {  // uniform
+          double acc[kTok4];
+#pragma unroll
+          for (int f = 0; f < kTok4; ++f) acc[f] = 0.0;
+#pragma unroll
+          for (int j = 0; j < SL; ++j) {
+            const uint4 u = ring[i][j];
+            const uint32_t wd[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const double wf = (double)((e & 1) != 0 ? bf16_hi(wd[e / 2]) : bf16_lo(wd[e / 2]));
+#pragma unroll
+              for (int f = 0; f < kTok4; ++f) acc[f] = __builtin_amdgcn_mfma_f64_4x4x4f64(wf, xd[j][f][e], acc[f], 0, 0, 0);
+            }
+          }
+          if (q + kDepth * step < ng) load(q + kDepth * step, ring[i]);
+#pragma unroll
+          for (int f = 0; f < kTok4; ++f) {  // row l / 16, token l % 4: the four blocks of columns
+            double v = acc[f] + dpp_move<0x124, 0xF>(0.0, acc[f]);
+            v += dpp_move<0x128, 0xF>(0.0, v);
+            if ((lane & 12) == 0)
+              red[(((size_t)(w & (ps - 1)) * kMaxGroups + q) * kTok4 + f) * 16 + (lane >> 4) * 4 + (lane & 3)] = v;
+          }
+        }
+      }
+    }
+  }
+  HIRE_TS(16);
+  lds_barrier();
+  HIRE_TS(17);
+  for (int o = tid; o < ng * kTok4 * 16; o += kTT) {
+    const int r = o / (kTok4 * 16) * 4 + (o >> 2 & 3), t = o / 16 % kTok4 * 4 + (o & 3);
+    double v = 0.0;
+    for (int j = 0; j * SL < nsl; ++j) v += red[(size_t)j * kMaxGroups * kTok4 * 16 + o];
+    if (r < cnt && t < B) out(r, t, v > 0.0 ? v : 0.0);  // ReLU, and -0 -> +0
+  }
+}
+
+// Where the selection of the k largest of n keys in memory cuts them, without a histogram.
+template <typename K>
+__device__ __forceinline__ Cut<K> streaming_cut(const K* keys, int n, int k, SelSharedT<kTT>& sh, int* wave_gt,
+                                                int* wave_eq) {
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const K t = KeyIO<K>::from_order_key(wg_kth_largest<K>(
+      [&](auto&& f) {
+#pragma unroll 1
+        for (int i = tid; i < n; i += kTT) f(KeyIO<K>::to_order_key(keys[i]));
+      },
+      n, k, sh));
+  const int M = ((n + kTW - 1) / kTW + kWave - 1) / kWave * kWave, lo = w * M, hi = min(n, lo + M);
+  int gt = 0, eq = 0;
+#pragma unroll 1
+  for (int i = lo + lane; i < hi; i += kWave) {
+    gt += keys[i] > t ? 1 : 0;
+    eq += keys[i] == t ? 1 : 0;
+  }
+  gt = wave_sum(gt);
+  eq = wave_sum(eq);
+  __syncthreads();
+  if (lane == 0) {
+    wave_gt[w] = gt;
+    wave_eq[w] = eq;
+  }
+  __syncthreads();
+  int all_gt = 0, before = 0;
+  for (int u = 0; u < kTW; ++u) {
+    all_gt += wave_gt[u];
+    before += u < w ? wave_eq[u] : 0;
+  }
+  const int need = k - all_gt;  // >= 1: t itself is selected
+  if (before < need && need <= before + eq) {  // one wave
+    int run = before;
+#pragma unroll 1
+    for (int i0 = lo; i0 < hi; i0 += kWave) {
+      const uint64_t m = __ballot(i0 + lane < hi && keys[min(i0 + lane, n - 1)] == t);
+      if (((m >> lane) & 1ull) != 0ull && run + mask_prefix(m) + 1 == need) sh.bc_bin = i0 + lane;
+      run += __popcll(m);
+    }
+  }
+  __syncthreads();
+  Cut<K> c;
+  c.key = t;
+  c.idx = sh.bc_bin;
+  return c;
+}
+
+// K: the keys' bit patterns.  TT: tokens rounded up to four or eight.
+// Measured at the ~1B shape and four tokens: 18.7 us (3.4 until the rows are known, 8.5 for the 9600 rows of the union,
+// 0.7 for the outputs; workgroups that have to settle a key of a threshold bin are 3 us behind), against 5.8 + 13 + the
+// larger part of 9.9 us for the three kernels of the longer sequence.
+template <typename K, int TT>
+__global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) {
+  constexpr int kWPT = kTW / TT, kChunks = kWin / 256, kMine = kChunks / kWPT;  // 256 counters per wave and load
+  __shared__ SelSharedT<kTT> sh;
+  __shared__ int wave_gt[kTW], wave_eq[kTW];
+  __shared__ int chunk_sum[TT][kChunks], slot[TT];
+  __shared__ K open_key[TT * kOwnUnits];  // units of the workgroup that only have keys of threshold bins: key,
+  __shared__ int open_unit[TT * kOwnUnits];  // unit and token,
+  constexpr int kOpenRound = 16;
+  __shared__ int open_ahead[kOpenRound][kTW];  // keys ahead of it, by wave
+  __shared__ int unit_of[kOwnUnits];
+  __shared__ double unit_h[TT][kOwnUnits];
+  extern __shared__ double red[];  // partial sums of rows_by_tokens
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int g = (int)blockIdx.x, nvec = p.d / 8, gs = p.gs, B = p.B;
+  HIRE_TS(10);
+  const bool sparse = g < p.own_blocks;  // uniform
+  // this workgroup's dense units
+  const int r0 = sparse ? g * p.share : p.own_blocks * p.share + (g - p.own_blocks) * kDenseRows;
+  const int dense = max(0, min(sparse ? p.share : kDenseRows, p.m1 - r0));
+  const int u0 = g * kOwnUnits;  // first unit of the workgroup
+  uint64_t rows = 0ull;          // units of the workgroup that any token shortlists
+  if (sparse) {
+    const int n = p.N >> gs;
+    const int clean = clean_regions(p.fr);
+    uint4 wr[kMine];
+    const int tw = w / kWPT, wt = w % kWPT;  // the token whose window this wave helps to walk, its part of it
+    {
+      const uint4* hist = reinterpret_cast<const uint4*>(p.fr[min(tw, B - 1)].hist1);
+#pragma unroll
+      for (int u = 0; u < kMine; ++u) wr[u] = hist[(wt * kMine + u) * kWave + lane];
+    }
+    const int entry = (u0 + lane) >> gs;  // lane's unit, or its group
+    const bool valid = u0 + lane < p.N;
+    K own[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) own[t] = reinterpret_cast<const K*>(p.keys)[min(t, B - 1) * p.stride + min(entry, n - 1)];
+    const uint32_t a1 = p.fr[min(lane, B - 1)].anchor1;  // lane t: token t's
+    if (tid < TT) slot[tid] = -1;
+    // walk: sums of 256 counters, the chunk that holds the k'-th key, its lane, its counter
+    int s[kMine];
+#pragma unroll
+    for (int u = 0; u < kMine; u += 2) {  // (sums of counters fit sixteen bits: 16384 keys at most)
+      s[u] = (int)(wr[u].x + wr[u].y + wr[u].z + wr[u].w);
+      s[u + 1] = (int)(wr[u + 1].x + wr[u + 1].y + wr[u + 1].z + wr[u + 1].w);
+      const uint32_t tot = wave_sum((uint32_t)s[u] | (uint32_t)s[u + 1] << 16);
+      if (lane == 0) {
+        chunk_sum[tw][wt * kMine + u] = (int)(tot & 0xFFFFu);
+        chunk_sum[tw][wt * kMine + u + 1] = (int)(tot >> 16);
+      }
+    }
+    lds_barrier();
+    HIRE_TS(11);
+    {
+      const int v = lane < kChunks ? chunk_sum[tw][lane] : 0, incl = wave_scan_incl(v);
+      const uint64_t at = __ballot(lane < kChunks && incl - v < p.kprime && p.kprime <= incl);
+      if (at != 0ull && tw < clean) {  // uniform; tokens without a clean histogram have no slot
+        const int q = __builtin_ctzll(at), run0 = __builtin_amdgcn_readlane(incl - v, q);
+#pragma unroll
+        for (int u = 0; u < kMine; ++u)
+          if (q == wt * kMine + u) {  // uniform: one wave
+            const int run = run0 + wave_scan_incl(s[u]) - s[u];
+            if (run < p.kprime && p.kprime <= run + s[u]) {  // one lane
+              const int c[4] = {(int)wr[u].x, (int)wr[u].y, (int)wr[u].z, (int)wr[u].w};
+              int rr = run;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                if (rr < p.kprime && p.kprime <= rr + c[e]) slot[tw] = (q * kWave + lane) * 4 + e;
+                rr += c[e];
+              }
+            }
+          }
+      }
+    }
+    lds_barrier();
+    HIRE_TS(15);
+    uint32_t unresolved = 0u;  // tokens
+    uint64_t in_bin[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      in_bin[t] = 0ull;
+      if (t < B) {  // uniform
+        const int sl = __builtin_amdgcn_readfirstlane(slot[t]);
+        const uint32_t anchor = (uint32_t)__builtin_amdgcn_readlane((int)a1, t), bin = anchor - (uint32_t)sl;
+        if (sl >= 0 && bin >= 1u && bin <= anchor) {  // uniform
+          const K lo = bin_floor<K>(bin), up = bin_floor<K>(bin + 1u);
+          rows |= __ballot(valid && own[t] >= up);
+          in_bin[t] = __ballot(valid && own[t] >= lo && own[t] < up);
+        } else {
+          unresolved |= 1u << t;
+        }
+      }
+    }
+    for (uint32_t m = unresolved; m != 0u; m &= m - 1u) {  // fresh workspace, threshold among the zeros or below the
+      const int t = __builtin_ctz(m);                      // window
+      if (g == 0 && tid == 0 && t < clean) atomicAdd(&p.fr->fallbacks[0], 1u);
+      const K* row = reinterpret_cast<const K*>(p.keys) + (size_t)t * p.stride;
+      __syncthreads();
+      const Cut<K> cut = streaming_cut<K>(row, n, p.kprime, sh, wave_gt, wave_eq);
+      rows |= __ballot(valid && cut_takes(cut, row[min(entry, n - 1)], entry));
+    }
+    // every wave notes the undecided units (the same values) and reads its own notes; of a group its first unit
+    int opens = 0;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      const uint64_t m = in_bin[t] & ~rows & (gs != 0 ? 0x0101010101010101ull : ~0ull);
+      if (((m >> lane) & 1ull) != 0ull) {
+        open_key[opens + mask_prefix(m)] = own[t];
+        open_unit[opens + mask_prefix(m)] = lane * TT + t;
+      }
+      opens += __popcll(m);
+    }
+    // A unit that only has keys of threshold bins, of which some are selected: its key is compared with all others of
+    // the token.  One workgroup in six has such a unit, and then one or two; the code is in no cache when they come
+    // here, so the loop is as short as it can be (unrolled over the tokens it took 6 us).
+#pragma unroll 1
+    for (int j0 = 0; j0 < opens; j0 += kOpenRound) {  // uniform over the workgroup
+      constexpr int PER = KeyIO<K>::PER, kLoads = 16 / PER;  // the row of 16384 keys at a time
+      const int vecs = (n + PER - 1) / PER, j1 = min(opens, j0 + kOpenRound);
+      uint4 raw[kLoads];
+      auto load = [&](int j) {
+        const int t = __builtin_amdgcn_readfirstlane(open_unit[j]) % TT;
+        const uint4* row = reinterpret_cast<const uint4*>(reinterpret_cast<const K*>(p.keys) + (size_t)t * p.stride);
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) raw[u] = row[min(u * kTT + tid, vecs - 1)];
+      };
+      load(j0);
+#pragma unroll 1
+      for (int j = j0; j < j1; ++j) {
+        const K mine = open_key[j];
+        const int at = (u0 + __builtin_amdgcn_readfirstlane(open_unit[j]) / TT) >> gs;
+        K k[kLoads][PER];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) KeyIO<K>::unpack(raw[u], k[u]);
+        load(min(j + 1, j1 - 1));
+        int ahead = 0;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+          const int i = (u * kTT + tid) * PER;
+#pragma unroll
+          for (int q = 0; q < PER; ++q) ahead += i + q < n && k[u][q] >= mine + (i + q < at ? 0u : 1u) ? 1 : 0;
+        }
+        ahead = wave_sum(ahead);
+        if (lane == 0) open_ahead[j - j0][w] = ahead;
+      }
+      lds_barrier();
+#pragma unroll 1
+      for (int j = j0; j < j1; ++j)
+        if (wave_sum(lane < kTW ? open_ahead[j - j0][lane] : 0) < p.kprime)
+          rows |= (gs != 0 ? 0xFFull : 1ull) << (__builtin_amdgcn_readfirstlane(open_unit[j]) / TT);
+      lds_barrier();
+    }
+  }
+  HIRE_TS(12);
+  const int cnt = __popcll(rows);
+  // every wave notes all rows (the same values) and reads its own notes
+  if (((rows >> lane) & 1ull) != 0ull) unit_of[mask_prefix(rows)] = lane;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  HIRE_TS(13);
+  auto count_h = [&](int t, double v) {  // the scorer kernel of this step has cleared the windows
+    if (v > 0.0) {
+      const uint32_t sl = p.fr[t].anchor2 - fine_bin((uint64_t)__double_as_longlong(v));  // v is at or below the anchor
+      if (sl < (uint32_t)kWin) atomicAdd(&p.fr[t].hist2[sl], 1u);
+    }
+  };
+  if (sparse && gs == 0 && w < B && ((rows >> lane) & 1ull) == 0ull) {
+    p.h32[(size_t)w * p.entries + u0 + lane] = 0.0f;
+    p.h64[(size_t)w * p.entries + u0 + lane] = -1.0;
+  }
+  // (one base and an offset: between two pointers the compiler selects where they are stored, and every row's loads
+  // wait for the load of an address)
+  const char* base = reinterpret_cast<const char*>(p.W1);
+  const long long row_bytes = 2ll * p.d, own_at = u0 * row_bytes,
+                  dense_at = reinterpret_cast<const char*>(p.Wd) - base + (r0 - cnt) * row_bytes;
+  rows_by_tokens<TT>(
+      cnt + dense,
+      [&](int r) {
+        const int at = r < cnt ? unit_of[min(r, kOwnUnits - 1)] : r;
+        return reinterpret_cast<const uint4*>(base + ((r < cnt ? own_at : dense_at) + at * row_bytes));
+      },
+      p.x, B, nvec, red,
+      [&](int r, int t, double v) {
+        if (r >= cnt) {
+          p.hd[(size_t)t * p.m1 + r0 + r - cnt] = v;
+          return;
+        }
+        const int pos = unit_of[r];
+        if (gs != 0) {
+          unit_h[t][pos] = v;
+        } else {
+          p.h32[(size_t)t * p.entries + u0 + pos] = (float)v;
+          p.h64[(size_t)t * p.entries + u0 + pos] = v;
+          count_h(t, v);
+        }
+      });
+  if (!sparse) return;
+  if (gs != 0) {  // exact group activations, units added in order; wave t: token t
+    __syncthreads();
+    if (w < B) {
+      p.u32[(size_t)w * (p.entries << gs) + u0 + lane] = ((rows >> lane) & 1ull) != 0ull ? (float)unit_h[w][lane] : 0.0f;
+      if (lane < kOwnUnits >> gs) {
+        const bool in = ((rows >> (lane << gs)) & 1ull) != 0ull;
+        double e = 0.0;
+        if (in)
+          for (int l = 0; l < (1 << gs); ++l) e += fabs(unit_h[w][(lane << gs) + l]);
+        const size_t at = (size_t)w * p.entries + (u0 >> gs) + lane;
+        p.h32[at] = in ? (float)e : 0.0f;
+        p.h64[at] = in ? e : -1.0;
+        if (in) count_h(w, e);
+      }
+    }
+  }
+  if (tid == 0) {  // the workgroup's part of the union
+    if (gs == 0) {
+      p.bitmap[2 * g] = (uint32_t)rows;
+      p.bitmap[2 * g + 1] = (uint32_t)(rows >> 32);
+    } else {
+      uint32_t bits = 0u;
+      for (int J = 0; J < kOwnUnits >> gs; ++J) bits |= (uint32_t)((rows >> (J << gs)) & 1ull) << J;
+      uint8_t* bytes = reinterpret_cast<uint8_t*>(p.bitmap);
+      bytes[g] = (uint8_t)bits;
+      if (g == p.own_blocks - 1)
+        for (int i = g + 1; (i & 3) != 0; ++i) bytes[i] = 0u;  // the last word is read whole
+    }
+  }
+  HIRE_TS(14);
+}
+
+// ---------------------------------------------------------------------------------------------------
+static int token_slots(int B) { return B <= 4 ? 4 : 8; }
+
+// Steps on units: up to four tokens.  With eight the fp64 products and two windows of counters per wave outweigh the
+// selections saved, at the ~1B shape 50.5 us against 47.9 for five tokens and 63 against 51.5 for eight; groups of
+// eight, whose longer sequence forms its activations in fp64 too, gain up to eight (275 us for four layers against 322
+// with dense units, 164 against 166 for a small layer without).  The scorer keeps a token in four vectors per thread.
+bool ffn_fast_tokens_supported(int B, int d, bool groups) {
+  return B >= 2 && B <= (groups ? kFastTokens : 4) && token_slots(B) * d <= 32768;
+}
+
+hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lrq, hipStream_t s) {
+  FastScoreTokens p{};
+  p.q4 = reinterpret_cast<const uint4*>(lrq ? a.lr_b : a.q4);
+  p.scale = lrq ? a.lr_b_scale : a.q4_scale;
+  p.x = x;
+  p.B = a.B; p.N = a.N; p.d = lrq ? a.r : a.d;
+  p.keys = a.keys; p.stride = a.key_stride;
+  p.acc_out = a.scorer_acc;
+  p.fr = reinterpret_cast<FastRegion*>(a.fast_region);
+  p.gkeys = a.gs ? a.gkeys : nullptr;
+  p.gstride = a.gkey_stride;
+  p.xn = reinterpret_cast<const uint4*>(a.x); p.xn_d = a.d; p.umax = a.norm_bounds;
+  const size_t lds = (size_t)token_slots(a.B) * (p.d / 16 + 1) * sizeof(uint4);
+  const dim3 grid((a.N + kTokRows - 1) / kTokRows);
+  static std::atomic<size_t> raised_to[7] = {};
+  auto go = [&](auto kernel, int i) -> hipError_t {
+    if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to[i]); e != hipSuccess)
+      return e;
+    return launch(kernel, grid, dim3(kTT), lds, s, p);
+  };
+  const bool four = token_slots(a.B) == 4;
+  if (lrq) return four ? go(k_fast_score_tokens<true, 4, 1>, 0) : hipErrorInvalidValue;  // r <= 1024
+  const int values = token_slots(a.B) * p.d;  // a workgroup loads 8192 of them at a time
+  if (values <= 8192) return four ? go(k_fast_score_tokens<false, 4, 1>, 1) : go(k_fast_score_tokens<false, 8, 1>, 2);
+  if (values <= 16384) return four ? go(k_fast_score_tokens<false, 4, 2>, 3) : go(k_fast_score_tokens<false, 8, 2>, 4);
+  return four ? go(k_fast_score_tokens<false, 4, 4>, 5) : go(k_fast_score_tokens<false, 8, 4>, 6);
+}
+
+hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s) {
+  FastGatherTokens p{};
+  p.keys = a.gs ? a.gkeys : a.keys;
+  p.stride = a.gs ? a.gkey_stride : a.key_stride;
+  p.B = a.B; p.N = a.N; p.kprime = a.kprime >> a.gs; p.d = a.d;
+  p.fr = reinterpret_cast<FastRegion*>(a.fast_region);
+  p.W1 = a.w1u; p.x = reinterpret_cast<const uint4*>(a.x);
+  p.h32 = a.h32; p.h64 = a.h; p.entries = ffn_fast_entries(a.N, a.gs); p.gs = a.gs; p.u32 = a.u32;
+  p.bitmap = a.bitmap;
+  p.own_blocks = (a.N + kOwnUnits - 1) / kOwnUnits;
+  p.Wd = a.dense_w1u; p.m1 = a.m1; p.hd = a.h_dense;
+  // dense units go to the compute units left over first (a workgroup more than there are units waits for a whole
+  // workgroup's time), then to the workgroups of the sparse ones, then to workgroups of their own after all
+  const int spare = max(0, 256 - p.own_blocks) * kDenseRows;
+  p.share = min(kMostRows - kOwnUnits, (max(0, a.m1 - spare) + p.own_blocks - 1) / p.own_blocks);
+  const int rest = max(0, a.m1 - p.own_blocks * p.share);
+  const size_t lds = (size_t)kTW * (kMostRows / 4) * (token_slots(a.B) / 4) * 16 * sizeof(double);
+  const dim3 grid(p.own_blocks + (rest + kDenseRows - 1) / kDenseRows);
+  static std::atomic<size_t> raised_to[2] = {};
+  auto go = [&](auto kernel, int i) -> hipError_t {
+    if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to[i]); e != hipSuccess)
+      return e;
+    return launch(kernel, grid, dim3(kTT), lds, s, p);
+  };
+  switch (token_slots(a.B)) {
+    case 4: return go(k_fast_gather_tokens<uint32_t, 4>, 0);
+    default: return go(k_fast_gather_tokens<uint32_t, 8>, 1);
+  }
+}
+
+}  // namespace hire
+
+#ifdef HIRE_TIMESTAMPS
+extern "C" int hire_debug_timestamps_fast_tokens(unsigned long long* host64) {
+  return (int)hipMemcpyFromSymbol(host64, HIP_SYMBOL(hire_ts), sizeof(hire_ts));
+}
+#endif

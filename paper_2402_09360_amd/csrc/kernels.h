@@ -308,8 +308,10 @@ hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* l
 
 // ---- ffn_fast.hip ----------------------------------------------------------
 // Batch-1 FFN step in three kernels; see the file header.  All pointers device.
+constexpr int kFastTokens = 8;               // most tokens of a step that takes this route
+constexpr size_t kFastRegionBytes = 256 + 2 * 8192 * 4;  // state and histograms of one token
 struct FfnFastArgs {
-  int N, d, k, kprime;
+  int B, N, d, k, kprime;
   const void* q4;
   const float* q4_scale;
   const uint16_t* w1u;
@@ -323,21 +325,29 @@ struct FfnFastArgs {
   int32_t* scorer_acc; // optional
   // workspace
   void* fast_region;   // ffn_fast_region_bytes() bytes at the head of the workspace (cookie, maxima, histograms)
-  float* keys;         // [N] padded to a multiple of 4
-  double* h;           // [ffn_fast_entries(N, gs)]: activations of the units (gs = 3: of the groups)
+  float* keys;         // [B, key_stride], key_stride a multiple of 4
+  long long key_stride;
+  double* h;           // [B, ffn_fast_entries(N, gs)]: activations of the units (gs = 3: of the groups)
   float* h32;          // the same rounded to fp32
   // group-sparse step with groups of eight units (gs = 3; 0 otherwise): N, k, kprime still count units; cand_out,
   // n_cand and topk_idx are in groups, topk_val per unit
   int gs;
-  float* gkeys;        // gs = 3: [N/8] padded to a multiple of 4
-  float* u32;          // gs = 3: [ffn_fast_entries(N, 0)] activations of the units
+  float* gkeys;        // gs = 3: [B, gkey_stride], gkey_stride a multiple of 4
+  long long gkey_stride;
+  float* u32;          // gs = 3: [B, ffn_fast_entries(N, gs) << gs] activations of the units
   // CommonPath (eq. (7)): m1 dense units next to the sparse ones, folded into the gather and second-layer
   // launches as extra workgroups (m1 = 0: none).
   const uint16_t* dense_w1u;  // [m1, d]
   const uint16_t* dense_w2u;  // [m1, d]
   int m1;
-  double* h_dense;            // [m1] workspace
-  // Low-rank scorer (lowrank; otherwise the int4 one): keys are fp64 (keys64, [N] padded to
+  double* h_dense;            // [B, m1] workspace
+  // several tokens: the union of their shortlists, a place for its list where the caller wants its length only, and
+  // (lrq) the quantised tokens
+  uint32_t* bitmap;
+  int32_t* cand_scratch;
+  int8_t* xq;
+  float* sumabs;
+  // Low-rank scorer (lowrank, one token; otherwise the int4 one): keys are fp64 (keys64, [N] padded to
   // a multiple of 2), t_partial holds lr_project_slices(d) * r doubles, norm_bounds the two row-norm bounds of
   // hire_lr_prepare.  Plain units only (gs = 0, m1 = 0).
   bool lowrank;
@@ -353,7 +363,7 @@ struct FfnFastArgs {
   const float* lr_a_scale;
   const float* lr_b_scale;
   float* keys_t;
-  hipEvent_t* stage_events;  // optional: 5 events recorded around the kernels (the last two behind the last one)
+  hipEvent_t* stage_events;  // optional: 4 events recorded around the kernels
   unsigned long long* scorer_clocks;  // optional: start/end wall clock (100 MHz ticks) of every scorer workgroup
 };
 size_t ffn_fast_region_bytes();
@@ -362,10 +372,14 @@ size_t ffn_fast_fallbacks_offset();  // two uint32 counters inside the region
 // Where the region keeps its cookie (and the value that says "key histogram all zero") and its two histograms.
 void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_t* hist1_off, size_t* hist2_off,
                            size_t* hist_words);
-bool ffn_fast_supported(int B, int N, int d, int k, int kprime);
+bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool groups = false);
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime);  // the same route for groups of eight units
 int ffn_fast_entries(int N, int gs);
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s);
+// ---- ffn_fast_tokens.hip: the first two kernels for two to kFastTokens tokens
+bool ffn_fast_tokens_supported(int B, int d, bool groups);
+hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lrq, hipStream_t s);
+hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s);
 
 // ---- ffn_shard.hip -----------------------------------------------------------
 // HiRE-FFN step with Algorithm 2's sharded approximate top-k, one workgroup per shard; see the file header.

@@ -32,6 +32,14 @@ FAST = [
                    (22, "bin settled"), (26, "selected rows listed"), (27, "second-layer rows read and accumulated"),
                    (28, "reduced over the waves, y written")]),
 ]
+TOKENS = [
+    ("k_fast_score_tokens", [(30, "kernel start"), (31, "tokens loaded, largest |x| known"), (32, "tokens quantised"),
+                             (33, "integer dot products done"), (34, "keys stored and counted into the windows")]),
+    ("k_fast_gather_tokens", [(10, "kernel start"), (11, "windows read, sums of 256 counters"),
+                              (15, "windows walked: threshold bins known"), (12, "workgroup's units settled"),
+                              (13, "rows noted"), (16, "rows read and multiplied"), (17, "... by all waves"),
+                              (14, "activations stored and counted")]),
+]
 BATCH = [
     ("k_keys_select (top-k' of the keys)",
      [(10, "kernel start"), (11, "keys loaded, window cleared"), (12, "window built and walked: threshold bin known"),
@@ -126,6 +134,9 @@ def main():
     print(f"# phase stamps, FFN step d_model={d} d_ff={N} k={k} k'={kp} batch={B}, after {args.steps} steps on one workspace")
     if B == 1 and not args.general:
         show(FAST, *table("hire_debug_timestamps_fast"))
+    elif B <= 4 and not args.general:
+        show(TOKENS, *table("hire_debug_timestamps_fast_tokens"))
+        show(FAST[2:], *table("hire_debug_timestamps_fast"))
     else:
         show(BATCH, *table("hire_debug_timestamps_batch_select"))
         show(GATHER, *table("hire_debug_timestamps_gather"))

@@ -209,6 +209,41 @@ def test_batch1_gather_and_second_layer_edges(hire, oracle, d, N, k, kp, lr):
     T.check_ffn(layer, scorer, L, I.tokens(98, 1, d), k, kp)
 
 
+@pytest.mark.parametrize("d,N,B,k,kp,m1", [
+    (64, 65, 2, 5, 20, 0),             # a workgroup with one unit
+    (8192, 300, 4, 40, 100, 0),        # longest tokens
+    (2080, 16384, 3, 900, 3000, 0),    # most units; columns not in whole slices
+    (96, 4097, 4, 4097, 4097, 0),      # everything selected
+    (4096, 640, 8, 80, 240, 33),       # groups of eight from here on: longest eight tokens, dense units in two workgroups
+    (800, 16000, 5, 400, 1600, 16001), # more dense units than the workgroups of the sparse ones take along
+    (160, 1040, 7, 8, 8, 0),           # one group of each token
+])
+def test_few_tokens_edges(hire, oracle, d, N, B, k, kp, m1):
+    log(f"few tokens d={d} N={N} B={B} k={k} kp={kp} m1={m1}")
+    L = I.ffn_layer(99 + B, d, N)
+    L["w1u"][N // 4:N // 4 + 40] = L["w1u"][N // 4]     # equal keys and activations
+    layer, scorer = T.make_ffn_layer(L)
+    x = I.tokens(100 + B, B, d)
+    if B <= 4:
+        T.check_ffn(layer, scorer, L, x, k, kp)
+    else:
+        D = I.ffn_layer(101, d, max(m1, 1))
+        T.check_ffn_commonpath(layer, scorer, L, (D["w1u"][:m1], D["w2u"][:m1]), x, k, kp, 8)
+
+
+def test_few_tokens_share_a_workspace(hire, oracle):
+    """Steps of different numbers of tokens in turn on one workspace: each finds the histograms as its kernels need them."""
+    from oracle import hire_oracle as O
+    d, N, k, kp = 256, 1500, 60, 300
+    L = I.ffn_layer(102, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    ws = hire.alloc_workspace(max(hire.hire_ffn_workspace_bytes(layer, B, k, kp) for B in (1, 2, 3, 4, 6)))
+    for B in (3, 1, 4, 6, 2, 4, 1, 3):
+        log(f"few tokens on a shared workspace, B={B}")
+        x = I.tokens(103 + B, B, d)
+        T.compare_ffn(T.run_ffn(layer, x, k, kp, ws=ws), O.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp, want_acc=True))
+
+
 @pytest.mark.parametrize("B", [1, 4, 16])
 def test_ffn_step_1b_shape(hire, oracle, ffn_1b, B):
     """Config 2: d_m=2048, d_ff=16384, k=819, k'=3276, iid tokens, union across the batch."""
