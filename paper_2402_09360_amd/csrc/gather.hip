@@ -79,9 +79,10 @@ __global__ __launch_bounds__(256) void k_gather_dot(const uint16_t* __restrict__
 //
 // Bound: the round trips list -> rows for few tokens; for many the caches (64 tokens read 215 MB of rows that are
 // 67 MB in HBM, 11 TB/s).  Narrow slices spread few tokens over the chip; wide ones read longer runs and are faster
-// once 256 workgroups exist (64 tokens: 128-byte runs 29 us, 256-byte 22, 512-byte 19.5).  The dispatcher places
-// workgroup i on die i % 8, and die x takes the column slices x, 8 + x, ..., one for all tokens before the next, so
-// that the tokens share a slice's rows in one L2 (32-column slices: the two halves of a line on one die).  Measured at d = 2048, k = 819 of 16384 units, 4 / 16 / 64 tokens:
+// once 256 workgroups exist.  The dispatcher places workgroup i on die i % 8, and a die takes an eighth of the
+// (slice, token) pairs, slice by slice, so that the tokens share a slice's rows in one L2 and every die has as much to do
+// (whole slices per die left dies idle where slices do not come in eights: 49 tokens of d = 288, k = 1949 12.2 us, now
+// 10.2; 64 of d = 640, k = 1200 15.9, now 13.7).  Measured at d = 2048, k = 819 of 16384 units, 4 / 16 / 64 tokens:
 // 5 / 8.4 / 19.5 us, against 9.4 / 12.2 us for a kernel with partial sums and a reducing one, 23.7 us for
 // 256-column workgroups without the second batch in flight.
 constexpr int kW2Threads = 512;
@@ -99,10 +100,10 @@ __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __res
   __shared__ uint2 entries[kW2Chunk];
   __shared__ float red[kW2Waves][kCols];
   const int lane = lane_id(), w = wave_id(), tid = (int)threadIdx.x;
-  constexpr int kPair = LPR < 8 ? 8 / LPR : 1;  // slices that share a 128-byte line stay on one die
-  const int seq = (int)(blockIdx.x >> 3) / B, b = (int)(blockIdx.x >> 3) % B;
-  const int slice = ((seq / kPair) * 8 + (int)(blockIdx.x & 7)) * kPair + seq % kPair;
-  if (slice * kCols >= d) return;  // uniform: the last group of slices may be partial
+  const int n_items = (d + kCols - 1) / kCols * B;
+  const int item = (int)(blockIdx.x & 7) * ((n_items + 7) / 8) + (int)(blockIdx.x >> 3);
+  if (item >= n_items) return;  // uniform: the last dies' shares may be short
+  const int slice = item / B, b = item % B;
   const int sub = lane % LPR, first = w * (kWave / LPR) + lane / LPR;
   const int colc = min(slice * kCols + sub * 8, d - 8);  // d is a multiple of 8
   float acc[8];
@@ -247,15 +248,19 @@ hipError_t launch_gather_dot(const uint16_t* W, const uint16_t* x, int d, const 
 
 hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* list, const uint16_t* Wd, int m1,
                           const double* hd, float* y, hipStream_t s) {
+  auto items = [&](int cols) { return (d + cols - 1) / cols * B; };
   auto go = [&](auto kernel, int cols) {
-    const int slices = (d + cols - 1) / cols, step = max(8, 512 / cols);
-    return launch(kernel, dim3((slices + step - 1) / step * step * B), dim3(kW2Threads), 0, s, W2, d, B, k,
+    return launch(kernel, dim3((items(cols) + 7) / 8 * 8), dim3(kW2Threads), 0, s, W2, d, B, k,
                   static_cast<const uint2*>(list), Wd, m1, hd, y);
   };
-  // the widest slices that still give a workgroup to every compute unit
-  if (d / 256 * B >= 256) return go(k_w2_list<32, 4>, 256);
-  if (d / 128 * B >= 160) return go(k_w2_list<16, 4>, 128);
-  if (d / 64 * B >= 160) return go(k_w2_list<8, 8>, 64);
+  // The widest slices that still give a workgroup to (nearly) every compute unit and leave few of them out of the last
+  // round of 256: 320 or 384 workgroups of 256 columns lose to twice as many of 128, 256 and 512 win; of 128 columns 200
+  // to 256 and 320 are as good as or better than twice as many of 64, 126, 147 and 260 worse; 64 columns lose to 32 below
+  // half a workgroup per unit.
+  auto fill = [&](int n) { return (double)n / ((n + 255) / 256 * 256); };
+  if (items(256) >= 250 && fill(items(256)) > 0.9) return go(k_w2_list<32, 4>, 256);
+  if (items(128) >= 200 && fill(items(128)) > 0.6) return go(k_w2_list<16, 4>, 128);
+  if (items(64) >= 128) return go(k_w2_list<8, 8>, 64);
   return go(k_w2_list<4, 8>, 32);
 }
 
