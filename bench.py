@@ -324,7 +324,7 @@ def main():
     # the three-kernel route for few tokens (units, or groups of eight)
     fast = ((B <= 8 and kind in ("ffn_g8", "ffn_cp") and scorer == "int4") or
             (B <= 4 and kind in ("ffn", "ffn_small") and scorer == "int4") or
-            (B <= 4 and kind == "ffn" and scorer == "lrq") or (B == 1 and kind == "ffn" and scorer == "lowrank"))
+            (B <= 4 and kind == "ffn" and scorer in ("lowrank", "lrq")))
     stages = hire.SOFTMAX_STAGES if kind == "softmax" else (hire.FAST_FFN_STAGES if fast else hire.FFN_STAGES)
     if shards > 1:
         stages = ("shard_step", "reduce")

@@ -543,7 +543,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr && L->r <= 1024;
   const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && L->r <= 8192 &&
                         scorer_int4_fused_supported(d);
-  if ((fast_int4 || (fast_lr && B == 1) || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic &&
+  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic &&
       !(B > 1 && g_force_exact_stage)) {
     FfnFastArgs a{};
     a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;

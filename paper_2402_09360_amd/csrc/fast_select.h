@@ -39,7 +39,7 @@ __device__ __forceinline__ uint64_t bin_floor<uint64_t>(uint32_t b) {
 
 // ---------------------------------------------------------------------------------------------------
 // Register-resident non-negative keys of an NT-thread workgroup, as raw IEEE bits.  Wave w owns the index
-// range [w*M, (w+1)*M); one load brings PER consecutive values per lane (16 bytes), so element (load e, lane
+// range [w*M, (w+1)*M), M a whole number of loads; one load brings PER consecutive values per lane (16 bytes), so element (load e, lane
 // l, part q) has index w*M + e*64*PER + l*PER + q.  Lanes whose vector starts at or beyond n load zeros; the
 // array itself must be zero from n up to the next multiple of PER.
 template <typename K>
@@ -71,7 +71,9 @@ struct KeyIO<uint64_t> {
 
 // FRESH: index() is computed anew at every use instead of being kept in registers from the first use on (for
 // kernels short of registers).
-template <typename K, int LOADS, int NT, bool FRESH = false>
+// EVEN: M is as even a share as multiples of 32 allow, for kernels whose waves go on working with what they selected
+// (in whole loads a row of 400 keys sits in two waves); elsewhere fewer waves in the passes over the keys are faster.
+template <typename K, int LOADS, int NT, bool FRESH = false, bool EVEN = false>
 struct KeyRegs {
   static constexpr int kLoads = LOADS;
   static constexpr int PER = KeyIO<K>::PER;
@@ -80,11 +82,16 @@ struct KeyRegs {
   static constexpr int CAPACITY = NW * LOADS * SPAN;
   K r[LOADS][PER];
   int base, len, n;  // the wave's index range is [base, base + len)
+  static __device__ __forceinline__ int share(int count) {  // <= LOADS * SPAN
+    constexpr int kUnit = EVEN ? 32 : SPAN;
+    return ((count + NW - 1) / NW + kUnit - 1) / kUnit * kUnit;
+  }
+  __device__ __forceinline__ bool owns(int e) const { return e * SPAN + (EVEN ? lane_id() * PER : 0) < len; }
   // Starts the loads (into r, still packed); finish() unpacks in place.
   uint4 raw[LOADS];
   __device__ __forceinline__ void issue(const void* vals, int n_, const uint32_t* zeros16) {
     n = n_;
-    const int M = (((n + NW - 1) / NW) + SPAN - 1) / SPAN * SPAN;  // <= LOADS * SPAN
+    const int M = share(n);
     len = M;
     base = wave_id() * M;
     const int vecs = (n + PER - 1) / PER;
@@ -93,14 +100,14 @@ struct KeyRegs {
 #pragma unroll
     for (int e = 0; e < LOADS; ++e) {
       const int vec = (base + e * SPAN) / PER + lane_id();
-      raw[e] = *(e * SPAN < M && vec < vecs ? v4 + vec : z4);
+      raw[e] = *(owns(e) && vec < vecs ? v4 + vec : z4);
     }
   }
   // The same for an array whose valid length is not known yet: cap values are readable (cap >= 1), the loads
   // stay inside them, and mask_beyond() zeroes what lies at and beyond the length once it is known.
   __device__ __forceinline__ void issue_clamped(const void* vals, int cap) {
     n = cap;
-    const int M = (((cap + NW - 1) / NW) + SPAN - 1) / SPAN * SPAN;
+    const int M = share(cap);
     len = M;
     base = wave_id() * M;
     const int last_vec = (cap - 1) / PER;
@@ -118,14 +125,14 @@ struct KeyRegs {
     for (int e = 0; e < LOADS; ++e)
 #pragma unroll
       for (int q = 0; q < PER; ++q)
-        if (!(e * SPAN < len && index(e, q) < n_)) r[e][q] = (K)0;
+        if (!(owns(e) && index(e, q) < n_)) r[e][q] = (K)0;
   }
   __device__ __forceinline__ int index(int e, int q) const {
     int b = base + lane_id() * PER;
     if constexpr (FRESH) asm volatile("" : "+v"(b));  // opaque: not merged with the same sum computed elsewhere
     return b + e * SPAN + q;
   }
-  __device__ __forceinline__ bool valid(int e, int q) const { return e * SPAN < len && index(e, q) < n; }
+  __device__ __forceinline__ bool valid(int e, int q) const { return owns(e) && index(e, q) < n; }
 };
 
 // A window histogram, walked from the top: thread t holds slots VEC*4*t .. VEC*4*(t+1) - 1 (requested by the
@@ -233,13 +240,13 @@ __device__ __forceinline__ bool ranks_ahead(uint64_t ok, int oi, uint64_t mk, in
 // will emit.  fallback_counter (optional) counts the selections that took the narrowing: of workgroup 0 (all
 // workgroups select the same keys) or, count_every_workgroup, of every one.  TS: first of three phase stamps of
 // the profiling build.
-template <int TS, typename K, int LOADS, int NT, bool FR>
-__device__ __forceinline__ Selection<K> fast_select(const KeyRegs<K, LOADS, NT, FR>& kr, const void* vals,
+template <int TS, typename K, int LOADS, int NT, bool FR, bool EV>
+__device__ __forceinline__ Selection<K> fast_select(const KeyRegs<K, LOADS, NT, FR, EV>& kr, const void* vals,
                                                            int need_total, const WinRegs<NT>& wr, uint32_t anchor,
                                                            bool hist_ok, SelSharedT<NT>& sh, int* wave_cnt,
                                                            uint32_t* fallback_counter, int out_lo, int out_hi,
                                                            bool count_every_workgroup = false) {
-  constexpr int PER = KeyRegs<K, LOADS, NT, FR>::PER;
+  constexpr int PER = KeyRegs<K, LOADS, NT, FR, EV>::PER;
   constexpr int NW = NT / kWave;
   const int tid = (int)threadIdx.x, lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(wave_id());

@@ -248,29 +248,33 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
 // Cauchy-Schwarz bounds: key_j <= |Z2_j| |t| and <u_j, x> <= |u_j| |x| with the layer's largest row norms
 // (bounds[1], bounds[0]: upper bounds, prepared once per layer) and the norms of t and x formed here in fp32 and
 // rounded up by more than their own error.  ROW_LANES lanes share a row as in k_lr_score_b1.
-template <int ROW_LANES>
+// TT: tokens, 1 or up to 4; kSW / TT waves add a token's slices.
+template <int ROW_LANES, int TT>
 __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict__ partial, int slices,
                                                        const uint16_t* __restrict__ z2, const uint4* __restrict__ x,
-                                                       int N, int d, int r, const float* __restrict__ bounds,
-                                                       double* __restrict__ keys, FastRegion* __restrict__ fr) {
-  __shared__ uint4 ts[128];  // t as raw bf16: r <= 1024
+                                                       int B, int N, int d, int r, const float* __restrict__ bounds,
+                                                       double* __restrict__ keys, long long stride,
+                                                       FastRegion* __restrict__ fr) {
+  constexpr int kWPT = kSW / TT;
+  __shared__ uint4 ts[TT][128];  // t as raw bf16: r <= 1024
   __shared__ float red_t[kSW], red_x[kSW];
   constexpr int kRows = kWave / ROW_LANES;  // rows per wave and trip
   const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
   const int sub = lane % ROW_LANES, rw = lane / ROW_LANES;
   const int cpr = r / 8;
   HIRE_TS(30);
-  const bool hist_ok = clean_regions(fr) > 0;
+  const int clean = clean_regions(fr);
   const float umax = bounds[0], zmax = bounds[1];
-  for (int i = (int)blockIdx.x * kST + tid; i < kWin; i += (int)gridDim.x * kST) fr->hist2[i] = 0u;
+  for (int i = (int)blockIdx.x * kST + tid; i < B * kWin; i += (int)gridDim.x * kST) fr[i / kWin].hist2[i % kWin] = 0u;
+  const int mine = min(w / kWPT, B - 1), lt = w % kWPT * kWave + lane;  // the token this wave prepares
   float tsq = 0.0f, xsq = 0.0f;
-  uint16_t* t16 = reinterpret_cast<uint16_t*>(ts);
-  for (int p = tid; p < r; p += kST) {
+  uint16_t* t16 = reinterpret_cast<uint16_t*>(ts[w / kWPT]);
+  for (int p = lt; p < r; p += kWPT * kWave) {
     double tot = 0.0;
     for (int s0 = 0; s0 < slices; s0 += 8) {  // eight loads in flight; added in slice order
       double v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = partial[(size_t)min(s0 + j, slices - 1) * r + p];
+      for (int j = 0; j < 8; ++j) v[j] = partial[((size_t)mine * slices + min(s0 + j, slices - 1)) * r + p];
 #pragma unroll
       for (int j = 0; j < 8; ++j) tot += s0 + j < slices ? v[j] : 0.0;
     }
@@ -279,8 +283,8 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
     const float tf = bf16_to_f32(tb);
     tsq = fmaf(tf, tf, tsq);
   }
-  for (int i = tid; i < d / 8; i += kST) {
-    const uint4 u = x[i];
+  for (int i = lt; i < d / 8; i += kWPT * kWave) {
+    const uint4 u = x[(size_t)mine * (d / 8) + i];
     const uint32_t ud[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -297,51 +301,63 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   }
   __syncthreads();
   HIRE_TS(32);
-  tsq = wave_sum(lane < kSW ? red_t[lane] : 0.0f);
-  xsq = wave_sum(lane < kSW ? red_x[lane] : 0.0f);
-  const float tnorm = sqrtf(tsq * (1.0f + (float)r * 0x1p-22f)) * 1.0001f;
-  const float xnorm = sqrtf(xsq * (1.0f + (float)d * 0x1p-22f)) * 1.0001f;
-  const float bound1 = tnorm * zmax * 1.0001f, bound2 = xnorm * umax * 1.0001f;
-  const uint32_t anchor1 = fine_bin(__float_as_uint(bound1)), anchor2 = fine_bin(__float_as_uint(bound2));
-  if (blockIdx.x == 0 && tid == 0) {
-    fr->anchor1 = anchor1;
-    fr->anchor2 = anchor2;
-    if (N & 1) keys[N] = 0.0;  // zero padding of the handed-on key array up to a whole 16-byte vector
+  uint32_t anchor1[TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) {
+    const float tt = wave_sum(lane < kWPT ? red_t[t * kWPT + lane] : 0.0f);
+    const float xx = wave_sum(lane < kWPT ? red_x[t * kWPT + lane] : 0.0f);
+    const float tnorm = sqrtf(tt * (1.0f + (float)r * 0x1p-22f)) * 1.0001f;
+    const float xnorm = sqrtf(xx * (1.0f + (float)d * 0x1p-22f)) * 1.0001f;
+    const float bound1 = tnorm * zmax * 1.0001f, bound2 = xnorm * umax * 1.0001f;
+    anchor1[t] = fine_bin(__float_as_uint(bound1));
+    if (blockIdx.x == 0 && tid == 0 && t < B) {
+      fr[t].anchor1 = anchor1[t];
+      fr[t].anchor2 = fine_bin(__float_as_uint(bound2));
+      if (N & 1) keys[t * stride + N] = 0.0;  // zero padding of the handed-on keys up to a whole 16-byte vector
+    }
   }
   const int total = (int)gridDim.x * kSW * kRows;
   for (int j0 = ((int)blockIdx.x * kSW + w) * kRows; j0 < N; j0 += total) {
     const int j = j0 + rw;
     const uint4* row = reinterpret_cast<const uint4*>(z2 + (size_t)min(j, N - 1) * r);
-    double acc = 0.0;
+    double acc[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[t] = 0.0;
     for (int c0 = 0; c0 < cpr; c0 += ROW_LANES) {
       const int c = c0 + sub;
       const uint4 wv = row[min(c, cpr - 1)];
-      const uint4 tv = ts[min(c, cpr - 1)];
       const uint32_t keep = c < cpr ? 0xFFFFFFFFu : 0u;
       const uint32_t wd[4] = {wv.x & keep, wv.y & keep, wv.z & keep, wv.w & keep};
-      const uint32_t td[4] = {tv.x, tv.y, tv.z, tv.w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc += (double)(bf16_lo(wd[q]) * bf16_lo(td[q]));
-        acc += (double)(bf16_hi(wd[q]) * bf16_hi(td[q]));
+      for (int t = 0; t < TT; ++t) {
+        const uint4 tv = ts[t][min(c, cpr - 1)];
+        const uint32_t td[4] = {tv.x, tv.y, tv.z, tv.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[t] += (double)(bf16_lo(wd[q]) * bf16_lo(td[q]));
+          acc[t] += (double)(bf16_hi(wd[q]) * bf16_hi(td[q]));
+        }
       }
     }
-    double s;
-    if constexpr (ROW_LANES == kWave) {
-      s = wave_sum(acc);
-    } else {  // prefix sum along the 16 lanes of a DPP row: the row's last lane holds its total
-      auto add = [](double a, double b) { return a + b; };
-      s = acc;
-      s = add(s, dpp_move<0x111, 0xF>(0.0, s));
-      s = add(s, dpp_move<0x112, 0xF>(0.0, s));
-      s = add(s, dpp_move<0x114, 0xF>(0.0, s));
-      s = add(s, dpp_move<0x118, 0xF>(0.0, s));
-    }
-    if (sub == ROW_LANES - 1 && j < N) {
-      s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-      keys[j] = s;
-      const uint32_t slot = anchor1 - fine_bin((uint64_t)__double_as_longlong(s));  // keys lie at or below the anchor
-      if (hist_ok && s > 0.0 && slot < (uint32_t)kWin) atomicAdd(&fr->hist1[slot], 1u);  // zeros are never counted
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      double s;
+      if constexpr (ROW_LANES == kWave) {
+        s = wave_sum(acc[t]);
+      } else {  // prefix sum along the 16 lanes of a DPP row: the row's last lane holds its total
+        auto add = [](double a, double b) { return a + b; };
+        s = acc[t];
+        s = add(s, dpp_move<0x111, 0xF>(0.0, s));
+        s = add(s, dpp_move<0x112, 0xF>(0.0, s));
+        s = add(s, dpp_move<0x114, 0xF>(0.0, s));
+        s = add(s, dpp_move<0x118, 0xF>(0.0, s));
+      }
+      if (sub == ROW_LANES - 1 && j < N && t < B) {
+        s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
+        keys[t * stride + j] = s;
+        const uint32_t slot = anchor1[t] - fine_bin((uint64_t)__double_as_longlong(s));  // at or below the anchor
+        if (t < clean && s > 0.0 && slot < (uint32_t)kWin) atomicAdd(&fr[t].hist1[slot], 1u);  // (never a zero)
+      }
     }
   }
   HIRE_TS(34);
@@ -425,7 +441,7 @@ __device__ __forceinline__ void token_to_lds(const uint4* __restrict__ x, int xv
 
 template <typename K, int LOADS>
 __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
-  using Keys = KeyRegs<K, LOADS, kGT>;
+  using Keys = KeyRegs<K, LOADS, kGT, false, true>;
   __shared__ GatherShared sh;
   __shared__ int wave_cnt[kGW];
   __shared__ BinList<K> list;
@@ -623,7 +639,7 @@ __device__ __forceinline__ int slice_of(int b, int slices) {
 // The shortlist in ascending order, for the caller, by one workgroup: K, LK as in the gathering kernel.
 template <typename K, int LK>
 __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& sh, int* wave_cnt, BinList<K>& list) {
-  using Keys = KeyRegs<K, LK, kWT>;
+  using Keys = KeyRegs<K, LK, kWT, false, true>;
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const uint32_t bin = p.fr->bin1;
   const int need = (int)p.fr->need1;
@@ -671,7 +687,7 @@ __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& 
 template <typename KEY, int LOADS, int COLS>
 __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   using K = uint32_t;
-  using Keys = KeyRegs<K, LOADS, kWT>;
+  using Keys = KeyRegs<K, LOADS, kWT, false, true>;
   constexpr int PER = Keys::PER;
   __shared__ W2Shared sh;
   __shared__ BinList<KEY> list;
@@ -711,6 +727,16 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   kr.issue(h32, p.n, p.fr->zeros);
   if (tid == 0) sh.list_n = 0;
   kr.finish();
+  // rows of the wave: slot-th of every sixteen, eight columns per lane
+  const int slot = lane / kRowLanes, part = lane % kRowLanes;
+  const int colc = min(cs * COLS + part * 8, p.d - 8);
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  auto add_row = [&](const uint4& wv, float cf) {
+    const float wf[8] = {bf16_lo(wv.x), bf16_hi(wv.x), bf16_lo(wv.y), bf16_hi(wv.y),
+                         bf16_lo(wv.z), bf16_hi(wv.z), bf16_lo(wv.w), bf16_hi(wv.w)};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf, wf[q], acc[q]);
+  };
   // the activations' window is valid on any workspace: this step's scorer kernel cleared it, its gather filled it
   const WinWalk wk = walk_window<kWT>(wr, p.k, sh);
   HIRE_TS(20);
@@ -798,29 +824,20 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
     const int run = w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0;
     uint32_t ordered = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
+    int* places = reinterpret_cast<int*>(&red[0][0]);  // groups: for the copy of their units' activations
+    static_assert(sizeof(red) >= 2048 * sizeof(int), "2048 groups of eight at most");
     place_taken<Keys>(ordered, run, [&](int at, int e, int q) {
       const int i = kr.index(e, q);
       if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
-      if (p.topk_val) {
-        if (gs == 0) p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
-        else
-          for (int l = 0; l < (1 << gs); ++l) p.topk_val[((b * p.k + at) << gs) + l] = u32[(i << gs) + l];
-      }
+      if (gs != 0) places[at] = i;
+      else if (p.topk_val) p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
     });
+    if (gs != 0 && p.topk_val) {
+      __syncthreads();
+      for (int i = tid; i < p.k << gs; i += kWT)
+        p.topk_val[(b * p.k << gs) + i] = u32[(places[i >> gs] << gs) + (i & ((1 << gs) - 1))];
+    }
   } else {
-    // rows of the wave: slot-th of every sixteen, eight columns per lane
-    const int slot = lane / kRowLanes, part = lane % kRowLanes;
-    const int colc = min(cs * COLS + part * 8, p.d - 8);
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto add_rows = [&](const uint4 (&wv)[kW2Batch], const float (&cf)[kW2Batch]) {
-#pragma unroll
-      for (int u = 0; u < kW2Batch; ++u) {
-        const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
-                             bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf[u], wf[q], acc[q]);
-      }
-    };
     // The wave's selected entries go to LDS lane by lane (any fixed order will do), at most kSegRows rows at a time;
     // their coefficients are loaded with the rows.
     const int mine_n = __popc(take), incl = wave_scan_incl(mine_n);
@@ -838,32 +855,35 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       HIRE_TS(26);
       const int m = min(kSegRows, rows - c0);
       uint4 wv[kW2Batch];
-      float cf[kW2Batch];
+      float raw[kW2Batch];
 #pragma unroll
       for (int u = 0; u < kW2Batch; ++u)
         if (u * kRowsPerLoad < m) {  // uniform
-          const int r = u * kRowsPerLoad + slot, rc = min(r, m - 1);
+          const int rc = min(u * kRowsPerLoad + slot, m - 1);
           const int unit = (seg[w][rc >> gs] << gs) + (rc & ((1 << gs) - 1));
           wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2 + (size_t)unit * p.d + colc));
-          const float c = coef[unit];
-          cf[u] = r < m ? c : 0.0f;
-        } else {
-          wv[u] = make_uint4(0, 0, 0, 0);
-          cf[u] = 0.0f;
+          raw[u] = coef[unit];
         }
-      add_rows(wv, cf);
-    }
-    for (int r0 = w * kRowsPerLoad + slot; r0 < p.m1; r0 += kWW * kRowsPerLoad * kW2Batch) {  // dense units
-      uint4 wv[kW2Batch];
-      float cf[kW2Batch];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < kW2Batch; ++u) {
-        const int r = r0 + u * kWW * kRowsPerLoad, rc = min(r, p.m1 - 1);
-        wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc));
-        const float c = (float)p.hd[b * p.m1 + rc];
-        cf[u] = r < p.m1 ? c : 0.0f;
-      }
-      add_rows(wv, cf);
+      for (int u = 0; u < kW2Batch; ++u)
+        if (u * kRowsPerLoad < m) add_row(wv[u], u * kRowsPerLoad + slot < m ? raw[u] : 0.0f);
+    }
+    for (int r0 = w * kRowsPerLoad; r0 < p.m1; r0 += kWW * kRowsPerLoad * kW2Batch) {  // dense units, uniform
+      uint4 wv[kW2Batch];
+      double raw[kW2Batch];  // (nothing is done with a load before all are out)
+#pragma unroll
+      for (int u = 0; u < kW2Batch; ++u)
+        if (r0 + u * kWW * kRowsPerLoad < p.m1) {  // uniform
+          const int rc = min(r0 + u * kWW * kRowsPerLoad + slot, p.m1 - 1);
+          wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc));
+          raw[u] = p.hd[b * p.m1 + rc];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kW2Batch; ++u)
+        if (r0 + u * kWW * kRowsPerLoad < p.m1)
+          add_row(wv[u], r0 + u * kWW * kRowsPerLoad + slot < p.m1 ? (float)raw[u] : 0.0f);
     }
     HIRE_TS(27);
     // fixed-order reduction: the slots of a DPP row (its last lanes then hold their sums), the rows of all
@@ -942,21 +962,20 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   // what the selections rank: units with their keys and activations, or groups with their summed ones
   const int n_sel = a.N >> gs, kp_sel = a.kprime >> gs, k_sel = a.k >> gs;
   const bool lowrank = a.lowrank, several = a.B > 1;
-  if (several && lowrank) return hipErrorInvalidValue;
   const void* sel_keys = lowrank ? static_cast<const void*>(a.keys64) : (gs ? a.gkeys : a.keys);
   if (lowrank) {
     if (gs != 0 || a.m1 != 0 || a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
-    e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, 1, a.d, a.r, nullptr, a.t_partial, nullptr, 0, nullptr,
+    e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, a.B, a.d, a.r, nullptr, a.t_partial, nullptr, 0, nullptr,
                           0ull, s);
     if (e != hipSuccess) return e;
     const int slices = lr_project_slices(a.d);
     const uint4* x4 = reinterpret_cast<const uint4*>(a.x);
-    if (a.r <= 128)
-      e = launch(k_fast_score_lr<16>, dim3(score_blocks), dim3(kST), 0, s, a.t_partial, slices,
-                 static_cast<const uint16_t*>(a.lr_b), x4, a.N, a.d, a.r, a.norm_bounds, a.keys64, fr);
-    else
-      e = launch(k_fast_score_lr<kWave>, dim3(score_blocks), dim3(kST), 0, s, a.t_partial, slices,
-                 static_cast<const uint16_t*>(a.lr_b), x4, a.N, a.d, a.r, a.norm_bounds, a.keys64, fr);
+    auto go = [&](auto kernel) {
+      return launch(kernel, dim3(score_blocks), dim3(kST), 0, s, a.t_partial, slices, static_cast<const uint16_t*>(a.lr_b),
+                    x4, a.B, a.N, a.d, a.r, a.norm_bounds, a.keys64, a.key_stride, fr);
+    };
+    if (a.r <= 128) e = several ? go(k_fast_score_lr<16, 4>) : go(k_fast_score_lr<16, 1>);
+    else e = several ? go(k_fast_score_lr<kWave, 4>) : go(k_fast_score_lr<kWave, 1>);
     if (e != hipSuccess) return e;
     if ((e = mark(1)) != hipSuccess) return e;
   } else if (a.lrq) {
@@ -1024,7 +1043,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     const int extra = (a.topk_idx || a.topk_val ? 1 : 0) + (a.cand_out || (several && a.n_cand) ? 1 : 0);
     int cols = 32;
     while (cols < 128 && ((a.d + cols - 1) / cols + extra) * a.B > 256) cols *= 2;
-    if (lowrank) cols = 32;
+    if (lowrank && !several) cols = 32;
     p.col_slices = (a.d + cols - 1) / cols;
     int blocks = p.col_slices;
     p.out_block = a.topk_idx || a.topk_val ? blocks++ : -1;
@@ -1037,7 +1056,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     p.W2d = a.dense_w2u; p.hd = a.h_dense; p.m1 = a.m1;
     auto go = [&](auto kernel) { return launch(kernel, dim3(blocks, a.B), dim3(kWT), 0, s, p); };
     auto by_cols = [&](auto k32, auto k64, auto k128) { return cols == 32 ? go(k32) : (cols == 64 ? go(k64) : go(k128)); };
-    if (lowrank)
+    if (lowrank && !several)  // (its list of the shortlist reads the fp64 keys)
       e = n_sel <= 4096 ? go(k_fast_w2<uint64_t, 1, 32>)
                         : (n_sel <= 8192 ? go(k_fast_w2<uint64_t, 2, 32>) : go(k_fast_w2<uint64_t, 4, 32>));
     else if (n_sel <= 4096)

@@ -687,7 +687,7 @@ hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lr
 
 hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s) {
   FastGatherTokens p{};
-  p.keys = a.gs ? a.gkeys : a.keys;
+  p.keys = a.lowrank ? static_cast<const void*>(a.keys64) : (a.gs ? a.gkeys : a.keys);
   p.stride = a.gs ? a.gkey_stride : a.key_stride;
   p.B = a.B; p.N = a.N; p.kprime = a.kprime >> a.gs; p.d = a.d;
   p.fr = reinterpret_cast<FastRegion*>(a.fast_region);
@@ -703,12 +703,13 @@ hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s) {
   const int rest = max(0, a.m1 - p.own_blocks * p.share);
   const size_t lds = (size_t)kTW * (kMostRows / 4) * (token_slots(a.B) / 4) * 16 * sizeof(double);
   const dim3 grid(p.own_blocks + (rest + kDenseRows - 1) / kDenseRows);
-  static std::atomic<size_t> raised_to[2] = {};
+  static std::atomic<size_t> raised_to[3] = {};
   auto go = [&](auto kernel, int i) -> hipError_t {
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to[i]); e != hipSuccess)
       return e;
     return launch(kernel, grid, dim3(kTT), lds, s, p);
   };
+  if (a.lowrank) return token_slots(a.B) == 4 ? go(k_fast_gather_tokens<uint64_t, 4>, 2) : hipErrorInvalidValue;
   switch (token_slots(a.B)) {
     case 4: return go(k_fast_gather_tokens<uint32_t, 4>, 0);
     default: return go(k_fast_gather_tokens<uint32_t, 8>, 1);

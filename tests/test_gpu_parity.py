@@ -217,6 +217,8 @@ def test_batch1_gather_and_second_layer_edges(hire, oracle, d, N, k, kp, lr):
     (4096, 640, 8, 80, 240, 33),       # groups of eight from here on: longest eight tokens, dense units in two workgroups
     (800, 16000, 5, 400, 1600, 16001), # more dense units than the workgroups of the sparse ones take along
     (160, 1040, 7, 8, 8, 0),           # one group of each token
+    (320, 2048, 1, 2048, 2048, 300),   # one token, every group
+    (2048, 16384, 2, 1024, 4096, 40),  # most groups
 ])
 def test_few_tokens_edges(hire, oracle, d, N, B, k, kp, m1):
     log(f"few tokens d={d} N={N} B={B} k={k} kp={kp} m1={m1}")
@@ -224,11 +226,21 @@ def test_few_tokens_edges(hire, oracle, d, N, B, k, kp, m1):
     L["w1u"][N // 4:N // 4 + 40] = L["w1u"][N // 4]     # equal keys and activations
     layer, scorer = T.make_ffn_layer(L)
     x = I.tokens(100 + B, B, d)
-    if B <= 4:
+    if B <= 4 and m1 == 0:
         T.check_ffn(layer, scorer, L, x, k, kp)
     else:
         D = I.ffn_layer(101, d, max(m1, 1))
         T.check_ffn_commonpath(layer, scorer, L, (D["w1u"][:m1], D["w2u"][:m1]), x, k, kp, 8)
+
+
+@pytest.mark.parametrize("d,N,r,B,k,kp", [(64, 16383, 24, 4, 700, 2500), (512, 777, 136, 2, 40, 200), (1024, 1025, 1024, 3, 9, 30)])
+def test_few_tokens_lowrank_edges(hire, oracle, d, N, r, B, k, kp):
+    log(f"few tokens, low-rank scorer d={d} N={N} r={r} B={B}")
+    L = I.lowrank_ffn_layer(104 + d, d, N, r)
+    L["w1u"][N // 4:N // 4 + 40] = L["w1u"][N // 4]
+    L["z2"][N // 4:N // 4 + 40] = L["z2"][N // 4]
+    layer, scorer = T.make_ffn_layer(L, lowrank=True)
+    T.check_ffn(layer, scorer, L, I.tokens(105, B, d), k, kp)
 
 
 def test_few_tokens_share_a_workspace(hire, oracle):
