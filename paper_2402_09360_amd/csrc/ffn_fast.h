@@ -3,6 +3,7 @@
 
 #include "fast_select.h"
 #include "kernels.h"
+#include "rows_mfma.h"
 
 namespace hire {
 
@@ -40,7 +41,4 @@ struct RowChunks {
     for (int u = 0; u < 4; ++u) v[u] = load_streaming(&row[min(c0 + u * kWave + lane_id(), cpr - 1)]);
   }
 };
-// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 }  // namespace hire

@@ -11,9 +11,7 @@
 
 namespace hire {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-constexpr int kTT = 1024;  // threads
+constexpr int kTT = kRowsThreads;
 constexpr int kTW = kTT / kWave;
 constexpr int kTokRows = 64;  // rows of a workgroup of the scorer
 
@@ -108,47 +106,23 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
   lds_barrier();
   HIRE_TS(31);
   amax = wave_max(lane < kWPT ? red[t * kWPT + lane] : 0.0f);
-  float sx = __fdiv_rn(amax, 127.0f);
-  if (amax == 0.0f) sx = 1.0f;
-  // code = rint(x / sx), the quotient correctly rounded: with the correctly rounded reciprocal of a divisor whose
-  // significand is not all ones, one residual corrects the product (Markstein, IBM J. Res. Dev. 34, 1990).  The
-  // division itself where that does not apply or the residual could underflow.
-  const float rs = __fdiv_rn(1.0f, sx);
-  const bool plain = sx > 0x1p-100f && sx < 0x1p100f && (__float_as_uint(sx) & 0x7FFFFFu) != 0x7FFFFFu;  // uniform
+  const TokenScale ts = token_scale(amax);
   float sabs = 0.0f;
 #pragma unroll
   for (int m = 0; m < VECS; ++m)
     if (m * kWPT * kWave < nvec) {  // uniform
-      const uint32_t ud[4] = {xv[m].x, xv[m].y, xv[m].z, xv[m].w};
-      float r[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float f = (e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), y = f * rs;
-        r[e] = rintf(fmaf(fmaf(-y, sx, f), rs, y));
-      }
-      if (!plain) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          r[e] = rintf(__fdiv_rn((e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), sx));
-      }
-      uint32_t packed[2] = {0u, 0u};
-      float sum8 = 0.0f;
+      float sum8;
+      const uint2 codes = quantise8(xv[m], ts, &sum8);
       const int i = m * kWPT * kWave + lt;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        r[e] = fminf(fmaxf(r[e], -127.0f), 127.0f);
-        sum8 += fabsf(r[e]);
-        packed[e / 4] = __builtin_amdgcn_cvt_pk_u8_f32(r[e] + 128.0f, e & 3, packed[e / 4]);  // (whole numbers)
-      }
       if (i < nvec) {
         sabs += sum8;
-        reinterpret_cast<uint2*>(xs + t * xstride)[i] = make_uint2(packed[0] ^ 0x80808080u, packed[1] ^ 0x80808080u);
+        reinterpret_cast<uint2*>(xs + t * xstride)[i] = codes;
       }
     }
   sabs = wave_sum(sabs);
   if (lane == 0) {
     isum[w] = sabs;
-    if (w % kWPT == 0) sxs[t] = sx;
+    if (w % kWPT == 0) sxs[t] = ts.sx;
   }
   lds_barrier();
   HIRE_TS(32);
@@ -185,17 +159,11 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
       if (s0 + i < nsl) {  // uniform
         const int c = (s0 + i) * 16 + (lane >> 2), cc = min(c, cpr - 1);
         const uint32_t keep = c < cpr ? 0xFFFFFFFFu : 0u;  // past the row's end: zeros
-        const uint32_t wd[4] = {wv[i].x & keep, wv[i].y & keep, wv[i].z & keep, wv[i].w & keep};
+        const uint4 codes = make_uint4(wv[i].x & keep, wv[i].y & keep, wv[i].z & keep, wv[i].w & keep);
 #pragma unroll
         for (int f = 0; f < kTok4; ++f) {
           const uint4* xr = xs + (f * 4 + (lane & 3)) * xstride + 2 * cc;
-          const uint4 ta = xr[0], tb = xr[1];
-          const int xd[8] = {(int)ta.x, (int)ta.y, (int)ta.z, (int)ta.w, (int)tb.x, (int)tb.y, (int)tb.z, (int)tb.w};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[f] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)(wd[q] & 0xF0F0F0F0u), xd[2 * q], acc[f], 0, 0, 0);
-            acc[f] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)((wd[q] << 4) & 0xF0F0F0F0u), xd[2 * q + 1], acc[f], 0, 0, 0);
-          }
+          int4_rows_by_tokens(codes, xr[0], xr[1], acc[f]);
         }
       }
   }
@@ -270,99 +238,7 @@ struct FastGatherTokens {
   int m1;
   double* hd;                 // [B, m1]
 };
-constexpr int kDenseRows = 32, kMostRows = kOwnUnits + 32;
-
-// out(r, t, relu(<row r, x_t>)) for r < cnt <= kMostRows rows and all tokens, by the workgroup.  v_mfma_f64_4x4x4: four
-// rows and four tokens at a time, in lane l row l % 4 of A, token l % 4 of B and column chunk l / 4 of both, element by
-// element of the sixteen-byte chunks (the order of the columns does not matter to a dot product).  A wave has SL slices
-// of sixteen chunks of the columns, whose token values stay in its registers as fp64, and runs over its share of the
-// rows, four at a time, eight loads in flight; nothing goes through LDS but the waves' sums.  SL as large as the
-// registers allow: a wave then reads up to a KB of a row (9.9 us for the rows of four tokens at the ~1B shape with 256
-// bytes, 8.6 with a KB, 7.8 with whole rows).  red: [parts of the columns][groups of four rows][TT / 4][16] sums, added
-// in a fixed order.
-template <int TT, typename RowOf, typename Out>
-__device__ __forceinline__ void rows_by_tokens(int cnt, RowOf&& row_of, const uint4* __restrict__ x, int B, int nvec,
-                                               double* red, Out&& out) {
-  constexpr int kTok4 = TT / 4, SL = 4 / kTok4, kDepth = 8 / SL, kMaxGroups = kMostRows / 4;
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int nsl = (nvec + 15) / 16, ng = (cnt + 3) / 4;
-  int ps = 1;  // waves side by side over the columns: sixteen parts are enough (TT d <= 32768)
-  while (ps * SL < nsl) ps <<= 1;
-  const int s0 = (w & (ps - 1)) * SL, rp = w / ps, step = kTW / ps;
-  uint4 ring[kDepth][SL];
-  auto load = [&](int q, uint4 (&v)[SL]) {
-    const uint4* row = row_of(min(q * 4 + (lane & 3), cnt - 1));
-#pragma unroll
-    for (int j = 0; j < SL; ++j) v[j] = load_streaming(row + min((s0 + j) * 16 + (lane >> 2), nvec - 1));
-  };
-  uint4 xr[SL][kTok4];  // asked for ahead of the rows: loads return in order
-#pragma unroll
-  for (int j = 0; j < SL; ++j)
-#pragma unroll
-    for (int f = 0; f < kTok4; ++f)
-      xr[j][f] = x[(size_t)min(f * 4 + (lane & 3), B - 1) * nvec + min((s0 + j) * 16 + (lane >> 2), nvec - 1)];
-#pragma unroll
-  for (int i = 0; i < kDepth; ++i)
-    if (s0 < nsl && rp + i * step < ng) load(rp + i * step, ring[i]);  // uniform
-  if (s0 < nsl) {  // uniform over the wave
-    double xd[SL][kTok4][8];
-    uint32_t keep[SL];  // past the row's end: zeros
-#pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      const int c = (s0 + j) * 16 + (lane >> 2);
-      keep[j] = c < nvec ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-      for (int f = 0; f < kTok4; ++f) {
-        const uint4 u = xr[j][f];
-        const uint32_t ud[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          xd[j][f][2 * q] = (double)bf16_lo(ud[q]);
-          xd[j][f][2 * q + 1] = (double)bf16_hi(ud[q]);
-        }
-      }
-    }
-    for (int q0 = rp; q0 < ng; q0 += kDepth * step) {
-#pragma unroll
-      for (int i = 0; i < kDepth; ++i) {
-        const int q = q0 + i * step;
-        if (q < ng) {  // uniform
-          double acc[kTok4];
-#pragma unroll
-          for (int f = 0; f < kTok4; ++f) acc[f] = 0.0;
-#pragma unroll
-          for (int j = 0; j < SL; ++j) {
-            const uint4 u = ring[i][j];
-            const uint32_t wd[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const double wf = (double)((e & 1) != 0 ? bf16_hi(wd[e / 2]) : bf16_lo(wd[e / 2]));
-#pragma unroll
-              for (int f = 0; f < kTok4; ++f) acc[f] = __builtin_amdgcn_mfma_f64_4x4x4f64(wf, xd[j][f][e], acc[f], 0, 0, 0);
-            }
-          }
-          if (q + kDepth * step < ng) load(q + kDepth * step, ring[i]);
-#pragma unroll
-          for (int f = 0; f < kTok4; ++f) {  // row l / 16, token l % 4: the four blocks of columns
-            double v = acc[f] + dpp_move<0x124, 0xF>(0.0, acc[f]);
-            v += dpp_move<0x128, 0xF>(0.0, v);
-            if ((lane & 12) == 0)
-              red[(((size_t)(w & (ps - 1)) * kMaxGroups + q) * kTok4 + f) * 16 + (lane >> 4) * 4 + (lane & 3)] = v;
-          }
-        }
-      }
-    }
-  }
-  HIRE_TS(16);
-  lds_barrier();
-  HIRE_TS(17);
-  for (int o = tid; o < ng * kTok4 * 16; o += kTT) {
-    const int r = o / (kTok4 * 16) * 4 + (o >> 2 & 3), t = o / 16 % kTok4 * 4 + (o & 3);
-    double v = 0.0;
-    for (int j = 0; j * SL < nsl; ++j) v += red[(size_t)j * kMaxGroups * kTok4 * 16 + o];
-    if (r < cnt && t < B) out(r, t, v > 0.0 ? v : 0.0);  // ReLU, and -0 -> +0
-  }
-}
+constexpr int kDenseRows = 32;
 
 // Where the selection of the k largest of n keys in memory cuts them, without a histogram.
 template <typename K>

@@ -11,15 +11,18 @@
 //
 // A shard is small (64 units at s = 256 for d_ff = 16384), so both selections are done by counting, for every
 // entry, how many entries beat it (larger value, or equal value and lower index): exact, tie rule included,
-// and a few LDS reads per thread.  Each phase issues all of its row loads before it uses any of them, spread over
-// the workgroup's 16 waves: four packed int4 rows per wave while scoring, one bf16 row per wave in the exact
-// stage, four per thread in the second layer.
+// and a few LDS reads per thread; shards of at most 64 units by one wave per token.  Each phase issues all of its row
+// loads before it uses any of them, spread over the workgroup's 16 waves: four packed int4 rows per wave while scoring,
+// one bf16 row per wave (several tokens: a part of four rows) in the exact stage, four per thread in the second layer.
 //
-// Batches are taken in bundles of up to four tokens that share every loaded row; larger batches run bundle after
-// bundle (rows re-read through the caches) with the union flags carried along: correct for any batch size, tuned
-// for one to four tokens.
+// Batches are taken in bundles of four tokens that share every loaded row, which goes through the matrix cores against
+// all four (rows_mfma.h); larger batches run bundle after bundle (rows re-read through the caches) with the union flags
+// carried along: correct for any batch size, tuned for one to four tokens.  Measured at the ~1B shape, 256 shards and
+// four tokens: 24.9 us, 35.5 with the scores (5.3) and exact values (about 13) on the vector units, token after token
+// in the first selection (3.2).
 #include "device_utils.h"
 #include "kernels.h"
+#include "rows_mfma.h"
 #include "select.h"
 
 namespace hire {
@@ -28,6 +31,8 @@ namespace hire {
 // and hold loads in flight, not by registers or LDS.
 constexpr int kShThreads = 1024;
 constexpr int kShWaves = kShThreads / kWave;
+static_assert(kShThreads == kRowsThreads, "rows_by_tokens");
+constexpr int kShRed = kRowsWaves * (kMostRows / 4) * 16;  // doubles
 
 __device__ __forceinline__ float shard_block_max(float v, float* red) {
   v = wave_max(v);
@@ -93,21 +98,30 @@ __device__ __forceinline__ void rank_flags(const T* v, int n, int want, int* fla
   __syncthreads();
 }
 
-// The same selection for a row of at most 64 entries by ONE wave (lane i counts for entry i; the other waves wait
-// at the caller's barrier and leave it the instruction issue): returns the selected entries as a bit mask.
+// The same selection for the rows of at most 64 entries of up to four tokens, four waves per token: lane i has entry i
+// and counts the larger ones among sixteen.  Of the equal entries at the boundary the first are taken.  masks[b]: the
+// selected entries of row b, v + b * stride.  All threads call this; it ends with a barrier.
 template <typename T>
-__device__ __forceinline__ uint64_t wave_rank_mask(const T* v, int n, int want) {
-  const int i = lane_id();
-  const T vi = v[min(i, n - 1)];
-  int cnt = 0;
-  for (int j0 = 0; j0 < n; j0 += 4) {
-    T vj[4];
+__device__ __forceinline__ void rank_masks(const T* v, int stride, int rows, int n, int want, int (*counts)[kWave],
+                                           uint64_t* masks) {
+  const int i = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  if (w >> 2 < rows) {
+    const T vi = i < n ? v[(w >> 2) * stride + i] : (T)-1;  // (below every entry)
+    int cnt = 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) vj[u] = v[j0 + u];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) cnt += (vj[u] > vi || (vj[u] == vi && j0 + u < i)) ? 1 : 0;
+    for (int j = 0; j < 16; ++j) cnt += read_lane(vi, (w & 3) * 16 + j) > vi ? 1 : 0;
+    counts[w][i] = cnt;
   }
-  return __ballot(i < n && cnt < want);
+  lds_barrier();
+  if (w < rows) {
+    const int cnt = counts[4 * w][i] + counts[4 * w + 1][i] + counts[4 * w + 2][i] + counts[4 * w + 3][i];
+    const uint64_t in = __ballot(i < n && cnt < want);
+    const int last = wave_max(i < n && cnt < want ? cnt : -1), need = want - last;  // the boundary's entries: cnt == last
+    const uint64_t tie = __ballot(i < n && cnt == last);
+    const uint64_t m = (in & ~tie) | __ballot(((tie >> i) & 1ull) != 0ull && mask_prefix(tie) < need);
+    if (i == 0) masks[w] = m;
+  }
+  lds_barrier();
 }
 
 // list[0..) = the indices i < n with flag[i] set, ascending; returns how many (to every thread).  256 entries per
@@ -155,16 +169,21 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
     const uint16_t* __restrict__ w2u, const uint16_t* __restrict__ x, int B, int N, int d, int Ls, int kps, int ks,
     int cap, float* __restrict__ partial, int32_t* __restrict__ topk_idx, float* __restrict__ topk_val,
     int32_t* __restrict__ cand, int32_t* __restrict__ n_cand, int32_t* __restrict__ acc_out) {
-  constexpr int kRowsPerWave = BT >= 4 ? 2 : 4 / CH;  // packed rows a wave has in flight while scoring (registers)
+  static_assert(BT <= 2 || BT == 4, "one or two tokens, or four on the matrix cores");
+  constexpr int kRowsPerWave = BT == 4 ? 4 : 4 / CH;  // packed rows a wave has in flight while scoring (registers)
   constexpr int kXch = 4 * CH;           // 16-byte chunks of a bf16 row per lane
   extern __shared__ uint4 lds[];
   __shared__ uint32_t amax_sh[BT];
   __shared__ int wave_cnt[kShWaves];
+  __shared__ uint64_t masks[BT];
+  __shared__ int counts[4 * BT][kWave];
   const int cpr = d / 32, c8 = d / 8, c16 = d / 16;
   const int Lp = (Ls + 3) & ~3;                      // padded to whole groups of four for the rank counting
-  uint4* xb = lds;                                   // [BT][d/8]  tokens, raw bf16
-  uint4* xq = xb + BT * c8;                          // [BT][d/16] tokens, int8
-  double* hv = reinterpret_cast<double*>(xq + BT * c16);  // [BT][Lp] exact pre-activations on the union
+  const int xqs = BT < 4 ? c16 : c16 + 1;            // (padded: four tokens are read at once)
+  uint4* xb = lds;                                   // [BT][d/8] one or two tokens: raw bf16
+  double* red = reinterpret_cast<double*>(lds);      // four: sums of rows_by_tokens
+  uint4* xq = xb + (BT < 4 ? BT * c8 : kShRed / 2);      // [BT][xqs] tokens, int8
+  double* hv = reinterpret_cast<double*>(xq + BT * xqs);  // [BT][Lp] exact pre-activations on the union
   float* keys = reinterpret_cast<float*>(hv + BT * Lp);   // [BT][Lp]
   int* uflag = reinterpret_cast<int*>(keys + BT * Lp);    // [Ls] unit is in the union
   int* ulist = uflag + Ls;                           // [Ls] the union, ascending local unit numbers
@@ -200,7 +219,7 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
       const int idx = tid + u * kShThreads;
       if (idx >= BT * c8) continue;
       const uint4 v = xreg[u];
-      xb[idx] = v;
+      if constexpr (BT < 4) xb[idx] = v;
       if (want_amax) {
         const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
         float amax = 0.0f;
@@ -224,19 +243,9 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
       const int idx = tid + u * kShThreads;
       if (idx >= BT * c8) continue;
       const float m = __uint_as_float(amax_sh[xbb[u]]);
-      float sx = __fdiv_rn(m, 127.0f);
-      if (m == 0.0f) sx = 1.0f;
-      auto code = [&](float f) -> uint32_t {
-        float r = rintf(__fdiv_rn(f, sx));
-        r = fminf(fmaxf(r, -127.0f), 127.0f);
-        return (uint32_t)((int)r) & 0xFFu;
-      };
-      const uint4 v = xreg[u];
-      const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-      uint2 o;
-      o.x = code(bf16_lo(wd[0])) | code(bf16_hi(wd[0])) << 8 | code(bf16_lo(wd[1])) << 16 | code(bf16_hi(wd[1])) << 24;
-      o.y = code(bf16_lo(wd[2])) | code(bf16_hi(wd[2])) << 8 | code(bf16_lo(wd[3])) << 16 | code(bf16_hi(wd[3])) << 24;
-      reinterpret_cast<uint2*>(xq)[idx] = o;  // [BT][d/16] uint4 = [BT][d/8] uint2
+      float unused;
+      const uint2 codes = quantise8(xreg[u], token_scale(m), &unused);
+      reinterpret_cast<uint2*>(xq)[xbb[u] * 2 * xqs + xc[u]] = codes;
     }
     __syncthreads();
     if (tid < BT) amax_sh[tid] = 0u;  // for the next bundle; the barriers of the scoring that follows publish it
@@ -259,15 +268,22 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
   uint4 wv[kRowsPerWave][CH];
   const uint4* q4s = q4 + unit0 * cpr;  // the shard's packed rows; offsets inside a shard fit 32 bits
   auto fetch_packed = [&](int r0) {
+    if constexpr (BT == 4) {  // sixteen chunks of four rows per load
+      const uint4* row = q4s + min(r0 + (lane & 3), Ls - 1) * cpr;
 #pragma unroll
-    for (int rr = 0; rr < kRowsPerWave; ++rr) {  // clamped and unconditional: one batch of loads
-      const int row = min(r0 + rr, Ls - 1) * cpr;
+      for (int u = 0; u < 4 * CH; ++u) wv[u / CH][u % CH] = load_streaming(&row[min(u * 16 + (lane >> 2), cpr - 1)]);
+    } else {
 #pragma unroll
-      for (int u = 0; u < CH; ++u) wv[rr][u] = load_streaming(&q4s[row + min(lane + u * kWave, cpr - 1)]);
+      for (int rr = 0; rr < kRowsPerWave; ++rr) {  // clamped and unconditional: one batch of loads
+        const int row = min(r0 + rr, Ls - 1) * cpr;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) wv[rr][u] = load_streaming(&q4s[row + min(lane + u * kWave, cpr - 1)]);
+      }
     }
   };
 
   // ---- every token's shortlist of k'/s units, marked in the union flags ----
+  uint64_t in_union = 0ull;  // shards of at most 64 units
   for (int b0 = 0; b0 < B; b0 += BT) {
     const int nb = min(BT, B - b0);
     const int first = w * kRowsPerWave;
@@ -280,57 +296,100 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
     HIRE_TS(1);
     for (int r0 = first; r0 < Ls; r0 += kShWaves * kRowsPerWave) {
       if (r0 != first) fetch_packed(r0);
-      int acc[BT][kRowsPerWave];
+      if constexpr (BT == 4) {
+        v4i acc{0, 0, 0, 0};
 #pragma unroll
-      for (int bb = 0; bb < BT; ++bb)
+        for (int u = 0; u < 4 * CH; ++u)
+          if (u * 16 < cpr) {  // uniform
+            const int c = u * 16 + (lane >> 2);
+            const uint32_t keep = c < cpr ? 0xFFFFFFFFu : 0u;  // past the row's end: zeros
+            const uint4 v = wv[u / CH][u % CH];
+            const uint4* xr = xq + (lane & 3) * xqs + 2 * min(c, cpr - 1);
+            int4_rows_by_tokens(make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep), xr[0], xr[1], acc);
+          }
+        int sum = 0;  // lane l < 16: row l / 4, token l % 4
 #pragma unroll
-        for (int rr = 0; rr < kRowsPerWave; ++rr) acc[bb][rr] = 0;
+        for (int r = 0; r < 4; ++r) {
+          int v = acc[r];
+          v += dpp_move<0x124, 0xF>(0, v);
+          v += dpp_move<0x128, 0xF>(0, v);
+          v += __shfl_xor(v, 16);
+          v += __shfl_xor(v, 32);
+          sum = lane >> 2 == r ? v >> 4 : sum;  // every partial is a multiple of 16
+        }
+        const int bb = lane & 3, row = r0 + (lane >> 2);
+        if (lane < 16 && row < Ls && bb < nb) {
+          const size_t j = unit0 + row;
+          float key = (float)sum * scale[j];
+          key = key > 0.0f ? key : 0.0f;  // phi = ReLU; also turns -0 into +0
+          keys[bb * Lp + row] = key;
+          if (acc_out) acc_out[(size_t)(b0 + bb) * N + j] = sum;
+        }
+      } else {
+        int acc[BT][kRowsPerWave];
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int c = lane + u * kWave;
-        if (c < cpr) {
+        for (int bb = 0; bb < BT; ++bb)
 #pragma unroll
-          for (int bb = 0; bb < BT; ++bb) {
-            const uint4 xa = xq[bb * c16 + 2 * c], xc = xq[bb * c16 + 2 * c + 1];
-            const int xd[8] = {(int)xa.x, (int)xa.y, (int)xa.z, (int)xa.w,
-                               (int)xc.x, (int)xc.y, (int)xc.z, (int)xc.w};
+          for (int rr = 0; rr < kRowsPerWave; ++rr) acc[bb][rr] = 0;
 #pragma unroll
-            for (int rr = 0; rr < kRowsPerWave; ++rr) {
-              const uint32_t wd[4] = {wv[rr][u].x, wv[rr][u].y, wv[rr][u].z, wv[rr][u].w};
-              int a = acc[bb][rr];
+        for (int u = 0; u < CH; ++u) {
+          const int c = lane + u * kWave;
+          if (c < cpr) {
 #pragma unroll
-              for (int t = 0; t < 4; ++t) {  // a byte holds two codes: 16 * code from the high nibble, then the low one
-                a = __builtin_amdgcn_sdot4((int)(wd[t] & 0xF0F0F0F0u), xd[2 * t], a, false);
-                a = __builtin_amdgcn_sdot4((int)((wd[t] << 4) & 0xF0F0F0F0u), xd[2 * t + 1], a, false);
+            for (int bb = 0; bb < BT; ++bb) {
+              const uint4 xa = xq[bb * xqs + 2 * c], xc = xq[bb * xqs + 2 * c + 1];
+              const int xd[8] = {(int)xa.x, (int)xa.y, (int)xa.z, (int)xa.w,
+                                 (int)xc.x, (int)xc.y, (int)xc.z, (int)xc.w};
+#pragma unroll
+              for (int rr = 0; rr < kRowsPerWave; ++rr) {
+                const uint32_t wd[4] = {wv[rr][u].x, wv[rr][u].y, wv[rr][u].z, wv[rr][u].w};
+                int a = acc[bb][rr];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {  // a byte holds two codes: 16 * code from the high nibble, then the low one
+                  a = __builtin_amdgcn_sdot4((int)(wd[t] & 0xF0F0F0F0u), xd[2 * t], a, false);
+                  a = __builtin_amdgcn_sdot4((int)((wd[t] << 4) & 0xF0F0F0F0u), xd[2 * t + 1], a, false);
+                }
+                acc[bb][rr] = a;
               }
-              acc[bb][rr] = a;
             }
           }
         }
-      }
 #pragma unroll
-      for (int bb = 0; bb < BT; ++bb) {
-        int mine = 0;
+        for (int bb = 0; bb < BT; ++bb) {
+          int mine = 0;
 #pragma unroll
-        for (int rr = 0; rr < kRowsPerWave; ++rr) {
-          const int sum = wave_sum(acc[bb][rr]) >> 4;  // every partial is a multiple of 16
-          mine = lane == rr ? sum : mine;
-        }
-        if (lane < kRowsPerWave && r0 + lane < Ls && bb < nb) {
-          const size_t j = unit0 + r0 + lane;
-          float key = (float)mine * scale[j];
-          key = key > 0.0f ? key : 0.0f;  // phi = ReLU; also turns -0 into +0
-          keys[bb * Lp + r0 + lane] = key;
-          if (acc_out) acc_out[(size_t)(b0 + bb) * N + j] = mine;
+          for (int rr = 0; rr < kRowsPerWave; ++rr) {
+            const int sum = wave_sum(acc[bb][rr]) >> 4;  // every partial is a multiple of 16
+            mine = lane == rr ? sum : mine;
+          }
+          if (lane < kRowsPerWave && r0 + lane < Ls && bb < nb) {
+            const size_t j = unit0 + r0 + lane;
+            float key = (float)mine * scale[j];
+            key = key > 0.0f ? key : 0.0f;  // phi = ReLU; also turns -0 into +0
+            keys[bb * Lp + r0 + lane] = key;
+            if (acc_out) acc_out[(size_t)(b0 + bb) * N + j] = mine;
+          }
         }
       }
     }
     __syncthreads();
     HIRE_TS(2);
-    for (int bb = 0; bb < nb; ++bb) rank_flags<float>(keys + bb * Lp, Ls, kps, uflag, beat, true);
+    if (BT == 4 && Ls <= kWave) {
+      rank_masks<float>(keys, Lp, nb, Ls, kps, counts, masks);
+      for (int bb = 0; bb < nb; ++bb) in_union |= masks[bb];
+    } else {
+      for (int bb = 0; bb < nb; ++bb) rank_flags<float>(keys + bb * Lp, Ls, kps, uflag, beat, true);
+    }
     HIRE_TS(3);
   }
-  const int n_u = compact_flags(uflag, Ls, ulist, wave_cnt);
+  int n_u;
+  if (BT == 4 && Ls <= kWave) {
+    n_u = __popcll(in_union);
+    if (w == 0 && ((in_union >> lane) & 1ull) != 0ull) ulist[mask_prefix(in_union)] = lane;
+    __syncthreads();
+  } else {
+    n_u = compact_flags(uflag, Ls, ulist, wave_cnt);
+  }
   if (cand != nullptr)
     for (int t = tid; t < n_u; t += kShThreads) cand[(size_t)sh * cap + t] = (int32_t)unit0 + ulist[t];
   if (n_cand != nullptr && tid == 0) n_cand[sh] = n_u;
@@ -342,49 +401,59 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
   const int n_up = (n_u + 3) & ~3;
   for (int b0 = 0; b0 < B; b0 += BT) {
     const int nb = min(BT, B - b0);
-    if (B > BT) {  // a single bundle is still in LDS
-      request_tokens(b0);
-      tokens_to_lds(false);
-      __syncthreads();
-    }
-    for (int t0 = w; t0 < n_u; t0 += kShWaves) {  // one bf16 row per wave in flight, used for every token
-      uint4 ev[kXch];
-      const int row = ulist[t0] * c8;
+    if constexpr (BT == 4) {
+      for (int r0 = 0; r0 < n_u; r0 += kMostRows) {
+        if (r0 > 0) __syncthreads();  // the sums are read
+        rows_by_tokens<4, 2, CH == 1 ? 4 : 2>(  // (what the rest of the kernel leaves of the registers)
+            min(kMostRows, n_u - r0), [&](int r) { return w1s + (size_t)ulist[r0 + r] * c8; },
+            reinterpret_cast<const uint4*>(x) + (size_t)b0 * c8, nb, c8, red,
+            [&](int r, int t, double v) { hv[t * Lp + r0 + r] = v; });
+      }
+    } else {
+      if (B > BT) {
+        request_tokens(b0);
+        tokens_to_lds(false);
+        __syncthreads();
+      }
+      for (int t0 = w; t0 < n_u; t0 += kShWaves) {  // one bf16 row per wave in flight, used for every token
+        uint4 ev[kXch];
+        const int row = ulist[t0] * c8;
 #pragma unroll
-      for (int u = 0; u < kXch; ++u) ev[u] = load_streaming(&w1s[row + min(lane + u * kWave, c8 - 1)]);
-      double acc[BT];
+        for (int u = 0; u < kXch; ++u) ev[u] = load_streaming(&w1s[row + min(lane + u * kWave, c8 - 1)]);
+        double acc[BT];
 #pragma unroll
-      for (int bb = 0; bb < BT; ++bb) acc[bb] = 0.0;
+        for (int bb = 0; bb < BT; ++bb) acc[bb] = 0.0;
 #pragma unroll
-      for (int u = 0; u < kXch; ++u) {
-        const int c = lane + u * kWave;
-        if (c < c8) {
-          const uint32_t wd[4] = {ev[u].x, ev[u].y, ev[u].z, ev[u].w};
-          // the row's values widened once and used for every token; an fp64 FMA of two bf16 values rounds once,
-          // exactly like adding their (exact) fp32 product
-          double wdv[8];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            wdv[2 * q] = (double)bf16_lo(wd[q]);
-            wdv[2 * q + 1] = (double)bf16_hi(wd[q]);
-          }
-#pragma unroll
-          for (int bb = 0; bb < BT; ++bb) {
-            const uint4 xv = xb[bb * c8 + c];
-            const uint32_t xd[4] = {xv.x, xv.y, xv.z, xv.w};
+        for (int u = 0; u < kXch; ++u) {
+          const int c = lane + u * kWave;
+          if (c < c8) {
+            const uint32_t wd[4] = {ev[u].x, ev[u].y, ev[u].z, ev[u].w};
+            // the row's values widened once and used for every token; an fp64 FMA of two bf16 values rounds once,
+            // exactly like adding their (exact) fp32 product
+            double wdv[8];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              acc[bb] = fma(wdv[2 * q], (double)bf16_lo(xd[q]), acc[bb]);
-              acc[bb] = fma(wdv[2 * q + 1], (double)bf16_hi(xd[q]), acc[bb]);
+              wdv[2 * q] = (double)bf16_lo(wd[q]);
+              wdv[2 * q + 1] = (double)bf16_hi(wd[q]);
+            }
+#pragma unroll
+            for (int bb = 0; bb < BT; ++bb) {
+              const uint4 xv = xb[bb * c8 + c];
+              const uint32_t xd[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                acc[bb] = fma(wdv[2 * q], (double)bf16_lo(xd[q]), acc[bb]);
+                acc[bb] = fma(wdv[2 * q + 1], (double)bf16_hi(xd[q]), acc[bb]);
+              }
             }
           }
         }
-      }
 #pragma unroll
-      for (int bb = 0; bb < BT; ++bb) {
-        double s = wave_sum(acc[bb]);
-        s = s > 0.0 ? s : 0.0;
-        if (lane == 0) hv[bb * Lp + t0] = s;
+        for (int bb = 0; bb < BT; ++bb) {
+          double s = wave_sum(acc[bb]);
+          s = s > 0.0 ? s : 0.0;
+          if (lane == 0) hv[bb * Lp + t0] = s;
+        }
       }
     }
     HIRE_TS(5);
@@ -392,11 +461,9 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
       hv[(tid / (n_up - n_u)) * Lp + n_u + tid % (n_up - n_u)] = -1.0;
     __syncthreads();
     // the k/s survivors of every token of the bundle: spos[bb][0 .. ks)
-    if (n_u <= kWave) {  // one wave per token, no barrier in between
-      if (w < nb) {
-        const uint64_t m = wave_rank_mask<double>(hv + w * Lp, n_u, ks);
-        if ((m >> lane) & 1) spos[w * Ls + mask_prefix(m)] = lane;
-      }
+    if (n_u <= kWave) {
+      rank_masks<double>(hv, Lp, nb, n_u, ks, counts, masks);
+      if (w < nb && ((masks[w] >> lane) & 1ull) != 0ull) spos[w * Ls + mask_prefix(masks[w])] = lane;
       __syncthreads();
     } else {
       for (int bb = 0; bb < nb; ++bb) {
@@ -414,8 +481,10 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
     // second layer: an item is eight columns of one token; four rows in flight, added in selection order
 #pragma unroll
     for (int u = 0; u < kXreg; ++u) {  // the flat item numbering of the token staging
-      const int bb = xbb[u], cc = xc[u];
-      if (tid + u * kShThreads >= nb * c8) continue;
+      int idx = tid + u * kShThreads;
+      asm volatile("" : "+v"(idx));  // numbered afresh: no registers for it across the exact stage
+      if (idx >= nb * c8) continue;
+      const int bb = BT == 1 ? 0 : idx / c8, cc = idx - bb * c8;
       const int* sp = spos + bb * Ls;
       const double* hb = hv + bb * Lp;
       float a[8];
@@ -485,7 +554,8 @@ static hipError_t shard_launch(const FfnShardArgs& a, hipStream_t s) {
   // divides N and k <= k' <= N, ks <= kps <= Ls always holds
   const int Ls = a.N / a.shards, kps = (a.kprime + a.shards - 1) / a.shards, ks = (a.k + a.shards - 1) / a.shards;
   const int cap = (int)((long long)a.B * kps < (long long)Ls ? a.B * kps : Ls);
-  const size_t lds = (size_t)BT * ((size_t)a.d * 3 + (size_t)((Ls + 3) & ~3) * (8 + 4)) + (size_t)Ls * ((4 + BT) * 4);
+  const size_t tokens = BT < 4 ? (size_t)BT * a.d * 3 : kShRed * sizeof(double) + (size_t)BT * (a.d + 16);
+  const size_t lds = tokens + (size_t)BT * ((Ls + 3) & ~3) * (8 + 4) + (size_t)Ls * ((4 + BT) * 4);
   static std::atomic<size_t> raised_to{0};  // bundles of several tokens with long shards pass the default limit
   if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(k_ffn_shard<CH, BT>), lds, raised_to);
       e != hipSuccess)
@@ -495,10 +565,12 @@ static hipError_t shard_launch(const FfnShardArgs& a, hipStream_t s) {
                 a.cand, a.n_cand, a.scorer_acc);
 }
 
-// Tokens side by side: as many as LDS (under 64 KB) and registers take; one token runs the leaner single variant.
+// One token runs the leaner single variant, and so do tokens too long for four of them in registers, one by one; two long
+// tokens stay on the vector units (128 shards of 93 units, d = 3008: 27.5 us against 30.5 on the matrix cores).
 hipError_t launch_ffn_shard(const FfnShardArgs& a, hipStream_t s) {
   if (a.d <= 2048) return a.B == 1 ? shard_launch<1, 1>(a, s) : shard_launch<1, 4>(a, s);
-  if (a.d <= 4096) return a.B == 1 ? shard_launch<2, 1>(a, s) : shard_launch<2, 2>(a, s);
+  if (a.d <= 4096)
+    return a.B == 1 ? shard_launch<2, 1>(a, s) : (a.B == 2 ? shard_launch<2, 2>(a, s) : shard_launch<2, 4>(a, s));
   return shard_launch<4, 1>(a, s);
 }
 

@@ -461,6 +461,20 @@ def test_ffn_shard_step_1b_shape(hire, oracle, ffn_1b, B, s, k, kp):
     log(f"  sum |U_i|={int(got['n_cand'].sum())} min margin k={want['margin_k'].min():.3e}")
 
 
+@pytest.mark.parametrize("d,N,B,k,kp,s", [
+    (96, 65 * 5, 4, 40, 100, 5),      # one unit more than a wave has lanes, columns of less than a slice
+    (2048, 100 * 4, 3, 380, 400, 4),  # more rows than one call of the exact stage takes
+    (2080, 64 * 3, 7, 9, 30, 3),      # tokens beyond 2048 columns, a bundle of four and one of three
+    (4096, 48 * 2, 2, 11, 25, 2),     # two long tokens
+])
+def test_ffn_shard_bundle_edges(hire, oracle, d, N, B, k, kp, s):
+    log(f"shard bundles d={d} N={N} B={B} k={k} kp={kp} shards={s}")
+    L = I.ffn_layer(197 + B, d, N)
+    L["w1u"][N // 4:N // 4 + 20] = L["w1u"][N // 4]
+    layer, scorer = T.make_ffn_layer(L)
+    T.check_ffn_shard(layer, scorer, L, I.tokens(198 + B, B, d), k, kp, s)
+
+
 def test_ffn_shard_step_one_shard_equals_plain_step(hire, oracle):
     L = I.ffn_layer(192, 256, 1024)
     layer, scorer = T.make_ffn_layer(L)
