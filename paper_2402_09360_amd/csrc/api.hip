@@ -592,6 +592,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     rp.bitmap = s.bitmap;
     if (cand_idx != nullptr || n_cand != nullptr) {
       rp.cand_out = cand_idx != nullptr ? cand_idx : s.cand;
+      rp.cand_cap = s.cap_u;
       rp.n_cand_out = n_cand;
     }
     rp.h64 = s.h64;

@@ -9,8 +9,8 @@
 // Both are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
 // count per thread times 16 cycles (four waves share a SIMD), so what counts is the number of sections and of passes
 // over the register-resident row.  The window histogram (fast_select.h) is anchored at an a-priori bound of the
-// row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves, so the
-// number of entries above the bin it proposes is exact and no counting pass confirms it.
+// row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves.  It only
+// proposes a bin: what lies above is counted from the masks that the pass over the registers leaves.
 #include "fast_select.h"
 #include "kernels.h"
 
@@ -25,10 +25,10 @@ struct BatchKeys {
 };
 
 // Window histogram of the registers' values below `anchor` (zeros are never counted) and the bin that holds the k-th
-// largest.  false: fewer than k values in the window.  *bin: that bin; *above: the values in higher bins.
+// largest of those.  false: fewer than k values in the window.  *bin: that bin.
 template <typename Keys>
 __device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int k, uint32_t* win,
-                                           SelSharedT<kSelThreads>& sh, uint32_t* bin, int* above) {
+                                           SelSharedT<kSelThreads>& sh, uint32_t* bin) {
 #pragma unroll
   for (int e = 0; e < (int)(sizeof(kr.r) / sizeof(kr.r[0])); ++e)
 #pragma unroll
@@ -41,7 +41,6 @@ __device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int 
   wr.issue(win);
   const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
   *bin = anchor - (uint32_t)wk.slot;
-  *above = wk.above;
   return wk.found && *bin >= 1u && *bin <= anchor;  // uniform
 }
 
@@ -76,20 +75,22 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
   __syncthreads();
   HIRE_TS(11);
   uint32_t bin;
-  int above;
-  bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above);
+  bool known = window_bin(kr, anchor, kprime, win, sh, &bin);
   HIRE_TS(12);
   uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
   if (known) {
     const BinMasks<uint32_t> bm = bin_masks<uint32_t>(kr, bin_floor<uint32_t>(bin), bin_floor<uint32_t>(bin + 1u));
     list_inside<uint32_t>(kr, bm.inside, &sh.list_n, list);
+    // What lies above the bin is counted from the keys themselves: scales that do not belong to the codes would put keys
+    // above the anchor, where the window does not count them.
+    const int above = wave_sum(__popc(bm.above));
+    if (lane == 0) wave_cnt[wave_id()] = above;
     __syncthreads();
     HIRE_TS(13);
-    const int m = sh.list_n;
-    known = m <= kFastAmbCap;  // uniform
+    const int m = sh.list_n, need = kprime - wave_sum(lane < kSelWaves ? wave_cnt[lane] : 0);
+    known = m <= kFastAmbCap && need >= 1 && need <= m;  // uniform
     if (known)
-      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
-                                      kprime - above);
+      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m, need);
     HIRE_TS(14);
   }
   if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
   const int N = p.N, k = p.k, d = p.d;
   if (b == p.B) {  // one more workgroup lists the candidates meanwhile
-    const int n = list_bitmap<kSelThreads>(p.bitmap, (N + 31) / 32, p.cand_out, L.sh);
+    const int n = list_bitmap<kSelThreads>(p.bitmap, (N + 31) / 32, p.cand_out, p.cand_cap, L.sh);
     if (tid == 0 && p.n_cand_out) *p.n_cand_out = n;
     return;
   }
@@ -288,10 +289,8 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   const double hw = 2.0 * (double)p.err_c * (double)xn * (double)wn * 1.000001;
   HIRE_TS(41);
   uint32_t bin;
-  int above_bin;
-  const bool found = window_bin(kr, anchor, k, L.win, L.sh, &bin, &above_bin);
+  const bool found = window_bin(kr, anchor, k, L.win, L.sh, &bin);
   HIRE_TS(42);
-  (void)above_bin;  // the band's own counts decide
   if (found) {  // uniform
     const double f = (double)__uint_as_float(bin << kFineShift), c = (double)__uint_as_float((bin + 1u) << kFineShift);
     const double lo_v = f - hw, hi_v = c + hw;

@@ -441,9 +441,9 @@ __device__ __forceinline__ void fast_emit(const KeyRegs<K, LOADS, NT, FR>& kr, c
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Selection of the `need` largest keys where their threshold bin is known.  A window histogram holds integer counts of
-// every positive key, all keys at or below its anchor, so it is exact and the walk gives that bin and the number of keys
-// above it: only the bin's own few keys (`list`, 64 at most) have to be compared, and no pass counts what lies above.
+// Selection of the `need` largest keys where their threshold bin and the number of keys above it are known, from a window
+// histogram in memory that is exact whenever it is used (ffn_fast.h says how) or from the masks below: only the bin's own
+// few keys (`list`, 64 at most) have to be compared.
 template <typename K>
 struct BinList {
   K key[kFastAmbCap];

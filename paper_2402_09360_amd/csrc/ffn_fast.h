@@ -7,8 +7,15 @@
 
 namespace hire {
 
-// State of the route at the head of every workspace, one region per token.  The histograms of the keys have to be zero
-// when a step starts; the step's last kernel leaves them so and says in the first region how many regions are clean.
+// State of the route at the head of every workspace, one region per token.  The consumers of a window histogram take
+// its counts for the keys' own, so it has to be exact whenever it is used.  Two things see to that:
+//  * The histograms of the keys are zero when a step that uses them starts.  The step's first kernel takes the cookie
+//    away, leaving the number of clean regions in `clean` for the kernels that follow, and the last one, which clears the
+//    histograms, gives it back: a step that ends in between (a launch that the runtime refused) leaves no cookie behind,
+//    and the next step selects without histograms.
+//  * The anchors bound every key and activation.  Should one lie above its anchor all the same (row-norm bounds of other
+//    weights, scales that do not belong to the codes), it would be missing from the counts: whoever meets it says so in
+//    `beyond1` / `beyond2`, and the selection goes by the keys alone.
 constexpr unsigned long long kCookie = 0x48695245464e4f00ull;  // + the number of clean regions
 
 struct FastRegion {
@@ -18,17 +25,36 @@ struct FastRegion {
                              // gathering kernel, with need1 the keys of that bin that are selected
   uint32_t anchor1, anchor2; // top bins of the two windows for the running step, written by the scorer kernel
   uint32_t need1;
+  uint32_t clean;            // first region: regions whose key histograms were zero when the running step started
+  uint32_t beyond1, beyond2; // not 0: a key (an activation) of the running step lies above its anchor
+  uint32_t spare;
   uint32_t zeros[8];         // stays zero: what lanes beyond the end of a key array load
-  uint32_t pad[48];
+  uint32_t pad[44];
   uint32_t hist1[kWin];      // slot s: scorer keys in fine bin anchor1 - s
   uint32_t hist2[kWin];      // slot s: activations in fine bin anchor2 - s
 };
-static_assert(offsetof(FastRegion, zeros) == 32 && offsetof(FastRegion, hist1) == 256, "region layout");
+static_assert(offsetof(FastRegion, zeros) % 16 == 0 && offsetof(FastRegion, hist1) == 256, "region layout");
 static_assert(sizeof(FastRegion) == kFastRegionBytes, "region size");
 
-__device__ __forceinline__ int clean_regions(const FastRegion* first) {
-  const unsigned long long n = first->cookie - kCookie;
-  return n <= (unsigned long long)kFastTokens ? (int)n : 0;
+// By one thread of a step's first kernel, with the cookie as it was found (asked for early: a round trip to memory): if
+// there is one, it is taken away.
+__device__ __forceinline__ void take_cookie(FastRegion* first, unsigned long long cookie) {
+  const unsigned long long n = cookie - kCookie;
+  first->clean = n <= (unsigned long long)kFastTokens ? (uint32_t)n : 0u;
+  first->cookie = 0ull;
+}
+// By a step's last kernel, which clears the key histograms of the step's B tokens.
+__device__ __forceinline__ void give_cookie(FastRegion* first, int clean, int B) {
+  first->cookie = kCookie + (unsigned long long)max(clean, B);
+}
+
+// Counts a key (its IEEE bits) in the window below the anchor; zeros are never counted.
+template <typename K>
+__device__ __forceinline__ void count_in_window(K bits, uint32_t anchor, uint32_t* hist, uint32_t* beyond) {
+  const uint32_t bin = fine_bin(bits), slot = anchor - bin;
+  if (bits == (K)0) return;
+  if (slot < (uint32_t)kWin) atomicAdd(&hist[slot], 1u);
+  else if (bin > anchor) *beyond = 1u;
 }
 
 constexpr int kOwnUnits = 64;  // units of a workgroup of the gathering kernels

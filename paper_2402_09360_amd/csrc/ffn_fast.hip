@@ -34,9 +34,11 @@
 // and are used as integer keys directly.
 //
 // The key histogram must be all zero when a step starts.  The second-layer kernel of every step leaves it so
-// and stamps a cookie into the workspace; on a workspace without the cookie (first use, arbitrary contents) the
-// first selection of one step takes a slower histogram-free route.  The h histogram is cleared by the scorer
-// kernel of the step that uses it.  No kernel waits for, or counts, the workgroups of another.
+// and stamps a cookie into the workspace, which the next step's scorer kernel takes away again; on a workspace without
+// the cookie (first use, arbitrary contents, a step that ended half-way) the first selection of one step takes a slower
+// histogram-free route, and so does a selection whose keys are not all at or below their anchor (ffn_fast.h).  The h
+// histogram is cleared by the scorer kernel of the step that uses it.  No kernel waits for, or counts, the workgroups of
+// another.
 #include "ffn_fast.h"
 
 namespace hire {
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
 
   // token first (loads return in order, and the token is needed first), then the first rows' weights and
   // scales: all of these loads are in flight together
-  const bool hist_ok = clean_regions(fr) > 0;
+  const unsigned long long cookie = fr->cookie;  // (workgroup 0 takes it away)
   const float smax = __uint_as_float(q4[(size_t)N * cpr].x);  // largest row scale, kept behind the codes
   // the window of the activations, filled by the next kernel, starts from zero (its last reader was the step before)
   for (int i = (int)blockIdx.x * kST + tid; i < kWin; i += (int)gridDim.x * kST) fr->hist2[i] = 0u;
@@ -164,17 +166,15 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
   if (blockIdx.x == 0 && tid == 0) {
     fr->anchor1 = anchor1;
     fr->anchor2 = anchor2;
+    fr->beyond2 = 0u;
+    take_cookie(fr, cookie);
   }
   {  // zero padding of the handed-on key array up to a whole 16-byte vector
     float* arr = gkeys != nullptr ? gkeys : keys;
     const int n = gkeys != nullptr ? N / 8 : N;
     if (blockIdx.x == 0 && tid < ((4 - (n & 3)) & 3)) arr[n + tid] = 0.0f;
   }
-  auto count_key = [&](float key) {
-    const uint32_t bits = __float_as_uint(key);
-    const uint32_t slot = anchor1 - fine_bin(bits);  // keys lie at or below the anchor; zeros are never counted
-    if (hist_ok && bits != 0u && slot < (uint32_t)kWin) atomicAdd(&fr->hist1[slot], 1u);
-  };
+  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
 
   const uint4* xq4 = reinterpret_cast<const uint4*>(xq);
   for (int g = gw; g * kRPW < N; g += total_waves) {
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   const int sub = lane % ROW_LANES, rw = lane / ROW_LANES;
   const int cpr = r / 8;
   HIRE_TS(30);
-  const int clean = clean_regions(fr);
+  const unsigned long long cookie = fr->cookie;  // (workgroup 0 takes it away)
   const float umax = bounds[0], zmax = bounds[1];
   for (int i = (int)blockIdx.x * kST + tid; i < B * kWin; i += (int)gridDim.x * kST) fr[i / kWin].hist2[i % kWin] = 0u;
   const int mine = min(w / kWPT, B - 1), lt = w % kWPT * kWave + lane;  // the token this wave prepares
@@ -313,6 +313,8 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
     if (blockIdx.x == 0 && tid == 0 && t < B) {
       fr[t].anchor1 = anchor1[t];
       fr[t].anchor2 = fine_bin(__float_as_uint(bound2));
+      fr[t].beyond2 = 0u;
+      if (t == 0) take_cookie(fr, cookie);
       if (N & 1) keys[t * stride + N] = 0.0;  // zero padding of the handed-on keys up to a whole 16-byte vector
     }
   }
@@ -355,8 +357,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
       if (sub == ROW_LANES - 1 && j < N && t < B) {
         s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
         keys[t * stride + j] = s;
-        const uint32_t slot = anchor1[t] - fine_bin((uint64_t)__double_as_longlong(s));  // at or below the anchor
-        if (t < clean && s > 0.0 && slot < (uint32_t)kWin) atomicAdd(&fr[t].hist1[slot], 1u);  // (never a zero)
+        count_in_window((uint64_t)__double_as_longlong(s), anchor1[t], fr[t].hist1, &fr[t].beyond1);
       }
     }
   }
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   HIRE_TS(10);
   // every load of the selection goes out here, before the first wait
   const int n = p.N >> gs;
-  const bool hist_ok = clean_regions(p.fr) > 0;
+  const bool hist_ok = p.fr->clean > 0u && p.fr->beyond1 == 0u;
   const uint32_t anchor1 = p.fr->anchor1, anchor2 = p.fr->anchor2;
   WinRegs<kGT> wr;
   wr.issue(p.fr->hist1);
@@ -539,10 +540,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   }
   HIRE_TS(13);
   auto count_h = [&](double v) {  // the scorer kernel of this step has cleared the window
-    if (v > 0.0) {
-      const uint32_t slot = anchor2 - fine_bin((uint64_t)__double_as_longlong(v));  // v lies at or below the anchor
-      if (slot < (uint32_t)kWin) atomicAdd(&p.fr->hist2[slot], 1u);
-    }
+    count_in_window((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
   };
   if (!found) __syncthreads();  // the token in LDS
   for (int r = w; r < cnt; r += kGW) {  // uniform over the wave; one trip for most
@@ -679,7 +677,9 @@ __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& 
   __syncthreads();
   const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
   place_taken<Keys>(__brev(take) >> (32 - LK * Keys::PER), w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0,
-                    [&](int at, int e, int q) { p.cand_out[at] = kr.index(e, q); });
+                    [&](int at, int e, int q) {
+                      if (at < p.kprime) p.cand_out[at] = kr.index(e, q);
+                    });
 }
 
 // KEY: the scorer keys' bit patterns (what the candidate list is selected from); LOADS: 16-byte loads of fp32
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   const bool output = (int)blockIdx.x == p.out_block;  // uniform
   if ((int)blockIdx.x == p.list_block && p.B > 1) {
     if (blockIdx.y > 0) return;
-    const int cnt = list_bitmap<kWT>(p.bitmap, (p.n + 31) / 32, p.cand_out, sh);
+    const int cnt = list_bitmap<kWT>(p.bitmap, (p.n + 31) / 32, p.cand_out, min(p.B * p.kprime, p.n), sh);
     if (tid == 0 && p.n_cand) *p.n_cand = cnt;
     return;
   }
@@ -720,7 +720,8 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   const float* u32 = p.u32 + (b * p.entries << p.gs);  // (gs = 3 only)
   HIRE_TS(24);
   const uint32_t anchor2 = fr->anchor2;
-  const int clean = clean_regions(p.fr);  // (asked for here: at the end its latency would count)
+  const bool whole = fr->beyond2 == 0u;     // the window counts every activation that it should
+  const int clean = (int)p.fr->clean;       // (asked for here: at the end its latency would count)
   WinRegs<kWT> wr;
   wr.issue(fr->hist2);
   Keys kr;
@@ -741,7 +742,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   const WinWalk wk = walk_window<kWT>(wr, p.k, sh);
   HIRE_TS(20);
   const uint32_t bin = anchor2 - (uint32_t)wk.slot;
-  const bool found = wk.found && bin >= 1u && bin <= anchor2;  // uniform
+  const bool found = whole && wk.found && bin >= 1u && bin <= anchor2;  // uniform
   uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
   bool known = false;
   if (found) {
@@ -828,6 +829,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     static_assert(sizeof(red) >= 2048 * sizeof(int), "2048 groups of eight at most");
     place_taken<Keys>(ordered, run, [&](int at, int e, int q) {
       const int i = kr.index(e, q);
+      if (at >= p.k) return;  // (never; but whatever the workspace holds, nothing is written past the token's row)
       if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
       if (gs != 0) places[at] = i;
       else if (p.topk_val) p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
@@ -921,7 +923,10 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   // The key histogram has served its purpose: the workgroups clear it between them and say so in the
   // cookie (the same value from each; the next kernel that looks at either starts after this one has ended).
   for (int i = (int)blockIdx.x * kWT + tid; i < kWin; i += p.col_slices * kWT) fr->hist1[i] = 0u;
-  if (tid == 0) p.fr->cookie = kCookie + (unsigned long long)max(clean, p.B);
+  if (tid == 0) {
+    fr->beyond1 = 0u;
+    give_cookie(p.fr, clean, p.B);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------

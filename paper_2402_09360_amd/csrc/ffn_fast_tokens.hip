@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int B = p.B, N = p.N, d = p.d;
   const int cpr = d / 32, xstride = d / 16 + 1;
-  const int clean = clean_regions(p.fr);
+  const unsigned long long cookie = p.fr->cookie;  // (workgroup 0 takes it away)
   const float smax = __uint_as_float(p.q4[(size_t)N * cpr].x);  // largest row scale, kept behind the codes
   // the windows of the activations, filled by the next kernel, start from zero
   for (int i = (int)blockIdx.x * kTT + tid; i < B * kWin; i += (int)gridDim.x * kTT)
@@ -143,6 +143,8 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
   if (here && blockIdx.x == 0 && lane == 0) {
     fr->anchor1 = anchor1;
     fr->anchor2 = anchor2;
+    fr->beyond2 = 0u;
+    if (b == 0) take_cookie(p.fr, cookie);
   }
 
   constexpr int kTok4 = TT / 4;
@@ -183,11 +185,7 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
     if (p.gkeys != nullptr) lds_barrier();
     return;
   }
-  auto count_key = [&](float key) {
-    const uint32_t bits = __float_as_uint(key);
-    const uint32_t slot = anchor1 - fine_bin(bits);  // keys lie at or below the anchor; zeros are never counted
-    if (b < clean && bits != 0u && slot < (uint32_t)kWin) atomicAdd(&fr->hist1[slot], 1u);
-  };
+  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
   const int j = (int)blockIdx.x * kTokRows + lane;
   int sum = 0;
 #pragma unroll
@@ -316,9 +314,10 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   uint64_t rows = 0ull;          // units of the workgroup that any token shortlists
   if (sparse) {
     const int n = p.N >> gs;
-    const int clean = clean_regions(p.fr);
+    const int clean = (int)p.fr->clean;
     uint4 wr[kMine];
     const int tw = w / kWPT, wt = w % kWPT;  // the token whose window this wave helps to walk, its part of it
+    const bool hist_ok = tw < clean && p.fr[min(tw, B - 1)].beyond1 == 0u;
     {
       const uint4* hist = reinterpret_cast<const uint4*>(p.fr[min(tw, B - 1)].hist1);
 #pragma unroll
@@ -348,7 +347,7 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
     {
       const int v = lane < kChunks ? chunk_sum[tw][lane] : 0, incl = wave_scan_incl(v);
       const uint64_t at = __ballot(lane < kChunks && incl - v < p.kprime && p.kprime <= incl);
-      if (at != 0ull && tw < clean) {  // uniform; tokens without a clean histogram have no slot
+      if (at != 0ull && hist_ok) {  // uniform; tokens without an exact histogram have no slot
         const int q = __builtin_ctzll(at), run0 = __builtin_amdgcn_readlane(incl - v, q);
 #pragma unroll
         for (int u = 0; u < kMine; ++u)
@@ -454,10 +453,7 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   HIRE_TS(13);
   auto count_h = [&](int t, double v) {  // the scorer kernel of this step has cleared the windows
-    if (v > 0.0) {
-      const uint32_t sl = p.fr[t].anchor2 - fine_bin((uint64_t)__double_as_longlong(v));  // v is at or below the anchor
-      if (sl < (uint32_t)kWin) atomicAdd(&p.fr[t].hist2[sl], 1u);
-    }
+    count_in_window((uint64_t)__double_as_longlong(v), p.fr[t].anchor2, p.fr[t].hist2, &p.fr[t].beyond2);
   };
   if (sparse && gs == 0 && w < B && ((rows >> lane) & 1ull) == 0ull) {
     p.h32[(size_t)w * p.entries + u0 + lane] = 0.0f;

@@ -214,7 +214,8 @@ struct RefineParams {
   int wnorm_n;
   float err_c;
   const uint32_t* bitmap;   // the candidates; they are listed as well: ascending, and their number
-  int32_t* cand_out;        // optional
+  int32_t* cand_out;        // optional; cand_cap entries fit
+  int cand_cap;
   int32_t* n_cand_out;      // optional (with cand_out)
   double* h64;              // [B, stride] scratch
   int32_t* idx_out;         // optional [B, k] ascending

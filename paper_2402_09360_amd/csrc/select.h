@@ -315,9 +315,9 @@ __device__ __forceinline__ int union_locate(const uint32_t* __restrict__ bitmap,
       out_sh);
 }
 
-// The set bits of a bitmap as an ascending list, by one workgroup (NT threads, words <= 16 NT).
+// The set bits of a bitmap as an ascending list of at most cap entries, by one workgroup (NT threads, words <= 16 NT).
 template <int NT>
-__device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, int words, int32_t* __restrict__ out,
+__device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, int words, int32_t* __restrict__ out, int cap,
                                            SelSharedT<NT>& sh) {
   const int tid = (int)threadIdx.x;
   int base = 0;
@@ -334,7 +334,7 @@ __device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, 
     int at = base + wg_scan_incl<NT>(cnt, sh, &total) - cnt;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      for (uint32_t mm = m[j]; mm != 0u; mm &= mm - 1u) out[at++] = (w0 + tid * 4 + j) * 32 + __builtin_ctz(mm);
+      for (uint32_t mm = m[j]; mm != 0u && at < cap; mm &= mm - 1u) out[at++] = (w0 + tid * 4 + j) * 32 + __builtin_ctz(mm);
     base += total;
   }
   return base;

@@ -1,0 +1,123 @@
+"""Steps on workspaces and layers that are not as the step before would have left them: a step that the runtime refused
+half-way, row-norm bounds and row scales that do not fit the layer.  The window histograms that guide the selections of
+one to eight tokens live in the workspace and are placed by bounds of the keys: neither may decide what is selected, only
+how fast.  Integers bit for bit, floats to the parity tests' bar."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import hire_testlib as T
+from paper_2402_09360_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+ELAUNCH = -4
+
+
+@pytest.fixture(scope="module")
+def hire():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2402_09360_amd import hire as H
+    return H
+
+
+def log(msg):
+    print(msg, flush=True)
+
+
+def _end_after(hire, kernels, step):
+    """Runs the step with an event array that makes it end behind its first `kernels` stages: the event that is recorded
+    there does not exist, which the runtime refuses on the host.  What was enqueued before runs to its end."""
+    from paper_2402_09360_amd.hiprt import Events, hip
+    ev = Events(hire.NUM_STAGE_EVENTS)
+    holes = (C.c_void_p * hire.NUM_STAGE_EVENTS)()
+    for i in range(kernels):
+        holes[i] = ev.array[i]
+    hire.hire_set_stage_events(holes)
+    try:
+        with pytest.raises(hire.HireError) as e:
+            step()
+        assert e.value.code == ELAUNCH
+    finally:
+        hire.hire_set_stage_events(None)
+        hip().hipGetLastError()
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("route,B", [("int4", 1), ("int4", 3), ("lowrank", 1), ("lowrank", 4), ("lrq", 1), ("lrq", 2),
+                                     ("groups", 1), ("groups", 8)])
+def test_step_after_one_that_ended_half_way(hire, oracle, route, B):
+    """The kernels that ran have counted keys which nobody has cleared: the next step must not take them for its own."""
+    d, N, k, kp = 256, 1504, 64, 304
+    L = I.ffn_layer(301, d, N) if route in ("int4", "groups") else I.lowrank_ffn_layer(302, d, N, 64)
+    layer, scorer = T.make_ffn_layer(L, lowrank=route == "lowrank", lrq=route == "lrq")
+    groups = route == "groups"
+    ws = hire.alloc_workspace(hire.hire_ffn_group_workspace_bytes(layer, B, k, kp, 8) if groups else
+                              hire.hire_ffn_workspace_bytes(layer, B, k, kp))
+
+    def step(x, steps=1):
+        if groups:
+            return T.run_ffn_group(layer, x, k, kp, 8, ws=ws, steps=steps, debug=False)
+        return T.run_ffn(layer, x, k, kp, ws=ws, steps=steps, debug=False)
+
+    step(I.tokens(303, B, d), steps=2)                       # the workspace's steady state
+    assert hire.hire_debug_fast_state(ws)[0] == 1
+    for kernels in (1, 2):
+        log(f"{route} B={B}: ends after {kernels} of its stages")
+        _end_after(hire, kernels, lambda: step(I.tokens(304, B, d)))
+        assert hire.hire_debug_fast_state(ws)[0] == 0        # no marker: the counts in the workspace are nobody's
+        x = I.tokens(305 + kernels, B, d)
+        if groups:
+            want = oracle.ffn_group_step(L["w1u"], L["w2u"], scorer, x, k, kp, 8)
+        else:
+            want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
+        for got in step(x, steps=3):
+            assert np.array_equal(got["cand"], want["cand"])
+            name = "topk_group" if groups else "topk_idx"
+            assert np.array_equal(got[name], want[name])
+            T.assert_float_close(got["topk_val"], want["topk_val"], "topk_val")
+            T.assert_float_close(got["y"], want["y"], "y")
+        assert hire.hire_debug_fast_state(ws)[:2] == (1, 0)
+
+
+@pytest.mark.parametrize("kind", ["lowrank", "lrq"])
+@pytest.mark.parametrize("B", [1, 3])
+def test_row_norm_bounds_only_place_the_histograms(hire, oracle, kind, B):
+    """Bounds of another layer: from a little too small, so that a few of the keys lie above the window, to useless."""
+    d, N, r, k, kp = 256, 1200, 32, 50, 200
+    L = I.lowrank_ffn_layer(311, d, N, r)
+    layer, scorer = T.make_ffn_layer(L, lowrank=kind == "lowrank", lrq=kind == "lrq")
+    right = layer.row_norm_bounds.clone()
+    x = I.tokens(312, B, d)
+    want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
+    slow = 0
+    for factor in (1.0, 0.5, 0.3, 0.2, 0.1, 2.0 ** -6, 2.0 ** -20, 0.0, 2.0 ** 20):
+        layer.row_norm_bounds.copy_(right * factor)
+        torch.cuda.synchronize()
+        ws = hire.alloc_workspace(hire.hire_ffn_workspace_bytes(layer, B, k, kp))
+        for got in T.run_ffn(layer, x, k, kp, steps=3, ws=ws):
+            assert np.array_equal(got["cand"], want["cand"]), factor
+            assert np.array_equal(got["topk_idx"], want["topk_idx"]), factor
+            T.assert_float_close(got["topk_val"], want["topk_val"], "topk_val")
+            T.assert_float_close(got["y"], want["y"], "y")
+        keys, activations = hire.hire_debug_fast_fallbacks(ws)
+        log(f"{kind} B={B} bounds times {factor}: selections without a histogram {keys}, {activations}")
+        slow += keys + activations
+    assert slow > 0
+
+
+@pytest.mark.parametrize("B", [1, 4, 8, 20])
+def test_row_scales_above_the_packed_maximum(hire, oracle, B):
+    """The codes carry the largest row scale, which bounds the keys; row scales that are larger than that put keys above
+    the bound.  They are ranked as what they are."""
+    d, N, k, kp = 128, 2000, 60, 400
+    L = I.ffn_layer(321, d, N)
+    layer, (kind, q, s) = T.make_ffn_layer(L)
+    factor = np.ones(N, dtype=np.float32)
+    factor[5::37] = 8.0
+    layer.q4_scale.mul_(torch.from_numpy(factor).cuda())
+    torch.cuda.synchronize()
+    log(f"row scales above the maximum, B={B}")
+    T.check_ffn(layer, (kind, q, s * factor), L, I.tokens(322 + B, B, d), k, kp)
