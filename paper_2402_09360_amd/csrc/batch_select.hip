@@ -6,7 +6,8 @@
 //                  in unit order), recomputing in fp64 what lies around the threshold -> indices, values and the
 //                  (row, coefficient) list of the second layer
 //
-// Both are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
+// and, where the values are to be rounded from 64 bits and not only selected by them, k_exact_values over the list.
+// The selections are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
 // count per thread times 16 cycles (four waves share a SIMD), so what counts is the number of sections and of passes
 // over the register-resident row.  The window histogram (fast_select.h) is anchored at an a-priori bound of the
 // row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves.  It only
@@ -413,6 +414,73 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------------
+// The activations of the selected (token, unit) pairs once more, in fp64 and rounded once: k_refine leaves the filter
+// stage's fp32 values outside the band around the threshold, up to 2.3 half ulps off where one rounding is 1.0 at most
+// (mean 0.39 to 0.50 against 0.34).  Two rows per wave, up to eight loads of a lane in flight.  A die takes an eighth of
+// the (entries, token) pairs, entries first: neighbours in the lists are neighbours among the units, so that what tokens
+// share comes from its L2.
+constexpr int kEvThreads = 256;
+constexpr int kEvRows = 2;                                  // of a wave
+constexpr int kEvEntries = kEvThreads / kWave * kEvRows;    // of a workgroup
+struct ExactValuesParams {
+  uint2* list;        // [B, k] (unit, value)
+  float* val_out;     // optional [B, k]
+  const uint16_t* W;  // bf16 [N, d]
+  const uint16_t* x;  // bf16 [B, d]
+  int B, k, d;
+};
+__global__ __launch_bounds__(kEvThreads) void k_exact_values(ExactValuesParams p) {
+  const int chunks = (p.k + kEvEntries - 1) / kEvEntries, n_items = chunks * p.B;
+  const int item = (int)(blockIdx.x & 7) * ((n_items + 7) / 8) + (int)(blockIdx.x >> 3);
+  if (item >= n_items) return;  // uniform: the last dies' shares may be short
+  const int b = item % p.B, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int e0 = item / p.B * kEvEntries + w * kEvRows, cpr = p.d / 8;
+  if (e0 >= p.k) return;
+  uint2* list = p.list + (size_t)b * p.k;
+  const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * p.d);
+  const uint4* row[kEvRows];
+#pragma unroll
+  for (int u = 0; u < kEvRows; ++u) row[u] = reinterpret_cast<const uint4*>(p.W + (size_t)list[min(e0 + u, p.k - 1)].x * p.d);
+  double acc[kEvRows][2];
+#pragma unroll
+  for (int u = 0; u < kEvRows; ++u) acc[u][0] = acc[u][1] = 0.0;
+#pragma nounroll
+  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
+    uint4 wv[kEvRows][4], xv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int c = min(c0 + v * kWave + lane, cpr - 1);
+#pragma unroll
+      for (int u = 0; u < kEvRows; ++u) wv[u][v] = row[u][c];
+      xv[v] = tok[c];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (c0 + v * kWave + lane < cpr) {
+        const uint32_t xd[4] = {xv[v].x, xv[v].y, xv[v].z, xv[v].w};
+#pragma unroll
+        for (int u = 0; u < kEvRows; ++u) {
+          const uint32_t wd[4] = {wv[u][v].x, wv[u][v].y, wv[u][v].z, wv[u][v].w};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[u][0] += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
+            acc[u][1] += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
+          }
+        }
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < kEvRows; ++u) {
+    const double s = wave_sum(acc[u][0] + acc[u][1]);
+    const float v = (float)(s > 0.0 ? s : 0.0);  // ReLU, and -0 -> +0
+    if (lane == 0 && e0 + u < p.k) {
+      list[e0 + u].y = __float_as_uint(v);
+      if (p.val_out) p.val_out[(size_t)b * p.k + e0 + u] = v;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
 bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k <= kWin / 2; }
 
 hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
@@ -425,6 +493,12 @@ hipError_t launch_keys_select(const float* keys, long long stride, int B, int N,
                 window_misses);
 }
 
+static hipError_t launch_exact_values(const RefineParams& p, hipStream_t s) {
+  const ExactValuesParams q{p.list_out, p.val_out, p.W, p.x, p.B, p.k, p.d};
+  const int items = (p.k + kEvEntries - 1) / kEvEntries * p.B;
+  return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, q);
+}
+
 hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
   if (!batch_select_supported(p.N, p.k) || p.stride % 4 != 0 || reinterpret_cast<uintptr_t>(p.vals) % 16 != 0 || p.d % 8 != 0)
     return hipErrorInvalidValue;
@@ -435,7 +509,8 @@ hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
       return e;
     return launch(kernel, dim3(p.B + (p.cand_out != nullptr ? 1 : 0)), dim3(kSelThreads), lds, s, p);
   };
-  return p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
+  const hipError_t e = p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
+  return e == hipSuccess && p.exact_values ? launch_exact_values(p, s) : e;
 }
 
 }  // namespace hire

@@ -221,6 +221,7 @@ struct RefineParams {
   int32_t* idx_out;         // optional [B, k] ascending
   float* val_out;           // optional [B, k]
   uint2* list_out;          // [B, k] (unit, value) for launch_w2_list
+  int exact_values;         // != 0: all values are rounded from fp64, not only those around the threshold
   uint32_t* window_misses;  // optional counter: tokens that the histogram and the list in LDS did not settle
 };
 hipError_t launch_refine(const RefineParams& p, hipStream_t s);
