@@ -24,7 +24,7 @@ constexpr int kSingleWgMaxRow = 32768;  // up to this row length one workgroup p
 constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the gather run on the matrix cores
 // FFN step, rows of at most 32768 units: filter and refine from kFilterMinBatch tokens on.  Up to four tokens are one tile
 // of the fp64 matrix cores (d = 512, 20003 units: 38 / 39 / 41 us for 2 / 3 / 4 tokens against 46 / 47 / 48; five: 43
-// against 49 there, but 58 against 54 at d = 2048 with 16384 units and 40 against 37 at d = 800 with 5003).  From
+// against 49 there, but 58 against 53 at d = 2048 with 16384 units and 40 against 36 at d = 800 with 5003).  From
 // kFilterValuesMinBatch on values of the filter stage may be handed out (hire_ffn_step says which).
 constexpr int kFilterMinBatch = 5;
 constexpr int kFilterValuesMinBatch = 16;
@@ -608,8 +608,8 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     // Which values are handed out.  From 16 tokens on, with unions of 1025 to 16384 units (an even number), the filter
     // stage's fp32 sums, up to 2.3 half ulps off, have been the result since that stage exists, and forming all B k of
     // them once more would cost most there (64 tokens at the ~1B shape: 215 MB of rows).  Everywhere else callers have
-    // had activations formed in fp64 and rounded once: 8 tokens at the ~1B shape 59.3 us per step, against 51.6 with the
-    // filter's values and 65.5 with the fp64 stage; 33 tokens of d = 800, 5003 units 47.6, 41.7 and 54.5.
+    // had activations formed in fp64 and rounded once: 8 tokens at the ~1B shape 57.7 us per step, against 51.6 with the
+    // filter's values and 65.5 with the fp64 stage; 33 tokens of d = 800, 5003 units 47.0, 41.7 and 54.5.
     rp.exact_values = !(B >= kFilterValuesMinBatch && s.cap_u > 1024 && s.cap_u <= 16384 && s.cap_u % 2 == 0);
     rp.window_misses = s.window_misses;
     HIRE_TRY(launch_refine(rp, st));

@@ -121,7 +121,9 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.
+// fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.  AHEAD: the token is
+// not in LDS, its loads go out with the row's.
+template <bool AHEAD = false>
 __device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row, const uint4* tok, int d) {
   const int cpr = d / 8, lane = lane_id();
   const uint4* r4 = reinterpret_cast<const uint4*>(row);
@@ -131,10 +133,15 @@ __device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row,
     uint4 wv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) wv[v] = r4[min(c0 + v * kWave + lane, cpr - 1)];
+    uint4 ahead[4];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ahead[v] = tok[min(c0 + v * kWave + lane, cpr - 1)];
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v)
       if (c0 + v * kWave + lane < cpr) {
-        const uint4 xv = tok[c0 + v * kWave + lane];
+        const uint4 xv = AHEAD ? ahead[v] : tok[c0 + v * kWave + lane];
         const uint32_t wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, xd[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -416,68 +423,25 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
 // ---------------------------------------------------------------------------------------------------
 // The activations of the selected (token, unit) pairs once more, in fp64 and rounded once: k_refine leaves the filter
 // stage's fp32 values outside the band around the threshold, up to 2.3 half ulps off where one rounding is 1.0 at most
-// (mean 0.39 to 0.50 against 0.34).  Two rows per wave, up to eight loads of a lane in flight.  A die takes an eighth of
-// the (entries, token) pairs, entries first: neighbours in the lists are neighbours among the units, so that what tokens
-// share comes from its L2.
+// (mean 0.39 to 0.50 against 0.34).  A wave per pair: bound by the round trips list -> row, 5.3 us for 33 tokens with 251
+// units of d = 800 (13 MB), 6.1 for 8 with 819 of 2048 (27 MB); two rows per wave 0.3 to 1.4 us more, four 1 to 2.4.  A die
+// takes an eighth of the (entries, token) pairs, entries first: neighbours in the lists are neighbours among the units, so
+// that what tokens share comes from its L2.
 constexpr int kEvThreads = 256;
-constexpr int kEvRows = 2;                                  // of a wave
-constexpr int kEvEntries = kEvThreads / kWave * kEvRows;    // of a workgroup
-struct ExactValuesParams {
-  uint2* list;        // [B, k] (unit, value)
-  float* val_out;     // optional [B, k]
-  const uint16_t* W;  // bf16 [N, d]
-  const uint16_t* x;  // bf16 [B, d]
-  int B, k, d;
-};
-__global__ __launch_bounds__(kEvThreads) void k_exact_values(ExactValuesParams p) {
-  const int chunks = (p.k + kEvEntries - 1) / kEvEntries, n_items = chunks * p.B;
+constexpr int kEvEntries = kEvThreads / kWave;  // of a workgroup
+__global__ __launch_bounds__(kEvThreads) void k_exact_values(uint2* __restrict__ lists, float* __restrict__ val_out,
+                                                             const uint16_t* __restrict__ W,
+                                                             const uint16_t* __restrict__ x, int B, int k, int d) {
+  const int n_items = (k + kEvEntries - 1) / kEvEntries * B;
   const int item = (int)(blockIdx.x & 7) * ((n_items + 7) / 8) + (int)(blockIdx.x >> 3);
   if (item >= n_items) return;  // uniform: the last dies' shares may be short
-  const int b = item % p.B, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int e0 = item / p.B * kEvEntries + w * kEvRows, cpr = p.d / 8;
-  if (e0 >= p.k) return;
-  uint2* list = p.list + (size_t)b * p.k;
-  const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * p.d);
-  const uint4* row[kEvRows];
-#pragma unroll
-  for (int u = 0; u < kEvRows; ++u) row[u] = reinterpret_cast<const uint4*>(p.W + (size_t)list[min(e0 + u, p.k - 1)].x * p.d);
-  double acc[kEvRows][2];
-#pragma unroll
-  for (int u = 0; u < kEvRows; ++u) acc[u][0] = acc[u][1] = 0.0;
-#pragma nounroll
-  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
-    uint4 wv[kEvRows][4], xv[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int c = min(c0 + v * kWave + lane, cpr - 1);
-#pragma unroll
-      for (int u = 0; u < kEvRows; ++u) wv[u][v] = row[u][c];
-      xv[v] = tok[c];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (c0 + v * kWave + lane < cpr) {
-        const uint32_t xd[4] = {xv[v].x, xv[v].y, xv[v].z, xv[v].w};
-#pragma unroll
-        for (int u = 0; u < kEvRows; ++u) {
-          const uint32_t wd[4] = {wv[u][v].x, wv[u][v].y, wv[u][v].z, wv[u][v].w};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[u][0] += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
-            acc[u][1] += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
-          }
-        }
-      }
-  }
-#pragma unroll
-  for (int u = 0; u < kEvRows; ++u) {
-    const double s = wave_sum(acc[u][0] + acc[u][1]);
-    const float v = (float)(s > 0.0 ? s : 0.0);  // ReLU, and -0 -> +0
-    if (lane == 0 && e0 + u < p.k) {
-      list[e0 + u].y = __float_as_uint(v);
-      if (p.val_out) p.val_out[(size_t)b * p.k + e0 + u] = v;
-    }
-  }
+  const int b = item % B, e = item / B * kEvEntries + __builtin_amdgcn_readfirstlane(wave_id());
+  if (e >= k) return;
+  const size_t at = (size_t)b * k + e;
+  const float v = (float)wave_row_dot<true>(W + (size_t)lists[at].x * d, reinterpret_cast<const uint4*>(x + (size_t)b * d), d);
+  if (lane_id() != 0) return;
+  lists[at].y = __float_as_uint(v);
+  if (val_out) val_out[at] = v;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -494,9 +458,9 @@ hipError_t launch_keys_select(const float* keys, long long stride, int B, int N,
 }
 
 static hipError_t launch_exact_values(const RefineParams& p, hipStream_t s) {
-  const ExactValuesParams q{p.list_out, p.val_out, p.W, p.x, p.B, p.k, p.d};
   const int items = (p.k + kEvEntries - 1) / kEvEntries * p.B;
-  return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, q);
+  return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, p.list_out, p.val_out, p.W, p.x, p.B, p.k,
+                p.d);
 }
 
 hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
