@@ -166,7 +166,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
  * array inside the library (HIRE_STATIC_SCRATCH_BYTES, one per GPU the library runs on, held until the process
  * ends) instead of the caller's workspace.  The call allocates and frees nothing, on the host or on the device.
  *   - Steps that would need a larger workspace (hire_ffn_workspace_bytes(L, B, k, kprime) beyond
- *     HIRE_STATIC_SCRATCH_BYTES; the ~1B layer shape fits up to batch 16) return HIRE_ENOSPC, nothing enqueued.
+ *     HIRE_STATIC_SCRATCH_BYTES; the ~1B layer shape fits up to batch 40) return HIRE_ENOSPC, nothing enqueued.
  *   - The array belongs to the device that is current when the call is made; its address is looked up on the
  *     first call on that device (no work is enqueued for that, but make that first call outside a capture).
  *   - All calls on one GPU share that GPU's array, which keeps what the last call left there (the steps keep it

@@ -11,9 +11,7 @@
 // all zero when the code object is loaded (which is the state hire_workspace_init gives a workspace).  In host
 // code this name only stands for the symbol; the memory is reached through the per-device address that
 // hipGetSymbolAddress returns (static_scratch below), never through the name.
-// (the regions of further tokens at the head of every workspace come on top of what is announced)
-constexpr size_t kStaticBytes = (size_t)HIRE_STATIC_SCRATCH_BYTES + (hire::kFastTokens - 1) * hire::kFastRegionBytes;
-static __device__ __align__(256) unsigned char scratch[kStaticBytes];
+static __device__ __align__(256) unsigned char scratch[HIRE_STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -34,6 +32,13 @@ constexpr int kCounters = 64;     // int32 counters behind the union bitmap, cle
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+// The head of every workspace: the general route's header, then the state of the route for few tokens, a region per token.
+// Both keep what the step before left, whichever entry point and shapes that had - with one exception: FFN layouts that
+// cannot take the route for few tokens keep the first region only and put their buffers on the others, and their steps
+// leave the cookie at one region (general_header_check).
+size_t regions_offset() { return align_up(general_header_bytes()); }
+size_t body_offset(int regions) { return regions_offset() + align_up((size_t)regions * kFastRegionBytes); }
+
 // Bump allocator over the caller's workspace; with base == nullptr it only measures.
 struct Carver {
   char* base;
@@ -48,8 +53,8 @@ struct Carver {
 };
 
 struct StepBuffers {
-  void* fast_region;  // fixed offset 0: state and histograms of the three-kernel route, a region per token
-  HistRefs hist;      // general route: header at a fixed offset after the fast region; key histograms (long rows)
+  HistRefs hist;      // general route: header at offset 0; key histograms (long rows)
+  void* fast_region;  // behind it: state and histograms of the three-kernel route, a region per token
   uint32_t* window_misses;  // counter inside the header
   unsigned long long sig;  // names this layout
   int8_t* xq;
@@ -66,7 +71,7 @@ struct StepBuffers {
   int32_t* counters; // [0] = |U|
   int32_t* cand;     // U
   double* h;         // [B, cap_u]
-  int32_t* pos;      // [B,k] positions inside U of every token's selected units
+  int32_t* pos;      // group-sparse: [B, k >> gs] positions inside U of every token's selected groups
   uint2* list;       // [B,k] selected units as (row, coefficient), for the second layer
   float* h32;        // few tokens: activations by unit (by group) in fp32
   float* u32;        // ... groups: the units'
@@ -75,10 +80,9 @@ struct StepBuffers {
   float* wnorm_tiles; // largest candidate row norm of every workgroup of the filter stage
   void* refine_slots; // softmax: the final selection's slots
   float* maxima;     // softmax: [B, kFilterMaxima] largest values of parts of hf's rows
-  float* hf;         // [B, hf_stride]: by unit (by_unit: FFN) or by rank in the union (softmax)
+  float* hf;         // [B, hf_stride]: by unit (FFN, in the keys' place) or by rank in the union (softmax)
   long long hf_stride;
-  bool by_unit;
-  double* h64;       // by_unit: [B, hf_stride] scratch of the refining selection
+  bool by_unit;      // FFN batches on rows of at most 32768 units: the selections of batch_select.hip
   void* sm1_slots;   // long rows: slots of the keys at or above the bound from the scorer's maxima
   bool sm1_ok;       // ... which this layout has
   bool max_ok;       // long rows: slots for the selection of k' from the scorer's maxima
@@ -94,16 +98,16 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   const int Ns = N >> gs, kps = kprime >> gs;
   s.cap_u = (int)((long long)B * kps < (long long)Ns ? B * kps : Ns);
   s.words = (Ns + 31) / 32 + 2;
-  s.fast_region = c.take<char>(ffn_fast_region_bytes());
+  const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
+                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the route for few tokens
   s.hist.header = c.take<char>(general_header_bytes());
-  s.sig = layout_signature(scorer_kind, B, d, N, r, k, kprime, (ffn ? 1 : 0) + 16 * gs);
+  s.fast_region = c.take<char>((ffn && !fast ? 1 : kFastTokens) * kFastRegionBytes);
+  s.sig = layout_signature(scorer_kind, B, d, N, r, k, kprime, (ffn ? 1 : 0) + 16 * gs) | (ffn && !fast ? kSigOverlays : 0);
   s.window_misses = s.hist.header ? reinterpret_cast<uint32_t*>(static_cast<char*>(s.hist.header) +
                                                                  general_fallbacks_offset(1))
                                   : nullptr;
   const bool int4_like = scorer_kind == HIRE_SCORER_INT4 || scorer_kind == HIRE_SCORER_LRQ;
   s.by_unit = ffn && B >= kMfmaMinBatch && gs == 0 && batch_select_supported(N, k);
-  const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
-                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the route for few tokens
   s.key_stride = s.by_unit || (fast && gs == 0) ? (N + 3) / 4 * 4 : N;  // whole 16-byte vectors
   if (int4_like && N > kSingleWgMaxRow && gs == 0) s.hist.multi_body = c.take<char>(multi_body_bytes_host(B));
   if (int4_like) {
@@ -128,32 +132,31 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
   const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
-  if (s.by_unit || sm_filter) {
+  if (s.by_unit && B >= kFilterMinBatch) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
-    s.wnorm_tiles = c.take<float>(s.by_unit ? filter_tiles(N) : filter_rank_blocks(s.cap_u));
-    if (!s.by_unit) {
-      s.maxima = c.take<float>((size_t)B * kFilterMaxima);
-      s.refine_slots = c.take<char>(softmax_refine_slot_bytes(B));
-    }
-    s.hf_stride = ((s.by_unit ? N : s.cap_u) + 3) / 4 * 4;  // rows start at multiples of 16 bytes
+    s.wnorm_tiles = c.take<float>(filter_tiles(N));
+    s.hf_stride = s.key_stride;  // rows start at multiples of 16 bytes
+    s.hf = static_cast<float*>(s.keys);  // nobody reads the keys any more when the filter stage runs
+  } else if (sm_filter) {
+    s.xnorm = c.take<float>(HIRE_MAX_BATCH);
+    s.wnorm_tiles = c.take<float>(filter_rank_blocks(s.cap_u));
+    s.maxima = c.take<float>((size_t)B * kFilterMaxima);
+    s.refine_slots = c.take<char>(softmax_refine_slot_bytes(B));
+    s.hf_stride = (s.cap_u + 3) / 4 * 4;
     s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
-  // by_unit: one place for the exact route's activations and the refining selection's scratch
-  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, row_doubles = s.by_unit ? (size_t)s.hf_stride : 0,
-               entry_doubles = fast ? (size_t)ffn_fast_entries(N, gs) : 0,
-               h64_doubles = (size_t)B * (row_doubles > entry_doubles ? row_doubles : entry_doubles);
-  s.h = c.take<double>(h_doubles > h64_doubles ? h_doubles : h64_doubles);
+  const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
+  s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
   if (fast) {
     s.h32 = c.take<float>((size_t)B * ffn_fast_entries(N, gs));
     if (gs > 0) s.u32 = c.take<float>((size_t)B * ffn_fast_entries(N, 0));
   }
-  s.h64 = s.by_unit ? s.h : nullptr;
   if (gs > 0) s.hg = c.take<double>((size_t)B * s.cap_u + 2);
   s.sm1_ok = !ffn && B == 1 && gs == 0 && int4_like && N > kSingleWgMaxRow && softmax_b1_supported(N, d, 1, 1);
   s.max_ok = gs == 0 && int4_like && N > kSingleWgMaxRow && maxima_select_supported(N);
   if (s.sm1_ok || s.max_ok) s.sm1_slots = c.take<char>(maxima_select_slot_bytes(B, N));
   if (ffn) {
-    s.pos = c.take<int32_t>((size_t)B * k);
+    if (gs > 0) s.pos = c.take<int32_t>((size_t)B * (k >> gs));
     s.list = c.take<uint2>((size_t)B * k);
   }
   s.bytes = c.off;
@@ -384,18 +387,16 @@ const char* hire_strerror(int code) {
 int hire_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
   if (!workspace || workspace_bytes < kAlign || !aligned(workspace, 256)) return HIRE_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  HIRE_TRY(launch_clear_words(static_cast<uint32_t*>(workspace), (int)(kAlign / 4), st));
-  const size_t second = align_up(ffn_fast_region_bytes());  // header of the general route's histograms
-  if (workspace_bytes >= second + general_header_bytes())
-    HIRE_TRY(launch_clear_words(reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + second),
-                                (int)(general_header_bytes() / 4), st));
+  // the general route's header and the head of the first region (smaller workspaces hold neither)
+  const size_t state = regions_offset() + kAlign;
+  HIRE_TRY(launch_clear_words(static_cast<uint32_t*>(workspace), (int)((workspace_bytes < state ? kAlign : state) / 4), st));
   return HIRE_OK;
 }
 
 int hire_debug_fast_fallbacks(const void* workspace, uint32_t* host_out2, void* stream) {
   if (!workspace || !host_out2) return HIRE_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  HIRE_TRY(hipMemcpyAsync(host_out2, static_cast<const char*>(workspace) + ffn_fast_fallbacks_offset(),
+  HIRE_TRY(hipMemcpyAsync(host_out2, static_cast<const char*>(workspace) + regions_offset() + ffn_fast_fallbacks_offset(),
                           2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   HIRE_TRY(hipStreamSynchronize(st));
   return HIRE_OK;
@@ -407,7 +408,7 @@ int hire_debug_fast_state(const void* workspace, uint32_t* host_out3, void* stre
   size_t cookie_off, h1, h2, words;
   unsigned long long want = 0, cookie = 0;
   ffn_fast_state_layout(&cookie_off, &want, &h1, &h2, &words);
-  const char* base = static_cast<const char*>(workspace);
+  const char* base = static_cast<const char*>(workspace) + regions_offset();
   std::vector<uint32_t> host(2 * words);
   HIRE_TRY(hipMemcpyAsync(&cookie, base + cookie_off, sizeof(cookie), hipMemcpyDeviceToHost, st));
   HIRE_TRY(hipMemcpyAsync(host.data(), base + h1, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -425,7 +426,7 @@ int hire_debug_fast_state(const void* workspace, uint32_t* host_out3, void* stre
 int hire_debug_general_fallbacks(const void* workspace, uint32_t* host_out3, void* stream) {
   if (!workspace || !host_out3) return HIRE_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const char* hdr = static_cast<const char*>(workspace) + align_up(ffn_fast_region_bytes());
+  const char* hdr = static_cast<const char*>(workspace);
   for (int i = 0; i < 3; ++i)
     HIRE_TRY(hipMemcpyAsync(host_out3 + i, hdr + general_fallbacks_offset(i), sizeof(uint32_t), hipMemcpyDeviceToHost,
                             st));
@@ -526,9 +527,8 @@ static size_t topk_rank_tmp_bytes(int B, int k, int flags) {
 size_t hire_topk_workspace_bytes(int B, int N, int k, int flags) {
   if (B < 1 || N < 1 || k < 1 || k > N) return 0;
   if (!topk_long_route(N, flags)) return kAlign;  // LDS and registers only; a token amount keeps the pointer non-null
-  // the header sits where the step workspaces have it, so that one initialisation routine serves all
-  return align_up(ffn_fast_region_bytes()) + align_up(general_header_bytes()) +
-         align_up(topk_long_workspace_bytes(B, N)) + topk_rank_tmp_bytes(B, k, flags);
+  // the head is that of the step workspaces, so that one initialisation routine serves all
+  return body_offset(kFastTokens) + align_up(topk_long_workspace_bytes(B, N)) + topk_rank_tmp_bytes(B, k, flags);
 }
 
 int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kprime, float* y, int32_t* topk_idx,
@@ -601,7 +601,8 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
       rp.cand_cap = s.cap_u;
       rp.n_cand_out = n_cand;
     }
-    rp.h64 = s.h64;
+    rp.h64 = s.h;
+    rp.h_stride = s.cap_u;
     rp.idx_out = topk_idx;
     rp.val_out = topk_val;
     rp.list_out = s.list;
@@ -663,11 +664,11 @@ int hire_ffn_step_static(const hire_ffn_layer* L, const void* x, int B, int k, i
                          float* topk_val, int32_t* cand_idx, int32_t* n_cand, int32_t* scorer_acc, void* stream) {
   const size_t need = hire_ffn_workspace_bytes(L, B, k, kprime);
   if (need == 0) return HIRE_EINVAL;
-  if (need > kStaticBytes) return HIRE_ENOSPC;
+  if (need > (size_t)HIRE_STATIC_SCRATCH_BYTES) return HIRE_ENOSPC;
   void* ws = nullptr;
   if (const int rc = static_scratch(&ws); rc != HIRE_OK) return rc;
   return hire_ffn_step(L, x, B, k, kprime, y, topk_idx, topk_val, cand_idx, n_cand, scorer_acc, ws,
-                       kStaticBytes, stream);
+                       (size_t)HIRE_STATIC_SCRATCH_BYTES, stream);
 }
 
 static int group_shift(int group) {
@@ -847,9 +848,8 @@ int hire_ffn_commonpath_step(const hire_ffn_layer* L, const void* dense_w1u, con
                              workspace, workspace_bytes, stream, (need != 0 && m1 > 0) ? &dense : nullptr);
 }
 
-// The partial rows sit behind the places of the two route headers, so that a workspace shared with the other
-// entry points keeps their headers intact.
-static size_t shard_partial_offset() { return align_up(ffn_fast_region_bytes()) + align_up(general_header_bytes()); }
+// The partial rows sit behind the head, so that a workspace shared with the other entry points keeps their state intact.
+static size_t shard_partial_offset() { return body_offset(kFastTokens); }
 
 static bool shard_args_ok(const hire_ffn_layer* L, int B, int k, int kprime, int shards) {
   if (!L || L->d_model < 32 || L->d_ff < 1 || B < 1 || B > HIRE_MAX_BATCH || k < 1 || k > kprime || kprime > L->d_ff)
@@ -973,8 +973,8 @@ int topk_select(const float* scores, int B, int N, int k, int flags, int32_t* id
   if (topk_long_route(N, flags)) {
     if (!workspace || !aligned(workspace, 256)) return HIRE_EINVAL;
     if (workspace_bytes < hire_topk_workspace_bytes(B, N, k, flags)) return HIRE_ENOSPC;
-    char* base = static_cast<char*>(workspace) + align_up(ffn_fast_region_bytes());
-    char* body = base + align_up(general_header_bytes());
+    char* base = static_cast<char*>(workspace);
+    char* body = base + body_offset(kFastTokens);
     const bool rank = (flags & HIRE_ORDER_RANK) != 0;
     int32_t* idx_tmp = reinterpret_cast<int32_t*>(body + align_up(topk_long_workspace_bytes(B, N)));
     float* val_tmp = reinterpret_cast<float*>(reinterpret_cast<char*>(idx_tmp) +

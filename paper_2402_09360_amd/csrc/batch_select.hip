@@ -165,18 +165,22 @@ struct RefineShared {
 
 // What the histogram and the list cannot settle (threshold among the zeros, very many activations within the error of
 // the threshold): exact, by streaming the row.  The k-th largest stored value among the candidates by range
-// narrowing; everything within hw of it recomputed in fp64; then the k-th largest of the row of fp64 values (stored
-// ones outside the band) with ties to the lower unit, and the outputs.
+// narrowing; everything within hw of it recomputed in fp64; then the k-th largest of the candidates' fp64 values (stored
+// ones outside the band) with ties to the lower unit, and the outputs.  The fp64 values lie in the order of the
+// candidates; a wave owns the units [i_lo, i_hi) and so the candidates from c_lo on.
 __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, const uint4* tok, RefineShared& L, double hw) {
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int N = p.N, k = p.k;
   const float* row = p.vals + (size_t)b * p.stride;
-  double* h = p.h64 + (size_t)b * p.stride;
+  double* h = p.h64 + (size_t)b * p.h_stride;
   auto candidate = [&](int i) { return ((p.bitmap[i >> 5] >> (i & 31)) & 1u) != 0u; };
+  const int M = ((N + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave * kWave, i_lo = w * M, i_hi = min(N, i_lo + M);
   int mine = 0;
-  for (int i = tid; i < (N + 31) / 32; i += kSelThreads) mine += __popc(p.bitmap[i]);
+#pragma unroll 1
+  for (int i0 = i_lo; i0 < i_hi; i0 += kWave) mine += i0 + lane < i_hi && candidate(i0 + lane) ? 1 : 0;
   int n_units;
-  wg_scan_incl<kSelThreads>(mine, L.sh, &n_units);
+  const int incl = wg_scan_incl<kSelThreads>(mine, L.sh, &n_units);
+  const int c_lo = __builtin_amdgcn_readfirstlane(incl - mine), c_hi = __builtin_amdgcn_readlane(incl, kWave - 1);
   const uint32_t okey = wg_kth_largest<uint32_t>(
       [&](auto&& f) {
 #pragma unroll 1
@@ -186,33 +190,36 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
   const double cut0 = (double)key_value(okey);
   const double lo = cut0 - hw, hi = cut0 + hw;
   // the same positions are written and read by this workgroup only; a barrier orders them
+  int run_c = c_lo;
 #pragma unroll 1
-  for (int i0 = w * kWave; i0 < N; i0 += kSelThreads) {
+  for (int i0 = i_lo; i0 < i_hi; i0 += kWave) {
     const int i = i0 + lane;
-    const float v = i < N ? row[i] : 0.0f;
-    const bool cand = i < N && candidate(i);
-    if (i < N) h[i] = cand ? (double)v : -1.0;
+    const float v = i < i_hi ? row[i] : 0.0f;
+    const bool cand = i < i_hi && candidate(i);
+    const uint64_t cands = __ballot(cand);
+    const int at = run_c + mask_prefix(cands);
+    run_c += __popcll(cands);
+    if (cand) h[at] = (double)v;
     // exact zeros are activations already; with k = all candidates nothing needs to be decided
     uint64_t band = __ballot(cand && k < n_units && v > 0.0f && (double)v >= lo && (double)v <= hi);
     while (band != 0ull) {
       const int s = __builtin_ctzll(band);
       band &= band - 1ull;
       const double r = wave_row_dot(p.W + (size_t)(i0 + s) * p.d, tok, p.d);
-      if (lane == s) h[i] = r;
+      if (lane == s) h[at] = r;
     }
   }
   __syncthreads();
   const uint64_t t = wg_kth_largest<uint64_t>(
       [&](auto&& f) {
 #pragma unroll 1
-        for (int i = tid; i < N; i += kSelThreads) f(order_key(h[i]));
+        for (int i = tid; i < n_units; i += kSelThreads) f(order_key(h[i]));
       },
-      N, k, L.sh);
-  const int M = ((N + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave * kWave, i_lo = w * M, i_hi = min(N, i_lo + M);
+      n_units, k, L.sh);
   int gt = 0, eq = 0;
 #pragma unroll 1
-  for (int i = i_lo + lane; i < i_hi; i += kWave) {
-    const uint64_t key = order_key(h[i]);
+  for (int c = c_lo + lane; c < c_hi; c += kWave) {
+    const uint64_t key = order_key(h[c]);
     gt += key > t ? 1 : 0;
     eq += key == t ? 1 : 0;
   }
@@ -231,16 +238,20 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
     all_gt += L.wave_cnt[u];
   }
   const int need_eq = k - all_gt;
+  run_c = c_lo;
 #pragma unroll 1
   for (int i0 = i_lo; i0 < i_hi; i0 += kWave) {  // uniform trip count per wave
     const int i = i0 + lane;
-    const double v = i < i_hi ? h[i] : -1.0;
+    const bool cand = i < i_hi && candidate(i);
+    const uint64_t cands = __ballot(cand);
+    const double v = cand ? h[run_c + mask_prefix(cands)] : -1.0;
+    run_c += __popcll(cands);
     const uint64_t key = order_key(v);
-    const uint64_t mg = __ballot(i < i_hi && key > t), me = __ballot(i < i_hi && key == t);
+    const uint64_t mg = __ballot(cand && key > t), me = __ballot(cand && key == t);
     const int gt_before = run_gt + mask_prefix(mg), eq_before = run_eq + mask_prefix(me);
     run_gt += __popcll(mg);
     run_eq += __popcll(me);
-    if (i < i_hi && (key > t || (key == t && eq_before < need_eq))) {
+    if (cand && (key > t || (key == t && eq_before < need_eq))) {
       const size_t o = (size_t)b * k + gt_before + min(eq_before, need_eq);
       if (p.idx_out) p.idx_out[o] = i;
       if (p.val_out) p.val_out[o] = (float)v;

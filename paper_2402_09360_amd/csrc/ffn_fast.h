@@ -2,6 +2,7 @@
 #pragma once
 
 #include "fast_select.h"
+#include "hist.h"
 #include "kernels.h"
 #include "rows_mfma.h"
 
@@ -16,7 +17,7 @@ namespace hire {
 //  * The anchors bound every key and activation.  Should one lie above its anchor all the same (row-norm bounds of other
 //    weights, scales that do not belong to the codes), it would be missing from the counts: whoever meets it says so in
 //    `beyond1` / `beyond2`, and the selection goes by the keys alone.
-constexpr unsigned long long kCookie = 0x48695245464e4f00ull;  // + the number of clean regions
+// (kCookie, in hist.h: steps whose layout lies on the regions of further tokens leave it at one region)
 
 struct FastRegion {
   unsigned long long cookie; // of the first region

@@ -930,7 +930,6 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-size_t ffn_fast_region_bytes() { return kFastTokens * sizeof(FastRegion); }
 size_t ffn_fast_fallbacks_offset() { return offsetof(FastRegion, fallbacks); }
 void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_t* hist1_off, size_t* hist2_off,
                            size_t* hist_words) {

@@ -163,10 +163,19 @@ __host__ __device__ inline MultiRegion multi_of(const HistRefs& hr, int B) {
   if (!hr.header || !hr.multi_body) return MultiRegion{};
   return carve_multi(&static_cast<GeneralHeader*>(hr.header)->multi, hr.multi_body, B);
 }
+// The route for few tokens (ffn_fast.h) keeps a region per token behind the header; the first word of the first one is
+// its cookie, kCookie + the number of regions whose histograms are clean.
+constexpr unsigned long long kCookie = 0x48695245464e4f00ull;
 // Called by workgroup 0 of a step's first kernel.
 __device__ __forceinline__ void general_header_check(GeneralHeader* gh, unsigned long long sig) {
-  if (gh == nullptr || gh->layout_sig == sig) return;  // uniform
+  if (gh == nullptr) return;
   const int tid = (int)threadIdx.x;
+  if ((sig & kSigOverlays) != 0ull && tid == 0) {  // the step's buffers lie on the regions of further tokens
+    unsigned long long* cookie = reinterpret_cast<unsigned long long*>(gh + 1);
+    const unsigned long long n = *cookie - kCookie;
+    if (n > 1ull && n <= (unsigned long long)kFastTokens) *cookie = kCookie + 1ull;
+  }
+  if (gh->layout_sig == sig) return;  // uniform
   if (tid == 0) {
     gh->multi.cookie = 0ull;
     gh->window_misses = 0u;

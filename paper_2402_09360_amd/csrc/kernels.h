@@ -41,6 +41,7 @@ struct HistRefs {
 };
 size_t general_header_bytes();
 unsigned long long layout_signature(int scorer_kind, int B, int d, int N, int r, int k, int kprime, int ffn);
+constexpr unsigned long long kSigOverlays = 1ull << 63;  // set in signatures of layouts that reuse the token regions
 
 // ---- scorer.hip ------------------------------------------------------------
 // The packed blob is rows * cols / 2 bytes of codes followed by kPackTrailerBytes: the first trailer word holds the
@@ -217,7 +218,8 @@ struct RefineParams {
   int32_t* cand_out;        // optional; cand_cap entries fit
   int cand_cap;
   int32_t* n_cand_out;      // optional (with cand_out)
-  double* h64;              // [B, stride] scratch
+  double* h64;              // [B, h_stride] scratch, as many per token as there can be candidates
+  long long h_stride;
   int32_t* idx_out;         // optional [B, k] ascending
   float* val_out;           // optional [B, k]
   uint2* list_out;          // [B, k] (unit, value) for launch_w2_list
@@ -326,7 +328,7 @@ struct FfnFastArgs {
   int32_t* n_cand;     // optional
   int32_t* scorer_acc; // optional
   // workspace
-  void* fast_region;   // ffn_fast_region_bytes() bytes at the head of the workspace (cookie, maxima, histograms)
+  void* fast_region;   // kFastTokens regions near the head of the workspace (cookie, anchors, histograms)
   float* keys;         // [B, key_stride], key_stride a multiple of 4
   long long key_stride;
   double* h;           // [B, ffn_fast_entries(N, gs)]: activations of the units (gs = 3: of the groups)
@@ -368,7 +370,6 @@ struct FfnFastArgs {
   hipEvent_t* stage_events;  // optional: 4 events recorded around the kernels
   unsigned long long* scorer_clocks;  // optional: start/end wall clock (100 MHz ticks) of every scorer workgroup
 };
-size_t ffn_fast_region_bytes();
 int ffn_fast_score_blocks(int N);
 size_t ffn_fast_fallbacks_offset();  // two uint32 counters inside the region
 // Where the region keeps its cookie (and the value that says "key histogram all zero") and its two histograms.

@@ -483,7 +483,7 @@ unsigned long long layout_signature(int scorer_kind, int B, int d, int N, int r,
     h ^= (unsigned long long)(unsigned)v[i] + 0x9E3779B97F4A7C15ull + (h << 6) + (h >> 2);
     h *= 0xBF58476D1CE4E5B9ull;
   }
-  return h | 1ull;  // never the cleared header's zero
+  return (h | 1ull) & ~kSigOverlays;  // never the cleared header's zero
 }
 
 hipError_t launch_clear_words(uint32_t* p, int words, hipStream_t s) {

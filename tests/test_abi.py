@@ -189,3 +189,32 @@ def test_lrq_scorer_arguments_are_checked_on_the_host(lib):
     L = FFNLayer(2048, 16384, 0x10000, 0x20000, 2, None, None, 0x30000, 0x40000, 128, 0x50000, 0x60000)
     assert lib.hire_ffn_workspace_bytes(C.byref(L), 1, 819, 3276) > 0
     assert lib.hire_ffn_workspace_bytes(C.byref(L), 1, 819, 20000) == 0    # k' beyond the units
+
+
+def test_static_scratch_takes_what_it_announces(lib):
+    """hire_ffn_step_static refuses exactly the steps whose workspace is larger than HIRE_STATIC_SCRATCH_BYTES.  Its check
+    comes before anything else that could fail, so the refused ones are called here; for those that fit (large batches on
+    long rows with small unions among them) the announced size is what decides."""
+    size = lib.hire_ffn_workspace_bytes
+    size.restype = C.c_size_t
+    size.argtypes = [C.POINTER(FFNLayer)] + [C.c_int] * 3
+    step = lib.hire_ffn_step_static
+    step.restype = C.c_int
+    step.argtypes = [C.POINTER(FFNLayer), C.c_void_p, C.c_int, C.c_int, C.c_int] + [C.c_void_p] * 7
+    limit = 8 << 20
+
+    def layer(d, N, kind=0, r=0):
+        return FFNLayer(d, N, 0x10000, 0x20000, kind, 0x30000, 0x40000, 0x50000, 0x60000, r, 0x70000, 0x80000)
+
+    for d, N, B, k, kp, kind, r in [(2048, 16384, 32, 81, 327, 0, 0), (2048, 32768, 16, 163, 655, 0, 0),
+                                    (704, 29819, 16, 379, 558, 1, 160), (288, 8992, 64, 1, 18, 2, 896),
+                                    (1280, 26596, 33, 5, 35, 0, 0), (2016, 31302, 33, 96, 125, 2, 992),
+                                    (2048, 16384, 16, 819, 3276, 0, 0), (8192, 16384, 4, 16384, 16384, 1, 1024)]:
+        assert 0 < size(C.byref(layer(d, N, kind, r)), B, k, kp) <= limit, (d, N, B, k, kp, kind, r)
+    refused = 0
+    L = layer(2048, 16384)
+    for B in range(1, 65):
+        if size(C.byref(L), B, 819, 3276) > limit:
+            assert step(C.byref(L), 0x90000, B, 819, 3276, 0xA0000, None, None, None, None, None, None) == -2
+            refused += 1
+    assert refused > 0

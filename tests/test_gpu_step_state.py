@@ -121,3 +121,30 @@ def test_row_scales_above_the_packed_maximum(hire, oracle, B):
     torch.cuda.synchronize()
     log(f"row scales above the maximum, B={B}")
     T.check_ffn(layer, (kind, q, s * factor), L, I.tokens(322 + B, B, d), k, kp)
+
+
+@pytest.mark.parametrize("d,N,B,k,kp", [(512, 16384, 32, 81, 327), (256, 30000, 16, 163, 655), (64, 9000, 64, 3, 18)])
+def test_static_scratch_takes_large_batches_with_small_unions(hire, oracle, d, N, B, k, kp):
+    """Steps whose buffers are sized by their unions, next to one of few tokens whose state lies where theirs do."""
+    L = I.ffn_layer(341, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    small = I.ffn_layer(342, 128, 700)
+    small_layer, small_scorer = T.make_ffn_layer(small)
+
+    def static(layer, x_bits, k, kp):
+        x = T.dev_bf16(x_bits)
+        out = hire.FFNOutputs(layer, x.shape[0], k, kp)
+        hire.hire_ffn_step_static(layer, x, k, kp, out)
+        torch.cuda.synchronize()
+        n = int(out.n_cand.item())
+        return dict(y=out.y.cpu().numpy(), topk_idx=out.topk_idx.cpu().numpy(), topk_val=out.topk_val.cpu().numpy(),
+                    cand=out.cand_idx.cpu().numpy()[:n], n_cand=n, acc=None)
+
+    x, xs = I.tokens(343, B, d), I.tokens(344, 3, 128)
+    want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
+    want_small = oracle.ffn_step(small["w1u"], small["w2u"], small_scorer, xs, 30, 150)
+    for turn in range(3):
+        log(f"static scratch, turn {turn}: B={B} N={N} k'={kp}, then 3 tokens twice")
+        T.compare_ffn(static(layer, x, k, kp), want)
+        for _ in range(2):
+            T.compare_ffn(static(small_layer, xs, 30, 150), want_small)
