@@ -10,8 +10,9 @@
 // The selections are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
 // count per thread times 16 cycles (four waves share a SIMD), so what counts is the number of sections and of passes
 // over the register-resident row.  The window histogram (fast_select.h) is anchored at an a-priori bound of the
-// row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves.  It only
-// proposes a bin: what lies above is counted from the masks that the pass over the registers leaves.
+// row's values - no pass and no barrier for their maximum - and is built in LDS from the registers themselves, so the
+// number of entries above the bin it proposes is exact and no counting pass confirms it, unless a value lies above the
+// anchor, which whoever holds it sees.
 #include "fast_select.h"
 #include "kernels.h"
 
@@ -26,22 +27,27 @@ struct BatchKeys {
 };
 
 // Window histogram of the registers' values below `anchor` (zeros are never counted) and the bin that holds the k-th
-// largest of those.  false: fewer than k values in the window.  *bin: that bin.
+// largest of those.  false: fewer than k values in the window.  *bin: that bin; *above: the values counted in higher ones;
+// *beyond: this thread has a value above the anchor, which is not counted.
 template <typename Keys>
 __device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int k, uint32_t* win,
-                                           SelSharedT<kSelThreads>& sh, uint32_t* bin) {
+                                           SelSharedT<kSelThreads>& sh, uint32_t* bin, int* above, bool* beyond) {
+  uint32_t farthest = 0u;
 #pragma unroll
   for (int e = 0; e < (int)(sizeof(kr.r) / sizeof(kr.r[0])); ++e)
 #pragma unroll
     for (int q = 0; q < Keys::PER; ++q) {
-      const uint32_t slot = anchor - fine_bin(kr.r[e][q]);
+      const uint32_t slot = anchor - fine_bin(kr.r[e][q]);  // (wraps above the anchor)
+      farthest = max(farthest, slot);
       if (kr.r[e][q] != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
     }
+  *beyond = farthest > anchor;
   __syncthreads();
   WinRegs<kSelThreads> wr;
   wr.issue(win);
   const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
   *bin = anchor - (uint32_t)wk.slot;
+  *above = wk.above;
   return wk.found && *bin >= 1u && *bin <= anchor;  // uniform
 }
 
@@ -59,6 +65,7 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
   __shared__ SelSharedT<kSelThreads> sh;
   __shared__ __align__(16) uint32_t win[kWin];
   __shared__ int wave_cnt[kSelWaves];
+  __shared__ int off_window;  // not 0: the window does not count every key that it should
   __shared__ BinList<uint32_t> list;
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
   HIRE_TS(10);
@@ -70,28 +77,28 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __rest
     uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
     z[0] = z[1] = make_uint4(0, 0, 0, 0);
   }
-  if (tid == 0) sh.list_n = 0;
+  if (tid == 0) sh.list_n = off_window = 0;
   kr.finish();
   kr.mask_beyond(N);
   __syncthreads();
   HIRE_TS(11);
   uint32_t bin;
-  bool known = window_bin(kr, anchor, kprime, win, sh, &bin);
+  int above;
+  bool beyond;
+  bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above, &beyond);
+  if (beyond) off_window = 1;  // (row scales that do not belong to the codes)
   HIRE_TS(12);
   uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
   if (known) {
     const BinMasks<uint32_t> bm = bin_masks<uint32_t>(kr, bin_floor<uint32_t>(bin), bin_floor<uint32_t>(bin + 1u));
     list_inside<uint32_t>(kr, bm.inside, &sh.list_n, list);
-    // What lies above the bin is counted from the keys themselves: scales that do not belong to the codes would put keys
-    // above the anchor, where the window does not count them.
-    const int above = wave_sum(__popc(bm.above));
-    if (lane == 0) wave_cnt[wave_id()] = above;
     __syncthreads();
     HIRE_TS(13);
-    const int m = sh.list_n, need = kprime - wave_sum(lane < kSelWaves ? wave_cnt[lane] : 0);
-    known = m <= kFastAmbCap && need >= 1 && need <= m;  // uniform
+    const int m = sh.list_n;
+    known = m <= kFastAmbCap && off_window == 0;  // uniform
     if (known)
-      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m, need);
+      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
+                                      kprime - above);
     HIRE_TS(14);
   }
   if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
@@ -308,7 +315,11 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   const double hw = 2.0 * (double)p.err_c * (double)xn * (double)wn * 1.000001;
   HIRE_TS(41);
   uint32_t bin;
-  const bool found = window_bin(kr, anchor, k, L.win, L.sh, &bin);
+  int above_bin;
+  bool beyond;
+  const bool found = window_bin(kr, anchor, k, L.win, L.sh, &bin, &above_bin, &beyond);
+  (void)above_bin;  // the window only proposes: the band's own counts decide
+  (void)beyond;
   HIRE_TS(42);
   if (found) {  // uniform
     const double f = (double)__uint_as_float(bin << kFineShift), c = (double)__uint_as_float((bin + 1u) << kFineShift);
