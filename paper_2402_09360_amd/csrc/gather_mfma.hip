@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_gather_dot_mfma(const uint16_t* __restr
 // Stored per (token, candidate), as fp32 - with phi = identity (RELU false: the classifier) the sum itself; with
 // the ReLU: the sum if it is positive (never rounded to zero); the smallest
 // positive float if it lies in (-2 delta, 0], where the true activation may still be positive; exactly 0 below
-// that, where the true activation is exactly 0.  The selection (k_select_refine) recomputes in fp64 the entries
+// that, where the true activation is exactly 0.  The selection (k_refine) recomputes in fp64 the entries
 // whose stored value lies within 2 max_j delta(b, j) of the k-th largest stored value and selects on the result:
 // the selected set is that of the fp64 values.  xnorm[b] receives an upper bound of |x_b|, wnorm_tiles[i] one of the
 // largest |u_j| over workgroup i's candidates (or, without it, *wnorm_max over all: float bits, atomic max).
@@ -217,7 +217,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 __device__ __forceinline__ void load_to_lds(const void* g, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g),
                "s"(__builtin_amdgcn_readfirstlane((int)lds_off))
-               : "memory");
+               : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
