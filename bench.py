@@ -88,8 +88,8 @@ _STAGE_KERNELS = {
                       "k_sm1_gather<false"),
     "union": ("k_resolve_compact", "k_bitmap_compact", "k_union_compact", "k_max_resolve"),
     "gather_dot": ("k_gather_dot", "k_filter_units", "k_filter_ranks", "k_sm1_gather<true", "k_sm1_final"),
-    "select_k": ("k_select<double", "k_select_nonneg<double", "k_refine"),
-    "select_k_softmax": ("k_select<double",),
+    "select_k": ("k_select<double", "k_select_nonneg<double", "k_refine", "k_exact_values"),
+    "select_k_softmax": ("k_select<double", "k_softmax_parts", "k_softmax_refine"),
     "second_layer": ("k_w2_list",),
     "shard_step": ("k_ffn_shard",),
     "reduce": ("k_shard_reduce",),

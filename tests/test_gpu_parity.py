@@ -86,9 +86,10 @@ def test_topk_select_large_vocab(hire, oracle):
 
 
 def test_topk_select_long_rows_steady_state(hire, oracle):
-    """Rows beyond 32768 in index order: many workgroups per row and histograms in the workspace.  A fresh workspace
-    selects by streaming once; from the second call on the histograms answer (no streaming selections counted),
-    except for inputs that defeat them (all keys equal: a crowded bin), which stay exact through the fallback."""
+    """Rows beyond 32768 in index order, several calls on one workspace.  The first two shapes (k up to 2048) are bounded by
+    the maxima of interleaved groups; the third keeps histograms in the workspace, selects by streaming once on a fresh
+    one, and its k-th key lies outside their window.  Either way the workspace takes its layout in the first call and no
+    row is selected by streaming after it, except for inputs that defeat both (all keys equal), which stay exact."""
     rng = np.random.default_rng(9)
     for N, k, B in ((70001, 700, 3), (256000, 1024, 2), (40000, 39999, 1)):
         for relu in (False, True):
