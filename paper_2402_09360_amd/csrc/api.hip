@@ -99,7 +99,7 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.cap_u = (int)((long long)B * kps < (long long)Ns ? B * kps : Ns);
   s.words = (Ns + 31) / 32 + 2;
   const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
-                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));  // the route for few tokens
+                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime, scorer_kind == HIRE_SCORER_INT4)));
   s.hist.header = c.take<char>(general_header_bytes());
   s.fast_region = c.take<char>((ffn && !fast ? 1 : kFastTokens) * kFastRegionBytes);
   s.sig = layout_signature(scorer_kind, B, d, N, r, k, kprime, (ffn ? 1 : 0) + 16 * gs) | (ffn && !fast ? kSigOverlays : 0);
@@ -546,10 +546,9 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   const bool fast_int4 = L->scorer_kind == HIRE_SCORER_INT4;
-  const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr && L->r <= 1024;
-  const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && L->r <= 8192 &&
-                        scorer_int4_fused_supported(d);
-  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic &&
+  const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr;
+  const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && scorer_int4_fused_supported(d);
+  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime, fast_int4) && !g_force_generic &&
       !(B > 1 && g_force_exact_stage)) {
     FfnFastArgs a{};
     a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;

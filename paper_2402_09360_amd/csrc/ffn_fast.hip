@@ -948,12 +948,12 @@ int ffn_fast_entries(int N, int gs) { return ((N + kOwnUnits - 1) / kOwnUnits * 
 
 // Group-sparse step with groups of eight: N, k, k' count units.  The selections see N/8, k'/8 and k/8 entries.
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime) {
-  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime, true);
+  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime, true, true);
 }
 
-bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool groups) {
-  return (B == 1 || ffn_fast_tokens_supported(B, d, groups)) && N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 &&
-         k >= 1 && kprime <= N;
+bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool int4, bool groups) {
+  return N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 && k >= 1 && kprime <= N &&
+         (B == 1 || ffn_fast_tokens_supported(B, N, d, int4, groups));
 }
 
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
@@ -985,7 +985,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   } else if (a.lrq) {
     // first product: the r rows of the int4 copy of Z1^T against the token (no phi), fp32 intermediate; then the
     // scorer kernel on the int4 copy of Z2 with that intermediate as its token
-    if (gs != 0 || a.m1 != 0 || a.r < 32 || a.r > 8192 || a.r % 32 != 0) return hipErrorInvalidValue;
+    if (gs != 0 || a.m1 != 0 || a.r < 32 || a.r > 1024 || a.r % 32 != 0) return hipErrorInvalidValue;
     if (several) {
       if ((e = launch_quantize_tokens(a.x, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
       e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.xq, a.B, a.r, a.d, 0, a.keys_t,

@@ -1,6 +1,6 @@
-// HiRE-FFN step for two to eight tokens (arXiv 2402.09360, Algorithm 1 + eq. (4)): the scorer and the gather of the
-// batch-1 sequence (ffn_fast.hip) for several tokens at once; the second layer is that sequence's own kernel, a row of
-// workgroups per token.
+// HiRE-FFN step for two to eight tokens (arXiv 2402.09360, Algorithm 1 + eq. (4); ffn_fast_tokens_supported says which):
+// the scorer and the gather of the batch-1 sequence (ffn_fast.hip) for several tokens at once; the second layer is that
+// sequence's own kernel, a row of workgroups per token.
 //
 // The longer sequence for batches runs seven kernels, of which the two selections keep one compute unit per token busy
 // for 6 and 10 us: at a few tokens that is a third of the step.  Here nothing runs on a unit per token.  The scorer
@@ -521,12 +521,20 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
 // ---------------------------------------------------------------------------------------------------
 static int token_slots(int B) { return B <= 4 ? 4 : 8; }
 
-// Steps on units: up to four tokens.  With eight the fp64 products and two windows of counters per wave outweigh the
-// selections saved, at the ~1B shape 50.5 us against 47.9 for five tokens and 63 against 51.5 for eight; groups of
-// eight, whose longer sequence forms its activations in fp64 too, gain up to eight (275 us for four layers against 322
-// with dense units, 164 against 166 for a small layer without).  The scorer keeps a token in four vectors per thread.
-bool ffn_fast_tokens_supported(int B, int d, bool groups) {
-  return B >= 2 && B <= (groups ? kFastTokens : 4) && token_slots(B) * d <= 32768;
+// Steps on units: up to four tokens; five to eight (int4 scorer) while the rows are short.  With more tokens the fp64
+// products and two windows of counters per wave outweigh the selections saved, the more so the more keys there are: the
+// longer sequence, its values rounded from 64 bits like these, against this one in us per step, for 5 / 6 / 7 / 8 tokens
+//   d = 1024,  4096 units  37.2 38.3 38.0 37.9   32.0 32.7 34.5 36.4
+//   d =  800,  5003 units  36.4 37.1 37.2 37.5   31.5 32.4 33.5 34.6
+//   d = 4096,  8192 units  59.0 60.5 61.4 63.3   56.4 58.9 61.5 67.4
+//   d =  512, 16000 units  36.9 37.1 38.0 38.6   40.0 43.2 46.1 49.7
+//   d = 2048, 16384 units  53.1 54.8 56.7 58.2   51.7 55.5 60.3 68.0
+// Groups of eight, whose longer sequence forms its activations in fp64 too, gain up to eight (275 us for four layers
+// against 322 with dense units, 164 against 166 for a small layer without).  The scorer keeps a token in four vectors per
+// thread.
+bool ffn_fast_tokens_supported(int B, int N, int d, bool int4, bool groups) {
+  if (B < 2 || B > kFastTokens || token_slots(B) * d > 32768) return false;
+  return groups || B <= 4 || (int4 && N * (B - 2) <= 32768);
 }
 
 hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lrq, hipStream_t s) {

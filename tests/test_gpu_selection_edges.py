@@ -81,3 +81,22 @@ def test_softmax_step_with_masked_classes(hire, oracle, c, B, k, kp):
         assert np.array_equal(got["top_idx"], want["top_idx"])
         assert np.isfinite(got["top_logit"]).all() and not (got["top_idx"] % 3 == 0).any()
         T.assert_float_close(got["top_prob"], want["top_prob"], "top_prob")
+
+
+@pytest.mark.parametrize("d,N,B,k,kp", [
+    (64, 5461, 8, 300, 1400),     # the longest rows that eight tokens take the few-token kernels with
+    (64, 5462, 8, 300, 1400),     # one unit more: the longer sequence
+    (96, 8192, 6, 8192, 8192),    # six tokens, everything selected
+    (4096, 640, 8, 40, 160),      # the longest eight tokens
+    (4128, 640, 5, 40, 160),      # too long for them
+    (160, 65, 7, 5, 20),          # a workgroup with one unit
+    (288, 1000, 5, 1, 1),
+])
+def test_five_to_eight_tokens(hire, oracle, d, N, B, k, kp):
+    log(f"five to eight tokens d={d} N={N} B={B} k={k} kp={kp}")
+    L = I.ffn_layer(361 + B, d, N)
+    L["w1u"][N // 4:N // 4 + 40] = L["w1u"][N // 4]     # equal keys and activations
+    layer, scorer = T.make_ffn_layer(L)
+    x = I.tokens(362 + B, B, d)
+    x[B // 2] = 0                                       # every key ties at zero
+    T.check_ffn(layer, scorer, L, x, k, kp)
