@@ -343,8 +343,8 @@ def main():
         finally:
             hire.hire_set_stage_events(None)
         stage_us = dict(zip(stages, (acc / S).round(3).tolist()))
-        # execution span of the batch-1 scorer kernel without launch cost: per-workgroup wall clocks written by it
-        if fast:
+        # execution span of the one-token scorer kernel without launch cost: per-workgroup wall clocks written by it
+        if fast and B == 1 and scorer != "lowrank":
             clk = torch.zeros(2048, dtype=torch.int64, device="cuda")
             nwg = hire.hire_ffn_scorer_workgroups(N)
             hire.hire_set_scorer_clocks(clk)
@@ -405,7 +405,7 @@ def main():
         rows = sorted(prof, key=lambda r: -r[1] * r[2])
         if rows:
             name, calls, avg = rows[0]
-            per_launch = {"k_gather_dot_mfma": fby["w1_gather"] + B * d * 2,
+            per_launch = {"k_filter_units": fby["w1_gather"] + B * d * 2,
                           "k_scorer_int4_mfma": fby["scorer"] + B * d}.get(name.split("<")[0].replace("hire::", ""))
             roofline = {"bound": "hbm", "kernel": name, "achieved": (round(per_launch / (avg * 1e-6) / 1e9, 1)
                                                                        if per_launch else None),

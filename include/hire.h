@@ -77,8 +77,9 @@ typedef struct hire_ffn_layer {
   const float* lr_a_scale; /* LRQ: fp32 [r] row scales of lr_a; otherwise unused */
   const float* lr_b_scale; /* LRQ: fp32 [d_ff] row scales of lr_b; otherwise unused */
   const float* row_norm_bounds; /* LOWRANK and LRQ, optional (may be NULL): DEVICE fp32 [2] written by hire_lr_prepare
-                             for this layer.  With it a batch-1 step of a layer of at most 16384 units takes the same
-                             short kernel sequence as with the int4 scorer; the results do not depend on it. */
+                             for this layer.  With it steps of one to four tokens of a layer of at most 16384 units
+                             take the same short kernel sequence as with the int4 scorer; the results do not depend
+                             on it, nor on the values in it. */
 } hire_ffn_layer;
 
 /* The classifier of eq. (1): logits = W x, one row per class. */
@@ -112,7 +113,7 @@ const char* hire_last_launch_error(void);
  * scale_j), -7, 7) with fp32 division and round-half-even.  The codes are
  * written to q4_out in the library's packed layout (hire_pack_int4_bytes
  * bytes, opaque: the codes, then a short trailer that holds the largest row
- * scale, from which the batch-1 FFN step bounds its scorer keys), scales to
+ * scale, from which the steps bound their scorer keys), scales to
  * scale_out [rows].  cols must be a multiple of 32.  A blob must be passed to
  * the steps whole and unchanged.  Not part of the timed step. */
 size_t hire_pack_int4_bytes(int rows, int cols);
@@ -120,16 +121,18 @@ int hire_pack_int4(const void* w_bf16, int rows, int cols, void* q4_out, float* 
 
 /* HiRE-LR / HiRE-LRQ preparation (Sec. 3.2), optional and not part of the timed step: bounds2_out (DEVICE fp32 [2])
  * receives upper bounds of the largest row norm of L->w1u and (LOWRANK; 0 for LRQ, whose int4 copy of Z2 carries its
- * own bound) of L->lr_b (fp32 sums of squares, rounded up by more than their error).  Cauchy-Schwarz with the norms of the token and of Z1^T x then bounds every activation and every scorer
- * key of a step before it is computed, which the batch-1 kernels use to place their histograms.  L must be a
- * HIRE_SCORER_LOWRANK or HIRE_SCORER_LRQ layer; its row_norm_bounds field is not read here.  The values must be recomputed when
- * w1u or lr_b change.  Returns HIRE_EINVAL for a NULL or misaligned argument or another scorer kind. */
+ * own bound) of L->lr_b (fp32 sums of squares, rounded up by more than their error).  Cauchy-Schwarz with the norms of
+ * the token and of Z1^T x then bounds every activation and every scorer key of a step before it is computed, which the
+ * kernels for few tokens use to place their histograms.  L must be a HIRE_SCORER_LOWRANK or HIRE_SCORER_LRQ layer; its
+ * row_norm_bounds field is not read here.  The values should be recomputed when w1u or lr_b change: others cost time
+ * (selections without histograms), not correctness.  Returns HIRE_EINVAL for a NULL or misaligned argument or another
+ * scorer kind. */
 int hire_lr_prepare(const hire_ffn_layer* L, float* bounds2_out, void* stream);
 
 /* Must be called once on a workspace after its memory was allocated (or reused for anything else) and before
- * the first step that uses it: clears the marker at the head of the workspace that tells the batch-1 FFN
- * kernels whether their key histogram is in the clean state the previous step left.  Steps keep that state
- * consistent among themselves afterwards. */
+ * the first step that uses it: clears the markers at the head of the workspace that tell the FFN kernels for few
+ * tokens and the selections on long rows whether their key histograms are in the clean state the previous step left.
+ * Steps keep that state consistent among themselves afterwards, also where one ends half-way (HIRE_ELAUNCH). */
 int hire_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 
 /* Workspace sizes in bytes for one step with the given batch / k / k'.  0 when the sizes are invalid (B outside
@@ -155,6 +158,10 @@ size_t hire_topk_workspace_bytes(int B, int N, int k, int flags);
  * topk_val fp32 [B,k] = h in the same order; cand_idx int32 [min(B*k', d_ff)]
  * = U ascending (entries past |U| are left untouched); n_cand = |U| (one
  * int32); scorer_acc int32 [B, d_ff] = the integer scores (INT4 only).
+ * The selected sets are always those of h in fp64.  The h handed out and used in step 5 is rounded once from fp64 to
+ * fp32, except in steps of 16 tokens and more whose unions can hold 1025 to 16384 units (min(B*k', d_ff), an even
+ * number) and whose rows are at most 32768 long: there it is a sum of fp32 segments away from the k-th value, within
+ * 2^-17 |u_j| |x_b| of h (beyond 32 tokens 2^-16; measured: at most 2.3 units of 2^-24 h, mean 0.5).
  * Requires 1 <= k <= k' <= d_ff, 1 <= B <= HIRE_MAX_BATCH. */
 int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kprime, float* y, int32_t* topk_idx,
                   float* topk_val, int32_t* cand_idx, int32_t* n_cand, int32_t* scorer_acc, void* workspace,

@@ -23,29 +23,30 @@ extern "C" {
  * 3 resolving the threshold bin (rows beyond 32768) and union compaction where the gather does not do it itself
  * (bitmaps beyond 8192 words), 4 exact scores on the candidates (with the union compaction in its prologue),
  * 5 exact top-k, 6 second layer; event 7 closes the step.  The softmax step ends with
- * event 6 after its stage 5 (top-k + softmax).  The batch-1 FFN step with the int4 scorer runs four kernels
- * and records five events: 0 scorer (with token quantisation), 1 k'-selection + exact scores on the candidates,
- * 2 k-selection + second-layer partial sums, 3 final reduction; event 4 closes the step.
+ * event 6 after its stage 5 (top-k + softmax).  FFN steps of few tokens that take the short kernel sequence record
+ * four events: 0 scorer (with token quantisation or projection), 1 k'-selection + exact scores on the candidates,
+ * 2 k-selection + second layer; event 3 closes the step.  The sharded step records three: 0 the shards, 1 the sum over
+ * them; event 2 closes it.  An event that the runtime refuses ends the step there (HIRE_ELAUNCH).
  * Do not use while the stream is being captured. */
 #define HIRE_NUM_STAGE_EVENTS 8
 void hire_set_stage_events(void** events);
 
-/* Testing aid; synchronises the stream.  host_out2 (HOST memory, two uint32) receives how many batch-1 FFN
- * steps on this workspace, since it took its steady state, had to find the k'-th scorer key (first counter)
- * or the k-th activation (second) without the key histogram: a slower, equally exact route taken for unusual
- * value distributions. */
+/* Testing aid; synchronises the stream.  host_out2 (HOST memory, two uint32) receives how many times FFN steps of
+ * few tokens on this workspace, since it took its steady state, had to find a token's k'-th scorer key (first counter)
+ * or its k-th activation (second) without the window histogram: a slower, equally exact route taken for unusual
+ * value distributions and for keys that their bounds do not hold for. */
 int hire_debug_fast_fallbacks(const void* workspace, uint32_t* host_out2, void* stream);
 
-/* Testing aid; synchronises the stream.  State that batch-1 FFN steps keep at the head of their workspace between
+/* Testing aid; synchronises the stream.  State that FFN steps of few tokens keep near the head of their workspace between
  * steps, read back to host_out3 (HOST memory, three uint32): [0] 1 if the marker is set that says "the histogram of
- * the scorer keys is all zero" (set by every completed step), else 0; [1] the number of counters of that histogram
+ * the (first) token's scorer keys is all zero" (taken away when a step starts, set by every completed one), else 0; [1] the number of counters of that histogram
  * that are not zero (0 after any completed step); [2] the sum of the counters of the histogram of the exact
  * activations, which the next step clears: after a step, the number of its candidates with a positive activation
  * that lie inside the histogram's window.  Allocates a host buffer for the copy. */
 int hire_debug_fast_state(const void* workspace, uint32_t* host_out3, void* stream);
 
 /* Testing aid; synchronises the stream.  host_out3 (HOST memory, three uint32) receives, for steps on the general
- * kernel sequence (softmax steps, FFN steps at batch > 1 or with the low-rank scorer), since this workspace took
+ * kernel sequence (softmax steps, FFN steps that do not take the short sequence for few tokens), since this workspace took
  * its steady state for the current shapes: [0] how many tokens of long-row steps (rows beyond 32768, selected by
  * many workgroups through key histograms in the workspace) had their k'-th scorer key found by the streaming
  * selection instead; [1] how many single-workgroup selections (k' on shorter rows, k on the activations) found
@@ -55,7 +56,7 @@ int hire_debug_fast_state(const void* workspace, uint32_t* host_out3, void* stre
 int hire_debug_general_fallbacks(const void* workspace, uint32_t* host_out3, void* stream);
 
 /* Measurement aid (per calling thread).  device_buf: DEVICE buffer of at least 16 KiB, or NULL to switch off.
- * While set, every workgroup g of the batch-1 FFN scorer kernel stores the 100 MHz wall clock at its start and
+ * While set, every workgroup g of the one-token FFN scorer kernel of the int4 scorers stores the 100 MHz wall clock at its start and
  * at its end into device_buf[2g] and device_buf[2g+1] (uint64); the span from the smallest start to the largest
  * end over the hire_ffn_scorer_workgroups(d_ff) workgroups is the kernel's execution time without launch cost. */
 int hire_set_scorer_clocks(void* device_buf, size_t bytes);
@@ -74,8 +75,8 @@ int hire_debug_plain_copy(const void* src, void* dst, size_t bytes, void* stream
 int hire_debug_filter_stage(const void* W, const void* x, int B, int d, int rows, const int32_t* rows_dev, float* stored,
                             float* xnorm, uint32_t* wnorm_max, float* err_c, void* stream);
 
-/* Testing aid (per calling thread): with on != 0 every step takes the general kernel sequence, also where the
- * batch-1 fast sequence would apply.  Both produce the same outputs. */
+/* Testing aid (per calling thread): with on != 0 every step takes the general kernel sequence, also where a shorter
+ * one for few tokens would apply.  Both produce the same outputs. */
 void hire_force_generic_path(int on);
 
 /* Testing aid (per calling thread): with on != 0 the FFN step at batch > 1 computes the exact pre-activation of

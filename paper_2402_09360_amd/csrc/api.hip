@@ -198,9 +198,9 @@ thread_local hipError_t g_last_hip_error = hipSuccess;
 // Optional stage timing: when the caller has handed over events, event i is recorded on the stream in front of
 // stage i and one more after the last stage.
 thread_local hipEvent_t* g_stage_events = nullptr;
-thread_local int g_force_generic = 0;
+thread_local int g_force_generic = 0;      // testing: route every step through the general multi-kernel path
 thread_local int g_force_exact_stage = 0;  // testing: batches compute every candidate's activation in fp64
-thread_local unsigned long long* g_scorer_clocks = nullptr;  // testing: route every step through the general multi-kernel path
+thread_local unsigned long long* g_scorer_clocks = nullptr;  // measuring: where the one-token scorer leaves its clocks
 
 #define HIRE_STAGE(i, st)                                             \
   do {                                                                \
@@ -573,7 +573,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     return HIRE_OK;
   }
 
-  // steps 1-3.  Batches: filter and refine.  The exact stage runs on the bf16 matrix cores and stores fp32 values
+  // steps 1-3.  Batches: filter and refine (kFilterMinBatch).  The exact stage runs on the bf16 matrix cores and stores fp32 values
   // within a proven distance of the activations; the selection recomputes in fp64 those around every token's k-th
   // largest.  Whatever lies outside that band is on the same side of the threshold in fp64 as its stored value, so
   // the selected sets are those of the fp64 activations.

@@ -1,6 +1,6 @@
 // Exact selection of the largest keys of a workgroup's register-resident, non-negative keys (TopInd_k of
-// arXiv 2402.09360 Sec. 3.1, both lines of Algorithm 1), guided by a window histogram: shared by the batch-1
-// FFN kernels (histograms filled by the producing kernel, in the workspace) and by the per-token selection of
+// arXiv 2402.09360 Sec. 3.1, both lines of Algorithm 1), guided by a window histogram: shared by the FFN
+// kernels for few tokens (histograms filled by the producing kernel, in the workspace) and by the per-token selections of
 // the general route (histogram built in LDS).
 //
 // A fine bin is 2^14 consecutive fp32 bit patterns (exponent and nine mantissa bits), so few keys share a

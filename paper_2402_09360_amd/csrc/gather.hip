@@ -254,9 +254,15 @@ hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* l
                   static_cast<const uint2*>(list), Wd, m1, hd, y);
   };
   // The widest slices that still give a workgroup to (nearly) every compute unit and leave few of them out of the last
-  // round of 256: 320 or 384 workgroups of 256 columns lose to twice as many of 128, 256 and 512 win; of 128 columns 200
-  // to 256 and 320 are as good as or better than twice as many of 64, 126, 147 and 260 worse; 64 columns lose to 32 below
-  // half a workgroup per unit.
+  // round of 256.  us with slices of 256 / 128 / 64 / 32 columns, units drawn at random, W2 not in the caches, * the rule:
+  //   d = 2048, k = 819 of 16384:  5 tokens  9.0  7.0  6.4* 6.7    8   9.8  7.5  7.5* 7.2   12  11.1  8.6  9.5* 9.5
+  //     16  12.2  9.8* 10.3 12.1   24  13.9 13.8* 14.3 17.0   33  19.9 17.3* 19.6 21.5   64  21.6* 20.8 28.5 34.7
+  //   d = 800, k = 251 of 5003:    8  4.8 4.2 4.1* 4.2   33  5.1 4.9* 5.1 7.4   64  5.5* 5.6 7.7 10.6
+  //   d = 4096, k = 400 of 8192:   5  6.5 5.7 5.7* 6.4   16  9.5* 9.4 11.1 14.3   33  16.6 16.0* 20.2 26.5
+  //   d = 288, k = 1949 of 24000, 49 tokens  18.3 12.4 10.6* 10.5     d = 512, k = 900 of 20003, 16  9.7 7.1 6.0* 5.6
+  // Of 28 shapes 22 within 4 % of the best width, 12 tokens and the last of these 7 to 10 % off; where few rows make the
+  // reduction count more the rule is too narrow (d = 256, k = 52: 3.5 against 2.9; d = 1024, k = 205, 33 tokens: 6.2
+  // with 64 columns, 4.9 with 128).
   auto fill = [&](int n) { return (double)n / ((n + 255) / 256 * 256); };
   if (items(256) >= 250 && fill(items(256)) > 0.9) return go(k_w2_list<32, 4>, 256);
   if (items(128) >= 200 && fill(items(128)) > 0.6) return go(k_w2_list<16, 4>, 128);

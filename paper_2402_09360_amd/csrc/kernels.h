@@ -45,7 +45,7 @@ constexpr unsigned long long kSigOverlays = 1ull << 63;  // set in signatures of
 
 // ---- scorer.hip ------------------------------------------------------------
 // The packed blob is rows * cols / 2 bytes of codes followed by kPackTrailerBytes: the first trailer word holds the
-// largest row scale (float bits; all-zero rows left out), which the batch-1 FFN scorer turns into an upper bound
+// largest row scale (float bits; all-zero rows left out), which the scorers turn into an upper bound
 // of every key of a step; the rest is zero.
 constexpr size_t kPackTrailerBytes = 64;
 hipError_t launch_pack_int4(const uint16_t* w, int rows, int cols, uint32_t* q4, float* scale, hipStream_t s);
@@ -311,7 +311,7 @@ hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* l
                           const double* hd, float* y, hipStream_t s);
 
 // ---- ffn_fast.hip ----------------------------------------------------------
-// Batch-1 FFN step in three kernels; see the file header.  All pointers device.
+// FFN step of few tokens in three kernels; see the file header.  All pointers device.
 constexpr int kFastTokens = 8;               // most tokens of a step that takes this route
 constexpr size_t kFastRegionBytes = 256 + 2 * 8192 * 4;  // state and histograms of one token
 struct FfnFastArgs {
@@ -351,8 +351,8 @@ struct FfnFastArgs {
   int32_t* cand_scratch;
   int8_t* xq;
   float* sumabs;
-  // Low-rank scorer (lowrank, one token; otherwise the int4 one): keys are fp64 (keys64, [N] padded to
-  // a multiple of 2), t_partial holds lr_project_slices(d) * r doubles, norm_bounds the two row-norm bounds of
+  // Low-rank scorer (lowrank, up to four tokens; otherwise the int4 one): keys are fp64 (keys64, [B, key_stride], rows of
+  // whole 16-byte vectors), t_partial holds B * lr_project_slices(d) * r doubles, norm_bounds the two row-norm bounds of
   // hire_lr_prepare.  Plain units only (gs = 0, m1 = 0).
   bool lowrank;
   const void* lr_a;
@@ -361,14 +361,14 @@ struct FfnFastArgs {
   const float* norm_bounds;
   double* t_partial;
   double* keys64;
-  // int4 low-rank scorer (lrq): lr_a / lr_b are the packed blobs of Z1 transposed and Z2 with their scales, keys_t
-  // r + 4 floats for the intermediate; the keys are fp32 (keys); norm_bounds[0] bounds the rows of w1u
+  // int4 low-rank scorer (lrq, up to four tokens): lr_a / lr_b are the packed blobs of Z1 transposed and Z2 with their
+  // scales, keys_t B * r + 4 floats for the intermediate; the keys are fp32 (keys); norm_bounds[0] bounds the rows of w1u
   bool lrq;
   const float* lr_a_scale;
   const float* lr_b_scale;
   float* keys_t;
   hipEvent_t* stage_events;  // optional: 4 events recorded around the kernels
-  unsigned long long* scorer_clocks;  // optional: start/end wall clock (100 MHz ticks) of every scorer workgroup
+  unsigned long long* scorer_clocks;  // optional, one token: start/end wall clock (100 MHz ticks) of every scorer workgroup
 };
 int ffn_fast_score_blocks(int N);
 size_t ffn_fast_fallbacks_offset();  // two uint32 counters inside the region

@@ -157,7 +157,7 @@ def hire_version() -> int:
 
 NUM_STAGE_EVENTS = 8
 FFN_STAGES = ("quantise_x", "scorer", "select_kprime", "union", "gather_dot", "select_k", "second_layer")
-FAST_FFN_STAGES = ("scorer", "select_gather", "select_w2")   # batch 1
+FAST_FFN_STAGES = ("scorer", "select_gather", "select_w2")   # few tokens
 SOFTMAX_STAGES = ("quantise_x", "scorer", "select_kprime", "union", "gather_dot", "select_k_softmax")
 
 
@@ -197,7 +197,7 @@ def hire_debug_filter_stage(W: torch.Tensor, x: torch.Tensor, stream=None):
 
 
 def hire_debug_fast_state(workspace: torch.Tensor, stream=None):
-    """(marker set, non-zero counters of the key histogram, counted activations) of a batch-1 FFN workspace."""
+    """(marker set, non-zero counters of the key histogram, counted activations) of an FFN workspace's first token."""
     out = (C.c_uint32 * 3)()
     _check(_lib.hire_debug_fast_state(_ptr(workspace), out, _stream(stream)), "hire_debug_fast_state")
     return tuple(int(v) for v in out)
@@ -267,7 +267,7 @@ class FFNLayer:
 
     def __init__(self, w1u, w2u, q4=None, q4_scale=None, lr_a=None, lr_b=None, lrq=None, prepare=True):
         """lrq: (int4 blob of Z1 transposed, its scales [r], int4 blob of Z2, its scales [d_ff]) for HiRE-LRQ.
-        prepare: run hire_lr_prepare for a low-rank layer (False: its batch-1 steps take the general sequence)."""
+        prepare: run hire_lr_prepare for a low-rank layer (False: its steps of few tokens take the general sequence)."""
         for t in (w1u, w2u):
             assert t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()
         self.w1u, self.w2u, self.q4, self.q4_scale, self.lr_a, self.lr_b = w1u, w2u, q4, q4_scale, lr_a, lr_b
@@ -284,7 +284,7 @@ class FFNLayer:
         self.ref = C.byref(self.c)
         self.row_norm_bounds = None
         if self.kind in (SCORER_LOWRANK, SCORER_LRQ) and prepare:
-            # one-off preparation: row-norm bounds that let batch-1 steps take the short kernel sequence
+            # one-off preparation: row-norm bounds that let steps of few tokens take the short kernel sequence
             self.row_norm_bounds = torch.zeros(2, dtype=torch.float32, device=w1u.device)
             _lib.hire_lr_prepare.restype = _i
             _lib.hire_lr_prepare.argtypes = [C.c_void_p, _vp, _vp]
