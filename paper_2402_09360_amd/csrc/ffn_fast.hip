@@ -373,8 +373,8 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
 // where a unit is not shortlisted), so no list of candidates is needed in between; the caller's is written beside
 // kernel 3 (a 257th workgroup here would wait for a compute unit).  K: the keys' bit patterns, 32 bits for the int4
 // scorer's fp32 keys, 64 for the low-rank scorer's fp64 ones; LOADS: 16-byte loads of keys per thread.
-// Measured at the ~1B shape: 7.7 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
-// its rows.  Inside: 1.8 until the window is walked, 2.0 for the rows; the workgroups that own a key of the threshold bin
+// Measured at the ~1B shape: 7.9 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
+// its rows.  Inside: 1.8 until the window is walked, 1.3 to 2 for the rows; workgroups that own a key of the threshold bin
 // need 1.6 more for its list and are the last to end.
 constexpr int kGT = 1024;
 constexpr int kGW = kGT / kWave;
@@ -592,8 +592,8 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
 //
 // The selection works on the activations rounded to fp32 (rounding is monotone; the coefficients of the second layer are
 // these values anyway); the keys of the threshold bin, and a selection without histogram, go by the fp64 values.
-// Measured at the ~1B shape: 9.5 us with the reduction over the workgroups' shares and the shortlist's list in it.  Inside:
-// window walked 1.9, masks 0.6, bin settled 0.8, rows listed 0.5, rows 2.4 to 3.3, reduction 1.4.
+// Measured at the ~1B shape: 9.7 us with the reduction over the waves and the shortlist's list in it.  Inside: window
+// walked 1.5, masks 0.7, bin settled 0.6, rows listed 0.5, rows 2.8, reduction 0.8.
 constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
 using W2Shared = SelSharedT<kWT>;

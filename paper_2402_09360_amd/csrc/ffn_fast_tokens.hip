@@ -19,7 +19,7 @@ constexpr int kTokRows = 64;  // rows of a workgroup of the scorer
 // Kernel 1: scorer.  Every workgroup quantises the tokens itself (a kernel for that alone costs 3.3 us), kTW / TT waves
 // per token, then scores 64 rows on the int8 matrix cores, four rows per wave: v_mfma_i32_4x4x4 takes row l % 4 and
 // token l % 4 from lane l and adds up sixteen blocks of columns l / 4 separately, so that a load covers 256 bytes of
-// four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 11.8 us against 3.3 +
+// four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 12.0 us against 3.3 +
 // 7.6 with the quantisation in front; 5.6 of them until the keys are stored, the rest is the 33000 counts in memory.
 // TT: tokens rounded up to four or eight; VECS: 16-byte vectors of a token per thread.  LRQ: as in k_fast_score_int4.
 struct FastScoreTokens {
@@ -287,8 +287,8 @@ __device__ __forceinline__ Cut<K> streaming_cut(const K* keys, int n, int k, Sel
 }
 
 // K: the keys' bit patterns.  TT: tokens rounded up to four or eight.
-// Measured at the ~1B shape and four tokens: 18.7 us (3.4 until the rows are known, 8.5 for the 9600 rows of the union,
-// 0.7 for the outputs; workgroups that have to settle a key of a threshold bin are 3 us behind), against 5.8 + 13 + the
+// Measured at the ~1B shape and four tokens: 19.9 us (3.8 until the rows are known, 8.7 for the 9600 rows of the union,
+// 0.8 for the outputs; workgroups that have to settle a key of a threshold bin are 3 us behind), against 5.8 + 13 + the
 // larger part of 9.9 us for the three kernels of the longer sequence.
 template <typename K, int TT>
 __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) {

@@ -94,7 +94,8 @@ struct MultiHeader {
   uint32_t layout_b;  // batch size the region was last laid out and cleaned for
   uint32_t stamps;    // times the region was found unstamped, cleared and stamped since the workspace was initialised
   uint32_t fallbacks; // tokens that took the streaming selection since the region was stamped
-  uint32_t pad[59];
+  uint32_t busy;      // not 0: keys have been counted that no kernel has taken out again (set_busy)
+  uint32_t pad[58];
 };
 struct AmbEntry {
   uint32_t okey;
@@ -129,6 +130,10 @@ __host__ __device__ inline MultiRegion carve_multi(MultiHeader* hdr, void* body,
   r.hist = reinterpret_cast<uint32_t*>(p);
   return r;
 }
+// By one thread of a kernel that counts keys; the resolving kernel, which restores the histograms, resets it.  A step that
+// ends in between (a launch that the runtime refused, a route that does not come to the histograms) leaves it set, and
+// the next step on the workspace drops the cookie.
+__device__ __forceinline__ void set_busy(MultiHeader* h) { h->busy = 1u; }
 // True when the histograms of this layout are known to be all zero between steps.
 __device__ __forceinline__ bool multi_hist_ok(const MultiHeader* h, int B) {
   return h->cookie == kMultiCookie && h->layout_b == (uint32_t)B;
@@ -175,10 +180,12 @@ __device__ __forceinline__ void general_header_check(GeneralHeader* gh, unsigned
     const unsigned long long n = *cookie - kCookie;
     if (n > 1ull && n <= (unsigned long long)kFastTokens) *cookie = kCookie + 1ull;
   }
-  if (gh->layout_sig == sig) return;  // uniform
+  const bool same = gh->layout_sig == sig;
+  if (same && gh->multi.busy == 0u) return;  // uniform
   if (tid == 0) {
     gh->multi.cookie = 0ull;
-    gh->window_misses = 0u;
+    gh->multi.busy = 0u;
+    if (!same) gh->window_misses = 0u;
   }
   __syncthreads();  // every thread has compared before the signature changes
   if (tid == 0) gh->layout_sig = sig;

@@ -139,6 +139,7 @@ __global__ __launch_bounds__(256) void k_scorer_int4(const uint4* __restrict__ q
   extern __shared__ uint4 xs[];  // [BT][d/16] : token tile, 16 int8 per uint4
   __shared__ uint32_t wmax_sh[4][BT];
   const bool hist_on = mr.hist != nullptr && multi_hist_ok(mr.hdr, B);
+  if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
   const int cpr = d / 32;        // 16-byte chunks per packed row
   const int xv = d / 16;         // uint4 per token row of xq
   const int lane = lane_id();
@@ -248,6 +249,7 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
   const int lane = lane_id();
   const int total_waves = (int)gridDim.x * 4;
   const bool hist_on = mr.hist != nullptr && multi_hist_ok(mr.hdr, 1);
+  if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
   const int groups = (N + kScorerRPW - 1) / kScorerRPW;
 
   auto fetch = [&](int g, uint4 (&wv)[kScorerRPW][CH]) {
@@ -560,6 +562,7 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1_short(const uint4* __res
   const int cpr = d / 32;
   const int lane = lane_id(), sub = lane % LPR, rsub = lane / LPR;
   const bool hist_on = mr.hist != nullptr && multi_hist_ok(mr.hdr, 1);
+  if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
   const int csub = min(sub, cpr - 1);
   const int trips = (N + kRowsPerTrip - 1) / kRowsPerTrip, stride = (int)gridDim.x * 4;
   auto fetch = [&](int trip, uint4 (&wv)[kLoads], float (&sc)[kLoads]) {

@@ -40,6 +40,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void k_scorer_int4_mfma(const uint
   const int xv = d / 16;               // uint4 per token
   const int nseg = (cpr + KI * 4 - 1) / (KI * 4);
   const bool hist_on = mr.hist != nullptr && multi_hist_ok(mr.hdr, B);
+  if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
   uint32_t wmax[CT][4];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)

@@ -512,6 +512,7 @@ __global__ __launch_bounds__(kSelThreads) void k_count_f32(const float* __restri
   __shared__ uint32_t cnt[kHistWindow];
   if (!multi_hist_ok(mr.hdr, B)) return;
   const int b = (int)blockIdx.y, tid = (int)threadIdx.x;
+  if (blockIdx.x == 0 && b == 0 && tid == 0) set_busy(mr.hdr);
   const float* row = keys + (size_t)b * N;
   const int i0 = (int)blockIdx.x * (kSelThreads * kCountKeys);
   float v[kCountKeys];
@@ -663,6 +664,7 @@ __global__ __launch_bounds__(kSelThreads) void k_resolve_compact(const float* __
     HIRE_TS(43);
     __syncthreads();  // every thread has read amb_n[b]
     if (tid == 0) mr.amb_n[b] = 0u;
+    if (tid == 0 && b == 0) mr.hdr->busy = 0u;
     HIRE_TS(44);
   } else {
     const int c = (int)blockIdx.x - 1, nc = (int)gridDim.x - 1;
@@ -1096,7 +1098,7 @@ __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4
 // edge of its fine bin.  With M maxima about -M ln(1 - k/M) entries reach it, 66 for k = 64 of 1024; the row itself
 // is passed over once, against the mark.  The entries go through an LDS list of kSmList; rows with more of them (many
 // equal logits, fewer maxima than k) take several rounds, each merged with the best k so far.
-// Measured at 64 tokens, 57600 entries: 13.7 + 7.0 us, 16 tokens, 16000 entries: 7.9 + 7.1.  One kernel with one
+// Measured at 64 tokens, 57600 entries: 12.5 + 6.8 us, 16 tokens, 16000 entries: 8.5 + 6.9.  One kernel with one
 // workgroup per token and a histogram of the whole row: 31 and 21 us, half of it the products and a ranking loop of
 // one thread per entry.
 constexpr int kSmList = 1024;

@@ -148,3 +148,34 @@ def test_static_scratch_takes_large_batches_with_small_unions(hire, oracle, d, N
         T.compare_ffn(static(layer, x, k, kp), want)
         for _ in range(2):
             T.compare_ffn(static(small_layer, xs, 30, 150), want_small)
+
+
+@pytest.mark.parametrize("B,stages", [(1, 2), (2, 3)])
+def test_long_rows_after_a_step_that_ended_half_way(hire, oracle, B, stages):
+    """The general sequence on rows beyond 32768 keeps key histograms in the workspace: counted by the scorer (one token)
+    or by a pass of the selection (two), restored by the kernel that resolves the threshold bin, which does not run here."""
+    d, c, k, kp = 256, 40000, 16, 400
+    W = I.classifier(345, c, d)
+    layer, scorer = T.make_softmax_layer(W)
+    ws = hire.alloc_workspace(hire.hire_softmax_workspace_bytes(layer, B, k, kp))
+    hire.hire_force_generic_path(True)
+    try:
+        T.run_softmax(layer, I.tokens(346, B, d), k, kp, ws=ws, steps=3)
+        assert hire.hire_debug_general_fallbacks(ws) == (0, 0, 1)
+        log(f"long rows B={B}: ends after {stages} stages")
+        _end_after(hire, stages, lambda: T.run_softmax(layer, I.tokens(347, B, d), k, kp, ws=ws))
+        x = I.tokens(348, B, d)
+        want = oracle.softmax_step(W, scorer, x, k, kp, want_acc=True)
+        for got in T.run_softmax(layer, x, k, kp, ws=ws, steps=3):
+            T.compare_softmax(got, want)
+        assert hire.hire_debug_general_fallbacks(ws) == (0, 0, 2)     # cleared and stamped once more
+    finally:
+        hire.hire_force_generic_path(False)
+    for got in T.run_softmax(layer, x, k, kp, ws=ws, steps=2):        # the sequence from the scorer's maxima
+        T.compare_softmax(got, want)
+    hire.hire_force_generic_path(True)
+    try:
+        for got in T.run_softmax(layer, x, k, kp, ws=ws, steps=2):    # and the histograms behind it
+            T.compare_softmax(got, want)
+    finally:
+        hire.hire_force_generic_path(False)
