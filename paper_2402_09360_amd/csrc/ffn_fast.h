@@ -10,7 +10,7 @@ namespace hire {
 
 // State of the route at the head of every workspace, one region per token.  The consumers of a window histogram take
 // its counts for the keys' own, so it has to be exact whenever it is used.  Two things see to that:
-//  * The histograms of the keys are zero when a step that uses them starts.  The step's first kernel takes the cookie
+//  * The histograms of the keys are zero when a step that uses them starts.  The step's scorer kernel takes the cookie
 //    away, leaving the number of clean regions in `clean` for the kernels that follow, and the last one, which clears the
 //    histograms, gives it back: a step that ends in between (a launch that the runtime refused) leaves no cookie behind,
 //    and the next step selects without histograms.
@@ -37,7 +37,7 @@ struct FastRegion {
 static_assert(offsetof(FastRegion, zeros) % 16 == 0 && offsetof(FastRegion, hist1) == 256, "region layout");
 static_assert(sizeof(FastRegion) == kFastRegionBytes, "region size");
 
-// By one thread of a step's first kernel, with the cookie as it was found (asked for early: a round trip to memory): if
+// By one thread of a step's scorer kernel, with the cookie as it was found (asked for early: a round trip to memory): if
 // there is one, it is taken away.
 __device__ __forceinline__ void take_cookie(FastRegion* first, unsigned long long cookie) {
   const unsigned long long n = cookie - kCookie;
