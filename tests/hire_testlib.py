@@ -128,7 +128,7 @@ def run_ffn_group(layer, x_bits, k, kprime, g, debug=True, steps=1, ws=None):
 
 def check_ffn_group(layer, scorer, L, x_bits, k, kprime, g):
     """Group-sparse step: three steps on one workspace (batch 1 with groups of eight: first-use route, then twice
-    the steady-state route of the four-kernel sequence) and three more through the general kernel sequence, all
+    the steady-state route of the three-kernel sequence) and three more through the general kernel sequence, all
     compared with the oracle."""
     from oracle import hire_oracle as O
     from paper_2402_09360_amd import hire

@@ -117,7 +117,7 @@ def test_topk_select_long_rows_steady_state(hire, oracle):
     (64, 100, 2, 100, 100),         # k = k' = N: dense FFN
     (128, 2000, 5, 1, 1),           # k = k' = 1
     (512, 3000, 64, 150, 600),      # maximum batch
-    (96, 777, 1, 40, 160),          # batch 1 (four-kernel route), ragged
+    (96, 777, 1, 40, 160),          # batch 1 (three-kernel route), ragged
     (64, 100, 1, 100, 100),         # batch 1, k = k' = N
     (128, 2000, 1, 1, 1),           # batch 1, k = k' = 1
     (2048, 16384, 1, 4000, 16384),  # batch 1, every unit is a candidate, large k
@@ -145,7 +145,7 @@ def test_ffn_step_degenerate_tokens(hire, oracle):
 
 
 def test_ffn_step_batch1_degenerate(hire, oracle):
-    """Batch 1 through the four-kernel route: an all-zero token, and a layer with many identical rows
+    """Batch 1 through the three-kernel route: an all-zero token, and a layer with many identical rows
     (crowded threshold bin, ties settled by index)."""
     d, N, k, kp = 128, 600, 20, 80
     L = I.ffn_layer(74, d, N)
@@ -369,7 +369,7 @@ def test_ffn_group_step_small(hire, oracle, d, N, B, k, kp, g):
 
 
 def test_ffn_group_step_batch1_degenerate(hire, oracle):
-    """Batch 1, groups of eight through the four-kernel route: half of the groups have all-zero keys (the shortlist
+    """Batch 1, groups of eight through the three-kernel route: half of the groups have all-zero keys (the shortlist
     reaches into them: ties at zero go to the lower group), many identical groups (crowded threshold bin), and an
     all-zero token."""
     d, N = 128, 4800

@@ -64,7 +64,7 @@ def test_static_scratch_step_matches_workspace_step(hire):
 def test_static_scratch_step_refuses_what_does_not_fit(hire):
     L = I.ffn_layer(97, 256, 1024)
     layer, _ = T.make_ffn_layer(L)
-    # a descriptor of the ~1B layer shape at batch 64 needs about 15 MB of scratch; the check comes before any
+    # a descriptor of the ~1B layer shape at batch 64 needs about 13 MB of scratch; the check comes before any
     # pointer is used, so the small layer's buffers stand in
     import ctypes as C
     fake = hire._FFNLayer.from_buffer_copy(layer.c)
