@@ -271,20 +271,25 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     if (B == 1 && scorer_int4_fused_supported(d)) {
       HIRE_TRY(launch_scorer_int4_fused(qa, sc.lr_a_scale, xb, false, r, d, 0, s.keys_t, nullptr, header_only, s.bitmap,
                                         s.zero_words, s.sig, st));
+    } else if (B >= kMfmaMinBatch) {
+      ScorerTokens tk{s.xq, nullptr, false, nullptr, s.bitmap, s.zero_words, s.hist.header, s.sig};
+      if (scorer_mfma_quantises(B, r, d, false)) tk.x = xb;
+      else HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      HIRE_TRY(launch_scorer_int4_mfma(qa, sc.lr_a_scale, tk, B, r, d, 0, s.keys_t, r, nullptr, header_only, st));
     } else {
       HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
-      if (B >= kMfmaMinBatch)
-        HIRE_TRY(launch_scorer_int4_mfma(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, r, nullptr, header_only, st));
-      else
-        HIRE_TRY(launch_scorer_int4(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
+      HIRE_TRY(launch_scorer_int4(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
     }
-    // the second product's batch-1 kernel for short rows rounds the intermediate itself
-    t_is_f32 = B == 1 && scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r);
+    // the second product's kernels round the intermediate themselves where they quantise it
+    t_is_f32 = B == 1 ? scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r)
+                      : scorer_mfma_quantises(B, N, r, true);
     if (!t_is_f32) HIRE_TRY(launch_f32_to_bf16(s.keys_t, B * r, s.t, st));
   }
   if (int4_like) {
-    const bool fused = B == 1 && scorer_int4_fused_supported(sd);  // the scorer quantises the token itself
-    if (!fused)
+    // the scorer quantises the token itself
+    const bool fused = B == 1 && scorer_int4_fused_supported(sd);
+    const bool fused_batch = B >= kMfmaMinBatch && scorer_mfma_quantises(B, N, sd, t_is_f32);
+    if (!fused && !fused_batch)
       HIRE_TRY(launch_quantize_tokens(tok, B, sd, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
     HIRE_STAGE(1, st);
     int slots;
@@ -296,7 +301,9 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
                                         st));
       slots = scorer_int4_fused_maxima(N, sd);
     } else if (B >= kMfmaMinBatch) {
-      HIRE_TRY(launch_scorer_int4_mfma(static_cast<const uint32_t*>(q4), q4_scale, s.xq, B, N, sd, relu,
+      ScorerTokens tk{s.xq, nullptr, t_is_f32, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig};
+      if (fused_batch) tk.x = t_is_f32 ? static_cast<const void*>(s.keys_t) : static_cast<const void*>(tok);
+      HIRE_TRY(launch_scorer_int4_mfma(static_cast<const uint32_t*>(q4), q4_scale, tk, B, N, sd, relu,
                                        static_cast<float*>(s.keys), s.key_stride, scorer_acc, s.hist, st));
       slots = scorer_mfma_maxima(N);
     } else {

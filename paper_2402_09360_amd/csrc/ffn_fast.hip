@@ -987,8 +987,14 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     // scorer kernel on the int4 copy of Z2 with that intermediate as its token
     if (gs != 0 || a.m1 != 0 || a.r < 32 || a.r > 1024 || a.r % 32 != 0) return hipErrorInvalidValue;
     if (several) {
-      if ((e = launch_quantize_tokens(a.x, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
-      e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.xq, a.B, a.r, a.d, 0, a.keys_t,
+      ScorerTokens tok{};
+      if (scorer_mfma_quantises(a.B, a.r, a.d, false)) {
+        tok.x = a.x;
+      } else {
+        if ((e = launch_quantize_tokens(a.x, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
+        tok.xq = a.xq;
+      }
+      e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, tok, a.B, a.r, a.d, 0, a.keys_t,
                                   a.r, nullptr, HistRefs{nullptr, nullptr}, s);
       if (e != hipSuccess) return e;
       if ((e = launch_fast_score_tokens(a, a.keys_t, true, s)) != hipSuccess) return e;

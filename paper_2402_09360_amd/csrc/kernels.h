@@ -74,11 +74,23 @@ hipError_t launch_scorer_int4_fused(const uint32_t* q4, const float* scale, cons
 bool scorer_int4_fused_takes_f32(int d);
 int scorer_int4_fused_blocks(int N, int d);  // workgroups launch_scorer_int4_fused uses
 int scorer_int4_fused_maxima(int N, int d);  // maxima it leaves per token: one per workgroup, short rows one per wave
-// The same on the int8 matrix cores, for batches (scorer_mfma.hip); B <= 64.  keys: [B, stride].
-hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
+// The same on the int8 matrix cores, for batches (scorer_mfma.hip); B <= 64.  keys: [B, stride].  The tokens come as codes
+// (launch_quantize_tokens), or the scorer quantises them itself (scorer_mfma_quantises) and is then, in that kernel's
+// place, the step's first.
+struct ScorerTokens {
+  const int8_t* xq;          // [B, d] codes; or, with x:
+  const void* x;             // [B, d] bf16, or
+  bool f32;                  // fp32, which is rounded to bf16 (nearest even) first
+  float* sumabs;             // optional [B]: sums of the codes' absolute values
+  uint32_t* zero_ptr;        // words to clear
+  int zero_words;
+  void* header;              // general header to check against sig; optional
+  unsigned long long sig;
+};
+bool scorer_mfma_quantises(int B, int N, int d, bool f32);
+hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const ScorerTokens& tok, int B, int N, int d,
                                    int relu, float* keys, long long stride, int32_t* acc, const HistRefs& hr, hipStream_t s);
-int scorer_mfma_blocks(int N);
-int scorer_mfma_maxima(int N);  // maxima it leaves per token: one per wave
+int scorer_mfma_maxima(int N);  // maxima it leaves per token (long rows): two per wave
 
 // t[b,:] = bf16(Z1^T x_b); also clears zero_words words at zero_ptr and, as a step's first kernel, checks the
 // general header (optional) against the layout signature.

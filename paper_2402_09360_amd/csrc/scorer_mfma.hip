@@ -1,13 +1,11 @@
 // HiRE-Q scorer for batches (arXiv 2402.09360, Algorithm 1 line 1 with the int4 Zapprox of Sec. 3.2) on the
 // int8 matrix cores: acc[b, j] = sum_i q_j[i] xq[b, i] as 16x16x64 MFMA tiles, 16 tokens by 16 weight rows.
 //
-// A wave owns 16 consecutive rows of the packed int4 matrix - one contiguous block of memory - and keeps a
-// K segment of it in registers while it runs over the token tiles, so the weights cross HBM once whatever
-// the batch size.  The packed layout (scorer.hip) turns one dword into two registers of four signed bytes
-// equal to 16*code with two ANDs and a shift; these feed the MFMA directly and the sums are shifted back by
-// four bits at the end (every partial is a multiple of 16, so this is exact).  Which 16 of a segment's codes a
-// lane contributes to which MFMA does not matter as long as its token operand holds the activations of the
-// same 16 positions: a dot product does not care about the order of its terms.
+// The packed layout (scorer.hip) turns one dword into two registers of four signed bytes equal to 16*code with two ANDs
+// and a shift; these feed the MFMA directly and the sums are shifted back by four bits at the end (every partial is a
+// multiple of 16, so this is exact).  Which 16 of a row's codes a lane contributes to which MFMA does not matter as
+// long as its token operand holds the activations of the same 16 positions: a dot product does not care about the
+// order of its terms.
 //
 // Operand roles: tokens are the A matrix (rows), weights the B matrix (columns), so lane l of the result holds
 // weight row l % 16 for tokens 4 * (l / 16) .. + 3, and the 16 lanes of a DPP row store 16 consecutive keys
@@ -15,181 +13,398 @@
 #include "device_utils.h"
 #include "hist.h"
 #include "kernels.h"
+#include "rows_mfma.h"
 
 namespace hire {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
+struct ScorerBatch {
+  const uint4* q4;
+  const float* scale;
+  ScorerTokens tok;
+  int B, N, d, relu;
+  float* keys;
+  long long stride;
+  int32_t* acc_out;  // optional [B, N]
+  uint32_t* wgmax;   // optional [B, kWgMaxSlots]
+  int seg_steps;     // steps of 128 codes of a K segment, whose codes of all tokens are in LDS
+};
 
-constexpr int kMfmaWaves = 4;          // waves (16-row tiles) per workgroup
-constexpr int kMfmaRows = 16 * kMfmaWaves;
+enum ScorerSource { kCodes, kBf16, kF32 };
 
-// CT: token tiles of 16 (batch <= 16 * CT).  KI: 16-byte weight chunks a lane holds per K segment; a segment
-// covers KI * 128 codes.
-template <int CT, int KI>
-__global__ __launch_bounds__(64 * kMfmaWaves) void k_scorer_int4_mfma(const uint4* __restrict__ q4,
-                                                                      const float* __restrict__ scale,
-                                                                      const int8_t* __restrict__ xq, int B, int N, int d,
-                                                                      int relu, float* __restrict__ keys, long long stride,
-                                                                      int32_t* __restrict__ acc_out, MultiRegion mr) {
-  constexpr int kTok = 16 * CT;
-  constexpr int kSegQ = KI * 8;        // uint4 (16 int8) per token and segment
-  constexpr int kStride = kSegQ + 1;   // padded: the 16 token rows a DPP row reads land in different banks
-  extern __shared__ uint4 xs[];        // [kTok][kStride]
-  const int lane = lane_id(), w = wave_id(), jl = lane & 15, g = lane >> 4;
-  const int cpr = d / 32;              // 16-byte chunks per packed row
-  const int xv = d / 16;               // uint4 per token
-  const int nseg = (cpr + KI * 4 - 1) / (KI * 4);
-  const bool hist_on = mr.hist != nullptr && multi_hist_ok(mr.hdr, B);
-  if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
-  uint32_t wmax[CT][4];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wmax[ct][r] = 0u;
+// A workgroup has RW x KW waves: RW groups of RT row tiles of 16 rows, the steps of a K segment shared out over KW waves,
+// whose integer sums are added in LDS.  CT: token tiles of 16 (batch <= 16 CT).  P: steps (16 bytes per lane and tile)
+// requested together.
+//
+// KW > 1 (rows of the FFN and of the low-rank factors): a workgroup has one group of tiles and sixteen waves, so that the
+// staging of the tokens, the unpacking and the epilogue are each a sixteenth of the work: the kernel is bound by that chain
+// and not by memory.  d = 2048, 16384 rows, 16 / 32 / 64 tokens: 5.9 / 6.7 / 8.7 us, where a workgroup of four waves with
+// whole rows each took 8.2 / 9.3 / 12.5; 5003 rows of 800 codes, 33 tokens: 4.9 with 32 rows per workgroup, 5.4 with 64.
+//
+// KW = 1 (vocabularies): a workgroup of eight waves per compute unit stages the tokens once and runs on from tile to tile,
+// the next request always out ahead of the current product.  No load there sits behind a branch: the wait for one request
+// would become one for the next (68 us instead of 54 for 256000 rows of 2048 codes and 16 tokens).  16 / 32 / 64 tokens: 54 / 62 /
+// 85 us (56 / 67 / 118 with a workgroup's tile in registers as a whole and four waves); the 263 MB alone take 42 us with
+// loads of this pattern, the keys 8 to 12 more, and from 33 tokens on the products (30 us of matrix cores and LDS) and the
+// stores that a wave waits for between its tiles are not hidden by two waves per SIMD.
+//
+// kBf16, kF32: the workgroup quantises the tokens itself.  VECS: 16-byte vectors (of bf16 values, or of codes) of a token
+// per lane.
+template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
+__global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p) {
+  constexpr int NW = RW * KW, NT = kWave * NW, kTok = 16 * CT, kRows = 16 * RT * RW;
+  static_assert(RT == 1 || KW == 1, "tiles of a wave");
+  static_assert(SRC == kCodes || KW > 1, "vocabularies: a kernel in front quantises");
+  extern __shared__ uint4 xs[];  // [kTok][8 seg_steps + 1]: a token row's first chunk in another bank than its neighbours'
+  const int tid = (int)threadIdx.x, lane = lane_id(), jl = lane & 15, g = lane >> 4;
+  // known to be uniform: a matrix-core instruction must never sit behind a branch that is lowered to lane masking
+  const int w = __builtin_amdgcn_readfirstlane(wave_id()), rw = w % RW, kw = w / RW;
+  const int B = p.B, N = p.N, cpr = p.d / 32;  // 16-byte chunks per packed row
+  const int steps = (cpr + 3) / 4, seg_steps = p.seg_steps, nseg = (steps + seg_steps - 1) / seg_steps;
+  const int per = (seg_steps + KW - 1) / KW, nblk = (per + P - 1) / P;  // steps, requests of a wave per segment
+  const int xstride = 8 * seg_steps + 1;
 
-  // Weights of one K segment of the wave's 16 rows.  Clamped and unconditional: the loads must not wait for one
-  // another.  Plain loads: a load covers half a cache line per row, the next one the other half, so the line has
-  // to stay (streaming loads cost 7 % here).
-  uint4 wv[KI];
-  auto load_weights = [&](int tile, int seg) {
-    const uint4* wrow = q4 + (size_t)min(tile * kMfmaRows + w * 16 + jl, N - 1) * cpr;
-#pragma unroll
-    for (int it = 0; it < KI; ++it) wv[it] = wrow[min(seg * KI * 4 + it * 4 + g, cpr - 1)];
+  struct Request {
+    uint4 v[P][RT];
+    float sj[RT];
   };
-  for (int tile = (int)blockIdx.x; tile * kMfmaRows < N; tile += (int)gridDim.x) {
-    const int j0 = tile * kMfmaRows + w * 16;
-    const int j = j0 + jl;
-    const float sj = scale[min(j, N - 1)];
-    v4i acc[CT];
+  // A wave's request: P steps of its tiles and their row scales.  Past the row's end a lane loads its last chunk (the
+  // tokens' codes are zero there), past the matrix its last row (nothing is stored).
+  auto request = [&](Request& q, int tile, int seg, int blk) __attribute__((always_inline)) {
+    const int s0 = seg * seg_steps + kw * per + blk * P;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = v4i{0, 0, 0, 0};
-    for (int seg = 0; seg < nseg; ++seg) {
-      // issued first, the weights fly while the token tile is staged
-      load_weights(tile, seg);
-      if (nseg > 1 || tile == (int)blockIdx.x) {
-        __syncthreads();  // readers of the previous tile are done
-        // eight loads per thread go out together (clamped and unconditional, zeroed where they do not count when
-        // they are stored): a loop with one load per trip would pay a round trip to L2 per trip
-        // (with one stage per workgroup - up to 32 tokens - that round trip is paid once and the registers of a
-        // batch would cost a resident workgroup: one load per trip there)
-        constexpr int kStageBatch = CT >= 4 ? 8 : 1, kStageStep = 64 * kMfmaWaves;
-        for (int i0 = (int)threadIdx.x; i0 < kTok * kSegQ; i0 += kStageStep * kStageBatch) {
-          uint4 v[kStageBatch];
+    for (int rt = 0; rt < RT; ++rt) {
+      const int row = min(tile * kRows + (rw * RT + rt) * 16 + jl, N - 1);
+      q.sj[rt] = p.scale[row];
+      const uint4* wrow = p.q4 + (size_t)row * cpr;
 #pragma unroll
-          for (int u = 0; u < kStageBatch; ++u) {
-            const int i = min(i0 + u * kStageStep, kTok * kSegQ - 1);
-            const int t = i / kSegQ, q = i - t * kSegQ;
-            v[u] = reinterpret_cast<const uint4*>(xq + (size_t)min(t, B - 1) * d)[min(seg * kSegQ + q, xv - 1)];
-          }
+      for (int u = 0; u < P; ++u) q.v[u][rt] = wrow[min((s0 + u) * 4 + g, cpr - 1)];
+    }
+  };
+
+  // The tokens' codes of a segment into LDS, a wave whole tokens: load_tokens ahead of the first request (loads return in
+  // order), stage behind it.
+  constexpr int TPW = kTok / NW, kAhead = SRC == kCodes && TPW > 4 ? 4 : TPW;  // tokens of a wave, loaded ahead
+  static_assert(TPW >= 1 && TPW % kAhead == 0 && (SRC != kCodes || VECS == 2), "whole tokens, segments of 256 vectors");
+  uint4 tv[kAhead][VECS], tv2[kAhead][SRC == kF32 ? VECS : 1];
+  const int segq = 8 * seg_steps, xv = p.d / 16, nvec = p.d / 8;
+  auto load_codes = [&](uint4 (&v)[kAhead][VECS], int seg, int q0) __attribute__((always_inline)) {
 #pragma unroll
-          for (int u = 0; u < kStageBatch; ++u) {
-            const int i = i0 + u * kStageStep;
-            if (i < kTok * kSegQ) {
-              const int t = i / kSegQ, q = i - t * kSegQ;
-              const bool counts = t < B && seg * kSegQ + q < xv;
-              xs[t * kStride + q] = counts ? v[u] : make_uint4(0, 0, 0, 0);
-            }
-          }
-        }
-        __syncthreads();
+    for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+      for (int m = 0; m < VECS; ++m)
+        v[q][m] = reinterpret_cast<const uint4*>(p.tok.xq)[(size_t)min(w + (q0 + q) * NW, B - 1) * xv +
+                                                           min(seg * segq + m * kWave + lane, xv - 1)];
+  };
+  auto store_codes = [&](const uint4 (&v)[kAhead][VECS], int seg, int q0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+      for (int m = 0; m < VECS; ++m) {
+        const int t = w + (q0 + q) * NW, i = m * kWave + lane;
+        if (i < segq) xs[t * xstride + i] = t < B && seg * segq + i < xv ? v[q][m] : make_uint4(0, 0, 0, 0);
       }
+  };
+  auto load_tokens = [&](int seg) __attribute__((always_inline)) {
+    if constexpr (SRC == kCodes) {
+      load_codes(tv, seg, 0);
+    } else {
+      const uint4* x4 = reinterpret_cast<const uint4*>(p.tok.x);
 #pragma unroll
-      for (int it = 0; it < KI; ++it) {
-        const uint32_t keep = seg * KI * 4 + it * 4 + g < cpr ? 0xFFFFFFFFu : 0u;  // past the row's end: zeros
-        const uint32_t wd[4] = {wv[it].x & keep, wv[it].y & keep, wv[it].z & keep, wv[it].w & keep};
-        v4i wa, wb;
-        wa[0] = (int)(wd[0] & 0xF0F0F0F0u);
-        wa[1] = (int)((wd[0] << 4) & 0xF0F0F0F0u);
-        wa[2] = (int)(wd[1] & 0xF0F0F0F0u);
-        wa[3] = (int)((wd[1] << 4) & 0xF0F0F0F0u);
-        wb[0] = (int)(wd[2] & 0xF0F0F0F0u);
-        wb[1] = (int)((wd[2] << 4) & 0xF0F0F0F0u);
-        wb[2] = (int)(wd[3] & 0xF0F0F0F0u);
-        wb[3] = (int)((wd[3] << 4) & 0xF0F0F0F0u);
-        const int q = 2 * (it * 4 + g);  // the chunk's 32 codes meet token bytes 16q .. 16q + 31 of the segment
+      for (int q = 0; q < TPW; ++q)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const uint4 ta = xs[(ct * 16 + jl) * kStride + q], tb = xs[(ct * 16 + jl) * kStride + q + 1];
-          const v4i va = {(int)ta.x, (int)ta.y, (int)ta.z, (int)ta.w};
-          const v4i vb = {(int)tb.x, (int)tb.y, (int)tb.z, (int)tb.w};
-          acc[ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(va, wa, acc[ct], 0, 0, 0);
-          acc[ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vb, wb, acc[ct], 0, 0, 0);
+        for (int m = 0; m < VECS; ++m) {
+          const size_t at = (size_t)min(w + q * NW, B - 1) * nvec + min(m * kWave + lane, nvec - 1);
+          tv[q][m] = x4[SRC == kF32 ? 2 * at : at];
+          if constexpr (SRC == kF32) tv2[q][m] = x4[2 * at + 1];
+        }
+    }
+  };
+  auto stage = [&](int seg) __attribute__((always_inline)) {
+    if constexpr (SRC == kCodes) {
+      store_codes(tv, seg, 0);
+#pragma unroll
+      for (int q0 = kAhead; q0 < TPW; q0 += kAhead) {
+        uint4 v[kAhead][VECS];
+        load_codes(v, seg, q0);
+        store_codes(v, seg, q0);
+      }
+    } else {  // one segment
+#pragma unroll
+      for (int q = 0; q < TPW; ++q) {
+        const int t = w + q * NW;
+        float amax = 0.0f;
+#pragma unroll
+        for (int m = 0; m < VECS; ++m) {
+          if constexpr (SRC == kF32) {
+            auto rne = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; };
+            const uint4 a = tv[q][m], b = tv2[q][m];
+            tv[q][m] = make_uint4(rne(a.x) | (rne(a.y) << 16), rne(a.z) | (rne(a.w) << 16), rne(b.x) | (rne(b.y) << 16),
+                                  rne(b.z) | (rne(b.w) << 16));
+          }
+          const uint32_t ud[4] = {tv[q][m].x, tv[q][m].y, tv[q][m].z, tv[q][m].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(ud[e])), fabsf(bf16_hi(ud[e]))));
+        }
+        const TokenScale ts = token_scale(wave_max(amax));
+        float sabs = 0.0f;
+#pragma unroll
+        for (int m = 0; m < VECS; ++m)
+          if (m * kWave < 2 * segq) {  // uniform
+            const int i = m * kWave + lane;
+            const bool counts = t < B && i < nvec;
+            float sum8;
+            const uint2 codes = quantise8(tv[q][m], ts, &sum8);
+            sabs += counts ? sum8 : 0.0f;
+            if (i < 2 * segq) reinterpret_cast<uint2*>(xs + t * xstride)[i] = counts ? codes : make_uint2(0, 0);
+            __builtin_amdgcn_sched_barrier(0);  // (registers)
+          }
+        if (p.tok.sumabs != nullptr && blockIdx.x == 0) {
+          sabs = wave_sum(sabs);
+          if (lane == 0 && t < B) p.tok.sumabs[t] = sabs;
         }
       }
     }
-    // epilogue: this lane holds row j for tokens ct*16 + 4g + r
+  };
+  // every wave of the workgroup goes through the same tiles, segments and requests
+  auto stage_if_due = [&](int tile, int seg, int blk) __attribute__((always_inline)) {
+    if (blk == 0 && (nseg > 1 || tile == (int)blockIdx.x)) {
+      if (seg > 0 || tile != (int)blockIdx.x) {
+        load_tokens(seg);
+        lds_barrier();  // the readers of the segment before are done
+      }
+      stage(seg);
+      lds_barrier();
+    }
+  };
+
+  v4i acc[RT][CT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = v4i{0, 0, 0, 0};
+  auto multiply = [&](const Request& q, int seg, int blk) __attribute__((always_inline)) {
+    const int l0 = kw * per + blk * P, n = min(seg_steps, steps - seg * seg_steps);
+#pragma unroll
+    for (int u = 0; u < P; ++u)
+      if (blk * P + u < per && l0 + u < n) {  // uniform
+        v4i wa[RT], wb[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          const uint4 c = q.v[u][rt];
+          wa[rt] = v4i{(int)(c.x & 0xF0F0F0F0u), (int)((c.x << 4) & 0xF0F0F0F0u), (int)(c.y & 0xF0F0F0F0u),
+                       (int)((c.y << 4) & 0xF0F0F0F0u)};
+          wb[rt] = v4i{(int)(c.z & 0xF0F0F0F0u), (int)((c.z << 4) & 0xF0F0F0F0u), (int)(c.w & 0xF0F0F0F0u),
+                       (int)((c.w << 4) & 0xF0F0F0F0u)};
+        }
+        const uint4* col = xs + jl * xstride + 2 * ((l0 + u) * 4 + g);  // the chunk's 32 codes meet these token bytes
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          const uint4 ta = col[ct * 16 * xstride], tb = col[ct * 16 * xstride + 1];
+          const v4i va = {(int)ta.x, (int)ta.y, (int)ta.z, (int)ta.w}, vb = {(int)tb.x, (int)tb.y, (int)tb.z, (int)tb.w};
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[rt][ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(va, wa[rt], acc[rt][ct], 0, 0, 0);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[rt][ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vb, wb[rt], acc[rt][ct], 0, 0, 0);
+        }
+      }
+  };
+  // key of a sum of this lane's row
+  auto key_of = [&](int sum, float sj) __attribute__((always_inline)) {
+    float key = (float)sum * sj;
+    if (p.relu) key = key > 0.0f ? key : 0.0f;
+    return key + 0.0f;  // -0 -> +0
+  };
+
+  load_tokens(0);
+  if constexpr (KW > 1) {
+    if constexpr (SRC != kCodes) {
+      for (int i = (int)blockIdx.x * NT + tid; i < p.tok.zero_words; i += (int)gridDim.x * NT) p.tok.zero_ptr[i] = 0u;
+      if (blockIdx.x == 0) general_header_check(static_cast<GeneralHeader*>(p.tok.header), p.tok.sig);
+    }
+    const int tile = (int)blockIdx.x, j = tile * kRows + rw * 16 + jl;
+    Request q;
+    for (int seg = 0; seg < nseg; ++seg)
+      for (int blk = 0; blk < nblk; ++blk) {
+        request(q, tile, seg, blk);
+        stage_if_due(tile, seg, blk);
+        multiply(q, seg, blk);
+      }
+    lds_barrier();  // the codes' place takes the waves' sums
+    int* red = reinterpret_cast<int*>(xs);
+    constexpr int kUnits = CT * 4;
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) red[(w * kUnits + u) * kWave + lane] = acc[0][u / 4][u % 4];
+    lds_barrier();
+#pragma unroll
+    for (int u0 = 0; u0 < kUnits; u0 += KW) {
+      const int u = u0 + kw, t = u / 4 * 16 + 4 * g + u % 4;
+      if (u < kUnits) {  // uniform
+        int sum = 0;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) sum += red[((k * RW + rw) * kUnits + u) * kWave + lane];
+        sum >>= 4;
+        if (t < B && j < N) {
+          p.keys[(size_t)t * p.stride + j] = key_of(sum, q.sj[0]);
+          if (p.acc_out) p.acc_out[(size_t)t * N + j] = sum;
+        }
+      }
+    }
+  } else {
+    float wmax[CT][4];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) wmax[ct][r] = -INFINITY;
+    auto epilogue = [&](const float (&sj)[RT], int tile) __attribute__((always_inline)) {
+      const int j0 = tile * kRows + rw * RT * 16 + jl;
+      long long stride = p.stride;
+      asm("" : "+s"(stride));  // (or the loop keeps an address per value)
+      if ((tile + 1) * kRows <= N && B == kTok && p.acc_out == nullptr) {  // uniform: nothing to leave out
+        float* dst = p.keys + 4 * g * stride + j0;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              const float key = key_of(acc[rt][ct][r] >> 4, sj[rt]);
+              wmax[ct][r] = __builtin_amdgcn_fmed3f(key, wmax[ct][r], INFINITY);  // the larger one
+              dst[(ct * 16 + r) * stride + 16 * rt] = key;
+            }
+      } else {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              const int t = ct * 16 + r + 4 * g, j = j0 + 16 * rt, sum = acc[rt][ct][r] >> 4;
+              const float key = key_of(sum, sj[rt]);
+              if (j < N) wmax[ct][r] = fmaxf(wmax[ct][r], key);
+              if (t < B && j < N) {
+                p.keys[t * stride + j] = key;
+                if (p.acc_out) p.acc_out[(size_t)t * N + j] = sum;
+              }
+            }
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = v4i{0, 0, 0, 0};
+    };
+    Request qa, qb;
+    int tile = (int)blockIdx.x, seg = 0, blk = 0;
+    request(qa, tile, 0, 0);
+    if (nseg == 1) stage_if_due(tile, 0, 0);
+    // Multiplies one request, the next one out ahead of that, across segments and tiles.  false: that was the last.
+    auto turn = [&](Request& cur, Request& next) __attribute__((always_inline)) -> bool {
+      int ntile = tile, nsg = seg, nb = blk + 1;
+      if (nb == nblk) {
+        nb = 0;
+        if (++nsg == nseg) {
+          nsg = 0;
+          ntile += (int)gridDim.x;
+        }
+      }
+      const bool more = ntile * kRows < N;
+      request(next, more ? ntile : tile, nsg, nb);
+      __builtin_amdgcn_sched_barrier(0);
+      if (nseg > 1) stage_if_due(tile, seg, blk);
+      multiply(cur, seg, blk);
+      if (nb == 0 && nsg == 0) epilogue(cur.sj, tile);
+      tile = ntile;
+      seg = nsg;
+      blk = nb;
+      return more;
+    };
+    while (turn(qa, qb) && turn(qb, qa)) {
+    }
+    if (p.wgmax == nullptr) return;
+    // two of the largest keys per token and wave (scorer_mfma_maxima per token): across eight lanes of each DPP row
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
+        uint32_t v = wmax[ct][r] == -INFINITY ? 0u : order_key(wmax[ct][r]);
+        v = max(v, dpp_move<0x111, 0xF>(0u, v));
+        v = max(v, dpp_move<0x112, 0xF>(0u, v));
+        v = max(v, dpp_move<0x114, 0xF>(0u, v));
         const int t = ct * 16 + 4 * g + r;
-        const int sum = acc[ct][r] >> 4;
-        if (t < B && j < N) {
-          float key = (float)sum * sj;
-          if (relu) key = key > 0.0f ? key : 0.0f;
-          if (key == 0.0f) key = 0.0f;
-          keys[(size_t)t * stride + j] = key;
-          if (acc_out) acc_out[(size_t)t * N + j] = sum;
-          const uint32_t ok = order_key(key);
-          wmax[ct][r] = ok > wmax[ct][r] ? ok : wmax[ct][r];
-          if (hist_on && !(relu && key == 0.0f))
-            atomicAdd(&mr.hist[(size_t)t * kHistStride + kHistWindow + hist_bin(ok)], 1u);
-        }
+        if (jl % 8 == 7 && t < B) p.wgmax[(size_t)t * kWgMaxSlots + (blockIdx.x * NW + w) * 2 + jl / 8] = v;
       }
   }
-  if (mr.wgmax == nullptr) return;
-  // largest key per token and wave (scorer_mfma_maxima per token): across the 16 lanes of each DPP row
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      uint32_t v = wmax[ct][r];
-      auto mx = [](uint32_t a, uint32_t b) { return b > a ? b : a; };
-      v = mx(v, dpp_move<0x111, 0xF>(0u, v));
-      v = mx(v, dpp_move<0x112, 0xF>(0u, v));
-      v = mx(v, dpp_move<0x114, 0xF>(0u, v));
-      v = mx(v, dpp_move<0x118, 0xF>(0u, v));
-      const int t = ct * 16 + 4 * g + r;
-      if (jl == 15 && t < B) mr.wgmax[(size_t)t * kWgMaxSlots + blockIdx.x * kMfmaWaves + w] = v;
-    }
 }
 
-// Three workgroups per CU (what registers and LDS allow to be resident), each running over several tiles: the token
-// tile is staged once per workgroup.  Measured on the vocabulary matrix at batch 16: 70 us with one workgroup per
-// tile, 56 us with 768 workgroups; requesting the next tile's weights ahead of the epilogue made it slower (69 us).
-int scorer_mfma_blocks(int N) { return min((N + kMfmaRows - 1) / kMfmaRows, 768); }
-int scorer_mfma_maxima(int N) { return kMfmaWaves * scorer_mfma_blocks(N); }
-static_assert(kMfmaWaves * 768 <= kWgMaxSlots, "one maximum slot per wave of the scorer");
+constexpr int kVocabBlocks = 256, kVocabWaves = 8;  // KW = 1: workgroups, one per compute unit, and their waves
+constexpr int kSegSteps = 16;                       // most steps of a segment of codes
+constexpr int kVocabMinRows = 32769;                // rows from which KW = 1 serves; only these leave maxima
+static_assert(2 * kVocabBlocks * kVocabWaves <= kWgMaxSlots, "two maxima per wave");
 
-template <int CT, int KI>
-static hipError_t scorer_mfma_launch(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
-                                     int relu, float* keys, long long stride, int32_t* acc, const MultiRegion& mr, hipStream_t s) {
-  const size_t lds = (size_t)16 * CT * (KI * 8 + 1) * sizeof(uint4);
-  auto kernel = k_scorer_int4_mfma<CT, KI>;
+static int vocab_blocks(int N) { return min((N + 16 * kVocabWaves - 1) / (16 * kVocabWaves), kVocabBlocks); }
+int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
+
+// Where quantising in every workgroup is cheaper than a kernel in front (4.7 us): up to 32 tokens of 2048 values, a wave
+// then has one or two.  d = 2048, 16384 rows: 16 tokens 7.1 against 4.7 + 5.9 us, 32 tokens 10.2 against 4.7 + 6.7; 128 rows:
+// 5.7 against 4.7 + 3.1.  Beyond (33 tokens of 800 values: 9.8 against 4.2 + 4.9) a wave has four tokens, one after the other.
+// More than 16384 rows are more than one workgroup per compute unit, each with the same work.  The intermediate of the int4
+// low-rank scorer is short (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight
+// waves would take as long as the kernel in front (57.0 against 4.7 + 53.4).
+bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
+  if (N >= kVocabMinRows) return false;
+  return f32 ? d <= 1024 : B <= 32 && d <= 2048 && N <= 16384;
+}
+
+template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
+static hipError_t scorer_mfma_launch(ScorerBatch& p, int grid, hipStream_t s) {
+  const int steps = (p.d / 32 + 3) / 4, nseg = SRC == kCodes ? (steps + kSegSteps - 1) / kSegSteps : 1;
+  if (SRC != kCodes && p.d > 512 * VECS) return hipErrorInvalidValue;
+  p.seg_steps = (steps + nseg - 1) / nseg;
+  const size_t codes = (size_t)16 * CT * (8 * p.seg_steps + 1) * sizeof(uint4);
+  const size_t sums = KW > 1 ? (size_t)RW * KW * CT * 4 * kWave * sizeof(int) : 0;
+  const size_t lds = codes > sums ? codes : sums;
+  auto kernel = k_scorer_int4_mfma<CT, RT, RW, KW, P, SRC, VECS>;
   static std::atomic<size_t> raised_to{0};
   if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to); e != hipSuccess)
     return e;
-  return launch(kernel, dim3(scorer_mfma_blocks(N)), dim3(64 * kMfmaWaves), lds, s,
-                reinterpret_cast<const uint4*>(q4), scale, xq, B, N, d, relu, keys, stride, acc, mr);
+  return launch(kernel, dim3(grid), dim3(kWave * RW * KW), lds, s, p);
 }
 
-hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const int8_t* xq, int B, int N, int d,
+// Rows per workgroup for KW > 1: as many as still give a workgroup to every compute unit.
+template <int CT, int P, int SRC, int VECS>
+static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
+  if (p.N > 8192) return scorer_mfma_launch<CT, 1, 4, 4, P, SRC, VECS>(p, (p.N + 63) / 64, s);
+  if (p.N > 1024) return scorer_mfma_launch<CT, 1, 2, 8, 2, SRC, VECS>(p, (p.N + 31) / 32, s);
+  return scorer_mfma_launch<CT, 1, 1, 16, 1, SRC, VECS>(p, (p.N + 15) / 16, s);
+}
+
+template <int CT>
+static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
+  if (p.N >= kVocabMinRows) {
+    // 32 rows per wave read the tokens' codes half as often (64 tokens, 256000 rows of 2048: 85 against 92 us), unless they
+    // leave more of the last round of tiles empty (40 tokens, 90000 of 1024: 27.3 against 23.6)
+    auto rounds = [&](int rows) { return ((p.N + rows - 1) / rows + kVocabBlocks - 1) / kVocabBlocks; };
+    const int wide = 32 * kVocabWaves, blocks = min((p.N + wide - 1) / wide, kVocabBlocks);
+    if (CT == 4 && blocks == vocab_blocks(p.N) && 2 * rounds(wide) <= rounds(wide / 2))
+      return scorer_mfma_launch<CT, 2, kVocabWaves, 1, 2, kCodes, 2>(p, blocks, s);
+    return scorer_mfma_launch<CT, 1, kVocabWaves, 1, 4, kCodes, 2>(p, vocab_blocks(p.N), s);
+  }
+  if (p.tok.x == nullptr) return scorer_mfma_rows<CT, CT == 1 ? 4 : 2, kCodes, 2>(p, s);
+  if (p.tok.f32) return scorer_mfma_rows<CT, 2, kF32, 2>(p, s);
+  if constexpr (CT <= 2) return scorer_mfma_rows<CT, 4, kBf16, 4>(p, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const ScorerTokens& tok, int B, int N, int d,
                                    int relu, float* keys, long long stride, int32_t* acc, const HistRefs& hr, hipStream_t s) {
-  MultiRegion mr = multi_of(hr, B);
-  if (!multi_producer_counts(N, B)) mr.hist = nullptr;  // then the selection counts in a pass of its own
-  if (d <= 128) {  // short rows (the int4 low-rank scorer's second product): K segments no longer than a row
-    if (B <= 16) return scorer_mfma_launch<1, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-    if (B <= 32) return scorer_mfma_launch<2, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-    return scorer_mfma_launch<4, 1>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-  }
-  if (d <= 512) {
-    if (B <= 16) return scorer_mfma_launch<1, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-    if (B <= 32) return scorer_mfma_launch<2, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-    return scorer_mfma_launch<4, 4>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-  }
-  if (B <= 16) return scorer_mfma_launch<1, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-  if (B <= 32) return scorer_mfma_launch<2, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
-  return scorer_mfma_launch<4, 16>(q4, scale, xq, B, N, d, relu, keys, stride, acc, mr, s);
+  if (tok.x != nullptr && !scorer_mfma_quantises(B, N, d, tok.f32)) return hipErrorInvalidValue;
+  const MultiRegion mr = multi_of(hr, B);
+  ScorerBatch p{reinterpret_cast<const uint4*>(q4), scale, tok, B, N, d, relu, keys, stride, acc,
+                N >= kVocabMinRows ? mr.wgmax : nullptr, 0};
+  if (B <= 16) return scorer_mfma_tokens<1>(p, s);
+  if (B <= 32) return scorer_mfma_tokens<2>(p, s);
+  return scorer_mfma_tokens<4>(p, s);
 }
 
 }  // namespace hire
