@@ -319,7 +319,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     if (gs > 0 && !in_select)
       HIRE_TRY(launch_group_sums_f32(static_cast<const float*>(s.keys), B, N, Ns, gs, static_cast<float*>(s.gkeys), Ns,
                                      st));
-    if (many_wg && B >= 2 && s.max_ok && in_gather && maxima_select_worthwhile(N, kprime, slots) && !g_force_generic) {
+    if (many_wg && B >= 2 && s.max_ok && in_gather && maxima_select_worthwhile(B, N, kprime, slots) && !g_force_generic) {
       // long rows, batches: every token's k' largest keys from the bound that the scorer's maxima give (no key
       // histogram is filled or read, so none is stamped clean either)
       HIRE_TRY(launch_maxima_select(static_cast<const float*>(s.keys), B, N, sd, kprime, slots, q4, s.hist, s.sm1_slots,

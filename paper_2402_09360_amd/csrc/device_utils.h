@@ -178,6 +178,9 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
   return wave_prefix(v, 0, [](int a, int b) { return a + b; });
 }
 
+// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ __forceinline__ int ilog2_u64(uint64_t v) { return 63 - __clzll((long long)v); }
 
 }  // namespace hire

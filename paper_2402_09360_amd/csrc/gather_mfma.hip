@@ -210,8 +210,6 @@ constexpr int kFtRowBytes = 16 * kFtChunks;
 constexpr int kFtSteps = kFtChunks / 4;  // MFMA steps per stage
 constexpr int ft_stage_bytes(int TT) { return (kFtRows + 16 * TT) * kFtRowBytes; }
 
-// Workgroup barrier that orders LDS traffic only: loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 // Asynchronous load of 16 bytes per lane into LDS: lane l's go to lds_off + 16 l.  Not tracked by the compiler: the
 // barrier below waits for it.
 __device__ __forceinline__ void load_to_lds(const void* g, uint32_t lds_off) {

@@ -196,7 +196,7 @@ hipError_t launch_softmax_b1(const float* keys, int N, int d, int sd, int k, int
 // (which must be clear).  Replaces launch_mark_f32 + launch_resolve_compact; takes no histogram and leaves none.
 // slots: maxima_select_slot_bytes(B, N) of scratch.  maxima_select_worthwhile says whether the bound will serve.
 bool maxima_select_supported(int N);
-bool maxima_select_worthwhile(int N, int kprime, int n_max);
+bool maxima_select_worthwhile(int B, int N, int kprime, int n_max);
 size_t maxima_select_slot_bytes(int B, int N);
 hipError_t launch_maxima_select(const float* keys, int B, int N, int sd, int kprime, int n_max, const void* q4,
                                 const HistRefs& hr, void* slots, uint32_t* bitmap, hipStream_t s);

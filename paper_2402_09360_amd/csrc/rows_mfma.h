@@ -64,9 +64,6 @@ __device__ __forceinline__ void int4_rows_by_tokens(const uint4& wv, const uint4
   }
 }
 
-// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // out(r, t, relu(<row r, x_t>)) for r < cnt <= kMostRows rows and all tokens, by the workgroup.  v_mfma_f64_4x4x4: four
 // rows and four tokens at a time, in lane l row l % 4 of A, token l % 4 of B and column chunk l / 4 of both, element by
 // element of the sixteen-byte chunks (the order of the columns does not matter to a dot product).  A wave has SL slices

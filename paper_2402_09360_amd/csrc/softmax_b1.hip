@@ -35,10 +35,11 @@ namespace hire {
 constexpr int kSm1Threads = 1024;
 constexpr int kSm1Waves = kSm1Threads / kWave;
 constexpr int kSm1KeysPerThread = 2;    // one token: 2048 keys per workgroup of k_sm1_gather
-constexpr int kSm1KeysPerThreadB = 8;   // batches: 8192 (the grid has a token dimension as well)
+constexpr int kSm1KeysPerThreadB = 8;   // batches: 8192 per round (the grid has a token dimension as well)
 constexpr int kSm1Keys = kSm1KeysPerThread * kSm1Threads;
 constexpr int kSm1SlotsTotal = 4096;   // slots of all workgroups of k_sm1_gather together
 constexpr int kSm1SlotsMax = 1024;     // ... of one workgroup at most
+constexpr int kMaxWaveCap = 256;       // keys of a wave of k_max_gather
 constexpr int kSm1ListCap = 2048;      // entries of the final kernel's lists: a shortlist fits
 constexpr int kSm1SlotsPerThread = kSm1SlotsTotal / kSm1Threads;
 constexpr int kSm1DropBins = 256;      // fine bins above the superset's lower edge in which the D-th smallest key is looked for
@@ -48,6 +49,11 @@ static_assert(kSm1MaxRow / kSm1Keys * 32 <= kSm1SlotsTotal, "at least 32 slots p
 
 // Slots per workgroup of k_sm1_gather (kpt keys per thread): an even share of the total.
 inline int sm1_workgroups(int N, int kpt) { return (N + kpt * kSm1Threads - 1) / (kpt * kSm1Threads); }
+// Rounds of a workgroup of k_max_gather: two workgroups for every compute unit, at least four per token (their slots).
+inline int maxima_rounds(int B, int N) {
+  const int n_wg = sm1_workgroups(N, kSm1KeysPerThreadB), want = (n_wg * B + 511) / 512;
+  return want * 4 <= n_wg ? want : (n_wg >= 4 ? n_wg / 4 : 1);
+}
 inline int sm1_slots_per_wg(int N, int kpt = kSm1KeysPerThread) {
   const int n_wg = sm1_workgroups(N, kpt);
   return kSm1SlotsTotal / n_wg < kSm1SlotsMax ? kSm1SlotsTotal / n_wg : kSm1SlotsMax;
@@ -98,40 +104,15 @@ __device__ __forceinline__ int sm1_wave_base(const int* wave_cnt, int* total) {
   return w > 0 ? __builtin_amdgcn_readlane(p, w - 1) : 0;
 }
 
-// LOGITS = false (batches, launch_maxima_select): grid (workgroups, tokens), token b's keys, maxima and slots; the
-// entries carry no logit.  KPT: keys per thread (key q of thread t is KPT * 1024 * workgroup + 1024 q + t).
-template <bool LOGITS, int KPT>
-__global__ __launch_bounds__(kSm1Threads) void k_sm1_gather(const float* __restrict__ keys, int N, int d, int sd,
-                                                            int kprime, int n_max,
-                                                            const uint32_t* __restrict__ smax_word,
-                                                            const uint16_t* __restrict__ W,
-                                                            const uint16_t* __restrict__ x, MultiRegion mr,
-                                                            Sm1Entry* __restrict__ slots, int n_slots) {
-  __shared__ uint32_t win[kSm1WinBins];
-  constexpr int kCounts = KPT * kSm1Waves, kChunks = (kCounts + kWave - 1) / kWave;
-  __shared__ int wave_tot[kSm1Waves], wave_cnt[kChunks * kWave];
-  __shared__ int bc_slot;
-  __shared__ int loc_t[kSm1SlotsMax];
-  __shared__ uint32_t loc_key[kSm1SlotsMax];
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id(), b = (int)blockIdx.y;
-  const int i0 = (int)blockIdx.x * (KPT * kSm1Threads) + tid, c8 = d / 8;  // this thread's keys: i0 + 1024 q
-  keys += (size_t)b * N;
-  slots += (size_t)b * gridDim.x * n_slots;
-  HIRE_TS(20);
-  // everything this workgroup needs before it can decide, in one batch of loads
-  float key[KPT];
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) key[q] = keys[min(i0 + q * kSm1Threads, N - 1)];
-  const uint4 mx = reinterpret_cast<const uint4*>(mr.wgmax + (size_t)b * kWgMaxSlots)[tid];  // maxima 4 tid .. 4 tid + 3
-  const float smax = __uint_as_float(*smax_word);
-  uint4 xv[kSm1XChunks];
-  if (LOGITS) sm1_load_token(x, c8, xv);
-  reinterpret_cast<uint2*>(win)[tid] = make_uint2(0u, 0u);
-  if (tid == 0) bc_slot = 0;
-  __syncthreads();
-  HIRE_TS(21);
-
-  // ---- the maxima into the window; walk: the slot in which the running count, from the top, reaches k' ----
+// The scorer's maxima (four per thread: mx) into the window, walked from the top to the slot in which the running count
+// reaches k': the lower edge of that bin as an order key.  found: that there is such a slot.  win and bc_slot are clear.
+struct Sm1Bound {
+  bool found;
+  uint32_t okey_lb;
+};
+__device__ __forceinline__ Sm1Bound sm1_bound(const uint4& mx, float smax, int sd, int kprime, int n_max, uint32_t* win,
+                                              int* wave_tot, int* bc_slot) {
+  const int tid = (int)threadIdx.x, lane = lane_id();
   const int anchor = sm1_anchor_bin(smax, sd);  // the keys come from rows of sd codes
   const uint32_t mv[4] = {mx.x, mx.y, mx.z, mx.w};
 #pragma unroll
@@ -139,58 +120,76 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_gather(const float* __restr
     const int slot = anchor - (int)(mv[q] >> kSm1Shift);
     if (4 * tid + q < n_max && slot >= 0 && slot < kSm1WinBins) atomicAdd(&win[slot], 1u);
   }
-  __syncthreads();
+  lds_barrier();
   const uint2 hb = reinterpret_cast<const uint2*>(win)[tid];  // window slots 2 tid, 2 tid + 1
   const int s = (int)(hb.x + hb.y);
   const int incl = wave_scan_incl(s);
-  if (lane == kWave - 1) wave_tot[w] = incl;
-  __syncthreads();
+  if (lane == kWave - 1) wave_tot[wave_id()] = incl;
+  lds_barrier();
   int total;
   const int run = sm1_wave_base(wave_tot, &total) + incl - s;
-  const bool found = total >= kprime;  // the same in every workgroup: they all count the same maxima
-  if (found && run < kprime && kprime <= run + s) bc_slot = run + (int)hb.x >= kprime ? 2 * tid : 2 * tid + 1;
+  Sm1Bound r;
+  r.found = total >= kprime;  // the same in every workgroup: they all count the same maxima
+  if (r.found && run < kprime && kprime <= run + s) *bc_slot = run + (int)hb.x >= kprime ? 2 * tid : 2 * tid + 1;
+  lds_barrier();
+  r.okey_lb = (uint32_t)(anchor - *bc_slot) << kSm1Shift;
+  return r;
+}
+
+__global__ __launch_bounds__(kSm1Threads) void k_sm1_gather(const float* __restrict__ keys, int N, int d, int sd,
+                                                            int kprime, int n_max,
+                                                            const uint32_t* __restrict__ smax_word,
+                                                            const uint16_t* __restrict__ W,
+                                                            const uint16_t* __restrict__ x, MultiRegion mr,
+                                                            Sm1Entry* __restrict__ slots, int n_slots) {
+  __shared__ uint32_t win[kSm1WinBins];
+  constexpr int KPT = kSm1KeysPerThread, kCounts = KPT * kSm1Waves;
+  static_assert(kCounts <= kWave, "a lane per count");
+  __shared__ int wave_tot[kSm1Waves], wave_cnt[kCounts];
+  __shared__ int bc_slot;
+  __shared__ int loc_t[kSm1SlotsMax];
+  __shared__ uint32_t loc_key[kSm1SlotsMax];
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int i0 = (int)blockIdx.x * (KPT * kSm1Threads) + tid, c8 = d / 8;  // this thread's keys: i0 + 1024 q
+  HIRE_TS(20);
+  // everything this workgroup needs before it can decide, in one batch of loads
+  float key[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) key[q] = keys[min(i0 + q * kSm1Threads, N - 1)];
+  const uint4 mx = reinterpret_cast<const uint4*>(mr.wgmax)[tid];  // maxima 4 tid .. 4 tid + 3
+  const float smax = __uint_as_float(*smax_word);
+  uint4 xv[kSm1XChunks];
+  sm1_load_token(x, c8, xv);
+  reinterpret_cast<uint2*>(win)[tid] = make_uint2(0u, 0u);
+  if (tid == 0) bc_slot = 0;
   __syncthreads();
-  const uint32_t okey_lb = (uint32_t)(anchor - bc_slot) << kSm1Shift;  // lower edge of that bin
+  HIRE_TS(21);
+  const Sm1Bound lb = sm1_bound(mx, smax, sd, kprime, n_max, win, wave_tot, &bc_slot);
   if (blockIdx.x == 0 && tid == 0) {
-    mr.walk[4 * b + 1] = found ? 1 : 0;
-    mr.walk[4 * b + 2] = (int)okey_lb;
+    mr.walk[1] = lb.found ? 1 : 0;
+    mr.walk[2] = (int)lb.okey_lb;
   }
   HIRE_TS(22);
 
   // ---- this workgroup's keys at or above the edge, in index order (all of the first 1024, then the second) ----
   uint32_t okey[KPT];
   uint64_t ballot[KPT];
-  if (kCounts % kWave != 0 && tid < kChunks * kWave) wave_cnt[tid] = 0;  // the scan below reads whole chunks of 64
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     okey[q] = order_key(key[q]);
-    ballot[q] = __ballot(found && i0 + q * kSm1Threads < N && okey[q] >= okey_lb);
-  }
-  if (kCounts % kWave != 0) __syncthreads();
-#pragma unroll
-  for (int q = 0; q < KPT; ++q)
+    ballot[q] = __ballot(lb.found && i0 + q * kSm1Threads < N && okey[q] >= lb.okey_lb);
     if (lane == 0) wave_cnt[q * kSm1Waves + w] = __popcll(ballot[q]);
+  }
   __syncthreads();
-  int n_loc = 0;
-  {
-    // prefix over the KPT * 16 counts (key round q of wave w at q * 16 + w), 64 at a time
-    int p[kChunks], before[kChunks];
+  const int p = wave_scan_incl(lane < kCounts ? wave_cnt[min(lane, kCounts - 1)] : 0);  // key round q of wave w: lane 16 q + w
+  const int n_loc = __builtin_amdgcn_readlane(p, kWave - 1);
 #pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      p[c] = wave_scan_incl(wave_cnt[c * kWave + lane]);
-      before[c] = n_loc;
-      n_loc += __builtin_amdgcn_readlane(p[c], kWave - 1);
-    }
-    const int wv = __builtin_amdgcn_readfirstlane(w);
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int slot = q * kSm1Waves + wv;  // uniform over the wave
-      const int c = slot / kWave, l = slot % kWave;
-      const int pos = before[c] + (l > 0 ? __builtin_amdgcn_readlane(p[c], l - 1) : 0) + mask_prefix(ballot[q]);
-      if (((ballot[q] >> lane) & 1ull) && pos < n_slots) {
-        loc_t[pos] = tid + q * kSm1Threads;
-        loc_key[pos] = okey[q];
-      }
+  for (int q = 0; q < KPT; ++q) {
+    const int l = q * kSm1Waves + w;  // uniform over the wave
+    const int pos = (l > 0 ? __builtin_amdgcn_readlane(p, l - 1) : 0) + mask_prefix(ballot[q]);
+    if (((ballot[q] >> lane) & 1ull) && pos < n_slots) {
+      loc_t[pos] = i0 + q * kSm1Threads;
+      loc_key[pos] = okey[q];
     }
   }
   __syncthreads();
@@ -205,8 +204,8 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_gather(const float* __restr
     out.idx = -1;
     out.z = 0.0;
     if (e < n_take) {
-      const int j = (int)blockIdx.x * (KPT * kSm1Threads) + loc_t[e];
-      if (LOGITS) out.z = sm1_wave_dot(W + (size_t)j * d, c8, xv);
+      const int j = loc_t[e];
+      out.z = sm1_wave_dot(W + (size_t)j * d, c8, xv);
       out.okey = loc_key[e];
       out.idx = j;
     }
@@ -214,6 +213,72 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_gather(const float* __restr
     if (lane == 0 && e < n_slots) mine[e] = out;
   }
   HIRE_TS(23);
+}
+
+// Batches (launch_maxima_select), grid (workgroups, tokens): the keys of token b at or above its bound in the workgroup's
+// slots, without logits.  A wave has `rounds` times 512 adjacent keys, the next 512 requested while the current ones are
+// compared, and a list of its own, so that the row goes by without a barrier: few keys reach the bound (0.6 % of 256000 for
+// k' = 1024), and the rest cost a comparison each.  Counting the maxima is 2.5 us of a workgroup's time whatever its number
+// of rounds: batches take as many as leave two workgroups for every compute unit (maxima_rounds).  Bound: the read of the
+// keys (65 MB for 256000 classes, 64 tokens).  16.6 us there; 30.2 with one workgroup per 8192 keys, which ordered its keys
+// through barriers (16 tokens: 7.4, 10.2).
+__global__ __launch_bounds__(kSm1Threads) void k_max_gather(const float* __restrict__ keys, int N, int sd, int kprime, int n_max,
+                                                            const uint32_t* __restrict__ smax_word, MultiRegion mr,
+                                                            Sm1Entry* __restrict__ slots, int n_slots, int rounds) {
+  constexpr int KPT = kSm1KeysPerThreadB, kRound = KPT * kWave;
+  __shared__ uint32_t win[kSm1WinBins];
+  __shared__ int wave_tot[kSm1Waves], wave_cnt[kSm1Waves];
+  __shared__ int bc_slot;
+  __shared__ uint2 list[kSm1Waves][kMaxWaveCap];  // order key, class
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id()), b = (int)blockIdx.y;
+  const int first = ((int)blockIdx.x * kSm1Waves + w) * rounds * kRound;  // of the wave's keys
+  keys += (size_t)b * N;
+  slots += ((size_t)b * gridDim.x + blockIdx.x) * n_slots;
+  float key[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) key[q] = keys[min(first + q * kWave + lane, N - 1)];
+  const uint4 mx = reinterpret_cast<const uint4*>(mr.wgmax + (size_t)b * kWgMaxSlots)[tid];  // maxima 4 tid .. 4 tid + 3
+  const float smax = __uint_as_float(*smax_word);
+  reinterpret_cast<uint2*>(win)[tid] = make_uint2(0u, 0u);
+  if (tid == 0) bc_slot = 0;
+  lds_barrier();
+  const Sm1Bound lb = sm1_bound(mx, smax, sd, kprime, n_max, win, wave_tot, &bc_slot);
+  if (blockIdx.x == 0 && tid == 0) {
+    mr.walk[4 * b + 1] = lb.found ? 1 : 0;
+    mr.walk[4 * b + 2] = (int)lb.okey_lb;
+  }
+  int cnt = 0;  // keys of the wave so far (uniform)
+  if (lb.found) {  // uniform
+    const float bound = key_value(lb.okey_lb);
+    for (int rd = 0; rd < rounds; ++rd) {
+      const int i0 = first + rd * kRound + lane;  // this lane's keys: i0 + 64 q
+      float next[KPT];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) next[q] = keys[min(i0 + kRound + q * kWave, N - 1)];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q)
+        if (__ballot(!(key[q] < bound)) != 0ull) {  // uniform; the order keys decide (a NaN is not below the bound)
+          const uint32_t okey = order_key(key[q]);
+          const uint64_t m = __ballot(i0 + q * kWave < N && okey >= lb.okey_lb);
+          const int pos = cnt + mask_prefix(m);
+          if (((m >> lane) & 1ull) != 0ull && pos < kMaxWaveCap) list[w][pos] = make_uint2(okey, (uint32_t)(i0 + q * kWave));
+          cnt += __popcll(m);
+        }
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) key[q] = next[q];
+    }
+  }
+  if (lane == 0) wave_cnt[w] = cnt;
+  lds_barrier();
+  int total;
+  const int base = sm1_wave_base(wave_cnt, &total);
+  const bool over = total > n_slots || __ballot(lane < kSm1Waves && wave_cnt[lane % kSm1Waves] > kMaxWaveCap) != 0ull;
+  auto put = [&](int e, uint32_t okey, int idx) {
+    *reinterpret_cast<uint2*>(&slots[e]) = make_uint2(okey, (uint32_t)(e == 0 && over ? -2 : idx));
+  };
+  for (int i = lane; i < min(cnt, kMaxWaveCap); i += kWave)
+    if (base + i < n_slots) put(base + i, list[w][i].x, (int)list[w][i].y);
+  for (int e = total + tid; e < n_slots; e += kSm1Threads) put(e, 0u, -1);
 }
 
 constexpr int kSm1ZBins = 256;  // bins of the logit selection
@@ -776,8 +841,8 @@ static bool sm1_worthwhile(int N, int kprime, int n_max, int kpt) {
   return tail * n_wg < 1e-4;
 }
 bool softmax_b1_worthwhile(int N, int kprime, int n_max) { return sm1_worthwhile(N, kprime, n_max, kSm1KeysPerThread); }
-bool maxima_select_worthwhile(int N, int kprime, int n_max) {
-  return sm1_worthwhile(N, kprime, n_max, kSm1KeysPerThreadB);
+bool maxima_select_worthwhile(int B, int N, int kprime, int n_max) {
+  return sm1_worthwhile(N, kprime, n_max, maxima_rounds(B, N) * kSm1KeysPerThreadB);
 }
 
 size_t softmax_b1_slot_bytes(int N) {
@@ -793,7 +858,7 @@ hipError_t launch_softmax_b1(const float* keys, int N, int d, int sd, int k, int
   const int n_wg = (N + kSm1Keys - 1) / kSm1Keys;
   const uint32_t* smax_word = static_cast<const uint32_t*>(q4) + (size_t)N * (sd / 8);  // behind the codes
   Sm1Entry* sl = static_cast<Sm1Entry*>(slots);
-  if (const hipError_t e = launch(k_sm1_gather<true, kSm1KeysPerThread>, dim3(n_wg), dim3(kSm1Threads), 0, s, keys, N, d, sd, kprime, n_max, smax_word, W,
+  if (const hipError_t e = launch(k_sm1_gather, dim3(n_wg), dim3(kSm1Threads), 0, s, keys, N, d, sd, kprime, n_max, smax_word, W,
                                   x, mr, sl, sm1_slots_per_wg(N));
       e != hipSuccess)
     return e;
@@ -811,12 +876,12 @@ hipError_t launch_maxima_select(const float* keys, int B, int N, int sd, int kpr
                                 const HistRefs& hr, void* slots, uint32_t* bitmap, hipStream_t s) {
   const MultiRegion mr = multi_of(hr, B);
   if (mr.wgmax == nullptr || n_max > kWgMaxSlots || !maxima_select_supported(N)) return hipErrorInvalidValue;
-  const int n_wg = sm1_workgroups(N, kSm1KeysPerThreadB), per_wg = sm1_slots_per_wg(N, kSm1KeysPerThreadB);
+  const int rounds = maxima_rounds(B, N), kpt = rounds * kSm1KeysPerThreadB;
+  const int n_wg = sm1_workgroups(N, kpt), per_wg = sm1_slots_per_wg(N, kpt);
   const uint32_t* smax_word = static_cast<const uint32_t*>(q4) + (size_t)N * (sd / 8);  // behind the codes
   Sm1Entry* sl = static_cast<Sm1Entry*>(slots);
-  if (const hipError_t e = launch(k_sm1_gather<false, kSm1KeysPerThreadB>, dim3(n_wg, B), dim3(kSm1Threads), 0, s, keys, N, 8, sd, kprime,
-                                  n_max, smax_word, static_cast<const uint16_t*>(nullptr),
-                                  static_cast<const uint16_t*>(nullptr), mr, sl, per_wg);
+  if (const hipError_t e = launch(k_max_gather, dim3(n_wg, B), dim3(kSm1Threads), 0, s, keys, N, sd, kprime, n_max, smax_word,
+                                  mr, sl, per_wg, rounds);
       e != hipSuccess)
     return e;
   return launch(k_max_resolve, dim3(B), dim3(kSm1Threads), 0, s, keys, N, kprime, mr, static_cast<const Sm1Entry*>(sl),

@@ -65,3 +65,18 @@ def test_vocabulary_rows(hire, oracle, d, c, B):
     x = _tokens(941, B, d)
     _, want = T.check_softmax(layer, scorer, W, x, 8, 300)
     T.compare_softmax(T.run_softmax(layer, x, 8, 300, debug=False), dict(want, acc=None))  # no sums wanted: their own epilogue
+
+
+@pytest.mark.parametrize("copies", [3, 300])
+def test_vocabulary_rows_adjacent_shortlist(hire, oracle, copies):
+    """Every token's largest keys next to each other, in two rounds of a workgroup: 300 are more than a wave's list holds
+    (the token is then selected from its keys)."""
+    d, c, B = 32, 140000, 33
+    log(f"softmax_step d={d} c={c} B={B} copies={copies}")
+    W = I.classifier(960, c, d)
+    x = _tokens(961, B, d)
+    for b in range(B):
+        at = 4100 * b + 37
+        W[at:at + copies, :] = x[b]
+    layer, scorer = T.make_softmax_layer(W)
+    T.check_softmax(layer, scorer, W, x, 8, 500)
