@@ -5,6 +5,7 @@
 #include "kernels.h"
 
 #include <atomic>
+#include <cmath>
 #include <vector>
 
 // Scratch memory of hire_ffn_step_static: one array per GPU the library runs on, held until the process ends,
@@ -83,12 +84,29 @@ struct StepBuffers {
   float* hf;         // [B, hf_stride]: by unit (FFN, in the keys' place) or by rank in the union (softmax)
   long long hf_stride;
   bool by_unit;      // FFN batches on rows of at most 32768 units: the selections of batch_select.hip
+  bool all_rows;     // ... whose filter stage runs beside the selection of k', over all rows (filter_all_rows)
   void* sm1_slots;   // long rows: slots of the keys at or above the bound from the scorer's maxima
   bool sm1_ok;       // ... which this layout has
   bool max_ok;       // long rows: slots for the selection of k' from the scorer's maxima
   int words, cap_u, zero_words;
   size_t bytes;
 };
+
+// Whether the filter stage reads all rows of the FFN at once with the selection of k' instead of the union's rows behind it:
+// where what it reads in vain costs less than the wait that it saves, also for tokens that share most of their picks (about
+// k' (1 + log2(B) / 4) rows between them; independent ones soon need nearly all).  us per step behind the selection / beside
+// it, k' = N / 5, independent tokens; tokens with nine tenths in common:
+//   d = 2048, N = 8192: 16 tokens 38.8 / 34.7; 36.6 / 33.5   64: 55.8 / 50.1; 50.2 / 43.6
+//   d = 800, N = 5003:  16 tokens 34.7 / 30.4; 33.7 / 30.1   33: 42.7 / 36.7; 41.4 / 36.1
+//   d = 4096, N = 8192: 16 tokens 57.5 / 53.7; 49.1 / 51.1 (40 MB in vain)   64: 81.1 / 75.6; 70.5 / 70.1
+// With more workgroups than compute units, a token or 64 rows each, the last of them wait for a selection:
+//   d = 2048, N = 16384: 16 tokens 52.9 / 50.1; 41.3 / 47.4   33: 66.0 / 62.8; 55.1 / 58.6   64: 72.4 / 68.7; 60.9 / 63.9
+//   d = 1024, N = 16384: 16 tokens 38.4 / 37.2; 35.0 / 35.0   64: 53.8 / 51.0; 49.6 / 46.4
+// There up to 32 tokens, where samples of one query are more likely, need half as much to be read in vain.
+bool filter_all_rows(int B, int d, int N, int kprime) {
+  const double shared = kprime * (1.0 + 0.25 * std::log2((double)B)), vain = N - (shared < N ? shared : N);
+  return vain * 2.0 * d <= (B + filter_tiles(N) <= 256 || B > 32 ? 36.0 : 18.0) * (1 << 20);
+}
 
 // gs > 0: group-sparse FFN with groups of 2^gs units; the selections, the bitmap, the union and cap_u then count
 // groups, while keys and h keep one value per unit.
@@ -132,6 +150,8 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
   const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
+  s.all_rows = s.by_unit && B >= kFilterMinBatch && int4_like && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
+               filter_all_rows(B, d, N, kprime);
   if (s.by_unit && B >= kFilterMinBatch) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
     s.wnorm_tiles = c.take<float>(filter_tiles(N));
@@ -147,6 +167,7 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   }
   const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
   s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
+  if (s.all_rows) s.keys = s.h;  // the values take the keys' place while the keys are read; h is scratch after that
   if (fast) {
     s.h32 = c.take<float>((size_t)B * ffn_fast_entries(N, gs));
     if (gs > 0) s.u32 = c.take<float>((size_t)B * ffn_fast_entries(N, 0));
@@ -331,6 +352,14 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_STAGE(3, st);
       HIRE_TRY(launch_resolve_compact(static_cast<const float*>(s.keys), B, N, kprime, s.hist, s.bitmap, s.words,
                                       in_gather ? nullptr : cand, s.counters, n_cand, nullptr, 0, st));
+    } else if (s.all_rows && filter) {
+      HIRE_TRY(launch_select_filter(static_cast<const float*>(s.keys), s.key_stride, B, N, kprime, s.sumabs,
+                                    reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2)),
+                                    s.bitmap, s.window_misses, static_cast<const uint16_t*>(W), xb, d, s.hf, s.hf_stride,
+                                    s.xnorm, s.wnorm_tiles, st));
+      HIRE_STAGE(3, st);
+      HIRE_STAGE(4, st);
+      return HIRE_OK;
     } else if (s.by_unit) {
       HIRE_TRY(launch_keys_select(static_cast<const float*>(s.keys), s.key_stride, B, N, kprime, s.sumabs,
                                   reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2)),
@@ -602,6 +631,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     rp.wnorm_n = filter_tiles(N);
     rp.err_c = gather_filter_error(B);
     rp.bitmap = s.bitmap;
+    rp.all_rows = s.all_rows ? 1 : 0;
     if (cand_idx != nullptr || n_cand != nullptr) {
       rp.cand_out = cand_idx != nullptr ? cand_idx : s.cand;
       rp.cand_cap = s.cap_u;

@@ -15,116 +15,16 @@
 // anchor, which whoever holds it sees.
 #include "fast_select.h"
 #include "kernels.h"
+#include "keys_select.h"
 
 namespace hire {
 
 constexpr int kBsCap = 128;  // refined entries around the threshold kept in LDS
 
 template <int LOADS>
-struct BatchKeys {
-  using Keys = KeyRegs<uint32_t, LOADS, kSelThreads>;
-  static_assert(LOADS * Keys::PER <= 32, "one bit per key of a lane");
-};
-
-// Window histogram of the registers' values below `anchor` (zeros are never counted) and the bin that holds the k-th
-// largest of those.  false: fewer than k values in the window.  *bin: that bin; *above: the values counted in higher ones;
-// *beyond: this thread has a value above the anchor, which is not counted.
-template <typename Keys>
-__device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int k, uint32_t* win,
-                                           SelSharedT<kSelThreads>& sh, uint32_t* bin, int* above, bool* beyond) {
-  uint32_t farthest = 0u;
-#pragma unroll
-  for (int e = 0; e < (int)(sizeof(kr.r) / sizeof(kr.r[0])); ++e)
-#pragma unroll
-    for (int q = 0; q < Keys::PER; ++q) {
-      const uint32_t slot = anchor - fine_bin(kr.r[e][q]);  // (wraps above the anchor)
-      farthest = max(farthest, slot);
-      if (kr.r[e][q] != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
-    }
-  *beyond = farthest > anchor;
-  __syncthreads();
-  WinRegs<kSelThreads> wr;
-  wr.issue(win);
-  const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
-  *bin = anchor - (uint32_t)wk.slot;
-  *above = wk.above;
-  return wk.found && *bin >= 1u && *bin <= anchor;  // uniform
-}
-
-// ---------------------------------------------------------------------------------------------------
-// sumabs[b]: sum of the token's |int8 codes|, *smax: the largest row scale of the int4 copy that the keys were scored
-// with: key_j = fl(fl(acc_j) s_j) <= fl(7 sumabs smax), rounding being monotone (7 sumabs < 2^24).
-template <int LOADS>
-__global__ __launch_bounds__(kSelThreads) void k_keys_select(const float* __restrict__ keys, long long stride, int N,
-                                                             int kprime, const float* __restrict__ sumabs,
-                                                             const float* __restrict__ smax,
-                                                             uint32_t* __restrict__ bitmap,
-                                                             uint32_t* __restrict__ window_misses) {
-  using Keys = typename BatchKeys<LOADS>::Keys;
-  constexpr int PER = Keys::PER;
-  __shared__ SelSharedT<kSelThreads> sh;
-  __shared__ __align__(16) uint32_t win[kWin];
-  __shared__ int wave_cnt[kSelWaves];
-  __shared__ int off_window;  // not 0: the window does not count every key that it should
-  __shared__ BinList<uint32_t> list;
-  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
-  HIRE_TS(10);
-  const float* row = keys + (size_t)b * stride;
-  Keys kr;
-  kr.issue_clamped(row, N);  // rows are padded to whole vectors
-  const uint32_t anchor = fine_bin(__float_as_uint(7.0f * sumabs[b] * *smax));
-  {
-    uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
-    z[0] = z[1] = make_uint4(0, 0, 0, 0);
-  }
-  if (tid == 0) sh.list_n = off_window = 0;
-  kr.finish();
-  kr.mask_beyond(N);
-  __syncthreads();
-  HIRE_TS(11);
-  uint32_t bin;
-  int above;
-  bool beyond;
-  bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above, &beyond);
-  if (beyond) off_window = 1;  // (row scales that do not belong to the codes)
-  HIRE_TS(12);
-  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
-  if (known) {
-    const BinMasks<uint32_t> bm = bin_masks<uint32_t>(kr, bin_floor<uint32_t>(bin), bin_floor<uint32_t>(bin + 1u));
-    list_inside<uint32_t>(kr, bm.inside, &sh.list_n, list);
-    __syncthreads();
-    HIRE_TS(13);
-    const int m = sh.list_n;
-    known = m <= kFastAmbCap && off_window == 0;  // uniform
-    if (known)
-      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
-                                      kprime - above);
-    HIRE_TS(14);
-  }
-  if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
-    WinRegs<kSelThreads> none{};
-    const Selection<uint32_t> sel =
-        fast_select<60>(kr, row, kprime, none, 0u, false, sh, wave_cnt, window_misses, 0, kprime, true);
-    take = 0u;
-#pragma unroll
-    for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-      for (int q = 0; q < PER; ++q)
-        take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
-  }
-  // A bitmap word covers 32 consecutive indices: the keys of eight neighbouring lanes of one load.  Those lanes
-  // fold their bits together and one of them adds the word to the union.
-  static_assert(PER == 4, "eight lanes per word");
-  take = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
-#pragma unroll
-  for (int e = 0; e < LOADS; ++e) {
-    uint32_t bits = (take >> (e * PER) & 15u) << (lane % 8 * PER);
-    bits |= dpp_move<0xB1, 0xF>(0u, bits);   // lanes 1, 0, 3, 2 of a quad
-    bits |= dpp_move<0x4E, 0xF>(0u, bits);   // lanes 2, 3, 0, 1
-    bits |= dpp_move<0x141, 0xF>(0u, bits);  // eight lanes mirrored: the other quad
-    if (lane % 8 == 0 && bits != 0u) atomicOr(&bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / 8], bits);
-  }
-  HIRE_TS(15);
+__global__ __launch_bounds__(kSelThreads) void k_keys_select(KeysSelect p) {
+  __shared__ KeysSelectShared S;
+  keys_select_token<LOADS>(p, (int)blockIdx.x, S);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -293,6 +193,9 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * d);
   Keys kr;
   kr.issue_clamped(row, N);
+  uint32_t words[LOADS];  // the bitmap's words of this lane's units
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e) words[e] = p.bitmap[min(kr.index(e, 0), N - 1) >> 5];
   if (d <= kRefineTokenMax) {
     for (int i = tid; i < d / 8; i += kSelThreads) tok_sh[i] = tok[i];
     tok = tok_sh;
@@ -309,6 +212,14 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   if (tid == 0) L.sh.list_n = 0;
   kr.finish();
   kr.mask_beyond(N);
+  if (p.all_rows) {  // uniform: units that no token shortlists have values as well
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e) {
+      const uint32_t bits = words[e] >> (kr.index(e, 0) & 31);  // four units, all in one word
+#pragma unroll
+      for (int q = 0; q < PER; ++q) kr.r[e][q] &= 0u - (bits >> q & 1u);
+    }
+  }
   __syncthreads();
   wn = wave_max(lane < kSelWaves ? L.wave_max[lane] : 0.0f);
   const uint32_t anchor = fine_bin(__float_as_uint(xn * wn * 1.001f));  // of a bound of every stored value
@@ -472,11 +383,8 @@ bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k
 hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
                               const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s) {
   if (N > 32768 || stride % 4 != 0 || reinterpret_cast<uintptr_t>(keys) % 16 != 0) return hipErrorInvalidValue;
-  if (N <= 16384)
-    return launch(k_keys_select<4>, dim3(B), dim3(kSelThreads), 0, s, keys, stride, N, kprime, sumabs, smax, bitmap,
-                  window_misses);
-  return launch(k_keys_select<8>, dim3(B), dim3(kSelThreads), 0, s, keys, stride, N, kprime, sumabs, smax, bitmap,
-                window_misses);
+  const KeysSelect p{keys, stride, N, kprime, sumabs, smax, bitmap, window_misses};
+  return launch(N <= 16384 ? k_keys_select<4> : k_keys_select<8>, dim3(B), dim3(kSelThreads), 0, s, p);
 }
 
 static hipError_t launch_exact_values(const RefineParams& p, hipStream_t s) {

@@ -15,6 +15,7 @@
 #include "device_utils.h"
 #include "hist.h"
 #include "kernels.h"
+#include "keys_select.h"
 
 namespace hire {
 
@@ -313,23 +314,39 @@ __device__ __forceinline__ void ft_stage(const unsigned char* slot, int cw, int 
   }
 }
 
+struct FilterUnits {
+  const uint16_t* W;
+  const uint16_t* x;
+  int B, d;
+  const uint32_t* bitmap;  // candidates; nullptr: every row below the count
+  const int32_t* n_dev;    // optional count
+  int n_cap;
+  float* h;
+  long long stride_h;
+  float* xnorm;
+  float* wnorm_tiles;
+  uint32_t* wnorm_max;
+  float err_c;
+};
+
+// The 64 units of a tile, by a workgroup; lds: kFtStages stages.
 template <int TT, int TG, int KS>
-__global__ __launch_bounds__(256 * TG * KS) void k_filter_units(const uint16_t* __restrict__ W, const uint16_t* __restrict__ x,
-                                                          int B, int d, const uint32_t* __restrict__ bitmap,
-                                                          const int32_t* __restrict__ n_dev, int n_cap,
-                                                          float* __restrict__ h, long long stride_h,
-                                                          float* __restrict__ xnorm, float* __restrict__ wnorm_tiles,
-                                                          uint32_t* __restrict__ wnorm_max, float err_c) {
+__device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile, unsigned char* lds) {
   using S = FtShape<TT, TG, KS>;
   constexpr int NW = S::NW, NT = S::NT, TTW = S::TTW, CI = S::CI, TI = S::TI, kStage = S::kStage;
-  extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int32_t rows_sh[kFtRows];
   __shared__ float xsq[KS][TT][16];
   __shared__ float wmx[4];
+  const uint16_t* __restrict__ W = p.W;
+  const uint16_t* __restrict__ x = p.x;
+  const uint32_t* __restrict__ bitmap = p.bitmap;
+  float* __restrict__ h = p.h;
+  const long long stride_h = p.stride_h;
+  const int B = p.B, d = p.d;
+  const float err_c = p.err_c;
   const int tid = (int)threadIdx.x, lane = lane_id(), jl = lane & 15, g = lane >> 4;
   // known to be uniform: a matrix-core instruction must never sit behind a branch that is lowered to lane masking
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int tile = (int)blockIdx.x;
   const int e0 = tile * kFtRows;  // first unit of the workgroup
   const int cpr = d / 8;          // 16-byte chunks per row
   HIRE_TS(55);
@@ -337,7 +354,7 @@ __global__ __launch_bounds__(256 * TG * KS) void k_filter_units(const uint16_t* 
   if (bitmap != nullptr) {
     m = reinterpret_cast<const uint64_t*>(bitmap)[tile];  // padded to whole 64-bit words, no bits past the rows
   } else {  // every row below the count
-    const int left = min(*n_dev, n_cap) - e0;
+    const int left = (p.n_dev != nullptr ? min(*p.n_dev, p.n_cap) : p.n_cap) - e0;
     m = left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
   }
   m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
@@ -457,17 +474,38 @@ __global__ __launch_bounds__(256 * TG * KS) void k_filter_units(const uint16_t* 
   }
   if (tid == 0) {  // a place per workgroup: 256 atomics on one address at the kernel's end took 7 us
     const float m = c > 0 ? sqrtf(fmaxf(fmaxf(wmx[0], wmx[1]), fmaxf(wmx[2], wmx[3]))) * 1.0001f : 0.0f;
-    if (wnorm_tiles != nullptr) wnorm_tiles[tile] = m;
-    else atomicMax(wnorm_max, __float_as_uint(m));
+    if (p.wnorm_tiles != nullptr) p.wnorm_tiles[tile] = m;
+    else atomicMax(p.wnorm_max, __float_as_uint(m));
   }
   if (c <= 0) return;
   for (int t = tid; t < B; t += NT) {  // the same values from every workgroup that has candidates
     float xn2 = 0.0f;
 #pragma unroll
     for (int q = 0; q < KS; ++q) xn2 += xsq[q][t / 16][t % 16];
-    xnorm[t] = sqrtf(xn2 * up) * 1.0001f;
+    p.xnorm[t] = sqrtf(xn2 * up) * 1.0001f;
   }
   HIRE_TS(58);
+}
+
+template <int TT, int TG, int KS>
+__global__ __launch_bounds__(256 * TG * KS) void k_filter_units(FilterUnits p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  filter_units_tile<TT, TG, KS>(p, (int)blockIdx.x, lds);
+}
+
+// The selection of the k' largest keys and the filter stage at once: the first workgroups select, a token each, the others
+// form the values of all rows, shortlisted or not, and k_refine leaves out those that no token shortlists.  The selection
+// is a chain on one compute unit per token (6 us at 16 tokens, 8 at 64) during which the rest of the chip waits; the
+// stage's rows do not depend on it where nearly all of them are read anyway, or where they are few.  run_front says which
+// layouts take it.  d = 2048,
+// 64 tokens, 16384 rows: 23.6 us against 8.1 + 19.8 one after the other.
+template <int TT, int TG, int KS, int LOADS>
+__global__ __launch_bounds__(256 * TG * KS) void k_select_filter(KeysSelect ks, FilterUnits p) {
+  static_assert(256 * TG * KS == kSelThreads && sizeof(KeysSelectShared) <= kFtStages * ft_stage_bytes(TT), "one workgroup fits both");
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int tile = (int)blockIdx.x - p.B;
+  if (tile < 0) keys_select_token<LOADS>(ks, (int)blockIdx.x, *reinterpret_cast<KeysSelectShared*>(lds));  // uniform
+  else filter_units_tile<TT, TG, KS>(p, tile, lds);
 }
 
 // The same product for the classifier (phi = identity; the union is a small part of a long vocabulary): the candidates
@@ -671,12 +709,12 @@ hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int 
                                float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s) {
   if (B < 1 || B > 64 || d % 8 != 0) return hipErrorInvalidValue;
   static std::atomic<size_t> raised_to[3] = {};
+  const FilterUnits p{W, x, B, d, bitmap, n_dev, n_rows, h, stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B)};
   auto go = [&](auto kernel, int tt, int waves, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
       return e;
-    return launch(kernel, dim3(filter_tiles(n_rows)), dim3(64 * waves), lds, s, W, x, B, d, bitmap, n_dev, n_rows, h,
-                  stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B));
+    return launch(kernel, dim3(filter_tiles(n_rows)), dim3(64 * waves), lds, s, p);
   };
   // Two (beyond 16 tokens four) waves share a group of candidates: halves of every stage's steps and, with several
   // token tiles, halves of the tiles, so that the fp64 additions and the operand reads of a stage are short next to
@@ -684,6 +722,31 @@ hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int 
   if (B <= 16) return go(k_filter_units<1, 1, 2>, 1, 8, raised_to[0]);
   if (B <= 32) return go(k_filter_units<2, 2, 2>, 2, 16, raised_to[1]);
   return go(k_filter_units<4, 2, 2>, 4, 16, raised_to[2]);
+}
+
+hipError_t launch_select_filter(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
+                                const float* smax, uint32_t* bitmap, uint32_t* window_misses, const uint16_t* W,
+                                const uint16_t* x, int d, float* h, long long stride_h, float* xnorm, float* wnorm_tiles,
+                                hipStream_t s) {
+  if (B < 1 || B > 64 || d % 8 != 0 || N > 32768 || stride % 4 != 0 || reinterpret_cast<uintptr_t>(keys) % 16 != 0)
+    return hipErrorInvalidValue;
+  const KeysSelect ks{keys, stride, N, kprime, sumabs, smax, bitmap, window_misses};
+  const FilterUnits p{W, x, B, d, nullptr, nullptr, N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B)};
+  static std::atomic<size_t> raised_to[6] = {};
+  auto go = [&](auto kernel, int tt, std::atomic<size_t>& raised) {
+    const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
+    if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
+      return e;
+    return launch(kernel, dim3(B + filter_tiles(N)), dim3(kSelThreads), lds, s, ks, p);
+  };
+  if (N <= 16384) {
+    if (B <= 16) return go(k_select_filter<1, 1, 4, 4>, 1, raised_to[0]);
+    if (B <= 32) return go(k_select_filter<2, 2, 2, 4>, 2, raised_to[1]);
+    return go(k_select_filter<4, 2, 2, 4>, 4, raised_to[2]);
+  }
+  if (B <= 16) return go(k_select_filter<1, 1, 4, 8>, 1, raised_to[3]);
+  if (B <= 32) return go(k_select_filter<2, 2, 2, 8>, 2, raised_to[4]);
+  return go(k_select_filter<4, 2, 2, 8>, 4, raised_to[5]);
 }
 
 hipError_t launch_filter_ranks(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,

@@ -226,6 +226,7 @@ struct RefineParams {
   const float* wnorm_tiles;
   int wnorm_n;
   float err_c;
+  int all_rows;             // != 0: vals has values of units that are no candidates, too (launch_select_filter)
   const uint32_t* bitmap;   // the candidates; they are listed as well: ascending, and their number
   int32_t* cand_out;        // optional; cand_cap entries fit
   int cand_cap;
@@ -299,6 +300,11 @@ int filter_tiles(int n);
 hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int d, const uint32_t* bitmap,
                                const int32_t* n_dev, int n_rows, float* h, long long stride_h, float* xnorm,
                                float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s);
+// launch_keys_select and, at the same time, launch_filter_units over all N rows: keys and h do not overlap.
+hipError_t launch_select_filter(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
+                                const float* smax, uint32_t* bitmap, uint32_t* window_misses, const uint16_t* W,
+                                const uint16_t* x, int d, float* h, long long stride_h, float* xnorm, float* wnorm_tiles,
+                                hipStream_t s);
 // Classifier (phi = identity): the candidate of rank t (of un's bitmap over n_rows classes, or list with n_dev) goes to
 // h[b*stride_h + t]; n_cap <= kSoftmaxRefineMaxRow.  wnorm_tiles [filter_rank_blocks(n_cap)]; maxima [B,
 // kFilterMaxima], 4 filter_rank_blocks(n_cap) of them per token: the largest values of as many disjoint groups of
