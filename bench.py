@@ -82,7 +82,7 @@ def log(msg):
 
 # stage of the live event timing -> names (substrings) of its kernels in a rocprofv3 summary
 _STAGE_KERNELS = {
-    "scorer": ("k_fast_score", "k_scorer_int4", "k_lr_score", "k_lr_project", "k_lr_reduce"),
+    "scorer": ("k_fast_score", "k_scorer_int4", "k_lr_score", "k_lr_project"),
     "quantise_x": ("k_quantize_tokens",),
     "select_kprime": ("k_select<float", "k_select_nonneg<float", "k_keys_select", "k_count_f32", "k_mark_f32", "k_group_sums",
                       "k_max_gather"),

@@ -62,7 +62,6 @@ struct StepBuffers {
   float* sumabs;     // [B] sums of the tokens' absolute int8 codes
   uint16_t* t;       // low-rank intermediate, bf16 [B, r]
   float* keys_t;     // int4 low-rank scorer: the intermediate before rounding, fp32 [B, r]
-  double* t_partial; // its per-slice partial sums
   void* keys;        // fp32 or fp64 [B, key_stride]
   long long key_stride;
   void* gkeys;       // group-sparse: summed absolute keys, same type, [B, N >> gs] ([B, gkey_stride] for 1 to 8 tokens)
@@ -72,6 +71,7 @@ struct StepBuffers {
   int32_t* counters; // [0] = |U|
   int32_t* cand;     // U
   double* h;         // [B, cap_u]
+  double* h_refine;  // filter and refine: scratch of the refining selection, in the candidates' order
   int32_t* pos;      // group-sparse: [B, k >> gs] positions inside U of every token's selected groups
   uint2* list;       // [B,k] selected units as (row, coefficient), for the second layer
   float* h32;        // few tokens: activations by unit (by group) in fp32
@@ -102,7 +102,9 @@ struct StepBuffers {
 // With more workgroups than compute units, a token or 64 rows each, the last of them wait for a selection:
 //   d = 2048, N = 16384: 16 tokens 52.9 / 50.1; 41.3 / 47.4   33: 66.0 / 62.8; 55.1 / 58.6   64: 72.4 / 68.7; 60.9 / 63.9
 //   d = 1024, N = 16384: 16 tokens 38.4 / 37.2; 35.0 / 35.0   64: 53.8 / 51.0; 49.6 / 46.4
-// There up to 32 tokens, where samples of one query are more likely, need half as much to be read in vain.
+// There up to 32 tokens, where samples of one query are more likely, need half as much to be read in vain.  fp64 keys (the
+// low-rank scorer) gain a microsecond or two more each: d = 800, N = 5003, 33 tokens 46.5 / 38.2, d = 2048, N = 16384, 16
+// tokens 57.7 / 54.9; 45.5 / 51.5.
 bool filter_all_rows(int B, int d, int N, int kprime) {
   const double shared = kprime * (1.0 + 0.25 * std::log2((double)B)), vain = N - (shared < N ? shared : N);
   return vain * 2.0 * d <= (B + filter_tiles(N) <= 256 || B > 32 ? 36.0 : 18.0) * (1 << 20);
@@ -140,7 +142,6 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     }
   } else {
     s.t = c.take<uint16_t>((size_t)B * r);
-    s.t_partial = c.take<double>((size_t)B * lr_project_slices(d) * r);
     s.keys = c.take<double>((size_t)B * s.key_stride);
     if (gs > 0) s.gkeys = c.take<double>((size_t)B * Ns);
   }
@@ -150,8 +151,8 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
   const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
-  s.all_rows = s.by_unit && B >= kFilterMinBatch && int4_like && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
-               filter_all_rows(B, d, N, kprime);
+  s.all_rows = s.by_unit && B >= kFilterMinBatch && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
+               (int4_like || N <= kKeysSelectMaxF64) && filter_all_rows(B, d, N, kprime);
   if (s.by_unit && B >= kFilterMinBatch) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
     s.wnorm_tiles = c.take<float>(filter_tiles(N));
@@ -167,7 +168,15 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   }
   const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
   s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
-  if (s.all_rows) s.keys = s.h;  // the values take the keys' place while the keys are read; h is scratch after that
+  // all_rows: the filter stage writes its values while the keys are read.  h is the selection's scratch only after that, so
+  // the keys or the values go there: the fp32 keys, whose own place is too small for the scratch, or else the values
+  s.h_refine = s.h;
+  if (s.all_rows && int4_like) {
+    s.keys = s.h;
+  } else if (s.all_rows) {
+    s.hf = reinterpret_cast<float*>(s.h);
+    s.h_refine = static_cast<double*>(s.keys);
+  }
   if (fast) {
     s.h32 = c.take<float>((size_t)B * ffn_fast_entries(N, gs));
     if (gs > 0) s.u32 = c.take<float>((size_t)B * ffn_fast_entries(N, 0));
@@ -282,6 +291,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   const bool many_wg = int4_like && N > kSingleWgMaxRow && gs == 0;  // long rows: key histograms
   UnionRefs un{s.bitmap, s.words, cand, s.counters, n_cand, many_wg};
   sp.window_misses = s.window_misses;
+  KeysSelect ks{s.keys, !int4_like, s.key_stride, N, kprime, nullptr, nullptr, s.bitmap, s.window_misses};
   HIRE_STAGE(0, st);
   bool t_is_f32 = false;
   if (lrq) {
@@ -352,18 +362,17 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_STAGE(3, st);
       HIRE_TRY(launch_resolve_compact(static_cast<const float*>(s.keys), B, N, kprime, s.hist, s.bitmap, s.words,
                                       in_gather ? nullptr : cand, s.counters, n_cand, nullptr, 0, st));
-    } else if (s.all_rows && filter) {
-      HIRE_TRY(launch_select_filter(static_cast<const float*>(s.keys), s.key_stride, B, N, kprime, s.sumabs,
-                                    reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2)),
-                                    s.bitmap, s.window_misses, static_cast<const uint16_t*>(W), xb, d, s.hf, s.hf_stride,
-                                    s.xnorm, s.wnorm_tiles, st));
-      HIRE_STAGE(3, st);
-      HIRE_STAGE(4, st);
-      return HIRE_OK;
     } else if (s.by_unit) {
-      HIRE_TRY(launch_keys_select(static_cast<const float*>(s.keys), s.key_stride, B, N, kprime, s.sumabs,
-                                  reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2)),
-                                  s.bitmap, s.window_misses, st));
+      ks.sumabs = s.sumabs;
+      ks.smax = reinterpret_cast<const float*>(static_cast<const char*>(q4) + (size_t)N * (sd / 2));
+      if (s.all_rows && filter) {
+        HIRE_TRY(launch_select_filter(ks, B, static_cast<const uint16_t*>(W), xb, d, s.hf, s.hf_stride, s.xnorm, s.wnorm_tiles,
+                                      st));
+        HIRE_STAGE(3, st);
+        HIRE_STAGE(4, st);
+        return HIRE_OK;
+      }
+      HIRE_TRY(launch_keys_select(ks, B, st));
       HIRE_STAGE(3, st);
     } else {
       HIRE_TRY(launch_select_f32(sp, B, st));
@@ -371,19 +380,29 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       if (!in_gather) HIRE_TRY(launch_bitmap_compact(s.bitmap, s.words, cand, s.counters, n_cand, nullptr, 0, st));
     }
   } else {
-    HIRE_TRY(launch_lr_project(static_cast<const uint16_t*>(lr_a), xb, B, d, r, s.t, s.t_partial, s.bitmap, s.zero_words,
-                               s.hist.header, s.sig, st));
+    HIRE_TRY(launch_lr_project(static_cast<const uint16_t*>(lr_a), xb, B, d, r, s.t, s.bitmap, s.zero_words, s.hist.header,
+                               s.sig, st));
     HIRE_STAGE(1, st);
-    if (B >= kMfmaMinBatch)  // the same contraction as the exact stage, over all rows of Z2 with t as the tokens
-      HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(lr_b), s.t, B, r, nullptr, N, nullptr, N, relu,
-                                      static_cast<double*>(s.keys), s.key_stride, s.hist, nullptr, 0, st));
+    if (B >= kMfmaMinBatch)
+      HIRE_TRY(launch_lr_score_mfma(static_cast<const uint16_t*>(lr_b), s.t, B, N, r, relu, static_cast<double*>(s.keys),
+                                    s.key_stride, st));
     else
       HIRE_TRY(launch_lr_score(static_cast<const uint16_t*>(lr_b), s.t, N, r, relu, static_cast<double*>(s.keys), st));
     HIRE_STAGE(2, st);
+    if (s.all_rows && filter) {
+      HIRE_TRY(launch_select_filter(ks, B, static_cast<const uint16_t*>(W), xb, d, s.hf, s.hf_stride, s.xnorm, s.wnorm_tiles,
+                                    st));
+      HIRE_STAGE(3, st);
+      HIRE_STAGE(4, st);
+      return HIRE_OK;
+    }
     if (gs > 0 && !in_select)
       HIRE_TRY(launch_group_sums_f64(static_cast<const double*>(s.keys), B, N, Ns, nullptr, Ns, gs,
                                      static_cast<double*>(s.gkeys), Ns, st));
-    HIRE_TRY(launch_select_f64(sp, B, st));
+    if (s.by_unit && N <= kKeysSelectMaxF64)
+      HIRE_TRY(launch_keys_select(ks, B, st));
+    else
+      HIRE_TRY(launch_select_f64(sp, B, st));
     HIRE_STAGE(3, st);
     if (!in_gather) HIRE_TRY(launch_bitmap_compact(s.bitmap, s.words, cand, s.counters, n_cand, nullptr, 0, st));
   }
@@ -593,7 +612,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     a.lrq = fast_lrq;
     if (fast_lr || fast_lrq) {
       a.lr_a = L->lr_a; a.lr_b = L->lr_b; a.r = L->r; a.norm_bounds = L->row_norm_bounds;
-      a.t_partial = s.t_partial; a.keys64 = static_cast<double*>(s.keys);
+      a.t = s.t; a.keys64 = static_cast<double*>(s.keys);
       a.lr_a_scale = L->lr_a_scale; a.lr_b_scale = L->lr_b_scale; a.keys_t = s.keys_t;
     }
     a.w1u = static_cast<const uint16_t*>(L->w1u); a.w2u = static_cast<const uint16_t*>(L->w2u);
@@ -637,7 +656,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
       rp.cand_cap = s.cap_u;
       rp.n_cand_out = n_cand;
     }
-    rp.h64 = s.h;
+    rp.h64 = s.h_refine;
     rp.h_stride = s.cap_u;
     rp.idx_out = topk_idx;
     rp.val_out = topk_val;

@@ -21,10 +21,10 @@ namespace hire {
 
 constexpr int kBsCap = 128;  // refined entries around the threshold kept in LDS
 
-template <int LOADS>
+template <typename K, int LOADS>
 __global__ __launch_bounds__(kSelThreads) void k_keys_select(KeysSelect p) {
-  __shared__ KeysSelectShared S;
-  keys_select_token<LOADS>(p, (int)blockIdx.x, S);
+  __shared__ KeysSelectShared<K> S;
+  keys_select_token<K, LOADS>(p, (int)blockIdx.x, S);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -176,7 +176,7 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
 template <int LOADS>
 __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   using K = uint32_t;
-  using Keys = typename BatchKeys<LOADS>::Keys;
+  using Keys = typename BatchKeys<uint32_t, LOADS>::Keys;
   constexpr int PER = Keys::PER;
   __shared__ RefineShared L;
   extern __shared__ uint4 tok_sh[];  // the token, d <= kRefineTokenMax
@@ -380,11 +380,10 @@ __global__ __launch_bounds__(kEvThreads) void k_exact_values(uint2* __restrict__
 // ---------------------------------------------------------------------------------------------------
 bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k <= kWin / 2; }
 
-hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
-                              const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s) {
-  if (N > 32768 || stride % 4 != 0 || reinterpret_cast<uintptr_t>(keys) % 16 != 0) return hipErrorInvalidValue;
-  const KeysSelect p{keys, stride, N, kprime, sumabs, smax, bitmap, window_misses};
-  return launch(N <= 16384 ? k_keys_select<4> : k_keys_select<8>, dim3(B), dim3(kSelThreads), 0, s, p);
+hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s) {
+  if (!keys_select_ok(p)) return hipErrorInvalidValue;
+  if (p.f64) return launch(k_keys_select<uint64_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
+  return launch(p.N <= 16384 ? k_keys_select<uint32_t, 4> : k_keys_select<uint32_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
 }
 
 static hipError_t launch_exact_values(const RefineParams& p, hipStream_t s) {

@@ -243,14 +243,13 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
 
 // ---------------------------------------------------------------------------------------------------
 // Kernel 1 for the low-rank scorer (HiRE-LR, Sec. 3.2): keys[j] = relu(<Z2[j, :], t>) in fp64 with
-// t = bf16(Z1^T x).  The slices of Z1^T x come from k_lr_project; every workgroup adds them itself, in slice
-// order, and rounds once (what k_lr_reduce does), so no kernel of one workgroup runs in between.  The anchors are
+// t = bf16(Z1^T x) from k_lr_project.  The anchors are
 // Cauchy-Schwarz bounds: key_j <= |Z2_j| |t| and <u_j, x> <= |u_j| |x| with the layer's largest row norms
 // (bounds[1], bounds[0]: upper bounds, prepared once per layer) and the norms of t and x formed here in fp32 and
 // rounded up by more than their own error.  ROW_LANES lanes share a row as in k_lr_score_b1.
-// TT: tokens, 1 or up to 4; kSW / TT waves add a token's slices.
+// TT: tokens, 1 or up to 4; kSW / TT waves per token form the norms.
 template <int ROW_LANES, int TT>
-__global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict__ partial, int slices,
+__global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restrict__ t_in,
                                                        const uint16_t* __restrict__ z2, const uint4* __restrict__ x,
                                                        int B, int N, int d, int r, const float* __restrict__ bounds,
                                                        double* __restrict__ keys, long long stride,
@@ -270,15 +269,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const double* __restrict_
   float tsq = 0.0f, xsq = 0.0f;
   uint16_t* t16 = reinterpret_cast<uint16_t*>(ts[w / kWPT]);
   for (int p = lt; p < r; p += kWPT * kWave) {
-    double tot = 0.0;
-    for (int s0 = 0; s0 < slices; s0 += 8) {  // eight loads in flight; added in slice order
-      double v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = partial[((size_t)mine * slices + min(s0 + j, slices - 1)) * r + p];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) tot += s0 + j < slices ? v[j] : 0.0;
-    }
-    const uint16_t tb = f64_to_bf16_rne(tot);
+    const uint16_t tb = t_in[(size_t)mine * r + p];
     t16[p] = tb;
     const float tf = bf16_to_f32(tb);
     tsq = fmaf(tf, tf, tsq);
@@ -969,13 +960,11 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   const void* sel_keys = lowrank ? static_cast<const void*>(a.keys64) : (gs ? a.gkeys : a.keys);
   if (lowrank) {
     if (gs != 0 || a.m1 != 0 || a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
-    e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, a.B, a.d, a.r, nullptr, a.t_partial, nullptr, 0, nullptr,
-                          0ull, s);
+    e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, a.B, a.d, a.r, a.t, nullptr, 0, nullptr, 0ull, s);
     if (e != hipSuccess) return e;
-    const int slices = lr_project_slices(a.d);
     const uint4* x4 = reinterpret_cast<const uint4*>(a.x);
     auto go = [&](auto kernel) {
-      return launch(kernel, dim3(score_blocks), dim3(kST), 0, s, a.t_partial, slices, static_cast<const uint16_t*>(a.lr_b),
+      return launch(kernel, dim3(score_blocks), dim3(kST), 0, s, static_cast<const uint16_t*>(a.t), static_cast<const uint16_t*>(a.lr_b),
                     x4, a.B, a.N, a.d, a.r, a.norm_bounds, a.keys64, a.key_stride, fr);
     };
     if (a.r <= 128) e = several ? go(k_fast_score_lr<16, 4>) : go(k_fast_score_lr<16, 1>);

@@ -152,6 +152,61 @@ __global__ __launch_bounds__(256) void k_gather_dot_mfma(const uint16_t* __restr
 }
 
 // ---------------------------------------------------------------------------------------------------
+// Low-rank scorer for batches: keys[b, j] = phi(<Z2[j, :], t_b>) over all rows of Z2, the operands as in
+// k_gather_dot_mfma.  The rows are short (r values), so a wave has sixteen rows to itself and no share of the columns:
+// no LDS, no barrier, eight 16-byte chunks of both operands requested together.  Measured at r = 128, 16384 rows, 16
+// tokens: 5.0 us, against 9.4 with k_gather_dot_mfma, whose four waves had 32 columns each and added their tiles in LDS.
+constexpr int kLsThreads = 256;
+__global__ __launch_bounds__(kLsThreads) void k_lr_score_mfma(const uint16_t* __restrict__ z2, const uint16_t* __restrict__ t,
+                                                              int B, int N, int r, int relu, double* __restrict__ keys,
+                                                              long long stride) {
+  constexpr int kDepth = 4;
+  const int lane = lane_id(), jl = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());  // uniform for the matrix cores
+  const int j0 = ((int)blockIdx.x * (kLsThreads / kWave) + w) * 16, j = j0 + jl, cpr = r / 8;
+  if (j0 >= N) return;  // uniform
+  const uint4* zrow = reinterpret_cast<const uint4*>(z2 + (size_t)min(j, N - 1) * r);
+  const uint4* trow = reinterpret_cast<const uint4*>(t + (size_t)min((int)blockIdx.y * 16 + jl, B - 1) * r);
+  v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  for (int c0 = 0; c0 < cpr; c0 += 4 * kDepth) {
+    uint4 zv[kDepth], tv[kDepth];
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u) {
+      const int c = min(c0 + 4 * u + g, cpr - 1);
+      zv[u] = zrow[c];
+      tv[u] = trow[c];
+    }
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u)
+      if (c0 + 4 * u < cpr) {  // uniform
+        const uint32_t keep = c0 + 4 * u + g < cpr ? 0xFFFFFFFFu : 0u;  // past the row's end: zeros
+        const uint32_t zd[4] = {zv[u].x & keep, zv[u].y & keep, zv[u].z & keep, zv[u].w & keep};
+        const uint32_t td[4] = {tv[u].x & keep, tv[u].y & keep, tv[u].z & keep, tv[u].w & keep};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_lo(td[q]), (double)bf16_lo(zd[q]), acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_hi(td[q]), (double)bf16_hi(zd[q]), acc[1], 0, 0, 0);
+        }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int b = (int)blockIdx.y * 16 + g + 4 * i;
+    double s = acc[0][i] + acc[1][i];
+    if (relu) s = s > 0.0 ? s : 0.0;
+    if (s == 0.0) s = 0.0;
+    if (b < B && j < N) keys[(size_t)b * stride + j] = s;
+  }
+}
+
+hipError_t launch_lr_score_mfma(const uint16_t* z2, const uint16_t* t, int B, int N, int r, int relu, double* keys,
+                                long long stride, hipStream_t s) {
+  constexpr int kRows = 16 * kLsThreads / kWave;
+  return launch(k_lr_score_mfma, dim3((N + kRows - 1) / kRows, (B + 15) / 16), dim3(kLsThreads), 0, s, z2, t, B, N, r, relu,
+                keys, stride);
+}
+
+// ---------------------------------------------------------------------------------------------------
 // Filter stage of the exact pre-activations for batches (filter and refine): candidate rows times tokens on the
 // bf16 matrix cores, 50 times the fp64 rate, so the stage is a read of the candidate rows.  Tokens are the A matrix,
 // candidate rows the B matrix of a 16x16x32 MFMA: lane (j, g) feeds 16-byte chunk 4 it + g of token j and of
@@ -499,12 +554,12 @@ __global__ __launch_bounds__(256 * TG * KS) void k_filter_units(FilterUnits p) {
 // stage's rows do not depend on it where nearly all of them are read anyway, or where they are few.  run_front says which
 // layouts take it.  d = 2048,
 // 64 tokens, 16384 rows: 23.6 us against 8.1 + 19.8 one after the other.
-template <int TT, int TG, int KS, int LOADS>
+template <int TT, int TG, int KS, typename K, int LOADS>
 __global__ __launch_bounds__(256 * TG * KS) void k_select_filter(KeysSelect ks, FilterUnits p) {
-  static_assert(256 * TG * KS == kSelThreads && sizeof(KeysSelectShared) <= kFtStages * ft_stage_bytes(TT), "one workgroup fits both");
+  static_assert(256 * TG * KS == kSelThreads && sizeof(KeysSelectShared<K>) <= kFtStages * ft_stage_bytes(TT), "LDS fits both");
   extern __shared__ __align__(16) unsigned char lds[];
   const int tile = (int)blockIdx.x - p.B;
-  if (tile < 0) keys_select_token<LOADS>(ks, (int)blockIdx.x, *reinterpret_cast<KeysSelectShared*>(lds));  // uniform
+  if (tile < 0) keys_select_token<K, LOADS>(ks, (int)blockIdx.x, *reinterpret_cast<KeysSelectShared<K>*>(lds));  // uniform
   else filter_units_tile<TT, TG, KS>(p, tile, lds);
 }
 
@@ -724,29 +779,30 @@ hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int 
   return go(k_filter_units<4, 2, 2>, 4, 16, raised_to[2]);
 }
 
-hipError_t launch_select_filter(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
-                                const float* smax, uint32_t* bitmap, uint32_t* window_misses, const uint16_t* W,
-                                const uint16_t* x, int d, float* h, long long stride_h, float* xnorm, float* wnorm_tiles,
-                                hipStream_t s) {
-  if (B < 1 || B > 64 || d % 8 != 0 || N > 32768 || stride % 4 != 0 || reinterpret_cast<uintptr_t>(keys) % 16 != 0)
-    return hipErrorInvalidValue;
-  const KeysSelect ks{keys, stride, N, kprime, sumabs, smax, bitmap, window_misses};
-  const FilterUnits p{W, x, B, d, nullptr, nullptr, N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B)};
-  static std::atomic<size_t> raised_to[6] = {};
+hipError_t launch_select_filter(const KeysSelect& ks, int B, const uint16_t* W, const uint16_t* x, int d, float* h,
+                                long long stride_h, float* xnorm, float* wnorm_tiles, hipStream_t s) {
+  if (B < 1 || B > 64 || d % 8 != 0 || !keys_select_ok(ks)) return hipErrorInvalidValue;
+  const FilterUnits p{W, x, B, d, nullptr, nullptr, ks.N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B)};
+  static std::atomic<size_t> raised_to[9] = {};
   auto go = [&](auto kernel, int tt, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
       return e;
-    return launch(kernel, dim3(B + filter_tiles(N)), dim3(kSelThreads), lds, s, ks, p);
+    return launch(kernel, dim3(B + filter_tiles(ks.N)), dim3(kSelThreads), lds, s, ks, p);
   };
-  if (N <= 16384) {
-    if (B <= 16) return go(k_select_filter<1, 1, 4, 4>, 1, raised_to[0]);
-    if (B <= 32) return go(k_select_filter<2, 2, 2, 4>, 2, raised_to[1]);
-    return go(k_select_filter<4, 2, 2, 4>, 4, raised_to[2]);
+  if (ks.f64) {
+    if (B <= 16) return go(k_select_filter<1, 1, 4, uint64_t, 8>, 1, raised_to[6]);
+    if (B <= 32) return go(k_select_filter<2, 2, 2, uint64_t, 8>, 2, raised_to[7]);
+    return go(k_select_filter<4, 2, 2, uint64_t, 8>, 4, raised_to[8]);
   }
-  if (B <= 16) return go(k_select_filter<1, 1, 4, 8>, 1, raised_to[3]);
-  if (B <= 32) return go(k_select_filter<2, 2, 2, 8>, 2, raised_to[4]);
-  return go(k_select_filter<4, 2, 2, 8>, 4, raised_to[5]);
+  if (ks.N <= 16384) {
+    if (B <= 16) return go(k_select_filter<1, 1, 4, uint32_t, 4>, 1, raised_to[0]);
+    if (B <= 32) return go(k_select_filter<2, 2, 2, uint32_t, 4>, 2, raised_to[1]);
+    return go(k_select_filter<4, 2, 2, uint32_t, 4>, 4, raised_to[2]);
+  }
+  if (B <= 16) return go(k_select_filter<1, 1, 4, uint32_t, 8>, 1, raised_to[3]);
+  if (B <= 32) return go(k_select_filter<2, 2, 2, uint32_t, 8>, 2, raised_to[4]);
+  return go(k_select_filter<4, 2, 2, uint32_t, 8>, 4, raised_to[5]);
 }
 
 hipError_t launch_filter_ranks(const uint16_t* W, const uint16_t* x, int B, int d, const int32_t* list,

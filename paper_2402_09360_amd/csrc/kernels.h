@@ -94,15 +94,15 @@ int scorer_mfma_maxima(int N);  // maxima it leaves per token (long rows): two p
 
 // t[b,:] = bf16(Z1^T x_b); also clears zero_words words at zero_ptr and, as a step's first kernel, checks the
 // general header (optional) against the layout signature.
-// partial: fp64 [B, lr_project_slices(d), r] scratch.
-int lr_project_slices(int d);
-hipError_t launch_lr_project(const uint16_t* z1, const uint16_t* x, int B, int d, int r, uint16_t* t, double* partial,
-                             uint32_t* zero_ptr, int zero_words, void* general_header, unsigned long long sig,
-                             hipStream_t s);
-// One token: keys[j] = phi(<Z2[j,:], t>) in fp64.  Batches run launch_gather_dot_mfma over all rows instead.
+hipError_t launch_lr_project(const uint16_t* z1, const uint16_t* x, int B, int d, int r, uint16_t* t, uint32_t* zero_ptr,
+                             int zero_words, void* general_header, unsigned long long sig, hipStream_t s);
+// One token: keys[j] = phi(<Z2[j,:], t>) in fp64.  Batches: launch_lr_score_mfma.
 // *out = an upper bound of the largest row norm of the bf16 matrix W [rows, cols] (cols a multiple of 8).
 hipError_t launch_row_norm_max(const uint16_t* W, int rows, int cols, float* out, hipStream_t s);
 hipError_t launch_lr_score(const uint16_t* z2, const uint16_t* t, int N, int r, int relu, double* keys, hipStream_t s);
+// The same for batches on the fp64 matrix cores (gather_mfma.hip); keys [B, stride].
+hipError_t launch_lr_score_mfma(const uint16_t* z2, const uint16_t* t, int B, int N, int r, int relu, double* keys,
+                                long long stride, hipStream_t s);
 
 // Clears `words` 32-bit words.
 hipError_t launch_clear_words(uint32_t* p, int words, hipStream_t s);
@@ -209,10 +209,19 @@ hipError_t launch_bitmap_compact(const uint32_t* bitmap, int words, int32_t* lis
 // ---- batch_select.hip --------------------------------------------------------
 // The selections of a batched FFN step, one workgroup per token, rows of at most 32768 units, k <= 4096.
 bool batch_select_supported(int N, int k);
-// The k' largest keys of every row (non-negative fp32 rows of keys, stride a multiple of 4) -> bits of the union
-// bitmap.  sumabs[b], *smax: bound of token b's keys (launch_quantize_tokens, the trailer of the packed codes).
-hipError_t launch_keys_select(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
-                              const float* smax, uint32_t* bitmap, uint32_t* window_misses, hipStream_t s);
+// The k' largest keys of every row of non-negative keys -> bits of the union bitmap (which must be clear).
+struct KeysSelect {
+  const void* keys;    // [B, stride] fp32, or
+  bool f64;            // fp64 (rows of at most kKeysSelectMaxF64); rows at multiples of 16 bytes
+  long long stride;
+  int N, kprime;
+  const float* sumabs;  // fp32: sumabs[b], *smax bound token b's keys (the sums of the absolute codes, the trailer of the
+  const float* smax;    // packed codes)
+  uint32_t* bitmap;
+  uint32_t* window_misses;
+};
+constexpr int kKeysSelectMaxF64 = 16384;
+hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s);
 // The k largest activations relu(<W[j, :], x_b>) of every token among the bitmap's units, ties to the lower unit, from
 // the filter stage's values in unit order (launch_filter_units).
 constexpr int kRefineTokenMax = 8192;  // longest token staged in LDS
@@ -300,11 +309,9 @@ int filter_tiles(int n);
 hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int d, const uint32_t* bitmap,
                                const int32_t* n_dev, int n_rows, float* h, long long stride_h, float* xnorm,
                                float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s);
-// launch_keys_select and, at the same time, launch_filter_units over all N rows: keys and h do not overlap.
-hipError_t launch_select_filter(const float* keys, long long stride, int B, int N, int kprime, const float* sumabs,
-                                const float* smax, uint32_t* bitmap, uint32_t* window_misses, const uint16_t* W,
-                                const uint16_t* x, int d, float* h, long long stride_h, float* xnorm, float* wnorm_tiles,
-                                hipStream_t s);
+// launch_keys_select and, at the same time, launch_filter_units over all rows: keys and h do not overlap.
+hipError_t launch_select_filter(const KeysSelect& ks, int B, const uint16_t* W, const uint16_t* x, int d, float* h,
+                                long long stride_h, float* xnorm, float* wnorm_tiles, hipStream_t s);
 // Classifier (phi = identity): the candidate of rank t (of un's bitmap over n_rows classes, or list with n_dev) goes to
 // h[b*stride_h + t]; n_cap <= kSoftmaxRefineMaxRow.  wnorm_tiles [filter_rank_blocks(n_cap)]; maxima [B,
 // kFilterMaxima], 4 filter_rank_blocks(n_cap) of them per token: the largest values of as many disjoint groups of
@@ -370,14 +377,14 @@ struct FfnFastArgs {
   int8_t* xq;
   float* sumabs;
   // Low-rank scorer (lowrank, up to four tokens; otherwise the int4 one): keys are fp64 (keys64, [B, key_stride], rows of
-  // whole 16-byte vectors), t_partial holds B * lr_project_slices(d) * r doubles, norm_bounds the two row-norm bounds of
+  // whole 16-byte vectors), t the bf16 intermediate [B, r], norm_bounds the two row-norm bounds of
   // hire_lr_prepare.  Plain units only (gs = 0, m1 = 0).
   bool lowrank;
   const void* lr_a;
   const void* lr_b;
   int r;
   const float* norm_bounds;
-  double* t_partial;
+  uint16_t* t;
   double* keys64;
   // int4 low-rank scorer (lrq, up to four tokens): lr_a / lr_b are the packed blobs of Z1 transposed and Z2 with their
   // scales, keys_t B * r + 4 floats for the intermediate; the keys are fp32 (keys); norm_bounds[0] bounds the rows of w1u

@@ -8,9 +8,9 @@
 
 namespace hire {
 
-template <int LOADS>
+template <typename K, int LOADS>
 struct BatchKeys {
-  using Keys = KeyRegs<uint32_t, LOADS, kSelThreads>;
+  using Keys = KeyRegs<K, LOADS, kSelThreads>;
   static_assert(LOADS * Keys::PER <= 32, "one bit per key of a lane");
 };
 
@@ -40,47 +40,62 @@ __device__ __forceinline__ bool window_bin(const Keys& kr, uint32_t anchor, int 
 }
 
 // ---------------------------------------------------------------------------------------------------
-// sumabs[b]: sum of the token's |int8 codes|, *smax: the largest row scale of the int4 copy that the keys were scored
-// with: key_j = fl(fl(acc_j) s_j) <= fl(7 sumabs smax), rounding being monotone (7 sumabs < 2^24).
-struct KeysSelect {
-  const float* keys;   // [B, stride], rows at multiples of 16 bytes
-  long long stride;
-  int N, kprime;
-  const float* sumabs;
-  const float* smax;
-  uint32_t* bitmap;
-  uint32_t* window_misses;
-};
+// The window's anchor.  fp32 keys (the int4 scorers): sumabs[b], sum of the token's |int8 codes|, and *smax, the largest row
+// scale of the int4 copy that the keys were scored with, bound them: key_j = fl(fl(acc_j) s_j) <= fl(7 sumabs smax),
+// rounding being monotone (7 sumabs < 2^24).  fp64 keys (the low-rank scorer) have no bound at hand: their maximum, through
+// one barrier more.
+template <typename K>
 struct KeysSelectShared {
   __align__(16) uint32_t win[kWin];
   SelSharedT<kSelThreads> sh;
+  unsigned long long wave_top[kSelWaves];
   int wave_cnt[kSelWaves];
   int off_window;  // not 0: the window does not count every key that it should
-  BinList<uint32_t> list;
+  BinList<K> list;
 };
 
+inline bool keys_select_ok(const KeysSelect& p) {
+  return p.N <= (p.f64 ? kKeysSelectMaxF64 : 32768) && p.stride % (p.f64 ? 2 : 4) == 0 &&
+         reinterpret_cast<uintptr_t>(p.keys) % 16 == 0;
+}
+
 // Token b, by the whole workgroup.
-template <int LOADS>
-__device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, KeysSelectShared& S) {
-  using Keys = typename BatchKeys<LOADS>::Keys;
+template <typename K, int LOADS>
+__device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, KeysSelectShared<K>& S) {
+  using Keys = typename BatchKeys<K, LOADS>::Keys;
   constexpr int PER = Keys::PER;
   const int tid = (int)threadIdx.x, lane = lane_id(), N = p.N, kprime = p.kprime;
   auto& sh = S.sh;
   auto& win = S.win;
   auto& list = S.list;
   HIRE_TS(10);
-  const float* row = p.keys + (size_t)b * p.stride;
+  const K* row = static_cast<const K*>(p.keys) + (size_t)b * p.stride;
   Keys kr;
   kr.issue_clamped(row, N);  // rows are padded to whole vectors
-  const uint32_t anchor = fine_bin(__float_as_uint(7.0f * p.sumabs[b] * *p.smax));
   {
     uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
     z[0] = z[1] = make_uint4(0, 0, 0, 0);
   }
   if (tid == 0) sh.list_n = S.off_window = 0;
-  kr.finish();
-  kr.mask_beyond(N);
-  __syncthreads();
+  uint32_t anchor;
+  if constexpr (sizeof(K) == 4) {
+    anchor = fine_bin(__float_as_uint(7.0f * p.sumabs[b] * *p.smax));
+    kr.finish();
+    kr.mask_beyond(N);
+    __syncthreads();
+  } else {
+    kr.finish();
+    kr.mask_beyond(N);
+    K top = 0;  // non-negative doubles order like their bits
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+      for (int q = 0; q < PER; ++q) top = kr.r[e][q] > top ? kr.r[e][q] : top;
+    top = wave_max(top);
+    if (lane == 0) S.wave_top[wave_id()] = top;
+    __syncthreads();
+    anchor = fine_bin((K)wave_max((K)(lane < kSelWaves ? S.wave_top[lane] : 0)));
+  }
   HIRE_TS(11);
   uint32_t bin;
   int above;
@@ -90,20 +105,20 @@ __device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, Ke
   HIRE_TS(12);
   uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
   if (known) {
-    const BinMasks<uint32_t> bm = bin_masks<uint32_t>(kr, bin_floor<uint32_t>(bin), bin_floor<uint32_t>(bin + 1u));
-    list_inside<uint32_t>(kr, bm.inside, &sh.list_n, list);
+    const BinMasks<K> bm = bin_masks<K>(kr, bin_floor<K>(bin), bin_floor<K>(bin + 1u));
+    list_inside<K>(kr, bm.inside, &sh.list_n, list);
     __syncthreads();
     HIRE_TS(13);
     const int m = sh.list_n;
     known = m <= kFastAmbCap && S.off_window == 0;  // uniform
     if (known)
-      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : 0u, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
+      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : (K)0, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
                                       kprime - above);
     HIRE_TS(14);
   }
   if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
     WinRegs<kSelThreads> none{};
-    const Selection<uint32_t> sel =
+    const Selection<K> sel =
         fast_select<60>(kr, row, kprime, none, 0u, false, sh, S.wave_cnt, p.window_misses, 0, kprime, true);
     take = 0u;
 #pragma unroll
@@ -112,17 +127,19 @@ __device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, Ke
       for (int q = 0; q < PER; ++q)
         take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
   }
-  // A bitmap word covers 32 consecutive indices: the keys of eight neighbouring lanes of one load.  Those lanes
+  // A bitmap word covers 32 consecutive indices: the keys of 32 / PER neighbouring lanes of one load.  Those lanes
   // fold their bits together and one of them adds the word to the union.
-  static_assert(PER == 4, "eight lanes per word");
+  constexpr int kLanes = 32 / PER;
+  static_assert(kLanes == 8 || kLanes == 16, "lanes per word");
   take = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
 #pragma unroll
   for (int e = 0; e < LOADS; ++e) {
-    uint32_t bits = (take >> (e * PER) & 15u) << (lane % 8 * PER);
+    uint32_t bits = (take >> (e * PER) & ((1u << PER) - 1u)) << (lane % kLanes * PER);
     bits |= dpp_move<0xB1, 0xF>(0u, bits);   // lanes 1, 0, 3, 2 of a quad
     bits |= dpp_move<0x4E, 0xF>(0u, bits);   // lanes 2, 3, 0, 1
     bits |= dpp_move<0x141, 0xF>(0u, bits);  // eight lanes mirrored: the other quad
-    if (lane % 8 == 0 && bits != 0u) atomicOr(&p.bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / 8], bits);
+    if constexpr (kLanes == 16) bits |= dpp_move<0x140, 0xF>(0u, bits);  // sixteen: the other eight
+    if (lane % kLanes == 0 && bits != 0u) atomicOr(&p.bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / kLanes], bits);
   }
   HIRE_TS(15);
 }

@@ -45,3 +45,18 @@ def test_a_unit_outside_the_union_is_never_selected(hire, oracle):
     packed[37] = 0
     got, _ = T.check_ffn(layer, (kind, q, s), L, x, k, kp)
     assert 37 not in got["cand"]
+
+
+@pytest.mark.parametrize("d,N,r,B,k,kp", [
+    (40, 64, 8, 9, 3, 9), (72, 777, 24, 16, 20, 60), (520, 5003, 136, 17, 100, 1003),   # odd rows, ranks and token lengths
+    (1032, 1033, 1024, 5, 50, 200), (64, 16384, 16, 33, 819, 3276), (64, 16384, 40, 64, 100, 900),  # beside the filter stage
+    (1024, 13000, 24, 6, 400, 700),                                                      # in front of it
+    (64, 16390, 16, 12, 300, 2000)])                                                     # rows too long for the fp64 keys
+def test_lowrank_keys(hire, oracle, d, N, r, B, k, kp):
+    """fp64 keys: the projection's sums over all rows of Z1, the scores of whole rows per wave, their selection."""
+    print(f"ffn_step lowrank d={d} N={N} r={r} B={B} k={k} k'={kp}", flush=True)
+    L = I.lowrank_ffn_layer(990 + d, d, N, r)
+    layer, scorer = T.make_ffn_layer(L, lowrank=True)
+    x = I.tokens(991 + B, B, d)
+    x[1, :] = 0
+    T.check_ffn(layer, scorer, L, x, k, kp)
