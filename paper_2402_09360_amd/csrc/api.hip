@@ -22,8 +22,7 @@ constexpr size_t kAlign = 256;
 constexpr int kSingleWgMaxRow = 32768;  // up to this row length one workgroup per token selects the k' keys
 constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the gather run on the matrix cores
 // FFN step, rows of at most 32768 units: filter and refine from kFilterMinBatch tokens on.  Up to four tokens are one tile
-// of the fp64 matrix cores (d = 512, 20003 units: 38 / 39 / 41 us for 2 / 3 / 4 tokens against 46 / 47 / 48; five: 43
-// against 49 there, but 58 against 53 at d = 2048 with 16384 units and 40 against 36 at d = 800 with 5003).  From
+// of the fp64 matrix cores (d = 512, 20003 units: 38 / 39 / 41 us for 2 / 3 / 4 tokens against 46 / 47 / 48).  From
 // kFilterValuesMinBatch on values of the filter stage may be handed out (hire_ffn_step says which).
 constexpr int kFilterMinBatch = 5;
 constexpr int kFilterValuesMinBatch = 16;
@@ -119,7 +118,7 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.cap_u = (int)((long long)B * kps < (long long)Ns ? B * kps : Ns);
   s.words = (Ns + 31) / 32 + 2;
   const bool fast = ffn && (gs == 3 ? ffn_fast_group8_supported(B, N, d, k, kprime)
-                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime, scorer_kind == HIRE_SCORER_INT4)));
+                                    : (gs == 0 && ffn_fast_supported(B, N, d, k, kprime)));
   s.hist.header = c.take<char>(general_header_bytes());
   s.fast_region = c.take<char>((ffn && !fast ? 1 : kFastTokens) * kFastRegionBytes);
   s.sig = layout_signature(scorer_kind, B, d, N, r, k, kprime, (ffn ? 1 : 0) + 16 * gs) | (ffn && !fast ? kSigOverlays : 0);
@@ -603,7 +602,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   const bool fast_int4 = L->scorer_kind == HIRE_SCORER_INT4;
   const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr;
   const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && scorer_int4_fused_supported(d);
-  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime, fast_int4) && !g_force_generic &&
+  if ((fast_int4 || fast_lr || fast_lrq) && ffn_fast_supported(B, N, d, k, kprime) && !g_force_generic &&
       !(B > 1 && g_force_exact_stage)) {
     FfnFastArgs a{};
     a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;

@@ -939,12 +939,12 @@ int ffn_fast_entries(int N, int gs) { return ((N + kOwnUnits - 1) / kOwnUnits * 
 
 // Group-sparse step with groups of eight: N, k, k' count units.  The selections see N/8, k'/8 and k/8 entries.
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime) {
-  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime, true, true);
+  return N % 8 == 0 && k % 8 == 0 && kprime % 8 == 0 && ffn_fast_supported(B, N, d, k, kprime, true);
 }
 
-bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool int4, bool groups) {
+bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool groups) {
   return N <= kFastMaxUnits && d % 32 == 0 && d >= 64 && d <= 8192 && k >= 1 && kprime <= N &&
-         (B == 1 || ffn_fast_tokens_supported(B, N, d, int4, groups));
+         (B == 1 || ffn_fast_tokens_supported(B, d, groups));
 }
 
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {

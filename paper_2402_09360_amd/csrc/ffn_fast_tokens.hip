@@ -1,9 +1,9 @@
-// HiRE-FFN step for two to eight tokens (arXiv 2402.09360, Algorithm 1 + eq. (4); ffn_fast_tokens_supported says which):
+// HiRE-FFN step for two to four tokens, groups of eight up to eight (arXiv 2402.09360, Algorithm 1 + eq. (4)):
 // the scorer and the gather of the batch-1 sequence (ffn_fast.hip) for several tokens at once; the second layer is that
 // sequence's own kernel, a row of workgroups per token.
 //
-// The longer sequence for batches runs seven kernels, of which the two selections keep one compute unit per token busy
-// for 6 and 10 us: at a few tokens that is a third of the step.  Here nothing runs on a unit per token.  The scorer
+// The two selections of the longer sequence for batches keep one compute unit per token busy for 6 and 10 us.  Here nothing
+// runs on a unit per token.  The scorer
 // counts every token's keys into a window histogram in memory; every workgroup of the gather walks all tokens'
 // histograms, knows which of its own 64 units are shortlisted, and forms their activations for all tokens in fp64 on
 // the matrix cores, so that no band around the threshold has to be computed again.
@@ -521,20 +521,22 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
 // ---------------------------------------------------------------------------------------------------
 static int token_slots(int B) { return B <= 4 ? 4 : 8; }
 
-// Steps on units: up to four tokens; five to eight (int4 scorer) while the rows are short.  With more tokens the fp64
-// products and two windows of counters per wave outweigh the selections saved, the more so the more keys there are: the
-// longer sequence, its values rounded from 64 bits like these, against this one in us per step, for 5 / 6 / 7 / 8 tokens
-//   d = 1024,  4096 units  37.2 38.3 38.0 37.9   32.0 32.7 34.5 36.4
-//   d =  800,  5003 units  36.4 37.1 37.2 37.5   31.5 32.4 33.5 34.6
-//   d = 4096,  8192 units  59.0 60.5 61.4 63.3   56.4 58.9 61.5 67.4
-//   d =  512, 16000 units  36.9 37.1 38.0 38.6   40.0 43.2 46.1 49.7
-//   d = 2048, 16384 units  53.1 54.8 56.7 58.2   51.7 55.5 60.3 68.0
+// Steps on units: up to four tokens.  With more the fp64 products and two windows of counters per wave outweigh the
+// selections saved: the longer sequence (its values rounded from 64 bits like these, k' = N / 5) against this one in us per step,
+// int4 scorer, for 2 / 3 / 4 and 5 / 6 / 7 / 8 tokens
+//   d =  256,  1024 units  27.9 24.3 24.5   21.4 22.1 23.8 and 24.2 24.6 24.4 24.7   25.8 26.8 27.9 29.0
+//   d = 1024,  4096 units  32.5 29.2 29.0   24.4 25.1 27.1 and 29.3 29.7 29.6 29.8   31.2 32.5 33.5 36.0
+//   d =  800,  5003 units  31.3 28.8 28.8   23.6 24.8 26.8 and 29.0 29.1 29.2 29.4   30.8 31.8 32.9 33.9
+//   d = 4096,  8192 units  48.9 51.1 52.4   35.9 39.9 45.8 and 54.7 55.2   56.8 59.4
+//   d = 2048,  8192 units  37.5 35.7 36.1   28.6 30.0 33.7 and 36.5 36.8   41.5 43.9
+//   d =  512, 16000 units  34.0 30.5 31.0   28.0 30.6 34.5
+//   d = 2048, 16384 units  42.7 44.3 46.4   34.0 37.8 43.7
 // Groups of eight, whose longer sequence forms its activations in fp64 too, gain up to eight (275 us for four layers
 // against 322 with dense units, 164 against 166 for a small layer without).  The scorer keeps a token in four vectors per
 // thread.
-bool ffn_fast_tokens_supported(int B, int N, int d, bool int4, bool groups) {
+bool ffn_fast_tokens_supported(int B, int d, bool groups) {
   if (B < 2 || B > kFastTokens || token_slots(B) * d > 32768) return false;
-  return groups || B <= 4 || (int4 && N * (B - 2) <= 32768);
+  return groups || B <= 4;
 }
 
 hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lrq, hipStream_t s) {

@@ -400,12 +400,12 @@ size_t ffn_fast_fallbacks_offset();  // two uint32 counters inside the region
 // Where the region keeps its cookie (and the value that says "key histogram all zero") and its two histograms.
 void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_t* hist1_off, size_t* hist2_off,
                            size_t* hist_words);
-bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool int4, bool groups = false);
+bool ffn_fast_supported(int B, int N, int d, int k, int kprime, bool groups = false);
 bool ffn_fast_group8_supported(int B, int N, int d, int k, int kprime);  // the same route for groups of eight units
 int ffn_fast_entries(int N, int gs);
 hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s);
 // ---- ffn_fast_tokens.hip: the first two kernels for two to kFastTokens tokens
-bool ffn_fast_tokens_supported(int B, int N, int d, bool int4, bool groups);
+bool ffn_fast_tokens_supported(int B, int d, bool groups);
 hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lrq, hipStream_t s);
 hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s);
 
