@@ -589,6 +589,7 @@ constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
 using W2Shared = SelSharedT<kWT>;
 constexpr int kW2Batch = 8;  // loads a lane has in flight
+constexpr int kFastMaxUnits = 16384;
 
 struct FastW2Params {    // (what the first loads need comes first)
   FastRegion* fr;        // of the first token
@@ -598,6 +599,7 @@ struct FastW2Params {    // (what the first loads need comes first)
   int col_slices;
   int out_block;         // the workgroup that writes topk_idx / topk_val; -1: none
   int list_block;        // the workgroup that writes the shortlist; -1: none
+  int shared_out;        // != 0 (several tokens, groups): the slices' workgroups write both beside their columns
   // gs = 3 (group-sparse step): entries are groups of eight units, u32 holds the units' activations.
   int gs;
   const float* u32;      // [B, entries << gs]
@@ -624,6 +626,45 @@ __device__ __forceinline__ int slice_of(int b, int slices) {
   if (slices % 16 != 0) return b;
   return 2 * (b % 8) + (b / 8) % 2 + 16 * (b / 16);
 }
+
+// Several tokens: the union of the shortlists in ascending order and its length, for the caller, a share of its words by one
+// wave of every workgroup that writes columns: issue() among the kernel's first loads, write() when the wave has nothing
+// else to do.  (A workgroup of its own would wait for a compute unit where the slices take all of them.)
+struct UnionShare {
+  static constexpr int kSteps = kFastMaxUnits / 32 / kWave;
+  uint32_t word[kSteps];
+  __device__ __forceinline__ void issue(const FastW2Params& p) {
+    const int words = (p.n + 31) / 32;
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) word[u] = p.bitmap[min(u * kWave + lane_id(), words - 1)];
+  }
+  __device__ __forceinline__ void write(const FastW2Params& p) const {
+    const int lane = lane_id(), words = (p.n + 31) / 32, blocks = p.col_slices * p.B;
+    const int per = ((words + blocks - 1) / blocks + 1) / 2 * 2;  // an even number
+    const int lo = ((int)blockIdx.y * p.col_slices + (int)blockIdx.x) * per;
+    int ahead = 0, all = 0;
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const int c = u * kWave + lane < words ? __popc(word[u]) : 0;
+      ahead += u * kWave + lane < lo ? c : 0;
+      all += c;
+    }
+    if (lo == 0 && p.n_cand) {
+      all = wave_sum(all);
+      if (lane == 0) *p.n_cand = all;
+    }
+    int at = wave_sum(ahead);
+    const int cap = min(p.B * p.kprime, p.n);
+    for (int i = lo; i < min(lo + per, words); i += 2) {  // uniform
+      const uint32_t v = p.bitmap[min(i + (lane >> 5), words - 1)];
+      const bool in = i + (lane >> 5) < words && (v >> (lane & 31) & 1u) != 0u;
+      const uint64_t m = __ballot(in);
+      const int place = at + mask_prefix(m);
+      if (in && place < cap) p.cand_out[place] = i * 32 + lane;
+      at += __popcll(m);
+    }
+  }
+};
 
 // The shortlist in ascending order, for the caller, by one workgroup: K, LK as in the gathering kernel.
 template <typename K, int LK>
@@ -675,8 +716,13 @@ __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& 
 
 // KEY: the scorer keys' bit patterns (what the candidate list is selected from); LOADS: 16-byte loads of fp32
 // activations per thread.
+// Selected rows: streaming loads where a workgroup reads whole lines; slices of 32 columns read half of them, and the other
+// half is another workgroup's, which has to find the line in L2 (one token at the ~1B shape 24.0 us per step, 24.3 with
+// streaming loads; four tokens in slices of 64 42.4 with, 43.0 without).  Dense rows are every token's: plain loads (2736 of them
+// and four tokens, groups of eight: 46.5 -> 40.5 us per step, one token 30.3 -> 25.7).
 template <typename KEY, int LOADS, int COLS>
 __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
+  auto load_w2 = [](const uint4* row) { return COLS == 32 ? *row : load_streaming(row); };
   using K = uint32_t;
   using Keys = KeyRegs<K, LOADS, kWT, false, true>;
   constexpr int PER = Keys::PER;
@@ -719,6 +765,9 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   kr.issue(h32, p.n, p.fr->zeros);
   if (tid == 0) sh.list_n = 0;
   kr.finish();
+  const bool lists = p.shared_out != 0 && w == kWW - 1 && p.cand_out != nullptr;  // uniform over the wave
+  UnionShare share;
+  if (lists) share.issue(p);
   // rows of the wave: slot-th of every sixteen, eight columns per lane
   const int slot = lane / kRowLanes, part = lane % kRowLanes;
   const int colc = min(cs * COLS + part * 8, p.d - 8);
@@ -808,28 +857,33 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
     }
   }
   const int gs = p.gs;
-  if (output) {  // the selected entries and their activations, ascending
+  // the selected entries and their activations, ascending: every wave its own, once the waves' numbers are in wave_cnt
+  auto write_selected = [&](bool units) {
+    const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
+    const int run = w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0;
+    place_taken<Keys>(__brev(take) >> (32 - LOADS * PER), run, [&](int at, int e, int q) {
+      const int i = kr.index(e, q);
+      if (at >= p.k) return;  // (never; but whatever the workspace holds, nothing is written past the token's row)
+      if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
+      if (p.topk_val == nullptr) return;
+      if (units) {
+        p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
+      } else {  // groups of eight: their units' activations
+        const float4* act = reinterpret_cast<const float4*>(u32 + ((size_t)i << 3));
+        const float4 lo = act[0], hi = act[1];
+        const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        float* out = p.topk_val + ((b * p.k + at) << 3);
+#pragma unroll
+        for (int l = 0; l < 8; ++l) out[l] = v[l];
+      }
+    });
+  };
+  if (output) {
     const int mine = wave_sum(__popc(take));
     __syncthreads();
     if (lane == 0) wave_cnt[w] = mine;
     __syncthreads();
-    const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
-    const int run = w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0;
-    uint32_t ordered = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
-    int* places = reinterpret_cast<int*>(&red[0][0]);  // groups: for the copy of their units' activations
-    static_assert(sizeof(red) >= 2048 * sizeof(int), "2048 groups of eight at most");
-    place_taken<Keys>(ordered, run, [&](int at, int e, int q) {
-      const int i = kr.index(e, q);
-      if (at >= p.k) return;  // (never; but whatever the workspace holds, nothing is written past the token's row)
-      if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
-      if (gs != 0) places[at] = i;
-      else if (p.topk_val) p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
-    });
-    if (gs != 0 && p.topk_val) {
-      __syncthreads();
-      for (int i = tid; i < p.k << gs; i += kWT)
-        p.topk_val[(b * p.k << gs) + i] = u32[(places[i >> gs] << gs) + (i & ((1 << gs) - 1))];
-    }
+    write_selected(gs == 0);
   } else {
     // The wave's selected entries go to LDS lane by lane (any fixed order will do), at most kSegRows rows at a time;
     // their coefficients are loaded with the rows.
@@ -854,7 +908,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
         if (u * kRowsPerLoad < m) {  // uniform
           const int rc = min(u * kRowsPerLoad + slot, m - 1);
           const int unit = (seg[w][rc >> gs] << gs) + (rc & ((1 << gs) - 1));
-          wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2 + (size_t)unit * p.d + colc));
+          wv[u] = load_w2(reinterpret_cast<const uint4*>(p.W2 + (size_t)unit * p.d + colc));
           raw[u] = coef[unit];
         }
       __builtin_amdgcn_sched_barrier(0);
@@ -869,7 +923,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       for (int u = 0; u < kW2Batch; ++u)
         if (r0 + u * kWW * kRowsPerLoad < p.m1) {  // uniform
           const int rc = min(r0 + u * kWW * kRowsPerLoad + slot, p.m1 - 1);
-          wv[u] = load_streaming(reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc));
+          wv[u] = *reinterpret_cast<const uint4*>(p.W2d + (size_t)rc * p.d + colc);
           raw[u] = p.hd[b * p.m1 + rc];
         }
       __builtin_amdgcn_sched_barrier(0);
@@ -891,6 +945,12 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
       dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
     }
+    // one of the token's workgroups writes the selected groups behind its columns
+    const bool writes = p.shared_out != 0 && blockIdx.x == 0 && (p.topk_idx != nullptr || p.topk_val != nullptr);  // uniform
+    if (writes) {
+      const int mine = wave_sum(__popc(take));
+      if (lane == 0) wave_cnt[w] = mine;
+    }
     __syncthreads();
     if (tid < 8 * COLS) {
       const int c = tid % COLS, j = tid / COLS;
@@ -909,6 +969,8 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
         p.y[b * p.d + c] = t;
       }
     }
+    if (lists) share.write(p);
+    if (writes) write_selected(false);
     HIRE_TS(28);
   }
   // The key histogram has served its purpose: the workgroups clear it between them and say so in the
@@ -932,7 +994,6 @@ void ffn_fast_state_layout(size_t* cookie_off, unsigned long long* cookie, size_
 }
 int ffn_fast_score_blocks(int N) { return min(((N + kRPW - 1) / kRPW + kSW - 1) / kSW, 1024); }
 
-constexpr int kFastMaxUnits = 16384;
 
 // Entries (units or groups) of the arrays of activations: whole workgroups of the gather write them.
 int ffn_fast_entries(int N, int gs) { return ((N + kOwnUnits - 1) / kOwnUnits * kOwnUnits) >> gs; }
@@ -1038,19 +1099,27 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     p.topk_idx = a.topk_idx; p.topk_val = a.topk_val; p.y = a.y;
     p.B = a.B; p.entries = ffn_fast_entries(a.N, gs); p.bitmap = a.bitmap; p.n_cand = a.n_cand;
     // The narrowest slices whose workgroups fit the compute units, one each: what is left over would wait for a whole
-    // workgroup's time (registers do not admit two).
+    // workgroup's time (registers do not admit two).  Two workgroups more per token write the selected entries and the
+    // shortlist; where slices of half the width fit without them, the slices' workgroups do it for groups of eight (four tokens
+    // of d = 2048 with 2736 dense units: 39.2 us per step against 40.4, eight: 52.8 against 58.3).  Not for units: the code
+    // that places the selected keys of sixteen loads comes cold and costs the slices' workgroups 3 us (four tokens at the ~1B
+    // shape 43.7 against 40.4).
     const int extra = (a.topk_idx || a.topk_val ? 1 : 0) + (a.cand_out || (several && a.n_cand) ? 1 : 0);
-    int cols = 32;
+    int cols = 32, cols_alone = 32;  // with the extra workgroups, without
     while (cols < 128 && ((a.d + cols - 1) / cols + extra) * a.B > 256) cols *= 2;
+    while (cols_alone < cols && (a.d + cols_alone - 1) / cols_alone * a.B > 256) cols_alone *= 2;
+    p.shared_out = several && gs != 0 && cols_alone < cols ? 1 : 0;
+    if (p.shared_out) cols = cols_alone;
     if (lowrank && !several) cols = 32;
     p.col_slices = (a.d + cols - 1) / cols;
     int blocks = p.col_slices;
-    p.out_block = a.topk_idx || a.topk_val ? blocks++ : -1;
-    p.list_block = a.cand_out || (several && a.n_cand) ? blocks++ : -1;
+    p.out_block = !p.shared_out && (a.topk_idx || a.topk_val) ? blocks++ : -1;
+    p.list_block = !p.shared_out && (a.cand_out || (several && a.n_cand)) ? blocks++ : -1;
     // several tokens read the dense rows of a slice: on one die (workgroups go round the eight), so that they come from
     // its L2 for all but the first
     if (several && a.m1 > 0) blocks = (blocks + 7) / 8 * 8;
-    p.keys = sel_keys; p.kprime = kp_sel; p.cand_out = a.cand_out ? a.cand_out : a.cand_scratch;
+    p.keys = sel_keys; p.kprime = kp_sel;
+    p.cand_out = a.cand_out || !several || !a.n_cand ? a.cand_out : a.cand_scratch;  // (the length is wanted: listed)
     p.gs = gs; p.u32 = a.u32;
     p.W2d = a.dense_w2u; p.hd = a.h_dense; p.m1 = a.m1;
     auto go = [&](auto kernel) { return launch(kernel, dim3(blocks, a.B), dim3(kWT), 0, s, p); };
