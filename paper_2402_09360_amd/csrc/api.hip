@@ -911,8 +911,28 @@ static bool shard_args_ok(const hire_ffn_layer* L, int B, int k, int kprime, int
   return shards >= 1 && L->d_ff % shards == 0;
 }
 
+// Batches and long shards (ffn_shard_batch); behind the head as well.
+static size_t carve_shard_batch(void* ws, int B, int d, int N, int k, int shards, FfnShardBuffers* out) {
+  Carver c(ws);
+  c.take<char>(shard_partial_offset());
+  FfnShardBuffers f{};
+  f.xq = c.take<int8_t>((size_t)B * d);
+  f.sumabs = c.take<float>(B);
+  f.stride = (N + 3) / 4 * 4;
+  f.vals = c.take<float>((size_t)B * f.stride + 4);
+  f.zero_words = (N + 63) / 64 * 2 + 2;
+  f.bitmap = c.take<uint32_t>(f.zero_words);
+  f.xnorm = c.take<float>(HIRE_MAX_BATCH);
+  f.wnorm_tiles = c.take<float>(filter_tiles(N));
+  f.list = c.take<uint2>((size_t)B * shards * ((k + shards - 1) / shards));
+  if (out) *out = f;
+  return c.off;
+}
+
 size_t hire_ffn_shard_workspace_bytes(const hire_ffn_layer* L, int B, int k, int kprime, int shards) {
   if (!shard_args_ok(L, B, k, kprime, shards) || !ffn_shard_supported(L->d_ff, L->d_model, shards)) return 0;
+  if (ffn_shard_batch(B, L->d_ff, L->d_model, shards))
+    return carve_shard_batch(nullptr, B, L->d_model, L->d_ff, k, shards, nullptr);
   return shard_partial_offset() + align_up(ffn_shard_partial_floats(B, L->d_model, shards) * sizeof(float));
 }
 
@@ -935,8 +955,17 @@ int hire_ffn_shard_step(const hire_ffn_layer* L, const void* x, int B, int k, in
   a.w1u = static_cast<const uint16_t*>(L->w1u); a.w2u = static_cast<const uint16_t*>(L->w2u);
   a.x = static_cast<const uint16_t*>(x); a.y = y;
   a.topk_idx = topk_idx; a.topk_val = topk_val; a.cand = cand_idx; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
-  a.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + shard_partial_offset());
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (ffn_shard_batch(B, N, d, shards)) {
+    FfnShardBuffers f{};
+    carve_shard_batch(workspace, B, d, N, k, shards, &f);
+    HIRE_STAGE(0, st);
+    HIRE_TRY(launch_ffn_shard_batch(a, f, st));
+    HIRE_STAGE(1, st);
+    HIRE_STAGE(2, st);
+    return HIRE_OK;
+  }
+  a.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + shard_partial_offset());
   HIRE_STAGE(0, st);
   HIRE_TRY(launch_ffn_shard(a, st));
   HIRE_STAGE(1, st);

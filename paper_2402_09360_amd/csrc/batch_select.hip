@@ -386,10 +386,10 @@ hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s) {
   return launch(p.N <= 16384 ? k_keys_select<uint32_t, 4> : k_keys_select<uint32_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
 }
 
-static hipError_t launch_exact_values(const RefineParams& p, hipStream_t s) {
-  const int items = (p.k + kEvEntries - 1) / kEvEntries * p.B;
-  return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, p.list_out, p.val_out, p.W, p.x, p.B, p.k,
-                p.d);
+hipError_t launch_exact_values(uint2* lists, float* val_out, const uint16_t* W, const uint16_t* x, int B, int k, int d,
+                               hipStream_t s) {
+  const int items = (k + kEvEntries - 1) / kEvEntries * B;
+  return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, lists, val_out, W, x, B, k, d);
 }
 
 hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
@@ -403,7 +403,7 @@ hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
     return launch(kernel, dim3(p.B + (p.cand_out != nullptr ? 1 : 0)), dim3(kSelThreads), lds, s, p);
   };
   const hipError_t e = p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
-  return e == hipSuccess && p.exact_values ? launch_exact_values(p, s) : e;
+  return e == hipSuccess && p.exact_values ? launch_exact_values(p.list_out, p.val_out, p.W, p.x, p.B, p.k, p.d, s) : e;
 }
 
 }  // namespace hire

@@ -249,6 +249,9 @@ struct RefineParams {
   uint32_t* window_misses;  // optional counter: tokens that the histogram and the list in LDS did not settle
 };
 hipError_t launch_refine(const RefineParams& p, hipStream_t s);
+// The activations of the listed (token, unit) pairs, rounded once from fp64: into lists [B, k] and (optional) val_out.
+hipError_t launch_exact_values(uint2* lists, float* val_out, const uint16_t* W, const uint16_t* x, int B, int k, int d,
+                               hipStream_t s);
 
 // Histogram-guided top-k' of every token's keys and their union, for keys whose producer has filled the
 // key histograms:
@@ -431,6 +434,20 @@ struct FfnShardArgs {
 bool ffn_shard_supported(int N, int d, int shards);
 size_t ffn_shard_partial_floats(int B, int d, int shards);
 hipError_t launch_ffn_shard(const FfnShardArgs& a, hipStream_t s);         // the shards' partial rows
+// ---- ffn_shard_batch.hip: the same step for batches and long shards, in the unsharded step's kernels
+bool ffn_shard_batch(int B, int N, int d, int shards);  // whether it is the faster one
+struct FfnShardBuffers {
+  int8_t* xq;            // [B, d]
+  float* sumabs;         // [B]
+  float* vals;           // [B, stride], stride a multiple of 4: keys, then the filter stage's values
+  long long stride;
+  uint32_t* bitmap;      // union: zero_words words, whole 64-bit ones over the units
+  int zero_words;
+  float* xnorm;          // [HIRE_MAX_BATCH]
+  float* wnorm_tiles;    // [filter_tiles(N)]
+  uint2* list;           // [B, shards ceil(k/shards)]
+};
+hipError_t launch_ffn_shard_batch(const FfnShardArgs& a, const FfnShardBuffers& f, hipStream_t s);
 hipError_t launch_ffn_shard_reduce(const FfnShardArgs& a, hipStream_t s);  // y = their sum
 
 }  // namespace hire
