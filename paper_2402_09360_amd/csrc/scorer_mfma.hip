@@ -83,7 +83,8 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
 
   // The tokens' codes of a segment into LDS, a wave whole tokens: load_tokens ahead of the first request (loads return in
   // order), stage behind it.
-  constexpr int TPW = kTok / NW, kAhead = SRC == kCodes && TPW > 4 ? 4 : TPW;  // tokens of a wave, loaded ahead
+  constexpr int TPW = kTok / NW;  // tokens of a wave
+  constexpr int kMost = SRC == kCodes ? 4 : (SRC == kF32 ? 4 / VECS : TPW), kAhead = TPW > kMost ? kMost : TPW;  // (registers)
   static_assert(TPW >= 1 && TPW % kAhead == 0 && (SRC != kCodes || VECS == 2), "whole tokens, segments of 256 vectors");
   uint4 tv[kAhead][VECS], tv2[kAhead][SRC == kF32 ? VECS : 1];
   const int segq = 8 * seg_steps, xv = p.d / 16, nvec = p.d / 8;
@@ -104,20 +105,20 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
         if (i < segq) xs[t * xstride + i] = t < B && seg * segq + i < xv ? v[q][m] : make_uint4(0, 0, 0, 0);
       }
   };
+  auto load_values = [&](int q0) __attribute__((always_inline)) {
+    const uint4* x4 = reinterpret_cast<const uint4*>(p.tok.x);
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+      for (int m = 0; m < VECS; ++m) {
+        const size_t at = (size_t)min(w + (q0 + q) * NW, B - 1) * nvec + min(m * kWave + lane, nvec - 1);
+        tv[q][m] = x4[SRC == kF32 ? 2 * at : at];
+        if constexpr (SRC == kF32) tv2[q][m] = x4[2 * at + 1];
+      }
+  };
   auto load_tokens = [&](int seg) __attribute__((always_inline)) {
-    if constexpr (SRC == kCodes) {
-      load_codes(tv, seg, 0);
-    } else {
-      const uint4* x4 = reinterpret_cast<const uint4*>(p.tok.x);
-#pragma unroll
-      for (int q = 0; q < TPW; ++q)
-#pragma unroll
-        for (int m = 0; m < VECS; ++m) {
-          const size_t at = (size_t)min(w + q * NW, B - 1) * nvec + min(m * kWave + lane, nvec - 1);
-          tv[q][m] = x4[SRC == kF32 ? 2 * at : at];
-          if constexpr (SRC == kF32) tv2[q][m] = x4[2 * at + 1];
-        }
-    }
+    if constexpr (SRC == kCodes) load_codes(tv, seg, 0);
+    else load_values(0);
   };
   auto stage = [&](int seg) __attribute__((always_inline)) {
     if constexpr (SRC == kCodes) {
@@ -130,8 +131,9 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
       }
     } else {  // one segment
 #pragma unroll
-      for (int q = 0; q < TPW; ++q) {
-        const int t = w + q * NW;
+      for (int at = 0; at < TPW; ++at) {
+        const int q = at % kAhead, t = w + at * NW;
+        if (at > 0 && q == 0) load_values(at);
         float amax = 0.0f;
 #pragma unroll
         for (int m = 0; m < VECS; ++m) {
@@ -345,15 +347,15 @@ static_assert(2 * kVocabBlocks * kVocabWaves <= kWgMaxSlots, "two maxima per wav
 static int vocab_blocks(int N) { return min((N + 16 * kVocabWaves - 1) / (16 * kVocabWaves), kVocabBlocks); }
 int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 
-// Where quantising in every workgroup is cheaper than a kernel in front (4.7 us): up to 32 tokens of 2048 values, a wave
-// then has one or two.  d = 2048, 16384 rows: 16 tokens 7.1 against 4.7 + 5.9 us, 32 tokens 10.2 against 4.7 + 6.7; 128 rows:
-// 5.7 against 4.7 + 3.1.  Beyond (33 tokens of 800 values: 9.8 against 4.2 + 4.9) a wave has four tokens, one after the other.
-// More than 16384 rows are more than one workgroup per compute unit, each with the same work.  The intermediate of the int4
+// Where quantising in every workgroup is cheaper than a kernel in front (3.5 to 4.7 us): up to 32 tokens of 2048 values, a wave
+// then has one or two, or 64 of 512.  d = 2048, 16384 rows: 16 tokens 7.3 against 4.7 + 5.9 us, 32 tokens 10.7 against 4.7 +
+// 6.7; 32000 rows, 32 tokens 15.2 against 4.7 + 10.8; d = 512, 3600 rows, 64 tokens 7.8 against 4.7 + 4.6.  Beyond (33 tokens
+// of 800 values: 9.8 against 4.2 + 4.9) a wave has four long tokens, one after the other.  The intermediate of the int4
 // low-rank scorer is short (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight
 // waves would take as long as the kernel in front (57.0 against 4.7 + 53.4).
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
   if (N >= kVocabMinRows) return false;
-  return f32 ? d <= 1024 : B <= 32 && d <= 2048 && N <= 16384;
+  return f32 ? d <= 1024 : d <= (B <= 32 ? 2048 : 512);
 }
 
 template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
@@ -371,11 +373,14 @@ static hipError_t scorer_mfma_launch(ScorerBatch& p, int grid, hipStream_t s) {
   return launch(kernel, dim3(grid), dim3(kWave * RW * KW), lds, s, p);
 }
 
-// Rows per workgroup for KW > 1: as many as still give a workgroup to every compute unit.
+// Rows per workgroup for KW > 1: so many that the workgroups, one of which fills a compute unit, are 256 at most; a second
+// round costs as much as the first (20184 rows of 512 codes, 32 tokens: 7.5 us with 64 rows each, 5.4 with 128; 64 tokens of
+// 2048 codes 14.4 and 10.7).
 template <int CT, int P, int SRC, int VECS>
 static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
+  if (p.N > 16384) return scorer_mfma_launch<CT, 1, 8, 2, 2, SRC, VECS>(p, (p.N + 127) / 128, s);
   if (p.N > 8192) return scorer_mfma_launch<CT, 1, 4, 4, P, SRC, VECS>(p, (p.N + 63) / 64, s);
-  if (p.N > 1024) return scorer_mfma_launch<CT, 1, 2, 8, 2, SRC, VECS>(p, (p.N + 31) / 32, s);
+  if (p.N > 4096) return scorer_mfma_launch<CT, 1, 2, 8, 2, SRC, VECS>(p, (p.N + 31) / 32, s);
   return scorer_mfma_launch<CT, 1, 1, 16, 1, SRC, VECS>(p, (p.N + 15) / 16, s);
 }
 
@@ -390,9 +395,10 @@ static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
       return scorer_mfma_launch<CT, 2, kVocabWaves, 1, 2, kCodes, 2>(p, blocks, s);
     return scorer_mfma_launch<CT, 1, kVocabWaves, 1, 4, kCodes, 2>(p, vocab_blocks(p.N), s);
   }
-  if (p.tok.x == nullptr) return scorer_mfma_rows<CT, CT == 1 ? 4 : 2, kCodes, 2>(p, s);
-  if (p.tok.f32) return scorer_mfma_rows<CT, 2, kF32, 2>(p, s);
-  if constexpr (CT <= 2) return scorer_mfma_rows<CT, 4, kBf16, 4>(p, s);
+  if (p.tok.x == nullptr) return scorer_mfma_rows<CT, 2, kCodes, 2>(p, s);
+  if (p.tok.f32) return p.d <= 512 ? scorer_mfma_rows<CT, 2, kF32, 1>(p, s) : scorer_mfma_rows<CT, 2, kF32, 2>(p, s);
+  if (p.d <= 512) return scorer_mfma_rows<CT, 2, kBf16, 1>(p, s);
+  if constexpr (CT <= 2) return p.d <= 1024 ? scorer_mfma_rows<CT, 2, kBf16, 2>(p, s) : scorer_mfma_rows<CT, 4, kBf16, 4>(p, s);
   return hipErrorInvalidValue;
 }
 

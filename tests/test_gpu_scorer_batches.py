@@ -37,7 +37,9 @@ def _tokens(seed, B, d):
     (32, 17, 9), (2048, 1024, 16), (2048, 1025, 32),           # quantised by the scorer, 16 and 32 rows per workgroup
     (2080, 1023, 16), (96, 3001, 33), (4128, 130, 64),         # codes: long tokens, more than 32 tokens, three segments
     (64, 8192, 17), (64, 8193, 31), (160, 16384, 24),          # 32 and 64 rows per workgroup
-    (64, 16385, 16), (32, 32768, 64)])                         # two workgroups per compute unit: codes
+    (64, 16385, 16), (32, 32768, 64),                          # 128
+    (512, 4096, 33), (512, 4097, 64), (544, 4097, 33),         # more than 32 tokens: short ones are quantised here too
+    (1024, 20003, 24), (1056, 8193, 7), (2048, 16385, 17)])    # the vectors of a token per lane
 def test_ffn_rows(hire, oracle, d, N, B):
     log(f"ffn_step d={d} N={N} B={B}")
     L = I.ffn_layer(900 + d, d, N)
@@ -45,7 +47,7 @@ def test_ffn_rows(hire, oracle, d, N, B):
     T.check_ffn(layer, scorer, L, _tokens(901 + B, B, d), max(1, N // 40), max(2, N // 8))
 
 
-@pytest.mark.parametrize("d,N,r,B", [(576, 1500, 544, 64), (1536, 1537, 64, 32), (1056, 2090, 1024, 17), (64, 8200, 32, 48),
+@pytest.mark.parametrize("d,N,r,B", [(576, 1500, 544, 64), (576, 4100, 512, 64), (1536, 1537, 64, 32), (1056, 2090, 1024, 17), (64, 8200, 32, 48),
                                      (96, 20003, 96, 18), (64, 16390, 64, 3)])
 def test_ffn_rows_lrq(hire, oracle, d, N, r, B):
     """The intermediate is rounded and quantised by the second product's kernel."""
