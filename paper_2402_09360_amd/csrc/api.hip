@@ -26,8 +26,6 @@ constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the 
 // kFilterValuesMinBatch on values of the filter stage may be handed out (hire_ffn_step says which).
 constexpr int kFilterMinBatch = 5;
 constexpr int kFilterValuesMinBatch = 16;
-constexpr int kSoftmaxFilterMinBatch = 16;  // softmax step: filter and refine from here on (the refining selection is
-                                            // dearer than ranking fp64 logits until the fp64 tiles outgrow it)
 constexpr int kCounters = 64;     // int32 counters behind the union bitmap, cleared with it by a step's first kernel
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -91,6 +89,19 @@ struct StepBuffers {
   size_t bytes;
 };
 
+// Softmax step, filter and refine: for which unions (of at most cap_u classes) and k the refining selection is cheaper than
+// ranking fp64 logits.  It finds its mark from the filter stage's maxima, up to four per workgroup; with few more than k of
+// them much of the union lies above the mark, with fewer than k all of it, and what does not fit the slots goes through one
+// workgroup in rounds.  The maxima are counted for a union of 1.5 k' too, about what tokens of one query leave; beyond 32 tokens
+// it is larger, and ranking dearer.  40000 classes of d = 512, us per step, fp64 / refined: k' = 1536, k = 128, eight tokens
+// 60.9 / 46.4, fifteen 85.7 / 51.7; k' = 256, k = 128, three (48 maxima) 34 / 89, eight (128) 37 / 396, fifteen (240) 40 / 46;
+// k' = 1024, k = 512, eight 68 / 1929, fifteen 77 / 107, 64 (1024) 205 / 127.  Two tokens: k' = 1024, k = 16 36.4 / 37.4.
+bool softmax_filter(int B, int cap_u, int k, int kprime) {
+  if (B < 3 || cap_u > kSoftmaxRefineMaxRow || k > (B < 16 ? kSoftmaxRefineMaxK / 2 : kSoftmaxRefineMaxK)) return false;
+  const int blocks = filter_rank_blocks(cap_u), each = (kprime + kprime / 2 + blocks - 1) / blocks;
+  return 2 * blocks >= k && 4 * blocks * min(4, (each + 3) / 4) >= (B > 32 ? 3 : 5) * k;
+}
+
 // Whether the filter stage reads all rows of the FFN at once with the selection of k' instead of the union's rows behind it:
 // where what it reads in vain costs less than the wait that it saves, also for tokens that share most of their picks (about
 // k' (1 + log2(B) / 4) rows between them; independent ones soon need nearly all).  us per step behind the selection / beside
@@ -149,7 +160,7 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.counters = s.bitmap ? reinterpret_cast<int32_t*>(s.bitmap + s.words) : nullptr;
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
-  const bool sm_filter = !ffn && B >= kSoftmaxFilterMinBatch && gs == 0 && s.cap_u <= kSoftmaxRefineMaxRow;
+  const bool sm_filter = !ffn && gs == 0 && softmax_filter(B, s.cap_u, k, kprime);
   s.all_rows = s.by_unit && B >= kFilterMinBatch && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
                (int4_like || N <= kKeysSelectMaxF64) && filter_all_rows(B, d, N, kprime);
   if (s.by_unit && B >= kFilterMinBatch) {
@@ -991,8 +1002,7 @@ int hire_softmax_step(const hire_softmax_layer* L, const void* x, int B, int k, 
 
   // Batches: filter and refine as in the FFN step - fp32 logits with a proven error from the bf16 matrix cores,
   // fp64 only for the entries that can still be among the k largest.
-  const bool filter = B >= kSoftmaxFilterMinBatch && s.hf != nullptr && s.cap_u <= kSoftmaxRefineMaxRow &&
-                      k <= kSoftmaxRefineMaxK && d % 8 == 0 && !g_force_exact_stage;
+  const bool filter = s.hf != nullptr && d % 8 == 0 && !g_force_exact_stage;
   // One token on a long vocabulary: the scorer (both int4 kinds), the exact logits of a superset of the shortlist
   // (from the scorer's maxima), and the final selections with the softmax.
   const bool lrq = L->scorer_kind == HIRE_SCORER_LRQ;

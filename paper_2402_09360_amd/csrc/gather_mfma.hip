@@ -567,9 +567,11 @@ __global__ __launch_bounds__(256 * TG * KS) void k_select_filter(KeysSelect ks, 
 // in rank order, from the union bitmap (or a list), values to h[token][rank].  Every workgroup counts the bitmap's
 // bits itself and takes an equal contiguous share of the ranks - tiles of at most 64, equally long - and its stages
 // run on from tile to tile: the next tile's rows are requested while the current one is finished (its sums pass
-// through LDS of their own, behind barriers that do not wait for loads).  Every wave also leaves the largest value of
-// its candidates per token (maxima[token][4 workgroup + group], -inf for none): the final selection bounds the k-th
-// largest logit with them instead of passing over the row for a histogram.
+// through LDS of their own, behind barriers that do not wait for loads).  A workgroup also leaves the largest values of four
+// sets of its candidates per token (maxima[token][4 workgroup + set], -inf for none): the final selection bounds the k-th
+// largest logit with them instead of passing over the row for a histogram.  The sets are the waves' groups of sixteen, or,
+// where short tiles fill one or two of these only, quarters or halves of them: tokens of one query share most of their
+// candidates, and with fewer maxima than k everything would have to be recomputed.
 // Measured at d = 2048, 64 tokens, 57600 of 256000 classes (236 MB): 65 us (3.6 TB/s); with a workgroup per tile, each locating
 // its own 64 candidates first, 92.
 constexpr int kFrMaxRows = 256;  // candidates per workgroup
@@ -718,16 +720,19 @@ __global__ __launch_bounds__(256 * TG * KS) void k_filter_ranks(const uint16_t* 
     wmax = fmaxf(wmax, __shfl_xor(wmax, 8));
     if (lane == 0) wmx[cw] = wmax;
   }
-  if (kh == 0) {
+  const int groups = (rt + 15) / 16, split = groups == 1 ? 4 : (groups == 2 ? 2 : 1);  // sets of a group
+  if (kh == 0 && (split == 1 || cw < groups)) {  // uniform
 #pragma unroll
     for (int t = 0; t < TTW; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float v = vmax[t][r];
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) v = fmaxf(v, __shfl_xor(v, m));
-        const int tk = 16 * (tt0 + t) + 4 * g + r;
-        if (jl == 0 && tk < B) my_max[(size_t)tk * kFilterMaxima + cw] = v;
+        v = fmaxf(v, __shfl_xor(v, 1));
+        v = fmaxf(v, __shfl_xor(v, 2));
+        if (split < 4) v = fmaxf(v, __shfl_xor(v, 4));
+        if (split < 2) v = fmaxf(v, __shfl_xor(v, 8));
+        const int tk = 16 * (tt0 + t) + 4 * g + r, lanes = 16 / split;
+        if (jl % lanes == 0 && tk < B) my_max[(size_t)tk * kFilterMaxima + split * cw + jl / lanes] = v;
       }
   }
   __syncthreads();
