@@ -206,11 +206,10 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
       }
     }
     HIRE_TS(33);
-    // four row sums (wave-uniform results); lanes 0, 16, 32, 48 take rows j0 + 0, 1, 2, 3
-    const int t0 = wave_sum(acc[0]), t1 = wave_sum(acc[1]), t2 = wave_sum(acc[2]), t3 = wave_sum(acc[3]);
-    const int s = (lane & 32) ? ((lane & 16) ? t3 : t2) : ((lane & 16) ? t1 : t0);
+    // lanes 15, 31, 47, 63 take rows j0 + 0, 1, 2, 3
+    const int s = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
     const int j = j0 + (lane >> 4);
-    if ((lane & 15) == 0 && j < N) {
+    if ((lane & 15) == 15 && j < N) {
       const int sum = s >> 4;  // every partial is a multiple of 16
       float key = (float)sum * (g == gw ? pre_scale : scale[j]);
       key = key > 0.0f ? key : 0.0f;  // ReLU, and -0 -> +0
@@ -232,6 +231,188 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
       for (int l = 0; l < 8; ++l) sum += fabsf(unit_keys[tid * 8 + l]);
       gkeys[J] = sum;
       count_key(sum);
+    }
+  }
+  HIRE_TS(34);
+  if (clocks) {
+    __syncthreads();
+    if (tid == 0) clocks[2 * blockIdx.x + 1] = wall_clock64();
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Kernel 1 for the int4 low-rank scorer where both products fit one kernel: every workgroup quantises the token, forms all r
+// sums of the first product itself - the codes of Z1 transposed, r d / 2 bytes, come from L2 - rounds them to bf16, quantises
+// them, and scores its own 64 rows of Z2 with sixteen lanes per row.  Everything that does not depend on a result (the
+// token, a wave's rows of Z1 up to d = 2048, its rows of Z2) is requested at the start.  With a kernel for the first product in
+// front, and a wave's lanes on four rows of Z2 together, a step takes, us, that / this: d = 2048, 16384 units, r = 128 28.8 /
+// 25.4, r = 256 28.6 / 28.5; d = 256, 4000 units, r = 64 21.3 / 17.4, r = 256 22.5 / 20.9; r = 512 (eight rows at a time,
+// d = 1024, 8000 units) 23.5 / 26.6.
+// ROWS: rows of Z1 per wave, all of them requested at once (r <= 16 ROWS).
+constexpr int kLrqFusedRank = 256;         // largest r
+constexpr int kLrqFusedBytes = 256 << 10;  // most bytes of Z1's codes
+
+// sum of a chunk of 32 codes with its activations (two vectors of sixteen)
+__device__ __forceinline__ int chunk_dot(const uint4& v, const uint4& xa, const uint4& xb, int a) {
+  const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+  const int xd[8] = {(int)xa.x, (int)xa.y, (int)xa.z, (int)xa.w, (int)xb.x, (int)xb.y, (int)xb.z, (int)xb.w};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    a = __builtin_amdgcn_sdot4((int)(wd[t] & 0xF0F0F0F0u), xd[2 * t], a, false);
+    a = __builtin_amdgcn_sdot4((int)((wd[t] << 4) & 0xF0F0F0F0u), xd[2 * t + 1], a, false);
+  }
+  return a;
+}
+// code of a value, scale sx
+__device__ __forceinline__ int code_of(float f, float sx) {
+  return (int)fminf(fmaxf(rintf(__fdiv_rn(f, sx)), -127.0f), 127.0f);
+}
+
+template <int ROWS>
+__global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict__ q1, const float* __restrict__ scale1,
+                                                        const uint4* __restrict__ q2, const float* __restrict__ scale2,
+                                                        const uint4* __restrict__ x, int N, int d, int r,
+                                                        float* __restrict__ keys, FastRegion* __restrict__ fr,
+                                                        unsigned long long* __restrict__ clocks,
+                                                        const float* __restrict__ umax) {
+  extern __shared__ uint4 tok[];  // the token, d/8 vectors of bf16; then its codes, d/16
+  __shared__ float red[kSW], sq[kSW], t_sh[kLrqFusedRank];
+  __shared__ __align__(16) uint32_t tq[kLrqFusedRank / 4];  // the intermediate's codes
+  __shared__ int isum[kSW];
+  if (clocks && threadIdx.x == 0) clocks[2 * blockIdx.x] = wall_clock64();
+  HIRE_TS(30);
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int cpr1 = d / 32, cpr2 = r / 32, xvecs = d / 8;
+  const int sub = lane & 15, per = (r + kSW - 1) / kSW, ja = w * per;  // rows of Z1 of this wave: [ja, min(ja + per, r))
+  const unsigned long long cookie = fr->cookie;
+  const float smax = __uint_as_float(q2[(size_t)N * cpr2].x), um = umax[0];
+  for (int i = (int)blockIdx.x * kST + tid; i < kWin; i += (int)gridDim.x * kST) fr->hist2[i] = 0u;
+  const uint4 xv = x[min(tid, xvecs - 1)];  // d <= 8192: one vector per thread
+  uint4 z1[ROWS], z2;
+  auto load_z1 = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) z1[i] = q1[(size_t)min(ja + min(i, per - 1), r - 1) * cpr1 + c];
+  };
+  load_z1(min(lane, cpr1 - 1));
+  float z1_scale[ROWS / 4];
+#pragma unroll
+  for (int q = 0; q < ROWS / 4; ++q) z1_scale[q] = scale1[min(ja + 4 * q + (lane >> 4), r - 1)];
+  auto load_z2 = [&](int g) __attribute__((always_inline)) {
+    z2 = load_streaming(&q2[(size_t)min(4 * g + (lane >> 4), N - 1) * cpr2 + min(sub, cpr2 - 1)]);
+  };
+  const int gw = (int)blockIdx.x * kSW + w, waves = (int)gridDim.x * kSW;
+  load_z2(gw);
+  float row_scale = scale2[min(4 * gw + (lane >> 4), N - 1)];
+  {  // largest value, and the sum of squares of the token
+    const uint32_t ud[4] = {xv.x, xv.y, xv.z, xv.w};
+    float amax = 0.0f, xsq = 0.0f;
+    if (tid < xvecs) {
+      tok[tid] = xv;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float a = bf16_lo(ud[q]), b = bf16_hi(ud[q]);
+        amax = fmaxf(amax, fmaxf(fabsf(a), fabsf(b)));
+        xsq = fmaf(a, a, xsq);
+        xsq = fmaf(b, b, xsq);
+      }
+    }
+    amax = wave_max(amax);
+    xsq = wave_sum(xsq);
+    if (lane == 0) {
+      red[w] = amax;
+      sq[w] = xsq;
+    }
+  }
+  lds_barrier();  // the codes stay under way
+  HIRE_TS(31);
+  uint32_t* xq = reinterpret_cast<uint32_t*>(tok + xvecs);
+  {
+    const float amax = wave_max(lane < kSW ? red[lane] : 0.0f), sx = amax == 0.0f ? 1.0f : __fdiv_rn(amax, 127.0f);
+    const uint2* raw = reinterpret_cast<const uint2*>(tok);
+    for (int i = tid; i < d / 4; i += kST) {
+      const uint2 v = raw[i];
+      xq[i] = ((uint32_t)code_of(bf16_lo(v.x), sx) & 0xFFu) | ((uint32_t)code_of(bf16_hi(v.x), sx) & 0xFFu) << 8 |
+              ((uint32_t)code_of(bf16_lo(v.y), sx) & 0xFFu) << 16 | (uint32_t)code_of(bf16_hi(v.y), sx) << 24;
+    }
+  }
+  lds_barrier();
+  const uint4* xq4 = reinterpret_cast<const uint4*>(xq);
+  {
+    int acc[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) acc[i] = 0;
+    for (int c0 = 0; c0 < cpr1; c0 += kWave) {  // uniform
+      const int c = c0 + lane, cc = min(c, cpr1 - 1);
+      if (c0 > 0) load_z1(cc);
+      const uint4 xa = xq4[2 * cc], xb = xq4[2 * cc + 1];
+      if (c < cpr1) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) acc[i] = chunk_dot(z1[i], xa, xb, acc[i]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < ROWS / 4; ++q) {  // lanes 15, 31, 47, 63: rows 4 q + 0, 1, 2, 3
+      const int sum = wave_sum4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]) >> 4;  // multiples of 16
+      const int i = 4 * q + (lane >> 4);
+      if (sub == 15 && i < per && ja + i < r) {
+        const uint32_t u = __float_as_uint((float)sum * z1_scale[q] + 0.0f);  // -0 -> +0
+        t_sh[ja + i] = __uint_as_float((u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u);  // to bf16, nearest even
+      }
+    }
+  }
+  lds_barrier();
+  HIRE_TS(32);
+  {
+    float tmax = 0.0f;
+    for (int i = lane; i < r; i += kWave) tmax = fmaxf(tmax, fabsf(t_sh[i]));
+    tmax = wave_max(tmax);
+    const float st = tmax == 0.0f ? 1.0f : __fdiv_rn(tmax, 127.0f);
+    int sabs = 0;
+    if (w * kWave < r / 4) {  // uniform over the wave
+      const int i = min(tid, r / 4 - 1);
+      const float4 v = reinterpret_cast<const float4*>(t_sh)[i];
+      const int c[4] = {code_of(v.x, st), code_of(v.y, st), code_of(v.z, st), code_of(v.w, st)};
+      if (tid < r / 4) {
+        tq[i] = ((uint32_t)c[0] & 0xFFu) | ((uint32_t)c[1] & 0xFFu) << 8 | ((uint32_t)c[2] & 0xFFu) << 16 | (uint32_t)c[3] << 24;
+        sabs = abs(c[0]) + abs(c[1]) + abs(c[2]) + abs(c[3]);
+      }
+      sabs = wave_sum(sabs);
+    }
+    if (lane == 0) isum[w] = sabs;
+  }
+  lds_barrier();
+  // bounds as in k_fast_score_int4
+  const int sumabs = wave_sum(lane < kSW ? isum[lane] : 0);
+  const float xsq = wave_sum(lane < kSW ? sq[lane] : 0.0f);
+  const float bound1 = (float)(7 * sumabs) * smax;
+  const float bound2 = sqrtf(xsq * (1.0f + (float)d * 0x1p-22f)) * 1.0001f * um * 1.0001f;
+  const uint32_t anchor1 = fine_bin(__float_as_uint(bound1));
+  if (blockIdx.x == 0 && tid == 0) {
+    fr->anchor1 = anchor1;
+    fr->anchor2 = fine_bin(__float_as_uint(bound2));
+    fr->beyond2 = 0u;
+    take_cookie(fr, cookie);
+  }
+  if (blockIdx.x == 0 && tid < ((4 - (N & 3)) & 3)) keys[N + tid] = 0.0f;
+  const uint4* tq4 = reinterpret_cast<const uint4*>(tq);
+  for (int g = gw; 4 * g < N; g += waves) {  // uniform
+    if (g != gw) {
+      load_z2(g);
+      row_scale = scale2[min(4 * g + (lane >> 4), N - 1)];
+    }
+    int acc = 0;
+    if (sub < cpr2) acc = chunk_dot(z2, tq4[2 * sub], tq4[2 * sub + 1], acc);
+    auto add = [](int a, int b) { return a + b; };
+    acc = add(acc, dpp_move<0x111, 0xF>(0, acc));  // the last of the row's sixteen lanes has its sum
+    acc = add(acc, dpp_move<0x112, 0xF>(0, acc));
+    acc = add(acc, dpp_move<0x114, 0xF>(0, acc));
+    acc = add(acc, dpp_move<0x118, 0xF>(0, acc));
+    const int j = 4 * g + (lane >> 4);
+    if (sub == 15 && j < N) {
+      float key = (float)(acc >> 4) * row_scale;
+      key = key > 0.0f ? key : 0.0f;  // ReLU, and -0 -> +0
+      keys[j] = key;
+      count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1);
     }
   }
   HIRE_TS(34);
@@ -1048,6 +1229,13 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
                                   a.r, nullptr, HistRefs{nullptr, nullptr}, s);
       if (e != hipSuccess) return e;
       if ((e = launch_fast_score_tokens(a, a.keys_t, true, s)) != hipSuccess) return e;
+    } else if (a.r <= kLrqFusedRank && a.r * a.d / 2 <= kLrqFusedBytes) {
+      auto go = [&](auto kernel) {
+        return launch(kernel, dim3(score_blocks), dim3(kST), (size_t)a.d * 3, s, reinterpret_cast<const uint4*>(a.lr_a),
+                      a.lr_a_scale, reinterpret_cast<const uint4*>(a.lr_b), a.lr_b_scale, reinterpret_cast<const uint4*>(a.x),
+                      a.N, a.d, a.r, a.keys, fr, a.scorer_clocks, a.norm_bounds);
+      };
+      if ((e = a.r <= 128 ? go(k_fast_score_lrq<8>) : go(k_fast_score_lrq<16>)) != hipSuccess) return e;
     } else {
       e = launch_scorer_int4_fused(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, a.x, false, a.r, a.d, 0,
                                    a.keys_t, nullptr, HistRefs{nullptr, nullptr}, nullptr, 0, 0ull, s);
