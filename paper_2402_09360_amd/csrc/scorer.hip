@@ -230,8 +230,8 @@ __global__ __launch_bounds__(256) void k_scorer_int4(const uint4* __restrict__ q
 // ---------------------------------------------------------------------------
 // The same for one token and rows of at most 64 * CH 16-byte chunks (d <= 2048 * CH), software-pipelined: a wave
 // holds two sets of four rows in registers and issues the loads of the next set before it reduces the current
-// one, so that its memory latency overlaps its own arithmetic as well as other waves'.  Lanes 0..3 finish one row
-// each (key, store, histogram atomic), so the four keys leave as one 16-byte store.  The kernel is the first of
+// one, so that its memory latency overlaps its own arithmetic as well as other waves'.  The last lane of each row
+// of sixteen finishes one row of weights (key, store, histogram atomic).  The kernel is the first of
 // its step: every workgroup quantises the token into LDS itself (4 KB of bf16 from L2 is cheaper than a kernel of
 // its own), and together they clear the words at zero_ptr and check the workspace's layout signature.
 template <int CH>
@@ -252,7 +252,8 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
   if (hist_on && blockIdx.x == 0 && threadIdx.x == 0) set_busy(mr.hdr);
   const int groups = (N + kScorerRPW - 1) / kScorerRPW;
 
-  auto fetch = [&](int g, uint4 (&wv)[kScorerRPW][CH]) {
+  auto fetch = [&](int g, uint4 (&wv)[kScorerRPW][CH], float& sj) {
+    sj = scale[min(g * kScorerRPW + (lane >> 4), N - 1)];
 #pragma unroll
     for (int rr = 0; rr < kScorerRPW; ++rr) {
       const uint4* row = q4 + (size_t)min(g * kScorerRPW + rr, N - 1) * cpr;
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
     }
   };
   uint32_t wmax = 0u;
-  auto finish = [&](int g, const uint4 (&wv)[kScorerRPW][CH]) {
+  auto finish = [&](int g, const uint4 (&wv)[kScorerRPW][CH], float sj) {
     int acc[kScorerRPW];
 #pragma unroll
     for (int rr = 0; rr < kScorerRPW; ++rr) acc[rr] = 0;
@@ -284,15 +285,11 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
         }
       }
     }
-    int mine = 0;
-#pragma unroll
-    for (int rr = 0; rr < kScorerRPW; ++rr) {
-      const int sum = wave_sum(acc[rr]) >> 4;  // every partial is a multiple of 16
-      mine = lane == rr ? sum : mine;
-    }
-    const int j = g * kScorerRPW + lane;
-    if (lane < kScorerRPW && j < N) {
-      float key = (float)mine * scale[j];
+    static_assert(kScorerRPW == 4, "wave_sum4");
+    const int mine = wave_sum4(acc[0], acc[1], acc[2], acc[3]) >> 4;  // every partial is a multiple of 16
+    const int j = g * kScorerRPW + (lane >> 4);
+    if ((lane & 15) == 15 && j < N) {
+      float key = (float)mine * sj;
       if (relu) key = key > 0.0f ? key : 0.0f;
       if (key == 0.0f) key = 0.0f;
       keys[j] = key;
@@ -304,8 +301,9 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
   };
 
   uint4 wa[kScorerRPW][CH], wb[kScorerRPW][CH];
+  float sa = 0.0f, sb = 0.0f;
   int g = (int)blockIdx.x * 4 + wave_id();
-  if (g < groups) fetch(g, wa);  // in flight while the token is quantised
+  if (g < groups) fetch(g, wa, sa);  // in flight while the token is quantised
   {
     const uint4* xr = reinterpret_cast<const uint4*>(x);  // d is a multiple of 32: whole 16-byte chunks of 8 bf16
     const int chunks = d / 8;
@@ -336,14 +334,14 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
   }
   while (g < groups) {
     const int g1 = g + total_waves, g2 = g1 + total_waves;
-    fetch(min(g1, groups - 1), wb);
+    fetch(min(g1, groups - 1), wb, sb);
     __builtin_amdgcn_sched_barrier(0);
-    finish(g, wa);
+    finish(g, wa, sa);
     __builtin_amdgcn_sched_barrier(0);
     if (g1 >= groups) break;
-    fetch(min(g2, groups - 1), wa);
+    fetch(min(g2, groups - 1), wa, sa);
     __builtin_amdgcn_sched_barrier(0);
-    finish(g1, wb);
+    finish(g1, wb, sb);
     __builtin_amdgcn_sched_barrier(0);
     g = g2;
   }
