@@ -776,34 +776,44 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
 // than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
 // largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
 // Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
-// Measured for 16 rows of 256000, k = 1024, rank order: 21.6 us (6.3 + 9.5 + 6.4); the histogram route below took 45, of it 9 for
+// Measured for 16 rows of 256000, k = 1024, rank order: 20.2 us (4.4 + 9.5 + 6.7); the histogram route below took 45, of it 9 for
 // the ranking pass.
 constexpr int kTkGroups = 4096;
 constexpr int kTkMaxK = 2048;
-constexpr int kTkMaxThreads = 256;
+constexpr int kTkMaxGroups = 256;
 constexpr int kTkKeys = 16;  // keys per thread of the gathering kernel
 static_assert(kTkGroups == kWgMaxSlots && kAmbCap == kBucketMax, "the maxima and the list use the histogram route's places");
 static_assert(kTkMaxK * (4 + 2 * 4) <= kAmbCap * (int)sizeof(AmbEntry), "rank order from memory: the list's LDS");
 
 __device__ __forceinline__ uint32_t row_key(float v, int relu) { return order_key(relu && !(v > 0.0f) ? 0.0f : v); }
 
-// Grid (16, B).  Also the sequence's first kernel: empties the rows' lists and checks the layout signature.
-__global__ __launch_bounds__(kTkMaxThreads) void k_tk_maxima(const float* __restrict__ keys, int N, int relu,
+// Grid (16, B): 256 groups per workgroup, PARTS threads share one.  Also the sequence's first kernel: empties the rows' lists
+// and checks the layout signature.
+template <int PARTS>
+__global__ __launch_bounds__(kTkMaxGroups * PARTS) void k_tk_maxima(const float* __restrict__ keys, int N, int relu,
                                                              MultiRegion mr, GeneralHeader* gh, unsigned long long sig) {
+  constexpr int kStep = PARTS * kTkGroups;
+  __shared__ uint32_t part_max[PARTS][kTkMaxGroups];
   if (blockIdx.x == 0 && blockIdx.y == 0) general_header_check(gh, sig);
-  const int b = (int)blockIdx.y, g = (int)blockIdx.x * kTkMaxThreads + (int)threadIdx.x;
+  const int b = (int)blockIdx.y, tid = (int)threadIdx.x, own = tid % kTkMaxGroups, part = tid / kTkMaxGroups;
+  const int g = (int)blockIdx.x * kTkMaxGroups + own, first = g + part * kTkGroups;
   const float* row = keys + (size_t)b * N;
   uint32_t m = 0u;
-  for (int i0 = g; i0 < N; i0 += 16 * kTkGroups) {  // sixteen loads in flight; those past the end repeat the first
+  for (int i0 = first; i0 < N; i0 += 16 * kStep) {  // sixteen loads in flight; those past the end repeat the first
     float v[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = row[i0 + u * kTkGroups < N ? i0 + u * kTkGroups : i0];
+    for (int u = 0; u < 16; ++u) v[u] = row[i0 + u * kStep < N ? i0 + u * kStep : i0];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const uint32_t k = row_key(v[u], relu);
       m = k > m ? k : m;
     }
   }
+  part_max[part][own] = m;
+  __syncthreads();
+  if (part != 0) return;
+#pragma unroll
+  for (int q = 1; q < PARTS; ++q) m = max(m, part_max[q][own]);
   mr.wgmax[(size_t)b * kWgMaxSlots + g] = m;
   if (g == 0) mr.amb_n[b] = 0u;
 }
@@ -1495,8 +1505,13 @@ hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, 
                             float* val_out, void* general_header, void* body, unsigned long long sig, hipStream_t s) {
   GeneralHeader* gh = static_cast<GeneralHeader*>(general_header);
   const MultiRegion mr = carve_multi(&gh->multi, body, B);
-  hipError_t e = launch(k_tk_maxima, dim3(kTkGroups / kTkMaxThreads, B), dim3(kTkMaxThreads), 0, s, scores, N, relu, mr, gh,
-                        sig);
+  auto maxima = [&](auto kernel, int parts) {
+    return launch(kernel, dim3(kTkGroups / kTkMaxGroups, B), dim3(kTkMaxGroups * parts), 0, s, scores, N, relu, mr, gh, sig);
+  };
+  // as many threads per group as have sixteen entries each: one round of loads.  16 rows of 256000: 18.0, 17.0, 16.9 us for the
+  // three kernels with one, two, four; of 131072: 15.1, 14.8, 15.3; of 40000: 13.6, 13.6, 14.2
+  hipError_t e = N > 32 * kTkGroups ? maxima(k_tk_maxima<4>, 4)
+                                    : (N > 16 * kTkGroups ? maxima(k_tk_maxima<2>, 2) : maxima(k_tk_maxima<1>, 1));
   if (e != hipSuccess) return e;
   const int chunks = (N + kSelThreads * kTkKeys - 1) / (kSelThreads * kTkKeys);
   if ((e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr)) != hipSuccess) return e;
