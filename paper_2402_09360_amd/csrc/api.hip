@@ -315,15 +315,14 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     } else if (B >= kMfmaMinBatch) {
       ScorerTokens tk{s.xq, nullptr, false, nullptr, s.bitmap, s.zero_words, s.hist.header, s.sig};
       if (scorer_mfma_quantises(B, r, d, false)) tk.x = xb;
-      else HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      else HIRE_TRY(launch_quantize_tokens(xb, false, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
       HIRE_TRY(launch_scorer_int4_mfma(qa, sc.lr_a_scale, tk, B, r, d, 0, s.keys_t, r, nullptr, header_only, st));
     } else {
-      HIRE_TRY(launch_quantize_tokens(xb, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      HIRE_TRY(launch_quantize_tokens(xb, false, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
       HIRE_TRY(launch_scorer_int4(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
     }
-    // the second product's kernels round the intermediate themselves where they quantise it
-    t_is_f32 = B == 1 ? scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r)
-                      : scorer_mfma_quantises(B, N, r, true);
+    // whatever quantises the intermediate rounds it as well
+    t_is_f32 = B >= kMfmaMinBatch || (scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r));
     if (!t_is_f32) HIRE_TRY(launch_f32_to_bf16(s.keys_t, B * r, s.t, st));
   }
   if (int4_like) {
@@ -331,7 +330,8 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     const bool fused = B == 1 && scorer_int4_fused_supported(sd);
     const bool fused_batch = B >= kMfmaMinBatch && scorer_mfma_quantises(B, N, sd, t_is_f32);
     if (!fused && !fused_batch)
-      HIRE_TRY(launch_quantize_tokens(tok, B, sd, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
+      HIRE_TRY(launch_quantize_tokens(t_is_f32 ? static_cast<const void*>(s.keys_t) : tok, t_is_f32, B, sd, s.xq, s.sumabs,
+                                      s.bitmap, s.zero_words, s.hist.header, s.sig, st));
     HIRE_STAGE(1, st);
     int slots;
     if (fused) {

@@ -1222,7 +1222,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
       if (scorer_mfma_quantises(a.B, a.r, a.d, false)) {
         tok.x = a.x;
       } else {
-        if ((e = launch_quantize_tokens(a.x, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
+        if ((e = launch_quantize_tokens(a.x, false, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
         tok.xq = a.xq;
       }
       e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, tok, a.B, a.r, a.d, 0, a.keys_t,

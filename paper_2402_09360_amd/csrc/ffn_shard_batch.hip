@@ -253,7 +253,7 @@ hipError_t launch_ffn_shard_batch(const FfnShardArgs& a, const FfnShardBuffers& 
   ScorerTokens tok{f.xq, nullptr, false, nullptr, f.bitmap, f.zero_words, nullptr, 0ull};
   hipError_t e = hipSuccess;
   if (scorer_mfma_quantises(a.B, a.N, a.d, false)) tok.x = a.x;
-  else e = launch_quantize_tokens(a.x, a.B, a.d, f.xq, f.sumabs, f.bitmap, f.zero_words, nullptr, 0ull, s);
+  else e = launch_quantize_tokens(a.x, false, a.B, a.d, f.xq, f.sumabs, f.bitmap, f.zero_words, nullptr, 0ull, s);
   if (e != hipSuccess) return e;
   e = launch_scorer_int4_mfma(static_cast<const uint32_t*>(a.q4), a.q4_scale, tok, a.B, a.N, a.d, 1, f.vals, f.stride,
                               a.scorer_acc, HistRefs{nullptr, nullptr}, s);

@@ -51,9 +51,9 @@ constexpr size_t kPackTrailerBytes = 64;
 hipError_t launch_pack_int4(const uint16_t* w, int rows, int cols, uint32_t* q4, float* scale, hipStream_t s);
 hipError_t launch_unpack_int4(const uint32_t* q4, int rows, int cols, int8_t* codes, hipStream_t s);
 
-// x bf16 [B,d] -> xq int8 [B,d], sumabs fp32 [B] = sum |xq|; also clears `zero_words` 32-bit words at zero_ptr.  As
+// x bf16, or fp32 that is rounded to it (nearest even) first, [B,d] -> xq int8 [B,d], sumabs fp32 [B] = sum |xq|; also clears `zero_words` 32-bit words at zero_ptr.  As
 // a step's first kernel it checks the general header (optional) against the layout signature.
-hipError_t launch_quantize_tokens(const uint16_t* x, int B, int d, int8_t* xq, float* sumabs, uint32_t* zero_ptr,
+hipError_t launch_quantize_tokens(const void* x, bool f32, int B, int d, int8_t* xq, float* sumabs, uint32_t* zero_ptr,
                                   int zero_words, void* general_header, unsigned long long sig, hipStream_t s);
 
 // One token (B == 1): keys[j] = phi(float(sum_i q[j,i] xq[i]) * scale[j]); acc (optional) gets the integer sums.
