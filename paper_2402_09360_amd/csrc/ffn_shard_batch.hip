@@ -233,10 +233,11 @@ __global__ __launch_bounds__(kWave * kSbWaves) void k_shard_refine(ShardBatch p)
 // 26.0; d = 2048, 16 x 32 29.9 / 27.0, 256 x 64 50.8 / 42.6.  Longer ones: d = 512, 16 x 128, two tokens 20.6 / 23.9, three
 // 26.4 / 24.2; 16 x 256, one 24.0 / 24.1, two 38.5 / 25.3; 16 x 512, one 49.2 / 37.4; of 32768 units, whose filter stage
 // needs two rounds of workgroups, 256 x 128, four 34.6 / 45.4, six 58.8 / 47.6; 64 x 512, one 49.9 / 57.9, two 84.1 / 60.3.
+// d = 4096, 16 x 100, two 32.8 / 39.4, three 45.5 / 40.4.
 bool ffn_shard_batch(int B, int N, int d, int shards) {
   const int Ls = N / shards;
   if (Ls <= kWave) return B > 4 && (long long)B * d * Ls >= 3 << 16;
-  return B > 4 || B * Ls >= (N <= 16384 ? 384 : 640);
+  return B > 4 || B * Ls >= (N > 16384 ? 640 : (d > 2048 ? 256 : 384));
 }
 
 template <int E>
