@@ -153,7 +153,8 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   } else {
     s.t = c.take<uint16_t>((size_t)B * r);
     s.keys = c.take<double>((size_t)B * s.key_stride);
-    if (gs > 0) s.gkeys = c.take<double>((size_t)B * Ns);
+    s.gkey_stride = (Ns + 1) / 2 * 2;
+    if (gs > 0) s.gkeys = c.take<double>((size_t)B * s.gkey_stride);
   }
   // bitmap and counters are contiguous so that one pass clears both.  counters[0] = |U|
   s.bitmap = c.take<uint32_t>((size_t)s.words + kCounters);
@@ -785,8 +786,12 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
   if (workspace_bytes < s.bytes) return HIRE_ENOSPC;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
-  if (L->scorer_kind == HIRE_SCORER_INT4 && gs == 3 && ffn_fast_group8_supported(B, N, d, k, kprime) &&
-      !g_force_generic) {  // few tokens, groups of eight: the three-kernel route on group activations
+  // few tokens, groups of eight: the three-kernel route on group activations (the low-rank scorers' kernels take up to four)
+  const bool fast_int4 = L->scorer_kind == HIRE_SCORER_INT4;
+  const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr && B <= 4;
+  const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && B <= 4 &&
+                        scorer_int4_fused_supported(d);
+  if ((fast_int4 || fast_lr || fast_lrq) && gs == 3 && ffn_fast_group8_supported(B, N, d, k, kprime) && !g_force_generic) {
     FfnFastArgs a{};
     a.B = B; a.N = N; a.d = d; a.k = k; a.kprime = kprime;
     a.q4 = L->q4; a.q4_scale = L->q4_scale;
@@ -798,6 +803,14 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
     a.keys = static_cast<float*>(s.keys); a.key_stride = s.key_stride; a.h = s.h; a.h32 = s.h32;
     a.bitmap = s.bitmap; a.cand_scratch = s.cand;
     a.gs = 3; a.gkeys = static_cast<float*>(s.gkeys); a.gkey_stride = s.gkey_stride; a.u32 = s.u32;
+    a.lowrank = fast_lr;
+    a.lrq = fast_lrq;
+    if (fast_lr || fast_lrq) {
+      a.lr_a = L->lr_a; a.lr_b = L->lr_b; a.r = L->r; a.norm_bounds = L->row_norm_bounds;
+      a.t = s.t; a.keys64 = static_cast<double*>(s.keys); a.gkeys64 = static_cast<double*>(s.gkeys);
+      a.lr_a_scale = L->lr_a_scale; a.lr_b_scale = L->lr_b_scale; a.keys_t = s.keys_t;
+      a.xq = s.xq; a.sumabs = s.sumabs;
+    }
     if (dense != nullptr && dense->m1 > 0) {
       a.dense_w1u = dense->w1u; a.dense_w2u = dense->w2u; a.m1 = dense->m1; a.h_dense = dense->h;
     }

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
     if (lane == 0) red[w] = xsq;
     __syncthreads();
     xsq = wave_sum(lane < kSW ? red[lane] : 0.0f);
-    bound2 = sqrtf(xsq * (1.0f + (float)xn_d * 0x1p-22f)) * 1.0001f * umax[0] * 1.0001f;
+    bound2 = sqrtf(xsq * (1.0f + (float)xn_d * 0x1p-22f)) * 1.0001f * umax[0] * 1.0001f * group_factor;
   }
   const uint32_t anchor1 = fine_bin(__float_as_uint(bound1)), anchor2 = fine_bin(__float_as_uint(bound2));
   if (blockIdx.x == 0 && tid == 0) {
@@ -274,11 +274,12 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
                                                         const uint4* __restrict__ x, int N, int d, int r,
                                                         float* __restrict__ keys, FastRegion* __restrict__ fr,
                                                         unsigned long long* __restrict__ clocks,
-                                                        const float* __restrict__ umax) {
+                                                        const float* __restrict__ umax, float* __restrict__ gkeys) {
   extern __shared__ uint4 tok[];  // the token, d/8 vectors of bf16; then its codes, d/16
   __shared__ float red[kSW], sq[kSW], t_sh[kLrqFusedRank];
   __shared__ __align__(16) uint32_t tq[kLrqFusedRank / 4];  // the intermediate's codes
   __shared__ int isum[kSW];
+  __shared__ float unit_keys[kSW * kRPW];  // groups, as in k_fast_score_int4
   if (clocks && threadIdx.x == 0) clocks[2 * blockIdx.x] = wall_clock64();
   HIRE_TS(30);
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
@@ -384,8 +385,9 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
   // bounds as in k_fast_score_int4
   const int sumabs = wave_sum(lane < kSW ? isum[lane] : 0);
   const float xsq = wave_sum(lane < kSW ? sq[lane] : 0.0f);
-  const float bound1 = (float)(7 * sumabs) * smax;
-  const float bound2 = sqrtf(xsq * (1.0f + (float)d * 0x1p-22f)) * 1.0001f * um * 1.0001f;
+  const float group_factor = gkeys != nullptr ? 8.001f : 1.0f;
+  const float bound1 = (float)(7 * sumabs) * smax * group_factor;
+  const float bound2 = sqrtf(xsq * (1.0f + (float)d * 0x1p-22f)) * 1.0001f * um * 1.0001f * group_factor;
   const uint32_t anchor1 = fine_bin(__float_as_uint(bound1));
   if (blockIdx.x == 0 && tid == 0) {
     fr->anchor1 = anchor1;
@@ -393,7 +395,12 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
     fr->beyond2 = 0u;
     take_cookie(fr, cookie);
   }
-  if (blockIdx.x == 0 && tid < ((4 - (N & 3)) & 3)) keys[N + tid] = 0.0f;
+  {
+    float* arr = gkeys != nullptr ? gkeys : keys;
+    const int n = gkeys != nullptr ? N / 8 : N;
+    if (blockIdx.x == 0 && tid < ((4 - (n & 3)) & 3)) arr[n + tid] = 0.0f;
+  }
+  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
   const uint4* tq4 = reinterpret_cast<const uint4*>(tq);
   for (int g = gw; 4 * g < N; g += waves) {  // uniform
     if (g != gw) {
@@ -411,8 +418,23 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
     if (sub == 15 && j < N) {
       float key = (float)(acc >> 4) * row_scale;
       key = key > 0.0f ? key : 0.0f;  // ReLU, and -0 -> +0
-      keys[j] = key;
-      count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1);
+      if (gkeys != nullptr) {
+        unit_keys[w * kRPW + (lane >> 4)] = key;  // one pass per workgroup here
+      } else {
+        keys[j] = key;
+        count_key(key);
+      }
+    }
+  }
+  if (gkeys != nullptr) {
+    __syncthreads();
+    const int J = (int)blockIdx.x * (kSW * kRPW / 8) + tid;
+    if (tid < kSW * kRPW / 8 && J * 8 < N) {
+      float sum = 0.0f;
+#pragma unroll
+      for (int l = 0; l < 8; ++l) sum += fabsf(unit_keys[tid * 8 + l]);
+      gkeys[J] = sum;
+      count_key(sum);
     }
   }
   HIRE_TS(34);
@@ -434,14 +456,17 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
                                                        const uint16_t* __restrict__ z2, const uint4* __restrict__ x,
                                                        int B, int N, int d, int r, const float* __restrict__ bounds,
                                                        double* __restrict__ keys, long long stride,
-                                                       FastRegion* __restrict__ fr) {
+                                                       FastRegion* __restrict__ fr, int groups) {
+  // groups != 0: keys are the activations of groups of eight adjacent units, keys[J] = sum_{l<8} |key[8J + l]|
   constexpr int kWPT = kSW / TT;
   __shared__ uint4 ts[TT][128];  // t as raw bf16: r <= 1024
   __shared__ float red_t[kSW], red_x[kSW];
   constexpr int kRows = kWave / ROW_LANES;  // rows per wave and trip
+  __shared__ double unit_keys[TT][kSW * kRows];
   const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
   const int sub = lane % ROW_LANES, rw = lane / ROW_LANES;
-  const int cpr = r / 8;
+  const int cpr = r / 8, n_keys = groups ? N / 8 : N;
+  const float group_factor = groups ? 8.001f : 1.0f;
   HIRE_TS(30);
   const unsigned long long cookie = fr->cookie;  // (workgroup 0 takes it away)
   const float umax = bounds[0], zmax = bounds[1];
@@ -480,19 +505,18 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
     const float xx = wave_sum(lane < kWPT ? red_x[t * kWPT + lane] : 0.0f);
     const float tnorm = sqrtf(tt * (1.0f + (float)r * 0x1p-22f)) * 1.0001f;
     const float xnorm = sqrtf(xx * (1.0f + (float)d * 0x1p-22f)) * 1.0001f;
-    const float bound1 = tnorm * zmax * 1.0001f, bound2 = xnorm * umax * 1.0001f;
+    const float bound1 = tnorm * zmax * 1.0001f * group_factor, bound2 = xnorm * umax * 1.0001f * group_factor;
     anchor1[t] = fine_bin(__float_as_uint(bound1));
     if (blockIdx.x == 0 && tid == 0 && t < B) {
       fr[t].anchor1 = anchor1[t];
       fr[t].anchor2 = fine_bin(__float_as_uint(bound2));
       fr[t].beyond2 = 0u;
       if (t == 0) take_cookie(fr, cookie);
-      if (N & 1) keys[t * stride + N] = 0.0;  // zero padding of the handed-on keys up to a whole 16-byte vector
+      if (n_keys & 1) keys[t * stride + n_keys] = 0.0;  // zero padding of the handed-on keys up to a whole 16-byte vector
     }
   }
-  const int total = (int)gridDim.x * kSW * kRows;
-  for (int j0 = ((int)blockIdx.x * kSW + w) * kRows; j0 < N; j0 += total) {
-    const int j = j0 + rw;
+  for (int b0 = (int)blockIdx.x * kSW * kRows; b0 < N; b0 += (int)gridDim.x * kSW * kRows) {  // uniform over the workgroup
+    const int j = b0 + w * kRows + rw;
     const uint4* row = reinterpret_cast<const uint4*>(z2 + (size_t)min(j, N - 1) * r);
     double acc[TT];
 #pragma unroll
@@ -528,9 +552,29 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
       }
       if (sub == ROW_LANES - 1 && j < N && t < B) {
         s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-        keys[t * stride + j] = s;
-        count_in_window((uint64_t)__double_as_longlong(s), anchor1[t], fr[t].hist1, &fr[t].beyond1);
+        if (groups) {
+          unit_keys[t][w * kRows + rw] = s;
+        } else {
+          keys[t * stride + j] = s;
+          count_in_window((uint64_t)__double_as_longlong(s), anchor1[t], fr[t].hist1, &fr[t].beyond1);
+        }
       }
+    }
+    if (groups) {  // (N is a multiple of eight, like a trip's rows)
+      constexpr int kGroups = kSW * kRows / 8;
+      lds_barrier();
+      const int t = tid / kGroups, J = b0 / 8 + tid % kGroups;
+      if (t < min(TT, B) && J < n_keys) {
+        double sum = 0.0;
+#pragma unroll
+        for (int l = 0; l < 8; ++l) sum += fabs(unit_keys[t][tid % kGroups * 8 + l]);
+        keys[t * stride + J] = sum;
+        uint32_t anchor = 0u;
+#pragma unroll
+        for (int u = 0; u < TT; ++u) anchor = t == u ? anchor1[u] : anchor;
+        count_in_window((uint64_t)__double_as_longlong(sum), anchor, fr[t].hist1, &fr[t].beyond1);
+      }
+      lds_barrier();
     }
   }
   HIRE_TS(34);
@@ -1199,15 +1243,15 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   // what the selections rank: units with their keys and activations, or groups with their summed ones
   const int n_sel = a.N >> gs, kp_sel = a.kprime >> gs, k_sel = a.k >> gs;
   const bool lowrank = a.lowrank, several = a.B > 1;
-  const void* sel_keys = lowrank ? static_cast<const void*>(a.keys64) : (gs ? a.gkeys : a.keys);
+  const void* sel_keys = lowrank ? static_cast<const void*>(gs ? a.gkeys64 : a.keys64) : (gs ? a.gkeys : a.keys);
   if (lowrank) {
-    if (gs != 0 || a.m1 != 0 || a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
+    if (a.r < 8 || a.r > 1024 || a.r % 8 != 0) return hipErrorInvalidValue;
     e = launch_lr_project(static_cast<const uint16_t*>(a.lr_a), a.x, a.B, a.d, a.r, a.t, nullptr, 0, nullptr, 0ull, s);
     if (e != hipSuccess) return e;
     const uint4* x4 = reinterpret_cast<const uint4*>(a.x);
     auto go = [&](auto kernel) {
       return launch(kernel, dim3(score_blocks), dim3(kST), 0, s, static_cast<const uint16_t*>(a.t), static_cast<const uint16_t*>(a.lr_b),
-                    x4, a.B, a.N, a.d, a.r, a.norm_bounds, a.keys64, a.key_stride, fr);
+                    x4, a.B, a.N, a.d, a.r, a.norm_bounds, gs ? a.gkeys64 : a.keys64, gs ? a.gkey_stride : a.key_stride, fr, gs);
     };
     if (a.r <= 128) e = several ? go(k_fast_score_lr<16, 4>) : go(k_fast_score_lr<16, 1>);
     else e = several ? go(k_fast_score_lr<kWave, 4>) : go(k_fast_score_lr<kWave, 1>);
@@ -1216,7 +1260,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
   } else if (a.lrq) {
     // first product: the r rows of the int4 copy of Z1^T against the token (no phi), fp32 intermediate; then the
     // scorer kernel on the int4 copy of Z2 with that intermediate as its token
-    if (gs != 0 || a.m1 != 0 || a.r < 32 || a.r > 1024 || a.r % 32 != 0) return hipErrorInvalidValue;
+    if (a.r < 32 || a.r > 1024 || a.r % 32 != 0) return hipErrorInvalidValue;
     if (several) {
       ScorerTokens tok{};
       if (scorer_mfma_quantises(a.B, a.r, a.d, false)) {
@@ -1233,7 +1277,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
       auto go = [&](auto kernel) {
         return launch(kernel, dim3(score_blocks), dim3(kST), (size_t)a.d * 3, s, reinterpret_cast<const uint4*>(a.lr_a),
                       a.lr_a_scale, reinterpret_cast<const uint4*>(a.lr_b), a.lr_b_scale, reinterpret_cast<const uint4*>(a.x),
-                      a.N, a.d, a.r, a.keys, fr, a.scorer_clocks, a.norm_bounds);
+                      a.N, a.d, a.r, a.keys, fr, a.scorer_clocks, a.norm_bounds, gs ? a.gkeys : static_cast<float*>(nullptr));
       };
       if ((e = a.r <= 128 ? go(k_fast_score_lrq<8>) : go(k_fast_score_lrq<16>)) != hipSuccess) return e;
     } else {
@@ -1243,7 +1287,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
       const size_t lds = (size_t)a.r * 2 + (size_t)a.r;
       e = launch(k_fast_score_int4<true>, dim3(score_blocks), dim3(kST), lds, s, reinterpret_cast<const uint4*>(a.lr_b),
                  a.lr_b_scale, reinterpret_cast<const uint32_t*>(a.keys_t), a.N, a.r, a.keys, static_cast<int32_t*>(nullptr),
-                 fr, a.scorer_clocks, static_cast<float*>(nullptr), reinterpret_cast<const uint4*>(a.x), a.d,
+                 fr, a.scorer_clocks, gs ? a.gkeys : static_cast<float*>(nullptr), reinterpret_cast<const uint4*>(a.x), a.d,
                  a.norm_bounds);
       if (e != hipSuccess) return e;
     }

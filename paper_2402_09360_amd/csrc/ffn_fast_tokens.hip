@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
   float bound2 = smax * sxs[bt] * (7.6f * sumabs + 3.8f * (float)d + 1.0f) * 1.01f * group_factor;
   if constexpr (LRQ) {
     const float xsq = wave_sum(lane < kWPT ? xsqs[bt * kWPT + lane] : 0.0f);
-    bound2 = sqrtf(xsq * (1.0f + (float)p.xn_d * 0x1p-22f)) * 1.0001f * p.umax[0] * 1.0001f;
+    bound2 = sqrtf(xsq * (1.0f + (float)p.xn_d * 0x1p-22f)) * 1.0001f * p.umax[0] * 1.0001f * group_factor;
   }
   FastRegion* fr = p.fr + min(b, B - 1);
   const uint32_t anchor1 = fine_bin(__float_as_uint(bound1)), anchor2 = fine_bin(__float_as_uint(bound2));
@@ -569,7 +569,7 @@ hipError_t launch_fast_score_tokens(const FfnFastArgs& a, const void* x, bool lr
 
 hipError_t launch_fast_gather_tokens(const FfnFastArgs& a, hipStream_t s) {
   FastGatherTokens p{};
-  p.keys = a.lowrank ? static_cast<const void*>(a.keys64) : (a.gs ? a.gkeys : a.keys);
+  p.keys = a.lowrank ? static_cast<const void*>(a.gs ? a.gkeys64 : a.keys64) : (a.gs ? a.gkeys : a.keys);
   p.stride = a.gs ? a.gkey_stride : a.key_stride;
   p.B = a.B; p.N = a.N; p.kprime = a.kprime >> a.gs; p.d = a.d;
   p.fr = reinterpret_cast<FastRegion*>(a.fast_region);

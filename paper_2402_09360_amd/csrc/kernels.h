@@ -381,7 +381,7 @@ struct FfnFastArgs {
   float* sumabs;
   // Low-rank scorer (lowrank, up to four tokens; otherwise the int4 one): keys are fp64 (keys64, [B, key_stride], rows of
   // whole 16-byte vectors), t the bf16 intermediate [B, r], norm_bounds the two row-norm bounds of
-  // hire_lr_prepare.  Plain units only (gs = 0, m1 = 0).
+  // hire_lr_prepare; gs = 3: gkeys64 instead of gkeys, in rows of whole vectors as well.
   bool lowrank;
   const void* lr_a;
   const void* lr_b;
@@ -389,6 +389,7 @@ struct FfnFastArgs {
   const float* norm_bounds;
   uint16_t* t;
   double* keys64;
+  double* gkeys64;
   // int4 low-rank scorer (lrq, up to four tokens): lr_a / lr_b are the packed blobs of Z1 transposed and Z2 with their
   // scales, keys_t B * r + 4 floats for the intermediate; the keys are fp32 (keys); norm_bounds[0] bounds the rows of w1u
   bool lrq;
