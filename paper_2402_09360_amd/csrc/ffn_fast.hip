@@ -449,9 +449,11 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
 // t = bf16(Z1^T x) from k_lr_project.  The anchors are
 // Cauchy-Schwarz bounds: key_j <= |Z2_j| |t| and <u_j, x> <= |u_j| |x| with the layer's largest row norms
 // (bounds[1], bounds[0]: upper bounds, prepared once per layer) and the norms of t and x formed here in fp32 and
-// rounded up by more than their own error.  ROW_LANES lanes share a row as in k_lr_score_b1.
+// rounded up by more than their own error.  Sixteen lanes share a row, four rows a wave: a workgroup's 64 rows take one trip.
+// (From r = 136 on a whole wave per row, in four trips: d = 2048, 16384 units, r = 256, one token 33.4 against 30.5 us per
+// step, four 58.1 against 51.6; d = 256, 1200 units, r = 160, four 35.8 against 28.8.)
 // TT: tokens, 1 or up to 4; kSW / TT waves per token form the norms.
-template <int ROW_LANES, int TT>
+template <int TT>
 __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restrict__ t_in,
                                                        const uint16_t* __restrict__ z2, const uint4* __restrict__ x,
                                                        int B, int N, int d, int r, const float* __restrict__ bounds,
@@ -461,10 +463,10 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
   constexpr int kWPT = kSW / TT;
   __shared__ uint4 ts[TT][128];  // t as raw bf16: r <= 1024
   __shared__ float red_t[kSW], red_x[kSW];
-  constexpr int kRows = kWave / ROW_LANES;  // rows per wave and trip
+  constexpr int kRowLanes = 16, kRows = kWave / kRowLanes;  // lanes per row, rows per wave and trip
   __shared__ double unit_keys[TT][kSW * kRows];
   const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
-  const int sub = lane % ROW_LANES, rw = lane / ROW_LANES;
+  const int sub = lane % kRowLanes, rw = lane / kRowLanes;
   const int cpr = r / 8, n_keys = groups ? N / 8 : N;
   const float group_factor = groups ? 8.001f : 1.0f;
   HIRE_TS(30);
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
     double acc[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) acc[t] = 0.0;
-    for (int c0 = 0; c0 < cpr; c0 += ROW_LANES) {
+    for (int c0 = 0; c0 < cpr; c0 += kRowLanes) {
       const int c = c0 + sub;
       const uint4 wv = row[min(c, cpr - 1)];
       const uint32_t keep = c < cpr ? 0xFFFFFFFFu : 0u;
@@ -539,18 +541,14 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
     }
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
-      double s;
-      if constexpr (ROW_LANES == kWave) {
-        s = wave_sum(acc[t]);
-      } else {  // prefix sum along the 16 lanes of a DPP row: the row's last lane holds its total
-        auto add = [](double a, double b) { return a + b; };
-        s = acc[t];
-        s = add(s, dpp_move<0x111, 0xF>(0.0, s));
-        s = add(s, dpp_move<0x112, 0xF>(0.0, s));
-        s = add(s, dpp_move<0x114, 0xF>(0.0, s));
-        s = add(s, dpp_move<0x118, 0xF>(0.0, s));
-      }
-      if (sub == ROW_LANES - 1 && j < N && t < B) {
+      // prefix sum along the sixteen lanes of a DPP row: the row's last lane holds its total
+      auto add = [](double a, double b) { return a + b; };
+      double s = acc[t];
+      s = add(s, dpp_move<0x111, 0xF>(0.0, s));
+      s = add(s, dpp_move<0x112, 0xF>(0.0, s));
+      s = add(s, dpp_move<0x114, 0xF>(0.0, s));
+      s = add(s, dpp_move<0x118, 0xF>(0.0, s));
+      if (sub == kRowLanes - 1 && j < N && t < B) {
         s = s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
         if (groups) {
           unit_keys[t][w * kRows + rw] = s;
@@ -1253,8 +1251,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
       return launch(kernel, dim3(score_blocks), dim3(kST), 0, s, static_cast<const uint16_t*>(a.t), static_cast<const uint16_t*>(a.lr_b),
                     x4, a.B, a.N, a.d, a.r, a.norm_bounds, gs ? a.gkeys64 : a.keys64, gs ? a.gkey_stride : a.key_stride, fr, gs);
     };
-    if (a.r <= 128) e = several ? go(k_fast_score_lr<16, 4>) : go(k_fast_score_lr<16, 1>);
-    else e = several ? go(k_fast_score_lr<kWave, 4>) : go(k_fast_score_lr<kWave, 1>);
+    e = several ? go(k_fast_score_lr<4>) : go(k_fast_score_lr<1>);
     if (e != hipSuccess) return e;
     if ((e = mark(1)) != hipSuccess) return e;
   } else if (a.lrq) {
