@@ -20,9 +20,14 @@ using namespace hire;
 
 constexpr size_t kAlign = 256;
 constexpr int kSingleWgMaxRow = 32768;  // up to this row length one workgroup per token selects the k' keys
-constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the gather run on the matrix cores
+constexpr int kMfmaMinBatch = 2;  // from this batch size on the scorer and the gather run on the matrix cores; and one token of
+                                  // an FFN with more units than the route for few tokens takes, up to 32768: its kernels are
+                                  // the batch's.  20000 units of d = 800 37.3 us per step, against 56.4 with selections that
+                                  // stream the keys; 24000 of 1440 42.7 against 70.5, fp64 keys 50.4 against 80.8
 // FFN step, rows of at most 32768 units: filter and refine from kFilterMinBatch tokens on.  Up to four tokens are one tile
-// of the fp64 matrix cores (d = 512, 20003 units: 38 / 39 / 41 us for 2 / 3 / 4 tokens against 46 / 47 / 48).  From
+// of the fp64 matrix cores (d = 512, 20003 units: 38 / 39 / 41 us for 2 / 3 / 4 tokens against 46 / 47 / 48); they take it
+// where the union may have more than 16384 units, which the selection of fp64 values streams (ffn_filter; four tokens, 24000
+// units: d = 288 40.4 against 63.9, d = 1440 58.9 against 73.2).  From
 // kFilterValuesMinBatch on values of the filter stage may be handed out (hire_ffn_step says which).
 constexpr int kFilterMinBatch = 5;
 constexpr int kFilterValuesMinBatch = 16;
@@ -89,6 +94,9 @@ struct StepBuffers {
   size_t bytes;
 };
 
+constexpr int kKeysInRegisters = 16384;  // rows that the route for few tokens and the selection of fp64 values hold
+bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilterMinBatch || s.cap_u > kKeysInRegisters); }
+
 // Softmax step, filter and refine: for which unions (of at most cap_u classes) and k the refining selection is cheaper than
 // ranking fp64 logits.  It finds its mark from the filter stage's maxima, up to four per workgroup; with few more than k of
 // them much of the union lies above the mark, with fewer than k all of it, and what does not fit the slots goes through one
@@ -137,7 +145,7 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
                                                                  general_fallbacks_offset(1))
                                   : nullptr;
   const bool int4_like = scorer_kind == HIRE_SCORER_INT4 || scorer_kind == HIRE_SCORER_LRQ;
-  s.by_unit = ffn && B >= kMfmaMinBatch && gs == 0 && batch_select_supported(N, k);
+  s.by_unit = ffn && (B >= kMfmaMinBatch || N > kKeysInRegisters) && gs == 0 && batch_select_supported(N, k);
   s.key_stride = s.by_unit || (fast && gs == 0) ? (N + 3) / 4 * 4 : N;  // whole 16-byte vectors
   if (int4_like && N > kSingleWgMaxRow && gs == 0) s.hist.multi_body = c.take<char>(multi_body_bytes_host(B));
   if (int4_like) {
@@ -162,9 +170,9 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
   const bool sm_filter = !ffn && gs == 0 && softmax_filter(B, s.cap_u, k, kprime);
-  s.all_rows = s.by_unit && B >= kFilterMinBatch && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
-               (int4_like || N <= kKeysSelectMaxF64) && filter_all_rows(B, d, N, kprime);
-  if (s.by_unit && B >= kFilterMinBatch) {
+  s.all_rows = ffn_filter(s, B) && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
+               (int4_like || N <= kSelectFilterMaxF64) && filter_all_rows(B, d, N, kprime);
+  if (ffn_filter(s, B)) {
     s.xnorm = c.take<float>(HIRE_MAX_BATCH);
     s.wnorm_tiles = c.take<float>(filter_tiles(N));
     s.hf_stride = s.key_stride;  // rows start at multiples of 16 bytes
@@ -278,6 +286,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   // (int4 low-rank scorer) the int4 copy of Z2 and the r-vector t
   const bool lrq = scorer_kind == HIRE_SCORER_LRQ;
   const bool int4_like = scorer_kind == HIRE_SCORER_INT4 || lrq;
+  const bool batch = B >= kMfmaMinBatch || s.by_unit;
   const void* q4 = lrq ? sc.lr_b : sc.q4;
   const float* q4_scale = lrq ? sc.lr_b_scale : sc.q4_scale;
   const uint16_t* tok = lrq ? s.t : xb;
@@ -310,10 +319,10 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     // any int4 matrix (no phi), then rounded to the bf16 activation the second product quantises
     const HistRefs header_only{s.hist.header, nullptr};
     const uint32_t* qa = static_cast<const uint32_t*>(lr_a);
-    if (B == 1 && scorer_int4_fused_supported(d)) {
+    if (!batch && scorer_int4_fused_supported(d)) {
       HIRE_TRY(launch_scorer_int4_fused(qa, sc.lr_a_scale, xb, false, r, d, 0, s.keys_t, nullptr, header_only, s.bitmap,
                                         s.zero_words, s.sig, st));
-    } else if (B >= kMfmaMinBatch) {
+    } else if (batch) {
       ScorerTokens tk{s.xq, nullptr, false, nullptr, s.bitmap, s.zero_words, s.hist.header, s.sig};
       if (scorer_mfma_quantises(B, r, d, false)) tk.x = xb;
       else HIRE_TRY(launch_quantize_tokens(xb, false, B, d, s.xq, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig, st));
@@ -323,13 +332,13 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_TRY(launch_scorer_int4(qa, sc.lr_a_scale, s.xq, B, r, d, 0, s.keys_t, nullptr, header_only, st));
     }
     // whatever quantises the intermediate rounds it as well
-    t_is_f32 = B >= kMfmaMinBatch || (scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r));
+    t_is_f32 = batch || (scorer_int4_fused_supported(r) && scorer_int4_fused_takes_f32(r));
     if (!t_is_f32) HIRE_TRY(launch_f32_to_bf16(s.keys_t, B * r, s.t, st));
   }
   if (int4_like) {
     // the scorer quantises the token itself
-    const bool fused = B == 1 && scorer_int4_fused_supported(sd);
-    const bool fused_batch = B >= kMfmaMinBatch && scorer_mfma_quantises(B, N, sd, t_is_f32);
+    const bool fused = !batch && scorer_int4_fused_supported(sd);
+    const bool fused_batch = batch && scorer_mfma_quantises(B, N, sd, t_is_f32);
     if (!fused && !fused_batch)
       HIRE_TRY(launch_quantize_tokens(t_is_f32 ? static_cast<const void*>(s.keys_t) : tok, t_is_f32, B, sd, s.xq, s.sumabs,
                                       s.bitmap, s.zero_words, s.hist.header, s.sig, st));
@@ -342,7 +351,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
                                         static_cast<float*>(s.keys), scorer_acc, s.hist, s.bitmap, s.zero_words, s.sig,
                                         st));
       slots = scorer_int4_fused_maxima(N, sd);
-    } else if (B >= kMfmaMinBatch) {
+    } else if (batch) {
       ScorerTokens tk{s.xq, nullptr, t_is_f32, s.sumabs, s.bitmap, s.zero_words, s.hist.header, s.sig};
       if (fused_batch) tk.x = t_is_f32 ? static_cast<const void*>(s.keys_t) : static_cast<const void*>(tok);
       HIRE_TRY(launch_scorer_int4_mfma(static_cast<const uint32_t*>(q4), q4_scale, tk, B, N, sd, relu,
@@ -394,7 +403,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     HIRE_TRY(launch_lr_project(static_cast<const uint16_t*>(lr_a), xb, B, d, r, s.t, s.bitmap, s.zero_words, s.hist.header,
                                s.sig, st));
     HIRE_STAGE(1, st);
-    if (B >= kMfmaMinBatch)
+    if (batch)
       HIRE_TRY(launch_lr_score_mfma(static_cast<const uint16_t*>(lr_b), s.t, B, N, r, relu, static_cast<double*>(s.keys),
                                     s.key_stride, st));
     else
@@ -410,7 +419,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
     if (gs > 0 && !in_select)
       HIRE_TRY(launch_group_sums_f64(static_cast<const double*>(s.keys), B, N, Ns, nullptr, Ns, gs,
                                      static_cast<double*>(s.gkeys), Ns, st));
-    if (s.by_unit && N <= kKeysSelectMaxF64)
+    if (s.by_unit)
       HIRE_TRY(launch_keys_select(ks, B, st));
     else
       HIRE_TRY(launch_select_f64(sp, B, st));
@@ -424,7 +433,7 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   else if (filter)
     HIRE_TRY(launch_filter_ranks(static_cast<const uint16_t*>(W), xb, B, d, cand, s.counters, s.cap_u, s.hf, s.hf_stride,
                                  s.hist, in_gather ? &un : nullptr, N, s.xnorm, s.wnorm_tiles, s.maxima, st));
-  else if (B >= kMfmaMinBatch)
+  else if (batch)
     HIRE_TRY(launch_gather_dot_mfma(static_cast<const uint16_t*>(W), xb, B, d, cand, 0, s.counters, s.cap_u, relu, s.h,
                                     (long long)s.cap_u << gs, s.hist, in_gather ? &un : nullptr, gs, st));
   else
@@ -643,7 +652,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
   // within a proven distance of the activations; the selection recomputes in fp64 those around every token's k-th
   // largest.  Whatever lies outside that band is on the same side of the threshold in fp64 as its stored value, so
   // the selected sets are those of the fp64 activations.
-  const bool filter = s.by_unit && B >= kFilterMinBatch && !g_force_exact_stage;
+  const bool filter = ffn_filter(s, B) && !g_force_exact_stage;
   rc = run_front(s, scorer_of(L), L->w1u, x, B, d, N, kprime, 1, cand_idx, n_cand, scorer_acc, st, 0, filter);
   if (rc != HIRE_OK) return rc;
   HIRE_STAGE(5, st);

@@ -382,7 +382,8 @@ bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k
 
 hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s) {
   if (!keys_select_ok(p)) return hipErrorInvalidValue;
-  if (p.f64) return launch(k_keys_select<uint64_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
+  if (p.f64)
+    return launch(p.N <= 16384 ? k_keys_select<uint64_t, 8> : k_keys_select<uint64_t, 16>, dim3(B), dim3(kSelThreads), 0, s, p);
   return launch(p.N <= 16384 ? k_keys_select<uint32_t, 4> : k_keys_select<uint32_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
 }
 

@@ -786,7 +786,7 @@ hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int 
 
 hipError_t launch_select_filter(const KeysSelect& ks, int B, const uint16_t* W, const uint16_t* x, int d, float* h,
                                 long long stride_h, float* xnorm, float* wnorm_tiles, hipStream_t s) {
-  if (B < 1 || B > 64 || d % 8 != 0 || !keys_select_ok(ks)) return hipErrorInvalidValue;
+  if (B < 1 || B > 64 || d % 8 != 0 || !keys_select_ok(ks) || (ks.f64 && ks.N > kSelectFilterMaxF64)) return hipErrorInvalidValue;
   const FilterUnits p{W, x, B, d, nullptr, nullptr, ks.N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B)};
   static std::atomic<size_t> raised_to[9] = {};
   auto go = [&](auto kernel, int tt, std::atomic<size_t>& raised) {

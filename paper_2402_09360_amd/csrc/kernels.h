@@ -212,7 +212,7 @@ bool batch_select_supported(int N, int k);
 // The k' largest keys of every row of non-negative keys -> bits of the union bitmap (which must be clear).
 struct KeysSelect {
   const void* keys;    // [B, stride] fp32, or
-  bool f64;            // fp64 (rows of at most kKeysSelectMaxF64); rows at multiples of 16 bytes
+  bool f64;            // fp64; rows at multiples of 16 bytes
   long long stride;
   int N, kprime;
   const float* sumabs;  // fp32: sumabs[b], *smax bound token b's keys (the sums of the absolute codes, the trailer of the
@@ -220,7 +220,7 @@ struct KeysSelect {
   uint32_t* bitmap;
   uint32_t* window_misses;
 };
-constexpr int kKeysSelectMaxF64 = 16384;
+constexpr int kSelectFilterMaxF64 = 16384;  // rows of fp64 keys that launch_select_filter takes
 hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s);
 // The k largest activations relu(<W[j, :], x_b>) of every token among the bitmap's units, ties to the lower unit, from
 // the filter stage's values in unit order (launch_filter_units).

@@ -55,7 +55,7 @@ struct KeysSelectShared {
 };
 
 inline bool keys_select_ok(const KeysSelect& p) {
-  return p.N <= (p.f64 ? kKeysSelectMaxF64 : 32768) && p.stride % (p.f64 ? 2 : 4) == 0 &&
+  return p.N <= 32768 && p.stride % (p.f64 ? 2 : 4) == 0 &&
          reinterpret_cast<uintptr_t>(p.keys) % 16 == 0;
 }
 
