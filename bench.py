@@ -85,10 +85,10 @@ _STAGE_KERNELS = {
     "scorer": ("k_fast_score", "k_scorer_int4", "k_lr_score", "k_lr_project"),
     "quantise_x": ("k_quantize_tokens",),
     "select_kprime": ("k_select<float", "k_select_nonneg<float", "k_keys_select", "k_count_f32", "k_mark_f32", "k_group_sums",
-                      "k_max_gather"),
+                      "k_max_gather", "k_group_select<unsigned int"),
     "union": ("k_resolve_compact", "k_bitmap_compact", "k_union_compact", "k_max_resolve"),
     "gather_dot": ("k_gather_dot", "k_filter_units", "k_filter_ranks", "k_sm1_gather", "k_sm1_final"),
-    "select_k": ("k_select<double", "k_select_nonneg<double", "k_refine", "k_exact_values"),
+    "select_k": ("k_select<double", "k_select_nonneg<double", "k_refine", "k_exact_values", "k_group_select<unsigned long"),
     "select_k_softmax": ("k_select<double", "k_softmax_parts", "k_softmax_refine"),
     "second_layer": ("k_w2_list",),
     "shard_step": ("k_ffn_shard",),

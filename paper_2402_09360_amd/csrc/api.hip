@@ -294,10 +294,10 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
   // what is ranked: units, or groups of 2^gs units by their summed absolute keys.  Groups of eight are summed by
   // the selection as it loads the keys; other sizes by a kernel of their own.
   const int Ns = N >> gs;
-  const bool in_select = gs == 3 && Ns <= kSelectGroup8Max;
+  const bool in_select = gs == 3 && Ns <= kGroupSelectMax;
+  GroupSelect gsel{s.keys, !int4_like, N, Ns, nullptr, kprime >> gs, s.bitmap, nullptr, nullptr, nullptr, nullptr, s.window_misses};
   SelectParams sp{};
-  sp.group8 = in_select ? 1 : 0;
-  sp.stride = gs == 0 ? s.key_stride : (in_select ? N : Ns);
+  sp.stride = gs == 0 ? s.key_stride : Ns;
   sp.n = Ns;
   sp.n_cap = Ns;
   sp.k = kprime >> gs;
@@ -395,7 +395,8 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
       HIRE_TRY(launch_keys_select(ks, B, st));
       HIRE_STAGE(3, st);
     } else {
-      HIRE_TRY(launch_select_f32(sp, B, st));
+      if (in_select) HIRE_TRY(launch_group_select(gsel, B, st));
+      else HIRE_TRY(launch_select_f32(sp, B, st));
       HIRE_STAGE(3, st);
       if (!in_gather) HIRE_TRY(launch_bitmap_compact(s.bitmap, s.words, cand, s.counters, n_cand, nullptr, 0, st));
     }
@@ -421,6 +422,8 @@ int run_front(const StepBuffers& s, const ScorerRefs& sc, const void* W, const v
                                      static_cast<double*>(s.gkeys), Ns, st));
     if (s.by_unit)
       HIRE_TRY(launch_keys_select(ks, B, st));
+    else if (in_select)
+      HIRE_TRY(launch_group_select(gsel, B, st));
     else
       HIRE_TRY(launch_select_f64(sp, B, st));
     HIRE_STAGE(3, st);
@@ -837,34 +840,38 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
 
   // exact group activations and the top k/g groups of every token
   // (groups of eight: summed by the selection as it loads h; other sizes by a kernel of their own)
-  const bool in_select = gs == 3 && s.cap_u <= kSelectGroup8Max;
-  const double* ranked = s.h;
-  if (gs > 0 && !in_select) {
-    HIRE_TRY(launch_group_sums_f64(s.h, B, (long long)s.cap_u << gs, 0, s.counters, s.cap_u, gs, s.hg, s.cap_u, st));
-    ranked = s.hg;
-  }
-  SelectParams sp{};
-  sp.vals = ranked;
-  sp.group8 = in_select ? 1 : 0;
-  sp.stride = in_select ? ((long long)s.cap_u << gs) : s.cap_u;
-  sp.n_dev = s.counters;
-  sp.n_cap = s.cap_u;
-  sp.k = k >> gs;
-  sp.idx_out = topk_group;
-  sp.map = cand;
-  sp.list_out = s.list;
-  if (gs > 0) {
-    sp.pos_out = s.pos;
-    sp.gs = gs;
-    sp.unit_h = s.h;
-    sp.unit_h_stride = (long long)s.cap_u << gs;
-    sp.unit_val_out = topk_val;
+  if (gs == 3 && s.cap_u <= kGroupSelectMax) {
+    const GroupSelect gsel{s.h, true, (long long)s.cap_u << gs, s.cap_u, s.counters, k >> gs, nullptr, cand, topk_group, s.list,
+                           topk_val, s.window_misses};
+    HIRE_TRY(launch_group_select(gsel, B, st));
   } else {
-    sp.val_out = topk_val;
+    const double* ranked = s.h;
+    if (gs > 0) {
+      HIRE_TRY(launch_group_sums_f64(s.h, B, (long long)s.cap_u << gs, 0, s.counters, s.cap_u, gs, s.hg, s.cap_u, st));
+      ranked = s.hg;
+    }
+    SelectParams sp{};
+    sp.vals = ranked;
+    sp.stride = s.cap_u;
+    sp.n_dev = s.counters;
+    sp.n_cap = s.cap_u;
+    sp.k = k >> gs;
+    sp.idx_out = topk_group;
+    sp.map = cand;
+    sp.list_out = s.list;
+    if (gs > 0) {
+      sp.pos_out = s.pos;
+      sp.gs = gs;
+      sp.unit_h = s.h;
+      sp.unit_h_stride = (long long)s.cap_u << gs;
+      sp.unit_val_out = topk_val;
+    } else {
+      sp.val_out = topk_val;
+    }
+    sp.nonneg = 1;  // activations after the ReLU, or sums of their absolute values
+    sp.window_misses = s.window_misses;
+    HIRE_TRY(launch_select_f64(sp, B, st));
   }
-  sp.nonneg = 1;  // activations after the ReLU, or sums of their absolute values
-  sp.window_misses = s.window_misses;
-  HIRE_TRY(launch_select_f64(sp, B, st));
   HIRE_STAGE(6, st);
 
   // second layer over the units of each token's groups, and over the dense units

@@ -378,6 +378,128 @@ __global__ __launch_bounds__(kEvThreads) void k_exact_values(uint2* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------------
+// Both selections of a group-sparse step (groups of eight, eq. (6)), one workgroup per token: the k groups with the largest
+// sums of eight absolute values, added in unit order in the values' own type.  A wave sums the groups of its own part of the
+// row: whole vectors side by side, the lanes that share a group hand the sum on.  The sums stay in LDS for rows that need the
+// narrowing.  Bound by the same chain as k_keys_select, behind a barrier more for the largest sum, the window's anchor.
+// d = 512, 16000 units, 16 tokens 48.2 -> 37.8 us per step against the general selection, which reads the eight values a lane
+// at a time; 64 tokens 96.9 -> 74.9; d = 1024, 6000 units, 16 tokens 42.8 -> 33.9; fp64 keys, 16000 units, 64 tokens 115 -> 81.
+template <typename K, int LOADS>
+struct GroupShared {
+  using Keys = KeyRegs<K, LOADS, kSelThreads, false, true>;
+  KeysSelectShared<K> s;
+  __align__(16) K sums[Keys::CAPACITY + Keys::SPAN * LOADS];  // bit patterns, by group
+};
+
+template <typename K, int LOADS>
+__global__ __launch_bounds__(kSelThreads) void k_group_select(GroupSelect p) {
+  using Keys = typename GroupShared<K, LOADS>::Keys;
+  constexpr int PER = Keys::PER, VPG = 8 * (int)sizeof(K) / 16, kVecs = LOADS * Keys::SPAN * VPG / kWave;  // vectors per group, lane
+  extern __shared__ uint4 group_lds[];
+  auto& G = *reinterpret_cast<GroupShared<K, LOADS>*>(group_lds);
+  auto& S = G.s;
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  Keys kr;
+  kr.len = Keys::share(p.n_cap);
+  kr.base = w * kr.len;
+  const uint4* row = reinterpret_cast<const uint4*>(static_cast<const K*>(p.vals) + (size_t)b * p.stride);
+  uint4 raw[kVecs];
+#pragma unroll
+  for (int i = 0; i < kVecs; ++i)
+    if (i * kWave < kr.len * VPG) raw[i] = row[min(kr.base * VPG + i * kWave + lane, p.n_cap * VPG - 1)];  // uniform
+  const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n_cap;
+  {
+    uint4* z = reinterpret_cast<uint4*>(S.win) + 2 * tid;
+    z[0] = z[1] = make_uint4(0, 0, 0, 0);
+  }
+  if (tid == 0) S.sh.list_n = S.off_window = 0;
+#pragma unroll
+  for (int i = 0; i < kVecs; ++i)
+    if (i * kWave < kr.len * VPG) {
+      const int at = i * kWave + lane;  // vector of the wave's part
+      K sum;
+      if constexpr (sizeof(K) == 4) {
+        const float x = fabsf(__uint_as_float(raw[i].x)), y = fabsf(__uint_as_float(raw[i].y)),
+                    z = fabsf(__uint_as_float(raw[i].z)), u = fabsf(__uint_as_float(raw[i].w));
+        const float before = dpp_move<0x111, 0xF>(0.0f, x + y + z + u);
+        sum = __float_as_uint(before + x + y + z + u);
+      } else {
+        const double x = fabs(__hiloint2double((int)raw[i].y, (int)raw[i].x)), y = fabs(__hiloint2double((int)raw[i].w, (int)raw[i].z));
+        double t = x + y;
+#pragma unroll
+        for (int q = 1; q < VPG; ++q) {
+          const double before = dpp_move<0x111, 0xF>(0.0, t);
+          t = lane % VPG == q ? before + x + y : t;
+        }
+        sum = (K)__double_as_longlong(t);
+      }
+      if (lane % VPG == VPG - 1 && at < kr.len * VPG) G.sums[kr.base + at / VPG] = sum;
+    }
+  __builtin_amdgcn_wave_barrier();  // a wave reads what it has written itself
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  K top = 0;
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+    for (int q = 0; q < PER; ++q) kr.r[e][q] = G.sums[kr.index(e, q)];
+  kr.mask_beyond(n);
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+    for (int q = 0; q < PER; ++q) top = kr.r[e][q] > top ? kr.r[e][q] : top;
+  top = wave_max(top);
+  if (lane == 0) S.wave_top[w] = top;
+  __syncthreads();
+  const uint32_t anchor = fine_bin((K)wave_max((K)(lane < kSelWaves ? S.wave_top[lane] : 0)));
+  const uint32_t take = keys_take<K>(kr, G.sums, p.k, anchor, S, p.window_misses);
+  if (p.bitmap != nullptr) {
+    add_bits(kr, take, p.bitmap);
+    return;
+  }
+  // places of the selected groups in order; then their units, eight neighbouring threads a group
+  __syncthreads();  // the narrowing's readers of wave_cnt are done
+  const int mine = wave_sum(__popc(take));
+  if (lane == 0) S.wave_cnt[w] = mine;
+  __syncthreads();
+  const int incl = wave_scan_incl(lane < kSelWaves ? S.wave_cnt[lane] : 0);
+  int at = w > 0 ? __builtin_amdgcn_readlane(incl, w - 1) : 0;
+  int* place = reinterpret_cast<int*>(S.win);  // (k <= kWin)
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e) {
+    const uint32_t bits = take >> (e * PER) & ((1u << PER) - 1u);
+    const int c = __popc(bits), upto = wave_scan_incl(c);
+    int o = at + upto - c;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if ((bits >> q & 1u) != 0u) place[o++] = kr.index(e, q);
+    at += __builtin_amdgcn_readlane(upto, kWave - 1);
+  }
+  __syncthreads();
+  const int units = 8 * p.k;
+  const double* h = static_cast<const double*>(p.vals) + (size_t)b * p.stride;
+  for (int t0 = tid; t0 < units; t0 += 4 * kSelThreads) {  // four position -> value chains in flight
+    int group[4];
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = min(t0 + u * kSelThreads, units - 1), pos = place[t / 8];
+      group[u] = p.map[pos];
+      v[u] = h[(size_t)pos * 8 + t % 8];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + u * kSelThreads;
+      if (t < units) {
+        const size_t o = (size_t)b * units + t;
+        p.list_out[o] = make_uint2((uint32_t)(group[u] * 8 + t % 8), __float_as_uint((float)v[u]));
+        if (p.val_out) p.val_out[o] = (float)v[u];
+        if (p.idx_out && t % 8 == 0) p.idx_out[(size_t)b * p.k + t / 8] = group[u];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
 bool batch_select_supported(int N, int k) { return N >= 1 && N <= 2 * 16384 && k <= kWin / 2; }
 
 hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s) {
@@ -385,6 +507,21 @@ hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s) {
   if (p.f64)
     return launch(p.N <= 16384 ? k_keys_select<uint64_t, 8> : k_keys_select<uint64_t, 16>, dim3(B), dim3(kSelThreads), 0, s, p);
   return launch(p.N <= 16384 ? k_keys_select<uint32_t, 4> : k_keys_select<uint32_t, 8>, dim3(B), dim3(kSelThreads), 0, s, p);
+}
+
+hipError_t launch_group_select(const GroupSelect& p, int B, hipStream_t s) {
+  if (p.n_cap < 1 || p.n_cap > kGroupSelectMax || p.k < 1 || p.k > p.n_cap || reinterpret_cast<uintptr_t>(p.vals) % 16 != 0 ||
+      p.stride % 8 != 0 || (p.bitmap == nullptr && (!p.f64 || !p.map || !p.list_out)))
+    return hipErrorInvalidValue;
+  static std::atomic<size_t> raised_to[3] = {};
+  auto go = [&](auto kernel, size_t lds, std::atomic<size_t>& raised) {
+    if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
+      return e;
+    return launch(kernel, dim3(B), dim3(kSelThreads), lds, s, p);
+  };
+  if (!p.f64) return go(k_group_select<uint32_t, 1>, sizeof(GroupShared<uint32_t, 1>), raised_to[0]);
+  if (p.n_cap <= kGroupSelectMax / 2) return go(k_group_select<uint64_t, 1>, sizeof(GroupShared<uint64_t, 1>), raised_to[1]);
+  return go(k_group_select<uint64_t, 2>, sizeof(GroupShared<uint64_t, 2>), raised_to[2]);
 }
 
 hipError_t launch_exact_values(uint2* lists, float* val_out, const uint16_t* W, const uint16_t* x, int B, int k, int d,

@@ -153,11 +153,7 @@ struct SelectParams {
   const double* unit_h;
   long long unit_h_stride;
   float* unit_val_out;
-  int group8;               // != 0 (rows of at most kSelectGroup8Max entries): entry i is the sum of |vals[8 i + l]|,
-                            // l < 8, added in index order in the values'
-                            // type (group activations of eq. (6)); stride counts values, n / n_dev / n_cap entries
 };
-constexpr int kSelectGroup8Max = 4096;
 hipError_t launch_select_f32(const SelectParams& p, int B, hipStream_t s);
 // The k largest of every row of scores [B, N] in ascending index order, selected by many workgroups per row
 // through key histograms (for long rows).  general_header: general_header_bytes() cleared by the workspace
@@ -222,6 +218,24 @@ struct KeysSelect {
 };
 constexpr int kSelectFilterMaxF64 = 16384;  // rows of fp64 keys that launch_select_filter takes
 hipError_t launch_keys_select(const KeysSelect& p, int B, hipStream_t s);
+// The k groups of eight with the largest sums of |vals[8 i + l]| (added in index order), ties to the lower group: bits of a
+// bitmap; or, of fp64 activations by candidate, the selected groups and their units.
+constexpr int kGroupSelectMax = 4096;  // groups
+struct GroupSelect {
+  const void* vals;      // [B, stride] fp32, or
+  bool f64;              // fp64; rows at multiples of 16 bytes, stride a multiple of 8
+  long long stride;
+  int n_cap;             // groups,
+  const int32_t* n_dev;  // optional: the first *n_dev of them
+  int k;
+  uint32_t* bitmap;      // the selected groups' bits are added to it; or nullptr:
+  const int32_t* map;    // group of position i
+  int32_t* idx_out;      // optional [B, k]: groups, in the order of their positions
+  uint2* list_out;       // [B, 8 k] (unit, value) for launch_w2_list
+  float* val_out;        // optional [B, 8 k]
+  uint32_t* window_misses;
+};
+hipError_t launch_group_select(const GroupSelect& p, int B, hipStream_t s);
 // The k largest activations relu(<W[j, :], x_b>) of every token among the bitmap's units, ties to the lower unit, from
 // the filter stage's values in unit order (launch_filter_units).
 constexpr int kRefineTokenMax = 8192;  // longest token staged in LDS

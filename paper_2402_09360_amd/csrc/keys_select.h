@@ -59,6 +59,67 @@ inline bool keys_select_ok(const KeysSelect& p) {
          reinterpret_cast<uintptr_t>(p.keys) % 16 == 0;
 }
 
+// The `want` largest of the registers' keys, ties to the lower index: bit e * PER + q.  vals: the same keys by index, in memory.
+// The window is clear, and so are sh.list_n and off_window; all of it behind a barrier.
+template <typename K, typename Keys>
+__device__ __forceinline__ uint32_t keys_take(const Keys& kr, const void* vals, int want, uint32_t anchor,
+                                              KeysSelectShared<K>& S, uint32_t* window_misses) {
+  constexpr int PER = Keys::PER, LOADS = Keys::kLoads;
+  const int lane = lane_id();
+  auto& sh = S.sh;
+  auto& list = S.list;
+  HIRE_TS(11);
+  uint32_t bin;
+  int above;
+  bool beyond;
+  bool known = window_bin(kr, anchor, want, S.win, sh, &bin, &above, &beyond);
+  if (beyond) S.off_window = 1;  // (row scales that do not belong to the codes)
+  HIRE_TS(12);
+  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
+  if (known) {
+    const BinMasks<K> bm = bin_masks<K>(kr, bin_floor<K>(bin), bin_floor<K>(bin + 1u));
+    list_inside<K>(kr, bm.inside, &sh.list_n, list);
+    __syncthreads();
+    HIRE_TS(13);
+    const int m = sh.list_n;
+    known = m <= kFastAmbCap && S.off_window == 0;  // uniform
+    if (known)
+      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : (K)0, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
+                                      want - above);
+    HIRE_TS(14);
+  }
+  if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
+    WinRegs<kSelThreads> none{};
+    const Selection<K> sel =
+        fast_select<60>(kr, vals, want, none, 0u, false, sh, S.wave_cnt, window_misses, 0, want, true);
+    take = 0u;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
+  }
+  return __brev(take) >> (32 - LOADS * PER);
+}
+
+// Adds the taken keys' bits to a bitmap: a word covers 32 consecutive indices, the keys of 32 / PER neighbouring lanes of one
+// load.  Those lanes fold their bits together and one of them adds the word.
+template <typename Keys>
+__device__ __forceinline__ void add_bits(const Keys& kr, uint32_t take, uint32_t* bitmap) {
+  constexpr int PER = Keys::PER, LOADS = Keys::kLoads, kLanes = 32 / PER;
+  static_assert(kLanes == 8 || kLanes == 16, "lanes per word");
+  const int lane = lane_id();
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e) {
+    uint32_t bits = (take >> (e * PER) & ((1u << PER) - 1u)) << (lane % kLanes * PER);
+    bits |= dpp_move<0xB1, 0xF>(0u, bits);   // lanes 1, 0, 3, 2 of a quad
+    bits |= dpp_move<0x4E, 0xF>(0u, bits);   // lanes 2, 3, 0, 1
+    bits |= dpp_move<0x141, 0xF>(0u, bits);  // eight lanes mirrored: the other quad
+    if constexpr (kLanes == 16) bits |= dpp_move<0x140, 0xF>(0u, bits);  // sixteen: the other eight
+    if (lane % kLanes == 0 && bits != 0u) atomicOr(&bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / kLanes], bits);
+  }
+}
+
 // Token b, by the whole workgroup.
 template <typename K, int LOADS>
 __device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, KeysSelectShared<K>& S) {
@@ -67,7 +128,6 @@ __device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, Ke
   const int tid = (int)threadIdx.x, lane = lane_id(), N = p.N, kprime = p.kprime;
   auto& sh = S.sh;
   auto& win = S.win;
-  auto& list = S.list;
   HIRE_TS(10);
   const K* row = static_cast<const K*>(p.keys) + (size_t)b * p.stride;
   Keys kr;
@@ -96,51 +156,7 @@ __device__ __forceinline__ void keys_select_token(const KeysSelect& p, int b, Ke
     __syncthreads();
     anchor = fine_bin((K)wave_max((K)(lane < kSelWaves ? S.wave_top[lane] : 0)));
   }
-  HIRE_TS(11);
-  uint32_t bin;
-  int above;
-  bool beyond;
-  bool known = window_bin(kr, anchor, kprime, win, sh, &bin, &above, &beyond);
-  if (beyond) S.off_window = 1;  // (row scales that do not belong to the codes)
-  HIRE_TS(12);
-  uint32_t take = 0u;  // this lane's selected keys, as in BinMasks
-  if (known) {
-    const BinMasks<K> bm = bin_masks<K>(kr, bin_floor<K>(bin), bin_floor<K>(bin + 1u));
-    list_inside<K>(kr, bm.inside, &sh.list_n, list);
-    __syncthreads();
-    HIRE_TS(13);
-    const int m = sh.list_n;
-    known = m <= kFastAmbCap && S.off_window == 0;  // uniform
-    if (known)
-      take = bm.above | taken_of_list(kr, lane < m ? list.key[lane] : (K)0, lane < m ? list.idx[lane] : 0x7FFFFFFF, m,
-                                      kprime - above);
-    HIRE_TS(14);
-  }
-  if (!known) {  // threshold among the zeros or below the window, crowded bin: range narrowing
-    WinRegs<kSelThreads> none{};
-    const Selection<K> sel =
-        fast_select<60>(kr, row, kprime, none, 0u, false, sh, S.wave_cnt, p.window_misses, 0, kprime, true);
-    take = 0u;
-#pragma unroll
-    for (int e = 0; e < LOADS; ++e)
-#pragma unroll
-      for (int q = 0; q < PER; ++q)
-        take = take + take + (kr.valid(e, q) && cut_takes(sel.cut, kr.r[e][q], kr.index(e, q)) ? 1u : 0u);
-  }
-  // A bitmap word covers 32 consecutive indices: the keys of 32 / PER neighbouring lanes of one load.  Those lanes
-  // fold their bits together and one of them adds the word to the union.
-  constexpr int kLanes = 32 / PER;
-  static_assert(kLanes == 8 || kLanes == 16, "lanes per word");
-  take = __brev(take) >> (32 - LOADS * PER);  // bit e * PER + q
-#pragma unroll
-  for (int e = 0; e < LOADS; ++e) {
-    uint32_t bits = (take >> (e * PER) & ((1u << PER) - 1u)) << (lane % kLanes * PER);
-    bits |= dpp_move<0xB1, 0xF>(0u, bits);   // lanes 1, 0, 3, 2 of a quad
-    bits |= dpp_move<0x4E, 0xF>(0u, bits);   // lanes 2, 3, 0, 1
-    bits |= dpp_move<0x141, 0xF>(0u, bits);  // eight lanes mirrored: the other quad
-    if constexpr (kLanes == 16) bits |= dpp_move<0x140, 0xF>(0u, bits);  // sixteen: the other eight
-    if (lane % kLanes == 0 && bits != 0u) atomicOr(&p.bitmap[(kr.base + e * Keys::SPAN) / 32 + lane / kLanes], bits);
-  }
+  add_bits(kr, keys_take<K>(kr, row, kprime, anchor, S, p.window_misses), p.bitmap);
   HIRE_TS(15);
 }
 

@@ -31,39 +31,11 @@ struct KeyOf<double> {
   using K = uint64_t;
 };
 
-// Group activation of eq. (6) for groups of eight: sum of the absolute values of the eight entries at src (32-
-// or 64-byte aligned), added in index order in their own type; vector loads, nothing that waits in between.
-__device__ __forceinline__ float group8_abs_sum(const float* __restrict__ src) {
-  const float4 a = reinterpret_cast<const float4*>(src)[0], b = reinterpret_cast<const float4*>(src)[1];
-  float s = fabsf(a.x);
-  s += fabsf(a.y);
-  s += fabsf(a.z);
-  s += fabsf(a.w);
-  s += fabsf(b.x);
-  s += fabsf(b.y);
-  s += fabsf(b.z);
-  s += fabsf(b.w);
-  return s;
-}
-__device__ __forceinline__ double group8_abs_sum(const double* __restrict__ src) {
-  const double2* p = reinterpret_cast<const double2*>(src);
-  const double2 a = p[0], b = p[1], c = p[2], d = p[3];
-  double s = fabs(a.x);
-  s += fabs(a.y);
-  s += fabs(b.x);
-  s += fabs(b.y);
-  s += fabs(c.x);
-  s += fabs(c.y);
-  s += fabs(d.x);
-  s += fabs(d.y);
-  return s;
-}
-
 // Selection of row b by one whole workgroup.  dyn: rank order only, K keys[k] then int pos[k], int rank[k].
 // win: kHistWindow words of LDS for the window histogram, or nullptr to go straight to range narrowing.
 // ITEMS: keys a thread keeps in registers (rows of at most ITEMS * 1024 entries), or 0 to stream the row from
 // memory on every pass.
-template <typename V, int ITEMS, bool G8 = false>
+template <typename V, int ITEMS>
 __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShared& sh, unsigned long long* dyn,
                                            uint32_t* win) {
   using K = typename KeyOf<V>::K;
@@ -85,13 +57,7 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
     if (p.relu) v = v > (V)0 ? v : (V)0;
     return order_key(v);
   };
-  // entry i of the row: the value itself, or (G8, for SelectParams::group8) the group activation of the eight values
-  // 8 i .. 8 i + 7.  A template parameter: the vector loads of the group form cost registers that the kernels with
-  // 16 entries per thread do not have.
-  auto load_key = [&](int i) -> K {
-    if constexpr (G8) return to_key(group8_abs_sum(vals + (size_t)i * 8));
-    else return to_key(vals[i]);
-  };
+  auto load_key = [&](int i) -> K { return to_key(vals[i]); };
 
   HIRE_TS(0);
   const int n_raw = p.n_dev ? *p.n_dev : p.n;
@@ -106,20 +72,11 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
   int mapped[kItems];
   if (CACHED) {
     V raw[kItems];
-    if constexpr (!G8) {
 #pragma unroll
-      for (int e = 0; e < kItems; ++e) {  // clamped and unconditional, so that the loads do not wait for one another
-        const int i = min(base + e * kWave + lane, nload - 1);
-        raw[e] = vals[i];
-        mapped[e] = (map && !p.rank_order && !packed) ? map[i] : base + e * kWave + lane;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < kItems; ++e) {
-        const int i = min(base + e * kWave + lane, nload - 1);
-        raw[e] = group8_abs_sum(vals + (size_t)i * 8);
-        mapped[e] = (map && !p.rank_order && !packed) ? map[i] : base + e * kWave + lane;
-      }
+    for (int e = 0; e < kItems; ++e) {  // clamped and unconditional, so that the loads do not wait for one another
+      const int i = min(base + e * kWave + lane, nload - 1);
+      raw[e] = vals[i];
+      mapped[e] = (map && !p.rank_order && !packed) ? map[i] : base + e * kWave + lane;
     }
     const int n_now = p.n_dev ? min(n_raw, p.n_cap) : p.n;
 #pragma unroll
@@ -413,12 +370,12 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
   HIRE_TS(35);
 }
 
-template <typename V, int ITEMS, bool G8 = false>
+template <typename V, int ITEMS>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelectParams p) {
   __shared__ SelShared sh;
   __shared__ uint32_t win[kHistWindow];
   extern __shared__ unsigned long long dyn[];
-  select_row<V, ITEMS, G8>(p, (int)blockIdx.x, sh, dyn, win);
+  select_row<V, ITEMS>(p, (int)blockIdx.x, sh, dyn, win);
 }
 
 // ---------------------------------------------------------------------------
@@ -1426,7 +1383,7 @@ hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s) {
 template <typename V>
 static bool select_is_lean(const SelectParams& p) {
   const int cap = p.n_dev ? p.n_cap : p.n;
-  return p.nonneg && !p.rank_order && !p.group8 && p.gs == 0 && !p.relu && cap > kSelThreads && cap <= kCachedMax &&
+  return p.nonneg && !p.rank_order && p.gs == 0 && !p.relu && cap > kSelThreads && cap <= kCachedMax &&
          p.k <= kWin / 2 && reinterpret_cast<uintptr_t>(p.vals) % 16 == 0 && (p.stride * (long long)sizeof(V)) % 16 == 0;
 }
 template <typename V>
@@ -1435,11 +1392,6 @@ static hipError_t launch_select(const SelectParams& p, int B, hipStream_t s) {
   if (p.rank_order) lds = (size_t)p.k * (sizeof(typename KeyOf<V>::K) + 2 * sizeof(int));
   const int cap = p.n_dev ? p.n_cap : p.n;
   if (select_is_lean<V>(p)) return launch(k_select_nonneg<V>, dim3(B), dim3(kSelThreads), 0, s, p);
-  if (p.group8) {  // rows of at most kSelectGroup8Max groups
-    if (cap <= kSelThreads) return launch(k_select<V, 1, true>, dim3(B), dim3(kSelThreads), lds, s, p);
-    if (cap <= 4 * kSelThreads) return launch(k_select<V, 4, true>, dim3(B), dim3(kSelThreads), lds, s, p);
-    return hipErrorInvalidValue;
-  }
   if (cap <= kSelThreads) return launch(k_select<V, 1>, dim3(B), dim3(kSelThreads), lds, s, p);
   if (cap <= 4 * kSelThreads) return launch(k_select<V, 4>, dim3(B), dim3(kSelThreads), lds, s, p);
   if (cap <= kCachedMax) return launch(k_select<V, kItemsMax>, dim3(B), dim3(kSelThreads), lds, s, p);
