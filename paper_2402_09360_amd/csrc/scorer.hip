@@ -21,12 +21,11 @@ __device__ __forceinline__ void zero_slice(uint32_t* p, int words) {
   for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < words; i += stride) p[i] = 0u;
 }
 
-// Block-wide max of non-negative floats (256 threads).
+// Block-wide max of non-negative floats (256 threads), once per kernel.  Loads stay under way.
 __device__ __forceinline__ float block_max_256(float v, float* red) {
   v = wave_max(v);
-  __syncthreads();
   if (lane_id() == 0) red[wave_id()] = v;
-  __syncthreads();
+  lds_barrier();
   float m = red[0];
   for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmaxf(m, red[w]);
   return m;
@@ -325,34 +324,32 @@ __global__ __launch_bounds__(256) void k_scorer_int4_b1(const uint4* __restrict_
   uint4 wa[kScorerRPW][CH], wb[kScorerRPW][CH];
   float sa = 0.0f, sb = 0.0f;
   int g = (int)blockIdx.x * 4 + wave_id();
-  if (g < groups) fetch(g, wa, sa);  // in flight while the token is quantised
   {
+    // the token first, then the first rows (loads return in order), which fly while it is quantised
     const uint4* xr = reinterpret_cast<const uint4*>(x);  // d is a multiple of 32: whole 16-byte chunks of 8 bf16
     const int chunks = d / 8;
+    uint4 tok[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) tok[u] = xr[min((int)threadIdx.x + 256 * u, chunks - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    if (g < groups) fetch(g, wa, sa);
+    __builtin_amdgcn_sched_barrier(0);
     float amax = 0.0f;
-    for (int c = (int)threadIdx.x; c < chunks; c += 256) {
-      const uint4 v = xr[c];
-      const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const uint32_t wd[4] = {tok[u].x, tok[u].y, tok[u].z, tok[u].w};
 #pragma unroll
       for (int q = 0; q < 4; ++q) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(wd[q])), fabsf(bf16_hi(wd[q]))));
     }
-    amax = block_max_256(amax, red);
-    float sx = __fdiv_rn(amax, 127.0f);
-    if (amax == 0.0f) sx = 1.0f;
-    auto code = [&](float f) -> uint32_t {
-      float r = rintf(__fdiv_rn(f, sx));
-      r = fminf(fmaxf(r, -127.0f), 127.0f);
-      return (uint32_t)((int)r) & 0xFFu;
-    };
-    for (int c = (int)threadIdx.x; c < chunks; c += 256) {
-      const uint4 v = xr[c];
-      const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-      uint2 o;
-      o.x = code(bf16_lo(wd[0])) | code(bf16_hi(wd[0])) << 8 | code(bf16_lo(wd[1])) << 16 | code(bf16_hi(wd[1])) << 24;
-      o.y = code(bf16_lo(wd[2])) | code(bf16_hi(wd[2])) << 8 | code(bf16_lo(wd[3])) << 16 | code(bf16_hi(wd[3])) << 24;
-      reinterpret_cast<uint2*>(xs)[c] = o;
+    const TokenScale ts = token_scale(block_max_256(amax, red));
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int c = (int)threadIdx.x + 256 * u;
+      float unused;
+      const uint2 codes = quantise8(tok[u], ts, &unused);
+      if (c < chunks) reinterpret_cast<uint2*>(xs)[c] = codes;
     }
-    __syncthreads();
+    lds_barrier();
   }
   while (g < groups) {
     const int g1 = g + total_waves, g2 = g1 + total_waves;
