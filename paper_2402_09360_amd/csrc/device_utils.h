@@ -163,15 +163,20 @@ template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
   return read_lane63(wave_prefix(v, (T)0, [](T a, T b) { return a + b; }));
 }
-// Sums of four values over the 64 lanes: lane 16 q + 15 has that of value q (other lanes: parts).  Halves and rows of sixteen
-// change places between two values, so that one addition goes on with both: 7 additions where four wave_sum take 24.
-__device__ __forceinline__ int wave_sum4(int v0, int v1, int v2, int v3) {
+// Row q of sixteen lanes: value q added over the four rows, lane by lane.  Halves and rows change places between two values, so
+// that one addition goes on with both.
+__device__ __forceinline__ int fold_rows4(int v0, int v1, int v2, int v3) {
   auto swap32 = [](int a, int b) {
     const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
     return (int)(r[0] + r[1]);  // lower half: a's two halves together, upper half: b's
   };
   const auto r = __builtin_amdgcn_permlane16_swap(swap32(v0, v2), swap32(v1, v3), false, false);
-  int s = (int)(r[0] + r[1]);
+  return (int)(r[0] + r[1]);
+}
+// Sums of four values over the 64 lanes: lane 16 q + 15 has that of value q (other lanes: parts).  7 additions where four
+// wave_sum take 24.
+__device__ __forceinline__ int wave_sum4(int v0, int v1, int v2, int v3) {
+  int s = fold_rows4(v0, v1, v2, v3);
   s += dpp_move<0x111, 0xF>(0, s);
   s += dpp_move<0x112, 0xF>(0, s);
   s += dpp_move<0x114, 0xF>(0, s);

@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
     }
   };
   auto quantise_tokens = [&]() {
-    __syncthreads();  // amax_sh and xb are complete
+    lds_barrier();  // amax_sh and xb are complete; the packed rows stay under way
 #pragma unroll
     for (int u = 0; u < kXreg; ++u) {
       const int idx = tid + u * kShThreads;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
       const uint2 codes = quantise8(xreg[u], token_scale(m), &unused);
       reinterpret_cast<uint2*>(xq)[xbb[u] * 2 * xqs + xc[u]] = codes;
     }
-    __syncthreads();
+    lds_barrier();
     if (tid < BT) amax_sh[tid] = 0u;  // for the next bundle; the barriers of the scoring that follows publish it
   };
 
@@ -266,8 +266,10 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
     keys[(tid / (Lp - Ls)) * Lp + Ls + tid % (Lp - Ls)] = -1.0f;
 
   uint4 wv[kRowsPerWave][CH];
+  float row_scale = 0.0f;  // of the row whose sum this lane has: r0 + lane / 16
   const uint4* q4s = q4 + unit0 * cpr;  // the shard's packed rows; offsets inside a shard fit 32 bits
   auto fetch_packed = [&](int r0) {
+    row_scale = scale[unit0 + min(r0 + (lane >> 4), Ls - 1)];
     if constexpr (BT == 4) {  // sixteen chunks of four rows per load
       const uint4* row = q4s + min(r0 + (lane & 3), Ls - 1) * cpr;
 #pragma unroll
@@ -307,23 +309,16 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
             const uint4* xr = xq + (lane & 3) * xqs + 2 * min(c, cpr - 1);
             int4_rows_by_tokens(make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep), xr[0], xr[1], acc);
           }
-        int sum = 0;  // lane l < 16: row l / 4, token l % 4
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int v = acc[r];
-          v += dpp_move<0x124, 0xF>(0, v);
-          v += dpp_move<0x128, 0xF>(0, v);
-          v += __shfl_xor(v, 16);
-          v += __shfl_xor(v, 32);
-          sum = lane >> 2 == r ? v >> 4 : sum;  // every partial is a multiple of 16
-        }
-        const int bb = lane & 3, row = r0 + (lane >> 2);
-        if (lane < 16 && row < Ls && bb < nb) {
-          const size_t j = unit0 + row;
-          float key = (float)sum * scale[j];
+        int sum = fold_rows4(acc[0], acc[1], acc[2], acc[3]);  // lane l: row l / 16, token l % 4
+        sum += dpp_move<0x124, 0xF>(0, sum);
+        sum += dpp_move<0x128, 0xF>(0, sum);
+        sum >>= 4;  // every partial is a multiple of 16
+        const int bb = lane & 3, row = r0 + (lane >> 4);
+        if ((lane & 12) == 0 && row < Ls && bb < nb) {
+          float key = (float)sum * row_scale;
           key = key > 0.0f ? key : 0.0f;  // phi = ReLU; also turns -0 into +0
           keys[bb * Lp + row] = key;
-          if (acc_out) acc_out[(size_t)(b0 + bb) * N + j] = sum;
+          if (acc_out) acc_out[(size_t)(b0 + bb) * N + unit0 + row] = sum;
         }
       } else {
         int acc[BT][kRowsPerWave];
@@ -356,18 +351,16 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
         }
 #pragma unroll
         for (int bb = 0; bb < BT; ++bb) {
-          int mine = 0;
+          int v[4] = {0, 0, 0, 0};
 #pragma unroll
-          for (int rr = 0; rr < kRowsPerWave; ++rr) {
-            const int sum = wave_sum(acc[bb][rr]) >> 4;  // every partial is a multiple of 16
-            mine = lane == rr ? sum : mine;
-          }
-          if (lane < kRowsPerWave && r0 + lane < Ls && bb < nb) {
-            const size_t j = unit0 + r0 + lane;
-            float key = (float)mine * scale[j];
+          for (int rr = 0; rr < kRowsPerWave; ++rr) v[rr] = acc[bb][rr];
+          const int sum = wave_sum4(v[0], v[1], v[2], v[3]) >> 4;  // every partial is a multiple of 16
+          const int row = r0 + (lane >> 4);
+          if ((lane & 15) == 15 && (lane >> 4) < kRowsPerWave && row < Ls && bb < nb) {
+            float key = (float)sum * row_scale;
             key = key > 0.0f ? key : 0.0f;  // phi = ReLU; also turns -0 into +0
-            keys[bb * Lp + r0 + lane] = key;
-            if (acc_out) acc_out[(size_t)(b0 + bb) * N + j] = mine;
+            keys[bb * Lp + row] = key;
+            if (acc_out) acc_out[(size_t)(b0 + bb) * N + unit0 + row] = sum;
           }
         }
       }
