@@ -806,7 +806,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
 //
 // The selection works on the activations rounded to fp32 (rounding is monotone; the coefficients of the second layer are
 // these values anyway); the keys of the threshold bin, and a selection without histogram, go by the fp64 values.
-// Measured at the ~1B shape: 9.7 us with the reduction over the waves and the shortlist's list in it.  Inside: window
+// Measured at the ~1B shape: 9.0 us with the reduction over the waves and the shortlist's list in it.  Inside: window
 // walked 1.5, masks 0.7, bin settled 0.6, rows listed 0.5, rows 2.8, reduction 0.8.
 constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
@@ -943,7 +943,8 @@ __device__ __forceinline__ void list_shortlist(const FastW2Params& p, W2Shared& 
 // half is another workgroup's, which has to find the line in L2 (one token at the ~1B shape 24.0 us per step, 24.3 with
 // streaming loads; four tokens in slices of 64 42.4 with, 43.0 without).  Dense rows are every token's: plain loads (2736 of them
 // and four tokens, groups of eight: 46.5 -> 40.5 us per step, one token 30.3 -> 25.7).
-template <typename KEY, int LOADS, int COLS>
+// SHARED: p.shared_out may be set (kernels without it are free of its branches).
+template <typename KEY, int LOADS, int COLS, bool SHARED = false>
 __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   auto load_w2 = [](const uint4* row) { return COLS == 32 ? *row : load_streaming(row); };
   using K = uint32_t;
@@ -988,7 +989,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   kr.issue(h32, p.n, p.fr->zeros);
   if (tid == 0) sh.list_n = 0;
   kr.finish();
-  const bool lists = p.shared_out != 0 && w == kWW - 1 && p.cand_out != nullptr;  // uniform over the wave
+  const bool lists = SHARED && p.shared_out != 0 && w == kWW - 1 && p.cand_out != nullptr;  // uniform over the wave
   UnionShare share;
   if (lists) share.issue(p);
   // rows of the wave: slot-th of every sixteen, eight columns per lane
@@ -1169,7 +1170,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
     }
     // one of the token's workgroups writes the selected groups behind its columns
-    const bool writes = p.shared_out != 0 && blockIdx.x == 0 && (p.topk_idx != nullptr || p.topk_val != nullptr);  // uniform
+    const bool writes = SHARED && p.shared_out != 0 && blockIdx.x == 0 && (p.topk_idx != nullptr || p.topk_val != nullptr);  // uniform
     if (writes) {
       const int mine = wave_sum(__popc(take));
       if (lane == 0) wave_cnt[w] = mine;
@@ -1356,6 +1357,8 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     if (lowrank && !several)  // (its list of the shortlist reads the fp64 keys)
       e = n_sel <= 4096 ? go(k_fast_w2<uint64_t, 1, 32>)
                         : (n_sel <= 8192 ? go(k_fast_w2<uint64_t, 2, 32>) : go(k_fast_w2<uint64_t, 4, 32>));
+    else if (p.shared_out)  // groups: 2048 at most
+      e = cols == 32 ? go(k_fast_w2<uint32_t, 1, 32, true>) : go(k_fast_w2<uint32_t, 1, 64, true>);
     else if (n_sel <= 4096)
       e = by_cols(k_fast_w2<uint32_t, 1, 32>, k_fast_w2<uint32_t, 1, 64>, k_fast_w2<uint32_t, 1, 128>);
     else if (n_sel <= 8192)

@@ -531,9 +531,8 @@ static int token_slots(int B) { return B <= 4 ? 4 : 8; }
 //   d = 2048,  8192 units  37.5 35.7 36.1   28.6 30.0 33.7 and 36.5 36.8   41.5 43.9
 //   d =  512, 16000 units  34.0 30.5 31.0   28.0 30.6 34.5
 //   d = 2048, 16384 units  42.7 44.3 46.4   34.0 37.8 43.7
-// Groups of eight, whose longer sequence forms its activations in fp64 too, gain up to eight (275 us for four layers
-// against 322 with dense units, 164 against 166 for a small layer without).  The scorer keeps a token in four vectors per
-// thread.
+// Groups of eight, whose longer sequence forms its activations in fp64 too, gain up to eight where they have dense units beside
+// them or many units (ffn_group_step_impl holds the line).  The scorer keeps a token in four vectors per thread.
 bool ffn_fast_tokens_supported(int B, int d, bool groups) {
   if (B < 2 || B > kFastTokens || token_slots(B) * d > 32768) return false;
   return groups || B <= 4;
