@@ -1060,6 +1060,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       all_gt += wave_cnt[u];
       run_eq += u < w ? wave_eq[u] : 0;
     }
+    __syncthreads();  // wave_cnt is free: a wave without selected keys is far ahead of the others when it counts them below
     const int need_eq = p.k - all_gt;
 #pragma unroll
     for (int e = 0; e < LOADS; ++e) {
@@ -1104,7 +1105,6 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   };
   if (output) {
     const int mine = wave_sum(__popc(take));
-    __syncthreads();
     if (lane == 0) wave_cnt[w] = mine;
     __syncthreads();
     write_selected(gs == 0);

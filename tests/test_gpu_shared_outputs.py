@@ -1,6 +1,7 @@
 """Groups of eight, few tokens: the workgroups of the second layer's slices write the caller's lists as well, where that
 admits slices of half the width (four tokens of d = 2048, eight of d = 1024): lists shorter than the workgroups are many,
-ends inside a word, everything selected.  Against the oracle; then without the optional outputs."""
+ends inside a word, everything selected; rows whose threshold only the range narrowing finds.  Against the oracle; then
+without the optional outputs."""
 import numpy as np
 import pytest
 import torch
@@ -38,3 +39,21 @@ def test_shared_outputs(hire, oracle, d, N, B, k, kp, m1):
         hire.hire_ffn_commonpath_step(layer, dw[0], dw[1], x, k, kp, 8, out, ws, minimal=True)
         torch.cuda.synchronize()
         T.assert_float_close(out.y.cpu().numpy(), want["y"], "y")
+
+
+@pytest.mark.parametrize("d,groups,B,k,kp,m1,distinct", [
+    (2048, 24, 4, 5, 12, 0, 24), (2048, 1, 4, 1, 1, 0, 1), (2048, 200, 4, 120, 160, 0, 2), (2048, 2048, 4, 300, 900, 40, 3),
+    (1024, 70, 8, 30, 66, 40, 1), (1024, 33, 8, 32, 33, 7, 33)])
+def test_thresholds_among_zeros_and_equal_groups(hire, oracle, d, groups, B, k, kp, m1, distinct):
+    """The first token is zero: its threshold lies among the zeros.  Groups that repeat put more than 64 equal activations
+    around the other tokens' thresholds.  Few groups leave most waves without keys: nothing that the narrowing shares
+    between the waves may be written again before all of them have read it."""
+    print(f"narrowing d={d} groups={groups} B={B} k={k} k'={kp} m1={m1} distinct={distinct}", flush=True)
+    L = I.ffn_layer(1010 + distinct, d, 8 * groups)
+    rows = (np.arange(groups) % distinct)[:, None] * 8 + np.arange(8)
+    L["w1u"] = np.ascontiguousarray(L["w1u"][rows.ravel()])
+    D = I.ffn_layer(1011, d, max(m1, 1))
+    layer, scorer = T.make_ffn_layer(L)
+    x_bits = I.tokens(1012 + B, B, d)
+    x_bits[0] = 0
+    T.check_ffn_commonpath(layer, scorer, L, (D["w1u"][:m1], D["w2u"][:m1]), x_bits, 8 * k, 8 * kp, 8)
