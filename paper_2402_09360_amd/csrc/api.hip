@@ -644,7 +644,7 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     a.cand_out = cand_idx; a.n_cand = n_cand; a.scorer_acc = scorer_acc;
     a.fast_region = s.fast_region;
     a.keys = static_cast<float*>(s.keys); a.key_stride = s.key_stride; a.h = s.h; a.h32 = s.h32;
-    a.bitmap = s.bitmap; a.cand_scratch = s.cand; a.xq = s.xq; a.sumabs = s.sumabs;
+    a.bitmap = s.bitmap; a.cand_scratch = s.cand; a.xq = s.xq;
     a.stage_events = g_stage_events;
     a.scorer_clocks = g_scorer_clocks;
     HIRE_TRY(launch_ffn_fast(a, st));
@@ -825,7 +825,7 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
       a.lr_a = L->lr_a; a.lr_b = L->lr_b; a.r = L->r; a.norm_bounds = L->row_norm_bounds;
       a.t = s.t; a.keys64 = static_cast<double*>(s.keys); a.gkeys64 = static_cast<double*>(s.gkeys);
       a.lr_a_scale = L->lr_a_scale; a.lr_b_scale = L->lr_b_scale; a.keys_t = s.keys_t;
-      a.xq = s.xq; a.sumabs = s.sumabs;
+      a.xq = s.xq;
     }
     if (dense != nullptr && dense->m1 > 0) {
       a.dense_w1u = dense->w1u; a.dense_w2u = dense->w2u; a.m1 = dense->m1; a.h_dense = dense->h;
@@ -961,7 +961,6 @@ static size_t carve_shard_batch(void* ws, int B, int d, int N, int k, int shards
   c.take<char>(shard_partial_offset());
   FfnShardBuffers f{};
   f.xq = c.take<int8_t>((size_t)B * d);
-  f.sumabs = c.take<float>(B);
   f.stride = (N + 3) / 4 * 4;
   f.vals = c.take<float>((size_t)B * f.stride + 4);
   f.zero_words = (N + 63) / 64 * 2 + 2;

@@ -28,39 +28,6 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(KeysSelect p) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.  AHEAD: the token is
-// not in LDS, its loads go out with the row's.
-template <bool AHEAD = false>
-__device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row, const uint4* tok, int d) {
-  const int cpr = d / 8, lane = lane_id();
-  const uint4* r4 = reinterpret_cast<const uint4*>(row);
-  double acc0 = 0.0, acc1 = 0.0;
-#pragma nounroll
-  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
-    uint4 wv[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) wv[v] = r4[min(c0 + v * kWave + lane, cpr - 1)];
-    uint4 ahead[4];
-    if constexpr (AHEAD) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) ahead[v] = tok[min(c0 + v * kWave + lane, cpr - 1)];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (c0 + v * kWave + lane < cpr) {
-        const uint4 xv = AHEAD ? ahead[v] : tok[c0 + v * kWave + lane];
-        const uint32_t wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, xd[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc0 += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
-          acc1 += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
-        }
-      }
-  }
-  const double s = wave_sum(acc0 + acc1);
-  return s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-}
-
 struct RefineShared {
   SelSharedT<kSelThreads> sh;
   __align__(16) uint32_t win[kWin + 2 * kWave];  // window histogram; then the packed outputs (k <= kWin / 2)

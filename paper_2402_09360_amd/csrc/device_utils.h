@@ -22,6 +22,13 @@ __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xFFFF0000u); }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Nearest bf16 of an fp32, round-half-even, from and as bits; eight of them (two vectors of four) as bf16 pairs.
+__device__ __forceinline__ uint32_t f32_to_bf16_rne(uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; }
+__device__ __forceinline__ uint4 bf16_pairs(const uint4& a, const uint4& b) {
+  return make_uint4(f32_to_bf16_rne(a.x) | f32_to_bf16_rne(a.y) << 16, f32_to_bf16_rne(a.z) | f32_to_bf16_rne(a.w) << 16,
+                    f32_to_bf16_rne(b.x) | f32_to_bf16_rne(b.y) << 16, f32_to_bf16_rne(b.z) | f32_to_bf16_rne(b.w) << 16);
+}
+
 // Nearest bf16 of a double, round-half-even, straight from the binary64 bits
 // (no intermediate binary32, which would round twice).  Finite inputs whose
 // result is a normal bf16; smaller magnitudes flush through the generic path.
@@ -196,6 +203,39 @@ __device__ __forceinline__ T wave_min(T v) {
 // Inclusive prefix sum over the lanes of a wave.
 __device__ __forceinline__ int wave_scan_incl(int v) {
   return wave_prefix(v, 0, [](int a, int b) { return a + b; });
+}
+
+// ReLU of the fp64 dot product of a bf16 row and a bf16 token by one wave: products exact in fp32, sums in fp64.  AHEAD: the
+// token is not in LDS, its loads go out with the row's.
+template <bool AHEAD = false>
+__device__ __forceinline__ double wave_row_dot(const uint16_t* __restrict__ row, const uint4* tok, int d) {
+  const int cpr = d / 8, lane = lane_id();
+  const uint4* r4 = reinterpret_cast<const uint4*>(row);
+  double acc0 = 0.0, acc1 = 0.0;
+#pragma nounroll
+  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
+    uint4 wv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) wv[v] = r4[min(c0 + v * kWave + lane, cpr - 1)];
+    uint4 ahead[4];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ahead[v] = tok[min(c0 + v * kWave + lane, cpr - 1)];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (c0 + v * kWave + lane < cpr) {
+        const uint4 xv = AHEAD ? ahead[v] : tok[c0 + v * kWave + lane];
+        const uint32_t wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, xd[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc0 += (double)(bf16_lo(wd[q]) * bf16_lo(xd[q]));
+          acc1 += (double)(bf16_hi(wd[q]) * bf16_hi(xd[q]));
+        }
+      }
+  }
+  const double s = wave_sum(acc0 + acc1);
+  return s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
 }
 
 // Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.

@@ -49,6 +49,13 @@ constexpr int kRPW = 4;     // rows per wave and pass
 constexpr int kST = 1024;   // threads per scorer workgroup: one workgroup per CU, the token is quantised once per CU
 constexpr int kSW = kST / kWave;
 
+// Code of a value, scale sx, by the division itself: a thread has one word of codes to form.  (quantise8 of rows_mfma.h, whose
+// eight values per thread leave most waves idle, is slower in the one-token kernels: 18 steps at the ~1B shape 435 us against 430,
+// four steps of the int4 low-rank scorer there 102.5 against 101.6.)
+__device__ __forceinline__ int code_of(float f, float sx) {
+  return (int)fminf(fmaxf(rintf(__fdiv_rn(f, sx)), -127.0f), 127.0f);
+}
+
 // LRQ (the int4 low-rank scorer's second product): the "token" is the fp32 intermediate t of the first product,
 // rounded to bf16 here as it is loaded, the rows are those of the int4 copy of Z2, and the activations' bound comes
 // from the real token's norm and the layer's largest row norm (xn, xn_d, umax) instead of from the int4 codes.
@@ -89,10 +96,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
     if constexpr (!LRQ) {
       return x4[i];
     } else {
-      const uint4 a = x4[2 * i], b = x4[2 * i + 1];
-      auto rne = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; };
-      return make_uint4(rne(a.x) | (rne(a.y) << 16), rne(a.z) | (rne(a.w) << 16), rne(b.x) | (rne(b.y) << 16),
-                        rne(b.z) | (rne(b.w) << 16));
+      return bf16_pairs(x4[2 * i], x4[2 * i + 1]);
     }
   };
   const uint4 xv0 = token_vec(min(tid, xvecs - 1));
@@ -123,10 +127,9 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
     uint32_t packed = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float r = rintf(__fdiv_rn(f[e], sx));
-      r = fminf(fmaxf(r, -127.0f), 127.0f);
-      sabs += (int)fabsf(r);
-      packed |= ((uint32_t)(int)r & 0xFFu) << (8 * e);
+      const int c = code_of(f[e], sx);
+      sabs += abs(c);
+      packed |= ((uint32_t)c & 0xFFu) << (8 * e);
     }
     xq[i] = packed;
   }
@@ -263,10 +266,6 @@ __device__ __forceinline__ int chunk_dot(const uint4& v, const uint4& xa, const 
   }
   return a;
 }
-// code of a value, scale sx
-__device__ __forceinline__ int code_of(float f, float sx) {
-  return (int)fminf(fmaxf(rintf(__fdiv_rn(f, sx)), -127.0f), 127.0f);
-}
 
 template <int ROWS>
 __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict__ q1, const float* __restrict__ scale1,
@@ -357,7 +356,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
       const int i = 4 * q + (lane >> 4);
       if (sub == 15 && i < per && ja + i < r) {
         const uint32_t u = __float_as_uint((float)sum * z1_scale[q] + 0.0f);  // -0 -> +0
-        t_sh[ja + i] = __uint_as_float((u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u);  // to bf16, nearest even
+        t_sh[ja + i] = __uint_as_float(f32_to_bf16_rne(u) << 16);
       }
     }
   }
@@ -1264,7 +1263,7 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
       if (scorer_mfma_quantises(a.B, a.r, a.d, false)) {
         tok.x = a.x;
       } else {
-        if ((e = launch_quantize_tokens(a.x, false, a.B, a.d, a.xq, a.sumabs, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
+        if ((e = launch_quantize_tokens(a.x, false, a.B, a.d, a.xq, nullptr, nullptr, 0, nullptr, 0ull, s)) != hipSuccess) return e;
         tok.xq = a.xq;
       }
       e = launch_scorer_int4_mfma(reinterpret_cast<const uint32_t*>(a.lr_a), a.lr_a_scale, tok, a.B, a.r, a.d, 0, a.keys_t,

@@ -61,10 +61,7 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
     if constexpr (!LRQ) {
       return reinterpret_cast<const uint4*>(p.x)[at];
     } else {
-      const uint4 a = reinterpret_cast<const uint4*>(p.x)[2 * at], b = reinterpret_cast<const uint4*>(p.x)[2 * at + 1];
-      auto rne = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; };
-      return make_uint4(rne(a.x) | (rne(a.y) << 16), rne(a.z) | (rne(a.w) << 16), rne(b.x) | (rne(b.y) << 16),
-                        rne(b.z) | (rne(b.w) << 16));
+      return bf16_pairs(reinterpret_cast<const uint4*>(p.x)[2 * at], reinterpret_cast<const uint4*>(p.x)[2 * at + 1]);
     }
   };
   // All loads are unconditional: the wait for the tokens must not become one for the weights, which are issued next.

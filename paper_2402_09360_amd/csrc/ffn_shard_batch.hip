@@ -113,35 +113,6 @@ __global__ __launch_bounds__(kWave * kSbWaves) void k_shard_keys(ShardBatch p) {
   }
 }
 
-// fp64 dot product of a bf16 row and a bf16 token by one wave, both from memory: products exact in fp32, sums in fp64.
-__device__ __forceinline__ double wave_dot(const uint16_t* row, const uint16_t* tok, int d) {
-  const int cpr = d / 8, lane = lane_id();
-  const uint4 *r4 = reinterpret_cast<const uint4*>(row), *t4 = reinterpret_cast<const uint4*>(tok);
-  double acc0 = 0.0, acc1 = 0.0;
-#pragma nounroll
-  for (int c0 = 0; c0 < cpr; c0 += 4 * kWave) {
-    uint4 rv[4], tv[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int c = min(c0 + v * kWave + lane, cpr - 1);
-      rv[v] = r4[c];
-      tv[v] = t4[c];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (c0 + v * kWave + lane < cpr) {
-        const uint32_t rd[4] = {rv[v].x, rv[v].y, rv[v].z, rv[v].w}, td[4] = {tv[v].x, tv[v].y, tv[v].z, tv[v].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc0 += (double)(bf16_lo(rd[q]) * bf16_lo(td[q]));
-          acc1 += (double)(bf16_hi(rd[q]) * bf16_hi(td[q]));
-        }
-      }
-  }
-  const double s = wave_sum(acc0 + acc1);
-  return s > 0.0 ? s : 0.0;  // ReLU, and -0 -> +0
-}
-
 // The stored values are within hw / 2 of the activations (hw = 2 err_c max|u| |x|; zeros are exact).  With v the ks-th largest
 // stored value of the shard's candidates, the ks-th largest activation lies in [v - hw / 2, v + hw / 2]: what is stored
 // above v + hw is selected, what is stored below v - hw is not, and what lies between - the ks-th itself and seldom another -
@@ -160,6 +131,7 @@ __global__ __launch_bounds__(kWave * kSbWaves) void k_shard_refine(ShardBatch p)
     word[e] = p.bitmap[i >> 5];
   }
   const float xn = p.xnorm[b];
+  const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * p.d);
   float wn = 0.0f;
   for (int i = lane; i < p.wnorm_n; i += kWave) wn = fmaxf(wn, p.wnorm_tiles[i]);
   wn = wave_max(wn);
@@ -205,7 +177,7 @@ __global__ __launch_bounds__(kWave * kSbWaves) void k_shard_refine(ShardBatch p)
       while (open != 0ull) {
         const int l = __builtin_ctzll(open);
         open &= open - 1ull;
-        const double r = wave_dot(p.W + (size_t)(u0 + 64 * e + l) * p.d, p.x + (size_t)b * p.d, p.d);
+        const double r = wave_row_dot<true>(p.W + (size_t)(u0 + 64 * e + l) * p.d, tok, p.d);
         if (lane == l) act[e] = (uint64_t)__double_as_longlong(r);
       }
     }
@@ -254,7 +226,7 @@ hipError_t launch_ffn_shard_batch(const FfnShardArgs& a, const FfnShardBuffers& 
   ScorerTokens tok{f.xq, nullptr, false, nullptr, f.bitmap, f.zero_words, nullptr, 0ull};
   hipError_t e = hipSuccess;
   if (scorer_mfma_quantises(a.B, a.N, a.d, false)) tok.x = a.x;
-  else e = launch_quantize_tokens(a.x, false, a.B, a.d, f.xq, f.sumabs, f.bitmap, f.zero_words, nullptr, 0ull, s);
+  else e = launch_quantize_tokens(a.x, false, a.B, a.d, f.xq, nullptr, f.bitmap, f.zero_words, nullptr, 0ull, s);
   if (e != hipSuccess) return e;
   e = launch_scorer_int4_mfma(static_cast<const uint32_t*>(a.q4), a.q4_scale, tok, a.B, a.N, a.d, 1, f.vals, f.stride,
                               a.scorer_acc, HistRefs{nullptr, nullptr}, s);

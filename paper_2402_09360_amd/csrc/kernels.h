@@ -51,8 +51,9 @@ constexpr size_t kPackTrailerBytes = 64;
 hipError_t launch_pack_int4(const uint16_t* w, int rows, int cols, uint32_t* q4, float* scale, hipStream_t s);
 hipError_t launch_unpack_int4(const uint32_t* q4, int rows, int cols, int8_t* codes, hipStream_t s);
 
-// x bf16, or fp32 that is rounded to it (nearest even) first, [B,d] -> xq int8 [B,d], sumabs fp32 [B] = sum |xq|; also clears `zero_words` 32-bit words at zero_ptr.  As
-// a step's first kernel it checks the general header (optional) against the layout signature.
+// x bf16, or fp32 that is rounded to it (nearest even) first, [B,d] -> xq int8 [B,d], sumabs (optional) fp32 [B] = sum |xq|;
+// also clears `zero_words` 32-bit words at zero_ptr.  As a step's first kernel it checks the general header (optional)
+// against the layout signature.
 hipError_t launch_quantize_tokens(const void* x, bool f32, int B, int d, int8_t* xq, float* sumabs, uint32_t* zero_ptr,
                                   int zero_words, void* general_header, unsigned long long sig, hipStream_t s);
 
@@ -392,7 +393,6 @@ struct FfnFastArgs {
   uint32_t* bitmap;
   int32_t* cand_scratch;
   int8_t* xq;
-  float* sumabs;
   // Low-rank scorer (lowrank, up to four tokens; otherwise the int4 one): keys are fp64 (keys64, [B, key_stride], rows of
   // whole 16-byte vectors), t the bf16 intermediate [B, r], norm_bounds the two row-norm bounds of
   // hire_lr_prepare; gs = 3: gkeys64 instead of gkeys, in rows of whole vectors as well.
@@ -453,7 +453,6 @@ hipError_t launch_ffn_shard(const FfnShardArgs& a, hipStream_t s);         // th
 bool ffn_shard_batch(int B, int N, int d, int shards);  // whether it is the faster one
 struct FfnShardBuffers {
   int8_t* xq;            // [B, d]
-  float* sumabs;         // [B]
   float* vals;           // [B, stride], stride a multiple of 4: keys, then the filter stage's values
   long long stride;
   uint32_t* bitmap;      // union: zero_words words, whole 64-bit ones over the units

@@ -103,11 +103,8 @@ __global__ __launch_bounds__(256) void k_quantize_tokens(const void* __restrict_
       if constexpr (F32) hi[u] = row[2 * c + 1];
     }
     if constexpr (F32) {
-      auto rne = [](uint32_t w) { return (w + 0x7FFFu + ((w >> 16) & 1u)) >> 16; };
 #pragma unroll
-      for (int u = 0; u < CHUNKS; ++u)
-        v[u] = make_uint4(rne(v[u].x) | rne(v[u].y) << 16, rne(v[u].z) | rne(v[u].w) << 16, rne(hi[u].x) | rne(hi[u].y) << 16,
-                          rne(hi[u].z) | rne(hi[u].w) << 16);
+      for (int u = 0; u < CHUNKS; ++u) v[u] = bf16_pairs(v[u], hi[u]);
     }
   };
   load(0);
@@ -141,7 +138,7 @@ __global__ __launch_bounds__(256) void k_quantize_tokens(const void* __restrict_
   sabs = wave_sum(sabs);
   if (lane_id() == 0) isum[wave_id()] = sabs;
   __syncthreads();
-  if (tid == 0) sumabs[b] = (float)(isum[0] + isum[1] + isum[2] + isum[3]);
+  if (tid == 0 && sumabs != nullptr) sumabs[b] = (float)(isum[0] + isum[1] + isum[2] + isum[3]);
 }
 
 // ---------------------------------------------------------------------------

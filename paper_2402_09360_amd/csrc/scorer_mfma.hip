@@ -138,10 +138,7 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
 #pragma unroll
         for (int m = 0; m < VECS; ++m) {
           if constexpr (SRC == kF32) {
-            auto rne = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16; };
-            const uint4 a = tv[q][m], b = tv2[q][m];
-            tv[q][m] = make_uint4(rne(a.x) | (rne(a.y) << 16), rne(a.z) | (rne(a.w) << 16), rne(b.x) | (rne(b.y) << 16),
-                                  rne(b.z) | (rne(b.w) << 16));
+            tv[q][m] = bf16_pairs(tv[q][m], tv2[q][m]);
           }
           const uint32_t ud[4] = {tv[q][m].x, tv[q][m].y, tv[q][m].z, tv[q][m].w};
 #pragma unroll
