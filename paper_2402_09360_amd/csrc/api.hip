@@ -799,11 +799,14 @@ static int ffn_group_step_impl(const hire_ffn_layer* L, const void* x, int B, in
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   // few tokens, groups of eight: the three-kernel route on group activations (the low-rank scorers' kernels take up to four).
-  // Five to eight tokens of d >= 512 without dense units on up to 8192 units are faster in the longer sequence, us per step for
-  // five and eight, three kernels / longer sequence: d = 512, 6000 units 28.5 / 26.9, 30.4 / 28.5; d = 1024, 6000 units 31.9 / 29.2,
-  // 36.9 / 32.1; d = 3200, 4000 units 57.0 / 39.3, 61.5 / 40.6; but d = 256, 14000 units 29.9 / 33.0, 33.5 / 33.8; d = 2048,
-  // 16384 units 48.5 / 51.5, 59.3 / 59.0; with 1600 dense units d = 2048, 8000 units 46.7 / 52.5, 56.7 / 53.7
-  const bool fast_int4 = L->scorer_kind == HIRE_SCORER_INT4 && (B <= 4 || N > 8192 || d < 512 || (dense != nullptr && dense->m1 > 0));
+  // Five to eight tokens without dense units on up to 8192 units are faster in the longer sequence from d = 288 on, us per step for
+  // five and eight, three kernels / longer sequence: d = 288, 1504 units 26.2 / 23.9, 27.9 / 24.4, 8192 units 27.3 / 27.3, 30.0 / 28.3;
+  // d = 480, 2000 units 27.1 / 24.0, 28.2 / 24.6, 8192 units 26.9 / 27.8, 30.5 / 28.5; d = 512, 6000 units 28.5 / 26.9, 30.4 / 28.5;
+  // d = 1024, 6000 units 31.9 / 29.2, 36.9 / 32.1; d = 3200, 4000 units 57.0 / 39.3, 61.5 / 40.6.  Up to d = 256
+  // neither is the faster one throughout: d = 256, 1504 units 24.8 / 24.3, 28.0 / 24.8, 6000 units 26.3 / 26.0, 28.8 / 27.9, 8192 units
+  // 26.2 / 27.9, 29.4 / 28.6; d = 64, 8192 units 25.9 / 26.9, 28.7 / 27.4.  More units, or 1600 dense ones: d = 256, 14000 units
+  // 29.9 / 33.0, 33.5 / 33.8; d = 2048, 16384 units 48.5 / 51.5, 59.3 / 59.0, 8000 and dense ones 46.7 / 52.5, 56.7 / 53.7.
+  const bool fast_int4 = L->scorer_kind == HIRE_SCORER_INT4 && (B <= 4 || N > 8192 || d <= 256 || (dense != nullptr && dense->m1 > 0));
   const bool fast_lr = L->scorer_kind == HIRE_SCORER_LOWRANK && L->row_norm_bounds != nullptr && B <= 4;
   const bool fast_lrq = L->scorer_kind == HIRE_SCORER_LRQ && L->row_norm_bounds != nullptr && B <= 4 &&
                         scorer_int4_fused_supported(d);

@@ -30,3 +30,14 @@ def test_group_select(hire, oracle, kind, d, N, B, k, kp):
     x = I.correlated_tokens(1601, B, d, 0.9)
     x[1] = 0
     T.check_ffn_group(layer, scorer, L, x, k, kp, 8)
+
+
+@pytest.mark.parametrize("d,N,B,k,kp", [(288, 8192, 5, 8 * 60, 8 * 204), (288, 8200, 5, 8 * 60, 8 * 204), (256, 8192, 8, 8 * 61, 8 * 203),
+                                        (288, 64, 8, 8, 8 * 2), (480, 8 * 1023, 8, 8 * 1023, 8 * 1023)])
+def test_five_to_eight_tokens_around_the_line_between_the_routes(hire, oracle, d, N, B, k, kp):
+    print(f"groups around the line d={d} N={N} B={B} k={k} k'={kp}", flush=True)
+    L = I.ffn_layer(1610 + d, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    x = I.tokens(1611 + B, B, d)
+    x[1] = 0
+    T.check_ffn_group(layer, scorer, L, x, k, kp, 8)
