@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
 // ---------------------------------------------------------------------------------------------------
 // The activations of the selected (token, unit) pairs once more, in fp64 and rounded once: k_refine leaves the filter
 // stage's fp32 values outside the band around the threshold, up to 2.3 half ulps off where one rounding is 1.0 at most
-// (mean 0.39 to 0.50 against 0.34).  A wave per pair: bound by the round trips list -> row, 5.3 us for 33 tokens with 251
+// (mean 0.39 to 0.50 against 0.34).  A wave per pair: bound by the round trips list -> row, 5.0 us for 33 tokens with 251
 // units of d = 800 (13 MB), 6.1 for 8 with 819 of 2048 (27 MB); two rows per wave 0.3 to 1.4 us more, four 1 to 2.4.  A die
 // takes an eighth of the (entries, token) pairs, entries first: neighbours in the lists are neighbours among the units, so
 // that what tokens share comes from its L2.

@@ -37,15 +37,16 @@ enum ScorerSource { kCodes, kBf16, kF32 };
 //
 // KW > 1 (rows of the FFN and of the low-rank factors): a workgroup has one group of tiles and sixteen waves, so that the
 // staging of the tokens, the unpacking and the epilogue are each a sixteenth of the work: the kernel is bound by that chain
-// and not by memory.  d = 2048, 16384 rows, 16 / 32 / 64 tokens: 5.9 / 6.7 / 8.7 us, where a workgroup of four waves with
-// whole rows each took 8.2 / 9.3 / 12.5; 5003 rows of 800 codes, 33 tokens: 4.9 with 32 rows per workgroup, 5.4 with 64.
+// and not by memory.  In steps whose weights come from HBM, averages under rocprofv3 (as all times here): d = 2048, 16384 rows,
+// 16 / 32 / 64 tokens 7.4 / 8.0 / 9.5 us, where a workgroup of four waves with whole rows each took 8.9 / 12.5 / 13.4; 5003 rows
+// of 800 codes, 33 tokens 5.8, 10.8.
 //
 // KW = 1 (vocabularies): a workgroup of eight waves per compute unit stages the tokens once and runs on from tile to tile,
 // the next request always out ahead of the current product.  No load there sits behind a branch: the wait for one request
-// would become one for the next (68 us instead of 54 for 256000 rows of 2048 codes and 16 tokens).  16 / 32 / 64 tokens: 54 / 62 /
-// 85 us (56 / 67 / 118 with a workgroup's tile in registers as a whole and four waves); the 263 MB alone take 42 us with
-// loads of this pattern, the keys 8 to 12 more, and from 33 tokens on the products (30 us of matrix cores and LDS) and the
-// stores that a wave waits for between its tiles are not hidden by two waves per SIMD.
+// would become one for the next (64 to 68 us instead of 52 to 54 for 256000 rows of 2048 codes and 16 tokens).  16 / 32 / 64
+// tokens: 52 / 58 / 73 to 80 us (54 / 80 / 124 with a workgroup's tile in registers as a whole and four waves); the 263 MB alone
+// take 42 us with loads of this pattern, the keys 8 to 12 more, and from 33 tokens on the products (30 us of matrix cores and
+// LDS) and the stores that a wave waits for between its tiles are not hidden by two waves per SIMD.
 //
 // kBf16, kF32: the workgroup quantises the tokens itself.  VECS: 16-byte vectors (of bf16 values, or of codes) of a token
 // per lane.
@@ -344,12 +345,12 @@ static_assert(2 * kVocabBlocks * kVocabWaves <= kWgMaxSlots, "two maxima per wav
 static int vocab_blocks(int N) { return min((N + 16 * kVocabWaves - 1) / (16 * kVocabWaves), kVocabBlocks); }
 int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 
-// Where quantising in every workgroup is cheaper than a kernel in front (3.5 to 4.7 us): up to 32 tokens of 2048 values, a wave
-// then has one or two, or 64 of 512.  d = 2048, 16384 rows: 16 tokens 7.3 against 4.7 + 5.9 us, 32 tokens 10.7 against 4.7 +
-// 6.7; 32000 rows, 32 tokens 15.2 against 4.7 + 10.8; d = 512, 3600 rows, 64 tokens 7.8 against 4.7 + 4.6.  Beyond (33 tokens
-// of 800 values: 9.8 against 4.2 + 4.9) a wave has four long tokens, one after the other.  The intermediate of the int4
-// low-rank scorer is short (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight
-// waves would take as long as the kernel in front (57.0 against 4.7 + 53.4).
+// Where quantising in every workgroup is cheaper than a kernel in front (3.6 to 4.8 us, and the boundary behind it, 1.5 to 2.5): up
+// to 32 tokens of 2048 values, a wave then has one or two, or 64 of 512.  d = 2048, 16384 rows: 16 tokens 8.4 against 3.8 + 7.4
+// us, 32 tokens 11.9 against 4.1 + 8.0; 32000 rows, 32 tokens 14.8 against 4.7 + 9.7; d = 512, 3600 rows, 64 tokens 8.6 against
+// 3.6 + 5.9, 20184 rows, 32 tokens 7.4 against 4.4 + 5.7.  Beyond (33 tokens of 800 values, 5003 rows: 12.2 against 3.8 + 5.8) a
+// wave has four long tokens, one after the other.  The intermediate of the int4 low-rank scorer is short (r <= 1024), and a
+// rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight waves would take as long as the kernel in front.
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
   if (N >= kVocabMinRows) return false;
   return f32 ? d <= 1024 : d <= (B <= 32 ? 2048 : 512);
@@ -371,8 +372,8 @@ static hipError_t scorer_mfma_launch(ScorerBatch& p, int grid, hipStream_t s) {
 }
 
 // Rows per workgroup for KW > 1: so many that the workgroups, one of which fills a compute unit, are 256 at most; a second
-// round costs as much as the first (20184 rows of 512 codes, 32 tokens: 7.5 us with 64 rows each, 5.4 with 128; 64 tokens of
-// 2048 codes 14.4 and 10.7).
+// round costs as much as the first (20184 rows of 512 codes, 32 tokens, quantised in place: 8.6 us with 64 rows each, 7.3 with 128;
+// 64 tokens of 2048 codes 16.3 and 12.2).
 template <int CT, int P, int SRC, int VECS>
 static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
   if (p.N > 16384) return scorer_mfma_launch<CT, 1, 8, 2, 2, SRC, VECS>(p, (p.N + 127) / 128, s);
@@ -384,8 +385,8 @@ static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
 template <int CT>
 static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
   if (p.N >= kVocabMinRows) {
-    // 32 rows per wave read the tokens' codes half as often (64 tokens, 256000 rows of 2048: 85 against 92 us), unless they
-    // leave more of the last round of tiles empty (40 tokens, 90000 of 1024: 27.3 against 23.6)
+    // 32 rows per wave read the tokens' codes half as often (64 tokens, 256000 rows of 2048: 79.1 against 80.9 us), unless they
+    // leave more of the last round of tiles empty (40 tokens, 90000 of 1024: 24.8 against 22.5)
     auto rounds = [&](int rows) { return ((p.N + rows - 1) / rows + kVocabBlocks - 1) / kVocabBlocks; };
     const int wide = 32 * kVocabWaves, blocks = min((p.N + wide - 1) / wide, kVocabBlocks);
     if (CT == 4 && blocks == vocab_blocks(p.N) && 2 * rounds(wide) <= rounds(wide / 2))
