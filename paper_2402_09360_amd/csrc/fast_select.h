@@ -135,6 +135,20 @@ struct KeyRegs {
   __device__ __forceinline__ bool valid(int e, int q) const { return owns(e) && index(e, q) < n; }
 };
 
+// Where a window in memory keeps slot s if several tokens are counted at once.  Most keys of a row lie within two octaves, 4 KB of
+// counters that many workgroups add to at once, and additions to the same few lines wait for one another; pieces of sixteen
+// counters are therefore 256 bytes apart, so that a step's counts go to four times as many lines.  33000 counts into four
+// windows by 256 workgroups: 6.6 us with the slots side by side, 3.1 like this (2.5 with stores in their place); pieces of
+// eight counters 2.9, of 32 4.2, 128 bytes apart 4.2, one copy of the windows per die 3.0.  A scorer of four tokens at
+// the ~1B shape is followed by the gather 3.2 us sooner (763 -> 689 us for 18 steps).  One token's 8200 counts
+// do not queue, and a reader has twice as many lines to ask for: there the slots stay side by side (d = 256, 1024 units 14.9
+// us per step, 15.5 spread).
+__device__ __forceinline__ int spread_slot(int s) {
+  constexpr int kPiece = 16, kApart = 64;
+  const int g = s / kPiece;
+  return g % (kWin / kApart) * kApart + g / (kWin / kApart) * kPiece + s % kPiece;
+}
+
 // A window histogram, walked from the top: thread t holds slots VEC*4*t .. VEC*4*(t+1) - 1 (requested by the
 // caller as its first loads).  found == false if the window holds fewer than `need` keys; otherwise the slot
 // holding the need-th largest counted key, to all threads.
@@ -151,6 +165,14 @@ struct WinRegs {
     const uint4* p = reinterpret_cast<const uint4*>(hist) + VEC * threadIdx.x;
 #pragma unroll
     for (int u = 0; u < VEC; ++u) v[u] = p[u];
+  }
+  __device__ __forceinline__ void issue(const uint32_t* hist, bool spread) {
+    const uint4* p = reinterpret_cast<const uint4*>(hist);
+#pragma unroll
+    for (int u = 0; u < VEC; ++u) {
+      const int at = (VEC * (int)threadIdx.x + u) * 4;
+      v[u] = p[(spread ? spread_slot(at) : at) / 4];
+    }
   }
 };
 template <int NT>

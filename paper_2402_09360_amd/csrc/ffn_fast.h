@@ -31,8 +31,8 @@ struct FastRegion {
   uint32_t spare;
   uint32_t zeros[8];         // stays zero: what lanes beyond the end of a key array load
   uint32_t pad[44];
-  uint32_t hist1[kWin];      // slot s: scorer keys in fine bin anchor1 - s
-  uint32_t hist2[kWin];      // slot s: activations in fine bin anchor2 - s
+  uint32_t hist1[kWin];      // slot s (steps of several tokens: at spread_slot(s)): scorer keys in fine bin anchor1 - s
+  uint32_t hist2[kWin];      // ... activations in fine bin anchor2 - s
 };
 static_assert(offsetof(FastRegion, zeros) % 16 == 0 && offsetof(FastRegion, hist1) == 256, "region layout");
 static_assert(sizeof(FastRegion) == kFastRegionBytes, "region size");
@@ -50,11 +50,11 @@ __device__ __forceinline__ void give_cookie(FastRegion* first, int clean, int B)
 }
 
 // Counts a key (its IEEE bits) in the window below the anchor; zeros are never counted.
-template <typename K>
+template <bool SPREAD, typename K>
 __device__ __forceinline__ void count_in_window(K bits, uint32_t anchor, uint32_t* hist, uint32_t* beyond) {
   const uint32_t bin = fine_bin(bits), slot = anchor - bin;
   if (bits == (K)0) return;
-  if (slot < (uint32_t)kWin) atomicAdd(&hist[slot], 1u);
+  if (slot < (uint32_t)kWin) atomicAdd(&hist[SPREAD ? spread_slot((int)slot) : (int)slot], 1u);
   else if (bin > anchor) *beyond = 1u;
 }
 

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_int4(const uint4* __restrict
     const int n = gkeys != nullptr ? N / 8 : N;
     if (blockIdx.x == 0 && tid < ((4 - (n & 3)) & 3)) arr[n + tid] = 0.0f;
   }
-  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
+  auto count_key = [&](float key) { count_in_window<false>(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
 
   const uint4* xq4 = reinterpret_cast<const uint4*>(xq);
   for (int g = gw; g * kRPW < N; g += total_waves) {
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lrq(const uint4* __restrict_
     const int n = gkeys != nullptr ? N / 8 : N;
     if (blockIdx.x == 0 && tid < ((4 - (n & 3)) & 3)) arr[n + tid] = 0.0f;
   }
-  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
+  auto count_key = [&](float key) { count_in_window<false>(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
   const uint4* tq4 = reinterpret_cast<const uint4*>(tq);
   for (int g = gw; 4 * g < N; g += waves) {  // uniform
     if (g != gw) {
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
           unit_keys[t][w * kRows + rw] = s;
         } else {
           keys[t * stride + j] = s;
-          count_in_window((uint64_t)__double_as_longlong(s), anchor1[t], fr[t].hist1, &fr[t].beyond1);
+          count_in_window<(TT > 1)>((uint64_t)__double_as_longlong(s), anchor1[t], fr[t].hist1, &fr[t].beyond1);
         }
       }
     }
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
         uint32_t anchor = 0u;
 #pragma unroll
         for (int u = 0; u < TT; ++u) anchor = t == u ? anchor1[u] : anchor;
-        count_in_window((uint64_t)__double_as_longlong(sum), anchor, fr[t].hist1, &fr[t].beyond1);
+        count_in_window<(TT > 1)>((uint64_t)__double_as_longlong(sum), anchor, fr[t].hist1, &fr[t].beyond1);
       }
       lds_barrier();
     }
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   }
   HIRE_TS(13);
   auto count_h = [&](double v) {  // the scorer kernel of this step has cleared the window
-    count_in_window((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
+    count_in_window<false>((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
   };
   if (!found) __syncthreads();  // the token in LDS
   for (int r = w; r < cnt; r += kGW) {  // uniform over the wave; one trip for most
@@ -983,7 +983,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   const bool whole = fr->beyond2 == 0u;     // the window counts every activation that it should
   const int clean = (int)p.fr->clean;       // (asked for here: at the end its latency would count)
   WinRegs<kWT> wr;
-  wr.issue(fr->hist2);
+  wr.issue(fr->hist2, p.B > 1);
   Keys kr;
   kr.issue(h32, p.n, p.fr->zeros);
   if (tid == 0) sh.list_n = 0;

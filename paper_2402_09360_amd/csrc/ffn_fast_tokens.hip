@@ -19,8 +19,9 @@ constexpr int kTokRows = 64;  // rows of a workgroup of the scorer
 // Kernel 1: scorer.  Every workgroup quantises the tokens itself (a kernel for that alone costs 3.3 us), kTW / TT waves
 // per token, then scores 64 rows on the int8 matrix cores, four rows per wave: v_mfma_i32_4x4x4 takes row l % 4 and
 // token l % 4 from lane l and adds up sixteen blocks of columns l / 4 separately, so that a load covers 256 bytes of
-// four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 12.0 us against 3.3 +
-// 7.6 with the quantisation in front; 5.6 of them until the keys are stored, the rest is the 33000 counts in memory.
+// four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 5.9 us until the
+// keys are stored, and 1.3 more than a kernel boundary takes until the 33000 counts have reached memory (4.5 with the
+// counters of adjacent bins side by side, see spread_slot); 3.3 more with the quantisation in front.
 // TT: tokens rounded up to four or eight; VECS: 16-byte vectors of a token per thread.  LRQ: as in k_fast_score_int4.
 struct FastScoreTokens {
   const uint4* q4;
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(kTT) void k_fast_score_tokens(FastScoreTokens p) {
     if (p.gkeys != nullptr) lds_barrier();
     return;
   }
-  auto count_key = [&](float key) { count_in_window(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
+  auto count_key = [&](float key) { count_in_window<true>(__float_as_uint(key), anchor1, fr->hist1, &fr->beyond1); };
   const int j = (int)blockIdx.x * kTokRows + lane;
   int sum = 0;
 #pragma unroll
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
     {
       const uint4* hist = reinterpret_cast<const uint4*>(p.fr[min(tw, B - 1)].hist1);
 #pragma unroll
-      for (int u = 0; u < kMine; ++u) wr[u] = hist[(wt * kMine + u) * kWave + lane];
+      for (int u = 0; u < kMine; ++u) wr[u] = hist[spread_slot(((wt * kMine + u) * kWave + lane) * 4) / 4];
     }
     const int entry = (u0 + lane) >> gs;  // lane's unit, or its group
     const bool valid = u0 + lane < p.N;
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   HIRE_TS(13);
   auto count_h = [&](int t, double v) {  // the scorer kernel of this step has cleared the windows
-    count_in_window((uint64_t)__double_as_longlong(v), p.fr[t].anchor2, p.fr[t].hist2, &p.fr[t].beyond2);
+    count_in_window<true>((uint64_t)__double_as_longlong(v), p.fr[t].anchor2, p.fr[t].hist2, &p.fr[t].beyond2);
   };
   if (sparse && gs == 0 && w < B && ((rows >> lane) & 1ull) == 0ull) {
     p.h32[(size_t)w * p.entries + u0 + lane] = 0.0f;
