@@ -285,19 +285,20 @@ __device__ __forceinline__ Cut<K> streaming_cut(const K* keys, int n, int k, Sel
 }
 
 // K: the keys' bit patterns.  TT: tokens rounded up to four or eight.
-// Measured at the ~1B shape and four tokens: 19.9 us (3.8 until the rows are known, 8.7 for the 9600 rows of the union,
-// 0.8 for the outputs; workgroups that have to settle a key of a threshold bin are 3 us behind), against 5.8 + 13 + the
-// larger part of 9.9 us for the three kernels of the longer sequence.
+// Measured at the ~1B shape and four tokens, from the first wave's start: 4.2 us until the rows are known, the 9600 rows of the
+// union until 13.2 (40 MB, 4.5 TB/s), 1.2 for the outputs; half the workgroups have ended by 14.3 and the last by 17.6, one
+// that has two keys of threshold bins to settle (19.8 when they were settled ahead of the rows).
 template <typename K, int TT>
 __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) {
   constexpr int kWPT = kTW / TT, kChunks = kWin / 256, kMine = kChunks / kWPT;  // 256 counters per wave and load
   __shared__ SelSharedT<kTT> sh;
   __shared__ int wave_gt[kTW], wave_eq[kTW];
   __shared__ int chunk_sum[TT][kChunks], slot[TT];
-  __shared__ K open_key[TT * kOwnUnits];  // units of the workgroup that only have keys of threshold bins: key,
-  __shared__ int open_unit[TT * kOwnUnits];  // unit and token,
-  constexpr int kOpenRound = 16;
-  __shared__ int open_ahead[kOpenRound][kTW];  // keys ahead of it, by wave
+  // units of the workgroup that only have keys of threshold bins: key, unit and token, keys ahead of it by wave.  More than four
+  // tokens come with groups of eight, whose first units stand for them.
+  constexpr int kOpen = TT <= 4 ? TT * kOwnUnits : TT * kOwnUnits / 8;
+  __shared__ K open_key[kOpen];
+  __shared__ int open_unit[kOpen], open_ahead[kOpen][kTW];
   __shared__ int unit_of[kOwnUnits];
   __shared__ double unit_h[TT][kOwnUnits];
   extern __shared__ double red[];  // partial sums of rows_by_tokens
@@ -309,9 +310,10 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   const int r0 = sparse ? g * p.share : p.own_blocks * p.share + (g - p.own_blocks) * kDenseRows;
   const int dense = max(0, min(sparse ? p.share : kDenseRows, p.m1 - r0));
   const int u0 = g * kOwnUnits;  // first unit of the workgroup
-  uint64_t rows = 0ull;          // units of the workgroup that any token shortlists
+  uint64_t rows = 0ull, taken = 0ull;  // units of the workgroup: whose rows are read; that any token shortlists
+  int opens = 0;                       // (unit, token) pairs that settle the difference
+  const int n = p.N >> gs;
   if (sparse) {
-    const int n = p.N >> gs;
     const int clean = (int)p.fr->clean;
     uint4 wr[kMine];
     const int tw = w / kWPT, wt = w % kWPT;  // the token whose window this wave helps to walk, its part of it
@@ -390,8 +392,9 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
       const Cut<K> cut = streaming_cut<K>(row, n, p.kprime, sh, wave_gt, wave_eq);
       rows |= __ballot(valid && cut_takes(cut, row[min(entry, n - 1)], entry));
     }
-    // every wave notes the undecided units (the same values) and reads its own notes; of a group its first unit
-    int opens = 0;
+    // every wave notes the undecided units (the same values) and reads its own notes; of a group its first unit.  Their rows
+    // are read with the others.
+    uint64_t undecided = 0ull;
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       const uint64_t m = in_bin[t] & ~rows & (gs != 0 ? 0x0101010101010101ull : ~0ull);
@@ -400,47 +403,10 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
         open_unit[opens + mask_prefix(m)] = lane * TT + t;
       }
       opens += __popcll(m);
+      undecided |= m;
     }
-    // A unit that only has keys of threshold bins, of which some are selected: its key is compared with all others of
-    // the token.  One workgroup in six has such a unit, and then one or two; the code is in no cache when they come
-    // here, so the loop is as short as it can be (unrolled over the tokens it took 6 us).
-#pragma unroll 1
-    for (int j0 = 0; j0 < opens; j0 += kOpenRound) {  // uniform over the workgroup
-      constexpr int PER = KeyIO<K>::PER, kLoads = 16 / PER;  // the row of 16384 keys at a time
-      const int vecs = (n + PER - 1) / PER, j1 = min(opens, j0 + kOpenRound);
-      uint4 raw[kLoads];
-      auto load = [&](int j) {
-        const int t = __builtin_amdgcn_readfirstlane(open_unit[j]) % TT;
-        const uint4* row = reinterpret_cast<const uint4*>(reinterpret_cast<const K*>(p.keys) + (size_t)t * p.stride);
-#pragma unroll
-        for (int u = 0; u < kLoads; ++u) raw[u] = row[min(u * kTT + tid, vecs - 1)];
-      };
-      load(j0);
-#pragma unroll 1
-      for (int j = j0; j < j1; ++j) {
-        const K mine = open_key[j];
-        const int at = (u0 + __builtin_amdgcn_readfirstlane(open_unit[j]) / TT) >> gs;
-        K k[kLoads][PER];
-#pragma unroll
-        for (int u = 0; u < kLoads; ++u) KeyIO<K>::unpack(raw[u], k[u]);
-        load(min(j + 1, j1 - 1));
-        int ahead = 0;
-#pragma unroll
-        for (int u = 0; u < kLoads; ++u) {
-          const int i = (u * kTT + tid) * PER;
-#pragma unroll
-          for (int q = 0; q < PER; ++q) ahead += i + q < n && k[u][q] >= mine + (i + q < at ? 0u : 1u) ? 1 : 0;
-        }
-        ahead = wave_sum(ahead);
-        if (lane == 0) open_ahead[j - j0][w] = ahead;
-      }
-      lds_barrier();
-#pragma unroll 1
-      for (int j = j0; j < j1; ++j)
-        if (wave_sum(lane < kTW ? open_ahead[j - j0][lane] : 0) < p.kprime)
-          rows |= (gs != 0 ? 0xFFull : 1ull) << (__builtin_amdgcn_readfirstlane(open_unit[j]) / TT);
-      lds_barrier();
-    }
+    taken = rows;
+    rows |= gs != 0 ? undecided * 0xFFull : undecided;  // (of a group its first unit's bit)
   }
   HIRE_TS(12);
   const int cnt = __popcll(rows);
@@ -462,13 +428,46 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   const char* base = reinterpret_cast<const char*>(p.W1);
   const long long row_bytes = 2ll * p.d, own_at = u0 * row_bytes,
                   dense_at = reinterpret_cast<const char*>(p.Wd) - base + (r0 - cnt) * row_bytes;
-  rows_by_tokens<TT>(
+  rows_sums<TT>(
       cnt + dense,
       [&](int r) {
         const int at = r < cnt ? unit_of[min(r, kOwnUnits - 1)] : r;
         return reinterpret_cast<const uint4*>(base + ((r < cnt ? own_at : dense_at) + at * row_bytes));
       },
-      p.x, B, nvec, red,
+      p.x, B, nvec, red);
+  // A unit that only has keys of threshold bins, of which some are selected: its key is compared with all others of the token.
+  // One workgroup in six has such a unit, and then one or two, and would be the last to end.  Its rows are read with the others,
+  // and a wave that has its rows asks for its part of the keys while other waves still wait for theirs: ahead of the rows, or
+  // beside their first loads, the keys cost 2 to 5 us instead of one.
+#pragma unroll 1
+  for (int j = 0; j < opens; ++j) {  // uniform over the workgroup
+    constexpr int PER = KeyIO<K>::PER, kLoads = 16 / PER;  // the row of 16384 keys at a time
+    const int unit = __builtin_amdgcn_readfirstlane(open_unit[j]), vecs = (n + PER - 1) / PER, at = (u0 + unit / TT) >> gs;
+    const uint4* row = reinterpret_cast<const uint4*>(reinterpret_cast<const K*>(p.keys) + (size_t)(unit % TT) * p.stride);
+    uint4 raw[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) raw[u] = row[min(u * kTT + tid, vecs - 1)];
+    const K mine = open_key[j];
+    int ahead = 0;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int i = (u * kTT + tid) * PER;
+      K k[PER];
+      KeyIO<K>::unpack(raw[u], k);
+#pragma unroll
+      for (int q = 0; q < PER; ++q) ahead += i + q < n && k[q] >= mine + (i + q < at ? 0u : 1u) ? 1 : 0;
+    }
+    ahead = wave_sum(ahead);
+    if (lane == 0) open_ahead[j][w] = ahead;
+  }
+  lds_barrier();
+  HIRE_TS(17);
+#pragma unroll 1
+  for (int j = 0; j < opens; ++j)
+    if (wave_sum(lane < kTW ? open_ahead[j][lane] : 0) < p.kprime)
+      taken |= (gs != 0 ? 0xFFull : 1ull) << (__builtin_amdgcn_readfirstlane(open_unit[j]) / TT);
+  rows_out<TT>(
+      cnt + dense, B, nvec, red,
       [&](int r, int t, double v) {
         if (r >= cnt) {
           p.hd[(size_t)t * p.m1 + r0 + r - cnt] = v;
@@ -478,18 +477,19 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
         if (gs != 0) {
           unit_h[t][pos] = v;
         } else {
-          p.h32[(size_t)t * p.entries + u0 + pos] = (float)v;
-          p.h64[(size_t)t * p.entries + u0 + pos] = v;
-          count_h(t, v);
+          const bool in = ((taken >> pos) & 1ull) != 0ull;
+          p.h32[(size_t)t * p.entries + u0 + pos] = in ? (float)v : 0.0f;
+          p.h64[(size_t)t * p.entries + u0 + pos] = in ? v : -1.0;
+          if (in) count_h(t, v);
         }
       });
   if (!sparse) return;
   if (gs != 0) {  // exact group activations, units added in order; wave t: token t
     __syncthreads();
     if (w < B) {
-      p.u32[(size_t)w * (p.entries << gs) + u0 + lane] = ((rows >> lane) & 1ull) != 0ull ? (float)unit_h[w][lane] : 0.0f;
+      p.u32[(size_t)w * (p.entries << gs) + u0 + lane] = ((taken >> lane) & 1ull) != 0ull ? (float)unit_h[w][lane] : 0.0f;
       if (lane < kOwnUnits >> gs) {
-        const bool in = ((rows >> (lane << gs)) & 1ull) != 0ull;
+        const bool in = ((taken >> (lane << gs)) & 1ull) != 0ull;
         double e = 0.0;
         if (in)
           for (int l = 0; l < (1 << gs); ++l) e += fabs(unit_h[w][(lane << gs) + l]);
@@ -502,11 +502,11 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   }
   if (tid == 0) {  // the workgroup's part of the union
     if (gs == 0) {
-      p.bitmap[2 * g] = (uint32_t)rows;
-      p.bitmap[2 * g + 1] = (uint32_t)(rows >> 32);
+      p.bitmap[2 * g] = (uint32_t)taken;
+      p.bitmap[2 * g + 1] = (uint32_t)(taken >> 32);
     } else {
       uint32_t bits = 0u;
-      for (int J = 0; J < kOwnUnits >> gs; ++J) bits |= (uint32_t)((rows >> (J << gs)) & 1ull) << J;
+      for (int J = 0; J < kOwnUnits >> gs; ++J) bits |= (uint32_t)((taken >> (J << gs)) & 1ull) << J;
       uint8_t* bytes = reinterpret_cast<uint8_t*>(p.bitmap);
       bytes[g] = (uint8_t)bits;
       if (g == p.own_blocks - 1)

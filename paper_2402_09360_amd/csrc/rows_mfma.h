@@ -72,11 +72,11 @@ __device__ __forceinline__ void int4_rows_by_tokens(const uint4& wv, const uint4
 // registers allow: a wave then reads up to a KB of a row (9.9 us for the rows of four tokens at the ~1B shape with 256
 // bytes, 8.6 with a KB, 7.8 with whole rows).  red: [parts of the columns][groups of four rows][TT / 4][16] sums, added
 // in a fixed order.
-template <int TT, int SL = 16 / TT, int kDepth = 8 / SL, typename RowOf, typename Out>
-__device__ __forceinline__ void rows_by_tokens(int cnt, RowOf&& row_of, const uint4* __restrict__ x, int B, int nvec,
-                                               double* red, Out&& out) {
+// The waves' sums; rows_out, behind a barrier, adds them up.
+template <int TT, int SL = 16 / TT, int kDepth = 8 / SL, typename RowOf>
+__device__ __forceinline__ void rows_sums(int cnt, RowOf&& row_of, const uint4* __restrict__ x, int B, int nvec, double* red) {
   constexpr int kTok4 = TT / 4, kMaxGroups = kMostRows / 4;
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int nsl = (nvec + 15) / 16, ng = (cnt + 3) / 4;
   int ps = 1;  // waves side by side over the columns: sixteen parts are enough (TT d <= 32768)
   while (ps * SL < nsl) ps <<= 1;
@@ -146,14 +146,26 @@ __device__ __forceinline__ void rows_by_tokens(int cnt, RowOf&& row_of, const ui
     }
   }
   HIRE_TS(16);
-  lds_barrier();
-  HIRE_TS(17);
+}
+template <int TT, int SL = 16 / TT, typename Out>
+__device__ __forceinline__ void rows_out(int cnt, int B, int nvec, const double* red, Out&& out) {
+  constexpr int kTok4 = TT / 4, kMaxGroups = kMostRows / 4;
+  const int tid = (int)threadIdx.x, nsl = (nvec + 15) / 16, ng = (cnt + 3) / 4;
   for (int o = tid; o < ng * kTok4 * 16; o += kRowsThreads) {
     const int r = o / (kTok4 * 16) * 4 + (o >> 2 & 3), t = o / 16 % kTok4 * 4 + (o & 3);
     double v = 0.0;
     for (int j = 0; j * SL < nsl; ++j) v += red[(size_t)j * kMaxGroups * kTok4 * 16 + o];
     if (r < cnt && t < B) out(r, t, v > 0.0 ? v : 0.0);  // ReLU, and -0 -> +0
   }
+}
+
+template <int TT, int SL = 16 / TT, int kDepth = 8 / SL, typename RowOf, typename Out>
+__device__ __forceinline__ void rows_by_tokens(int cnt, RowOf&& row_of, const uint4* __restrict__ x, int B, int nvec,
+                                               double* red, Out&& out) {
+  rows_sums<TT, SL, kDepth>(cnt, row_of, x, B, nvec, red);
+  lds_barrier();
+  HIRE_TS(17);
+  rows_out<TT, SL>(cnt, B, nvec, red, out);
 }
 
 }  // namespace hire

@@ -27,3 +27,29 @@ def test_one_and_several_tokens_in_turn(oracle, d, N):
             T.compare_ffn(got, want)
         assert hire.hire_debug_fast_state(ws)[:2] == (1, 0)
     assert hire.hire_debug_fast_fallbacks(ws) == before
+
+
+@pytest.mark.parametrize("B,group,distinct", [(2, 1, 3), (4, 1, 1), (4, 1, 40), (3, 8, 2), (8, 8, 1), (8, 8, 30)])
+def test_many_units_in_the_threshold_bins(oracle, B, group, distinct):
+    """Rows that repeat: whole workgroups' units share the threshold bins of several tokens, up to every unit of all of them,
+    and the lower index decides."""
+    import numpy as np
+    from paper_2402_09360_amd import hire
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    d, N, k, kp = 256, 1504, 64, 304
+    L = dict(I.ffn_layer(711, d, N))
+    rows = np.random.default_rng(712 + distinct).integers(0, distinct, N // group).repeat(group)
+    L["w1u"] = np.ascontiguousarray((L["w1u"] & 0x7FFF)[rows])  # keys of one sign
+    x = I.tokens(713, B, d) & 0x7FFF
+    print(f"{distinct} distinct rows, B={B}, groups of {group}", flush=True)
+    layer, scorer = T.make_ffn_layer(L)
+    if group == 1:
+        want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
+        for got in T.run_ffn(layer, x, k, kp, steps=3, debug=False):
+            T.compare_ffn(got, dict(want, acc=None))
+        return
+    want = oracle.ffn_group_step(L["w1u"], L["w2u"], scorer, x, k, kp, group)
+    for got in T.run_ffn_group(layer, x, k, kp, group, steps=3, debug=False):
+        assert np.array_equal(got["cand"], want["cand"]) and np.array_equal(got["topk_group"], want["topk_group"])
+        T.assert_float_close(got["topk_val"], want["topk_val"], "topk_val")
+        T.assert_float_close(got["y"], want["y"], "y")
