@@ -501,6 +501,31 @@ __device__ __forceinline__ int place_taken(uint32_t take, int run, Put&& put) {
   return run;
 }
 
+// The same for selections of about a key per lane, by the keys that there are (take as in BinMasks): put(place, index, j), j the
+// key's position among the lane's.
+template <typename Keys, typename Put>
+__device__ __forceinline__ void place_few(const Keys& kr, uint32_t take, int run, Put&& put) {
+  constexpr int LOADS = Keys::kLoads, PER = Keys::PER, COUNT = LOADS * PER;
+  constexpr uint32_t kField = (1u << PER) - 1u;
+  const uint32_t t = __brev(take) >> (32 - COUNT);  // bit e * PER + q
+  int first[LOADS];
+#pragma unroll
+  for (int e0 = 0; e0 < LOADS; e0 += 2) {
+    const int c0 = __popc(t >> (e0 * PER) & kField), c1 = e0 + 1 < LOADS ? __popc(t >> ((e0 + 1) * PER) & kField) : 0;
+    const int incl = wave_scan_incl(c0 | c1 << 16), tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+    first[e0] = run + (incl & 0xFFFF) - c0;
+    if (e0 + 1 < LOADS) first[e0 + 1] = run + (tot & 0xFFFF) + (incl >> 16) - c1;
+    run += (tot & 0xFFFF) + (tot >> 16);
+  }
+  for (uint32_t m = t; m != 0u; m &= m - 1u) {
+    const int j = __builtin_ctz(m), e = j / PER;
+    int at = first[0];
+#pragma unroll
+    for (int f = 1; f < LOADS; ++f) at = e == f ? first[f] : at;
+    put(at + __popc(t & ((1u << j) - 1u) & (kField << (e * PER))), kr.base + e * Keys::SPAN + lane_id() * PER + j % PER, j);
+  }
+}
+
 // One pass over a lane's keys against a bin: bit COUNT - 1 - j of above / inside says where key j = e * PER + q lies.
 // The masks are shifted in through the carry input: five instructions per key.
 template <typename K>

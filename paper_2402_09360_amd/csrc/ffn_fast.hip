@@ -1085,13 +1085,12 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
   auto write_selected = [&](bool units) {
     const int before = wave_scan_incl(lane < kWW ? wave_cnt[lane] : 0);
     const int run = w > 0 ? __builtin_amdgcn_readlane(before, w - 1) : 0;
-    place_taken<Keys>(__brev(take) >> (32 - LOADS * PER), run, [&](int at, int e, int q) {
-      const int i = kr.index(e, q);
+    place_few<Keys>(kr, take, run, [&](int at, int i, int j) {
       if (at >= p.k) return;  // (never; but whatever the workspace holds, nothing is written past the token's row)
       if (p.topk_idx) p.topk_idx[b * p.k + at] = i;
       if (p.topk_val == nullptr) return;
       if (units) {
-        p.topk_val[b * p.k + at] = __uint_as_float(kr.r[e][q]);
+        p.topk_val[b * p.k + at] = __uint_as_float(key_at<0, LOADS * PER>(kr, j));
       } else {  // groups of eight: their units' activations
         const float4* act = reinterpret_cast<const float4*>(u32 + ((size_t)i << 3));
         const float4 lo = act[0], hi = act[1];
