@@ -382,10 +382,11 @@ struct FilterUnits {
   float* wnorm_tiles;
   uint32_t* wnorm_max;
   float err_c;
+  int turn;                // the workgroups of a die start in different stages (launch_filter_units)
 };
 
 // The 64 units of a tile, by a workgroup; lds: kFtStages stages.
-template <int TT, int TG, int KS>
+template <int TT, int TG, int KS, bool TURN>
 __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile, unsigned char* lds) {
   using S = FtShape<TT, TG, KS>;
   constexpr int NW = S::NW, NT = S::NT, TTW = S::TTW, CI = S::CI, TI = S::TI, kStage = S::kStage;
@@ -444,17 +445,31 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
 #pragma unroll
       for (int i = 0; i < TI; ++i) load_to_lds(xptr[i] + off, to_tok + 1024 * NW * i);
     };
+    // the stages in turn from `at` on, round the end of the row
+    auto run = [&](auto turned, int at) __attribute__((always_inline)) {
+      int next = at;
+      auto forward = [&](int st) { return turned() && st + 1 == nst ? 0 : st + 1; };
 #pragma unroll
-    for (int st = 0; st < kFtStages - 1; ++st)
-      if (st < nst) request(st, st);
-    int slot = 0;
-    for (int st = 0; st < nst; ++st) {
-      stage_barrier_loads<CI, TI>(ci, st + kFtStages - 2 < nst);
-      if (st + kFtStages - 1 < nst) request(st + kFtStages - 1, slot == 0 ? kFtStages - 1 : slot - 1);
-      if (16 * cw < c)  // uniform
-        ft_stage<TT, TG, KS>(lds + slot * kStage, cw, tt0, kh, cpr - kFtChunks * st, true, acc);
-      slot = slot == kFtStages - 1 ? 0 : slot + 1;
-    }
+      for (int st = 0; st < kFtStages - 1; ++st)
+        if (st < nst) {
+          request(next, st);
+          next = forward(next);
+        }
+      int slot = 0;
+      for (int st = 0; st < nst; ++st) {
+        stage_barrier_loads<CI, TI>(ci, st + kFtStages - 2 < nst);
+        if (st + kFtStages - 1 < nst) {
+          request(next, slot == 0 ? kFtStages - 1 : slot - 1);
+          next = forward(next);
+        }
+        if (16 * cw < c)  // uniform
+          ft_stage<TT, TG, KS>(lds + slot * kStage, cw, tt0, kh, cpr - kFtChunks * at, true, acc);
+        at = forward(at);
+        slot = slot == kFtStages - 1 ? 0 : slot + 1;
+      }
+    };
+    if (TURN && p.turn && c > 3 * kFtRows / 4) run(std::true_type{}, tile / 8 % nst);  // uniform
+    else run(std::false_type{}, 0);
   }
   HIRE_TS(57);
   // LDS from here on: the result tile [16 TT][64], the rows' squared norms [KS][64], the other K shares' sums
@@ -545,7 +560,7 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
 template <int TT, int TG, int KS>
 __global__ __launch_bounds__(256 * TG * KS) void k_filter_units(FilterUnits p) {
   extern __shared__ __align__(16) unsigned char lds[];
-  filter_units_tile<TT, TG, KS>(p, (int)blockIdx.x, lds);
+  filter_units_tile<TT, TG, KS, TT <= 2>(p, (int)blockIdx.x, lds);
 }
 
 // The selection of the k' largest keys and the filter stage at once: the first workgroups select, a token each, the others
@@ -560,7 +575,7 @@ __global__ __launch_bounds__(256 * TG * KS) void k_select_filter(KeysSelect ks, 
   extern __shared__ __align__(16) unsigned char lds[];
   const int tile = (int)blockIdx.x - p.B;
   if (tile < 0) keys_select_token<K, LOADS>(ks, (int)blockIdx.x, *reinterpret_cast<KeysSelectShared<K>*>(lds));  // uniform
-  else filter_units_tile<TT, TG, KS>(p, tile, lds);
+  else filter_units_tile<TT, TG, KS, false>(p, tile, lds);
 }
 
 // The same product for the classifier (phi = identity; the union is a small part of a long vocabulary): the candidates
@@ -764,12 +779,18 @@ int filter_tiles(int n) { return max(1, (n + kFtRows - 1) / kFtRows); }
 int filter_rank_blocks(int n_cap) { return min(filter_tiles(n_cap), 256); }
 static_assert(4 * 256 <= kFilterMaxima && kFrMaxRows * 256 >= kSoftmaxRefineMaxRow, "maxima and rows per workgroup");
 
+// Where every workgroup reads the same 256 bytes of its rows at a time, rows of 4 KB and more queue in the memory system; with up to
+// 32 tokens, whose stages are mostly rows, and most of a workgroup's units candidates, the workgroups of a die
+// therefore start in different stages.  us per layer, not turned / turned: d = 2048, 16384 units, 9 / 16 / 32 tokens 56.2 / 55.0,
+// 53.0 / 50.1, 60.9 / 59.3 (65 MB in 14.8 us instead of 16.7); d = 4096, 9216 units, 16 tokens 61.4 / 60.4; d = 3072, 12288, 60.2 / 60.0.
+// Shorter rows gain nothing (d = 1024, 32 tokens 42.0 / 42.3; d = 1536, 16 46.6 / 46.9), nor do 64 tokens (68.8 / 69.4), workgroups
+// with a selection beside them (8192 units, 16 tokens 35.1 / 35.9) or few candidates (tokens of one query 41.5 / 42.1).
 hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int d, const uint32_t* bitmap,
                                const int32_t* n_dev, int n_rows, float* h, long long stride_h, float* xnorm,
                                float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s) {
   if (B < 1 || B > 64 || d % 8 != 0) return hipErrorInvalidValue;
   static std::atomic<size_t> raised_to[3] = {};
-  const FilterUnits p{W, x, B, d, bitmap, n_dev, n_rows, h, stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B)};
+  const FilterUnits p{W, x, B, d, bitmap, n_dev, n_rows, h, stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B), d >= 2048 ? 1 : 0};
   auto go = [&](auto kernel, int tt, int waves, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
@@ -787,7 +808,7 @@ hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int 
 hipError_t launch_select_filter(const KeysSelect& ks, int B, const uint16_t* W, const uint16_t* x, int d, float* h,
                                 long long stride_h, float* xnorm, float* wnorm_tiles, hipStream_t s) {
   if (B < 1 || B > 64 || d % 8 != 0 || !keys_select_ok(ks) || (ks.f64 && ks.N > kSelectFilterMaxF64)) return hipErrorInvalidValue;
-  const FilterUnits p{W, x, B, d, nullptr, nullptr, ks.N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B)};
+  const FilterUnits p{W, x, B, d, nullptr, nullptr, ks.N, h, stride_h, xnorm, wnorm_tiles, nullptr, gather_filter_error(B), 0};
   static std::atomic<size_t> raised_to[9] = {};
   auto go = [&](auto kernel, int tt, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
