@@ -733,7 +733,8 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
 // than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
 // largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
 // Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
-// Measured for 16 rows of 256000, k = 1024, rank order: 20.2 us (4.4 + 9.5 + 6.7); the histogram route below took 45, of it 9 for
+// Measured for 16 rows of 256000, k = 1024, rank order: 18.7 us per call (20.6 with the gathered keys placed by a prefix sum over the
+// threads and the rows' counters in one line: 5.5 us instead of 7.7 inside k_tk_gather); the histogram route below took 45, of it 9 for
 // the ranking pass.
 constexpr int kTkGroups = 4096;
 constexpr int kTkMaxK = 2048;
@@ -742,13 +743,22 @@ constexpr int kTkKeys = 16;  // keys per thread of the gathering kernel
 static_assert(kTkGroups == kWgMaxSlots && kAmbCap == kBucketMax, "the maxima and the list use the histogram route's places");
 static_assert(kTkMaxK * (4 + 2 * 4) <= kAmbCap * (int)sizeof(AmbEntry), "rank order from memory: the list's LDS");
 
+// The lengths of the rows' lists, in the place of the bitmaps that the longer sequence clears for itself: kilobytes apart, as
+// the workgroups of all rows wait for what they add (side by side in one line 1.9 us longer for 16 rows of 256000).
+struct TkCounts {
+  uint32_t* first;
+  int stride;
+  __device__ __forceinline__ uint32_t* of(int b) const { return first + (size_t)b * stride; }
+};
+
 __device__ __forceinline__ uint32_t row_key(float v, int relu) { return order_key(relu && !(v > 0.0f) ? 0.0f : v); }
 
 // Grid (16, B): 256 groups per workgroup, PARTS threads share one.  Also the sequence's first kernel: empties the rows' lists
 // and checks the layout signature.
 template <int PARTS>
 __global__ __launch_bounds__(kTkMaxGroups * PARTS) void k_tk_maxima(const float* __restrict__ keys, int N, int relu,
-                                                             MultiRegion mr, GeneralHeader* gh, unsigned long long sig) {
+                                                             MultiRegion mr, TkCounts cnt, GeneralHeader* gh,
+                                                             unsigned long long sig) {
   constexpr int kStep = PARTS * kTkGroups;
   __shared__ uint32_t part_max[PARTS][kTkMaxGroups];
   if (blockIdx.x == 0 && blockIdx.y == 0) general_header_check(gh, sig);
@@ -772,16 +782,16 @@ __global__ __launch_bounds__(kTkMaxGroups * PARTS) void k_tk_maxima(const float*
 #pragma unroll
   for (int q = 1; q < PARTS; ++q) m = max(m, part_max[q][own]);
   mr.wgmax[(size_t)b * kWgMaxSlots + g] = m;
-  if (g == 0) mr.amb_n[b] = 0u;
+  if (g == 0) *cnt.of(b) = 0u;
 }
 
 // Grid (ceil(N / 16384), B).
 __global__ __launch_bounds__(kSelThreads) void k_tk_gather(const float* __restrict__ keys, int N, int k, int relu,
-                                                           MultiRegion mr) {
+                                                           MultiRegion mr, TkCounts counts) {
   __shared__ SelShared sh;
   __shared__ __align__(16) uint32_t win[kWin];
-  __shared__ int base_sh;
-  const int b = (int)blockIdx.y, tid = (int)threadIdx.x;
+  __shared__ int base_sh, wave_cnt[kSelWaves];
+  const int b = (int)blockIdx.y, tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const float* row = keys + (size_t)b * N;
   const int i0 = (int)blockIdx.x * (kSelThreads * kTkKeys);
   const uint4 mx4 = reinterpret_cast<const uint4*>(mr.wgmax + (size_t)b * kWgMaxSlots)[tid];
@@ -805,40 +815,51 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_gather(const float* __restri
   wr.issue(win);
   const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
   if (!wk.found) {  // uniform
-    if (blockIdx.x == 0 && tid == 0) mr.amb_n[b] = kAmbCap + 1;
+    if (blockIdx.x == 0 && tid == 0) *counts.of(b) = kAmbCap + 1;
     return;
   }
-  const uint32_t bound = max((anchor - (uint32_t)wk.slot) << kFineShift, 1u);  // key 0 stands for "past the end"
-  uint32_t key[kTkKeys];
-  int c = 0;
+  const uint32_t bound = max((anchor - (uint32_t)wk.slot) << kFineShift, 1u);
+  const float bound_f = key_value(bound);
+  // few keys reach the bound: a comparison each, and their order keys decide only where one is not below it (as a NaN is not)
+  if (relu) {  // uniform
+#pragma unroll
+    for (int e = 0; e < kTkKeys; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+  }
+  uint64_t mine[kTkKeys];
+  int cnt = 0;
 #pragma unroll
   for (int e = 0; e < kTkKeys; ++e) {
-    key[e] = i0 + e * kSelThreads + tid < N ? row_key(v[e], relu) : 0u;
-    c += key[e] >= bound ? 1 : 0;
+    const bool in = i0 + e * kSelThreads + tid < N;
+    mine[e] = __ballot(in && !(v[e] < bound_f));
+    if (mine[e] != 0ull) mine[e] = __ballot(in && order_key(v[e]) >= bound);  // uniform
+    cnt += __popcll(mine[e]);
   }
-  int total;
-  const int incl = wg_scan_incl(c, sh, &total);
-  if (total == 0) return;  // uniform
-  if (tid == 0) base_sh = (int)atomicAdd(&mr.amb_n[b], (uint32_t)total);
+  if (lane == 0) wave_cnt[w] = cnt;
   __syncthreads();
-  int at = base_sh + incl - c;
+  const int incl = wave_scan_incl(lane < kSelWaves ? wave_cnt[lane] : 0), total = __builtin_amdgcn_readlane(incl, kSelWaves - 1);
+  if (total == 0) return;  // uniform
+  if (tid == 0) base_sh = (int)atomicAdd(counts.of(b), (uint32_t)total);
+  __syncthreads();
+  int at = base_sh + (w > 0 ? __builtin_amdgcn_readlane(incl, w - 1) : 0);
 #pragma unroll
   for (int e = 0; e < kTkKeys; ++e)
-    if (key[e] >= bound) {
-      if (at < kAmbCap) mr.amb[(size_t)b * kAmbCap + at] = AmbEntry{key[e], i0 + e * kSelThreads + tid};
-      ++at;
+    if (mine[e] != 0ull) {  // uniform
+      const int place = at + mask_prefix(mine[e]);
+      if (((mine[e] >> lane) & 1ull) != 0ull && place < kAmbCap)
+        mr.amb[(size_t)b * kAmbCap + place] = AmbEntry{order_key(v[e]), i0 + e * kSelThreads + tid};
+      at += __popcll(mine[e]);
     }
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restrict__ keys, int B, int N, int k, int relu,
-                                                          int rank_order, MultiRegion mr, int32_t* __restrict__ idx_out,
-                                                          float* __restrict__ val_out) {
+                                                          int rank_order, MultiRegion mr, TkCounts counts,
+                                                          int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
   __shared__ SelShared sh;
   __shared__ __align__(16) uint32_t bins[kHistWindow];
   __shared__ __align__(16) AmbEntry list[kAmbCap];
   __shared__ AmbEntry chosen[kTkMaxK];
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x;
-  const int n = (int)mr.amb_n[b];
+  const int n = (int)*counts.of(b);
   int32_t* idx = idx_out + (size_t)b * k;
   float* val = val_out ? val_out + (size_t)b * k : nullptr;
   if (b == 0 && tid == 0 && !multi_hist_ok(mr.hdr, B)) {  // the workspace has taken this layout
@@ -1457,8 +1478,9 @@ hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, 
                             float* val_out, void* general_header, void* body, unsigned long long sig, hipStream_t s) {
   GeneralHeader* gh = static_cast<GeneralHeader*>(general_header);
   const MultiRegion mr = carve_multi(&gh->multi, body, B);
+  const TkCounts counts{reinterpret_cast<uint32_t*>(static_cast<char*>(body) + multi_body_bytes(B)), (N + 31) / 32 + 2};
   auto maxima = [&](auto kernel, int parts) {
-    return launch(kernel, dim3(kTkGroups / kTkMaxGroups, B), dim3(kTkMaxGroups * parts), 0, s, scores, N, relu, mr, gh, sig);
+    return launch(kernel, dim3(kTkGroups / kTkMaxGroups, B), dim3(kTkMaxGroups * parts), 0, s, scores, N, relu, mr, counts, gh, sig);
   };
   // as many threads per group as have sixteen entries each: one round of loads.  16 rows of 256000: 18.0, 17.0, 16.9 us for the
   // three kernels with one, two, four; of 131072: 15.1, 14.8, 15.3; of 40000: 13.6, 13.6, 14.2
@@ -1466,8 +1488,8 @@ hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, 
                                     : (N > 16 * kTkGroups ? maxima(k_tk_maxima<2>, 2) : maxima(k_tk_maxima<1>, 1));
   if (e != hipSuccess) return e;
   const int chunks = (N + kSelThreads * kTkKeys - 1) / (kSelThreads * kTkKeys);
-  if ((e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr)) != hipSuccess) return e;
-  return launch(k_tk_final, dim3(B), dim3(kSelThreads), 0, s, scores, B, N, k, relu, rank_order, mr, idx_out, val_out);
+  if ((e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr, counts)) != hipSuccess) return e;
+  return launch(k_tk_final, dim3(B), dim3(kSelThreads), 0, s, scores, B, N, k, relu, rank_order, mr, counts, idx_out, val_out);
 }
 
 size_t topk_long_workspace_bytes(int B, int N) {
