@@ -445,26 +445,19 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
 #pragma unroll
       for (int i = 0; i < TI; ++i) load_to_lds(xptr[i] + off, to_tok + 1024 * NW * i);
     };
-    // the stages in turn from `at` on, round the end of the row
-    auto run = [&](auto turned, int at) __attribute__((always_inline)) {
-      int next = at;
-      auto forward = [&](int st) { return turned() && st + 1 == nst ? 0 : st + 1; };
+    // the stages in order, or (TURNED) from stage `from` on round the end of the row
+    auto run = [&](auto turned, int from) __attribute__((always_inline)) {
+      constexpr bool TURNED = decltype(turned)::value;
+      auto stage_of = [&](int st) { return !TURNED ? st : (st + from < nst ? st + from : st + from - nst); };
 #pragma unroll
       for (int st = 0; st < kFtStages - 1; ++st)
-        if (st < nst) {
-          request(next, st);
-          next = forward(next);
-        }
+        if (st < nst) request(stage_of(st), st);
       int slot = 0;
       for (int st = 0; st < nst; ++st) {
         stage_barrier_loads<CI, TI>(ci, st + kFtStages - 2 < nst);
-        if (st + kFtStages - 1 < nst) {
-          request(next, slot == 0 ? kFtStages - 1 : slot - 1);
-          next = forward(next);
-        }
+        if (st + kFtStages - 1 < nst) request(stage_of(st + kFtStages - 1), slot == 0 ? kFtStages - 1 : slot - 1);
         if (16 * cw < c)  // uniform
-          ft_stage<TT, TG, KS>(lds + slot * kStage, cw, tt0, kh, cpr - kFtChunks * at, true, acc);
-        at = forward(at);
+          ft_stage<TT, TG, KS>(lds + slot * kStage, cw, tt0, kh, cpr - kFtChunks * stage_of(st), true, acc);
         slot = slot == kFtStages - 1 ? 0 : slot + 1;
       }
     };
