@@ -835,9 +835,11 @@ static bool sm1_worthwhile(int N, int kprime, int n_max, int kpt) {
   const double q = (double)kprime / n_max;
   const double mean = -(double)n_max * std::log1p(-q) / n_wg;  // superset entries per workgroup
   if (mean >= c) return false;
-  // P(X > c) for X ~ Poisson(mean): terms c + 1, c + 2, ... in log space
-  double tail = 0.0;
-  for (int j = c + 1; j < c + 400; ++j) tail += std::exp(j * std::log(mean) - mean - std::lgamma(j + 1.0));
+  // P(X > c) for X ~ Poisson(mean): term c + 1 in log space, every further one mean / j times the one before, and fewer than half
+  // a bit of the sum once they are small (400 terms in log space took the host 10 us: a step that
+  // is waited for 47.9 us, now 40.0, for one token on 60000 classes of d = 704, 72.2 and 66.4 for six of rank 96)
+  double term = std::exp((c + 1) * std::log(mean) - mean - std::lgamma(c + 2.0)), tail = term;
+  for (int j = c + 2; j < c + 400 && term > 0x1p-54 * tail; ++j) tail += term *= mean / j;
   return tail * n_wg < 1e-4;
 }
 bool softmax_b1_worthwhile(int N, int kprime, int n_max) { return sm1_worthwhile(N, kprime, n_max, kSm1KeysPerThread); }
