@@ -135,6 +135,9 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
       for (int at = 0; at < TPW; ++at) {
         const int q = at % kAhead, t = w + at * NW;
         if (at > 0 && q == 0) load_values(at);
+        // uniform; what LDS holds in the place of tokens beyond the batch reaches no result (17 tokens of 2048 values, 16384 rows
+        // 58.0 -> 55.9 us per step, 5 of 800, 5003 rows 28.7 -> 28.0, against quantising the last token in their place)
+        if (t >= B) continue;
         float amax = 0.0f;
 #pragma unroll
         for (int m = 0; m < VECS; ++m) {
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
         for (int m = 0; m < VECS; ++m)
           if (m * kWave < 2 * segq) {  // uniform
             const int i = m * kWave + lane;
-            const bool counts = t < B && i < nvec;
+            const bool counts = i < nvec;
             float sum8;
             const uint2 codes = quantise8(tv[q][m], ts, &sum8);
             sabs += counts ? sum8 : 0.0f;
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
           }
         if (p.tok.sumabs != nullptr && blockIdx.x == 0) {
           sabs = wave_sum(sabs);
-          if (lane == 0 && t < B) p.tok.sumabs[t] = sabs;
+          if (lane == 0) p.tok.sumabs[t] = sabs;
         }
       }
     }
@@ -346,14 +349,17 @@ static int vocab_blocks(int N) { return min((N + 16 * kVocabWaves - 1) / (16 * k
 int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 
 // Where quantising in every workgroup is cheaper than a kernel in front (3.6 to 4.8 us, and the boundary behind it, 1.5 to 2.5): up
-// to 32 tokens of 2048 values, a wave then has one or two, or 64 of 512.  d = 2048, 16384 rows: 16 tokens 8.4 against 3.8 + 7.4
+// to 32 tokens of 2048 values, a wave then has one or two, 40 of 1024, where half of the waves have a third, or 64 of 512.
+// d = 2048, 16384 rows: 16 tokens 8.4 against 3.8 + 7.4
 // us, 32 tokens 11.9 against 4.1 + 8.0; 32000 rows, 32 tokens 14.8 against 4.7 + 9.7; d = 512, 3600 rows, 64 tokens 8.6 against
-// 3.6 + 5.9, 20184 rows, 32 tokens 7.4 against 4.4 + 5.7.  Beyond (33 tokens of 800 values, 5003 rows: 12.2 against 3.8 + 5.8) a
-// wave has four long tokens, one after the other.  The intermediate of the int4 low-rank scorer is short (r <= 1024), and a
-// rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight waves would take as long as the kernel in front.
+// 3.6 + 5.9, 20184 rows, 32 tokens 7.4 against 4.4 + 5.7.  us per step: 33 tokens of 1024, 16384 rows 47.3 against 48.7, of 800, 5003
+// rows 36.3 against 36.6, 40 of 1024, 4000 rows 31.9 against 31.8.  Beyond (48 of 800: 39.4 against 38.5; 64 of 1024, 16384 rows 52.0
+// against 50.8) a wave has three or four long tokens, one after the other.  The intermediate of the int4 low-rank scorer is short
+// (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight waves would take as long as the
+// kernel in front.
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
   if (N >= kVocabMinRows) return false;
-  return f32 ? d <= 1024 : d <= (B <= 32 ? 2048 : 512);
+  return f32 ? d <= 1024 : d <= (B <= 32 ? 2048 : (B <= 40 ? 1024 : 512));
 }
 
 template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
@@ -396,6 +402,8 @@ static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
   if (p.tok.x == nullptr) return scorer_mfma_rows<CT, 2, kCodes, 2>(p, s);
   if (p.tok.f32) return p.d <= 512 ? scorer_mfma_rows<CT, 2, kF32, 1>(p, s) : scorer_mfma_rows<CT, 2, kF32, 2>(p, s);
   if (p.d <= 512) return scorer_mfma_rows<CT, 2, kBf16, 1>(p, s);
+  if constexpr (CT == 4)
+    if (p.d <= 1024) return scorer_mfma_rows<CT, 2, kBf16, 2>(p, s);
   if constexpr (CT <= 2) return p.d <= 1024 ? scorer_mfma_rows<CT, 2, kBf16, 2>(p, s) : scorer_mfma_rows<CT, 4, kBf16, 4>(p, s);
   return hipErrorInvalidValue;
 }
