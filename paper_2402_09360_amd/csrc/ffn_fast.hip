@@ -700,16 +700,23 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   const uint32_t bin = anchor1 - (uint32_t)wk.slot;
   const bool found = wk.found && bin >= 1u && bin <= anchor1;  // uniform
   bool known = false;  // which of the workgroup's units are shortlisted is
-  RowChunks first;
-  int pos = 0;         // the wave's row (unit of the workgroup)
-  const uint4* row = nullptr;
-  // the r-th unit of `rows`, and its first loads
-  auto aim = [&](int r) {
-    pos = __builtin_ctzll(__ballot(((rows >> lane) & 1ull) != 0ull && mask_prefix(rows) == r));
-    row = reinterpret_cast<const uint4*>(p.W1 + (size_t)(u0 + pos) * p.d);
-    first.issue(row, 0, xvecs);
+  int cnt = 0;         // rows
+  // a row of the wave: unit of the workgroup, address, first loads.  A wave has one or two, and those of both go out at once: every
+  // eighth workgroup has more than sixteen rows, and a second trip would make it the last to end (1.4 us behind the others)
+  struct Row {
+    int pos;
+    const uint4* row;
+    RowChunks first;
+  } wave_row[2];
+  auto aim = [&](Row& a, int r) {  // the r-th unit of `rows`
+    a.pos = __builtin_ctzll(__ballot(((rows >> lane) & 1ull) != 0ull && mask_prefix(rows) == r));
+    a.row = reinterpret_cast<const uint4*>(p.W1 + (size_t)(u0 + a.pos) * p.d);
+    a.first.issue(a.row, 0, xvecs);
   };
-  int cnt = 0;
+  auto aim_both = [&](int r) {
+    if (r < cnt) aim(wave_row[0], r);
+    if (r + kGW < cnt) aim(wave_row[1], r + kGW);
+  };
   // The keys have arrived by now.  Said to the compiler here, before the rows' loads go out: where paths with and without
   // those meet, it would otherwise wait for the youngest loads, the rows, wherever a key is used.
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -719,7 +726,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
     const uint64_t open = __ballot(valid && own >= lo && own < up);
     rows = taken | open;
     cnt = __popcll(rows);
-    if (w < cnt) aim(w);
+    aim_both(w);
     __builtin_amdgcn_sched_barrier(0);  // the rows' loads are not sunk below what follows
     if (open != 0ull) {                 // uniform over the workgroup
       list_inside<K>(kr, bin_masks<K>(kr, lo, up).inside, &sh.list_n, list);
@@ -749,24 +756,29 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   if (!found) {
     rows = taken;
     cnt = __popcll(rows);
-    if (w < cnt) aim(w);
+    aim_both(w);
   }
   HIRE_TS(13);
   auto count_h = [&](double v) {  // the scorer kernel of this step has cleared the window
     count_in_window<false>((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
   };
   if (!found) __syncthreads();  // the token in LDS
-  for (int r = w; r < cnt; r += kGW) {  // uniform over the wave; one trip for most
-    if (r > w) aim(r);
-    const double s = row_dot_relu(row, first, xtok, xvecs);
-    const bool in = ((taken >> pos) & 1ull) != 0ull;
-    if (lane == 0) {
-      if (gs != 0) {
-        unit_h[pos] = s;
-      } else {
-        p.h32[u0 + pos] = in ? (float)s : 0.0f;
-        p.h64[u0 + pos] = in ? s : -1.0;
-        if (in) count_h(s);
+  for (int r = w; r < cnt; r += 2 * kGW) {  // uniform over the wave; one trip for nearly all
+    if (r > w) aim_both(r);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (r + u * kGW >= cnt) break;
+      const int pos = wave_row[u].pos;
+      const double s = row_dot_relu(wave_row[u].row, wave_row[u].first, xtok, xvecs);
+      const bool in = ((taken >> pos) & 1ull) != 0ull;
+      if (lane == 0) {
+        if (gs != 0) {
+          unit_h[pos] = s;
+        } else {
+          p.h32[u0 + pos] = in ? (float)s : 0.0f;
+          p.h64[u0 + pos] = in ? s : -1.0;
+          if (in) count_h(s);
+        }
       }
     }
   }

@@ -53,3 +53,18 @@ def test_many_units_in_the_threshold_bins(oracle, B, group, distinct):
         assert np.array_equal(got["cand"], want["cand"]) and np.array_equal(got["topk_group"], want["topk_group"])
         T.assert_float_close(got["topk_val"], want["topk_val"], "topk_val")
         T.assert_float_close(got["y"], want["y"], "y")
+
+
+@pytest.mark.parametrize("d,N,kp,kind", [(96, 1030, 1030, "int4"), (2080, 700, 350, "int4"), (256, 1000, 300, "lowrank"),
+                                         (256, 4100, 2050, "lrq")])
+def test_one_token_many_rows_per_workgroup(oracle, d, N, kp, kind):
+    """One token whose workgroups have up to all of their 64 units to read: one to four rows per wave."""
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    k = kp // 3
+    L = I.ffn_layer(741, d, N) if kind == "int4" else I.lowrank_ffn_layer(742, d, N, 32)
+    layer, scorer = T.make_ffn_layer(L, lowrank=kind == "lowrank", lrq=kind == "lrq")
+    print(f"one token, d={d} N={N} k'={kp} {kind}", flush=True)
+    x = I.tokens(743, 1, d)
+    want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
+    for got in T.run_ffn(layer, x, k, kp, steps=3, debug=False):
+        T.compare_ffn(got, dict(want, acc=None))
