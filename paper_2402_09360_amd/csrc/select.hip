@@ -733,8 +733,8 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
 // than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
 // largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
 // Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
-// Measured for 16 rows of 256000, k = 1024, rank order: 18.7 us per call (20.6 with the gathered keys placed by a prefix sum over the
-// threads and the rows' counters in one line: 5.5 us instead of 7.7 inside k_tk_gather); the histogram route below took 45, of it 9 for
+// Measured for 16 rows of 256000, k = 1024, rank order: 18.9 us per call (20.6 with the lengths of all rows' lists in one
+// line); the histogram route below took 45, of it 9 for
 // the ranking pass.
 constexpr int kTkGroups = 4096;
 constexpr int kTkMaxK = 2048;
@@ -790,8 +790,8 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_gather(const float* __restri
                                                            MultiRegion mr, TkCounts counts) {
   __shared__ SelShared sh;
   __shared__ __align__(16) uint32_t win[kWin];
-  __shared__ int base_sh, wave_cnt[kSelWaves];
-  const int b = (int)blockIdx.y, tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  __shared__ int base_sh;
+  const int b = (int)blockIdx.y, tid = (int)threadIdx.x;
   const float* row = keys + (size_t)b * N;
   const int i0 = (int)blockIdx.x * (kSelThreads * kTkKeys);
   const uint4 mx4 = reinterpret_cast<const uint4*>(mr.wgmax + (size_t)b * kWgMaxSlots)[tid];
@@ -818,36 +818,25 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_gather(const float* __restri
     if (blockIdx.x == 0 && tid == 0) *counts.of(b) = kAmbCap + 1;
     return;
   }
-  const uint32_t bound = max((anchor - (uint32_t)wk.slot) << kFineShift, 1u);
-  const float bound_f = key_value(bound);
-  // few keys reach the bound: a comparison each, and their order keys decide only where one is not below it (as a NaN is not)
-  if (relu) {  // uniform
-#pragma unroll
-    for (int e = 0; e < kTkKeys; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-  }
-  uint64_t mine[kTkKeys];
-  int cnt = 0;
+  const uint32_t bound = max((anchor - (uint32_t)wk.slot) << kFineShift, 1u);  // key 0 stands for "past the end"
+  uint32_t key[kTkKeys];
+  int c = 0;
 #pragma unroll
   for (int e = 0; e < kTkKeys; ++e) {
-    const bool in = i0 + e * kSelThreads + tid < N;
-    mine[e] = __ballot(in && !(v[e] < bound_f));
-    if (mine[e] != 0ull) mine[e] = __ballot(in && order_key(v[e]) >= bound);  // uniform
-    cnt += __popcll(mine[e]);
+    key[e] = i0 + e * kSelThreads + tid < N ? row_key(v[e], relu) : 0u;
+    c += key[e] >= bound ? 1 : 0;
   }
-  if (lane == 0) wave_cnt[w] = cnt;
-  __syncthreads();
-  const int incl = wave_scan_incl(lane < kSelWaves ? wave_cnt[lane] : 0), total = __builtin_amdgcn_readlane(incl, kSelWaves - 1);
+  int total;
+  const int incl = wg_scan_incl(c, sh, &total);
   if (total == 0) return;  // uniform
   if (tid == 0) base_sh = (int)atomicAdd(counts.of(b), (uint32_t)total);
   __syncthreads();
-  int at = base_sh + (w > 0 ? __builtin_amdgcn_readlane(incl, w - 1) : 0);
+  int at = base_sh + incl - c;
 #pragma unroll
   for (int e = 0; e < kTkKeys; ++e)
-    if (mine[e] != 0ull) {  // uniform
-      const int place = at + mask_prefix(mine[e]);
-      if (((mine[e] >> lane) & 1ull) != 0ull && place < kAmbCap)
-        mr.amb[(size_t)b * kAmbCap + place] = AmbEntry{order_key(v[e]), i0 + e * kSelThreads + tid};
-      at += __popcll(mine[e]);
+    if (key[e] >= bound) {
+      if (at < kAmbCap) mr.amb[(size_t)b * kAmbCap + at] = AmbEntry{key[e], i0 + e * kSelThreads + tid};
+      ++at;
     }
 }
 
@@ -1488,7 +1477,8 @@ hipError_t launch_topk_rows(const float* scores, int B, int N, int k, int relu, 
                                     : (N > 16 * kTkGroups ? maxima(k_tk_maxima<2>, 2) : maxima(k_tk_maxima<1>, 1));
   if (e != hipSuccess) return e;
   const int chunks = (N + kSelThreads * kTkKeys - 1) / (kSelThreads * kTkKeys);
-  if ((e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr, counts)) != hipSuccess) return e;
+  e = launch(k_tk_gather, dim3(chunks, B), dim3(kSelThreads), 0, s, scores, N, k, relu, mr, counts);
+  if (e != hipSuccess) return e;
   return launch(k_tk_final, dim3(B), dim3(kSelThreads), 0, s, scores, B, N, k, relu, rank_order, mr, counts, idx_out, val_out);
 }
 

@@ -1,6 +1,6 @@
-"""The bare selection on long rows: its gathering kernel compares floats and goes by the order keys only where one is not below
-the bound.  Values that a comparison of floats does not order (NaN), equal ones in their hundreds, masks of the lowest value,
-rows that end inside a workgroup's part, one row and many."""
+"""The bare selection on long rows, whose lists' lengths lie in the place of the longer sequence's bitmaps.  Values that a
+comparison of floats does not order (NaN), equal ones in their hundreds, masks of the lowest value, rows that end inside a
+workgroup's part, one row and many; then the longer sequence on the same workspace."""
 import numpy as np
 import pytest
 import torch
@@ -31,11 +31,12 @@ def test_long_rows_with_values_of_all_kinds(B, N, k, relu):
     order = np.lexsort((np.broadcast_to(np.arange(N), v.shape), ~keys), axis=1)[:, :k]
     scores = torch.from_numpy(v).cuda()
     flags = (hire.RELU if relu else 0) | hire.ORDER_RANK
-    ws = hire.alloc_workspace(hire.hire_topk_workspace_bytes(B, N, k, flags))
-    for rank in (True, False):
-        for _ in range(2):
-            idx, val = hire.topk_select(scores, k, relu=relu, rank_order=rank, workspace=ws)
-            want = order if rank else np.sort(order, axis=1)
-            assert np.array_equal(idx.cpu().numpy(), want)
-            got = val.cpu().numpy()
-            assert np.array_equal(_order_keys(got), np.take_along_axis(keys, want, axis=1))
+    ws = hire.alloc_workspace(max(hire.hire_topk_workspace_bytes(B, N, kk, flags) for kk in (k, 2049)))
+    long_order = np.lexsort((np.broadcast_to(np.arange(N), v.shape), ~keys), axis=1)[:, :2049]  # (k > 2048: with bitmaps)
+    for kk, first in ((k, order), (2049, long_order), (k, order)):
+        for rank in (True, False):
+            for _ in range(2):
+                idx, val = hire.topk_select(scores, kk, relu=relu, rank_order=rank, workspace=ws)
+                want = first if rank else np.sort(first, axis=1)
+                assert np.array_equal(idx.cpu().numpy(), want)
+                assert np.array_equal(_order_keys(val.cpu().numpy()), np.take_along_axis(keys, want, axis=1))
