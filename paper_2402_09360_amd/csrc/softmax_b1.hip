@@ -295,7 +295,7 @@ struct Sm1Shared {
   unsigned long long sel_key[kSm1MaxK];  // the k selected (logit as order key, class), unordered
   int32_t sel_idx[kSm1MaxK];
   double sel_z[kSm1MaxK];                // their logits in rank order
-  double wave_lo[kSm1Waves], wave_hi[kSm1Waves];
+  float wave_lo[kSm1Waves], wave_hi[kSm1Waves];
   int wave_cnt[kSm1Waves];
   int amb_n, zamb_n, sel_n;
 };
@@ -358,6 +358,23 @@ __device__ __noinline__ void sm1_shortlist_from_keys(const float* __restrict__ k
   __syncthreads();
 }
 
+// The entries of the bin that holds the D-th smallest key, listed in LDS: the order in which they go is ascending in
+// sm1_drop_order (smaller key, or the same key at a higher class).  `listed`: this lane's list entry, all ones beyond the list.
+// Of a round's entries in the bin (mask over the lanes), those that are among the first `need` of the list.  A wave has two or
+// three of them and asks for these by ballots; comparing them thread by thread with the whole list took as many turns for every
+// round of a wave that has any (2.7 us instead of 0.5 at 256000 classes).
+static_assert(kSm1AmbCap <= kWave, "an entry of the list per lane");
+__device__ __forceinline__ uint64_t sm1_drop_order(uint32_t okey, int32_t idx) { return (uint64_t)okey << 32 | (uint32_t)~idx; }
+__device__ __forceinline__ uint64_t sm1_dropped(uint64_t in_bin, uint32_t okey, int32_t idx, uint64_t listed, int need) {
+  uint64_t gone = 0ull;
+  for (uint64_t o = in_bin; o != 0ull; o &= o - 1ull) {  // uniform
+    const int l = __builtin_ctzll(o);
+    const uint64_t v = sm1_drop_order((uint32_t)__builtin_amdgcn_readlane((int)okey, l), __builtin_amdgcn_readlane(idx, l));
+    if ((int)__popcll(__ballot(listed < v)) < need) gone |= 1ull << l;
+  }
+  return gone;
+}
+
 __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restrict__ keys, int N, int d, int k,
                                                            int kprime, const uint16_t* __restrict__ W,
                                                            const uint16_t* __restrict__ x, MultiRegion mr,
@@ -404,26 +421,28 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
   }
   const uint32_t bin_lb = okey_lb >> kHistShift;
   int rel[E];
-  auto logit_range = [&](double& lo, double& hi) {  // over the kept entries, to all threads
+  // Of the kept entries, to all threads.  Rounded to fp32: the range only places the bins, and what lies outside counts in the
+  // first or the last of them.
+  auto logit_range = [&](float& lo, float& hi) {
     lo = INFINITY;
     hi = -INFINITY;
 #pragma unroll
     for (int j = 0; j < E; ++j)
       if ((keep >> j) & 1u) {
-        lo = fmin(lo, z[j]);
-        hi = fmax(hi, z[j]);
+        lo = fminf(lo, (float)z[j]);
+        hi = fmaxf(hi, (float)z[j]);
       }
-    auto lower = [](double a, double b) { return fmin(a, b); };
-    auto upper = [](double a, double b) { return fmax(a, b); };
-    lo = read_lane63(wave_prefix(lo, (double)INFINITY, lower));
-    hi = read_lane63(wave_prefix(hi, (double)-INFINITY, upper));
+    auto lower = [](float a, float b) { return fminf(a, b); };
+    auto upper = [](float a, float b) { return fmaxf(a, b); };
+    lo = read_lane63(wave_prefix(lo, (float)INFINITY, lower));
+    hi = read_lane63(wave_prefix(hi, (float)-INFINITY, upper));
     if (lane == 0) {
       sh.wave_lo[w] = lo;
       sh.wave_hi[w] = hi;
     }
     __syncthreads();
-    lo = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_lo[lane] : (double)INFINITY, (double)INFINITY, lower));
-    hi = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_hi[lane] : (double)-INFINITY, (double)-INFINITY, upper));
+    lo = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_lo[lane] : (float)INFINITY, (float)INFINITY, lower));
+    hi = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_hi[lane] : (float)-INFINITY, (float)-INFINITY, upper));
   };
 #pragma unroll
   for (int j = 0; j < E; ++j) {
@@ -435,7 +454,7 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
     const bool wave_over = __ballot(over) != 0ull;
     if (lane == 0) sh.wave_cnt[w] = wave_over ? -1 : c;
   }
-  double z_lo, z_hi;
+  float z_lo, z_hi;
   logit_range(z_lo, z_hi);  // its barrier publishes the counts and the bins as well
   int n_s = 0;
   bool direct = !answered;  // uniform
@@ -447,14 +466,15 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
   }
   HIRE_TS(31);
   // logit bins: linear in the logit between the smallest and the largest, hence monotone
-  double z_scale = z_hi > z_lo ? (double)(kSm1ZBins - 1) / (z_hi - z_lo) : 0.0;
+  auto bins_per_logit = [&]() { return z_hi > z_lo ? (double)fminf((float)(kSm1ZBins - 1) / (z_hi - z_lo), 3e38f) : 0.0; };
+  double z_scale = bins_per_logit();
   int zbin[E];
   auto count_logits = [&]() {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       zbin[j] = -1;
       if ((keep >> j) & 1u) {
-        zbin[j] = min(max((int)((z[j] - z_lo) * z_scale), 0), kSm1ZBins - 1);
+        zbin[j] = min(max((int)((z[j] - (double)z_lo) * z_scale), 0), kSm1ZBins - 1);
         atomicAdd(&sh.z_hist[zbin[j]], 1u);
       }
     }
@@ -505,25 +525,11 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
       if (m > kSm1AmbCap) {  // uniform
         direct = true;
       } else {
+        const uint64_t listed = lane < m ? sm1_drop_order(sh.amb_key[lane], sh.amb_idx[lane]) : ~0ull;
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          bool goes = rel[j] < beta;
-          if (rel[j] == beta) {
-            int lower = 0;  // entries of the bin that go first: smaller key, or the same key at a higher index
-            for (int u0 = 0; u0 < m; u0 += 8) {  // eight LDS reads in flight
-              uint32_t ok[8];
-              int32_t oi[8];
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                ok[q] = sh.amb_key[min(u0 + q, kSm1AmbCap - 1)];
-                oi[q] = sh.amb_idx[min(u0 + q, kSm1AmbCap - 1)];
-              }
-#pragma unroll
-              for (int q = 0; q < 8; ++q)
-                lower += u0 + q < m && (ok[q] < okey[j] || (ok[q] == okey[j] && oi[q] > idx[j]));
-            }
-            goes = lower < need_drop;
-          }
+          const uint64_t gone = sm1_dropped(__ballot(rel[j] == beta), okey[j], idx[j], listed, need_drop);
+          const bool goes = rel[j] < beta || ((gone >> lane) & 1ull) != 0ull;
           if (goes) {
             keep &= ~(1u << j);
             atomicSub(&sh.z_hist[zbin[j]], 1u);
@@ -556,7 +562,7 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
       }
     }
     logit_range(z_lo, z_hi);  // its barrier: the list has been read by everybody (its memory is reused below)
-    z_scale = z_hi > z_lo ? (double)(kSm1ZBins - 1) / (z_hi - z_lo) : 0.0;
+    z_scale = bins_per_logit();
     count_logits();
   }
   __syncthreads();
@@ -787,25 +793,11 @@ __global__ __launch_bounds__(kSm1Threads) void k_max_resolve(const float* __rest
       if (m > kSm1AmbCap) {  // uniform
         direct = true;
       } else {
+        const uint64_t listed = lane < m ? sm1_drop_order(sh.amb_key[lane], sh.amb_idx[lane]) : ~0ull;
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          bool goes = rel[j] < beta;
-          if (rel[j] == beta) {
-            int lower = 0;  // entries of the bin that go first: smaller key, or the same key at a higher index
-            for (int u0 = 0; u0 < m; u0 += 8) {
-              uint32_t ok[8];
-              int32_t oi[8];
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                ok[q] = sh.amb_key[min(u0 + q, kSm1AmbCap - 1)];
-                oi[q] = sh.amb_idx[min(u0 + q, kSm1AmbCap - 1)];
-              }
-#pragma unroll
-              for (int q = 0; q < 8; ++q)
-                lower += u0 + q < m && (ok[q] < okey[j] || (ok[q] == okey[j] && oi[q] > idx[j]));
-            }
-            goes = lower < need_drop;
-          }
+          const uint64_t gone = sm1_dropped(__ballot(rel[j] == beta), okey[j], idx[j], listed, need_drop);
+          const bool goes = rel[j] < beta || ((gone >> lane) & 1ull) != 0ull;
           if (((keep >> j) & 1u) && !goes) atomicOr(&bitmap[idx[j] >> 5], 1u << (idx[j] & 31));
         }
       }
