@@ -586,9 +586,9 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
 // where a unit is not shortlisted), so no list of candidates is needed in between; the caller's is written beside
 // kernel 3 (a 257th workgroup here would wait for a compute unit).  K: the keys' bit patterns, 32 bits for the int4
 // scorer's fp32 keys, 64 for the low-rank scorer's fp64 ones; LOADS: 16-byte loads of keys per thread.
-// Measured at the ~1B shape: 7.9 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
-// its rows.  Inside: 1.8 until the window is walked, 1.3 to 2 for the rows; workgroups that own a key of the threshold bin
-// need 1.6 more for its list and are the last to end.
+// Measured at the ~1B shape: 7.8 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
+// its rows.  Inside: 2.3 until the window is walked, 0.5 until the rows are known, 1.3 for the rows; workgroups that own a
+// key of the threshold bin need 1.6 more for its list and are the last to end.
 constexpr int kGT = 1024;
 constexpr int kGW = kGT / kWave;
 using GatherShared = SelSharedT<kGT>;
@@ -817,8 +817,9 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
 //
 // The selection works on the activations rounded to fp32 (rounding is monotone; the coefficients of the second layer are
 // these values anyway); the keys of the threshold bin, and a selection without histogram, go by the fp64 values.
-// Measured at the ~1B shape: 9.0 us with the reduction over the waves and the shortlist's list in it.  Inside: window
-// walked 1.5, masks 0.7, bin settled 0.6, rows listed 0.5, rows 2.8, reduction 0.8.
+// Measured at the ~1B shape: 8.1 us with the reduction over the waves and the lists for the caller in it (9.0 with the lists'
+// keys placed by code unrolled over all of a lane's, whose workgroups were the last to end).  Inside: window walked 1.6,
+// masks 0.6, bin settled 0.5, rows listed 0.5, rows 1.0 (from HBM 2.8), reduction 1.0.
 constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
 using W2Shared = SelSharedT<kWT>;
@@ -1341,9 +1342,9 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     // The narrowest slices whose workgroups fit the compute units, one each: what is left over would wait for a whole
     // workgroup's time (registers do not admit two).  Two workgroups more per token write the selected entries and the
     // shortlist; where slices of half the width fit without them, the slices' workgroups do it for groups of eight (four tokens
-    // of d = 2048 with 2736 dense units: 39.2 us per step against 40.4, eight: 52.8 against 58.3).  Not for units: the code
-    // that places the selected keys of sixteen loads comes cold and costs the slices' workgroups 3 us (four tokens at the ~1B
-    // shape 43.7 against 40.4).
+    // of d = 2048 with 2736 dense units: 39.2 us per step against 40.4, eight: 52.8 against 58.3).  Not for units: four tokens at
+    // the ~1B shape take 36.0 us instead of 37.9 where one layer is run again and again, but 38.2 instead of 37.9 where its
+    // rows come from HBM.
     const int extra = (a.topk_idx || a.topk_val ? 1 : 0) + (a.cand_out || (several && a.n_cand) ? 1 : 0);
     int cols = 32, cols_alone = 32;  // with the extra workgroups, without
     while (cols < 128 && ((a.d + cols - 1) / cols + extra) * a.B > 256) cols *= 2;

@@ -21,7 +21,8 @@ constexpr int kTokRows = 64;  // rows of a workgroup of the scorer
 // token l % 4 from lane l and adds up sixteen blocks of columns l / 4 separately, so that a load covers 256 bytes of
 // four adjacent rows and a wave's loads one piece of memory.  At the ~1B shape and four tokens 5.9 us until the
 // keys are stored, and 1.3 more than a kernel boundary takes until the 33000 counts have reached memory (4.5 with the
-// counters of adjacent bins side by side, see spread_slot); 3.3 more with the quantisation in front.
+// counters of adjacent bins side by side, see spread_slot); 3.3 more with the quantisation in front.  The kernel 8.5 us (12.0
+// with the counters side by side).
 // TT: tokens rounded up to four or eight; VECS: 16-byte vectors of a token per thread.  LRQ: as in k_fast_score_int4.
 struct FastScoreTokens {
   const uint4* q4;
@@ -287,7 +288,7 @@ __device__ __forceinline__ Cut<K> streaming_cut(const K* keys, int n, int k, Sel
 // K: the keys' bit patterns.  TT: tokens rounded up to four or eight.
 // Measured at the ~1B shape and four tokens, from the first wave's start: 4.2 us until the rows are known, the 9600 rows of the
 // union until 13.2 (40 MB, 4.5 TB/s), 1.2 for the outputs; half the workgroups have ended by 14.3 and the last by 17.6, one
-// that has two keys of threshold bins to settle (19.8 when they were settled ahead of the rows).
+// that has two keys of threshold bins to settle (19.8 when they were settled ahead of the rows).  The kernel 17.7 us (20.1).
 template <typename K, int TT>
 __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) {
   constexpr int kWPT = kTW / TT, kChunks = kWin / 256, kMine = kChunks / kWPT;  // 256 counters per wave and load

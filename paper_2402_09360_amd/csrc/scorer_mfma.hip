@@ -39,7 +39,7 @@ enum ScorerSource { kCodes, kBf16, kF32 };
 // staging of the tokens, the unpacking and the epilogue are each a sixteenth of the work: the kernel is bound by that chain
 // and not by memory.  In steps whose weights come from HBM, averages under rocprofv3 (as all times here): d = 2048, 16384 rows,
 // 16 / 32 / 64 tokens 7.4 / 8.0 / 9.5 us, where a workgroup of four waves with whole rows each took 8.9 / 12.5 / 13.4; 5003 rows
-// of 800 codes, 33 tokens 5.8, 10.8.
+// of 800 codes, 33 tokens 5.8, 10.8 (7.9 with the quantisation in it, against 5.5 + 3.6 and a kernel boundary).
 //
 // KW = 1 (vocabularies): a workgroup of eight waves per compute unit stages the tokens once and runs on from tile to tile,
 // the next request always out ahead of the current product.  No load there sits behind a branch: the wait for one request
