@@ -702,20 +702,24 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   bool known = false;  // which of the workgroup's units are shortlisted is
   int cnt = 0;         // rows
   // a row of the wave: unit of the workgroup, address, first loads.  A wave has one or two, and those of both go out at once: every
-  // eighth workgroup has more than sixteen rows, and a second trip would make it the last to end (1.4 us behind the others)
+  // eighth workgroup has more than sixteen rows, and a second trip would make it the last to end (1.4 us behind the others).  One
+  // load of keys per thread: groups of eight, whose rows come by eights and whose second trips are not the last to end (the ~1B
+  // shape's 22.1 us per step with one row at a time, 22.7 with two, with 2736 dense units 28.8 and 29.2), or few units.
+  constexpr int kRows = LOADS == 1 ? 1 : 2;
   struct Row {
     int pos;
     const uint4* row;
     RowChunks first;
-  } wave_row[2];
+  } wave_row[kRows];
   auto aim = [&](Row& a, int r) {  // the r-th unit of `rows`
     a.pos = __builtin_ctzll(__ballot(((rows >> lane) & 1ull) != 0ull && mask_prefix(rows) == r));
     a.row = reinterpret_cast<const uint4*>(p.W1 + (size_t)(u0 + a.pos) * p.d);
     a.first.issue(a.row, 0, xvecs);
   };
-  auto aim_both = [&](int r) {
-    if (r < cnt) aim(wave_row[0], r);
-    if (r + kGW < cnt) aim(wave_row[1], r + kGW);
+  auto aim_all = [&](int r) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (r + u * kGW < cnt) aim(wave_row[u], r + u * kGW);
   };
   // The keys have arrived by now.  Said to the compiler here, before the rows' loads go out: where paths with and without
   // those meet, it would otherwise wait for the youngest loads, the rows, wherever a key is used.
@@ -726,7 +730,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
     const uint64_t open = __ballot(valid && own >= lo && own < up);
     rows = taken | open;
     cnt = __popcll(rows);
-    aim_both(w);
+    aim_all(w);
     __builtin_amdgcn_sched_barrier(0);  // the rows' loads are not sunk below what follows
     if (open != 0ull) {                 // uniform over the workgroup
       list_inside<K>(kr, bin_masks<K>(kr, lo, up).inside, &sh.list_n, list);
@@ -756,17 +760,17 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   if (!found) {
     rows = taken;
     cnt = __popcll(rows);
-    aim_both(w);
+    aim_all(w);
   }
   HIRE_TS(13);
   auto count_h = [&](double v) {  // the scorer kernel of this step has cleared the window
     count_in_window<false>((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
   };
   if (!found) __syncthreads();  // the token in LDS
-  for (int r = w; r < cnt; r += 2 * kGW) {  // uniform over the wave; one trip for nearly all
-    if (r > w) aim_both(r);
+  for (int r = w; r < cnt; r += kRows * kGW) {  // uniform over the wave; one trip for nearly all
+    if (r > w) aim_all(r);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < kRows; ++u) {
       if (r + u * kGW >= cnt) break;
       const int pos = wave_row[u].pos;
       const double s = row_dot_relu(wave_row[u].row, wave_row[u].first, xtok, xvecs);
