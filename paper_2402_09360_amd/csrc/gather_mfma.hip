@@ -416,22 +416,26 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
   m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
       (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
   const int c = __popcll(m);  // candidates of the workgroup
+  // The tokens' norms that p.xnorm receives are the first tile's, which reads its first unit's row where it has no candidate: a
+  // norm's last bits go by the stage that its sum starts in, and k_refine's band must not go by which workgroup ends last.
+  const int rows = max(c, tile == 0 ? 1 : 0);  // read
   if (w == 0 && ((m >> lane) & 1ull)) rows_sh[mask_prefix(m)] = e0 + lane;
+  else if (tid == 0 && c == 0) rows_sh[0] = e0;
   __syncthreads();
   HIRE_TS(56);
   const int cw = w & 3, tt0 = (w >> 2) % TG * TTW, kh = (w >> 2) / TG;  // this wave's candidates, tokens, steps (uniform)
   FtAcc<TTW> acc{};
-  if (c > 0) {
+  if (rows > 0) {
     const uint32_t base = lds_offset(lds);
     const int nst = (cpr + kFtChunks - 1) / kFtChunks;
-    const int ci = (c + 4 * NW - 1) / (4 * NW);  // candidate loads of a stage: groups without candidates are left out
+    const int ci = (rows + 4 * NW - 1) / (4 * NW);  // candidate loads of a stage: groups without candidates are left out
     // instruction i of this wave fills rows 4 NW i + 4 w .. + 3 of the candidates' (tokens') part of a stage
     const char* wptr[CI];
     const char* xptr[TI];
     const int r4 = 4 * w + g, ch = jl ^ (r4 & 15);  // lane's row inside an instruction's stripe, its chunk of a stage
 #pragma unroll
     for (int i = 0; i < CI; ++i)
-      wptr[i] = reinterpret_cast<const char*>(W + (size_t)rows_sh[min(4 * NW * i + r4, c - 1)] * d);
+      wptr[i] = reinterpret_cast<const char*>(W + (size_t)rows_sh[min(4 * NW * i + r4, rows - 1)] * d);
 #pragma unroll
     for (int i = 0; i < TI; ++i) xptr[i] = reinterpret_cast<const char*>(x + (size_t)min((4 * NW * i + r4) % (16 * TT), B - 1) * d);
     auto request = [&](int st, int slot) {
@@ -456,7 +460,7 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
       for (int st = 0; st < nst; ++st) {
         stage_barrier_loads<CI, TI>(ci, st + kFtStages - 2 < nst);
         if (st + kFtStages - 1 < nst) request(stage_of(st + kFtStages - 1), slot == 0 ? kFtStages - 1 : slot - 1);
-        if (16 * cw < c)  // uniform
+        if (16 * cw < rows)  // uniform
           ft_stage<TT, TG, KS>(lds + slot * kStage, cw, tt0, kh, cpr - kFtChunks * stage_of(st), true, acc);
         slot = slot == kFtStages - 1 ? 0 : slot + 1;
       }
@@ -540,13 +544,13 @@ __device__ __forceinline__ void filter_units_tile(const FilterUnits& p, int tile
     if (p.wnorm_tiles != nullptr) p.wnorm_tiles[tile] = m;
     else atomicMax(p.wnorm_max, __float_as_uint(m));
   }
-  if (c <= 0) return;
-  for (int t = tid; t < B; t += NT) {  // the same values from every workgroup that has candidates
-    float xn2 = 0.0f;
+  if (tile == 0)  // uniform
+    for (int t = tid; t < B; t += NT) {
+      float xn2 = 0.0f;
 #pragma unroll
-    for (int q = 0; q < KS; ++q) xn2 += xsq[q][t / 16][t % 16];
-    p.xnorm[t] = sqrtf(xn2 * up) * 1.0001f;
-  }
+      for (int q = 0; q < KS; ++q) xn2 += xsq[q][t / 16][t % 16];
+      p.xnorm[t] = sqrtf(xn2 * up) * 1.0001f;
+    }
   HIRE_TS(58);
 }
 

@@ -30,3 +30,42 @@ def test_stages_in_turn(d, rows, B):
     assert un.max() <= wmax <= 1.01 * un.max()
     xg = xnorm.cpu().numpy().astype(np.float64)
     assert (xg >= xn).all() and (xg <= 1.01 * xn).all()
+
+
+@pytest.mark.parametrize("d,rows,B", [(2048, 8 * 64 * 16, 16), (2048, 8 * 64 * 16, 32), (2080, 8 * 64 * 17, 9)])
+def test_token_norms_come_from_one_order(d, rows, B):
+    """The selection's band goes by the tokens' norms: whatever stage the workgroups start in, they are bit for bit those
+    of the first 64 rows by themselves."""
+    from paper_2402_09360_amd import hire
+    W, x = T.dev_bf16(I.normal_bf16(731 + d, (rows, d))), T.dev_bf16(I.tokens(732 + d, B, d))
+    print(f"token norms d={d} rows={rows} B={B}", flush=True)
+    alone = hire.hire_debug_filter_stage(W[:64].contiguous(), x)[1]
+    for _ in range(8):
+        assert torch.equal(hire.hire_debug_filter_stage(W, x)[1], alone)
+
+
+@pytest.mark.parametrize("kind", ["int4", "lowrank"])
+@pytest.mark.parametrize("B", [16, 32])
+def test_steps_repeat_bit_for_bit(B, kind):
+    d, N, k, kp = 2048, 16384, 819, 3276
+    L = I.ffn_layer(741, d, N) if kind == "int4" else I.lowrank_ffn_layer(742, d, N, 32)
+    layer, _ = T.make_ffn_layer(L, lowrank=kind == "lowrank")
+    print(f"repeated steps B={B} {kind}", flush=True)
+    first, *more = T.run_ffn(layer, I.tokens(743, B, d), k, kp, steps=6, debug=False)
+    for got in more:
+        for name in ("y", "topk_idx", "topk_val", "cand"):
+            assert np.array_equal(got[name], first[name]), name
+
+
+@pytest.mark.parametrize("B", [16, 24])
+def test_first_units_outside_the_union(oracle, B):
+    """The workgroup that stores the tokens' norms has no candidates; the others start in all of the stages of rows that
+    end inside one."""
+    d, N = 2080, 16384
+    L = dict(I.ffn_layer(751, d, N))
+    L["w1u"] = L["w1u"].copy()
+    L["w1u"][:64] = 0x2000  # tiny weights, no token's pick
+    layer, scorer = T.make_ffn_layer(L)
+    print(f"first units outside the union, B={B}", flush=True)
+    got, _ = T.check_ffn(layer, scorer, L, I.tokens(752, B, d), 819, 3276)
+    assert got["cand"].min() >= 64
