@@ -653,7 +653,8 @@ __device__ __forceinline__ void token_to_lds(const uint4* __restrict__ x, int xv
   }
 }
 
-template <typename K, int LOADS>
+// ROWS: rows that a wave has under way at a time (launch_ffn_fast).
+template <typename K, int LOADS, int ROWS>
 __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   using Keys = KeyRegs<K, LOADS, kGT, false, true>;
   __shared__ GatherShared sh;
@@ -701,16 +702,11 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   const bool found = wk.found && bin >= 1u && bin <= anchor1;  // uniform
   bool known = false;  // which of the workgroup's units are shortlisted is
   int cnt = 0;         // rows
-  // a row of the wave: unit of the workgroup, address, first loads.  A wave has one or two, and those of both go out at once: every
-  // eighth workgroup has more than sixteen rows, and a second trip would make it the last to end (1.4 us behind the others).  One
-  // load of keys per thread: groups of eight, whose rows come by eights and whose second trips are not the last to end (the ~1B
-  // shape's 22.1 us per step with one row at a time, 22.7 with two, with 2736 dense units 28.8 and 29.2), or few units.
-  constexpr int kRows = LOADS == 1 ? 1 : 2;
-  struct Row {
+  struct Row {  // of the wave: unit of the workgroup, address, first loads
     int pos;
     const uint4* row;
     RowChunks first;
-  } wave_row[kRows];
+  } wave_row[ROWS];
   auto aim = [&](Row& a, int r) {  // the r-th unit of `rows`
     a.pos = __builtin_ctzll(__ballot(((rows >> lane) & 1ull) != 0ull && mask_prefix(rows) == r));
     a.row = reinterpret_cast<const uint4*>(p.W1 + (size_t)(u0 + a.pos) * p.d);
@@ -718,7 +714,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   };
   auto aim_all = [&](int r) {
 #pragma unroll
-    for (int u = 0; u < kRows; ++u)
+    for (int u = 0; u < ROWS; ++u)
       if (r + u * kGW < cnt) aim(wave_row[u], r + u * kGW);
   };
   // The keys have arrived by now.  Said to the compiler here, before the rows' loads go out: where paths with and without
@@ -767,10 +763,10 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
     count_in_window<false>((uint64_t)__double_as_longlong(v), anchor2, p.fr->hist2, &p.fr->beyond2);
   };
   if (!found) __syncthreads();  // the token in LDS
-  for (int r = w; r < cnt; r += kRows * kGW) {  // uniform over the wave; one trip for nearly all
+  for (int r = w; r < cnt; r += ROWS * kGW) {  // uniform over the wave
     if (r > w) aim_all(r);
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       if (r + u * kGW >= cnt) break;
       const int pos = wave_row[u].pos;
       const double s = row_dot_relu(wave_row[u].row, wave_row[u].first, xtok, xvecs);
@@ -1330,11 +1326,23 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     const dim3 grid(p.own_blocks + (a.m1 + kGW - 1) / kGW);
     const size_t lds = (size_t)a.d * 4;
     auto go = [&](auto kernel) { return launch(kernel, grid, dim3(kGT), lds, s, p); };
-    // the fewest loads that hold the keys: every pass over them is as long as a thread's share
+    // The fewest loads that hold the keys: every pass over them is as long as a thread's share.
+    // Units: two rows of a wave at a time.  At k' = N / 5 every eighth workgroup has more than sixteen rows, and a second trip
+    // would make it the last to end.  Groups of eight, whose rows come by eights: one.  us per step, one / two rows at a time:
+    // units of the int4 scorer, k' = 0.1, 0.2, 0.3 N: 1000 of d = 2048 15.5 / 15.5, 16.6 / 16.5, 16.9 / 17.1; 4000 16.0 / 16.0,
+    // 17.2 / 17.1, 18.2 / 18.1; 16384 19.7 / 19.8, 22.2 / 22.0, 24.3 / 24.5; k' = N / 5: 8192 of d = 1024 17.4 / 17.0, of
+    // d = 4096 22.9 / 22.6; fp64 keys, 4000 of d = 2048 18.6 / 18.8, 20.1 / 20.0, 21.3 / 21.4; 16384 24.3 / 24.5, 27.0 / 27.2,
+    // 29.9 / 29.8.  Groups, int4: 16384 units of d = 2048 21.9 / 22.6; fp64 keys: 13648 units of d = 2048, r = 32 21.9 / 22.4,
+    // r = 128 23.6 / 24.5, with 2736 dense units 28.8 / 29.9; 8192 of d = 4096 29.2 / 30.3.
+    static_assert(kFastMaxUnits / 8 <= 4096, "groups need the fewest loads");
     if (lowrank)
-      e = n_sel <= 4096 ? go(k_fast_gather<uint64_t, 2>) : (n_sel <= 8192 ? go(k_fast_gather<uint64_t, 4>) : go(k_fast_gather<uint64_t, 8>));
+      e = gs ? go(k_fast_gather<uint64_t, 2, 1>)
+             : (n_sel <= 4096 ? go(k_fast_gather<uint64_t, 2, 2>)
+                              : (n_sel <= 8192 ? go(k_fast_gather<uint64_t, 4, 2>) : go(k_fast_gather<uint64_t, 8, 2>)));
     else
-      e = n_sel <= 4096 ? go(k_fast_gather<uint32_t, 1>) : (n_sel <= 8192 ? go(k_fast_gather<uint32_t, 2>) : go(k_fast_gather<uint32_t, 4>));
+      e = gs ? go(k_fast_gather<uint32_t, 1, 1>)
+             : (n_sel <= 4096 ? go(k_fast_gather<uint32_t, 1, 2>)
+                              : (n_sel <= 8192 ? go(k_fast_gather<uint32_t, 2, 2>) : go(k_fast_gather<uint32_t, 4, 2>)));
     if (e != hipSuccess) return e;
     if ((e = mark(2)) != hipSuccess) return e;
   }

@@ -68,3 +68,14 @@ def test_one_token_many_rows_per_workgroup(oracle, d, N, kp, kind):
     want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
     for got in T.run_ffn(layer, x, k, kp, steps=3, debug=False):
         T.compare_ffn(got, dict(want, acc=None))
+
+
+@pytest.mark.parametrize("d,N,kp,kind", [(96, 1032, 1032, "int4"), (2080, 704, 352, "int4"), (256, 1000, 1000, "lowrank"),
+                                         (256, 4104, 2056, "lowrank")])
+def test_one_token_many_groups_per_workgroup(oracle, d, N, kp, kind):
+    """The same with groups of eight, whose waves have their rows one at a time: up to four trips."""
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    L = I.ffn_layer(761, d, N) if kind == "int4" else I.lowrank_ffn_layer(762, d, N, 32)
+    layer, scorer = T.make_ffn_layer(L, lowrank=kind == "lowrank")
+    print(f"one token, groups, d={d} N={N} k'={kp} {kind}", flush=True)
+    T.check_ffn_group(layer, scorer, L, I.tokens(763, 1, d), kp // 16 * 8, kp, 8)
