@@ -295,7 +295,7 @@ struct Sm1Shared {
   unsigned long long sel_key[kSm1MaxK];  // the k selected (logit as order key, class), unordered
   int32_t sel_idx[kSm1MaxK];
   double sel_z[kSm1MaxK];                // their logits in rank order
-  float wave_lo[kSm1Waves], wave_hi[kSm1Waves];
+  double wave_lo[kSm1Waves], wave_hi[kSm1Waves];
   int wave_cnt[kSm1Waves];
   int amb_n, zamb_n, sel_n;
 };
@@ -421,28 +421,29 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
   }
   const uint32_t bin_lb = okey_lb >> kHistShift;
   int rel[E];
-  // Of the kept entries, to all threads.  Rounded to fp32: the range only places the bins, and what lies outside counts in the
-  // first or the last of them.
-  auto logit_range = [&](float& lo, float& hi) {
+  // Of the kept entries, to all threads.  In fp64: logits that differ by less than fp32 holds would all fall into one bin, whose
+  // entries are ranked by comparing each with all (40000 classes, k' = 1536, logits around 2^26 that differ by a few units: 232 us
+  // per step, 305 with the range in fp32).
+  auto logit_range = [&](double& lo, double& hi) {
     lo = INFINITY;
     hi = -INFINITY;
 #pragma unroll
     for (int j = 0; j < E; ++j)
       if ((keep >> j) & 1u) {
-        lo = fminf(lo, (float)z[j]);
-        hi = fmaxf(hi, (float)z[j]);
+        lo = fmin(lo, z[j]);
+        hi = fmax(hi, z[j]);
       }
-    auto lower = [](float a, float b) { return fminf(a, b); };
-    auto upper = [](float a, float b) { return fmaxf(a, b); };
-    lo = read_lane63(wave_prefix(lo, (float)INFINITY, lower));
-    hi = read_lane63(wave_prefix(hi, (float)-INFINITY, upper));
+    auto lower = [](double a, double b) { return fmin(a, b); };
+    auto upper = [](double a, double b) { return fmax(a, b); };
+    lo = read_lane63(wave_prefix(lo, (double)INFINITY, lower));
+    hi = read_lane63(wave_prefix(hi, (double)-INFINITY, upper));
     if (lane == 0) {
       sh.wave_lo[w] = lo;
       sh.wave_hi[w] = hi;
     }
     __syncthreads();
-    lo = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_lo[lane] : (float)INFINITY, (float)INFINITY, lower));
-    hi = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_hi[lane] : (float)-INFINITY, (float)-INFINITY, upper));
+    lo = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_lo[lane] : (double)INFINITY, (double)INFINITY, lower));
+    hi = read_lane63(wave_prefix(lane < kSm1Waves ? sh.wave_hi[lane] : (double)-INFINITY, (double)-INFINITY, upper));
   };
 #pragma unroll
   for (int j = 0; j < E; ++j) {
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
     const bool wave_over = __ballot(over) != 0ull;
     if (lane == 0) sh.wave_cnt[w] = wave_over ? -1 : c;
   }
-  float z_lo, z_hi;
+  double z_lo, z_hi;
   logit_range(z_lo, z_hi);  // its barrier publishes the counts and the bins as well
   int n_s = 0;
   bool direct = !answered;  // uniform
@@ -466,15 +467,14 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
   }
   HIRE_TS(31);
   // logit bins: linear in the logit between the smallest and the largest, hence monotone
-  auto bins_per_logit = [&]() { return z_hi > z_lo ? (double)fminf((float)(kSm1ZBins - 1) / (z_hi - z_lo), 3e38f) : 0.0; };
-  double z_scale = bins_per_logit();
+  double z_scale = z_hi > z_lo ? (double)(kSm1ZBins - 1) / (z_hi - z_lo) : 0.0;
   int zbin[E];
   auto count_logits = [&]() {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       zbin[j] = -1;
       if ((keep >> j) & 1u) {
-        zbin[j] = min(max((int)((z[j] - (double)z_lo) * z_scale), 0), kSm1ZBins - 1);
+        zbin[j] = min(max((int)((z[j] - z_lo) * z_scale), 0), kSm1ZBins - 1);
         atomicAdd(&sh.z_hist[zbin[j]], 1u);
       }
     }
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
       }
     }
     logit_range(z_lo, z_hi);  // its barrier: the list has been read by everybody (its memory is reused below)
-    z_scale = bins_per_logit();
+    z_scale = z_hi > z_lo ? (double)(kSm1ZBins - 1) / (z_hi - z_lo) : 0.0;
     count_logits();
   }
   __syncthreads();

@@ -24,3 +24,17 @@ def test_copies_at_the_cut(oracle, B, c, copies, k, kp):
     want = oracle.softmax_step(W, scorer, x, k, kp, want_acc=True)
     for got in T.run_softmax(layer, x, k, kp, steps=2):
         T.compare_softmax(got, want)
+
+
+@pytest.mark.parametrize("B", [1, 4])
+@pytest.mark.parametrize("c,k,kp", [(40000, 64, 1024), (33001, 1, 1), (33001, 16, 300)])
+def test_logits_that_differ_below_fp32(oracle, B, c, k, kp):
+    """A common term of 2^26 beside terms of a few units: all logits round to a handful of fp32 values."""
+    d = 256
+    W, x = I.classifier(761, c, d).copy(), I.tokens(762, B, d).copy()
+    W[:, 0], x[:, 0] = 0x3D00, 0x4F00  # 2^-5, 2^31
+    layer, scorer = T.make_softmax_layer(W)
+    print(f"close logits, c={c} B={B} k={k} k'={kp}", flush=True)
+    want = oracle.softmax_step(W, scorer, x, k, kp, want_acc=True)
+    for got in T.run_softmax(layer, x, k, kp, steps=2):
+        T.compare_softmax(got, want)
