@@ -776,18 +776,23 @@ int filter_tiles(int n) { return max(1, (n + kFtRows - 1) / kFtRows); }
 int filter_rank_blocks(int n_cap) { return min(filter_tiles(n_cap), 256); }
 static_assert(4 * 256 <= kFilterMaxima && kFrMaxRows * 256 >= kSoftmaxRefineMaxRow, "maxima and rows per workgroup");
 
-// Where every workgroup reads the same 256 bytes of its rows at a time, rows of 4 KB and more queue in the memory system; with up to
-// 32 tokens, whose stages are mostly rows, and most of a workgroup's units candidates, the workgroups of a die
-// therefore start in different stages.  us per layer, not turned / turned: d = 2048, 16384 units, 9 / 16 / 32 tokens 56.2 / 55.0,
-// 53.0 / 50.1, 60.9 / 59.3 (65 MB in 14.8 us instead of 16.7); d = 4096, 9216 units, 16 tokens 61.4 / 60.4; d = 3072, 12288, 60.2 / 60.0.
-// Shorter rows gain nothing (d = 1024, 32 tokens 42.0 / 42.3; d = 1536, 16 46.6 / 46.9), nor do 64 tokens (68.8 / 69.4), workgroups
-// with a selection beside them (8192 units, 16 tokens 35.1 / 35.9) or few candidates (tokens of one query 41.5 / 42.1).
+// Where every workgroup reads the same 256 bytes of its rows at a time, rows that are whole multiples of 4 KB apart queue in the
+// memory system: all requests of a moment go to the same few channels.  With up to 32 tokens, whose stages are mostly rows, and most
+// of a workgroup's units candidates, the workgroups of a die therefore start in different stages.  us per layer, not turned /
+// turned, 9, 16 and 32 tokens: d = 2048, 16384 units 55.3 / 54.5, 53.2 / 50.5, 60.8 / 59.3 (65 MB in 14.8 us instead of 16.7 at 16
+// tokens); d = 4096, 9216 units 65.5 / 65.1, 61.5 / 60.7, 72.8 / 71.9; d = 6144, 6144 units 68.3 / 68.2, 68.3 / 67.8, 81.6 / 80.9;
+// d = 8192, 4608 units 76.6 / 77.1, 75.0 / 74.6, 90.9 / 91.0.  Rows of other lengths are spread over the channels as they are, and
+// lose by it: d = 2080, 16384 units 61.7 / 62.3, 59.7 / 60.8, 69.2 / 69.8; d = 2304 63.7 / 64.2, 61.3 / 61.8, 68.7 / 69.1; d = 3936,
+// 9590 units, 16 tokens 64.0 / 64.8; d = 2112, 2560, 2816 and 3072 within half a us either way.  Nor do shorter rows gain (d = 1024,
+// 32 tokens 42.0 / 42.3), 64 tokens (68.8 / 69.4), workgroups with a selection beside them (8192 units, 16 tokens 35.1 / 35.9) or few
+// candidates (tokens of one query 41.5 / 42.1).
 hipError_t launch_filter_units(const uint16_t* W, const uint16_t* x, int B, int d, const uint32_t* bitmap,
                                const int32_t* n_dev, int n_rows, float* h, long long stride_h, float* xnorm,
                                float* wnorm_tiles, uint32_t* wnorm_max, hipStream_t s) {
   if (B < 1 || B > 64 || d % 8 != 0) return hipErrorInvalidValue;
   static std::atomic<size_t> raised_to[3] = {};
-  const FilterUnits p{W, x, B, d, bitmap, n_dev, n_rows, h, stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B), d >= 2048 ? 1 : 0};
+  const FilterUnits p{W, x, B, d, bitmap, n_dev, n_rows, h, stride_h, xnorm, wnorm_tiles, wnorm_max, gather_filter_error(B),
+                      d % 2048 == 0 ? 1 : 0};
   auto go = [&](auto kernel, int tt, int waves, std::atomic<size_t>& raised) {
     const size_t lds = (size_t)kFtStages * ft_stage_bytes(tt);
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)

@@ -1,5 +1,6 @@
-"""The filter stage of long rows, whose workgroups start in different stages of a row: rows that end inside a stage, more
-workgroups than a die has stages, a last workgroup with few candidates.  |stored - <u, x>| <= err_c |u| |x|, the stage's
+"""The filter stage of long rows, whose workgroups start in different stages of a row where the rows are whole multiples of 4 KB
+apart: more workgroups of a die than a row has stages, a last workgroup with few candidates; and rows of other lengths, which
+end inside a stage.  |stored - <u, x>| <= err_c |u| |x|, the stage's
 proven bound."""
 import numpy as np
 import pytest
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,rows,B", [(2048, 1100, 16), (2080, 2113, 9), (2176, 8 * 64 * 3, 17), (4104, 700, 32), (2040, 1100, 16),
-                                      (2080, 2113, 33)])
+                                      (2080, 2113, 33), (2048, 8 * 64 * 17 + 50, 9), (2048, 8 * 64 * 17 + 50, 32),
+                                      (4096, 2113, 16), (4096, 8 * 64 * 3 + 49, 24)])
 def test_stages_in_turn(d, rows, B):
     from paper_2402_09360_amd import hire
     assert torch.cuda.is_available(), "these tests need the MI355X"
@@ -57,15 +59,14 @@ def test_steps_repeat_bit_for_bit(B, kind):
             assert np.array_equal(got[name], first[name]), name
 
 
-@pytest.mark.parametrize("B", [16, 24])
-def test_first_units_outside_the_union(oracle, B):
-    """The workgroup that stores the tokens' norms has no candidates; the others start in all of the stages of rows that
-    end inside one."""
-    d, N = 2080, 16384
+@pytest.mark.parametrize("d,B", [(2048, 16), (2080, 24)])  # the others start in all of the stages; rows that end inside one
+def test_first_units_outside_the_union(oracle, d, B):
+    """The workgroup that stores the tokens' norms has no candidates."""
+    N = 16384
     L = dict(I.ffn_layer(751, d, N))
     L["w1u"] = L["w1u"].copy()
     L["w1u"][:64] = 0x2000  # tiny weights, no token's pick
     layer, scorer = T.make_ffn_layer(L)
-    print(f"first units outside the union, B={B}", flush=True)
+    print(f"first units outside the union, d={d} B={B}", flush=True)
     got, _ = T.check_ffn(layer, scorer, L, I.tokens(752, B, d), 819, 3276)
     assert got["cand"].min() >= 64
