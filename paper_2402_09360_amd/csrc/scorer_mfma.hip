@@ -352,8 +352,9 @@ int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 // to 32 tokens of 2048 values, a wave then has one or two, 40 of 1024, where half of the waves have a third, or 64 of 512.
 // d = 2048, 16384 rows: 16 tokens 8.4 against 3.8 + 7.4
 // us, 32 tokens 11.9 against 4.1 + 8.0; 32000 rows, 32 tokens 14.8 against 4.7 + 9.7; d = 512, 3600 rows, 64 tokens 8.6 against
-// 3.6 + 5.9, 20184 rows, 32 tokens 7.4 against 4.4 + 5.7.  us per step: 33 tokens of 1024, 16384 rows 47.3 against 48.7, of 800, 5003
-// rows 36.3 against 36.6, 40 of 1024, 4000 rows 31.9 against 31.8.  Beyond (48 of 800: 39.4 against 38.5; 64 of 1024, 16384 rows 52.0
+// 3.6 + 5.9, 20184 rows, 32 tokens 7.4 against 4.4 + 5.7.  us per step, 33, 36 and 40 tokens: d = 1024, 16384 rows 47.3 against 48.9,
+// 48.2 / 49.4, 49.2 / 50.1, 4000 rows 32.5 / 32.9, 32.7 / 32.9, 31.7 / 31.7; d = 800, 5003 rows 36.2 / 36.5, 36.6 / 36.9, 38.5 / 38.7;
+// d = 544, 4000 rows 29.8 / 29.8, 29.8 / 29.9, 29.8 / 29.7.  Beyond (48 of 800: 39.4 against 38.5; 64 of 1024, 16384 rows 52.0
 // against 50.8) a wave has three or four long tokens, one after the other.  The intermediate of the int4 low-rank scorer is short
 // (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight waves would take as long as the
 // kernel in front.

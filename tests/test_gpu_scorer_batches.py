@@ -39,7 +39,9 @@ def _tokens(seed, B, d):
     (64, 8192, 17), (64, 8193, 31), (160, 16384, 24),          # 32 and 64 rows per workgroup
     (64, 16385, 16), (32, 32768, 64),                          # 128
     (512, 4096, 33), (512, 4097, 64), (544, 4097, 33),         # more than 32 tokens: short ones are quantised here too
-    (1024, 20003, 24), (1056, 8193, 7), (2048, 16385, 17)])    # the vectors of a token per lane
+    (1024, 20003, 24), (1056, 8193, 7), (2048, 16385, 17),     # the vectors of a token per lane
+    (544, 1023, 40), (1024, 4000, 40), (1024, 4097, 40), (800, 8193, 34), (1024, 16385, 40),  # four tokens per wave, two
+    (1024, 4097, 41), (1056, 4097, 33)])                       # vectors each: 16, 32, 64, 128 rows; past each limit
 def test_ffn_rows(hire, oracle, d, N, B):
     log(f"ffn_step d={d} N={N} B={B}")
     L = I.ffn_layer(900 + d, d, N)

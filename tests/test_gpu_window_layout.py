@@ -32,7 +32,8 @@ def test_one_and_several_tokens_in_turn(oracle, d, N):
 @pytest.mark.parametrize("B,group,distinct", [(2, 1, 3), (4, 1, 1), (4, 1, 40), (3, 8, 2), (8, 8, 1), (8, 8, 30)])
 def test_many_units_in_the_threshold_bins(oracle, B, group, distinct):
     """Rows that repeat: whole workgroups' units share the threshold bins of several tokens, up to every unit of all of them,
-    and the lower index decides."""
+    and the lower index decides.  The thresholds are found in the windows throughout; the second selection's bins may hold more
+    than its list."""
     import numpy as np
     from paper_2402_09360_amd import hire
     assert torch.cuda.is_available(), "these tests need the MI355X"
@@ -45,11 +46,16 @@ def test_many_units_in_the_threshold_bins(oracle, B, group, distinct):
     layer, scorer = T.make_ffn_layer(L)
     if group == 1:
         want = oracle.ffn_step(L["w1u"], L["w2u"], scorer, x, k, kp)
-        for got in T.run_ffn(layer, x, k, kp, steps=3, debug=False):
+        ws = hire.alloc_workspace(hire.hire_ffn_workspace_bytes(layer, B, k, kp))
+        for got in T.run_ffn(layer, x, k, kp, steps=3, debug=False, ws=ws):
             T.compare_ffn(got, dict(want, acc=None))
+        assert hire.hire_debug_fast_fallbacks(ws)[0] == 0
         return
     want = oracle.ffn_group_step(L["w1u"], L["w2u"], scorer, x, k, kp, group)
-    for got in T.run_ffn_group(layer, x, k, kp, group, steps=3, debug=False):
+    ws = hire.alloc_workspace(hire.hire_ffn_group_workspace_bytes(layer, B, k, kp, group))
+    results = T.run_ffn_group(layer, x, k, kp, group, steps=3, debug=False, ws=ws)
+    assert hire.hire_debug_fast_fallbacks(ws)[0] == 0
+    for got in results:
         assert np.array_equal(got["cand"], want["cand"]) and np.array_equal(got["topk_group"], want["topk_group"])
         T.assert_float_close(got["topk_val"], want["topk_val"], "topk_val")
         T.assert_float_close(got["y"], want["y"], "y")
