@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kST) void k_fast_score_lr(const uint16_t* __restric
 // where a unit is not shortlisted), so no list of candidates is needed in between; the caller's is written beside
 // kernel 3 (a 257th workgroup here would wait for a compute unit).  K: the keys' bit patterns, 32 bits for the int4
 // scorer's fp32 keys, 64 for the low-rank scorer's fp64 ones; LOADS: 16-byte loads of keys per thread.
-// Measured at the ~1B shape: 7.8 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
+// Measured at the ~1B shape: 7.6 us against 10.5 when every workgroup selected all of the shortlist for an equal share of
 // its rows.  Inside: 2.3 until the window is walked, 0.5 until the rows are known, 1.3 for the rows; workgroups that own a
 // key of the threshold bin need 1.6 more for its list and are the last to end.
 constexpr int kGT = 1024;

@@ -256,7 +256,7 @@ __device__ __forceinline__ float pick4(const f32x4& v, int i) {
 // activation of zero never displaces a positive one; the selection asks the bitmap where zeros are selected).
 //
 // Bound: HBM; one workgroup per compute unit keeps 48 KB of rows in flight.  Measured at d = 2048: 16 tokens, 15900
-// candidates (65 MB) 14.6 us (17.4 with all workgroups starting in the same columns, see launch_filter_units), 64 tokens,
+// candidates (65 MB) 14.5 us (17.4 with all workgroups starting in the same columns, see launch_filter_units), 64 tokens,
 // 16384 candidates 19.7 us (of which the stages 12: 5.6 TB/s).  The kernel before this one staged through registers and
 // located its candidates by rank: 22.4 us at 16 tokens, 30 at 64.  KS = 1: 17.6 and 19.9, not turned.
 constexpr int kFtRows = 64;        // candidates per workgroup

@@ -422,8 +422,8 @@ __global__ __launch_bounds__(kSm1Threads) void k_sm1_final(const float* __restri
   const uint32_t bin_lb = okey_lb >> kHistShift;
   int rel[E];
   // Of the kept entries, to all threads.  In fp64: logits that differ by less than fp32 holds would all fall into one bin, whose
-  // entries are ranked by comparing each with all (40000 classes, k' = 1536, logits around 2^26 that differ by a few units: 232 us
-  // per step, 305 with the range in fp32).
+  // entries are ranked by comparing each with all (40000 classes, k' = 1536, logits around 2^26 that differ by a few units: 231 us
+  // per step, 304 with the range in fp32).
   auto logit_range = [&](double& lo, double& hi) {
     lo = INFINITY;
     hi = -INFINITY;
