@@ -439,9 +439,9 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   // A unit that only has keys of threshold bins, of which some are selected: its key is compared with all others of the token.
   // One workgroup in six has such a unit, and then one or two, and would be the last to end.  Its rows are read with the others,
   // and a wave that has its rows asks for its part of the keys while other waves still wait for theirs: ahead of the rows, or
-  // beside their first loads, the keys cost 2 to 5 us instead of one.  Where rows repeat and a workgroup has many of them, one after
-  // the other, it is no slower either: the ~1B shape, four tokens, 40 distinct rows 84.0 us per step (89.1 with the next key's row
-  // requested ahead, in front of the rows), all rows equal 596 (638).
+  // beside their first loads, the keys cost 2 to 5 us instead of one.  Where rows repeat and a workgroup has many such units, they
+  // follow one another; the next one's keys requested ahead of the comparison are slower there as well: the ~1B shape, four
+  // tokens, 40 distinct rows 83.9 us per step (85.7), all rows equal 595 (625), no repeated rows 37.7 (37.9).
 #pragma unroll 1
   for (int j = 0; j < opens; ++j) {  // uniform over the workgroup
     constexpr int PER = KeyIO<K>::PER, kLoads = 16 / PER;  // the row of 16384 keys at a time
