@@ -10,6 +10,7 @@
 #include "device_utils.h"
 #include "hist.h"
 #include "kernels.h"
+#include "listed_rows.h"
 
 namespace hire {
 
@@ -74,15 +75,14 @@ __global__ __launch_bounds__(256) void k_gather_dot(const uint16_t* __restrict__
 // Second layer, y_b = sum_e coef(b, e) * W2[row(b, e), :] over the k entries (row, coefficient) that the selection
 // left for token b, plus (CommonPath, eq. (7)) sum_r fl32(hd[b, r]) * Wd[r, :] over m1 dense rows.  One kernel, no
 // partial sums: a workgroup owns 8 LPR columns of one token and all of its rows, and writes y itself.  The entries
-// pass through LDS in chunks; LPR lanes share a row (16 bytes each), and a lane has two batches of FL rows in
-// flight, the next one requested before the current one is added up.
+// pass through LDS in chunks; add_listed_rows (listed_rows.h) adds up a chunk.
 //
 // Bound: the round trips list -> rows for few tokens; for many the caches (64 tokens read 215 MB of rows that are
 // 67 MB in HBM, 11 TB/s).  Narrow slices spread few tokens over the chip; wide ones read longer runs and are faster
 // once 256 workgroups exist.  The dispatcher places workgroup i on die i % 8, and a die takes an eighth of the
 // (slice, token) pairs, slice by slice, so that the tokens share a slice's rows in one L2 and every die has as much to do
 // (whole slices per die left dies idle where slices do not come in eights: 49 tokens of d = 288, k = 1949 12.2 us, now
-// 10.2; 64 of d = 640, k = 1200 15.9, now 13.7).  Measured at d = 2048, k = 819 of 16384 units: 10.1 us for 16 tokens, 20.3
+// 10.2; 64 of d = 640, k = 1200 15.9, now 13.7).  Measured at d = 2048, k = 819 of 16384 units: 9.6 us for 16 tokens, 20.0
 // for 64, against 12.2 for a kernel with partial sums and a reducing one at 16 and 23.7 for 256-column workgroups without
 // the second batch in flight at 64.
 constexpr int kW2Threads = 512;
@@ -97,7 +97,8 @@ __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __res
   constexpr int kCols = 8 * LPR;                         // columns of the workgroup
   constexpr int kStride = kW2Waves * (kWave / LPR);      // rows of the workgroup per load instruction
   static_assert(kW2Chunk % (kStride * FL) == 0 && kCols <= kW2Threads, "whole batches per chunk, a thread per column");
-  __shared__ uint2 entries[kW2Chunk];
+  constexpr int kBatch = kStride * FL, kFill = (kW2Chunk + kBatch + kW2Threads - 1) / kW2Threads;
+  __shared__ uint2 entries[kFill * kW2Threads];
   __shared__ float red[kW2Waves][kCols];
   const int lane = lane_id(), w = wave_id(), tid = (int)threadIdx.x;
   const int n_items = (d + kCols - 1) / kCols * B;
@@ -109,51 +110,18 @@ __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __res
   float acc[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  // adds up the n entries in LDS (row 0 with coefficient 0 from n to the end of its batch)
+  // adds up the n entries in LDS (behind them some row with coefficient 0, to the end of one batch more)
   auto add_chunk = [&](const uint16_t* __restrict__ M, int n) {
-    const uint16_t* base = M + colc;
-    auto request = [&](int t0, uint4 (&wv)[FL], float (&cf)[FL]) {
-#pragma unroll
-      for (int u = 0; u < FL; ++u) {
-        const uint2 e = entries[min(t0 + u * kStride, kW2Chunk - 1)];
-        cf[u] = __uint_as_float(e.y);
-        wv[u] = *reinterpret_cast<const uint4*>(base + (size_t)e.x * d);
-      }
-    };
-    auto add = [&](const uint4 (&wv)[FL], const float (&cf)[FL]) {
-#pragma unroll
-      for (int u = 0; u < FL; ++u) {
-        const float wf[8] = {bf16_lo(wv[u].x), bf16_hi(wv[u].x), bf16_lo(wv[u].y), bf16_hi(wv[u].y),
-                             bf16_lo(wv[u].z), bf16_hi(wv[u].z), bf16_lo(wv[u].w), bf16_hi(wv[u].w)};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf[u], wf[q], acc[q]);
-      }
-    };
-    constexpr int kBatch = kStride * FL;
-    uint4 wa[FL], wb[FL];
-    float ca[FL], cb[FL];
-    request(first, wa, ca);
-    for (int t0 = 0; t0 < n; t0 += 2 * kBatch) {  // uniform; the scheduling barriers keep the requests ahead
-      const bool more = t0 + kBatch < n;
-      if (more) request(t0 + kBatch + first, wb, cb);
-      __builtin_amdgcn_sched_barrier(0);
-      add(wa, ca);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!more) break;
-      if (t0 + 2 * kBatch < n) request(t0 + 2 * kBatch + first, wa, ca);
-      __builtin_amdgcn_sched_barrier(0);
-      add(wb, cb);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    add_listed_rows<LPR, FL, kW2Waves>(M + colc, d, n, first, [&](int t) { return entries[t]; }, acc);
   };
   const uint2* mine = list + (size_t)b * k;
   for (int e0 = 0; e0 < k; e0 += kW2Chunk) {
     if (e0 > 0) __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kW2Chunk / kW2Threads; ++u) {
+    for (int u = 0; u < kFill; ++u) {
       const int i = u * kW2Threads + tid;
       const uint2 e = mine[min(e0 + i, k - 1)];
-      entries[i] = e0 + i < k ? e : make_uint2(0u, 0u);
+      entries[i] = make_uint2(e.x, i < kW2Chunk && e0 + i < k ? e.y : 0u);
     }
     __syncthreads();
     add_chunk(W2, min(kW2Chunk, k - e0));
@@ -161,20 +129,16 @@ __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __res
   for (int e0 = 0; e0 < m1; e0 += kW2Chunk) {
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kW2Chunk / kW2Threads; ++u) {
+    for (int u = 0; u < kFill; ++u) {
       const int i = u * kW2Threads + tid;
       const float c = (float)hd[(size_t)b * m1 + min(e0 + i, m1 - 1)];
-      entries[i] = e0 + i < m1 ? make_uint2((uint32_t)(e0 + i), __float_as_uint(c)) : make_uint2(0u, 0u);
+      entries[i] = make_uint2((uint32_t)min(e0 + i, m1 - 1), i < kW2Chunk && e0 + i < m1 ? __float_as_uint(c) : 0u);
     }
     __syncthreads();
     add_chunk(Wd, min(kW2Chunk, m1 - e0));
   }
   // the lanes of a wave that hold the same columns (fixed tree), then the waves in order
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-#pragma unroll
-    for (int m = LPR; m < kWave; m <<= 1) acc[q] += __shfl_xor(acc[q], m);
-  }
+  fold_lanes<LPR>(acc);
   if (lane < LPR) {
     float4* dst = reinterpret_cast<float4*>(&red[w][sub * 8]);
     dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
