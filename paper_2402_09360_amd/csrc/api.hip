@@ -691,6 +691,12 @@ int hire_ffn_step(const hire_ffn_layer* L, const void* x, int B, int k, int kpri
     // filter's values and 65.5 with the fp64 stage; 33 tokens of d = 800, 5003 units 47.0, 41.7 and 54.5.
     rp.exact_values = !(B >= kFilterValuesMinBatch && s.cap_u > 1024 && s.cap_u <= 16384 && s.cap_u % 2 == 0);
     rp.window_misses = s.window_misses;
+    if (refine_w2_supported(rp)) {
+      HIRE_TRY(launch_refine_w2(rp, static_cast<const uint16_t*>(L->w2u), y, st));
+      HIRE_STAGE(6, st);
+      HIRE_STAGE(7, st);
+      return HIRE_OK;
+    }
     HIRE_TRY(launch_refine(rp, st));
   } else {
     SelectParams sp{};

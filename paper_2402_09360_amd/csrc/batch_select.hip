@@ -5,6 +5,8 @@
 //   k_refine       the k largest exact activations of a token from the filter stage's values (launch_filter_units,
 //                  in unit order), recomputing in fp64 what lies around the threshold -> indices, values and the
 //                  (row, coefficient) list of the second layer
+//   k_refine_w2    the same with the second layer behind it, where the selected rows are few enough: several workgroups per
+//                  token, each with some columns of y
 //
 // and, where the values are to be rounded from 64 bits and not only selected by them, k_exact_values over the list.
 // The selections are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
@@ -16,6 +18,7 @@
 #include "fast_select.h"
 #include "kernels.h"
 #include "keys_select.h"
+#include "listed_rows.h"
 
 namespace hire {
 
@@ -30,18 +33,20 @@ __global__ __launch_bounds__(kSelThreads) void k_keys_select(KeysSelect p) {
 // ---------------------------------------------------------------------------------------------------
 struct RefineShared {
   SelSharedT<kSelThreads> sh;
-  __align__(16) uint32_t win[kWin + 2 * kWave];  // window histogram; then the packed outputs (k <= kWin / 2)
+  __align__(16) uint32_t win[kWin + 2 * kWave];  // window histogram; then the selected entries in order (k <= kWin / 2)
   unsigned long long l_val[kBsCap];  // refined values (fp64 bits) and their units
   int l_idx[kBsCap];
   int wave_cnt[kSelWaves], wave_eq[kSelWaves];
   float wave_max[kSelWaves];
+  int cand_cnt[kSelWaves];
 };
 
 // What the histogram and the list cannot settle (threshold among the zeros, very many activations within the error of
 // the threshold): exact, by streaming the row.  The k-th largest stored value among the candidates by range
 // narrowing; everything within hw of it recomputed in fp64; then the k-th largest of the candidates' fp64 values (stored
-// ones outside the band) with ties to the lower unit, and the outputs.  The fp64 values lie in the order of the
-// candidates; a wave owns the units [i_lo, i_hi) and so the candidates from c_lo on.
+// ones outside the band) with ties to the lower unit, packed into LDS in order.  The fp64 values lie in the order of the
+// candidates; a wave owns the units [i_lo, i_hi) and so the candidates from c_lo on.  Workgroups that select for the same token
+// share the scratch: each place is written once by each of them, with the same value, and read by its own writer behind a barrier.
 __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, const uint4* tok, RefineShared& L, double hw) {
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int N = p.N, k = p.k;
@@ -73,15 +78,16 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
     const uint64_t cands = __ballot(cand);
     const int at = run_c + mask_prefix(cands);
     run_c += __popcll(cands);
-    if (cand) h[at] = (double)v;
+    double stored = (double)v;
     // exact zeros are activations already; with k = all candidates nothing needs to be decided
     uint64_t band = __ballot(cand && k < n_units && v > 0.0f && (double)v >= lo && (double)v <= hi);
     while (band != 0ull) {
       const int s = __builtin_ctzll(band);
       band &= band - 1ull;
       const double r = wave_row_dot(p.W + (size_t)(i0 + s) * p.d, tok, p.d);
-      if (lane == s) h[at] = r;
+      stored = lane == s ? r : stored;
     }
+    if (cand) h[at] = stored;
   }
   __syncthreads();
   const uint64_t t = wg_kth_largest<uint64_t>(
@@ -125,12 +131,8 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
     const int gt_before = run_gt + mask_prefix(mg), eq_before = run_eq + mask_prefix(me);
     run_gt += __popcll(mg);
     run_eq += __popcll(me);
-    if (cand && (key > t || (key == t && eq_before < need_eq))) {
-      const size_t o = (size_t)b * k + gt_before + min(eq_before, need_eq);
-      if (p.idx_out) p.idx_out[o] = i;
-      if (p.val_out) p.val_out[o] = (float)v;
-      p.list_out[o] = make_uint2((uint32_t)i, __float_as_uint((float)v));
-    }
+    if (cand && (key > t || (key == t && eq_before < need_eq)))
+      reinterpret_cast<uint2*>(L.win)[gt_before + min(eq_before, need_eq)] = make_uint2((uint32_t)i, __float_as_uint((float)v));
   }
 }
 
@@ -140,21 +142,15 @@ __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, c
 // between is recomputed in fp64 (about fifteen entries at the ~1B shape).  With A entries above, the k - A largest recomputed
 // ones complete the selection.  The outcome is checked and not taken on trust: if the (k - A)-th largest recomputed
 // value r satisfies L + hw/2 <= r <= H - hw/2, every entry above H is at least r and every one below L less than r.
+// Leaves the selected (unit, value) pairs in L.win, in order, behind a barrier.  tok_sh: room for the token, d <= kRefineTokenMax.
 template <int LOADS>
-__global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
+__device__ __forceinline__ void refine_token(const RefineParams& p, int b, bool counts_misses, uint4* tok_sh, RefineShared& L) {
   using K = uint32_t;
   using Keys = typename BatchKeys<uint32_t, LOADS>::Keys;
   constexpr int PER = Keys::PER;
-  __shared__ RefineShared L;
-  extern __shared__ uint4 tok_sh[];  // the token, d <= kRefineTokenMax
-  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id();
+  const int tid = (int)threadIdx.x, lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
   const int N = p.N, k = p.k, d = p.d;
-  if (b == p.B) {  // one more workgroup lists the candidates meanwhile
-    const int n = list_bitmap<kSelThreads>(p.bitmap, (N + 31) / 32, p.cand_out, p.cand_cap, L.sh);
-    if (tid == 0 && p.n_cand_out) *p.n_cand_out = n;
-    return;
-  }
   HIRE_TS(40);
   const float* row = p.vals + (size_t)b * p.stride;
   const uint4* tok = reinterpret_cast<const uint4*>(p.x + (size_t)b * d);
@@ -302,22 +298,104 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
             }
           __syncthreads();
           HIRE_TS(46);
-          for (int t = tid; t < k; t += kSelThreads) {
-            const uint2 v = pk[t];
-            const size_t o = (size_t)b * k + t;
-            p.list_out[o] = v;
-            if (p.idx_out) p.idx_out[o] = (int)v.x;
-            if (p.val_out) p.val_out[o] = __uint_as_float(v.y);
-          }
-          HIRE_TS(47);
           return;
         }
       }
     }
   }
-  if (tid == 0 && p.window_misses) atomicAdd(p.window_misses, 1u);
+  if (tid == 0 && counts_misses && p.window_misses) atomicAdd(p.window_misses, 1u);
   __syncthreads();
   refine_streaming(p, b, tok, L, hw);
+  __syncthreads();
+}
+
+// Entries [t0, t1) of the packed ones -> the caller's columns.
+__device__ __forceinline__ void write_selected(const RefineParams& p, int b, const RefineShared& L, int t0, int t1, uint2* list) {
+  for (int t = t0 + (int)threadIdx.x; t < t1; t += kSelThreads) {
+    const uint2 v = reinterpret_cast<const uint2*>(L.win)[t];
+    const size_t o = (size_t)b * p.k + t;
+    if (list) list[o] = v;
+    if (p.idx_out) p.idx_out[o] = (int)v.x;
+    if (p.val_out) p.val_out[o] = __uint_as_float(v.y);
+  }
+}
+
+template <int LOADS>
+__global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
+  __shared__ RefineShared L;
+  extern __shared__ uint4 tok_sh[];
+  const int b = (int)blockIdx.x;
+  if (b == p.B) {  // one more workgroup lists the candidates meanwhile
+    const int n = list_bitmap<kSelThreads>(p.bitmap, (p.N + 31) / 32, p.cand_out, p.cand_cap, L.sh);
+    if (threadIdx.x == 0 && p.n_cand_out) *p.n_cand_out = n;
+    return;
+  }
+  refine_token<LOADS>(p, b, true, tok_sh, L);
+  write_selected(p, b, L, 0, p.k, p.list_out);
+  HIRE_TS(47);
+}
+
+// The same selection and the second layer in one kernel: a workgroup has 8 LPR columns of one token, selects for it (every
+// workgroup of a token does) and adds up the selected rows from the list in its own LDS.  Against k_refine and k_w2_list it saves
+// a boundary and the lists' way through memory, and pays for the values and the band's rows being read by every slice's workgroup.
+// Bound by the selection's chain (8.4 us at the ~1B shape), then by the rows (38 MB from HBM for 16 tokens in 7).  A workgroup
+// fills a compute unit (89 registers, sixteen waves), so that there is no place for one more that lists the candidates: all of
+// them do, 64 units each, behind their columns.
+template <int LPR>
+__global__ __launch_bounds__(kSelThreads) void k_refine_w2(RefineParams p, const uint16_t* __restrict__ W2, float* __restrict__ y) {
+  constexpr int kCols = 8 * LPR, FL = 4;
+  __shared__ RefineShared L;
+  extern __shared__ uint4 dyn_sh[];  // the token; then the waves' sums
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int N = p.N, k = p.k, d = p.d;
+  const int slices = (d + kCols - 1) / kCols, n_items = slices * p.B;
+  const int item = (int)(blockIdx.x & 7) * ((n_items + 7) / 8) + (int)(blockIdx.x >> 3);
+  if (item >= n_items) return;  // uniform: the last dies' shares may be short
+  const int slice = item / p.B, b = item % p.B;
+  // the candidates' bits, a word per thread: the workgroups share out the list of them
+  const int words = (N + 31) / 32;
+  const uint32_t word = p.bitmap[min(tid, words - 1)];
+  const uint32_t bits = tid < words ? word : 0u;
+  const int upto = wave_scan_incl(__popc(bits));
+  if (lane == kWave - 1) L.cand_cnt[w] = upto;
+  refine_token<4>(p, b, slice == 0, dyn_sh, L);
+  const uint2* entries = reinterpret_cast<const uint2*>(L.win);
+  const int sub = lane % LPR, first = w * (kWave / LPR) + lane / LPR;
+  const int colc = min(slice * kCols + sub * 8, d - 8);
+  float acc[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
+  add_listed_rows<LPR, FL, kSelWaves>(W2 + colc, d, k, first, [&](int t) { return make_uint2(entries[min(t, k - 1)].x, t < k ? entries[min(t, k - 1)].y : 0u); }, acc);
+  HIRE_TS(48);
+  float* red = reinterpret_cast<float*>(dyn_sh);  // [kSelWaves][kCols]; the token was last read ahead of a barrier
+  fold_lanes<LPR>(acc);
+  if (lane < LPR) {
+    float4* dst = reinterpret_cast<float4*>(&red[w * kCols + sub * 8]);
+    dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  }
+  __syncthreads();
+  if (tid < kCols && slice * kCols + tid < d) {
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kSelWaves; ++u) s += red[u * kCols + tid];
+    y[(size_t)b * d + slice * kCols + tid] = s;
+  }
+  write_selected(p, b, L, (int)((long long)k * slice / slices), (int)((long long)k * (slice + 1) / slices), nullptr);
+  if (p.cand_out != nullptr) {
+    const int cnt = wave_scan_incl(lane < kSelWaves ? L.cand_cnt[lane] : 0);
+    const int ahead = w > 0 ? __builtin_amdgcn_readlane(cnt, w - 1) : 0;
+    for (int pair = item; 2 * pair < words; pair += n_items) {
+      const int l = 2 * pair % kWave;  // (even: both words are the same wave's; beyond the end they are 0)
+      if (2 * pair / kWave != w) continue;  // uniform
+      const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, l), b1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, l + 1);
+      const uint64_t m = (uint64_t)b1 << 32 | b0;
+      const int at = ahead + __builtin_amdgcn_readlane(upto, l) - __popc(b0) + mask_prefix(m);
+      if ((m >> lane & 1ull) != 0ull && at < p.cand_cap) p.cand_out[at] = pair * kWave + lane;
+    }
+    if (item == 0 && tid == 0 && p.n_cand_out) *p.n_cand_out = __builtin_amdgcn_readlane(cnt, kSelWaves - 1);
+  }
+  HIRE_TS(49);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -509,6 +587,46 @@ hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
   };
   const hipError_t e = p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
   return e == hipSuccess && p.exact_values ? launch_exact_values(p.list_out, p.val_out, p.W, p.x, p.B, p.k, p.d, s) : e;
+}
+
+template <int LPR>
+static hipError_t refine_w2_launch(const RefineParams& p, const uint16_t* W2, float* y, hipStream_t s) {
+  const size_t sums = (size_t)kSelWaves * 8 * LPR * sizeof(float), tok = p.d <= kRefineTokenMax ? (size_t)p.d * 2 : 0;
+  const size_t lds = sums > tok ? sums : tok;
+  static std::atomic<size_t> raised_to{0};
+  if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(k_refine_w2<LPR>), lds, raised_to); e != hipSuccess)
+    return e;
+  const int items = (p.d + 8 * LPR - 1) / (8 * LPR) * p.B;
+  return launch(k_refine_w2<LPR>, dim3((items + 7) / 8 * 8), dim3(kSelThreads), lds, s, p, W2, y);
+}
+
+// A workgroup fills a compute unit, and every one of them selects: one round of 256, of the narrowest slices that fit.
+static int refine_w2_columns(int B, int d) {
+  for (int cols = 64; cols <= 512; cols *= 2)
+    if ((d + cols - 1) / cols * B <= 256) return cols;
+  return 0;
+}
+// Where the rows are many (96 MB, several tokens' repeats counted) the caches bound the second layer, and k_w2_list's even shares of
+// a die serve more of them from its L2: wide slices of one token per workgroup make two dies read the same columns, and 256 workgroups
+// read values and band.  us per step with k_refine and k_w2_list / this kernel, d = 2048, k = 819 of 16384 units: 16 tokens 49.9 / 48.9,
+// 24 56.9 / 56.1, 28 57.7 / 57.3 (94 MB), 32 58.8 / 59.5, 33 62.8 / 63.6, 48 64.6 / 65.6, 64 68.4 / 71.5 (with nine tenths in common 63.6 /
+// 61.5); d = 4096, k = 409 of 8192: 16 57.6 / 56.0, 33 66.1 / 66.3, 64 74.6 / 74.8; d = 1024, k = 400 of 8000: 16 30.6 / 29.5, 33 37.0 / 35.3,
+// 64 39.3 / 38.2; d = 512, k = 200 of 4000: 16 23.6 / 22.8, 64 29.0 / 27.9; d = 256, k = 51 of 1024: 24.7 / 24.8, 30.3 / 30.5.
+constexpr long long kRefineW2Bytes = 96ll << 20;
+bool refine_w2_supported(const RefineParams& p) {
+  return p.N <= 16384 && !p.exact_values && refine_w2_columns(p.B, p.d) != 0 &&
+         2ll * p.B * p.k * p.d <= kRefineW2Bytes;
+}
+hipError_t launch_refine_w2(const RefineParams& p, const uint16_t* W2, float* y, hipStream_t s) {
+  if (!batch_select_supported(p.N, p.k) || !refine_w2_supported(p) || p.stride % 4 != 0 ||
+      reinterpret_cast<uintptr_t>(p.vals) % 16 != 0 || p.d % 8 != 0)
+    return hipErrorInvalidValue;
+  switch (refine_w2_columns(p.B, p.d)) {
+    case 64: return refine_w2_launch<8>(p, W2, y, s);
+    case 128: return refine_w2_launch<16>(p, W2, y, s);
+    case 256: return refine_w2_launch<32>(p, W2, y, s);
+    default: return refine_w2_launch<64>(p, W2, y, s);
+  }
 }
 
 }  // namespace hire

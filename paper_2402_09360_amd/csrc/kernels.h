@@ -264,6 +264,10 @@ struct RefineParams {
   uint32_t* window_misses;  // optional counter: tokens that the histogram and the list in LDS did not settle
 };
 hipError_t launch_refine(const RefineParams& p, hipStream_t s);
+// The same and the second layer, y_b = sum of the selected (unit, value) pairs' rows of W2, in one kernel (list_out is not
+// written); what of it refine_w2_supported says.
+bool refine_w2_supported(const RefineParams& p);
+hipError_t launch_refine_w2(const RefineParams& p, const uint16_t* W2, float* y, hipStream_t s);
 // The activations of the listed (token, unit) pairs, rounded once from fp64: into lists [B, k] and (optional) val_out.
 hipError_t launch_exact_values(uint2* lists, float* val_out, const uint16_t* W, const uint16_t* x, int B, int k, int d,
                                hipStream_t s);
