@@ -82,10 +82,14 @@ __device__ __forceinline__ void rows_sums(int cnt, RowOf&& row_of, const uint4* 
   while (ps * SL < nsl) ps <<= 1;
   const int s0 = (w & (ps - 1)) * SL, rp = w / ps, step = kRowsWaves / ps;
   uint4 ring[kDepth][SL];
-  auto load = [&](int q, uint4 (&v)[SL]) {
+  // No load sits behind a branch, or the wait for one group's rows would become one for all that is under way: in the place of
+  // groups past the end a wave asks for the first token again, which is in the caches.
+  auto load = [&](int q, uint4 (&v)[SL]) __attribute__((always_inline)) {
     const uint4* row = row_of(min(q * 4 + (lane & 3), cnt - 1));
+    if (q >= ng) row = x;  // uniform
 #pragma unroll
     for (int j = 0; j < SL; ++j) v[j] = load_streaming(row + min((s0 + j) * 16 + (lane >> 2), nvec - 1));
+    __builtin_amdgcn_sched_barrier(0);
   };
   uint4 xr[SL][kTok4];  // asked for ahead of the rows: loads return in order
 #pragma unroll
@@ -93,10 +97,10 @@ __device__ __forceinline__ void rows_sums(int cnt, RowOf&& row_of, const uint4* 
 #pragma unroll
     for (int f = 0; f < kTok4; ++f)
       xr[j][f] = x[(size_t)min(f * 4 + (lane & 3), B - 1) * nvec + min((s0 + j) * 16 + (lane >> 2), nvec - 1)];
+  __builtin_amdgcn_sched_barrier(0);
+  if (s0 < nsl && rp < ng) {  // uniform over the wave
 #pragma unroll
-  for (int i = 0; i < kDepth; ++i)
-    if (s0 < nsl && rp + i * step < ng) load(rp + i * step, ring[i]);  // uniform
-  if (s0 < nsl) {  // uniform over the wave
+    for (int i = 0; i < kDepth; ++i) load(rp + i * step, ring[i]);
     double xd[SL][kTok4][8];
     uint32_t keep[SL];  // past the row's end: zeros
 #pragma unroll
@@ -114,36 +118,40 @@ __device__ __forceinline__ void rows_sums(int cnt, RowOf&& row_of, const uint4* 
         }
       }
     }
-    for (int q0 = rp; q0 < ng; q0 += kDepth * step) {
+    auto multiply = [&](int q, const uint4 (&v)[SL]) __attribute__((always_inline)) {
+      double acc[kTok4];
 #pragma unroll
-      for (int i = 0; i < kDepth; ++i) {
-        const int q = q0 + i * step;
-        if (q < ng) {  // uniform
-          double acc[kTok4];
+      for (int f = 0; f < kTok4; ++f) acc[f] = 0.0;
 #pragma unroll
-          for (int f = 0; f < kTok4; ++f) acc[f] = 0.0;
+      for (int j = 0; j < SL; ++j) {
+        const uint4 u = v[j];
+        const uint32_t wd[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
 #pragma unroll
-          for (int j = 0; j < SL; ++j) {
-            const uint4 u = ring[i][j];
-            const uint32_t wd[4] = {u.x & keep[j], u.y & keep[j], u.z & keep[j], u.w & keep[j]};
+        for (int e = 0; e < 8; ++e) {
+          const double wf = (double)((e & 1) != 0 ? bf16_hi(wd[e / 2]) : bf16_lo(wd[e / 2]));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const double wf = (double)((e & 1) != 0 ? bf16_hi(wd[e / 2]) : bf16_lo(wd[e / 2]));
-#pragma unroll
-              for (int f = 0; f < kTok4; ++f) acc[f] = __builtin_amdgcn_mfma_f64_4x4x4f64(wf, xd[j][f][e], acc[f], 0, 0, 0);
-            }
-          }
-          if (q + kDepth * step < ng) load(q + kDepth * step, ring[i]);
-#pragma unroll
-          for (int f = 0; f < kTok4; ++f) {  // row l / 16, token l % 4: the four blocks of columns
-            double v = acc[f] + dpp_move<0x124, 0xF>(0.0, acc[f]);
-            v += dpp_move<0x128, 0xF>(0.0, v);
-            if ((lane & 12) == 0)
-              red[(((size_t)(w & (ps - 1)) * kMaxGroups + q) * kTok4 + f) * 16 + (lane >> 4) * 4 + (lane & 3)] = v;
-          }
+          for (int f = 0; f < kTok4; ++f) acc[f] = __builtin_amdgcn_mfma_f64_4x4x4f64(wf, xd[j][f][e], acc[f], 0, 0, 0);
         }
       }
+#pragma unroll
+      for (int f = 0; f < kTok4; ++f) {  // row l / 16, token l % 4: the four blocks of columns
+        double t = acc[f] + dpp_move<0x124, 0xF>(0.0, acc[f]);
+        t += dpp_move<0x128, 0xF>(0.0, t);
+        if ((lane & 12) == 0)
+          red[(((size_t)(w & (ps - 1)) * kMaxGroups + q) * kTok4 + f) * 16 + (lane >> 4) * 4 + (lane & 3)] = t;
+      }
+    };
+    int q0 = rp;
+    for (; q0 + kDepth * step < ng; q0 += kDepth * step) {  // uniform
+#pragma unroll
+      for (int i = 0; i < kDepth; ++i) {
+        multiply(q0 + i * step, ring[i]);  // (all of this round's groups are there)
+        load(q0 + (kDepth + i) * step, ring[i]);
+      }
     }
+#pragma unroll
+    for (int i = 0; i < kDepth; ++i)
+      if (q0 + i * step < ng) multiply(q0 + i * step, ring[i]);  // uniform
   }
   HIRE_TS(16);
 }
