@@ -7,8 +7,9 @@
 //                  (row, coefficient) list of the second layer
 //   k_refine_w2    the same with the second layer behind it, where the selected rows are few enough: several workgroups per
 //                  token, each with some columns of y
+//   k_refine_values  the same where the values are to be rounded from 64 bits and not only selected by them: several workgroups
+//                  per token, each with some of the values; k_exact_values over the list where these are many
 //
-// and, where the values are to be rounded from 64 bits and not only selected by them, k_exact_values over the list.
 // The selections are chains of dependent steps on one compute unit: a barrier-separated section costs about its instruction
 // count per thread times 16 cycles (four waves share a SIMD), so what counts is the number of sections and of passes
 // over the register-resident row.  The window histogram (fast_select.h) is anchored at an a-priori bound of the
@@ -309,6 +310,12 @@ __device__ __forceinline__ void refine_token(const RefineParams& p, int b, bool 
   __syncthreads();
 }
 
+// Where a kernel leaves a compute unit for it, one more workgroup lists the candidates meanwhile.
+__device__ __forceinline__ void list_candidates(const RefineParams& p, RefineShared& L) {
+  const int n = list_bitmap<kSelThreads>(p.bitmap, (p.N + 31) / 32, p.cand_out, p.cand_cap, L.sh);
+  if (threadIdx.x == 0 && p.n_cand_out) *p.n_cand_out = n;
+}
+
 // Entries [t0, t1) of the packed ones -> the caller's columns.
 __device__ __forceinline__ void write_selected(const RefineParams& p, int b, const RefineShared& L, int t0, int t1, uint2* list) {
   for (int t = t0 + (int)threadIdx.x; t < t1; t += kSelThreads) {
@@ -325,9 +332,8 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   __shared__ RefineShared L;
   extern __shared__ uint4 tok_sh[];
   const int b = (int)blockIdx.x;
-  if (b == p.B) {  // one more workgroup lists the candidates meanwhile
-    const int n = list_bitmap<kSelThreads>(p.bitmap, (p.N + 31) / 32, p.cand_out, p.cand_cap, L.sh);
-    if (threadIdx.x == 0 && p.n_cand_out) *p.n_cand_out = n;
+  if (b == p.B) {
+    list_candidates(p, L);
     return;
   }
   refine_token<LOADS>(p, b, true, tok_sh, L);
@@ -335,54 +341,26 @@ __global__ __launch_bounds__(kSelThreads) void k_refine(RefineParams p) {
   HIRE_TS(47);
 }
 
-// The same selection and the second layer in one kernel: a workgroup has 8 LPR columns of one token, selects for it (every
-// workgroup of a token does) and adds up the selected rows from the list in its own LDS.  Against k_refine and k_w2_list it saves
-// a boundary and the lists' way through memory, and pays for the values and the band's rows being read by every slice's workgroup.
-// Bound by the selection's chain (8.4 us at the ~1B shape), then by the rows (38 MB from HBM for 16 tokens in 7).  A workgroup
-// fills a compute unit (89 registers, sixteen waves), so that there is no place for one more that lists the candidates: all of
-// them do, 64 units each, behind their columns.
-template <int LPR>
-__global__ __launch_bounds__(kSelThreads) void k_refine_w2(RefineParams p, const uint16_t* __restrict__ W2, float* __restrict__ y) {
-  constexpr int kCols = 8 * LPR, FL = 4;
-  __shared__ RefineShared L;
-  extern __shared__ uint4 dyn_sh[];  // the token; then the waves' sums
-  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int N = p.N, k = p.k, d = p.d;
-  const int slices = (d + kCols - 1) / kCols, n_items = slices * p.B;
-  const int item = (int)(blockIdx.x & 7) * ((n_items + 7) / 8) + (int)(blockIdx.x >> 3);
-  if (item >= n_items) return;  // uniform: the last dies' shares may be short
-  const int slice = item / p.B, b = item % p.B;
-  // the candidates' bits, a word per thread: the workgroups share out the list of them
-  const int words = (N + 31) / 32;
-  const uint32_t word = p.bitmap[min(tid, words - 1)];
-  const uint32_t bits = tid < words ? word : 0u;
-  const int upto = wave_scan_incl(__popc(bits));
-  if (lane == kWave - 1) L.cand_cnt[w] = upto;
-  refine_token<4>(p, b, slice == 0, dyn_sh, L);
-  const uint2* entries = reinterpret_cast<const uint2*>(L.win);
-  const int sub = lane % LPR, first = w * (kWave / LPR) + lane / LPR;
-  const int colc = min(slice * kCols + sub * 8, d - 8);
-  float acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  add_listed_rows<LPR, FL, kSelWaves>(W2 + colc, d, k, first, [&](int t) { return make_uint2(entries[min(t, k - 1)].x, t < k ? entries[min(t, k - 1)].y : 0u); }, acc);
-  HIRE_TS(48);
-  float* red = reinterpret_cast<float*>(dyn_sh);  // [kSelWaves][kCols]; the token was last read ahead of a barrier
-  fold_lanes<LPR>(acc);
-  if (lane < LPR) {
-    float4* dst = reinterpret_cast<float4*>(&red[w * kCols + sub * 8]);
-    dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+// Otherwise the list of the candidates is shared out over its workgroups, 64 units each.
+// The bits come a word per thread (N <= 32768): issue() at the kernel's start, count() once they are surely there, write() behind
+// a barrier.
+struct CandidateShare {
+  uint32_t bits;
+  int upto;  // bits of the wave's words up to this lane's
+  bool shared;
+  __device__ __forceinline__ void issue(const RefineParams& p, int padded) {
+    shared = p.cand_out != nullptr && (int)gridDim.x == padded;  // uniform
+    if (shared) bits = p.bitmap[min((int)threadIdx.x, (p.N + 31) / 32 - 1)];
   }
-  __syncthreads();
-  if (tid < kCols && slice * kCols + tid < d) {
-    float s = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kSelWaves; ++u) s += red[u * kCols + tid];
-    y[(size_t)b * d + slice * kCols + tid] = s;
+  __device__ __forceinline__ void count(const RefineParams& p, RefineShared& L) {
+    if (!shared) return;
+    if ((int)threadIdx.x >= (p.N + 31) / 32) bits = 0u;
+    upto = wave_scan_incl(__popc(bits));
+    if (lane_id() == kWave - 1) L.cand_cnt[threadIdx.x / kWave] = upto;
   }
-  write_selected(p, b, L, (int)((long long)k * slice / slices), (int)((long long)k * (slice + 1) / slices), nullptr);
-  if (p.cand_out != nullptr) {
+  __device__ __forceinline__ void write(const RefineParams& p, const RefineShared& L, int item, int n_items) const {
+    if (!shared) return;
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id()), words = (p.N + 31) / 32;
     const int cnt = wave_scan_incl(lane < kSelWaves ? L.cand_cnt[lane] : 0);
     const int ahead = w > 0 ? __builtin_amdgcn_readlane(cnt, w - 1) : 0;
     for (int pair = item; 2 * pair < words; pair += n_items) {
@@ -393,8 +371,98 @@ __global__ __launch_bounds__(kSelThreads) void k_refine_w2(RefineParams p, const
       const int at = ahead + __builtin_amdgcn_readlane(upto, l) - __popc(b0) + mask_prefix(m);
       if ((m >> lane & 1ull) != 0ull && at < p.cand_cap) p.cand_out[at] = pair * kWave + lane;
     }
-    if (item == 0 && tid == 0 && p.n_cand_out) *p.n_cand_out = __builtin_amdgcn_readlane(cnt, kSelWaves - 1);
+    if (item == 0 && threadIdx.x == 0 && p.n_cand_out) *p.n_cand_out = __builtin_amdgcn_readlane(cnt, kSelWaves - 1);
   }
+};
+
+// The same selection with all values from 64 bits: several workgroups per token, each of which selects and forms the values of its
+// share of the entries, a wave a row at a time.  Against k_exact_values behind k_refine it saves a boundary and the round trip
+// through the list.
+template <int LOADS>
+__global__ __launch_bounds__(kSelThreads) void k_refine_values(RefineParams p, int parts) {
+  __shared__ RefineShared L;
+  extern __shared__ uint4 tok_sh[];
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int n_items = parts * p.B, padded = (n_items + 7) / 8 * 8;
+  if ((int)blockIdx.x == padded) {
+    list_candidates(p, L);
+    return;
+  }
+  const int item = (int)(blockIdx.x & 7) * (padded / 8) + (int)(blockIdx.x >> 3);
+  if (item >= n_items) return;  // uniform
+  const int part = item / p.B, b = item % p.B;
+  CandidateShare cand;
+  cand.issue(p, padded);
+  refine_token<LOADS>(p, b, part == 0, tok_sh, L);
+  cand.count(p, L);
+  const uint4* tok = p.d <= kRefineTokenMax ? tok_sh : reinterpret_cast<const uint4*>(p.x + (size_t)b * p.d);
+  const int t1 = (int)((long long)p.k * (part + 1) / parts);
+  for (int t = (int)((long long)p.k * part / parts) + w; t < t1; t += kSelWaves) {  // uniform
+    const int unit = __builtin_amdgcn_readfirstlane((int)reinterpret_cast<const uint2*>(L.win)[t].x);
+    const float v = (float)wave_row_dot<true>(p.W + (size_t)unit * p.d, tok, p.d);
+    if (lane == 0) {
+      const size_t o = (size_t)b * p.k + t;
+      p.list_out[o] = make_uint2((uint32_t)unit, __float_as_uint(v));
+      if (p.idx_out) p.idx_out[o] = unit;
+      if (p.val_out) p.val_out[o] = v;
+    }
+  }
+  lds_barrier();
+  cand.write(p, L, item, n_items);
+  HIRE_TS(47);
+}
+
+// The same selection and the second layer in one kernel: a workgroup has 8 LPR columns of one token, selects for it (every
+// workgroup of a token does) and adds up the selected rows from the list in its own LDS.  Against k_refine and k_w2_list it saves
+// a boundary and the lists' way through memory, and pays for the values and the band's rows being read by every slice's workgroup.
+// Bound by the selection's chain (8.4 us at the ~1B shape), then by the rows (38 MB from HBM for 16 tokens in 7).
+template <int LPR>
+__global__ __launch_bounds__(kSelThreads) void k_refine_w2(RefineParams p, const uint16_t* __restrict__ W2, float* __restrict__ y) {
+  constexpr int kCols = 8 * LPR, FL = 4;
+  __shared__ RefineShared L;
+  extern __shared__ uint4 dyn_sh[];  // the token; then the waves' sums
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int k = p.k, d = p.d;
+  const int slices = (d + kCols - 1) / kCols, n_items = slices * p.B, padded = (n_items + 7) / 8 * 8;
+  if ((int)blockIdx.x == padded) {
+    list_candidates(p, L);
+    return;
+  }
+  const int item = (int)(blockIdx.x & 7) * (padded / 8) + (int)(blockIdx.x >> 3);
+  if (item >= n_items) return;  // uniform: the last dies' shares may be short
+  const int slice = item / p.B, b = item % p.B;
+  CandidateShare cand;
+  cand.issue(p, padded);
+  refine_token<4>(p, b, slice == 0, dyn_sh, L);
+  const uint2* entries = reinterpret_cast<const uint2*>(L.win);
+  const int sub = lane % LPR, first = w * (kWave / LPR) + lane / LPR;
+  const int colc = min(slice * kCols + sub * 8, d - 8);
+  float acc[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
+  auto entry = [&](int t) {
+    const uint2 e = entries[min(t, k - 1)];
+    return make_uint2(e.x, t < k ? e.y : 0u);
+  };
+  add_listed_rows<LPR, FL, kSelWaves>(W2 + colc, d, k, first, entry, acc);
+  HIRE_TS(48);
+  float* red = reinterpret_cast<float*>(dyn_sh);  // [kSelWaves][kCols]; the token was last read ahead of a barrier
+  fold_lanes<LPR>(acc);
+  if (lane < LPR) {
+    float4* dst = reinterpret_cast<float4*>(&red[w * kCols + sub * 8]);
+    dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  }
+  cand.count(p, L);
+  __syncthreads();
+  if (tid < kCols && slice * kCols + tid < d) {
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kSelWaves; ++u) s += red[u * kCols + tid];
+    y[(size_t)b * d + slice * kCols + tid] = s;
+  }
+  write_selected(p, b, L, (int)((long long)k * slice / slices), (int)((long long)k * (slice + 1) / slices), nullptr);
+  cand.write(p, L, item, n_items);
   HIRE_TS(49);
 }
 
@@ -575,16 +643,43 @@ hipError_t launch_exact_values(uint2* lists, float* val_out, const uint16_t* W, 
   return launch(k_exact_values, dim3((items + 7) / 8 * 8), dim3(kEvThreads), 0, s, lists, val_out, W, x, B, k, d);
 }
 
+// Workgroups of a kernel whose items are shared out over the dies, and one for the list of the candidates if there is a compute
+// unit for it.
+static int refine_grid(int items, const RefineParams& p) {
+  const int padded = (items + 7) / 8 * 8;
+  return padded + (p.cand_out != nullptr && padded < 256 ? 1 : 0);
+}
+
+// Workgroups per token of k_refine_values, up to sixteen entries each where they are few: as many as one round has.  0: a
+// wave would have more than three rows, one after the other, and k_exact_values, whose waves have one each, is faster.  us per step with
+// that / with k_refine_values: d = 2048, k = 819 of 16384 units, 5 tokens 46.7 / 45.0, 6 49.1 / 47.3, 8 51.5 / 49.9, 12 (2.4 rows per wave) 56.4 /
+// 55.1, 15 (3) 57.5 / 57.3; k = 409 of 8191, 16 43.2 / 42.5, 33 (3.3) 54.3 / 54.3, 64 (6.4) 62.8 / 63.7; d = 4096, k = 409 of 8192, 5 54.7 / 53.5,
+// 15 65.7 / 63.9; d = 1024, k = 400 of 8000, 8 32.4 / 30.6; k = 819 of 16383, 8 42.1 / 41.1, 33 (6.6) 57.7 / 60.7; d = 800, k = 251 of 5003, 8 28.7 /
+// 27.6, 33 (2) 36.2 / 35.5; d = 512, k = 1200 of 24000, 8 47.0 / 46.3, 64 75.0 / 80.2; d = 256, k = 51 of 1024, 15 25.0 / 23.7.  Requesting a
+// wave's next two rows ahead, with the last one again past the end, was slower up to three rows (d = 800, 8 tokens 30.3).
+static int refine_value_parts(int B, int k) {
+  return B * k > 3 * 256 * kSelWaves ? 0 : max(1, min(256 / B, (k + kSelWaves - 1) / kSelWaves));
+}
+
 hipError_t launch_refine(const RefineParams& p, hipStream_t s) {
   if (!batch_select_supported(p.N, p.k) || p.stride % 4 != 0 || reinterpret_cast<uintptr_t>(p.vals) % 16 != 0 || p.d % 8 != 0)
     return hipErrorInvalidValue;
   const size_t lds = p.d <= kRefineTokenMax ? (size_t)p.d * 2 : 0;
-  static std::atomic<size_t> raised_to[2] = {};
+  static std::atomic<size_t> raised_to[4] = {};
   auto go = [&](auto kernel, std::atomic<size_t>& raised) {
     if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
       return e;
     return launch(kernel, dim3(p.B + (p.cand_out != nullptr ? 1 : 0)), dim3(kSelThreads), lds, s, p);
   };
+  const int parts = refine_value_parts(p.B, p.k);
+  if (p.exact_values && parts > 0) {
+    auto values = [&](auto kernel, std::atomic<size_t>& raised) {
+      if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised); e != hipSuccess)
+        return e;
+      return launch(kernel, dim3(refine_grid(parts * p.B, p)), dim3(kSelThreads), lds, s, p, parts);
+    };
+    return p.N <= 16384 ? values(k_refine_values<4>, raised_to[2]) : values(k_refine_values<8>, raised_to[3]);
+  }
   const hipError_t e = p.N <= 16384 ? go(k_refine<4>, raised_to[0]) : go(k_refine<8>, raised_to[1]);
   return e == hipSuccess && p.exact_values ? launch_exact_values(p.list_out, p.val_out, p.W, p.x, p.B, p.k, p.d, s) : e;
 }
@@ -597,7 +692,7 @@ static hipError_t refine_w2_launch(const RefineParams& p, const uint16_t* W2, fl
   if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(k_refine_w2<LPR>), lds, raised_to); e != hipSuccess)
     return e;
   const int items = (p.d + 8 * LPR - 1) / (8 * LPR) * p.B;
-  return launch(k_refine_w2<LPR>, dim3((items + 7) / 8 * 8), dim3(kSelThreads), lds, s, p, W2, y);
+  return launch(k_refine_w2<LPR>, dim3(refine_grid(items, p)), dim3(kSelThreads), lds, s, p, W2, y);
 }
 
 // A workgroup fills a compute unit, and every one of them selects: one round of 256, of the narrowest slices that fit.

@@ -1,5 +1,5 @@
-"""The refining selection with the second layer in one kernel (16 tokens and more whose selected rows are few enough), against the
-oracle: slices of 64 to 512 columns with a remainder, lists that end inside, at and behind a batch of rows, the shared-out list
+"""The refining selection with the second layer in one kernel (16 tokens and more whose selected rows are few enough) and with its
+values rounded from 64 bits, against the oracle: slices of 64 to 512 columns with a remainder, lists that end inside, at and behind a batch of rows, the shared-out list
 of the candidates, tokens that the list in LDS does not settle; and infinite second-layer weights."""
 import numpy as np
 import pytest
@@ -38,6 +38,26 @@ def test_against_the_oracle(hire, oracle, d, N, B, k, kp):
     x[1, :] = 0                                    # threshold among the zeros
     x[3:6, :] = x[2, :]
     T.check_ffn(layer, scorer, L, x, k, kp)
+
+
+@pytest.mark.parametrize("d,N,B,k,kp", [
+    (64, 777, 5, 3, 9),            # a workgroup per token, fewer entries than waves
+    (96, 1091, 8, 512, 600),       # a round of workgroups, none left for the candidates' list: all of them share it
+    (800, 2003, 16, 250, 400),     # 256 workgroups again
+    (2080, 1501, 7, 33, 200),      # rows of more than one request of a wave
+    (64, 16390, 6, 300, 1500),     # more units than 16384
+    (8224, 1000, 5, 20, 100),      # a token that is not in LDS
+    (64, 2001, 33, 372, 800), (64, 2001, 33, 373, 800),  # three rows per wave, and more: the kernel behind the list
+])
+def test_values_from_64_bits_against_the_oracle(hire, oracle, d, N, B, k, kp):
+    print(f"ffn_step d={d} N={N} B={B} k={k} k'={kp}", flush=True)
+    L = I.ffn_layer(1220 + d, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    x = I.tokens(1221 + B, B, d)
+    x[1, :] = 0
+    got, want = T.check_ffn(layer, scorer, L, x, k, kp)
+    # one rounding of a 64-bit sum: half an ulp, and the difference between two orders of the sum
+    assert (np.abs(got["topk_val"].astype(np.float64) - want["topk_val"]) <= np.abs(want["topk_val"]) * (0.5 + 1e-3) * 2.0 ** -23).all()
 
 
 def test_infinite_weights_stay_in_their_columns(hire, oracle):
