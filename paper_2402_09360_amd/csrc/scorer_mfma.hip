@@ -27,6 +27,7 @@ struct ScorerBatch {
   int32_t* acc_out;  // optional [B, N]
   uint32_t* wgmax;   // optional [B, kWgMaxSlots]
   int seg_steps;     // steps of 128 codes of a K segment, whose codes of all tokens are in LDS
+  int parts;         // PARTS: of the tokens
 };
 
 enum ScorerSource { kCodes, kBf16, kF32 };
@@ -50,16 +51,25 @@ enum ScorerSource { kCodes, kBf16, kF32 };
 //
 // kBf16, kF32: the workgroup quantises the tokens itself.  VECS: 16-byte vectors (of bf16 values, or of codes) of a token
 // per lane.
-template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
+// PARTS: a workgroup has sixteen of the tokens, one to quantise per wave, and so many more rows; the workgroups with the same rows
+// are on one die, whose L2 has the codes.
+template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS, bool PARTS = false>
 __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p) {
   constexpr int NW = RW * KW, NT = kWave * NW, kTok = 16 * CT, kRows = 16 * RT * RW;
   static_assert(RT == 1 || KW == 1, "tiles of a wave");
   static_assert(SRC == kCodes || KW > 1, "vocabularies: a kernel in front quantises");
+  static_assert(!PARTS || (SRC == kBf16 && CT == 1), "a token per wave");
   extern __shared__ uint4 xs[];  // [kTok][8 seg_steps + 1]: a token row's first chunk in another bank than its neighbours'
   const int tid = (int)threadIdx.x, lane = lane_id(), jl = lane & 15, g = lane >> 4;
   // known to be uniform: a matrix-core instruction must never sit behind a branch that is lowered to lane masking
   const int w = __builtin_amdgcn_readfirstlane(wave_id()), rw = w % RW, kw = w / RW;
-  const int B = p.B, N = p.N, cpr = p.d / 32;  // 16-byte chunks per packed row
+  int first_tile = (int)blockIdx.x, tok0 = 0;
+  if constexpr (PARTS) {
+    const int at = (int)blockIdx.x % (8 * p.parts);
+    first_tile = (int)blockIdx.x / (8 * p.parts) * 8 + at % 8;
+    tok0 = at / 8 * kTok;
+  }
+  const int B = PARTS ? min(p.B - tok0, kTok) : p.B, N = p.N, cpr = p.d / 32;  // 16-byte chunks per packed row
   const int steps = (cpr + 3) / 4, seg_steps = p.seg_steps, nseg = (steps + seg_steps - 1) / seg_steps;
   const int per = (seg_steps + KW - 1) / KW, nblk = (per + P - 1) / P;  // steps, requests of a wave per segment
   const int xstride = 8 * seg_steps + 1;
@@ -107,7 +117,7 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
       }
   };
   auto load_values = [&](int q0) __attribute__((always_inline)) {
-    const uint4* x4 = reinterpret_cast<const uint4*>(p.tok.x);
+    const uint4* x4 = reinterpret_cast<const uint4*>(p.tok.x) + (size_t)tok0 * nvec;
 #pragma unroll
     for (int q = 0; q < kAhead; ++q)
 #pragma unroll
@@ -161,17 +171,17 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
             if (i < 2 * segq) reinterpret_cast<uint2*>(xs + t * xstride)[i] = counts ? codes : make_uint2(0, 0);
             __builtin_amdgcn_sched_barrier(0);  // (registers)
           }
-        if (p.tok.sumabs != nullptr && blockIdx.x == 0) {
+        if (p.tok.sumabs != nullptr && first_tile == 0) {
           sabs = wave_sum(sabs);
-          if (lane == 0) p.tok.sumabs[t] = sabs;
+          if (lane == 0) p.tok.sumabs[tok0 + t] = sabs;
         }
       }
     }
   };
   // every wave of the workgroup goes through the same tiles, segments and requests
   auto stage_if_due = [&](int tile, int seg, int blk) __attribute__((always_inline)) {
-    if (blk == 0 && (nseg > 1 || tile == (int)blockIdx.x)) {
-      if (seg > 0 || tile != (int)blockIdx.x) {
+    if (blk == 0 && (nseg > 1 || tile == first_tile)) {
+      if (seg > 0 || tile != first_tile) {
         load_tokens(seg);
         lds_barrier();  // the readers of the segment before are done
       }
@@ -226,7 +236,27 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
       for (int i = (int)blockIdx.x * NT + tid; i < p.tok.zero_words; i += (int)gridDim.x * NT) p.tok.zero_ptr[i] = 0u;
       if (blockIdx.x == 0) general_header_check(static_cast<GeneralHeader*>(p.tok.header), p.tok.sig);
     }
-    const int tile = (int)blockIdx.x, j = tile * kRows + rw * 16 + jl;
+    constexpr int kUnits = CT * 4;
+    // one of every KW of the workgroup's sums per wave
+    auto finish_tile = [&](const int* red, int tile, float sj) __attribute__((always_inline)) {
+      const int j = tile * kRows + rw * 16 + jl;
+#pragma unroll
+      for (int u0 = 0; u0 < kUnits; u0 += KW) {
+        const int u = u0 + kw, t = u / 4 * 16 + 4 * g + u % 4;
+        if (u < kUnits) {  // uniform
+          int sum = 0;
+#pragma unroll
+          for (int k = 0; k < KW; ++k) sum += red[((k * RW + rw) * kUnits + u) * kWave + lane];
+          sum >>= 4;
+          if (t < B && j < N) {
+            p.keys[(size_t)(tok0 + t) * p.stride + j] = key_of(sum, sj);
+            if (p.acc_out) p.acc_out[(size_t)(tok0 + t) * N + j] = sum;
+          }
+        }
+      }
+    };
+    if (PARTS && first_tile * kRows >= N) return;  // uniform: the last dies' shares may be short
+    const int tile = first_tile;
     Request q;
     for (int seg = 0; seg < nseg; ++seg)
       for (int blk = 0; blk < nblk; ++blk) {
@@ -236,24 +266,10 @@ __global__ __launch_bounds__(64 * RW * KW) void k_scorer_int4_mfma(ScorerBatch p
       }
     lds_barrier();  // the codes' place takes the waves' sums
     int* red = reinterpret_cast<int*>(xs);
-    constexpr int kUnits = CT * 4;
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) red[(w * kUnits + u) * kWave + lane] = acc[0][u / 4][u % 4];
     lds_barrier();
-#pragma unroll
-    for (int u0 = 0; u0 < kUnits; u0 += KW) {
-      const int u = u0 + kw, t = u / 4 * 16 + 4 * g + u % 4;
-      if (u < kUnits) {  // uniform
-        int sum = 0;
-#pragma unroll
-        for (int k = 0; k < KW; ++k) sum += red[((k * RW + rw) * kUnits + u) * kWave + lane];
-        sum >>= 4;
-        if (t < B && j < N) {
-          p.keys[(size_t)t * p.stride + j] = key_of(sum, q.sj[0]);
-          if (p.acc_out) p.acc_out[(size_t)t * N + j] = sum;
-        }
-      }
-    }
+    finish_tile(red, tile, q.sj[0]);
   } else {
     float wmax[CT][4];
 #pragma unroll
@@ -358,12 +374,28 @@ int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 // against 50.8) a wave has three or four long tokens, one after the other.  The intermediate of the int4 low-rank scorer is short
 // (r <= 1024), and a rounding kernel goes with it: always.  Vocabularies: 256 workgroups of eight waves would take as long as the
 // kernel in front.
+
+// Sixteen tokens to a workgroup: a wave quantises one token, whatever the batch, and the rows' codes are read once more for every
+// sixteen tokens, from the L2 of one die.  Where one round of workgroups has a single tile of up to 128 rows and 128 KB of codes each; three
+// parts of 16384 rows would leave two tiles to some (33 tokens of 2048: 62.9 -> 65.3 us per step, 64 68.1 -> 69.7), and twice as many codes
+// as that take as long as the kernel in front (33 of 4096, 8192 rows 66.2 -> 68.9).  us per step with the kernels that quantise all tokens
+// or have them quantised in front / with parts: d = 2048, 16384 rows, 20 tokens 54.3 / 54.8, 24 55.5 / 55.0, 32 59.2 / 57.8; d = 1024, 8000 rows,
+// 20 29.2 / 29.2, 24 30.1 / 29.6, 32 32.1 / 30.7, 33 34.7 / 33.1, 64 37.9 / 35.1; d = 800, 5003 rows, 22 31.2 / 30.7, 33 35.4 / 33.1, 64 39.9 / 37.3; d = 512,
+// 4000 rows, 33 24.8 / 24.6, 64 28.0 / 25.7; d = 256, 1024 rows, 33 26.3 / 25.0, 64 29.2 / 26.1; d = 1504, 12000 rows, 32 43.9 / 42.2.
+// Rows of a workgroup, at least:
+static int scorer_part_rows(int B, int N) { return (N * ((B + 15) / 16) + 255) / 256; }
+static bool scorer_mfma_parts(int B, int N, int d) {
+  static_assert(8192 * 4 / 256 <= 128 && 128 * 1024 <= 256 << 10, "more than 32 tokens that scorer_mfma_rows quantises: rows beyond 8192 only");
+  const int rows = scorer_part_rows(B, N), tile = rows <= 16 ? 16 : (rows <= 32 ? 32 : (rows <= 64 ? 64 : 128));
+  return B > 20 && d <= 2048 && rows <= 128 && (long long)tile * d <= 256 << 10;
+}
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
   if (N >= kVocabMinRows) return false;
+  if (!f32 && scorer_mfma_parts(B, N, d)) return true;
   return f32 ? d <= 1024 : d <= (B <= 32 ? 2048 : (B <= 40 ? 1024 : 512));
 }
 
-template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS>
+template <int CT, int RT, int RW, int KW, int P, int SRC, int VECS, bool PARTS = false>
 static hipError_t scorer_mfma_launch(ScorerBatch& p, int grid, hipStream_t s) {
   const int steps = (p.d / 32 + 3) / 4, nseg = SRC == kCodes ? (steps + kSegSteps - 1) / kSegSteps : 1;
   if (SRC != kCodes && p.d > 512 * VECS) return hipErrorInvalidValue;
@@ -371,7 +403,7 @@ static hipError_t scorer_mfma_launch(ScorerBatch& p, int grid, hipStream_t s) {
   const size_t codes = (size_t)16 * CT * (8 * p.seg_steps + 1) * sizeof(uint4);
   const size_t sums = KW > 1 ? (size_t)RW * KW * CT * 4 * kWave * sizeof(int) : 0;
   const size_t lds = codes > sums ? codes : sums;
-  auto kernel = k_scorer_int4_mfma<CT, RT, RW, KW, P, SRC, VECS>;
+  auto kernel = k_scorer_int4_mfma<CT, RT, RW, KW, P, SRC, VECS, PARTS>;
   static std::atomic<size_t> raised_to{0};
   if (const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, raised_to); e != hipSuccess)
     return e;
@@ -385,8 +417,23 @@ template <int CT, int P, int SRC, int VECS>
 static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
   if (p.N > 16384) return scorer_mfma_launch<CT, 1, 8, 2, 2, SRC, VECS>(p, (p.N + 127) / 128, s);
   if (p.N > 8192) return scorer_mfma_launch<CT, 1, 4, 4, P, SRC, VECS>(p, (p.N + 63) / 64, s);
-  if (p.N > 4096) return scorer_mfma_launch<CT, 1, 2, 8, 2, SRC, VECS>(p, (p.N + 31) / 32, s);
-  return scorer_mfma_launch<CT, 1, 1, 16, 1, SRC, VECS>(p, (p.N + 15) / 16, s);
+  if constexpr (CT == 4 && SRC == kBf16) {
+    return hipErrorInvalidValue;  // (scorer_mfma_parts)
+  } else {
+    if (p.N > 4096) return scorer_mfma_launch<CT, 1, 2, 8, 2, SRC, VECS>(p, (p.N + 31) / 32, s);
+    return scorer_mfma_launch<CT, 1, 1, 16, 1, SRC, VECS>(p, (p.N + 15) / 16, s);
+  }
+}
+
+// The same for sixteen tokens per workgroup, the workgroups of eight tiles and all parts after one another.
+template <int VECS>
+static hipError_t scorer_parts_rows(ScorerBatch& p, hipStream_t s) {
+  const int rows = scorer_part_rows(p.B, p.N);
+  auto grid = [&](int tile) { return ((p.N + tile - 1) / tile + 7) / 8 * 8 * p.parts; };
+  if (rows > 64) return scorer_mfma_launch<1, 1, 8, 2, 4, kBf16, VECS, true>(p, grid(128), s);
+  if (rows > 32) return scorer_mfma_launch<1, 1, 4, 4, 4, kBf16, VECS, true>(p, grid(64), s);
+  if (rows > 16) return scorer_mfma_launch<1, 1, 2, 8, 2, kBf16, VECS, true>(p, grid(32), s);
+  return scorer_mfma_launch<1, 1, 1, 16, 1, kBf16, VECS, true>(p, grid(16), s);
 }
 
 template <int CT>
@@ -401,6 +448,11 @@ static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
     return scorer_mfma_launch<CT, 1, kVocabWaves, 1, 4, kCodes, 2>(p, vocab_blocks(p.N), s);
   }
   if (p.tok.x == nullptr) return scorer_mfma_rows<CT, 2, kCodes, 2>(p, s);
+  if (!p.tok.f32 && scorer_mfma_parts(p.B, p.N, p.d)) {
+    p.parts = (p.B + 15) / 16;
+    if (p.d <= 1024) return scorer_parts_rows<2>(p, s);
+    return scorer_parts_rows<4>(p, s);
+  }
   if (p.tok.f32) return p.d <= 512 ? scorer_mfma_rows<CT, 2, kF32, 1>(p, s) : scorer_mfma_rows<CT, 2, kF32, 2>(p, s);
   if (p.d <= 512) return scorer_mfma_rows<CT, 2, kBf16, 1>(p, s);
   if constexpr (CT == 4)
@@ -414,7 +466,7 @@ hipError_t launch_scorer_int4_mfma(const uint32_t* q4, const float* scale, const
   if (tok.x != nullptr && !scorer_mfma_quantises(B, N, d, tok.f32)) return hipErrorInvalidValue;
   const MultiRegion mr = multi_of(hr, B);
   ScorerBatch p{reinterpret_cast<const uint4*>(q4), scale, tok, B, N, d, relu, keys, stride, acc,
-                N >= kVocabMinRows ? mr.wgmax : nullptr, 0};
+                N >= kVocabMinRows ? mr.wgmax : nullptr, 0, 1};
   if (B <= 16) return scorer_mfma_tokens<1>(p, s);
   if (B <= 32) return scorer_mfma_tokens<2>(p, s);
   return scorer_mfma_tokens<4>(p, s);

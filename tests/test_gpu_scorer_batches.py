@@ -49,6 +49,19 @@ def test_ffn_rows(hire, oracle, d, N, B):
     T.check_ffn(layer, scorer, L, _tokens(901 + B, B, d), max(1, N // 40), max(2, N // 8))
 
 
+@pytest.mark.parametrize("d,N,B", [
+    (96, 15, 21), (96, 700, 33), (1056, 2048, 32), (32, 1366, 64),   # sixteen tokens per workgroup: tiles of 16 rows, the last part
+    (160, 2049, 21), (64, 2731, 48), (1024, 2100, 49),               # of one token and of sixteen; 32 rows
+    (2048, 4097, 21), (544, 5461, 48), (64, 8000, 17),               # 64; (17 tokens take no parts)
+    (2048, 8193, 25), (1056, 8192, 49), (32, 10922, 33),             # 128
+    (32, 10923, 33), (2080, 1000, 33), (32, 16385, 21)])             # past each limit
+def test_parts_of_sixteen_tokens(hire, oracle, d, N, B):
+    log(f"ffn_step d={d} N={N} B={B}")
+    L = I.ffn_layer(940 + d, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    T.check_ffn(layer, scorer, L, _tokens(941 + B, B, d), max(1, N // 40), max(2, N // 8))
+
+
 @pytest.mark.parametrize("d,N,r,B", [(576, 1500, 544, 64), (576, 4100, 512, 64), (1536, 1537, 64, 32), (1056, 2090, 1024, 17), (64, 8200, 32, 48),
                                      (96, 20003, 96, 18), (64, 16390, 64, 3)])
 def test_ffn_rows_lrq(hire, oracle, d, N, r, B):
