@@ -25,29 +25,34 @@ __device__ __forceinline__ TokenScale token_scale(float amax) {
   t.plain = t.sx > 0x1p-100f && t.sx < 0x1p100f && (__float_as_uint(t.sx) & 0x7FFFFFu) != 0x7FFFFFu;
   return t;
 }
-// Eight values; *sum8: the sum of the codes' absolute values.
+// Eight values; *sum8: the sum of the codes' absolute values.  Adding 1.5 2^23 rounds to whole numbers, half to even, and leaves
+// them in the lowest bits in two's complement; bytes are gathered and summed four at a time.  With rintf, a conversion and an
+// addition per value instead, us per step with that / this at the ~1B shape: 16 tokens 49.3 / 49.1, 20 54.6 / 54.2, the int4 low-rank scorer
+// with 16 51.3 / 51.0; four tokens 38.15 / 38.05.
 __device__ __forceinline__ uint2 quantise8(const uint4& v, const TokenScale& t, float* sum8) {
   const uint32_t ud[4] = {v.x, v.y, v.z, v.w};
   float r[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float f = (e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), y = f * t.rs;
-    r[e] = rintf(fmaf(fmaf(-y, t.sx, f), t.rs, y));
+    r[e] = fmaf(fmaf(-y, t.sx, f), t.rs, y);
   }
   if (__ballot(!t.plain) != 0ull) {
     asm volatile("");  // keeps the compiler from dividing always and selecting
 #pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = rintf(__fdiv_rn((e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), t.sx));
+    for (int e = 0; e < 8; ++e) r[e] = __fdiv_rn((e & 1) != 0 ? bf16_hi(ud[e / 2]) : bf16_lo(ud[e / 2]), t.sx);
   }
-  uint32_t packed[2] = {0u, 0u};
-  *sum8 = 0.0f;
+  uint32_t packed[2], sum = 0u;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    r[e] = fminf(fmaxf(r[e], -127.0f), 127.0f);
-    *sum8 += fabsf(r[e]);
-    packed[e / 4] = __builtin_amdgcn_cvt_pk_u8_f32(r[e] + 128.0f, e & 3, packed[e / 4]);  // (whole numbers)
+  for (int h = 0; h < 2; ++h) {
+    uint32_t b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = __float_as_uint(fminf(fmaxf(r[4 * h + e], -127.0f), 127.0f) + 0x1.8p23f);
+    packed[h] = __builtin_amdgcn_perm(b[1], b[0], 0x0C0C0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000C0Cu);
+    sum = __builtin_amdgcn_sad_u8(packed[h] ^ 0x80808080u, 0x80808080u, sum);
   }
-  return make_uint2(packed[0] ^ 0x80808080u, packed[1] ^ 0x80808080u);
+  *sum8 = (float)sum;
+  return make_uint2(packed[0], packed[1]);
 }
 
 // Adds to acc what four rows of packed int4 codes (lane l: sixteen bytes of row l % 4) have in common with four tokens
