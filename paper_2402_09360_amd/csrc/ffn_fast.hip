@@ -679,10 +679,9 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   HIRE_TS(10);
   // every load of the selection goes out here, before the first wait
   const int n = p.N >> gs;
-  const bool hist_ok = p.fr->clean > 0u && p.fr->beyond1 == 0u;
-  const uint32_t anchor1 = p.fr->anchor1, anchor2 = p.fr->anchor2;
   WinRegs<kGT> wr;
   wr.issue(p.fr->hist1);
+  const uint32_t clean = p.fr->clean, beyond1 = p.fr->beyond1, anchor1 = p.fr->anchor1, anchor2 = p.fr->anchor2;
   const int u0 = g * kOwnUnits;                // first unit of the workgroup
   const int entry = (u0 + lane) >> gs;         // lane's unit, or its group
   const bool valid = u0 + lane < p.N;
@@ -692,6 +691,7 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
   token_to_lds(p.x, xvecs, xtok);
   if (tid == 0) sh.list_n = 0;
   if (tid < kOwnUnits) unit_h[tid] = 0.0;
+  const bool hist_ok = (clean > 0u) & (beyond1 == 0u);  // (both asked for at once: no branch between the two)
   kr.finish();
   HIRE_TS(11);
   uint64_t taken = 0ull, rows = 0ull;  // units of the workgroup: shortlisted; whose rows are read

@@ -315,10 +315,8 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
   int opens = 0;                       // (unit, token) pairs that settle the difference
   const int n = p.N >> gs;
   if (sparse) {
-    const int clean = (int)p.fr->clean;
     uint4 wr[kMine];
     const int tw = w / kWPT, wt = w % kWPT;  // the token whose window this wave helps to walk, its part of it
-    const bool hist_ok = tw < clean && p.fr[min(tw, B - 1)].beyond1 == 0u;
     {
       const uint4* hist = reinterpret_cast<const uint4*>(p.fr[min(tw, B - 1)].hist1);
 #pragma unroll
@@ -330,6 +328,9 @@ __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) 
 #pragma unroll
     for (int t = 0; t < TT; ++t) own[t] = reinterpret_cast<const K*>(p.keys)[min(t, B - 1) * p.stride + min(entry, n - 1)];
     const uint32_t a1 = p.fr[min(lane, B - 1)].anchor1;  // lane t: token t's
+    const int clean = (int)p.fr->clean;
+    const uint32_t beyond1 = p.fr[min(tw, B - 1)].beyond1;
+    const bool hist_ok = (tw < clean) & (beyond1 == 0u);  // (both asked for at once, behind the window: no branch between the two)
     if (tid < TT) slot[tid] = -1;
     // walk: sums of 256 counters, the chunk that holds the k'-th key, its lane, its counter
     int s[kMine];
