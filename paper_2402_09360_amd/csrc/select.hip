@@ -733,7 +733,7 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
 // than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
 // largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
 // Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
-// Measured for 16 rows of 256000, k = 1024, rank order: 18.9 us per call (20.6 with the lengths of all rows' lists in one
+// Measured for 16 rows of 256000, k = 1024, rank order: 17.2 us per call (20.6 with the lengths of all rows' lists in one
 // line); the histogram route below took 45, of it 9 for
 // the ranking pass.
 constexpr int kTkGroups = 4096;
@@ -849,6 +849,7 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
   __shared__ AmbEntry chosen[kTkMaxK];
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x;
   const int n = (int)*counts.of(b);
+  const AmbEntry first = mr.amb[(size_t)b * kAmbCap + tid];  // asked for with the number that says whether it counts: 0.13 us
   int32_t* idx = idx_out + (size_t)b * k;
   float* val = val_out ? val_out + (size_t)b * k : nullptr;
   if (b == 0 && tid == 0 && !multi_hist_ok(mr.hdr, B)) {  // the workspace has taken this layout
@@ -872,7 +873,8 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
     if (tid == 0) atomicAdd(&mr.hdr->fallbacks, 1u);
     return;
   }
-  for (int i = tid; i < n; i += kSelThreads) list[i] = mr.amb[(size_t)b * kAmbCap + i];
+  if (tid < n) list[tid] = first;
+  for (int i = tid + kSelThreads; i < n; i += kSelThreads) list[i] = mr.amb[(size_t)b * kAmbCap + i];
   bucket_ranks<uint32_t>(
       n, [&](int i) { return list[i].okey; },
       [&](int o, int i) { return list[o].okey > list[i].okey || (list[o].okey == list[i].okey && list[o].idx < list[i].idx); },
