@@ -340,51 +340,77 @@ __device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, 
   return base;
 }
 
-// Ranks of n <= kBucketMax entries in a total order whose keys are get(id), larger ahead, id < n; ahead(a, b) says
-// whether entry a comes before entry b (consulted between entries of one bin only).  The keys between the smallest and
-// the largest go to 2048 equal bins, a scan gives every bin's first rank, the entries are listed bin by bin and each
-// counts those ahead of it inside its bin: a few instead of n comparisons per entry (all of them only where all keys
-// crowd into one bin).  emit(id, rank) is called once per entry.  bins: 2 * kSelBins + kBucketMax words of LDS.
-// All threads call this; keys and entries must be visible (the first step is a barrier).
-constexpr int kBucketMax = 4096;
-template <typename K, typename Get, typename Ahead, typename Emit>
-__device__ __forceinline__ void bucket_ranks(int n, Get&& get, Ahead&& ahead, uint32_t* bins, SelShared& sh, Emit&& emit) {
-  static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
-  uint32_t* cursor = bins + kSelBins;
-  int* list = reinterpret_cast<int*>(bins + 2 * kSelBins);
+// Ranks of n <= PER * 1024 items, of which thread t holds the t-th, the (1024 + t)-th and so on, in a total order whose keys are
+// key(item), larger ahead; ahead(a, b) says whether item a comes before item b (consulted between items of one bin only).  The keys
+// between the smallest and the largest go to 4096 equal bins; the addition that counts a bin's items gives each its place in the
+// bin, a scan gives every bin's first rank, the items are listed bin by bin and each counts those ahead of it inside its bin: a few
+// instead of n comparisons per item (all of them only where all keys crowd into one bin).  emit(item, rank) is called once per
+// item.  bins: kRankBins words of LDS, 16-byte aligned; list: n items of LDS.  All threads call this; what key() reads of LDS must be
+// visible, and sh.red_a and sh.red_b free.
+// Bound: the chain of barriers and LDS round trips on one compute unit.  16 rows of 256000, in us per call of topk_select: k = 1024
+// 17.4 (2048 bins, the items' numbers listed, by a second pass of additions) -> 15.6 (this, 2048 bins) -> 15.1 (4096 bins: the keys
+// are densest at the threshold); k = 2048 27.1 -> 21.2 -> 18.8.
+constexpr int kRankBins = 4096;
+template <typename K, typename T, int PER, typename Key, typename Ahead, typename Emit>
+__device__ __forceinline__ void bucket_ranks(int n, const T (&own)[PER], Key&& key, Ahead&& ahead, uint32_t* bins, T* list,
+                                             SelShared& sh, Emit&& emit) {
+  static_assert(kRankBins == 4 * kSelThreads && PER * kSelThreads < 65536, "four bins per thread; first rank and length in one word");
   const int tid = (int)threadIdx.x;
+  uint4* quad = reinterpret_cast<uint4*>(bins) + tid;
+  *quad = make_uint4(0, 0, 0, 0);
   K lo = ~(K)0, hi = 0;
-  bins[tid] = bins[tid + kSelThreads] = 0u;
-  __syncthreads();
-  for (int id = tid; id < n; id += kSelThreads) {
-    const K k = get(id);
-    lo = k < lo ? k : lo;
-    hi = k > hi ? k : hi;
-  }
-  wg_minmax(lo, hi, sh);
-  const int shift = hi > lo ? max(0, ilog2_u64((uint64_t)(hi - lo)) + 1 - 11) : 0;
-  auto bin_of = [&](K k) { return (int)((hi - k) >> shift); };
-  for (int id = tid; id < n; id += kSelThreads) atomicAdd(&bins[bin_of(get(id))], 1u);
-  __syncthreads();
-  const int c0 = (int)bins[2 * tid], c1 = (int)bins[2 * tid + 1];
-  const int start = wg_scan_incl(c0 + c1, sh) - (c0 + c1);  // a barrier inside: every thread has read its counters
-  bins[2 * tid] = cursor[2 * tid] = (uint32_t)start;
-  bins[2 * tid + 1] = cursor[2 * tid + 1] = (uint32_t)(start + c0);
-  __syncthreads();
-  for (int id = tid; id < n; id += kSelThreads) list[atomicAdd(&cursor[bin_of(get(id))], 1u)] = id;
-  __syncthreads();
-  for (int id = tid; id < n; id += kSelThreads) {
-    const int b = bin_of(get(id)), first = (int)bins[b], end = (int)cursor[b];
-    int rank = first;
-    for (int u0 = first; u0 < end; u0 += 4) {  // four LDS reads in flight
-      int other[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) other[j] = list[min(u0 + j, end - 1)];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rank += u0 + j < end && ahead(other[j], id) ? 1 : 0;
+  for (int u = 0; u < PER; ++u)
+    if (u * kSelThreads + tid < n) {
+      const K k = key(own[u]);
+      lo = k < lo ? k : lo;
+      hi = k > hi ? k : hi;
     }
-    emit(id, rank);
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  if (lane_id() == 0) {
+    sh.red_a[wave_id()] = (unsigned long long)lo;
+    sh.red_b[wave_id()] = (unsigned long long)hi;
   }
+  __syncthreads();
+  lo = wave_min((K)sh.red_a[lane_id() % kSelWaves]);
+  hi = wave_max((K)sh.red_b[lane_id() % kSelWaves]);
+  const int shift = hi > lo ? max(0, ilog2_u64((uint64_t)(hi - lo)) + 1 - 12) : 0;
+  int bin[PER], at[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * kSelThreads + tid < n) {
+      bin[u] = (int)((hi - key(own[u])) >> shift);
+      at[u] = (int)atomicAdd(&bins[bin[u]], 1u);
+    }
+  __syncthreads();
+  const uint4 c = *quad;
+  const uint32_t sum = c.x + c.y + c.z + c.w;
+  const uint32_t s0 = (uint32_t)wg_scan_incl((int)sum, sh) - sum, s1 = s0 + c.x, s2 = s1 + c.y, s3 = s2 + c.z;
+  *quad = make_uint4(s0 << 16 | c.x, s1 << 16 | c.y, s2 << 16 | c.z, s3 << 16 | c.w);
+  __syncthreads();
+  uint32_t run[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * kSelThreads + tid < n) {
+      run[u] = bins[bin[u]];
+      list[(run[u] >> 16) + at[u]] = own[u];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * kSelThreads + tid < n) {
+      const int first = (int)(run[u] >> 16), end = first + (int)(run[u] & 0xFFFFu);
+      int rank = first;
+      for (int i0 = first; i0 < end; i0 += 4) {  // four LDS reads in flight
+        T other[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) other[j] = list[min(i0 + j, end - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rank += i0 + j < end && ahead(other[j], own[u]) ? 1 : 0;
+      }
+      emit(own[u], rank);
+    }
 }
 
 }  // namespace hire

@@ -293,30 +293,27 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
 
   // ---- rank order: position of each selected entry among the k (value desc, index asc) ----
   constexpr int kPerThread = kRankMax / kSelThreads;
-  int* rk_rank = rk_pos + k;  // small k: partial ranks from several threads per entry are added up here
-  const bool spread = k <= kSelThreads / 2;
-  if (spread)
-    for (int t = (int)threadIdx.x; t < k; t += kSelThreads) rk_rank[t] = 0;
+  // Up to a wave of entries: one lane each, every wave compares it with a sixteenth of the others and adds that up.  Beyond that by
+  // bins of the keys.  16 rows of 1000, in us per call: 64 entries 5.9 against 6.9; 100 of them 7.3, with two lanes' work per lane,
+  // against 7.0, 256 11.0 against 7.1, 512 27.9 against 11.3.
+  int* rk_rank = rk_pos + k;
+  const bool spread = k <= kWave;
+  if (spread && (int)threadIdx.x < k) rk_rank[threadIdx.x] = 0;
   __syncthreads();
   if (spread) {
-    const int padded = (k + kWave - 1) / kWave * kWave;
-    const int slices = kSelThreads / padded, group = kSelThreads / slices;
-    const int per = (k + slices - 1) / slices;
-    const int t = (int)threadIdx.x % group, sl = (int)threadIdx.x / group;
-    if (t < k && sl < slices) {
-      const K mine = rk_key[t];
-      const int u_lo = sl * per, u_hi = min(k, u_lo + per);
-      int rank = 0;
-      for (int u0 = u_lo; u0 < u_hi; u0 += 8) {  // eight LDS reads in flight
-        K other[8];
+    constexpr int kOthers = kWave / kSelWaves;
+    const int t = min(lane, k - 1);
+    const K mine = rk_key[t];
+    K other[kOthers];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) other[j] = rk_key[min(u0 + j, k - 1)];
+    for (int j = 0; j < kOthers; ++j) other[j] = rk_key[min(w * kOthers + j, k - 1)];
+    int rank = 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)  // the list is in index order, so u < t is "lower index"
-          rank += (u0 + j < u_hi) && ((other[j] > mine) || (other[j] == mine && u0 + j < t));
-      }
-      atomicAdd(&rk_rank[t], rank);
+    for (int j = 0; j < kOthers; ++j) {
+      const int u = w * kOthers + j;  // the list is in index order, so u < t is "lower index"
+      rank += u < k && (other[j] > mine || (other[j] == mine && u < t)) ? 1 : 0;
     }
+    if (lane < k) atomicAdd(&rk_rank[t], rank);
     __syncthreads();
   }
   int my_rank[kPerThread];
@@ -341,12 +338,15 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
   };
   if (spread) {
     if ((int)threadIdx.x < k) put((int)threadIdx.x, rk_rank[threadIdx.x]);
-  } else {  // many entries: by bins of their keys (1024 entries: 3 us; every entry against every other: 66)
-    static_assert(2 * kSelBins + kBucketMax <= kHistWindow && kRankMax <= kBucketMax, "the bins reuse the window's memory");
+  } else {
+    static_assert(kRankBins + kRankMax <= kHistWindow, "the bins and the list reuse the window's memory");
+    int own[kPerThread];
+#pragma unroll
+    for (int u = 0; u < kPerThread; ++u) own[u] = u * kSelThreads + (int)threadIdx.x;
     bucket_ranks<K>(
-        k, [&](int t) { return rk_key[t]; },
+        k, own, [&](int t) { return rk_key[t]; },
         [&](int o, int t) { return rk_key[o] > rk_key[t] || (rk_key[o] == rk_key[t] && o < t); },  // index order
-        win, sh, put);
+        win, reinterpret_cast<int*>(win) + kRankBins, sh, put);
   }
   HIRE_TS(34);
   if (!p.prob_out) return;
@@ -373,7 +373,7 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
 template <typename V, int ITEMS>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelectParams p) {
   __shared__ SelShared sh;
-  __shared__ uint32_t win[kHistWindow];
+  __shared__ __align__(16) uint32_t win[kHistWindow];
   extern __shared__ unsigned long long dyn[];
   select_row<V, ITEMS>(p, (int)blockIdx.x, sh, dyn, win);
 }
@@ -733,14 +733,13 @@ __global__ __launch_bounds__(kSelThreads) void k_union_compact(int B, MultiRegio
 // than the list holds (many equal ones) is selected from memory by the last kernel.  Interleaved groups, because the
 // largest entries of rows with an order of their own are neighbours.  k = 2048 is half of the groups: 2840 entries.
 // Bound: one read of the rows (16 x 256000: 16 MB) and the chain of the final kernel on one compute unit per row.
-// Measured for 16 rows of 256000, k = 1024, rank order: 17.2 us per call (20.6 with the lengths of all rows' lists in one
-// line); the histogram route below took 45, of it 9 for
-// the ranking pass.
+// Measured for 16 rows of 256000, k = 1024, rank order: 15.2 us per call (1.7 more with the lengths of all rows' lists in
+// one line); the histogram route below took 45.
 constexpr int kTkGroups = 4096;
 constexpr int kTkMaxK = 2048;
 constexpr int kTkMaxGroups = 256;
 constexpr int kTkKeys = 16;  // keys per thread of the gathering kernel
-static_assert(kTkGroups == kWgMaxSlots && kAmbCap == kBucketMax, "the maxima and the list use the histogram route's places");
+static_assert(kTkGroups == kWgMaxSlots && kAmbCap % kSelThreads == 0, "the maxima and the list use the histogram route's places");
 static_assert(kTkMaxK * (4 + 2 * 4) <= kAmbCap * (int)sizeof(AmbEntry), "rank order from memory: the list's LDS");
 
 // The lengths of the rows' lists, in the place of the bitmaps that the longer sequence clears for itself: kilobytes apart, as
@@ -844,7 +843,7 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
                                                           int rank_order, MultiRegion mr, TkCounts counts,
                                                           int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
   __shared__ SelShared sh;
-  __shared__ __align__(16) uint32_t bins[kHistWindow];
+  __shared__ __align__(16) uint32_t bins[kHistWindow];  // the ranking's; the window of a row selected from memory
   __shared__ __align__(16) AmbEntry list[kAmbCap];
   __shared__ AmbEntry chosen[kTkMaxK];
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x;
@@ -873,27 +872,33 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
     if (tid == 0) atomicAdd(&mr.hdr->fallbacks, 1u);
     return;
   }
-  if (tid < n) list[tid] = first;
-  for (int i = tid + kSelThreads; i < n; i += kSelThreads) list[i] = mr.amb[(size_t)b * kAmbCap + i];
+  AmbEntry own[kAmbCap / kSelThreads];
+  own[0] = first;
+#pragma unroll
+  for (int u = 1; u < kAmbCap / kSelThreads; ++u)
+    if (u * kSelThreads < n) own[u] = mr.amb[(size_t)b * kAmbCap + u * kSelThreads + tid];  // uniform; places past n hold old entries
   bucket_ranks<uint32_t>(
-      n, [&](int i) { return list[i].okey; },
-      [&](int o, int i) { return list[o].okey > list[i].okey || (list[o].okey == list[i].okey && list[o].idx < list[i].idx); },
-      bins, sh, [&](int i, int rank) {
+      n, own, [](const AmbEntry& e) { return e.okey; },
+      [](const AmbEntry& o, const AmbEntry& e) { return o.okey > e.okey || (o.okey == e.okey && o.idx < e.idx); }, bins, list, sh,
+      [&](const AmbEntry& e, int rank) {
         if (rank >= k) return;
         if (rank_order) {
-          idx[rank] = list[i].idx;
-          if (val) val[rank] = key_value(list[i].okey);
+          idx[rank] = e.idx;
+          if (val) val[rank] = key_value(e.okey);
         } else {
-          chosen[rank] = list[i];
+          chosen[rank] = e;
         }
       });
   if (rank_order) return;
   __syncthreads();
+  AmbEntry mine[kTkMaxK / kSelThreads];
+#pragma unroll
+  for (int u = 0; u < kTkMaxK / kSelThreads; ++u) mine[u] = chosen[min(u * kSelThreads + tid, k - 1)];
   bucket_ranks<uint32_t>(
-      k, [&](int i) { return ~(uint32_t)chosen[i].idx; }, [&](int o, int i) { return chosen[o].idx < chosen[i].idx; }, bins, sh,
-      [&](int i, int rank) {
-        idx[rank] = chosen[i].idx;
-        if (val) val[rank] = key_value(chosen[i].okey);
+      k, mine, [](const AmbEntry& e) { return ~(uint32_t)e.idx; },
+      [](const AmbEntry& o, const AmbEntry& e) { return o.idx < e.idx; }, bins, list, sh, [&](const AmbEntry& e, int rank) {
+        idx[rank] = e.idx;
+        if (val) val[rank] = key_value(e.okey);
       });
 }
 
