@@ -94,6 +94,7 @@ struct StepBuffers {
   size_t bytes;
 };
 
+constexpr int kSoftmaxOwnMaxRow = 65536;  // longer unions of a softmax step keep the refining selection's buffers in place of h
 constexpr int kKeysInRegisters = 16384;  // rows that the route for few tokens and the selection of fp64 values hold
 bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilterMinBatch || s.cap_u > kKeysInRegisters); }
 
@@ -103,7 +104,9 @@ bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilter
 // workgroup in rounds.  The maxima are counted for a union of 1.5 k' too, about what tokens of one query leave; beyond 32 tokens
 // it is larger, and ranking dearer.  40000 classes of d = 512, us per step, fp64 / refined: k' = 1536, k = 128, eight tokens
 // 60.9 / 46.4, fifteen 85.7 / 51.7; k' = 256, k = 128, three (48 maxima) 34 / 89, eight (128) 37 / 396, fifteen (240) 40 / 46;
-// k' = 1024, k = 512, eight 68 / 1929, fifteen 77 / 107, 64 (1024) 205 / 127.  Two tokens: k' = 1024, k = 16 36.4 / 37.4.
+// k' = 1024, k = 512, eight 68 / 1929, fifteen 77 / 107, 64 (1024) 205 / 127.  Two tokens: k' = 1024, k = 16 36.4 / 37.4.  Long
+// unions: 256000 classes of d = 2048, 64 tokens, k' = 1200, k = 100 681 / 200, k' = 1536, k = 128 814 / 217; 100000 of 512,
+// k' = 1100, k = 64 278 / 77.  The longest is what 256 workgroups of the filter stage list in LDS.
 bool softmax_filter(int B, int cap_u, int k, int kprime) {
   if (B < 3 || cap_u > kSoftmaxRefineMaxRow || k > (B < 16 ? kSoftmaxRefineMaxK / 2 : kSoftmaxRefineMaxK)) return false;
   const int blocks = filter_rank_blocks(cap_u), each = (kprime + kprime / 2 + blocks - 1) / blocks;
@@ -170,6 +173,17 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.zero_words = s.words + kCounters;
   s.cand = c.take<int32_t>(s.cap_u);
   const bool sm_filter = !ffn && gs == 0 && softmax_filter(B, s.cap_u, k, kprime);
+  auto sm_buffers = [&](Carver& at) {
+    s.xnorm = at.take<float>(HIRE_MAX_BATCH);
+    s.wnorm_tiles = at.take<float>(filter_rank_blocks(s.cap_u));
+    s.maxima = at.take<float>((size_t)B * kFilterMaxima);
+    s.refine_slots = at.take<char>(softmax_refine_slot_bytes(B));
+    s.hf_stride = (s.cap_u + 3) / 4 * 4;
+    s.hf = at.take<float>((size_t)B * s.hf_stride);
+  };
+  // Long unions keep all of that in the place of the fp64 logits (37 KB and 4 bytes per class for each token, in 8 per class), which
+  // this route does not form: they ask for no more workspace than the route through those.
+  const bool sm_in_h = sm_filter && s.cap_u > kSoftmaxOwnMaxRow;
   s.all_rows = ffn_filter(s, B) && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
                (int4_like || N <= kSelectFilterMaxF64) && filter_all_rows(B, d, N, kprime);
   if (ffn_filter(s, B)) {
@@ -178,15 +192,14 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.hf_stride = s.key_stride;  // rows start at multiples of 16 bytes
     s.hf = static_cast<float*>(s.keys);  // nobody reads the keys any more when the filter stage runs
   } else if (sm_filter) {
-    s.xnorm = c.take<float>(HIRE_MAX_BATCH);
-    s.wnorm_tiles = c.take<float>(filter_rank_blocks(s.cap_u));
-    s.maxima = c.take<float>((size_t)B * kFilterMaxima);
-    s.refine_slots = c.take<char>(softmax_refine_slot_bytes(B));
-    s.hf_stride = (s.cap_u + 3) / 4 * 4;
-    s.hf = c.take<float>((size_t)B * s.hf_stride);
+    if (!sm_in_h) sm_buffers(c);
   }
   const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
   s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
+  if (sm_in_h) {
+    Carver in_h(s.h);
+    sm_buffers(in_h);
+  }
   // all_rows: the filter stage writes its values while the keys are read.  h is the selection's scratch only after that, so
   // the keys or the values go there: the fp32 keys, whose own place is too small for the scratch, or else the values
   s.h_refine = s.h;

@@ -586,7 +586,8 @@ __global__ __launch_bounds__(256 * TG * KS) void k_select_filter(KeysSelect ks, 
 // candidates, and with fewer maxima than k everything would have to be recomputed.
 // Measured at d = 2048, 64 tokens, 57600 of 256000 classes (236 MB): 65 us (3.6 TB/s); with a workgroup per tile, each locating
 // its own 64 candidates first, 92.
-constexpr int kFrMaxRows = 256;  // candidates per workgroup
+constexpr int kFrMaxRows = 512;  // candidates per workgroup
+static_assert(kFrMaxRows * 256 >= kSoftmaxRefineMaxRow, "256 workgroups hold the longest row");
 constexpr int fr_stages(int TT) { return TT >= 4 ? 3 : 4; }
 
 template <int TT, int TG, int KS>

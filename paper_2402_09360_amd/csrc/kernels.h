@@ -171,7 +171,7 @@ hipError_t launch_select_f64(const SelectParams& p, int B, hipStream_t s);
 // entry within 2 * err_c * xnorm[b] * *wnorm_max below the k-th largest stored value is recomputed in fp64 and the k
 // largest of those are returned in rank order (idx_out through map, val_out, prob_out).  Rows of at most
 // kSoftmaxRefineMaxRow fp32 entries, k <= kSoftmaxRefineMaxK.
-constexpr int kSoftmaxRefineMaxRow = 65536, kSoftmaxRefineMaxK = 512;
+constexpr int kSoftmaxRefineMaxRow = 131072, kSoftmaxRefineMaxK = 512;
 size_t softmax_refine_slot_bytes(int B);
 hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s);
 

@@ -1087,7 +1087,7 @@ __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4
 // one thread per entry.  With 1024 slots instead of 2048 the parts of k = 512 overflow: 2048 shortlisted classes per token,
 // 16 tokens 168 instead of 125 us per step, 1150 instead of 119 where the tokens share most of them.
 constexpr int kSmList = 2048;
-static_assert(kSoftmaxRefineMaxRow / kSelThreads == 64, "one bit of a 64-bit mask per value of a thread");
+constexpr int kSmSpan = 64 * kSelThreads;  // entries that one 64-bit mask per thread stands for
 
 // Two kernels.  k_softmax_parts: every workgroup of a token takes an equal part of the row, finds the bound from the
 // maxima itself, recomputes its own part's entries at or above the mark and leaves them in its slots (position order).
@@ -1238,6 +1238,20 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
   }
   unsigned long long pending = 0ull;  // bit i: value i has to be recomputed and has not been listed yet
   int ready = 0;                      // entries the parts have recomputed
+  int first = 0, end = 0;             // the span of the row that the mask stands for, the row's length (0: the parts served it)
+  uint32_t mark_key = 1u;
+  const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
+  auto scan = [&]() {  // value i of thread t is entry first + t + 1024 i
+    const int n = min(end - first, kSmSpan);
+    for (int i0 = 0; kSelThreads * i0 < n; i0 += 16) {  // uniform
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = vals[first + min(tid + kSelThreads * (i0 + u), n - 1)];  // clamped, unconditional
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (order_key(v[u]) >= mark_key && tid + kSelThreads * (i0 + u) < n) pending |= 1ull << (i0 + u);
+    }
+  };
   if (!__syncthreads_or(have_n[0] > cap || have_n[1] > cap)) {
     static_assert(kOwn == 2, "two slots per thread");
     const uint64_t vm[kOwn] = {__ballot(tid % cap < have_n[0]), __ballot((tid + kSelThreads) % cap < have_n[1])};
@@ -1258,8 +1272,7 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
   } else {
     const float mine_max = p.maxima[(size_t)b * kFilterMaxima + min(tid, p.n_maxima - 1)];
     float tile_norm = p.wnorm_tiles[min(tid, p.wnorm_n - 1)];  // wnorm_n <= 256
-    const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
-    const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
+    end = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
     {
       uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
       z[0] = z[1] = make_uint4(0, 0, 0, 0);
@@ -1285,16 +1298,8 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
     const uint32_t floor_key = wk.found ? (anchor - (uint32_t)wk.slot) << kFineShift : 0u;
     const double mark = (floor_key != 0u ? (double)key_value(floor_key) : 0.0) -
                         2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001;
-    const uint32_t mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
-    // value i of thread t is entry t + 1024 i
-    for (int i0 = 0; kSelThreads * i0 < n; i0 += 16) {  // uniform
-      float v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = vals[min(tid + kSelThreads * (i0 + u), n - 1)];  // clamped, unconditional
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (order_key(v[u]) >= mark_key && tid + kSelThreads * (i0 + u) < n) pending |= 1ull << (i0 + u);
-    }
+    mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
+    scan();
     HIRE_TS(52);
   }
   int have = 0, cur = 0;  // entries of the best list so far, and which of its two copies holds them
@@ -1307,7 +1312,7 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
       const int i = __builtin_ctzll(pending);
       const int slot = atomicAdd(&l_n, 1);
       if (slot >= room) break;
-      l_pos[slot] = tid + kSelThreads * i;
+      l_pos[slot] = first + tid + kSelThreads * i;
       pending &= pending - 1ull;
     }
     __syncthreads();
@@ -1364,7 +1369,10 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
     }
     have = min(k, m);
     cur ^= 1;
-    if (!__syncthreads_or(pending != 0ull)) break;
+    if (__syncthreads_or(pending != 0ull)) continue;
+    if (end - first <= kSmSpan) break;  // uniform
+    first += kSmSpan;
+    scan();
   }
   HIRE_TS(55);
   // the k survivors in rank order; softmax: exp(z - zmax) / sum
