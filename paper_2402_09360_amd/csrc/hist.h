@@ -148,7 +148,7 @@ constexpr int kSm1Shift = 16;
 constexpr int kSm1WinBins = 2048;
 constexpr int kSm1MaxRow = 262144;      // longest vocabulary of the short sequence
 constexpr int kSm1MaxShortlist = 1536;  // largest k'
-constexpr int kSm1MaxK = 64;            // largest k
+constexpr int kSm1MaxK = 128;           // largest k
 __device__ __forceinline__ int sm1_anchor_bin(float smax, int d) {
   return (int)(order_key((float)(889 * d) * smax) >> kSm1Shift);
 }
