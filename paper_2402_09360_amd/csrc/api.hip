@@ -109,7 +109,7 @@ bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilter
 // k' = 1100, k = 64 278 / 77.  The longest is what 256 workgroups of the filter stage list in LDS.
 bool softmax_filter(int B, int cap_u, int k, int kprime) {
   if (B < 3 || cap_u > kSoftmaxRefineMaxRow || k > (B < 16 ? kSoftmaxRefineMaxK / 2 : kSoftmaxRefineMaxK)) return false;
-  const int blocks = filter_rank_blocks(cap_u), each = (kprime + kprime / 2 + blocks - 1) / blocks;
+  const int blocks = min(filter_tiles(cap_u), 256), each = (kprime + kprime / 2 + blocks - 1) / blocks;
   return 2 * blocks >= k && 4 * blocks * min(4, (each + 3) / 4) >= (B > 32 ? 3 : 5) * k;
 }
 
