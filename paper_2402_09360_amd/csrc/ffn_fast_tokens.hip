@@ -288,7 +288,7 @@ __device__ __forceinline__ Cut<K> streaming_cut(const K* keys, int n, int k, Sel
 // K: the keys' bit patterns.  TT: tokens rounded up to four or eight.
 // Measured at the ~1B shape and four tokens, from the first wave's start: 4.2 us until the rows are known, the 9600 rows of the
 // union until 13.2 (40 MB, 4.5 TB/s), 1.2 for the outputs; half the workgroups have ended by 14.3 and the last by 17.6, one
-// that has two keys of threshold bins to settle (19.8 when they were settled ahead of the rows).  The kernel 17.7 us (20.1).
+// that has two keys of threshold bins to settle (19.8 when they were settled ahead of the rows).  The kernel 17.3 us.
 template <typename K, int TT>
 __global__ __launch_bounds__(kTT) void k_fast_gather_tokens(FastGatherTokens p) {
   constexpr int kWPT = kTW / TT, kChunks = kWin / 256, kMine = kChunks / kWPT;  // 256 counters per wave and load

@@ -18,7 +18,7 @@
 // Batches are taken in bundles of four tokens that share every loaded row, which goes through the matrix cores against
 // all four (rows_mfma.h); larger batches run bundle after bundle (rows re-read through the caches) with the union flags
 // carried along.  Most batches, and long shards, take the sequence of ffn_shard_batch.hip instead.  Measured at the ~1B shape, 256 shards and
-// four tokens: 24.6 us, 35.5 with the scores (5.3) and exact values (about 13) on the vector units, token after token
+// four tokens: 24.0 us, 35.5 with the scores (5.3) and exact values (about 13) on the vector units, token after token
 // in the first selection (3.2).
 #include "device_utils.h"
 #include "kernels.h"

@@ -82,8 +82,8 @@ __global__ __launch_bounds__(256) void k_gather_dot(const uint16_t* __restrict__
 // once 256 workgroups exist.  The dispatcher places workgroup i on die i % 8, and a die takes an eighth of the
 // (slice, token) pairs, slice by slice, so that the tokens share a slice's rows in one L2 and every die has as much to do
 // (whole slices per die left dies idle where slices do not come in eights: 49 tokens of d = 288, k = 1949 12.2 us, now
-// 10.2; 64 of d = 640, k = 1200 15.9, now 13.7).  Measured at d = 2048, k = 819 of 16384 units: 9.6 us for 16 tokens, 20.0
-// for 64, against 12.2 for a kernel with partial sums and a reducing one at 16 and 23.7 for 256-column workgroups without
+// 10.2; 64 of d = 640, k = 1200 15.9, now 13.7).  Measured at d = 2048, k = 819 of 16384 units: 19.8 us for
+// 64 tokens (16 take k_refine_w2), against 23.7 for 256-column workgroups without
 // the second batch in flight at 64.
 constexpr int kW2Threads = 512;
 constexpr int kW2Waves = kW2Threads / kWave;
