@@ -150,7 +150,7 @@ __device__ __forceinline__ void rows_sums(int cnt, RowOf&& row_of, const uint4* 
     for (; q0 + kDepth * step < ng; q0 += kDepth * step) {  // uniform
 #pragma unroll
       for (int i = 0; i < kDepth; ++i) {
-        multiply(q0 + i * step, ring[i]);  // (all of this round's groups are there)
+        multiply(q0 + i * step, ring[i]);  // (all groups of this trip are there)
         load(q0 + (kDepth + i) * step, ring[i]);
       }
     }

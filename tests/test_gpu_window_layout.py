@@ -85,3 +85,26 @@ def test_one_token_many_groups_per_workgroup(oracle, d, N, kp, kind):
     layer, scorer = T.make_ffn_layer(L, lowrank=kind == "lowrank")
     print(f"one token, groups, d={d} N={N} k'={kp} {kind}", flush=True)
     T.check_ffn_group(layer, scorer, L, I.tokens(763, 1, d), kp // 16 * 8, kp, 8)
+
+
+@pytest.mark.parametrize("B,d", [(1, 64), (4, 2048), (4, 4096)])  # sixteen, eight and four rows per load
+def test_few_tokens_rows_per_wave_of_the_second_layer(oracle, B, d):
+    """All units selected, all of them one wave's: one to eight loads, whole and not, and more than one trip."""
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    for N in (1, 15, 24, 28, 40, 45, 50, 61, 65, 81, 100, 113, 128, 129, 250):
+        print(f"B={B} d={d} N={N}", flush=True)
+        L = dict(I.ffn_layer(781 + N, d, N))
+        L["w1u"] = L["w1u"] & 0x7FFF  # no activation is zero
+        layer, scorer = T.make_ffn_layer(L)
+        T.check_ffn(layer, scorer, L, I.tokens(782, B, d) & 0x7FFF, N, N)
+
+
+@pytest.mark.parametrize("m1", [1, 300, 700, 900, 1100, 1500, 1700, 2040, 2100])
+def test_one_token_dense_rows_per_wave_of_the_second_layer(oracle, m1):
+    """One to eight loads of dense rows per wave, and a second trip."""
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    print(f"m1={m1}", flush=True)
+    d, N = 64, 512
+    L, D = I.ffn_layer(791, d, N), I.ffn_layer(792, d, m1)
+    layer, scorer = T.make_ffn_layer(L)
+    T.check_ffn_commonpath(layer, scorer, L, (D["w1u"], D["w2u"]), I.tokens(793, 1, d), 64, 128, 8)
