@@ -817,8 +817,8 @@ __global__ __launch_bounds__(kGT) void k_fast_gather(FastGatherParams p) {
 //
 // The selection works on the activations rounded to fp32 (rounding is monotone; the coefficients of the second layer are
 // these values anyway); the keys of the threshold bin, and a selection without histogram, go by the fp64 values.
-// Measured at the ~1B shape: 8.1 us with the reduction over the waves and the lists for the caller in it (9.0 with the lists'
-// keys placed by code unrolled over all of a lane's, whose workgroups were the last to end).  Inside: window walked 1.6,
+// Measured at the ~1B shape: 7.8 us (8.1 with a branch around every load of rows; four tokens 10.8, 12.1), with the reduction over the
+// waves and the lists for the caller in it (9.0 with the lists' keys placed by code unrolled over all of a lane's, whose workgroups were the last to end).  Inside: window walked 1.6,
 // masks 0.6, bin settled 0.5, rows listed 0.5, rows 1.0 (from HBM 2.8), reduction 1.0.
 constexpr int kWT = 1024;
 constexpr int kWW = kWT / kWave;
