@@ -94,7 +94,7 @@ struct StepBuffers {
   size_t bytes;
 };
 
-constexpr int kSoftmaxOwnMaxRow = 65536;  // longer unions of a softmax step keep the refining selection's buffers in place of h
+constexpr int kSoftmaxOwnMaxRow = 65536;  // longer unions of a softmax step keep the refining selection's buffers in others' places
 constexpr int kKeysInRegisters = 16384;  // rows that the route for few tokens and the selection of fp64 values hold
 bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilterMinBatch || s.cap_u > kKeysInRegisters); }
 
@@ -178,12 +178,8 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.wnorm_tiles = at.take<float>(filter_rank_blocks(s.cap_u));
     s.maxima = at.take<float>((size_t)B * kFilterMaxima);
     s.refine_slots = at.take<char>(softmax_refine_slot_bytes(B));
-    s.hf_stride = (s.cap_u + 3) / 4 * 4;
-    s.hf = at.take<float>((size_t)B * s.hf_stride);
   };
-  // Long unions keep all of that in the place of the fp64 logits (37 KB and 4 bytes per class for each token, in 8 per class), which
-  // this route does not form: they ask for no more workspace than the route through those.
-  const bool sm_in_h = sm_filter && s.cap_u > kSoftmaxOwnMaxRow;
+  const bool sm_long = sm_filter && s.cap_u > kSoftmaxOwnMaxRow;
   s.all_rows = ffn_filter(s, B) && !fast && s.key_stride <= 2 * (long long)s.cap_u &&
                (int4_like || N <= kSelectFilterMaxF64) && filter_all_rows(B, d, N, kprime);
   if (ffn_filter(s, B)) {
@@ -191,15 +187,13 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.wnorm_tiles = c.take<float>(filter_tiles(N));
     s.hf_stride = s.key_stride;  // rows start at multiples of 16 bytes
     s.hf = static_cast<float*>(s.keys);  // nobody reads the keys any more when the filter stage runs
-  } else if (sm_filter) {
-    if (!sm_in_h) sm_buffers(c);
+  } else if (sm_filter && !sm_long) {
+    sm_buffers(c);
+    s.hf_stride = (s.cap_u + 3) / 4 * 4;
+    s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
   const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
   s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
-  if (sm_in_h) {
-    Carver in_h(s.h);
-    sm_buffers(in_h);
-  }
   // all_rows: the filter stage writes its values while the keys are read.  h is the selection's scratch only after that, so
   // the keys or the values go there: the fp32 keys, whose own place is too small for the scratch, or else the values
   s.h_refine = s.h;
@@ -217,6 +211,15 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.sm1_ok = !ffn && B == 1 && gs == 0 && int4_like && N > kSingleWgMaxRow && softmax_b1_supported(N, d, 1, 1);
   s.max_ok = gs == 0 && int4_like && N > kSingleWgMaxRow && maxima_select_supported(N);
   if (s.sm1_ok || s.max_ok) s.sm1_slots = c.take<char>(maxima_select_slot_bytes(B, N));
+  // Long unions ask for no more workspace than the route through fp64 logits: the fp32 ones lie in the place of the keys, which nobody
+  // reads any more when the filter stage runs, and the rest (37 KB per token) where the selection of k' had its slots (64 KB), or
+  // behind the fp32 logits where it has none: fp64 keys, and keys of more than 262144 classes, leave 256 KB per token there.
+  if (sm_long) {
+    Carver in_keys(s.keys), in_slots(s.sm1_slots);
+    s.hf_stride = s.cap_u;
+    s.hf = in_keys.take<float>((size_t)B * s.hf_stride);
+    sm_buffers(s.max_ok ? in_slots : in_keys);
+  }
   if (ffn) {
     if (gs > 0) s.pos = c.take<int32_t>((size_t)B * (k >> gs));
     s.list = c.take<uint2>((size_t)B * k);
@@ -1103,6 +1106,8 @@ int hire_softmax_step(const hire_softmax_layer* L, const void* x, int B, int k, 
     sp.wnorm_n = filter_rank_blocks(s.cap_u);
     sp.maxima = s.maxima;
     sp.refine_slots = s.refine_slots;
+    sp.refine_keys = reinterpret_cast<unsigned long long*>(s.h);  // (no fp64 logits are formed otherwise)
+    sp.refine_keys_stride = s.cap_u;
     sp.n_maxima = 4 * filter_rank_blocks(s.cap_u);
     sp.err_c = gather_filter_error(B);
     HIRE_TRY(launch_softmax_refine(sp, B, st));

@@ -130,7 +130,7 @@ struct SelectParams {
   uint32_t* bitmap;         // optional: bit i set (atomic or) for every selected position of any row
   uint32_t* window_misses;  // optional device counter: rows whose window histogram did not give the k-th largest
   // Filter and refine (launch_softmax_refine only): vals are fp32 rows written by launch_filter_ranks, within
-  // err_c |u| |x| of the logits; map lists the rows' classes.  The kernel recomputes in fp64
+  // err_c |u| |x| of the logits; map lists the rows' classes.  The kernels recompute in fp64
   // (<refine_w[map[i], :], refine_x[b, :]>) what can still be among the k largest.
   const uint16_t* refine_w;  // bf16 [rows, refine_d]
   const uint16_t* refine_x;  // bf16 [B, refine_d]
@@ -142,6 +142,8 @@ struct SelectParams {
   const float* maxima;      // [B, kFilterMaxima], n_maxima of them used: largest values of disjoint parts of the row
   int n_maxima;
   void* refine_slots;       // softmax_refine_slot_bytes(B) of scratch
+  unsigned long long* refine_keys;  // [B, refine_keys_stride] of scratch: logits of entries that do not fit the slots
+  long long refine_keys_stride;
   int nonneg;               // != 0: every value is known to be >= 0 (keys and activations after a ReLU); such rows
                             // of 1025..16384 entries in index order take a leaner kernel
   // Second layer: list_out (optional) receives for every row its k << gs selected units in ascending order, as

@@ -1085,15 +1085,24 @@ __device__ __forceinline__ void wave_rows_dot_f64(const uint16_t* const (&row)[4
 // Measured at 64 tokens, 57600 entries: 12.5 + 6.8 us, 16 tokens, 16000 entries: 8.5 + 6.9.  One kernel with one
 // workgroup per token and a histogram of the whole row: 31 and 21 us, half of it the products and a ranking loop of
 // one thread per entry.  With 1024 slots instead of 2048 the parts of k = 512 overflow: 2048 shortlisted classes per token,
-// 16 tokens 168 instead of 125 us per step, 1150 instead of 119 where the tokens share most of them.
+// 16 tokens 168 instead of 125 us per step (when one workgroup recomputed all that overflowed).
 constexpr int kSmList = 2048;
 constexpr int kSmSpan = 64 * kSelThreads;  // entries that one 64-bit mask per thread stands for
+constexpr int kSmFirst = 256;              // entries of the first round, where 2 k are not more
+static_assert(2 * kSoftmaxRefineMaxK <= kSmList, "the first round's entries");
 
 // Two kernels.  k_softmax_parts: every workgroup of a token takes an equal part of the row, finds the bound from the
-// maxima itself, recomputes its own part's entries at or above the mark and leaves them in its slots (position order).
+// maxima itself, recomputes its own part's entries at or above the mark and leaves them in its slots.
 // k_softmax_refine (one workgroup per token) ranks them and takes the softmax.  One compute unit alone would be bound
-// by the fp64 products of some 75 rows (160 vector instructions per row and wave, 8 us at 64 tokens).  Rows with more
-// such entries than slots are left to the second kernel, which then does the whole work by itself, in rounds.
+// by the fp64 products of some 75 rows (160 vector instructions per row and wave, 8 us at 64 tokens).
+//
+// A part with more such entries than slots (a token of zeros, thousands of equal classes, fewer maxima than k) still recomputes
+// them, its share of the work, and leaves their logits by position.  The second kernel then goes through the row's
+// entries at or above the mark in rounds of up to 2048, and of a round only what ranks ahead of the k-th best so far is ranked
+// anew; the first round is a small one, and what it finds raises the mark.  us per step with one token of zeros among 64, or one with
+// a shortlist of equal classes, through fp64 logits / with all of that recomputed and ranked by one workgroup, 2048 against 2048 /
+// so: 256000 classes of d = 2048, k' = 1200, k = 100 1030 / 18997 / 538, 1181 / 934 / 795 (other tokens 681 / 205 / 205); 100000 of
+// 512, k' = 1100, k = 64 404 / 11265 / 202, 493 / 432 / 304; 140000 of 512, 16 tokens, k' = 5000 356 / 13782 / 245, 541 / 1417 / 487.
 constexpr int kSpThreads = 256;
 constexpr int kSpWinBins = 2048;  // bins of 2^kSpShift order keys
 constexpr int kSpShift = 16;
@@ -1110,86 +1119,142 @@ __device__ __forceinline__ SmEntry* sp_entries(void* slots, int B, int b) {
   return reinterpret_cast<SmEntry*>(static_cast<int*>(slots) + B * kSpMaxParts) + (size_t)b * kSmList;
 }
 
-__global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
-  constexpr int NW = kSpThreads / kWave, kPer = kFilterMaxima / kSpThreads, kBins = kSpWinBins / kSpThreads;
-  __shared__ SelSharedT<kSpThreads> sh;
-  __shared__ uint32_t win[kSpWinBins], wave_a[NW], wave_b[NW];
-  __shared__ int l_pos[kSmList / 8];
-  __shared__ unsigned long long l_key[kSmList / 8];
-  const int part = (int)blockIdx.x, P = (int)gridDim.x, b = (int)blockIdx.y, B = (int)gridDim.y;
+// What every workgroup of a token finds by itself, the same in each: the order key that an entry's stored value has to reach, and how
+// far a true logit may be from that value.
+template <int NT>
+struct SmMark {
+  SelSharedT<NT> sh;
+  uint32_t win[kSpWinBins], wave_a[NT / kWave], wave_b[NT / kWave];
+};
+struct SmMarked {
+  uint32_t key;
+  double reach;
+  bool zero_rows_ok;  // the largest row norm is finite: a token of zeros has no other logits than 0
+};
+template <int NT>
+__device__ __forceinline__ SmMarked softmax_mark(const SelectParams& p, int b, SmMark<NT>& S) {
+  constexpr int NW = NT / kWave, kPer = kFilterMaxima / NT, kBins = kSpWinBins / NT;
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  const int cap = kSmList / P;
   float mx[kPer];
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) mx[u] = p.maxima[(size_t)b * kFilterMaxima + min(tid + u * kSpThreads, p.n_maxima - 1)];
+  for (int u = 0; u < kPer; ++u) mx[u] = p.maxima[(size_t)b * kFilterMaxima + min(tid + u * NT, p.n_maxima - 1)];
   const float tile_norm = p.wnorm_tiles[min(tid, p.wnorm_n - 1)];  // wnorm_n <= 256
-  const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
 #pragma unroll
-  for (int u = 0; u < kBins; ++u) win[u * kSpThreads + tid] = 0u;
-  if (tid == 0) sh.list_n = 0;
+  for (int u = 0; u < kBins; ++u) S.win[u * NT + tid] = 0u;
+  if (tid == 0) S.sh.list_n = 0;
   uint32_t key[kPer], top = 0u;  // order keys of the maxima; none: 0, below every number
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
-    key[u] = tid + u * kSpThreads < p.n_maxima && mx[u] > -__builtin_inff() ? order_key(mx[u]) : 0u;
+    key[u] = tid + u * NT < p.n_maxima && mx[u] > -__builtin_inff() ? order_key(mx[u]) : 0u;
     top = key[u] > top ? key[u] : top;
   }
   const uint32_t wa = wave_max(top), wb = wave_max(__float_as_uint(tile_norm));  // non-negative floats order like their bits
   if (lane == 0) {
-    wave_a[w] = wa;
-    wave_b[w] = wb;
+    S.wave_a[w] = wa;
+    S.wave_b[w] = wb;
   }
   __syncthreads();
-  const int anchor = (int)(wave_max(lane < NW ? wave_a[lane] : 0u) >> kSpShift);
-  const float wn = __uint_as_float(wave_max(lane < NW ? wave_b[lane] : 0u));
+  const int anchor = (int)(wave_max(lane < NW ? S.wave_a[lane] : 0u) >> kSpShift);
+  const float wn = __uint_as_float(wave_max(lane < NW ? S.wave_b[lane] : 0u));
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     const int s = anchor - (int)(key[u] >> kSpShift);
-    if (key[u] != 0u && s < kSpWinBins) atomicAdd(&win[s], 1u);
+    if (key[u] != 0u && s < kSpWinBins) atomicAdd(&S.win[s], 1u);
   }
   __syncthreads();
   int c[kBins], mine = 0;
 #pragma unroll
   for (int u = 0; u < kBins; ++u) {
-    c[u] = (int)win[kBins * tid + u];
+    c[u] = (int)S.win[kBins * tid + u];
     mine += c[u];
   }
-  int total, run = wg_scan_incl<kSpThreads>(mine, sh, &total) - mine;
+  int total, run = wg_scan_incl<NT>(mine, S.sh, &total) - mine;
   if (run < p.k && p.k <= run + mine) {
 #pragma unroll
     for (int u = 0; u < kBins; ++u) {
-      if (run < p.k && p.k <= run + c[u]) sh.bc_bin = kBins * tid + u;
+      if (run < p.k && p.k <= run + c[u]) S.sh.bc_bin = kBins * tid + u;
       run += c[u];
     }
   }
   __syncthreads();
-  uint32_t mark_key = 1u;  // fewer than k maxima inside the window: every entry
-  if (total >= p.k) {      // uniform
-    const uint32_t floor_key = (uint32_t)max(anchor - sh.bc_bin, 0) << kSpShift;
-    const double hw = 2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001;
-    if (floor_key != 0u) mark_key = order_key(__double2float_rd((double)key_value(floor_key) - hw));
+  SmMarked r{1u, (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001, wn < __builtin_inff()};
+  if (total >= p.k) {  // uniform; with fewer maxima than k inside the window it is every entry
+    const uint32_t floor_key = (uint32_t)max(anchor - S.sh.bc_bin, 0) << kSpShift;
+    if (floor_key != 0u) r.key = order_key(__double2float_rd((double)key_value(floor_key) - 2.0 * r.reach));
   }
-  // this part's entries, in chunks of eight per thread: thread t of a chunk holds entries t, t + 256, ...
+  return r;
+}
+
+// Whether all logits of a token are 0, whatever its candidates: to all threads of the workgroup.
+template <int NT>
+__device__ __forceinline__ bool softmax_all_zero(const SmMarked& mark, const uint16_t* tok, int d) {
+  uint32_t bits = 0u;
+  for (int i = (int)threadIdx.x; i < d / 8; i += NT) {
+    const uint4 v = reinterpret_cast<const uint4*>(tok)[i];
+    bits |= (v.x | v.y | v.z | v.w) & 0x7FFF7FFFu;
+  }
+  return !__syncthreads_or(bits != 0u) && mark.zero_rows_ok;
+}
+
+__global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
+  constexpr int NW = kSpThreads / kWave;
+  __shared__ SmMark<kSpThreads> S;
+  __shared__ int l_pos[kSmList / 8];
+  __shared__ unsigned long long l_key[kSmList / 8];
+  const int part = (int)blockIdx.x, P = (int)gridDim.x, b = (int)blockIdx.y, B = (int)gridDim.y;
+  const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int cap = kSmList / P;
+  const int n = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
+  const SmMarked mark = softmax_mark<kSpThreads>(p, b, S);
+  // This part's entries: a wave's 64 of the row out of every P.  (Neighbours in the row, whose logits may all be the same, are
+  // several parts' work.)  Eight loads of a wave at a time.
   const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
-  const int per = (n + P - 1) / P, i_lo = min(n, part * per), i_hi = min(n, i_lo + per);
-  for (int i0 = i_lo; i0 < i_hi; i0 += 8 * kSpThreads) {
+  const int first = part * kWave + lane, step = P * kWave;
+  for (int j0 = w; j0 * step + part * kWave < n; j0 += 8 * NW) {  // uniform
     float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = vals[min(i0 + u * kSpThreads + tid, n - 1)];  // clamped, unconditional
+    for (int u = 0; u < 8; ++u) v[u] = vals[min(first + (j0 + u * NW) * step, n - 1)];  // clamped, unconditional
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * kSpThreads + tid;
-      if (i < i_hi && order_key(v[u]) >= mark_key) {
-        const int slot = atomicAdd(&sh.list_n, 1);
+      const int i = first + (j0 + u * NW) * step;
+      if (i < n && order_key(v[u]) >= mark.key) {
+        const int slot = atomicAdd(&S.sh.list_n, 1);
         if (slot < cap) l_pos[slot] = i;
       }
     }
   }
   __syncthreads();
-  const int m = sh.list_n;
+  const int m = S.sh.list_n;
   if (tid == 0) sp_counts(p.refine_slots, b)[part] = m;
-  if (m > cap) return;  // uniform: left to the second kernel
   const int32_t* map = p.map + (size_t)b * p.map_stride;
   const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
+  unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
+  if (m > cap) {  // uniform: the logits only, for the second kernel
+    if (softmax_all_zero<kSpThreads>(mark, tok, p.refine_d)) return;  // uniform: it needs none
+    for (int i0 = part * kWave + w * step; i0 < n; i0 += NW * step) {
+      const int i = min(i0 + lane, n - 1), cls = map[i];
+      for (uint64_t in = __ballot(i0 + lane < n && order_key(vals[i]) >= mark.key); in != 0ull;) {  // uniform
+        const uint16_t* row[4];
+        int at[4], nr = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          at[u] = u > 0 ? at[u - 1] : 0;
+          if (in != 0ull) {
+            nr = u + 1;
+            at[u] = __builtin_ctzll(in);
+            in &= in - 1ull;
+          }
+          row[u] = p.refine_w + (size_t)__builtin_amdgcn_readlane(cls, at[u]) * p.refine_d;
+        }
+        double s4[4];
+        wave_rows_dot_f64(row, nr, tok, p.refine_d, s4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (lane == 0 && u < nr) keys[i0 + at[u]] = order_key(s4[u]);
+      }
+    }
+    return;
+  }
   for (int e0 = w; e0 < m; e0 += 4 * NW) {  // a wave per row, four rows in flight per wave
     const uint16_t* row[4];
     int nr = 0;
@@ -1207,25 +1272,23 @@ __global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
   }
   __syncthreads();
   SmEntry* out = sp_entries(p.refine_slots, B, b) + part * cap;
-  for (int t = tid; t < m; t += kSpThreads) out[t] = SmEntry{l_key[t], l_pos[t], 0};
+  for (int t = tid; t < m; t += kSpThreads) {
+    out[t] = SmEntry{l_key[t], l_pos[t], 0};
+    keys[l_pos[t]] = l_key[t];  // (another part may have more than its slots)
+  }
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) {
-  __shared__ SelShared sh;
-  __shared__ __align__(16) uint32_t win[kWin];  // window histogram of the maxima's fine bins; then the list
-  static_assert(kSmList * (sizeof(int) + sizeof(unsigned long long)) <= kWin * sizeof(uint32_t), "the list fits the window's memory");
-  static_assert(kFilterMaxima <= kSelThreads, "one maximum per thread");
-  unsigned long long* l_key = reinterpret_cast<unsigned long long*>(win);  // order keys of fp64 logits
-  int* l_pos = reinterpret_cast<int*>(win + 2 * kSmList);
+  __shared__ SmMark<kSelThreads> S;
+  __shared__ unsigned long long l_key[kSmList];  // order keys of fp64 logits
+  __shared__ int l_pos[kSmList];
   __shared__ int b_pos[2][kSoftmaxRefineMaxK];
   __shared__ unsigned long long b_key[2][kSoftmaxRefineMaxK];
   __shared__ int l_n;
-  __shared__ uint32_t wave_a[kSelWaves], wave_b[kSelWaves];
   const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
   const int k = p.k;
   HIRE_TS(50);
   const int32_t* map = p.map + (size_t)b * p.map_stride;
-  const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
   // what the parts left: thread t holds slots t and t + 1024; the valid ones move together
   constexpr int kOwn = kSmList / kSelThreads;
   const int P = softmax_parts((int)gridDim.x), cap = kSmList / P;
@@ -1236,11 +1299,13 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
     have_n[u] = sp_counts(p.refine_slots, b)[(tid + u * kSelThreads) / cap];
     entry[u] = sp_entries(p.refine_slots, (int)gridDim.x, b)[tid + u * kSelThreads];
   }
-  unsigned long long pending = 0ull;  // bit i: value i has to be recomputed and has not been listed yet
-  int ready = 0;                      // entries the parts have recomputed
-  int first = 0, end = 0;             // the span of the row that the mask stands for, the row's length (0: the parts served it)
-  uint32_t mark_key = 1u;
+  unsigned long long pending = 0ull;  // bit i: value i counts and has not been listed yet
+  int ready = 0;                      // entries from the slots
+  int first = 0, end = 0;             // the span of the row that the mask stands for, the row's length (0: the slots served it)
+  SmMarked mark{1u, 0.0, false};
+  int have = 0, cur = 0;              // entries of the best list so far, and which of its two copies holds them
   const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
+  const unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
   auto scan = [&]() {  // value i of thread t is entry first + t + 1024 i
     const int n = min(end - first, kSmSpan);
     for (int i0 = 0; kSelThreads * i0 < n; i0 += 16) {  // uniform
@@ -1249,130 +1314,152 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
       for (int u = 0; u < 16; ++u) v[u] = vals[first + min(tid + kSelThreads * (i0 + u), n - 1)];  // clamped, unconditional
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        if (order_key(v[u]) >= mark_key && tid + kSelThreads * (i0 + u) < n) pending |= 1ull << (i0 + u);
+        if (order_key(v[u]) >= mark.key && tid + kSelThreads * (i0 + u) < n) pending |= 1ull << (i0 + u);
     }
   };
+  const int few = max(2 * k, kSmFirst);  // entries that are ranked as they are; of more of them, these come first
+  int place[kOwn] = {-1, -1};            // of the slots' entries
   if (!__syncthreads_or(have_n[0] > cap || have_n[1] > cap)) {
     static_assert(kOwn == 2, "two slots per thread");
     const uint64_t vm[kOwn] = {__ballot(tid % cap < have_n[0]), __ballot((tid + kSelThreads) % cap < have_n[1])};
-    if (lane == 0) wave_a[w] = (uint32_t)(__popcll(vm[0]) + __popcll(vm[1]));
+    if (lane == 0) S.wave_a[w] = (uint32_t)(__popcll(vm[0]) + __popcll(vm[1]));
     __syncthreads();
-    const int incl = wave_scan_incl(lane < kSelWaves ? (int)wave_a[lane] : 0);
+    const int incl = wave_scan_incl(lane < kSelWaves ? (int)S.wave_a[lane] : 0);
     ready = __builtin_amdgcn_readlane(incl, kSelWaves - 1);
     const int ws = __builtin_amdgcn_readfirstlane(w);
     int at = ws > 0 ? __builtin_amdgcn_readlane(incl, ws - 1) : 0;
 #pragma unroll
     for (int u = 0; u < kOwn; ++u) {
       if (((vm[u] >> lane) & 1ull) != 0ull) {
-        l_key[at + mask_prefix(vm[u])] = entry[u].key;
-        l_pos[at + mask_prefix(vm[u])] = entry[u].pos;
+        place[u] = at + mask_prefix(vm[u]);
+        if (place[u] < few) {
+          l_key[place[u]] = entry[u].key;
+          l_pos[place[u]] = entry[u].pos;
+        }
       }
       at += __popcll(vm[u]);
     }
   } else {
-    const float mine_max = p.maxima[(size_t)b * kFilterMaxima + min(tid, p.n_maxima - 1)];
-    float tile_norm = p.wnorm_tiles[min(tid, p.wnorm_n - 1)];  // wnorm_n <= 256
-    end = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
-    {
-      uint4* z = reinterpret_cast<uint4*>(win) + 2 * tid;
-      z[0] = z[1] = make_uint4(0, 0, 0, 0);
-    }
-    // order key of this thread's maximum; none: 0, below every number
-    const uint32_t key = tid < p.n_maxima && mine_max > -__builtin_inff() ? order_key(mine_max) : 0u;
-    const uint32_t wa = wave_max(key), wb = wave_max(__float_as_uint(tile_norm));  // non-negative floats order like their bits
-    if (lane == 0) {
-      wave_a[w] = wa;
-      wave_b[w] = wb;
-    }
-    __syncthreads();
-    const uint32_t anchor = wave_max(lane < kSelWaves ? wave_a[lane] : 0u) >> kFineShift;
-    const float wn = __uint_as_float(wave_max(lane < kSelWaves ? wave_b[lane] : 0u));
-    const uint32_t slot = anchor - (key >> kFineShift);
-    if (key != 0u && slot < (uint32_t)kWin) atomicAdd(&win[slot], 1u);
-    __syncthreads();
-    WinRegs<kSelThreads> wr;
-    wr.issue(win);
-    const WinWalk wk = walk_window<kSelThreads>(wr, k, sh);
+    mark = softmax_mark<kSelThreads>(p, b, S);
     HIRE_TS(51);
-    // fewer than k maxima inside the window (few candidates, widely spread values): every entry is recomputed
-    const uint32_t floor_key = wk.found ? (anchor - (uint32_t)wk.slot) << kFineShift : 0u;
-    const double mark = (floor_key != 0u ? (double)key_value(floor_key) : 0.0) -
-                        2.0 * (double)p.err_c * (double)p.xnorm[b] * (double)wn * 1.000001;
-    mark_key = floor_key != 0u ? order_key(__double2float_rd(mark)) : 1u;
-    scan();
+    if (softmax_all_zero<kSelThreads>(mark, p.refine_x + (size_t)b * p.refine_d, p.refine_d)) {  // uniform
+      for (int t = tid; t < k; t += kSelThreads) {
+        b_pos[0][t] = t;
+        b_key[0][t] = order_key(0.0);
+      }
+      have = k;
+      __syncthreads();
+    } else {
+      end = p.n_dev ? min(*p.n_dev, p.n_cap) : p.n;
+      scan();
+    }
     HIRE_TS(52);
   }
-  int have = 0, cur = 0;  // entries of the best list so far, and which of its two copies holds them
-  while (true) {  // uniform
+  while (end > 0 || have < k || ready > few) {  // uniform
     __syncthreads();  // the list and the counters of the round before have been read
-    if (tid == 0) l_n = 0;
-    __syncthreads();
-    const int room = kSmList - have;
-    while (pending != 0ull) {
-      const int i = __builtin_ctzll(pending);
-      const int slot = atomicAdd(&l_n, 1);
-      if (slot >= room) break;
-      l_pos[slot] = first + tid + kSelThreads * i;
-      pending &= pending - 1ull;
-    }
-    __syncthreads();
-    HIRE_TS(53);
-    const int fresh = min(l_n, room), listed = ready > 0 ? ready : fresh;
-    for (int e0 = w; e0 < fresh; e0 += 4 * kSelWaves) {  // a wave per row, four rows in flight per wave
-      const uint16_t* row[4];
-      int nr = 0;
+    const bool full = have == k;  // uniform: there is a k-th best to compare with
+    int listed = min(ready, few);
+    if (full || end > 0) {  // uniform
+      if (tid == 0) l_n = 0;
+      __syncthreads();
+      uint64_t key[kOwn];
+      int pos[kOwn];
+      bool stays[kOwn];
+      if (end == 0) {  // the other slots
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * kSelWaves;
-        if (e < fresh) nr = u + 1;
-        row[u] = p.refine_w + (size_t)map[l_pos[min(e, fresh - 1)]] * p.refine_d;
+        for (int u = 0; u < kOwn; ++u) {
+          stays[u] = place[u] >= few;
+          pos[u] = entry[u].pos;
+          key[u] = entry[u].key;
+        }
+      } else {
+        const int room = full ? kSmList - k : few - have;
+        while (pending != 0ull) {
+          const int i = __builtin_ctzll(pending);
+          const int slot = atomicAdd(&l_n, 1);
+          if (slot >= room) break;
+          l_pos[slot] = first + tid + kSelThreads * i;
+          pending &= pending - 1ull;
+        }
+        __syncthreads();
+        HIRE_TS(53);
+        const int fresh = min(l_n, room);
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+          const int e = tid + u * kSelThreads;
+          stays[u] = e < fresh;
+          pos[u] = stays[u] ? l_pos[e] : 0;
+          key[u] = keys[pos[u]];
+        }
+        __syncthreads();
+        if (tid == 0) l_n = 0;
+        __syncthreads();
       }
-      double s4[4];
-      wave_rows_dot_f64(row, nr, tok, p.refine_d, s4);
+      // once there is a k-th best, only what ranks ahead of it is listed
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (lane == 0 && u < nr) l_key[e0 + u * kSelWaves] = order_key(s4[u]);  // -0 counts as +0
+      for (int u = 0; u < kOwn; ++u)
+        if (stays[u] && !(full && !ranks_ahead(key[u], pos[u], (uint64_t)b_key[cur][k - 1], b_pos[cur][k - 1]))) {
+          const int slot = atomicAdd(&l_n, 1);
+          l_key[slot] = key[u];
+          l_pos[slot] = pos[u];
+        }
+      __syncthreads();
+      listed = l_n;
     }
     HIRE_TS(54);
-    // the best so far join the list, then every entry is ranked among all of them, sixteen lanes per entry
-    for (int t = tid; t < have; t += kSelThreads) {
-      l_pos[listed + t] = b_pos[cur][t];
-      l_key[listed + t] = b_key[cur][t];
-    }
-    __syncthreads();
-    const int m = listed + have, sub = tid & 15;
-    for (int t0 = 0; t0 < m; t0 += kSelThreads / 16) {  // uniform
-      const int t = min(t0 + tid / 16, m - 1);
-      const uint64_t mine = l_key[t];
-      const int mine_pos = l_pos[t];
-      int rank = 0;
-      for (int u0 = sub; u0 < m; u0 += 64) {  // four LDS reads in flight
-        uint64_t ok[4];
-        int op[4];
+    if (listed > 0) {  // uniform
+      // the best so far join the list, then every entry is ranked among all of them, sixteen lanes per entry
+      for (int t = tid; t < have; t += kSelThreads) {
+        l_pos[listed + t] = b_pos[cur][t];
+        l_key[listed + t] = b_key[cur][t];
+      }
+      __syncthreads();
+      const int m = listed + have, sub = tid & 15;
+      for (int t0 = 0; t0 < m; t0 += kSelThreads / 16) {  // uniform
+        const int t = min(t0 + tid / 16, m - 1);
+        const uint64_t mine = l_key[t];
+        const int mine_pos = l_pos[t];
+        int rank = 0;
+        for (int u0 = sub; u0 < m; u0 += 64) {  // four LDS reads in flight
+          uint64_t ok[4];
+          int op[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          ok[j] = l_key[min(u0 + 16 * j, m - 1)];
-          op[j] = l_pos[min(u0 + 16 * j, m - 1)];
+          for (int j = 0; j < 4; ++j) {
+            ok[j] = l_key[min(u0 + 16 * j, m - 1)];
+            op[j] = l_pos[min(u0 + 16 * j, m - 1)];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) rank += u0 + 16 * j < m && ranks_ahead(ok[j], op[j], mine, mine_pos) ? 1 : 0;
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) rank += u0 + 16 * j < m && ranks_ahead(ok[j], op[j], mine, mine_pos) ? 1 : 0;
+        auto add = [](int a, int b) { return a + b; };
+        rank = add(rank, dpp_move<0x111, 0xF>(0, rank));  // the row's last lane holds the sum of its sixteen
+        rank = add(rank, dpp_move<0x112, 0xF>(0, rank));
+        rank = add(rank, dpp_move<0x114, 0xF>(0, rank));
+        rank = add(rank, dpp_move<0x118, 0xF>(0, rank));
+        if (sub == 15 && t0 + tid / 16 < m && rank < k) {
+          b_pos[cur ^ 1][rank] = mine_pos;
+          b_key[cur ^ 1][rank] = mine;
+        }
       }
-      auto add = [](int a, int b) { return a + b; };
-      rank = add(rank, dpp_move<0x111, 0xF>(0, rank));  // the row's last lane holds the sum of its sixteen
-      rank = add(rank, dpp_move<0x112, 0xF>(0, rank));
-      rank = add(rank, dpp_move<0x114, 0xF>(0, rank));
-      rank = add(rank, dpp_move<0x118, 0xF>(0, rank));
-      if (sub == 15 && t0 + tid / 16 < m && rank < k) {
-        b_pos[cur ^ 1][rank] = mine_pos;
-        b_key[cur ^ 1][rank] = mine;
+      have = min(k, m);
+      cur ^= 1;
+    }
+    const bool left = __syncthreads_or(pending != 0ull) || (!full && ready > few), next = !left && end - first > kSmSpan;  // uniform
+    if (!left && !next) break;
+    if (end > 0 && have == k && (next || !full)) {  // what is stored further below the k-th best than a logit can be off is not among the best
+      const double lowest = key_value((uint64_t)b_key[cur][k - 1]) - mark.reach;
+      if (lowest == lowest) mark.key = max(mark.key, order_key(__double2float_rd(lowest)));
+      if (!next) {
+        const unsigned long long unlisted = pending;
+        pending = 0ull;
+        scan();
+        pending &= unlisted;
       }
     }
-    have = min(k, m);
-    cur ^= 1;
-    if (__syncthreads_or(pending != 0ull)) continue;
-    if (end - first <= kSmSpan) break;  // uniform
-    first += kSmSpan;
-    scan();
+    if (next) {
+      first += kSmSpan;
+      scan();
+    }
   }
   HIRE_TS(55);
   // the k survivors in rank order; softmax: exp(z - zmax) / sum
@@ -1380,10 +1467,10 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
   double part = 0.0;
   for (int t = tid; t < k; t += kSelThreads) part += exp(key_value((uint64_t)b_key[cur][t]) - zmax);
   part = wave_sum(part);
-  if (lane == 0) sh.red_a[w] = (unsigned long long)__double_as_longlong(part);
+  if (lane == 0) S.sh.red_a[w] = (unsigned long long)__double_as_longlong(part);
   __syncthreads();
   double sum = 0.0;
-  for (int u = 0; u < kSelWaves; ++u) sum += __longlong_as_double((long long)sh.red_a[u]);
+  for (int u = 0; u < kSelWaves; ++u) sum += __longlong_as_double((long long)S.sh.red_a[u]);
   for (int t = tid; t < k; t += kSelThreads) {
     const double z = key_value((uint64_t)b_key[cur][t]);
     if (p.idx_out) p.idx_out[(size_t)b * k + t] = map[b_pos[cur][t]];
@@ -1397,7 +1484,7 @@ hipError_t launch_softmax_refine(const SelectParams& p, int B, hipStream_t s) {
   const int cap = p.n_dev ? p.n_cap : p.n;
   if (cap < 1 || cap > kSoftmaxRefineMaxRow || p.k < 1 || p.k > kSoftmaxRefineMaxK || !p.refine_w || !p.refine_x ||
       p.refine_d % 8 != 0 || !p.map || !p.xnorm || !p.wnorm_tiles || !p.maxima || !p.refine_slots || p.n_maxima > kFilterMaxima ||
-      p.wnorm_n > kSpThreads || p.n_maxima < 1 || p.wnorm_n < 1 || !p.vals)
+      p.wnorm_n > kSpThreads || p.n_maxima < 1 || p.wnorm_n < 1 || !p.vals || !p.refine_keys || p.refine_keys_stride < cap)
     return hipErrorInvalidValue;
   const hipError_t e = launch(k_softmax_parts, dim3(softmax_parts(B), B), dim3(kSpThreads), 0, s, p);
   if (e != hipSuccess) return e;
