@@ -218,3 +218,14 @@ def test_static_scratch_takes_what_it_announces(lib):
             assert step(C.byref(L), 0x90000, B, 819, 3276, 0xA0000, None, None, None, None, None, None) == -2
             refused += 1
     assert refused > 0
+
+
+@pytest.mark.parametrize("kind,d,vocab,r,B,k,kprime,bytes_before", [
+    (1, 32, 9415, 320, 16, 1, 2609, 4182528), (0, 672, 39988, 256, 8, 50, 227, 11864832), (1, 2656, 6437, 192, 16, 4, 198, 2572032),
+    (1, 64, 176519, 736, 3, 191, 2035, 5147136), (2, 384, 15709, 512, 64, 7, 17, 7988992), (0, 2048, 256000, 0, 64, 100, 1200, 182403328)])
+def test_softmax_workspaces_do_not_grow(kind, d, vocab, r, B, k, kprime, bytes_before):
+    """Callers that reserved what a step once asked for are still served."""
+    from paper_2402_09360_amd import hire
+    L = hire._SoftmaxLayer()
+    L.d_model, L.vocab, L.scorer_kind, L.r = d, vocab, kind, r
+    assert 0 < hire._lib.hire_softmax_workspace_bytes(C.byref(L), B, k, kprime) <= bytes_before
