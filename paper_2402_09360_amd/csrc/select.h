@@ -340,20 +340,95 @@ __device__ __forceinline__ int list_bitmap(const uint32_t* __restrict__ bitmap, 
   return base;
 }
 
+// A 64-bit key that ranks smaller ones first, ties by a number.
+struct KeyAndNumber {
+  unsigned long long key;
+  uint32_t number;
+};
+__device__ __forceinline__ bool comes_first(unsigned long long a, unsigned long long b) { return a < b; }
+__device__ __forceinline__ bool comes_first(const KeyAndNumber& a, const KeyAndNumber& b) {
+  return a.key < b.key || (a.key == b.key && a.number < b.number);
+}
+__device__ __forceinline__ unsigned long long lane_xor(unsigned long long v, int m) { return __shfl_xor(v, m); }
+__device__ __forceinline__ KeyAndNumber lane_xor(const KeyAndNumber& v, int m) {
+  return KeyAndNumber{__shfl_xor(v.key, m), (uint32_t)__shfl_xor((int)v.number, m)};
+}
+
+// The n items of a list in LDS in ascending order, by one workgroup: Batcher's exchanges with the first step of every merge mirrored,
+// so that the smaller item always belongs to the lower place.  A wave has 128 places in registers, two per lane, while the pairs lie
+// within those; `last`: no item is larger.  The list must be visible; ends behind a barrier.  16 rows, us per call of topk_select for k
+// equal values, with all items of a bin compared with one another / so: 1000 values, k = 256 31.0 / 11.1, 512 55.2 / 12.7; 16384, k =
+// 1024 131.7 / 36.3 (of it 22 before the ranking).
+template <typename T>
+__device__ __forceinline__ void sort_list(T* list, int n, const T& last) {
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  auto cross = [&](T& v, int m) {  // lanes l and l ^ m, the smaller one to the lower lane
+    const T other = lane_xor(v, m);
+    if (comes_first(other, v) == (lane < (lane ^ m))) v = other;
+  };
+  for (int size = 2 * kWave;; size <<= 1) {  // uniform
+    for (int s = size >> 1; s >= 2 * kWave; s >>= 1) {
+      for (int p = (int)threadIdx.x; 2 * (p & -s) < n; p += kSelThreads) {
+        const int at = p & (s - 1), lo = 2 * p - at, hi = 2 * s == size ? lo + 2 * (s - at) - 1 : lo + s;
+        if (hi < n) {  // (places past n would hold what comes last)
+          const T a = list[lo], b = list[hi];
+          if (comes_first(b, a)) {
+            list[lo] = b;
+            list[hi] = a;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    for (int i = 2 * kWave * w + lane; i - lane < n; i += 2 * kSelThreads) {  // uniform over the wave
+      T a = i < n ? list[i] : last, b = i + kWave < n ? list[i + kWave] : last;
+      if (size == 2 * kWave) {
+        for (int z = 2; z <= kWave; z <<= 1) {
+          cross(a, z - 1);
+          cross(b, z - 1);
+          for (int s = z >> 2; s > 0; s >>= 1) {
+            cross(a, s);
+            cross(b, s);
+          }
+        }
+        b = lane_xor(b, kWave - 1);  // mirrored: place 127 - l beside place l
+      }
+      if (comes_first(b, a)) {
+        const T t = a;
+        a = b;
+        b = t;
+      }
+      // (b may stay mirrored: what follows within its 64 places sorts them from any order that is bitonic)
+      for (int s = kWave / 2; s > 0; s >>= 1) {
+        cross(a, s);
+        cross(b, s);
+      }
+      if (i < n) list[i] = a;
+      if (i + kWave < n) list[i + kWave] = b;
+    }
+    __syncthreads();
+    if (size >= n) break;
+  }
+}
+
 // Ranks of n <= PER * 1024 items, of which thread t holds the t-th, the (1024 + t)-th and so on, in a total order whose keys are
 // key(item), larger ahead; ahead(a, b) says whether item a comes before item b (consulted between items of one bin only).  The keys
 // between the smallest and the largest go to 4096 equal bins; the addition that counts a bin's items gives each its place in the
 // bin, a scan gives every bin's first rank, the items are listed bin by bin and each counts those ahead of it inside its bin: a few
-// instead of n comparisons per item (all of them only where all keys crowd into one bin).  emit(item, rank) is called once per
-// item.  bins: kRankBins words of LDS, 16-byte aligned; list: n items of LDS.  All threads call this; what key() reads of LDS must be
-// visible, and sh.red_a and sh.red_b free.
+// instead of n comparisons per item.  emit(u, item, rank) is called once per item, a thread's u-th.  Where a bin has more than
+// longest_run items (equal keys, or all near each other and one far off) nothing is emitted and the result is false: the
+// caller sorts them, in memory of its own or, behind a barrier, in that of bins and list.  bins: kRankBins words of LDS, 16-byte aligned; list: n items of LDS.  All threads call this; what
+// key() reads of LDS must be visible, and sh.red_a and sh.red_b free.
 // Bound: the chain of barriers and LDS round trips on one compute unit.  16 rows of 256000, in us per call of topk_select: k = 1024
 // 17.4 (2048 bins, the items' numbers listed, by a second pass of additions) -> 15.6 (this, 2048 bins) -> 15.1 (4096 bins: the keys
 // are densest at the threshold); k = 2048 27.1 -> 21.2 -> 18.8.
 constexpr int kRankBins = 4096;
+// The longest run of items that is compared: it takes 0.1 us per item of the run, sorting 3 us for 256 items and 10 for 2000 (16
+// rows of 256000 values rounded to bf16, k = 1024, runs of about 60: 22.9 us per call compared, 26.0 sorted).
+__device__ __forceinline__ int rank_run(int n) { return 48 + n / 32; }
 template <typename K, typename T, int PER, typename Key, typename Ahead, typename Emit>
-__device__ __forceinline__ void bucket_ranks(int n, const T (&own)[PER], Key&& key, Ahead&& ahead, uint32_t* bins, T* list,
-                                             SelShared& sh, Emit&& emit) {
+__device__ __forceinline__ bool bucket_ranks(int n, const T (&own)[PER], Key&& key, Ahead&& ahead, uint32_t* bins, T* list,
+                                             int longest_run, SelShared& sh, Emit&& emit) {
   static_assert(kRankBins == 4 * kSelThreads && PER * kSelThreads < 65536, "four bins per thread; first rank and length in one word");
   const int tid = (int)threadIdx.x;
   uint4* quad = reinterpret_cast<uint4*>(bins) + tid;
@@ -386,7 +461,12 @@ __device__ __forceinline__ void bucket_ranks(int n, const T (&own)[PER], Key&& k
   __syncthreads();
   const uint4 c = *quad;
   const uint32_t sum = c.x + c.y + c.z + c.w;
-  const uint32_t s0 = (uint32_t)wg_scan_incl((int)sum, sh) - sum, s1 = s0 + c.x, s2 = s1 + c.y, s3 = s2 + c.z;
+  // (in the same scan, above the sums: the threads with a bin that has too many)
+  constexpr int kTooMany = 1 << 20;
+  const int mine = (int)sum + (max(max(c.x, c.y), max(c.z, c.w)) > (uint32_t)longest_run ? kTooMany : 0);
+  int total;
+  const uint32_t s0 = (uint32_t)(wg_scan_incl(mine, sh, &total) & (kTooMany - 1)) - sum, s1 = s0 + c.x, s2 = s1 + c.y, s3 = s2 + c.z;
+  if (total >= kTooMany) return false;  // uniform
   *quad = make_uint4(s0 << 16 | c.x, s1 << 16 | c.y, s2 << 16 | c.z, s3 << 16 | c.w);
   __syncthreads();
   uint32_t run[PER];
@@ -409,8 +489,9 @@ __device__ __forceinline__ void bucket_ranks(int n, const T (&own)[PER], Key&& k
 #pragma unroll
         for (int j = 0; j < 4; ++j) rank += i0 + j < end && ahead(other[j], own[u]) ? 1 : 0;
       }
-      emit(own[u], rank);
+      emit(u, own[u], rank);
     }
+  return true;
 }
 
 }  // namespace hire

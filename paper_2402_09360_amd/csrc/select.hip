@@ -293,28 +293,37 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
 
   // ---- rank order: position of each selected entry among the k (value desc, index asc) ----
   constexpr int kPerThread = kRankMax / kSelThreads;
-  // Up to a wave of entries: one lane each, every wave compares it with a sixteenth of the others and adds that up.  Beyond that by
-  // bins of the keys.  16 rows of 1000, in us per call: 64 entries 5.9 against 6.9; 100 of them 7.3, with two lanes' work per lane,
-  // against 7.0, 256 11.0 against 7.1, 512 27.9 against 11.3.
+  // Up to two waves of entries: a lane each, and the workgroup's waves (of two, every other one) compare them with an equal part
+  // of the others and add that up.  Beyond that by bins of the keys, or sorted where many share a bin.  us per call, compared /
+  // by bins: 16 rows of 1000, 64 entries 5.9 / 6.9, 100 of them 7.9 / 8.0 (of equal values 7.9 / 16.7), 256 11.3 / 8.0, 512 28.0 /
+  // 11.5; softmax step of two tokens through fp64 logits, 40000 classes, k = 100 31.2 / 32.4.
   int* rk_rank = rk_pos + k;
-  const bool spread = k <= kWave;
+  const bool spread = k <= 2 * kWave;
   if (spread && (int)threadIdx.x < k) rk_rank[threadIdx.x] = 0;
   __syncthreads();
-  if (spread) {
-    constexpr int kOthers = kWave / kSelWaves;
-    const int t = min(lane, k - 1);
+  auto spread_ranks = [&](auto entry_waves) __attribute__((always_inline)) {
+    constexpr int kEntries = decltype(entry_waves)::value * kWave, kOthers = kEntries / (kSelThreads / kEntries);
+    const int e = (int)threadIdx.x % kEntries, t = min(e, k - 1), first = (int)threadIdx.x / kEntries * kOthers;
     const K mine = rk_key[t];
-    K other[kOthers];
-#pragma unroll
-    for (int j = 0; j < kOthers; ++j) other[j] = rk_key[min(w * kOthers + j, k - 1)];
     int rank = 0;
 #pragma unroll
-    for (int j = 0; j < kOthers; ++j) {
-      const int u = w * kOthers + j;  // the list is in index order, so u < t is "lower index"
-      rank += u < k && (other[j] > mine || (other[j] == mine && u < t)) ? 1 : 0;
+    for (int j0 = 0; j0 < kOthers; j0 += 4) {
+      K other[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) other[j] = rk_key[min(first + j0 + j, k - 1)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int u = first + j0 + j;  // the list is in index order, so u < t is "lower index"
+        rank += u < k && (other[j] > mine || (other[j] == mine && u < t)) ? 1 : 0;
+      }
     }
-    if (lane < k) atomicAdd(&rk_rank[t], rank);
+    if (e < k) atomicAdd(&rk_rank[t], rank);
     __syncthreads();
+  };
+  if (k <= kWave) {
+    spread_ranks(std::integral_constant<int, 1>{});
+  } else if (spread) {
+    spread_ranks(std::integral_constant<int, 2>{});
   }
   int my_rank[kPerThread];
   V my_val[kPerThread];
@@ -323,30 +332,51 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
     my_rank[q] = -1;
     my_val[q] = (V)0;
   }
-  auto put = [&](int t, int rank) {
+  auto put = [&](int q, int t, int rank) {
     const int i = rk_pos[t];
     const V v = key_value(rk_key[t]);
     if (p.idx_out) p.idx_out[(size_t)b * k + rank] = map ? map[i] : i;
     if (p.pos_out) p.pos_out[(size_t)b * k + rank] = i;
     if (p.val_out) p.val_out[(size_t)b * k + rank] = (float)v;
-#pragma unroll
-    for (int q = 0; q < kPerThread; ++q)
-      if (t == (int)threadIdx.x + q * kSelThreads) {
-        my_rank[q] = rank;
-        my_val[q] = v;
-      }
+    my_rank[q] = rank;
+    my_val[q] = v;
   };
   if (spread) {
-    if ((int)threadIdx.x < k) put((int)threadIdx.x, rk_rank[threadIdx.x]);
+    if ((int)threadIdx.x < k) put(0, (int)threadIdx.x, rk_rank[threadIdx.x]);
   } else {
     static_assert(kRankBins + kRankMax <= kHistWindow, "the bins and the list reuse the window's memory");
     int own[kPerThread];
 #pragma unroll
     for (int u = 0; u < kPerThread; ++u) own[u] = u * kSelThreads + (int)threadIdx.x;
-    bucket_ranks<K>(
-        k, own, [&](int t) { return rk_key[t]; },
-        [&](int o, int t) { return rk_key[o] > rk_key[t] || (rk_key[o] == rk_key[t] && o < t); },  // index order
-        win, reinterpret_cast<int*>(win) + kRankBins, sh, put);
+    int* list = reinterpret_cast<int*>(win) + kRankBins;
+    auto ahead = [&](int o, int t) { return rk_key[o] > rk_key[t] || (rk_key[o] == rk_key[t] && o < t); };  // index order
+    using Item = std::conditional_t<sizeof(K) == 4, unsigned long long, KeyAndNumber>;  // key and place in the list
+    constexpr int kMost = kHistWindow * 4 / (int)sizeof(Item);                           // as many as the window's memory holds
+    if (!bucket_ranks<K>(k, own, [&](int t) { return rk_key[t]; }, ahead, win, list, k <= kMost ? rank_run(k) : k, sh, put)) {
+      Item* items = reinterpret_cast<Item*>(win);
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u)
+        if (own[u] < k) {
+          if constexpr (sizeof(K) == 4)
+            items[own[u]] = (unsigned long long)~rk_key[own[u]] << 32 | (uint32_t)own[u];
+          else
+            items[own[u]] = Item{~rk_key[own[u]], (uint32_t)own[u]};
+        }
+      __syncthreads();
+      if constexpr (sizeof(K) == 4)
+        sort_list(items, k, ~0ull);
+      else
+        sort_list(items, k, Item{~0ull, ~0u});
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u)
+        if (own[u] < k) {
+          if constexpr (sizeof(K) == 4)
+            put(u, (int)(uint32_t)items[own[u]], own[u]);
+          else
+            put(u, (int)items[own[u]].number, own[u]);
+        }
+    }
   }
   HIRE_TS(34);
   if (!p.prob_out) return;
@@ -877,29 +907,44 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
 #pragma unroll
   for (int u = 1; u < kAmbCap / kSelThreads; ++u)
     if (u * kSelThreads < n) own[u] = mr.amb[(size_t)b * kAmbCap + u * kSelThreads + tid];  // uniform; places past n hold old entries
-  bucket_ranks<uint32_t>(
-      n, own, [](const AmbEntry& e) { return e.okey; },
-      [](const AmbEntry& o, const AmbEntry& e) { return o.okey > e.okey || (o.okey == e.okey && o.idx < e.idx); }, bins, list, sh,
-      [&](const AmbEntry& e, int rank) {
-        if (rank >= k) return;
-        if (rank_order) {
-          idx[rank] = e.idx;
-          if (val) val[rank] = key_value(e.okey);
-        } else {
-          chosen[rank] = e;
-        }
-      });
+  unsigned long long* both = reinterpret_cast<unsigned long long*>(list);  // of rows with many equal keys: sorted in one word
+  static_assert(sizeof(AmbEntry) == sizeof(unsigned long long), "in the list's place");
+  auto place = [&](int, const AmbEntry& e, int rank) {
+    if (rank >= k) return;
+    if (rank_order) {
+      idx[rank] = e.idx;
+      if (val) val[rank] = key_value(e.okey);
+    } else {
+      chosen[rank] = e;
+    }
+  };
+  auto larger = [](const AmbEntry& o, const AmbEntry& e) { return o.okey > e.okey || (o.okey == e.okey && o.idx < e.idx); };
+  if (!bucket_ranks<uint32_t>(n, own, [](const AmbEntry& e) { return e.okey; }, larger, bins, list, rank_run(n), sh, place)) {
+#pragma unroll
+    for (int u = 0; u < kAmbCap / kSelThreads; ++u)
+      if (u * kSelThreads + tid < n) both[u * kSelThreads + tid] = (unsigned long long)~own[u].okey << 32 | (uint32_t)own[u].idx;
+    __syncthreads();
+    sort_list(both, n, ~0ull);
+    for (int t = tid; t < min(n, k); t += kSelThreads) place(0, AmbEntry{~(uint32_t)(both[t] >> 32), (int32_t)(uint32_t)both[t]}, t);
+  }
   if (rank_order) return;
   __syncthreads();
   AmbEntry mine[kTkMaxK / kSelThreads];
 #pragma unroll
   for (int u = 0; u < kTkMaxK / kSelThreads; ++u) mine[u] = chosen[min(u * kSelThreads + tid, k - 1)];
-  bucket_ranks<uint32_t>(
-      k, mine, [](const AmbEntry& e) { return ~(uint32_t)e.idx; },
-      [](const AmbEntry& o, const AmbEntry& e) { return o.idx < e.idx; }, bins, list, sh, [&](const AmbEntry& e, int rank) {
-        idx[rank] = e.idx;
-        if (val) val[rank] = key_value(e.okey);
-      });
+  auto write = [&](int, const AmbEntry& e, int rank) {
+    idx[rank] = e.idx;
+    if (val) val[rank] = key_value(e.okey);
+  };
+  auto lower = [](const AmbEntry& o, const AmbEntry& e) { return o.idx < e.idx; };
+  if (!bucket_ranks<uint32_t>(k, mine, [](const AmbEntry& e) { return ~(uint32_t)e.idx; }, lower, bins, list, rank_run(k), sh, write)) {
+#pragma unroll
+    for (int u = 0; u < kTkMaxK / kSelThreads; ++u)
+      if (u * kSelThreads + tid < k) both[u * kSelThreads + tid] = (unsigned long long)(uint32_t)mine[u].idx << 32 | mine[u].okey;
+    __syncthreads();
+    sort_list(both, k, ~0ull);
+    for (int t = tid; t < k; t += kSelThreads) write(0, AmbEntry{(uint32_t)both[t], (int32_t)(both[t] >> 32)}, t);
+  }
 }
 
 // ---------------------------------------------------------------------------
