@@ -1153,7 +1153,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
-          add_row(wv[u], u * kRowsPerLoad + slot < m ? raw[u] : 0.0f);
+          if (u < kLoads - 1 || u * kRowsPerLoad + slot < m) add_row(wv[u], raw[u]);  // (only the last load may not be whole)
           __builtin_amdgcn_sched_barrier(0);
         }
       };
@@ -1182,8 +1182,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < kW2Batch; ++u)
-        if (r0 + u * kWW * kRowsPerLoad < p.m1)
-          add_row(wv[u], r0 + u * kWW * kRowsPerLoad + slot < p.m1 ? (float)raw[u] : 0.0f);
+        if (r0 + u * kWW * kRowsPerLoad + slot < p.m1) add_row(wv[u], (float)raw[u]);
     }
     HIRE_TS(27);
     // fixed-order reduction: the slots of a DPP row (its last lanes then hold their sums), the rows of all

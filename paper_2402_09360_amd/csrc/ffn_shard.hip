@@ -494,6 +494,8 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
+          const uint32_t keep = t0 + u < ks ? 0xFFFFFFFFu : 0u;  // (an infinite weight behind the end is no 0 * inf)
+          rv[u] = make_uint4(rv[u].x & keep, rv[u].y & keep, rv[u].z & keep, rv[u].w & keep);
           const float wf[8] = {bf16_lo(rv[u].x), bf16_hi(rv[u].x), bf16_lo(rv[u].y), bf16_hi(rv[u].y),
                                bf16_lo(rv[u].z), bf16_hi(rv[u].z), bf16_lo(rv[u].w), bf16_hi(rv[u].w)};
 #pragma unroll

@@ -60,15 +60,67 @@ def test_values_from_64_bits_against_the_oracle(hire, oracle, d, N, B, k, kp):
     assert (np.abs(got["topk_val"].astype(np.float64) - want["topk_val"]) <= np.abs(want["topk_val"]) * (0.5 + 1e-3) * 2.0 ** -23).all()
 
 
-def test_infinite_weights_stay_in_their_columns(hire, oracle):
+def _infinite(y, plus, minus):
+    assert (y[:, plus] == np.inf).all() and (y[:, minus] == -np.inf).all()
+    assert np.isfinite(np.delete(y, [plus, minus], axis=1)).all()
+
+
+def _largest_everywhere(seed, d, N, B, at):
+    """A layer and B equal tokens whose largest activations are the units `at`; infinite in one column each."""
+    L = I.ffn_layer(seed, d, N)
+    x = np.repeat(I.tokens(seed + 1, 1, d), B, axis=0)
+    L["w1u"][at, :] = x[0, :]
+    L["w2u"][at[0], 5] = 0x7F80
+    L["w2u"][at[-1], 200] = 0xFF80
+    return L, x
+
+
+# one to eight tokens; the kernel with the second layer in it; the second layer by itself (1024 units; 96 MB of rows)
+@pytest.mark.parametrize("N,B,k,kp", [(2050, 16, 100, 300), (2050, 1, 100, 300), (2050, 1, 1, 2), (2050, 4, 100, 300), (2050, 4, 127, 300),
+                                      (2050, 8, 33, 300), (1024, 16, 52, 208), (1024, 16, 64, 208), (16384, 64, 3100, 4000)])
+@pytest.mark.parametrize("generic", [False, True])
+def test_infinite_weights_stay_in_their_columns(hire, oracle, N, B, k, kp, generic):
     """Rows that are selected for every token, the first and the last of its list, are infinite in one column each."""
-    d, N, B, k, kp = 256, 2050, 16, 100, 300
-    L = I.ffn_layer(1210, d, N)
-    x = np.repeat(I.tokens(1211, 1, d), B, axis=0)
-    L["w1u"][0, :] = L["w1u"][N - 1, :] = x[0, :]    # by far the largest activations
-    L["w2u"][0, 5] = 0x7F80
-    L["w2u"][N - 1, 200] = 0xFF80
+    print(f"infinite weights N={N} B={B} k={k} k'={kp} generic={generic}", flush=True)
+    L, x = _largest_everywhere(1210, 256, N, B, [0, N - 1] if k > 1 else [N - 1])
+    if k == 1:
+        L["w2u"][0, 5] = L["w2u"][N - 1, 200]
     layer, _ = T.make_ffn_layer(L)
-    y = T.run_ffn(layer, x, k, kp)["y"]
-    assert (y[:, 5] == np.inf).all() and (y[:, 200] == -np.inf).all()
-    assert np.isfinite(np.delete(y, [5, 200], axis=1)).all()
+    hire.hire_force_generic_path(generic)
+    try:
+        for r in T.run_ffn(layer, x, k, kp, steps=2):
+            _infinite(r["y"], 5, 200)
+    finally:
+        hire.hire_force_generic_path(False)
+
+
+@pytest.mark.parametrize("B", [1, 4, 8, 16])
+@pytest.mark.parametrize("k,kp,m1", [(104, 304, 0), (8, 16, 3), (104, 304, 300)])
+def test_infinite_weights_of_groups_and_dense_units(hire, oracle, B, k, kp, m1):
+    """The same for the last unit of the last selected group, and for the last of the dense units."""
+    print(f"infinite weights, groups, B={B} k={k} k'={kp} m1={m1}", flush=True)
+    d, N = 256, 2048
+    L, x = _largest_everywhere(1220, d, N, B, [N - 8, N - 1])
+    layer, _ = T.make_ffn_layer(L)
+    dense = None, None
+    if m1:
+        D = I.ffn_layer(1230, d, m1)
+        D["w1u"][m1 - 1, :] = x[0, :]
+        D["w2u"][m1 - 1, 5] = 0x7F80
+        dense = T.dev_bf16(D["w1u"]), T.dev_bf16(D["w2u"])
+    out = hire.FFNGroupOutputs(layer, B, k, kp, 8)
+    ws = hire.alloc_workspace(hire.hire_ffn_commonpath_workspace_bytes(layer, m1, B, k, kp, 8))
+    for _ in range(2):
+        hire.hire_ffn_commonpath_step(layer, *dense, T.dev_bf16(x), k, kp, 8, out, ws)
+        _infinite(out.y.cpu().numpy(), 5, 200)
+
+
+@pytest.mark.parametrize("shards,B,k,kp", [(16, 1, 80, 320), (16, 4, 48, 320), (16, 16, 48, 320), (8, 4, 600, 900), (8, 4, 66, 300)])
+def test_infinite_weights_of_shards(hire, oracle, shards, B, k, kp):
+    """The same for the first and last units of a layer in shards, whose lists do not come in fours."""
+    print(f"infinite weights, shards={shards} B={B} k={k} k'={kp}", flush=True)
+    N = 2048
+    L, x = _largest_everywhere(1240, 256, N, B, [0, N - 1])
+    layer, _ = T.make_ffn_layer(L)
+    for r in T.run_ffn_shard(layer, x, k, kp, shards, steps=2):
+        _infinite(r["y"], 5, 200)
