@@ -89,15 +89,16 @@ constexpr int kW2Threads = 512;
 constexpr int kW2Waves = kW2Threads / kWave;
 constexpr int kW2Chunk = 1024;  // entries staged in LDS at a time
 
-template <int LPR, int FL>
+template <int LPR, int FL, bool SHORT = false>
 __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __restrict__ W2, int d, int B, int k,
                                                            const uint2* __restrict__ list,
                                                            const uint16_t* __restrict__ Wd, int m1,
                                                            const double* __restrict__ hd, float* __restrict__ y) {
   constexpr int kCols = 8 * LPR;                         // columns of the workgroup
   constexpr int kStride = kW2Waves * (kWave / LPR);      // rows of the workgroup per load instruction
-  static_assert(kW2Chunk % (kStride * FL) == 0 && kCols <= kW2Threads, "whole batches per chunk, a thread per column");
-  constexpr int kBatch = kStride * FL, kFill = (kW2Chunk + kBatch + kW2Threads - 1) / kW2Threads;
+  static_assert((SHORT || kW2Chunk % (kStride * FL) == 0) && kCols <= kW2Threads, "whole batches per chunk, a thread per column");
+  constexpr int kBatch = kStride * FL, kChunk = SHORT ? kBatch : kW2Chunk;
+  constexpr int kFill = ((SHORT ? 0 : kW2Chunk) + kBatch + kW2Threads - 1) / kW2Threads;  // entries per thread
   __shared__ uint2 entries[kFill * kW2Threads];
   __shared__ float red[kW2Waves][kCols];
   const int lane = lane_id(), w = wave_id(), tid = (int)threadIdx.x;
@@ -112,21 +113,21 @@ __global__ __launch_bounds__(kW2Threads, 4) void k_w2_list(const uint16_t* __res
   for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
   // adds up the n entries in LDS (behind them some row with coefficient 0, to the end of one batch more)
   auto add_chunk = [&](const uint16_t* __restrict__ M, int n) {
-    add_listed_rows<LPR, FL, kW2Waves>(M + colc, d, n, first, [&](int t) { return entries[t]; }, acc);
+    add_listed_rows<LPR, FL, kW2Waves, SHORT>(M + colc, d, n, first, [&](int t) { return entries[t]; }, acc);
   };
   const uint2* mine = list + (size_t)b * k;
-  for (int e0 = 0; e0 < k; e0 += kW2Chunk) {
+  for (int e0 = 0; e0 < (SHORT ? 1 : k); e0 += kChunk) {
     if (e0 > 0) __syncthreads();
 #pragma unroll
     for (int u = 0; u < kFill; ++u) {
       const int i = u * kW2Threads + tid;
       const uint2 e = mine[min(e0 + i, k - 1)];
-      entries[i] = make_uint2(e.x, i < kW2Chunk && e0 + i < k ? e.y : 0u);
+      entries[i] = make_uint2(e.x, i < kChunk && e0 + i < k ? e.y : 0u);
     }
     __syncthreads();
-    add_chunk(W2, min(kW2Chunk, k - e0));
+    add_chunk(W2, min(kChunk, k - e0));
   }
-  for (int e0 = 0; e0 < m1; e0 += kW2Chunk) {
+  for (int e0 = 0; e0 < (SHORT ? 0 : m1); e0 += kW2Chunk) {
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kFill; ++u) {
@@ -228,10 +229,21 @@ hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* l
   // reduction count more the rule is too narrow (d = 256, k = 52: 3.5 against 2.9; d = 1024, k = 205, 33 tokens: 6.2
   // with 64 columns, 4.9 with 128).
   auto fill = [&](int n) { return (double)n / ((n + 255) / 256 * 256); };
-  if (items(256) >= 250 && fill(items(256)) > 0.9) return go(k_w2_list<32, 4>, 256);
-  if (items(128) >= 200 && fill(items(128)) > 0.6) return go(k_w2_list<16, 4>, 128);
-  if (items(64) >= 128) return go(k_w2_list<8, 8>, 64);
-  return go(k_w2_list<4, 8>, 32);
+  // Lists of up to eight loads per lane, and no dense rows, have kernels that ask for no second batch: by a branch inside the kernel it
+  // was slower than asking in vain (110 registers instead of 78).  us per step, two batches always / so: d = 256, k = 51 of 1024, eight
+  // tokens 22.4 / 21.7, 64 25.0 / 24.2; d = 800, k = 251 of 5003, five 26.8 / 26.3, 33 32.8 / 32.6; d = 2048, k = 256 of 16384, eight 39.4 / 39.0;
+  // d = 4096, k = 100 of 8192, 33 60.1 / 58.9 (59.2 with a branch around every request); groups of eight, d = 1024, 33 tokens 41.9 / 40.4.
+  auto pick = [&](auto l1, auto l2, auto l4, auto l8, auto longer, int cols) {
+    const int n = m1 == 0 ? (k * cols + 8 * kW2Threads - 1) / (8 * kW2Threads) : INT_MAX;  // a load: 8 columns per thread
+    return n <= 1 ? go(l1, cols) : (n <= 2 ? go(l2, cols) : (n <= 4 ? go(l4, cols) : (n <= 8 ? go(l8, cols) : go(longer, cols))));
+  };
+  if (items(256) >= 250 && fill(items(256)) > 0.9)
+    return pick(k_w2_list<32, 1, true>, k_w2_list<32, 2, true>, k_w2_list<32, 4, true>, k_w2_list<32, 8, true>, k_w2_list<32, 4>, 256);
+  if (items(128) >= 200 && fill(items(128)) > 0.6)
+    return pick(k_w2_list<16, 1, true>, k_w2_list<16, 2, true>, k_w2_list<16, 4, true>, k_w2_list<16, 8, true>, k_w2_list<16, 4>, 128);
+  if (items(64) >= 128)
+    return pick(k_w2_list<8, 1, true>, k_w2_list<8, 2, true>, k_w2_list<8, 4, true>, k_w2_list<8, 8, true>, k_w2_list<8, 8>, 64);
+  return pick(k_w2_list<4, 1, true>, k_w2_list<4, 2, true>, k_w2_list<4, 4, true>, k_w2_list<4, 8, true>, k_w2_list<4, 8>, 32);
 }
 
 }  // namespace hire

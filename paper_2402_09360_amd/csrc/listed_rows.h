@@ -12,9 +12,10 @@ namespace hire {
 // d values), the WAVES waves of a workgroup take kWave / LPR rows each per load.  `first`: this lane's first entry.  entry(t) has
 // to name a readable row with coefficient 0 for n <= t < n + 2 kBatch; what is read there is not used.  A lane has two batches of FL
 // rows in flight.  No request sits behind a branch, or the wait for the batch before it would be one for all that is under way,
-// and the rows of a batch are requested in the order in which they are added up, in which they return.  k_w2_list, us, with a
-// branch around the requests / this: 64 tokens at the ~1B shape 20.4 / 20.0, 16 tokens 10.1 / 9.6.
-template <int LPR, int FL, int WAVES, typename Entry>
+// and the rows of a batch are requested in the order in which they are added up, in which they return.  k_w2_list for 64 tokens at
+// the ~1B shape, us, with a branch around the requests / this: 20.4 / 20.0.
+// SHORT: n is one batch at most, and no second one is requested.
+template <int LPR, int FL, int WAVES, bool SHORT = false, typename Entry>
 __device__ __forceinline__ void add_listed_rows(const uint16_t* __restrict__ columns, int d, int n, int first,
                                                 Entry&& entry, float (&acc)[8]) {
   const char* base = reinterpret_cast<const char*>(columns);
@@ -48,6 +49,10 @@ __device__ __forceinline__ void add_listed_rows(const uint16_t* __restrict__ col
   uint4 wa[FL], wb[FL];
   float ca[FL], cb[FL];
   request(first, wa, ca);
+  if constexpr (SHORT) {
+    add(wa, ca, n);
+    return;
+  }
   request(first + kBatch, wb, cb);
   int t0 = 0;
   for (; t0 + 2 * kBatch < n; t0 += 2 * kBatch) {  // uniform

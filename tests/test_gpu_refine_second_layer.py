@@ -60,6 +60,19 @@ def test_values_from_64_bits_against_the_oracle(hire, oracle, d, N, B, k, kp):
     assert (np.abs(got["topk_val"].astype(np.float64) - want["topk_val"]) <= np.abs(want["topk_val"]) * (0.5 + 1e-3) * 2.0 ** -23).all()
 
 
+@pytest.mark.parametrize("d,B,rows", [(256, 16, 128), (1024, 8, 64), (1024, 30, 32), (1024, 64, 16)])  # rows per load of a workgroup
+def test_lists_of_every_number_of_loads(hire, oracle, d, B, rows):
+    """The second layer by itself, slices of 32 to 256 columns: one, two, four, eight loads per lane, and more; whole and not."""
+    N = 1101  # (odd: the values are rounded from 64 bits, by a kernel without the second layer)
+    L = I.ffn_layer(1250 + B, d, N)
+    layer, scorer = T.make_ffn_layer(L)
+    x = I.tokens(1251 + B, B, d)
+    for loads in (1, 2, 4, 8):
+        for k in (loads * rows - 1, loads * rows, loads * rows + 1):
+            print(f"d={d} B={B} k={k}", flush=True)
+            T.check_ffn(layer, scorer, L, x, k, N)
+
+
 def _infinite(y, plus, minus):
     assert (y[:, plus] == np.inf).all() and (y[:, minus] == -np.inf).all()
     assert np.isfinite(np.delete(y, [plus, minus], axis=1)).all()
