@@ -483,25 +483,28 @@ __global__ __launch_bounds__(kShThreads) void k_ffn_shard(
       float a[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) a[q] = 0.0f;
-      for (int t0 = 0; t0 < ks; t0 += 4) {
+      auto add_rows = [&](int t0, bool whole) __attribute__((always_inline)) {
         uint4 rv[4];
         float cf[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int p = sp[min(t0 + u, ks - 1)];
           rv[u] = load_streaming(&w2s[ulist[p] * c8 + cc]);
-          cf[u] = t0 + u < ks ? (float)hb[p] : 0.0f;
+          cf[u] = whole || t0 + u < ks ? (float)hb[p] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const uint32_t keep = t0 + u < ks ? 0xFFFFFFFFu : 0u;  // (an infinite weight behind the end is no 0 * inf)
+          const uint32_t keep = whole || t0 + u < ks ? 0xFFFFFFFFu : 0u;  // (an infinite weight behind the end is no 0 * inf)
           rv[u] = make_uint4(rv[u].x & keep, rv[u].y & keep, rv[u].z & keep, rv[u].w & keep);
           const float wf[8] = {bf16_lo(rv[u].x), bf16_hi(rv[u].x), bf16_lo(rv[u].y), bf16_hi(rv[u].y),
                                bf16_lo(rv[u].z), bf16_hi(rv[u].z), bf16_lo(rv[u].w), bf16_hi(rv[u].w)};
 #pragma unroll
           for (int q = 0; q < 8; ++q) a[q] = fmaf(cf[u], wf[q], a[q]);
         }
-      }
+      };
+      int t0 = 0;
+      for (; t0 + 4 <= ks; t0 += 4) add_rows(t0, true);
+      if (t0 < ks) add_rows(t0, false);
       float4* out = reinterpret_cast<float4*>(partial + ((size_t)sh * B + b0 + bb) * d + cc * 8);
       out[0] = make_float4(a[0], a[1], a[2], a[3]);
       out[1] = make_float4(a[4], a[5], a[6], a[7]);

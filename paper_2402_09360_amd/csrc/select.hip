@@ -352,7 +352,9 @@ __device__ __forceinline__ void select_row(const SelectParams& p, int b, SelShar
     auto ahead = [&](int o, int t) { return rk_key[o] > rk_key[t] || (rk_key[o] == rk_key[t] && o < t); };  // index order
     using Item = std::conditional_t<sizeof(K) == 4, unsigned long long, KeyAndNumber>;  // key and place in the list
     constexpr int kMost = kHistWindow * 4 / (int)sizeof(Item);                           // as many as the window's memory holds
-    if (!bucket_ranks<K>(k, own, [&](int t) { return rk_key[t]; }, ahead, win, list, k <= kMost ? rank_run(k) : k, sh, put)) {
+    const bool ranked = bucket_ranks<K>(
+        k, own, [&](int t) { return rk_key[t]; }, ahead, win, list, k <= kMost ? rank_run(k) : k, sh, put);
+    if (__builtin_expect(!ranked, 0)) {  // uniform
       Item* items = reinterpret_cast<Item*>(win);
       __syncthreads();
 #pragma unroll
@@ -919,7 +921,8 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
     }
   };
   auto larger = [](const AmbEntry& o, const AmbEntry& e) { return o.okey > e.okey || (o.okey == e.okey && o.idx < e.idx); };
-  if (!bucket_ranks<uint32_t>(n, own, [](const AmbEntry& e) { return e.okey; }, larger, bins, list, rank_run(n), sh, place)) {
+  const bool ranked = bucket_ranks<uint32_t>(n, own, [](const AmbEntry& e) { return e.okey; }, larger, bins, list, rank_run(n), sh, place);
+  if (__builtin_expect(!ranked, 0)) {  // uniform
 #pragma unroll
     for (int u = 0; u < kAmbCap / kSelThreads; ++u)
       if (u * kSelThreads + tid < n) both[u * kSelThreads + tid] = (unsigned long long)~own[u].okey << 32 | (uint32_t)own[u].idx;
@@ -937,7 +940,9 @@ __global__ __launch_bounds__(kSelThreads) void k_tk_final(const float* __restric
     if (val) val[rank] = key_value(e.okey);
   };
   auto lower = [](const AmbEntry& o, const AmbEntry& e) { return o.idx < e.idx; };
-  if (!bucket_ranks<uint32_t>(k, mine, [](const AmbEntry& e) { return ~(uint32_t)e.idx; }, lower, bins, list, rank_run(k), sh, write)) {
+  const bool listed = bucket_ranks<uint32_t>(
+      k, mine, [](const AmbEntry& e) { return ~(uint32_t)e.idx; }, lower, bins, list, rank_run(k), sh, write);
+  if (__builtin_expect(!listed, 0)) {  // uniform
 #pragma unroll
     for (int u = 0; u < kTkMaxK / kSelThreads; ++u)
       if (u * kSelThreads + tid < k) both[u * kSelThreads + tid] = (unsigned long long)(uint32_t)mine[u].idx << 32 | mine[u].okey;
