@@ -1014,6 +1014,11 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = fmaf(cf, wf[q], acc[q]);
   };
+  // what lies behind a list's end adds nothing, were its weight infinite
+  auto only_if = [&](bool counts, uint4& wv, auto& cf) __attribute__((always_inline)) {
+    cf = counts ? cf : 0;
+    wv = counts ? wv : make_uint4(0, 0, 0, 0);
+  };
   // the activations' window is valid on any workspace: this step's scorer kernel cleared it, its gather filled it
   const WinWalk wk = walk_window<kWT>(wr, p.k, sh);
   HIRE_TS(20);
@@ -1153,7 +1158,8 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
-          if (u < kLoads - 1 || u * kRowsPerLoad + slot < m) add_row(wv[u], raw[u]);  // (only the last load may not be whole)
+          if (u == kLoads - 1) only_if(u * kRowsPerLoad + slot < m, wv[u], raw[u]);  // (the others are whole)
+          add_row(wv[u], raw[u]);
           __builtin_amdgcn_sched_barrier(0);
         }
       };
@@ -1182,7 +1188,11 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < kW2Batch; ++u)
-        if (r0 + u * kWW * kRowsPerLoad + slot < p.m1) add_row(wv[u], (float)raw[u]);
+        if (r0 + u * kWW * kRowsPerLoad < p.m1) {
+          const int left = p.m1 - r0 - u * kWW * kRowsPerLoad;
+          if (left < kRowsPerLoad) only_if(slot < left, wv[u], raw[u]);  // uniform
+          add_row(wv[u], (float)raw[u]);
+        }
     }
     HIRE_TS(27);
     // fixed-order reduction: the slots of a DPP row (its last lanes then hold their sums), the rows of all
