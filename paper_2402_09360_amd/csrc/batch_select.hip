@@ -650,15 +650,17 @@ static int refine_grid(int items, const RefineParams& p) {
   return padded + (p.cand_out != nullptr && padded < 256 ? 1 : 0);
 }
 
-// Workgroups per token of k_refine_values, up to sixteen entries each where they are few: as many as one round has.  0: a
-// wave would have more than three rows, one after the other, and k_exact_values, whose waves have one each, is faster.  us per step with
-// that / with k_refine_values: d = 2048, k = 819 of 16384 units, 5 tokens 46.7 / 45.0, 6 49.1 / 47.3, 8 51.5 / 49.9, 12 (2.4 rows per wave) 56.4 /
-// 55.1, 15 (3) 57.5 / 57.3; k = 409 of 8191, 16 43.2 / 42.5, 33 (3.3) 54.3 / 54.3, 64 (6.4) 62.8 / 63.7; d = 4096, k = 409 of 8192, 5 54.7 / 53.5,
-// 15 65.7 / 63.9; d = 1024, k = 400 of 8000, 8 32.4 / 30.6; k = 819 of 16383, 8 42.1 / 41.1, 33 (6.6) 57.7 / 60.7; d = 800, k = 251 of 5003, 8 28.7 /
-// 27.6, 33 (2) 36.2 / 35.5; d = 512, k = 1200 of 24000, 8 47.0 / 46.3, 64 75.0 / 80.2; d = 256, k = 51 of 1024, 15 25.0 / 23.7.  Requesting a
-// wave's next two rows ahead, with the last one again past the end, was slower up to three rows (d = 800, 8 tokens 30.3).
+// Workgroups per token of k_refine_values, up to sixteen entries each where they are few: as many as one round has.  0: some wave would
+// have more than three rows, one after the other, and k_exact_values, whose waves have one each, is as fast or faster.  us per step with that /
+// with k_refine_values: d = 2048, k = 819 of 16384 units, 5 tokens 46.0 / 45.1, 8 51.3 / 50.0, 12 (three rows in some waves) 55.9 / 55.0, 15 57.0 /
+// 56.5; k = 409 of 8191, 16 39.6 / 38.3, 27 44.2 / 43.7, 33 (four) 51.1 / 50.8, 64 (seven) 62.8 / 63.7; d = 4096, k = 409 of 8192, 5 54.4 / 52.7, 15 65.2 /
+// 62.8; k = 51, 5 46.4 / 46.2; d = 1024, k = 400 of 8000, 8 29.5 / 27.9; k = 819 of 16383, 33 (seven) 57.7 / 60.7; k = 195 of 8001, 63 (four) 38.3 / 38.3; d = 800,
+// k = 251 of 5003, 8 27.2 / 26.5, 33 33.2 / 32.7, k = 337, 33 (four) 34.3 / 34.9; d = 512, k = 2449 of 12000, 5 (four) 35.4 / 35.1; k = 1200 of 24000, 64
+// 75.0 / 80.2; d = 256, k = 51 of 1024, 15 23.2 / 22.2, 64 25.3 / 24.5.  Requesting a wave's next two rows ahead, with the last one again past the
+// end, was slower up to three rows (d = 800, 8 tokens 30.3 instead of 27.6).
 static int refine_value_parts(int B, int k) {
-  return B * k > 3 * 256 * kSelWaves ? 0 : max(1, min(256 / B, (k + kSelWaves - 1) / kSelWaves));
+  const int parts = min(256 / B, (k + kSelWaves - 1) / kSelWaves);  // (B <= 64)
+  return (k + parts - 1) / parts > 3 * kSelWaves ? 0 : parts;
 }
 
 hipError_t launch_refine(const RefineParams& p, hipStream_t s) {

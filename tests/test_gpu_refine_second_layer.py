@@ -47,7 +47,8 @@ def test_against_the_oracle(hire, oracle, d, N, B, k, kp):
     (2080, 1501, 7, 33, 200),      # rows of more than one request of a wave
     (64, 16390, 6, 300, 1500),     # more units than 16384
     (8224, 1000, 5, 20, 100),      # a token that is not in LDS
-    (64, 2001, 33, 372, 800), (64, 2001, 33, 373, 800),  # three rows per wave, and more: the kernel behind the list
+    (64, 2001, 33, 336, 800), (64, 2001, 33, 337, 800),  # three rows per wave, and a wave with four: the kernel behind the list
+    (64, 2001, 63, 192, 800), (64, 2001, 63, 193, 800),
 ])
 def test_values_from_64_bits_against_the_oracle(hire, oracle, d, N, B, k, kp):
     print(f"ffn_step d={d} N={N} B={B} k={k} k'={kp}", flush=True)
