@@ -100,13 +100,16 @@ bool ffn_filter(const StepBuffers& s, int B) { return s.by_unit && (B >= kFilter
 
 // Softmax step, filter and refine: for which unions (of at most cap_u classes) and k the refining selection is cheaper than
 // ranking fp64 logits.  It finds its mark from the filter stage's maxima, up to four per workgroup; with few more than k of
-// them much of the union lies above the mark, with fewer than k all of it, and what does not fit the slots goes through one
-// workgroup in rounds.  The maxima are counted for a union of 1.5 k' too, about what tokens of one query leave; beyond 32 tokens
-// it is larger, and ranking dearer.  40000 classes of d = 512, us per step, fp64 / refined: k' = 1536, k = 128, eight tokens
-// 60.9 / 46.4, fifteen 85.7 / 51.7; k' = 256, k = 128, three (48 maxima) 34 / 89, eight (128) 37 / 396, fifteen (240) 40 / 46;
-// k' = 1024, k = 512, eight 68 / 1929, fifteen 77 / 107, 64 (1024) 205 / 127.  Two tokens: k' = 1024, k = 16 36.4 / 37.4.  Long
-// unions: 256000 classes of d = 2048, 64 tokens, k' = 1200, k = 100 681 / 200, k' = 1536, k = 128 814 / 217; 100000 of 512,
-// k' = 1100, k = 64 278 / 77.  The longest is what 256 workgroups of the filter stage list in LDS.
+// them much of the union lies above the mark, with fewer than k all of it, and what does not fit the slots is ranked in rounds.  The
+// maxima are counted for a union of 1.5 k' too, about what tokens of one query leave, and as if every workgroup had 64 classes;
+// small unions go to up to four times as many workgroups of sixteen, with more maxima, but where they are too few by this count
+// fp64 is still the faster one.  Beyond 32 tokens the union is larger, and ranking dearer.  us per step, fp64 / refined, * the rule: 40000
+// classes of d = 512, k' = 1536, k = 128, eight tokens 52.5 / 44.4*, fifteen 78.5 / 50.8*; k' = 256, k = 128, three (48 maxima by this count)
+// 33.2* / 41.4, of one query 33.1* / 48.3, eight (128) 36.8* / 39.5, fifteen (240) 39.1* / 41.3; k' = 1024, k = 512, sixteen 58.7* / 104.6, 64 189.6 /
+// 125.7*; k = 256, eight 47.5 / 49.2*, fifteen 57.0 / 55.9*; k' = 256, k = 64, 17 44.9 / 41.6*, 64 90.7 / 55.9*.  256000 classes of d = 2048, k' = 1024, k = 128,
+// three 79.6* / 85.0, eight 97.5 / 89.6*, fifteen 119.3 / 102.3*; k = 256, 64 589.7 / 203.9*; k' = 1200, k = 100, 64 681 / 200*.  A few tokens with
+// short lists would be faster through fp64 too: k' = 512, k = 64, three 32.9* / 36.6, eight 36.5 / 38.3*, of 256000 classes 82.0 / 84.7*; k' = 256, k = 16,
+// three 31.0 / 34.6*.  The longest union is what 256 workgroups of the filter stage list in LDS.
 bool softmax_filter(int B, int cap_u, int k, int kprime) {
   if (B < 3 || cap_u > kSoftmaxRefineMaxRow || k > (B < 16 ? kSoftmaxRefineMaxK / 2 : kSoftmaxRefineMaxK)) return false;
   const int blocks = min(filter_tiles(cap_u), 256), each = (kprime + kprime / 2 + blocks - 1) / blocks;

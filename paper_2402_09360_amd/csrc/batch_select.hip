@@ -48,6 +48,10 @@ struct RefineShared {
 // ones outside the band) with ties to the lower unit, packed into LDS in order.  The fp64 values lie in the order of the
 // candidates; a wave owns the units [i_lo, i_hi) and so the candidates from c_lo on.  Workgroups that select for the same token
 // share the scratch: each place is written once by each of them, with the same value, and read by its own writer behind a barrier.
+// What all of them read again comes from the caches.  us per step with 400 copies of a unit near the threshold, one workgroup per token
+// doing this / all of them: ~1B shape, 16 equal tokens, copies at random units 162.6 / 152.0, in a row 567.7 / 542.1, five tokens 165.9 / 154.7, 571.9 /
+// 548.4; d = 800, 5003 units, 33 tokens 96.5 / 89.1; d = 1024, 8000 units, 64 tokens 113.0 / 105.2 (without copies 47.6 / 45.4, 45.7 / 44.0, 36.6 / 33.4,
+// 37.3 / 32.5).
 __device__ __forceinline__ void refine_streaming(const RefineParams& p, int b, const uint4* tok, RefineShared& L, double hw) {
   const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int N = p.N, k = p.k;
@@ -705,10 +709,11 @@ static int refine_w2_columns(int B, int d) {
 }
 // Where the rows are many (96 MB, several tokens' repeats counted) the caches bound the second layer, and k_w2_list's even shares of
 // a die serve more of them from its L2: wide slices of one token per workgroup make two dies read the same columns, and 256 workgroups
-// read values and band.  us per step with k_refine and k_w2_list / this kernel, d = 2048, k = 819 of 16384 units: 16 tokens 49.9 / 48.9,
-// 24 56.9 / 56.1, 28 57.7 / 57.3 (94 MB), 32 58.8 / 59.5, 33 62.8 / 63.6, 48 64.6 / 65.6, 64 68.4 / 71.5 (with nine tenths in common 63.6 /
-// 61.5); d = 4096, k = 409 of 8192: 16 57.6 / 56.0, 33 66.1 / 66.3, 64 74.6 / 74.8; d = 1024, k = 400 of 8000: 16 30.6 / 29.5, 33 37.0 / 35.3,
-// 64 39.3 / 38.2; d = 512, k = 200 of 4000: 16 23.6 / 22.8, 64 29.0 / 27.9; d = 256, k = 51 of 1024: 24.7 / 24.8, 30.3 / 30.5.
+// read values and band.  us per step with k_refine and k_w2_list / this kernel, d = 2048, k = 819 of 16384 units: 16 tokens 49.1 / 47.7,
+// 24 55.6 / 54.4, 28 55.7 / 55.0 (94 MB), 32 58.8 / 59.5, 33 62.8 / 63.6, 48 64.6 / 65.6, 64 68.4 / 71.5 (with nine tenths in common 63.6 /
+// 61.5); k = 327, 33 58.4 / 57.3, 64 62.7 / 62.6; k = 51, 64 50.5 / 52.0; d = 4096, k = 409 of 8192, 16 56.7 / 55.3, 32 59.8 / 59.7, k = 100, 16 46.6 / 45.0;
+// d = 1024, k = 400 of 8000, 16 27.1 / 25.9, 33 31.4 / 30.0, 64 33.6 / 32.3; d = 512, k = 200 of 4000, 16 22.0 / 21.4, 64 26.4 / 26.0; d = 256, k = 51 of 2048,
+// 16 20.7 / 19.9, 64 23.4 / 23.4; d = 64, k = 200 of 4000, 64 24.5 / 23.6.
 constexpr long long kRefineW2Bytes = 96ll << 20;
 bool refine_w2_supported(const RefineParams& p) {
   return p.N <= 16384 && !p.exact_values && refine_w2_columns(p.B, p.d) != 0 &&

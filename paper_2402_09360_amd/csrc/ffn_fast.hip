@@ -1381,9 +1381,9 @@ hipError_t launch_ffn_fast(const FfnFastArgs& a, hipStream_t s) {
     // The narrowest slices whose workgroups fit the compute units, one each: what is left over would wait for a whole
     // workgroup's time (registers do not admit two).  Two workgroups more per token write the selected entries and the
     // shortlist; where slices of half the width fit without them, the slices' workgroups do it for groups of eight (four tokens
-    // of d = 2048 with 2736 dense units: 39.2 us per step against 40.4, eight: 52.8 against 58.3).  Not for units: four tokens at
-    // the ~1B shape take 36.0 us instead of 37.9 where one layer is run again and again, but 38.2 instead of 37.9 where its
-    // rows come from HBM.
+    // of d = 2048 with 2736 dense units: 39.2 us per step against 40.4, eight: 52.8 against 58.3).  Not for units, us per step
+    // without / with it: four tokens at the ~1B shape 35.3 / 35.2, with the rows in the caches 35.2 / 35.6, 8192 units 30.6 / 31.1, 4000
+    // 28.9 / 29.5; eight of d = 1024, 8000 units 28.1 / 29.5; two of d = 4096, 8192 units 33.5 / 34.2.
     const int extra = (a.topk_idx || a.topk_val ? 1 : 0) + (a.cand_out || (several && a.n_cand) ? 1 : 0);
     int cols = 32, cols_alone = 32;  // with the extra workgroups, without
     while (cols < 128 && ((a.d + cols - 1) / cols + extra) * a.B > 256) cols *= 2;

@@ -1,7 +1,8 @@
-"""The softmax step's filter and refine on unions of more classes than one mask of the refining selection stands for: just
-beyond 65536 and as many as the route takes; a token of zeros, whose logits are all equal.  Against the oracle; on no more
-workspace than fp64 logits of the union take.  Tokens with more equal logits than the selection has slots, which are
-settled in rounds, span by span; what such a token may cost."""
+"""The softmax step's filter and refine where the union may have more classes than one mask of the refining selection stands for:
+layouts for just more than 65536 and for as many as the route takes, on no more workspace than the route through fp64 logits, with
+a token of zeros, whose logits are all equal; unions that have 65535 to 65537 and 131072 classes.  Against the oracle.
+Tokens with more equal logits than the selection has slots, which are settled in rounds, span by span; what such a token
+may cost."""
 import numpy as np
 import pytest
 import torch
@@ -28,10 +29,9 @@ def test_softmax_long_union(hire, oracle, d, c, B, k, kp):
     layer, scorer = T.make_softmax_layer(W)
     x = I.tokens(1301, B, d)
     x[1, :] = 0
-    got, _ = T.check_softmax(layer, scorer, W, x, k, kp)
-    print(f"union of {len(got['cand'])}", flush=True)
-    rows = min(c, B * kp)
-    assert hire.hire_softmax_workspace_bytes(layer, B, k, kp) >= 8 * B * rows
+    T.check_softmax(layer, scorer, W, x, k, kp)
+    # (more than 512 logits go through fp64 always)
+    assert hire.hire_softmax_workspace_bytes(layer, B, k, kp) <= hire.hire_softmax_workspace_bytes(layer, B, 513, kp)
 
 
 def _tiling(c, d, seed):
