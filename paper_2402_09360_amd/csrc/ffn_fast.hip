@@ -1158,8 +1158,7 @@ __global__ __launch_bounds__(kWT) void k_fast_w2(FastW2Params p) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
-          if (u == kLoads - 1) only_if(u * kRowsPerLoad + slot < m, wv[u], raw[u]);  // (the others are whole)
-          add_row(wv[u], raw[u]);
+          if (u < kLoads - 1 || u * kRowsPerLoad + slot < m) add_row(wv[u], raw[u]);  // (only the last load may not be whole)
           __builtin_amdgcn_sched_barrier(0);
         }
       };
