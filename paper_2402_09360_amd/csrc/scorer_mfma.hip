@@ -382,15 +382,15 @@ int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 // or have them quantised in front / with parts: d = 2048, 16384 rows, 20 tokens 54.3 / 54.8, 24 55.5 / 55.0, 32 59.2 / 57.8; d = 1024, 8000 rows,
 // 20 29.2 / 29.2, 24 30.1 / 29.6, 32 32.1 / 30.7, 33 34.7 / 33.1, 64 37.9 / 35.1; d = 800, 5003 rows, 22 31.2 / 30.7, 33 35.4 / 33.1, 64 39.9 / 37.3; d = 512,
 // 4000 rows, 33 24.8 / 24.6, 64 28.0 / 25.7; d = 256, 1024 rows, 33 26.3 / 25.0, 64 29.2 / 26.1; d = 1504, 12000 rows, 32 43.9 / 42.2.
-// Short tokens are soon quantised, and many rows read again take longer: d = 512, 6000 rows, 21 tokens 22.6 / 23.4, 25 23.4 / 23.7, 16000 rows,
-// 25 31.1 / 31.5, 32 32.7 / 32.6; d = 256, 8000 rows, 21 22.6 / 23.6, 25 23.3 / 23.9, 32 24.2 / 24.3.  Long ones with more than 8192 rows: d = 1024,
-// 16000 rows, 21 tokens 37.0 / 37.4, 25 35.5 / 35.5, d = 1536, 12000 rows, 21 33.5 / 34.0, 25 34.7 / 34.5.
+// With four requests of rows at a time for every length, most of which a wave of short rows has no use for, 47 tokens on 5200 rows of 256 27.2
+// instead of 24.2, 25 on 6000 rows of 512 23.6 instead of 22.4 (23.0 with all tokens quantised by every workgroup).
+// Long tokens with more than 8192 rows: d = 1024, 16000 rows, 21 tokens 37.0 / 37.4, 25 35.5 / 35.5, d = 1536, 12000 rows, 21 33.5 / 34.0, 25 34.7 / 34.5.
 // Rows of a workgroup, at least:
 static int scorer_part_rows(int B, int N) { return (N * ((B + 15) / 16) + 255) / 256; }
 static bool scorer_mfma_parts(int B, int N, int d) {
   static_assert(8192 * 4 / 256 <= 128 && 128 * 1024 <= 256 << 10, "more than 32 tokens that scorer_mfma_rows quantises: rows beyond 8192 only");
   const int rows = scorer_part_rows(B, N), tile = rows <= 16 ? 16 : (rows <= 32 ? 32 : (rows <= 64 ? 64 : 128));
-  const int fewest = N > 4096 && d <= 512 ? 29 : (N > 8192 ? 25 : 21);
+  const int fewest = d > 512 && N > 8192 ? 25 : 21;
   return B >= fewest && d <= 2048 && rows <= 128 && (long long)tile * d <= 256 << 10;
 }
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
@@ -434,9 +434,10 @@ template <int VECS>
 static hipError_t scorer_parts_rows(ScorerBatch& p, hipStream_t s) {
   const int rows = scorer_part_rows(p.B, p.N);
   auto grid = [&](int tile) { return ((p.N + tile - 1) / tile + 7) / 8 * 8 * p.parts; };
-  if (rows > 64) return scorer_mfma_launch<1, 1, 8, 2, 4, kBf16, VECS, true>(p, grid(128), s);
-  if (rows > 32) return scorer_mfma_launch<1, 1, 4, 4, 4, kBf16, VECS, true>(p, grid(64), s);
-  if (rows > 16) return scorer_mfma_launch<1, 1, 2, 8, 2, kBf16, VECS, true>(p, grid(32), s);
+  constexpr int kSteps = 4 * VECS;  // of a row, at most; a wave requests no more of them at a time than its share
+  if (rows > 64) return scorer_mfma_launch<1, 1, 8, 2, kSteps >= 8 ? 4 : 2, kBf16, VECS, true>(p, grid(128), s);
+  if (rows > 32) return scorer_mfma_launch<1, 1, 4, 4, kSteps / 4, kBf16, VECS, true>(p, grid(64), s);
+  if (rows > 16) return scorer_mfma_launch<1, 1, 2, 8, kSteps >= 16 ? 2 : 1, kBf16, VECS, true>(p, grid(32), s);
   return scorer_mfma_launch<1, 1, 1, 16, 1, kBf16, VECS, true>(p, grid(16), s);
 }
 
@@ -454,6 +455,7 @@ static hipError_t scorer_mfma_tokens(ScorerBatch& p, hipStream_t s) {
   if (p.tok.x == nullptr) return scorer_mfma_rows<CT, 2, kCodes, 2>(p, s);
   if (!p.tok.f32 && scorer_mfma_parts(p.B, p.N, p.d)) {
     p.parts = (p.B + 15) / 16;
+    if (p.d <= 512) return scorer_parts_rows<1>(p, s);
     if (p.d <= 1024) return scorer_parts_rows<2>(p, s);
     return scorer_parts_rows<4>(p, s);
   }

@@ -54,7 +54,8 @@ def test_ffn_rows(hire, oracle, d, N, B):
     (160, 2049, 21), (64, 2731, 48), (1024, 2100, 49),               # of one token and of sixteen; 32 rows
     (2048, 4097, 21), (544, 5461, 48), (64, 8000, 17),               # 64; (17 tokens take no parts)
     (2048, 8193, 25), (1056, 8192, 49), (32, 10922, 33),             # 128
-    (512, 4097, 28), (512, 4097, 29), (512, 4096, 21), (544, 8193, 24), (544, 8192, 24),  # short tokens, many rows: more tokens
+    (512, 8193, 24), (544, 8193, 24), (544, 8192, 24), (544, 8193, 25),  # long tokens, many rows: from 25 on
+    (512, 4097, 28), (1024, 4097, 28), (1056, 4097, 28), (512, 2049, 28), (1056, 2049, 28),  # steps per wave: one, two, four; 32 rows
     (32, 10923, 33), (2080, 1000, 33), (32, 16385, 21)])             # past each limit
 def test_parts_of_sixteen_tokens(hire, oracle, d, N, B):
     log(f"ffn_step d={d} N={N} B={B}")
