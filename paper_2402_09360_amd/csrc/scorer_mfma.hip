@@ -379,19 +379,25 @@ int scorer_mfma_maxima(int N) { return 2 * kVocabWaves * vocab_blocks(N); }
 // sixteen tokens, from the L2 of one die.  Where one round of workgroups has a single tile of up to 128 rows and 128 KB of codes each; three
 // parts of 16384 rows would leave two tiles to some (33 tokens of 2048: 62.9 -> 65.3 us per step, 64 68.1 -> 69.7), and twice as many codes
 // as that take as long as the kernel in front (33 of 4096, 8192 rows 66.2 -> 68.9).  us per step with the kernels that quantise all tokens
-// or have them quantised in front / with parts: d = 2048, 16384 rows, 20 tokens 54.3 / 54.8, 24 55.5 / 55.0, 32 59.2 / 57.8; d = 1024, 8000 rows,
-// 20 29.2 / 29.2, 24 30.1 / 29.6, 32 32.1 / 30.7, 33 34.7 / 33.1, 64 37.9 / 35.1; d = 800, 5003 rows, 22 31.2 / 30.7, 33 35.4 / 33.1, 64 39.9 / 37.3; d = 512,
-// 4000 rows, 33 24.8 / 24.6, 64 28.0 / 25.7; d = 256, 1024 rows, 33 26.3 / 25.0, 64 29.2 / 26.1; d = 1504, 12000 rows, 32 43.9 / 42.2.
+// or have them quantised in front / with parts: d = 2048, 16000 rows, 21 tokens 48.3 / 48.4, 25 50.0 / 49.7, 32 53.5 / 52.6, 5200 rows, 47 38.7 / 37.9;
+// d = 1536, 10000 rows, 25 32.9 / 33.0, 12000, 32 36.4 / 35.7; d = 1024, 8000 rows, 21 26.7 / 25.9, 33 31.0 / 29.8, 64 34.9 / 32.3, 16000, 21 37.0 / 37.4;
+// d = 768, 5200 rows, 33 27.9 / 26.6, 47 29.8 / 27.8; d = 512, 6000 rows, 21 22.5 / 22.0, 4000, 64 27.4 / 24.5, 16000, 25 31.0 / 30.6; d = 256, 1000 rows, 33
+// 24.3 / 22.9, 64 27.3 / 24.1, 8000, 21 22.7 / 22.2.
 // With four requests of rows at a time for every length, most of which a wave of short rows has no use for, 47 tokens on 5200 rows of 256 27.2
-// instead of 24.2, 25 on 6000 rows of 512 23.6 instead of 22.4 (23.0 with all tokens quantised by every workgroup).
-// Long tokens with more than 8192 rows: d = 1024, 16000 rows, 21 tokens 37.0 / 37.4, 25 35.5 / 35.5, d = 1536, 12000 rows, 21 33.5 / 34.0, 25 34.7 / 34.5.
-// Rows of a workgroup, at least:
-static int scorer_part_rows(int B, int N) { return (N * ((B + 15) / 16) + 255) / 256; }
+// instead of 24.2, 25 on 6000 rows of 512 23.6 instead of 22.4.
+// Rows of a workgroup: so many that a round of 32 workgroups per die has them all, an eighth of the tiles and all parts of these; 0: more
+// than 128 would be needed.  With as few as 256 workgroups hold, of which a die or two had one too many for a round, three parts of 5200
+// rows: 47 tokens of 2048 40.5 instead of 37.9 us per step, of 768 30.6 instead of 27.8, of 256 24.2 instead of 23.5.
+static int scorer_part_tile(int B, int N) {
+  const int parts = (B + 15) / 16;
+  for (int tile = 16; tile <= 128; tile *= 2)
+    if (((N + tile - 1) / tile + 7) / 8 * parts <= 32) return tile;
+  return 0;
+}
 static bool scorer_mfma_parts(int B, int N, int d) {
-  static_assert(8192 * 4 / 256 <= 128 && 128 * 1024 <= 256 << 10, "more than 32 tokens that scorer_mfma_rows quantises: rows beyond 8192 only");
-  const int rows = scorer_part_rows(B, N), tile = rows <= 16 ? 16 : (rows <= 32 ? 32 : (rows <= 64 ? 64 : 128));
-  const int fewest = d > 512 && N > 8192 ? 25 : 21;
-  return B >= fewest && d <= 2048 && rows <= 128 && (long long)tile * d <= 256 << 10;
+  static_assert(8192 <= 64 * 128 && 128 * 1024 <= 256 << 10, "more than 32 tokens that scorer_mfma_rows quantises: rows beyond 8192 only");
+  const int fewest = d > 512 && N > 8192 ? 25 : 21, tile = scorer_part_tile(B, N);
+  return B >= fewest && d <= 2048 && tile != 0 && (long long)tile * d <= 256 << 10;
 }
 bool scorer_mfma_quantises(int B, int N, int d, bool f32) {
   if (N >= kVocabMinRows) return false;
@@ -432,13 +438,14 @@ static hipError_t scorer_mfma_rows(ScorerBatch& p, hipStream_t s) {
 // The same for sixteen tokens per workgroup, the workgroups of eight tiles and all parts after one another.
 template <int VECS>
 static hipError_t scorer_parts_rows(ScorerBatch& p, hipStream_t s) {
-  const int rows = scorer_part_rows(p.B, p.N);
-  auto grid = [&](int tile) { return ((p.N + tile - 1) / tile + 7) / 8 * 8 * p.parts; };
+  const int tile = scorer_part_tile(p.B, p.N), grid = ((p.N + tile - 1) / tile + 7) / 8 * 8 * p.parts;
   constexpr int kSteps = 4 * VECS;  // of a row, at most; a wave requests no more of them at a time than its share
-  if (rows > 64) return scorer_mfma_launch<1, 1, 8, 2, kSteps >= 8 ? 4 : 2, kBf16, VECS, true>(p, grid(128), s);
-  if (rows > 32) return scorer_mfma_launch<1, 1, 4, 4, kSteps / 4, kBf16, VECS, true>(p, grid(64), s);
-  if (rows > 16) return scorer_mfma_launch<1, 1, 2, 8, kSteps >= 16 ? 2 : 1, kBf16, VECS, true>(p, grid(32), s);
-  return scorer_mfma_launch<1, 1, 1, 16, 1, kBf16, VECS, true>(p, grid(16), s);
+  switch (tile) {
+    case 16: return scorer_mfma_launch<1, 1, 1, 16, 1, kBf16, VECS, true>(p, grid, s);
+    case 32: return scorer_mfma_launch<1, 1, 2, 8, kSteps >= 16 ? 2 : 1, kBf16, VECS, true>(p, grid, s);
+    case 64: return scorer_mfma_launch<1, 1, 4, 4, kSteps / 4, kBf16, VECS, true>(p, grid, s);
+    default: return scorer_mfma_launch<1, 1, 8, 2, kSteps >= 8 ? 4 : 2, kBf16, VECS, true>(p, grid, s);
+  }
 }
 
 template <int CT>

@@ -56,6 +56,7 @@ def test_ffn_rows(hire, oracle, d, N, B):
     (2048, 8193, 25), (1056, 8192, 49), (32, 10922, 33),             # 128
     (512, 8193, 24), (544, 8193, 24), (544, 8192, 24), (544, 8193, 25),  # long tokens, many rows: from 25 on
     (512, 4097, 28), (1024, 4097, 28), (1056, 4097, 28), (512, 2049, 28), (1056, 2049, 28),  # steps per wave: one, two, four; 32 rows
+    (64, 1280, 33), (64, 1281, 33), (544, 2561, 48), (1056, 5120, 40), (1056, 5121, 40), (512, 10240, 47), (512, 10241, 47),  # a round of every die
     (32, 10923, 33), (2080, 1000, 33), (32, 16385, 21)])             # past each limit
 def test_parts_of_sixteen_tokens(hire, oracle, d, N, B):
     log(f"ffn_step d={d} N={N} B={B}")
