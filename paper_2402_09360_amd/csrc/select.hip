@@ -1278,9 +1278,9 @@ __global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
   if (tid == 0) sp_counts(p.refine_slots, b)[part] = m;
   const int32_t* map = p.map + (size_t)b * p.map_stride;
   const uint16_t* tok = p.refine_x + (size_t)b * p.refine_d;
-  unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
   if (m > cap) {  // uniform: the logits only, for the second kernel
     if (softmax_all_zero<kSpThreads>(mark, tok, p.refine_d)) return;  // uniform: it needs none
+    unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
     for (int i0 = part * kWave + w * step; i0 < n; i0 += NW * step) {
       const int i = min(i0 + lane, n - 1), cls = map[i];
       for (uint64_t in = __ballot(i0 + lane < n && order_key(vals[i]) >= mark.key); in != 0ull;) {  // uniform
@@ -1322,10 +1322,7 @@ __global__ __launch_bounds__(kSpThreads) void k_softmax_parts(SelectParams p) {
   }
   __syncthreads();
   SmEntry* out = sp_entries(p.refine_slots, B, b) + part * cap;
-  for (int t = tid; t < m; t += kSpThreads) {
-    out[t] = SmEntry{l_key[t], l_pos[t], 0};
-    keys[l_pos[t]] = l_key[t];  // (another part may have more than its slots)
-  }
+  for (int t = tid; t < m; t += kSpThreads) out[t] = SmEntry{l_key[t], l_pos[t], 0};
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) {
@@ -1355,7 +1352,7 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
   SmMarked mark{1u, 0.0, false};
   int have = 0, cur = 0;              // entries of the best list so far, and which of its two copies holds them
   const float* vals = reinterpret_cast<const float*>(p.vals) + (size_t)b * p.stride;
-  const unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
+  unsigned long long* keys = p.refine_keys + (size_t)b * p.refine_keys_stride;
   auto scan = [&]() {  // value i of thread t is entry first + t + 1024 i
     const int n = min(end - first, kSmSpan);
     for (int i0 = 0; kSelThreads * i0 < n; i0 += 16) {  // uniform
@@ -1390,6 +1387,10 @@ __global__ __launch_bounds__(kSelThreads) void k_softmax_refine(SelectParams p) 
       at += __popcll(vm[u]);
     }
   } else {
+    // the parts that have not more than their slots: theirs by position too, behind the next barriers
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u)
+      if ((tid + u * kSelThreads) % cap < have_n[u] && have_n[u] <= cap) keys[entry[u].pos] = entry[u].key;
     mark = softmax_mark<kSelThreads>(p, b, S);
     HIRE_TS(51);
     if (softmax_all_zero<kSelThreads>(mark, p.refine_x + (size_t)b * p.refine_d, p.refine_d)) {  // uniform
