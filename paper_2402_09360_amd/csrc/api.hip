@@ -178,7 +178,6 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   const bool sm_filter = !ffn && gs == 0 && softmax_filter(B, s.cap_u, k, kprime);
   auto sm_buffers = [&](Carver& at) {
     s.xnorm = at.take<float>(HIRE_MAX_BATCH);
-    s.wnorm_tiles = at.take<float>(filter_rank_blocks(s.cap_u));
     s.maxima = at.take<float>((size_t)B * kFilterMaxima);
     s.refine_slots = at.take<char>(softmax_refine_slot_bytes(B));
   };
@@ -192,6 +191,8 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
     s.hf = static_cast<float*>(s.keys);  // nobody reads the keys any more when the filter stage runs
   } else if (sm_filter && !sm_long) {
     sm_buffers(c);
+    s.hf_stride = (s.cap_u + 3) / 4 * 4;
+    s.hf = c.take<float>((size_t)B * s.hf_stride);
   }
   const size_t h_doubles = ((size_t)B * s.cap_u << gs) + 2, fast_doubles = fast ? (size_t)B * ffn_fast_entries(N, gs) : 0;
   s.h = c.take<double>(h_doubles > fast_doubles ? h_doubles : fast_doubles);
@@ -212,14 +213,19 @@ StepBuffers carve(void* ws, int scorer_kind, int B, int d, int N, int r, int k, 
   s.sm1_ok = !ffn && B == 1 && gs == 0 && int4_like && N > kSingleWgMaxRow && softmax_b1_supported(N, d, 1, 1);
   s.max_ok = gs == 0 && int4_like && N > kSingleWgMaxRow && maxima_select_supported(N);
   if (s.sm1_ok || s.max_ok) s.sm1_slots = c.take<char>(maxima_select_slot_bytes(B, N));
-  // The fp32 logits lie in the place of the keys, which nobody reads any more when the filter stage runs.  Long unions ask for no more
-  // workspace than the route through fp64 logits: the rest (37 KB per token) lies where the selection of k' had its slots (64 KB), or
-  // behind the fp32 logits where it has none: fp64 keys, and keys of more than 262144 classes, leave 256 KB per token there.
+  // Long unions ask for no more workspace than the route through fp64 logits: their fp32 logits lie in the place of the keys, which nobody
+  // reads any more when the filter stage runs, and the rest (37 KB per token) where the selection of k' had its slots (64 KB), or
+  // behind the fp32 logits where it has none: fp64 keys, and keys of more than 262144 classes, leave 256 KB per token there.  Shorter
+  // ones have places of their own, but for the row norms, of which there may be more than there once were; with the logits in the keys' place
+  // too, 35 tokens of d = 352, 48950 classes took 56.5 us per step instead of 55.6, 36 of d = 1760, 117306 classes 82.6 instead of 81.5.
   if (sm_filter) {
     Carver in_keys(s.keys), in_slots(s.sm1_slots);
-    s.hf_stride = s.cap_u;
-    s.hf = in_keys.take<float>((size_t)B * s.hf_stride);
-    if (sm_long) sm_buffers(s.max_ok ? in_slots : in_keys);
+    if (sm_long) {
+      s.hf_stride = s.cap_u;
+      s.hf = in_keys.take<float>((size_t)B * s.hf_stride);
+      sm_buffers(s.max_ok ? in_slots : in_keys);
+    }
+    s.wnorm_tiles = in_keys.take<float>(filter_rank_blocks(s.cap_u));
   }
   if (ffn) {
     if (gs > 0) s.pos = c.take<int32_t>((size_t)B * (k >> gs));
