@@ -228,7 +228,7 @@ hipError_t launch_w2_list(const uint16_t* W2, int d, int B, int k, const void* l
   // Of 28 shapes 22 within 4 % of the best width, 12 tokens and the last of these 7 to 10 % off; where few rows make the
   // reduction count more the rule is too narrow.  Short lists, us per step: d = 256, k = 51 of 1024, five tokens 21.1 / 21.2 / 21.3 / 21.5*;
   // d = 1024, k = 205 of 4096, 33 29.2 / 28.8 / 29.6* / 31.5, 64 31.0 / 30.4 / 31.8 / 35.1 (the rule 30.9: 256); groups of eight, k = 104, 33 39.5 / 39.5 / 40.5* /
-  // 42.3, with 304 dense units 48.0 / 48.1 / 50.5* / 55.0; d = 2048, k = 256 of 16384, 33 50.8 / 50.3* / 50.5 / 53.5.
+  // 42.3, with 304 dense units 48.0 / 48.1 / 50.5* / 55.0; d = 2048, k = 256 of 16384, 33 50.8 / 50.5* / 50.5 / 53.5.
   auto fill = [&](int n) { return (double)n / ((n + 255) / 256 * 256); };
   // Lists of up to eight loads per lane, and no dense rows, have kernels that ask for no second batch: by a branch inside the kernel it
   // was slower than asking in vain (110 registers instead of 78).  us per step, two batches always / so: d = 256, k = 51 of 1024, eight

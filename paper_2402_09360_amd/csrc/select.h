@@ -416,9 +416,9 @@ __device__ __forceinline__ void sort_list(T* list, int n, const T& last) {
 // between the smallest and the largest go to 4096 equal bins; the addition that counts a bin's items gives each its place in the
 // bin, a scan gives every bin's first rank, the items are listed bin by bin and each counts those ahead of it inside its bin: a few
 // instead of n comparisons per item.  emit(u, item, rank) is called once per item, a thread's u-th.  Where a bin has more than
-// longest_run items (equal keys, or all near each other and one far off) nothing is emitted and the result is false: the
-// caller sorts them, in memory of its own or, behind a barrier, in that of bins and list.  bins: kRankBins words of LDS, 16-byte aligned; list: n items of LDS.  All threads call this; what
-// key() reads of LDS must be visible, and sh.red_a and sh.red_b free.
+// longest_run items (equal keys, or all near each other and one far off) nothing is emitted and the result is false: the caller sorts
+// them, in memory of its own or, behind a barrier, in that of bins and list.  bins: kRankBins words of LDS, 16-byte aligned; list: n
+// items of LDS.  All threads call this; what key() reads of LDS must be visible, and sh.red_a and sh.red_b free.
 // Bound: the chain of barriers and LDS round trips on one compute unit.  16 rows of 256000, in us per call of topk_select: k = 1024
 // 17.4 (2048 bins, the items' numbers listed, by a second pass of additions) -> 15.6 (this, 2048 bins) -> 15.1 (4096 bins: the keys
 // are densest at the threshold); k = 2048 27.1 -> 21.2 -> 18.8.
